@@ -1,0 +1,583 @@
+#include <cmath>
+#include <type_traits>
+
+#include "wgemm.h"
+
+namespace df {
+
+namespace {
+
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_b;
+
+#define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
+#define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+template <int VM>
+__device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
+  __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
+}
+__device__ __forceinline__ void block_sync() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+enum { EPI_PLAIN = 0, EPI_GEGLU = 1, EPI_QKV = 2, EPI_XA = 3 };
+
+// Geometry of a tile's epilogue: the accumulators go through LDS in passes of PI token fragment rows per wave.
+template <int WT, int WF, int TT, int TF, int KG, int OCC, bool LN>
+struct Epi {
+  static constexpr int BT = WT * TT, BF = WF * TF;
+  static constexpr int kStats = LN ? (KG * WF + 1) * BT * 32 * 2 * 4 : 0;
+  static constexpr int kVecs = (LN ? 2 : 1) * BF * 32 * 4;
+  static constexpr int kCap = 160 * 1024 / OCC - kStats - kVecs;
+  static constexpr int pass_bytes(int pi) { return KG * WT * pi * BF * 4096; }
+  static constexpr int pick() {
+    for (int pi = TT; pi > 1; --pi)
+      if (TT % pi == 0 && pass_bytes(pi) <= kCap) return pi;
+    return 1;
+  }
+  static constexpr int PI = pick();
+  static constexpr int kBytes = pass_bytes(PI) + kStats + kVecs;
+};
+
+template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
+__global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(WParams p) {
+  using E = Epi<WT, WF, TT, TF, KG, OCC, LN>;
+  constexpr int NW = WT * WF * KG;                     // waves
+  constexpr int BT = WT * TT, BF = WF * TF;            // token / feature fragment rows of the workgroup tile
+  constexpr int BKF = KS * KG;                         // k-fragments per stage
+  constexpr int STAGE = (BT + BF) * BKF * 1024;
+  constexpr int I = (BT + BF) * BKF;                   // 1 KB direct loads per stage
+  constexpr int NL = (I + NW - 1) / NW;                // per wave (the last wave repeats the last fragment)
+  static_assert(NL * (ST - 1) < 64, "vmcnt field is 6 bits");
+  static_assert((WF & (WF - 1)) == 0, "");
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+
+  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.group_m), "s"(p.residual), "s"(p.ldr));
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tok = lane & 31, g = lane >> 5;
+  const int kg = wave / (WT * WF), wq = wave % (WT * WF), wt = wq % WT, wf = wq / WT;
+  const int MT = (p.M + 31) >> 5, NF = p.N >> 5;
+  constexpr int JO = EPI == EPI_GEGLU ? TF / 2 : TF;   // output fragments per wave along the features
+  constexpr int BFO = WF * JO;
+  const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO, nwg = MG * NG;
+  int t = blockIdx.x;
+  {
+    const int xcd = t & 7, loc = t >> 3;
+    const int base = nwg >> 3, rem = nwg & 7;
+    t = xcd * base + (xcd < rem ? xcd : rem) + loc;
+  }
+  int mg, ng;
+  {
+    const int per = p.group_m * NG, pn = t / per, r = t - pn * per, m0 = pn * p.group_m;
+    const int gh = MG - m0 < p.group_m ? MG - m0 : p.group_m;
+    ng = r / gh;
+    mg = m0 + r - ng * gh;
+  }
+  const int KF = p.K >> 4, KT = KF / BKF;
+
+  // fragment row of the weights behind row r (0 .. BF-1) of the tile (geglu: of a wave's TF rows the first half are
+  // value rows, the second half their gates)
+  auto wrow = [&](int r) {
+    int nt;
+    if constexpr (EPI == EPI_GEGLU) {
+      const int w = r / TF, j = r - w * TF;
+      nt = ng * BFO + w * JO + (j < JO ? j : j - JO);
+      if (nt > NF - 1) nt = NF - 1;
+      return j < JO ? nt : NF + nt;
+    }
+    nt = ng * BF + r;
+    return nt < NF ? nt : NF - 1;
+  };
+  const int lo = lane * 16;
+  const char* src[NL];
+#pragma unroll
+  for (int q = 0; q < NL; ++q) {
+    int i = wave * NL + q;
+    if (i > I - 1) i = I - 1;
+    const int row = i / BKF, kk = i - row * BKF;
+    int mt = mg * BT + row;
+    if (mt > MT - 1) mt = MT - 1;                      // ragged last tile: re-read, never stored
+    src[q] = (row < BT ? (const char*)p.Xp + (size_t)mt * KF * 1024 : (const char*)p.Wp + (size_t)wrow(row - BT) * KF * 1024) +
+             kk * 1024;
+  }
+  auto issue = [&](int kt, int slot) {
+    const size_t ko = (size_t)kt * (BKF * 1024);
+#pragma unroll
+    for (int q = 0; q < NL; ++q) {
+      int i = wave * NL + q;
+      if (i > I - 1) i = I - 1;
+      __builtin_amdgcn_global_load_lds(DF_GPTR(src[q] + ko + lo), DF_LPTR(smem + slot * STAGE + i * 1024), 16, 0, 0);
+    }
+  };
+
+  // per-feature vectors of the tile (norm scale / shift, or bias): requested now, parked in LDS for the epilogue
+  constexpr int NV = BF * 32 / (64 * NW) > 0 ? BF * 32 / (64 * NW) : 1;
+  float vs[NV], vt[NV];
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int r = tid + q * 64 * NW;
+    vs[q] = vt[q] = 0.f;
+    if (r < BF * 32) {
+      const int n = wrow(r >> 5) * 32 + (r & 31);
+      if constexpr (LN) { vs[q] = p.ln_s[n]; vt[q] = p.ln_t[n]; }
+      else if (p.bias) vt[q] = p.bias[n];
+    }
+  }
+  f32x16 acc[TT][TF];
+  constexpr bool kResInit = EPI == EPI_PLAIN && !LN;
+  if (kResInit && p.residual && kg == 0) {
+    // the residual is the accumulators' start value: its latency runs beside the first stages'
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      const int m = (mg * BT + wt * TT + i) * 32 + tok;
+#pragma unroll
+      for (int j = 0; j < TF; ++j) {
+        const int nt = ng * BF + wf * TF + j;
+        f32x4 r[4];
+#pragma unroll
+        for (int f = 0; f < 4; ++f) r[f] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (m < p.M && nt < NF) {
+          const float* rp = p.residual + (long long)m * p.ldr + nt * 32 + 8 * g;
+#pragma unroll
+          for (int f = 0; f < 4; ++f) r[f] = *reinterpret_cast<const f32x4*>(rp + 16 * (f >> 1) + 4 * (f & 1));
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = r[e >> 2][e & 3];
+      }
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TF; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  }
+  float ln_sum[TT], ln_sq[TT];
+#pragma unroll
+  for (int i = 0; i < TT; ++i) { ln_sum[i] = 0.f; ln_sq[i] = 0.f; }
+
+  bf16x8 xa[2][TT], wa[2][TF];
+  auto rd = [&](int slot, int ks, auto bc) {
+    constexpr int b = decltype(bc)::value;
+    const char* s = smem + slot * STAGE + (kg * KS + ks) * 1024 + lo;
+#pragma unroll
+    for (int i = 0; i < TT; ++i) xa[b][i] = *reinterpret_cast<const bf16x8*>(s + (wt * TT + i) * (BKF * 1024));
+#pragma unroll
+    for (int j = 0; j < TF; ++j) wa[b][j] = *reinterpret_cast<const bf16x8*>(s + (BT + wf * TF + j) * (BKF * 1024));
+  };
+  auto mm = [&](int kidx, auto bc) {
+    constexpr int b = decltype(bc)::value;
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TF; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[b][j], xa[b][i], acc[i][j], 0, 0, 0);
+    if constexpr (LN) {
+      // row sums of the tokens; the waves that share a token row take alternate k-steps
+      if ((kidx & (WF - 1)) == wf) {
+        const bf16x2_b ones = __builtin_bit_cast(bf16x2_b, 0x3f803f80u);
+#pragma unroll
+        for (int i = 0; i < TT; ++i) {
+          const u32x4 raw = __builtin_bit_cast(u32x4, xa[b][i]);
+          const unsigned int wds[4] = {raw.x, raw.y, raw.z, raw.w};
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const bf16x2_b v2 = __builtin_bit_cast(bf16x2_b, wds[q]);
+            ln_sum[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, ones, ln_sum[i], false);
+            ln_sq[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, v2, ln_sq[i], false);
+          }
+        }
+      }
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+#define DF_SB __builtin_amdgcn_sched_barrier(0)
+#pragma unroll
+  for (int s = 0; s < ST; ++s)
+    if (s < KT) issue(s, s);
+  if (ST <= KT) wait_vm_lds<NL * (ST - 1)>();
+  else wait_vm_lds<0>();
+  block_sync();
+  rd(0, 0, I0{});
+  int slot = 0;
+  for (int kt = 0; kt < KT; ++kt) {
+    const int nslot = slot + 1 == ST ? 0 : slot + 1;
+    DF_SB; rd(slot, 1, I1{}); DF_SB; mm(kt * KS, I0{}); DF_SB;
+    if constexpr (KS == 4) {
+      rd(slot, 2, I0{}); DF_SB; mm(kt * KS + 1, I1{}); DF_SB;
+      rd(slot, 3, I1{}); DF_SB; mm(kt * KS + 2, I0{}); DF_SB;
+    }
+    if (kt + 1 < KT) {
+      if (kt + ST <= KT) wait_vm_lds<NL * (ST - 2)>();
+      else wait_vm_lds<0>();
+      block_sync();
+      rd(nslot, 0, I0{});
+      if (kt + ST < KT) issue(kt + ST, slot);
+    }
+    DF_SB; mm(kt * KS + KS - 1, I1{}); DF_SB;
+    slot = nslot;
+  }
+
+  // ---- epilogue: the operand ring is free ----
+  constexpr int PI = E::PI;
+  f32x4* red = reinterpret_cast<f32x4*>(smem);         // [KG][WT*PI rows][BF][2 f][2 halves][64 lanes]
+  float* s_part = reinterpret_cast<float*>(smem + E::pass_bytes(PI));   // [KG*WF][BT*32][2] partial (sum, sum of squares)
+  float* s_mr = s_part + (LN ? KG * WF * BT * 64 : 0);  // [BT*32][2] mean, rstd
+  float* s_t = s_part + E::kStats / 4;                 // [BF*32] shift / bias
+  float* s_s = s_t + BF * 32;                          // [BF*32] scale sums (folded LayerNorm)
+  block_sync();
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    const int r = tid + q * 64 * NW;
+    if (r < BF * 32) { s_t[r] = vt[q]; if constexpr (LN) s_s[r] = vs[q]; }
+  }
+  if constexpr (LN) {
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      const float sm = ln_sum[i] + __shfl_xor(ln_sum[i], 32, 64);
+      const float sq = ln_sq[i] + __shfl_xor(ln_sq[i], 32, 64);
+      if (g == 0) {
+        float* d = s_part + (((kg * WF + wf) * BT + wt * TT + i) * 32 + tok) * 2;
+        d[0] = sm; d[1] = sq;
+      }
+    }
+  }
+#pragma unroll 1
+  for (int pass = 0; pass < TT / PI; ++pass) {
+    if (pass > 0) __syncthreads();                     // the previous pass has been read
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      if (i / PI != pass) continue;                    // (uniform; accumulator indices stay compile-time)
+#pragma unroll
+      for (int j = 0; j < TF; ++j)
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          red[(((kg * WT * PI + wt * PI + i % PI) * BF + wf * TF + j) * 4 + h) * 64 + lane] =
+              f32x4{acc[i][j][4 * h], acc[i][j][4 * h + 1], acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]};
+    }
+    __syncthreads();
+    if constexpr (LN) {
+      if (pass == 0) {
+        for (int r = tid; r < BT * 32; r += 64 * NW) {
+          float sm = 0.f, sq = 0.f;
+#pragma unroll
+          for (int w = 0; w < KG * WF; ++w) { sm += s_part[(w * BT * 32 + r) * 2]; sq += s_part[(w * BT * 32 + r) * 2 + 1]; }
+          const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+          const float mean = sm * inv_k;
+          const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
+          s_mr[2 * r] = mean;
+          s_mr[2 * r + 1] = __builtin_amdgcn_rsqf(var + p.ln_eps);
+        }
+        __syncthreads();
+      }
+    }
+    // 8 consecutive features 16f + 8g .. of tile fragment (row r of the pass, weight row jf), token tk of the row
+    auto value8 = [&](int r, int trow, int jf, int f, int gg, int tk, float* v) {
+      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll
+      for (int k = 0; k < KG; ++k) {
+        const f32x4* q = red + (((k * WT * PI + r) * BF + jf) * 4 + 2 * f) * 64 + tk + 32 * gg;
+        a += q[0];
+        b += q[64];
+      }
+      const float* tv = s_t + jf * 32 + 16 * f + 8 * gg;
+      const f32x4 t0 = *reinterpret_cast<const f32x4*>(tv), t1 = *reinterpret_cast<const f32x4*>(tv + 4);
+      if constexpr (LN) {
+        const float* sv = s_s + jf * 32 + 16 * f + 8 * gg;
+        const f32x4 s0 = *reinterpret_cast<const f32x4*>(sv), s1 = *reinterpret_cast<const f32x4*>(sv + 4);
+        const float mean = s_mr[(trow * 32 + tk) * 2], rstd = s_mr[(trow * 32 + tk) * 2 + 1];
+        a = (a - s0 * mean) * rstd + t0;
+        b = (b - s1 * mean) * rstd + t1;
+      } else {
+        a += t0;
+        b += t1;
+      }
+      v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+    };
+
+    if constexpr (EPI == EPI_XA) {
+      // items (token row of the pass, head): the head's normalised, rounded query is the B operand of S^T = K Q^T
+      constexpr int HW = BF / 2;
+#pragma unroll 1
+      for (int it = wave; it < WT * PI * HW; it += NW) {
+        const int hd = it % HW, r = it / HW;
+        const int trow = (r / PI) * TT + pass * PI + r % PI, mt = mg * BT + trow, head = ng * HW + hd;
+        if (mt >= MT || head * 2 >= NF) continue;
+        const int bi = mt * 32 < p.xa_rows ? 0 : mt * 32 / p.xa_rows;
+        const bf16x8* kv = p.xkv + (size_t)bi * p.xa_bstride + (size_t)head * (12 * XA) * 64 + lane;
+        bf16x8 kf[XA][4];
+#pragma unroll
+        for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+          for (int ds = 0; ds < 4; ++ds) kf[kt][ds] = kv[(size_t)(kt * 4 + ds) * 64];
+        bf16x8 qf[4];
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds) {
+          float v[8];
+          value8(r, trow, hd * 2 + (ds >> 1), ds & 1, g, tok, v);
+          const u32x4 qv = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
+          qf[ds] = __builtin_bit_cast(bf16x8, qv);
+        }
+        f32x16 sa[XA];
+#pragma unroll
+        for (int kt = 0; kt < XA; ++kt) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) sa[kt][e] = 0.f;
+#pragma unroll
+          for (int ds = 0; ds < 4; ++ds) sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt][ds], qf[ds], sa[kt], 0, 0, 0);
+        }
+        bf16x8 vf[2 * XA][2];
+#pragma unroll
+        for (int ks = 0; ks < 2 * XA; ++ks)
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) vf[ks][dt] = kv[(size_t)(4 * XA + dt * 2 * XA + ks) * 64];
+        const float sc = p.xa_scale * 1.4426950408889634f;
+        float mx = -INFINITY;
+#pragma unroll
+        for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int key = kt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
+            if (key >= p.xa_keys) sa[kt][e] = -INFINITY;
+            mx = fmaxf(mx, sa[kt][e]);
+          }
+        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;
+        float l = 0.f;
+#pragma unroll
+        for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const float pv = __builtin_amdgcn_exp2f(fmaf(sa[kt][e], sc, -mx));
+            sa[kt][e] = pv;
+            l += pv;
+          }
+        l += __shfl_xor(l, 32, 64);
+        f32x16 oa[2];
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+          for (int e = 0; e < 16; ++e) oa[dt][e] = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < 2 * XA; ++ks) {
+          const int kt = ks >> 1, hf = ks & 1;
+          const u32x4 pk = {pack_bf2(sa[kt][8 * hf + 0], sa[kt][8 * hf + 1]), pack_bf2(sa[kt][8 * hf + 2], sa[kt][8 * hf + 3]),
+                            pack_bf2(sa[kt][8 * hf + 4], sa[kt][8 * hf + 5]), pack_bf2(sa[kt][8 * hf + 6], sa[kt][8 * hf + 7])};
+          const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) oa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][dt], pf, oa[dt], 0, 0, 0);
+        }
+        const float inv = __builtin_amdgcn_rcpf(l);
+        const int KFo = p.N >> 4;
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+          for (int f2 = 0; f2 < 2; ++f2) {
+            float o8[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) o8[q] = oa[dt][8 * f2 + q] * inv;
+            st_vec(p.out_packed + (((size_t)mt * KFo + head * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
+          }
+      }
+    } else {
+      // items (token row, output fragment, half of the row's tokens): lane -> token it*16 + lane%16, features 8*(lane/16) ..
+      const int tl = lane & 15, f = lane >> 5, gg = (lane >> 4) & 1;
+#pragma unroll 1
+      for (int it = wave; it < WT * PI * BFO * 2; it += NW) {
+        const int half = it & 1, jo = (it >> 1) % BFO, r = (it >> 1) / BFO;
+        const int trow = (r / PI) * TT + pass * PI + r % PI, mt = mg * BT + trow, nt = ng * BFO + jo;
+        if (mt >= MT || nt >= NF) continue;
+        const int jf = EPI == EPI_GEGLU ? (jo / JO) * TF + jo % JO : jo;
+        if constexpr (EPI == EPI_QKV) {
+          const int n0 = nt * 32, sg = (n0 >= p.seg_w ? 1 : 0) + (n0 >= 2 * p.seg_w ? 1 : 0);
+          if (p.seg_tr[sg]) {
+            // transposed segment (V^T), features 16*half .. +15 of the fragment, the row's 32 tokens
+            bf16_t* seg = p.seg_out[sg] + p.seg_row0[sg];
+            const long long sld = p.seg_ld[sg];
+            const int rin = p.seg_rows_in[sg], pin = p.seg_pin[sg], pout = p.seg_pout[sg];
+            auto one = [&](int fe, int tk2) {          // feature fe of the fragment, token tk2 of the row
+              float x = 0.f;
+#pragma unroll
+              for (int k = 0; k < KG; ++k)
+                x += reinterpret_cast<const float*>(red + (((k * WT * PI + r) * BF + jf) * 4 + 2 * half + ((fe >> 2) & 1)) * 64 + tk2 +
+                                                    32 * ((fe >> 3) & 1))[fe & 3];
+              if constexpr (LN) {
+                const float* mr = s_mr + (trow * 32 + tk2) * 2;
+                return mr[1] * (x - mr[0] * s_s[jf * 32 + fe]) + s_t[jf * 32 + fe];
+              }
+              return x + s_t[jf * 32 + fe];
+            };
+            auto at = [&](int fe, int m) {
+              const int bi = m < rin ? 0 : m / rin;
+              return seg + ((long long)bi * p.seg_w + (n0 + fe - sg * p.seg_w)) * sld + seg_pos(m - bi * rin, pin, pout);
+            };
+            if (p.seg_tr[sg] == 8) {                   // eight tokens stay together and 16-byte aligned (launcher)
+              const int fe = 16 * half + tl, t0 = 8 * (lane >> 4);
+              float v[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) v[q] = one(fe, t0 + q);
+              if (mt * 32 + t0 < p.M) st_vec(at(fe, mt * 32 + t0), v);
+            } else if (p.seg_tr[sg] == 2) {            // token pairs stay together: 64 contiguous bytes per feature and store
+              const int t0 = 2 * tl;
+#pragma unroll
+              for (int q = 0; q < 4; ++q) {
+                const int fe = 16 * half + 4 * q + (lane >> 4);
+                const unsigned int w = pack_bf2(one(fe, t0), one(fe, t0 + 1));
+                if (mt * 32 + t0 < p.M) *reinterpret_cast<unsigned int*>(at(fe, mt * 32 + t0)) = w;
+              }
+            } else {
+              const int t0 = lane & 31;
+#pragma unroll
+              for (int q = 0; q < 8; ++q) {
+                const int fe = 16 * half + 2 * q + (lane >> 5);
+                const bf16_t w = f2bf(one(fe, t0));
+                if (mt * 32 + t0 < p.M) *at(fe, mt * 32 + t0) = w;
+              }
+            }
+            continue;
+          }
+        }
+        const int tk = half * 16 + tl;
+        float v[8];
+        value8(r, trow, jf, f, gg, tk, v);
+        if constexpr (EPI == EPI_GEGLU) {
+          float gt[8];
+          value8(r, trow, jf + JO, f, gg, tk, gt);
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] *= gelu_erf(gt[q]);
+        }
+        const int m = mt * 32 + tk, n = nt * 32 + 16 * f + 8 * gg;
+        if constexpr (!kResInit) {
+          if (p.residual && m < p.M) {
+            float r8[8];
+            ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += r8[q];
+          }
+        }
+        wg_store_unit(p, mt, m, n, tk + 32 * gg, v);
+      }
+    }
+  }
+}
+
+template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
+int launch_one(const WParams& pin, hipStream_t st) {
+  constexpr int BT = WT * TT, BF = WF * TF, BFO = EPI == EPI_GEGLU ? BF / 2 : BF, NW = WT * WF * KG;
+  WParams p = pin;
+  const int MT = (p.M + 31) / 32, NF = p.N / 32;
+  const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO;
+  const long long nwg = (long long)MG * NG;
+  if ((p.K / 16) % (KS * KG)) return DF_ESHAPE;
+  const double conc = std::fmin((double)nwg / 8.0, 32.0 * OCC);
+  int gm = (int)(std::sqrt(conc * BF / BT) + 0.5);
+  if (gm < 1) gm = 1;
+  if (gm > MG) gm = MG;
+  const int np = (MG + gm - 1) / gm;
+  p.group_m = (MG + np - 1) / np;
+  constexpr int ring = ST * (BT + BF) * KS * KG * 1024;
+  constexpr int fin = Epi<WT, WF, TT, TF, KG, OCC, LN>::kBytes;
+  constexpr int smem = ring > fin ? ring : fin;
+  static_assert(smem <= 160 * 1024, "LDS of a compute unit");
+  auto k = bgemm_kernel<WT, WF, TT, TF, KG, KS, ST, OCC, EPI, LN, XA>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(k, dim3((unsigned)nwg), dim3(64 * NW), smem, st, p);
+  DF_LAUNCH_CHECK();
+  return DF_OK;
+}
+
+template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC>
+int launch_tile_cfg(const WParams& p, hipStream_t st) {
+  constexpr int BF = WF * TF;
+  if (p.xkv) {
+    if constexpr (BF % 2 == 0) {
+      switch ((p.xa_keys + 31) / 32) {
+        case 1: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 1>(p, st);
+        case 2: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 2>(p, st);
+        case 3: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 3>(p, st);
+        default: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 4>(p, st);
+      }
+    }
+    return DF_ESHAPE;
+  }
+  if (p.geglu) {
+    if constexpr (TF % 2 == 0) {
+      if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, true, 0>(p, st);
+      return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, false, 0>(p, st);
+    }
+    return DF_ESHAPE;
+  }
+  if (p.nseg) {
+    WParams q = p;
+    for (int i = 0; i < p.nseg; ++i) {
+      // transposed segments: how many consecutive tokens stay together and aligned in the destination
+      const long long al = p.seg_ld[i] | p.seg_row0[i] | p.seg_pin[i] | p.seg_pout[i] | p.seg_rows_in[i] | p.M;
+      if (p.seg_tr[i]) q.seg_tr[i] = (al % 8 == 0 && (uintptr_t)p.seg_out[i] % 16 == 0) ? 8 : (al % 2 == 0 && (uintptr_t)p.seg_out[i] % 4 == 0) ? 2 : 1;
+    }
+    if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
+    return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, false, 0>(q, st);
+  }
+  if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, true, 0>(p, st);
+  return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, false, 0>(p, st);
+}
+
+}  // namespace
+
+namespace {
+
+// Tile shapes.  `slab` and `epi` are the microseconds of a round of workgroups per 64 of K and for prologue + epilogue
+// (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, fitted to 27 token counts x 5 layers.
+struct TileCfg { int bt, bf, occ; double base, slab, epi[4]; };
+constexpr TileCfg kTiles[] = {
+    {10, 8, 1, 0.08, 1.677, {21.4, 28.8, 24.5, 39.2}},   // 320 x 256, eight waves of 160 x 64
+    {4, 4, 2, 2.42, 1.036, {5.5, 7.5, 6.5, 6.2}},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
+    {4, 4, 1, 0.74, 0.502, {6.0, 7.9, 7.0, 7.7}},        // 128 x 128, four ring stages
+    {2, 4, 2, 2.53, 0.588, {4.3, 6.9, 4.5, 6.2}},        // 64 x 128, two k-groups, two workgroups per unit
+    {2, 2, 2, 2.73, 0.425, {1e9, 3.4, 2.3, 5.1}},        // 64 x 64, two k-groups, two workgroups per unit
+    {2, 2, 1, 1.14, 0.218, {1e9, 3.8, 2.8, 5.5}},        // 64 x 64, two k-groups, four stages of 128
+};
+
+}  // namespace
+
+int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
+  switch (cfg) {
+    case 0: return launch_tile_cfg<2, 4, 5, 2, 1, 4, 2, 1>(p, st);
+    case 1: return launch_tile_cfg<4, 2, 1, 2, 1, 4, 2, 2>(p, st);
+    case 2: return launch_tile_cfg<4, 2, 1, 2, 1, 4, 4, 1>(p, st);
+    case 3: return launch_tile_cfg<2, 2, 1, 2, 2, 2, 3, 2>(p, st);
+    case 4: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 2, 2>(p, st);
+    case 5: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 4, 1>(p, st);
+    default: return DF_ESHAPE;
+  }
+}
+
+// The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.
+int pick_bgemm(const WParams& p, double other_us) {
+  const int mode = p.xkv ? 3 : p.geglu ? 0 : p.nseg ? 1 : 2;
+  const int MT = (p.M + 31) / 32, NF = p.N / 32;
+  const double kt = p.K / 64.0;
+  double best = other_us;
+  int pick = -1;
+  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+    const TileCfg& t = kTiles[c];
+    if ((p.K / 64) % (c == 5 || c == 4 ? 2 : 1)) continue;          // two k-groups of 64 per stage
+    const int bfo = p.geglu ? t.bf / 2 : t.bf;
+    const long long n = (long long)((MT + t.bt - 1) / t.bt) * ((NF + bfo - 1) / bfo);
+    // rounds of workgroups; two workgroups of a unit share it, so their rounds are continuous beyond the first few, and a
+    // workgroup with the unit to itself is faster
+    double r = (double)((n + 255) / 256);
+    if (t.occ == 2) r = n <= 256 ? 0.62 : n > 768 ? n / 512.0 : (double)((n + 511) / 512);
+    const double us = t.base + r * (kt * t.slab + t.epi[mode]);
+    if (us < best) { best = us; pick = c; }
+  }
+  return pick;
+}
+
+}  // namespace df

@@ -174,24 +174,15 @@ struct StaleEntry {
   size_t off, bytes;
 };
 
-// A linear weight the plan keeps in the tiled layout of the pipelined GEMM, optionally with the preceding
+// A linear weight the plan keeps in the fragment layout of wgemm.hip / bgemm.hip, optionally with the preceding
 // LayerNorm folded in (scale multiplied into the weight, shift and bias collected in `t`, column sums in `s`).
 struct PackSpec {
   std::string name;   // parameter name without ".w"
   int N, K;
   std::string norm;   // name of the folded norm ("" = none)
   bool has_bias;
-  size_t w_off, s_off, t_off;   // byte offsets inside the packed region (s/t only with a folded norm)
-  size_t f_off;                 // the same weight in the fragment layout of the wave-level GEMM
+  size_t f_off, s_off, t_off;   // byte offsets inside the packed region (s/t only with a folded norm)
 };
-
-// Token counts up to this use the fragment-packed transformer (wave-level GEMMs); larger ones (the synchronous first
-// step on the whole image) the workgroup-tiled kernels, whose operand traffic per flop is lower.
-constexpr int kFragMaxRows = 2048;
-inline bool frag_path() {
-  static const bool off = tune_env("DF_NO_FRAG") != nullptr;   // tuning aid
-  return !off;
-}
 
 inline size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -264,7 +255,6 @@ struct Prof {
 };
 
 struct PackedW {
-  const bf16_t* w = nullptr;
   const bf16_t* f = nullptr;    // fragment layout (wgemm.hip)
   const float* s = nullptr;
   const float* t = nullptr;
@@ -400,27 +390,6 @@ struct Exec {
     const void* W = weight(wn + ".w");
     const float* bp = bias ? (const float*)weight(wn + ".b") : nullptr;
     gemm_w(A, lda, W, bp, residual, ldr, out, ldo, M, Nn, K, out_dtype, extra);
-  }
-  // GEMM on a plan-packed weight; `ln` applies the folded LayerNorm of that weight (A then holds raw rows)
-  void gemm_packed(const void* A, long long lda, const std::string& wn, bool bias, bool ln, const float* residual,
-                   long long ldr, void* out, long long ldo, int M, int Nn, int K, int out_dtype, void* out2,
-                   const GemmArgs* extra = nullptr) {
-    GemmArgs g = {};
-    if (extra) g = *extra;
-    const float* bp = nullptr;
-    const void* W = nullptr;
-    if (!dry) {
-      auto it = packed->find(wn);
-      if (it == packed->end()) { err = DF_EINVAL; return; }
-      W = it->second.w;
-      g.packed_w = 1;
-      if (ln) { g.ln_s = it->second.s; g.ln_t = it->second.t; g.ln_eps = 1e-5f; }
-      else if (bias) bp = (const float*)weight(wn + ".b");
-      static const bool no_pack = tune_env("DF_NO_PACK") != nullptr;   // tuning aid: canonical layout where no norm is folded
-      if (no_pack && !ln) { W = weight(wn + ".w"); g.packed_w = 0; }
-    }
-    g.out2 = out2; g.ldo2 = Nn;
-    gemm_w(A, lda, W, bp, residual, ldr, out, ldo, M, Nn, K, out_dtype, &g);
   }
   void gemm_w(const void* A, long long lda, const void* W, const float* bp, const float* residual, long long ldr,
               void* out, long long ldo, int M, int Nn, int K, int out_dtype, const GemmArgs* extra = nullptr) {
@@ -612,7 +581,7 @@ struct Exec {
           [&] { return launch_wgemm(g, st); });
   }
 
-  // Transformer on fragment-packed activations (patch-sized token counts): every linear layer reads its operands in
+  // Transformer on fragment-packed activations: every linear layer reads its operands in
   // MFMA order straight into registers and writes the next layer's operand in that order; LayerNorms are folded into
   // the consuming layers; attention reads row-major Q/K/V and writes its output packed.
   void transformer_frag(const BlockDesc& b, const float* x, float* out, int R, int W) {
@@ -736,104 +705,17 @@ struct Exec {
     wg(hp, b.name + ".pout", true, false, x, out, nullptr, nullptr, 0, M, C, C);
   }
 
-  // Transformer with every LayerNorm folded into the GEMM that consumes it: the residual GEMMs also emit a bf16 copy
-  // of the hidden state, which is the A operand of the next projection; no LayerNorm, cast or GEGLU kernel is launched.
-  void transformer_folded(const BlockDesc& b, const float* x, float* out, bf16_t* nb, float* h, bf16_t* qkv, bf16_t* ao,
-                          bf16_t* fg, int R, int W) {
-    const int C = b.cin;
-    const int Lq = R * W, L = (c.H >> b.level) * (c.W >> b.level), heads = C / c.head_dim;
-    const int M = B() * Lq, TL = c.text_len;
-    const float scale = 1.0f / sqrtf((float)c.head_dim);
-    bf16_t* hb = (bf16_t*)alloc((size_t)M * C * 2);      // bf16 copy of the hidden state
-    const long long Lpad = (long long)((L + 63) / 64) * 64;   // key pitch of the V^T buffers: whole 64-key tiles
-    bf16_t* ks_tmp = nullptr; bf16_t* vs_tmp = nullptr;
-    if (!(full() || refresh)) {
-      ks_tmp = (bf16_t*)alloc((size_t)B() * L * C * 2);
-      vs_tmp = (bf16_t*)alloc((size_t)B() * C * Lpad * 2);
-    }
-    gemm_packed(nb, C, b.name + ".pin", true, false, nullptr, 0, h, C, M, C, C, DF_F32, hb);
-    for (int d = 0; d < b.depth; ++d) {
-      const std::string p = b.name + ".b" + std::to_string(d);
-      bf16_t* ks = (bf16_t*)stale_buf(p + ".attn1.k", (size_t)B() * L * C * 2);
-      bf16_t* vs = (bf16_t*)stale_buf(p + ".attn1.v", (size_t)B() * C * Lpad * 2);   // V^T: [B, C, Lpad]
-      // where the patch's tokens start in the key / value buffers: a block of Lq rows, or - vertical strips - W
-      // tokens of every grid row starting at the strip's first column
-      const bool strip = cols() && !full();
-      const size_t row0 = full() ? 0 : (strip ? (size_t)patch * W : (size_t)patch * Lq);
-      const int pin = strip ? W : 0, pout = strip ? (c.W >> b.level) : 0;
-      if (!(full() || refresh)) {
-        if (live()) {
-          timed(PC_REFRESH, 0.0, 4.0 * B() * L * C, [&] { return launch_copy_rows(ks_tmp, ks, 1, (long long)B() * L * C * 2, 0, 0, st); });
-          timed(PC_REFRESH, 0.0, 4.0 * B() * C * Lpad, [&] { return launch_copy_rows(vs_tmp, vs, 1, (long long)B() * C * Lpad * 2, 0, 0, st); });
-        }
-        ks = ks_tmp; vs = vs_tmp;
-      }
-      {
-        GemmArgs ex = {};
-        ex.nseg = 3; ex.seg_w = C;
-        ex.seg_out[0] = qkv; ex.seg_ld[0] = C; ex.seg_rows_in[0] = 0x7fffffff; ex.seg_rows_out[0] = 0; ex.seg_row0[0] = 0;
-        ex.seg_out[1] = ks; ex.seg_ld[1] = C; ex.seg_rows_in[1] = Lq; ex.seg_rows_out[1] = L; ex.seg_row0[1] = (long long)row0;
-        ex.seg_out[2] = vs; ex.seg_ld[2] = Lpad; ex.seg_rows_in[2] = Lq; ex.seg_rows_out[2] = 0; ex.seg_row0[2] = (long long)row0;
-        ex.seg_tr[2] = 1;
-        ex.seg_pin[1] = ex.seg_pin[2] = pin; ex.seg_pout[1] = ex.seg_pout[2] = pout;
-        gemm_packed(hb, C, p + ".attn1.qkv", false, true, nullptr, 0, qkv, C, M, 3 * C, C, DF_BF16, nullptr, &ex);
-      }
-      {
-        const size_t need = attention_scratch_bytes(B(), Lq, L, heads, c.head_dim);
-        if (need > scratch_need) scratch_need = need;
-      }
-      if (live()) {
-        AttnArgs a = {};
-        a.k_stale = ks; a.v_stale = vs; a.out = ao; a.q = qkv;
-        a.k_fresh = ks; a.v_fresh = vs; a.own_lo = 0; a.own_n = 0;
-        a.v_transposed = 1; a.vt_ld = Lpad;
-        a.B = B(); a.Lq = Lq; a.L = L; a.heads = heads; a.d = c.head_dim;
-        a.ldq = C; a.ldkf = a.ldvf = C; a.ldks = C; a.ldvs = C; a.ldo = C;
-        a.bsq = (long long)Lq * C; a.bskf = a.bsvf = (long long)L * C;
-        a.bsks = (long long)L * C; a.bsvs = (long long)C * Lpad; a.bso = (long long)Lq * C;
-        a.scale = scale; a.dtype = DF_BF16; a.scr = scr;
-        label = "self_attn " + dims({M, L, C});
-        timed(PC_SELF_ATTN, 4.0 * M * L * C, 2.0 * (2.0 * M * C + 2.0 * B() * L * C),
-              [&] { return launch_attention(a, st); });
-      }
-      gemm_packed(ao, C, p + ".attn1.o", true, false, h, C, h, C, M, C, C, DF_F32, hb);
-      // cross-attention to the text tokens
-      gemm_packed(hb, C, p + ".attn2.q", false, true, nullptr, 0, qkv, C, M, C, C, DF_BF16, nullptr);
-      const long long kvld = (long long)kv_count[b.level] * 2 * C;
-      const bf16_t* kv2 = kv2_all[b.level] + (size_t)kv_cursor[b.level] * 2 * C;
-      kv_cursor[b.level] += 1;
-      {
-        const size_t need = attention_scratch_bytes(B(), Lq, TL, heads, c.head_dim);
-        if (need > scratch_need) scratch_need = need;
-      }
-      if (live()) {
-        AttnArgs a = {};
-        a.q = qkv; a.k_fresh = kv2; a.v_fresh = kv2 + C; a.out = ao;
-        a.B = B(); a.Lq = Lq; a.L = TL; a.heads = heads; a.d = c.head_dim; a.own_lo = 0; a.own_n = TL;
-        a.ldq = C; a.ldkf = a.ldvf = kvld; a.ldks = a.ldvs = kvld; a.ldo = C;
-        a.bsq = (long long)Lq * C; a.bskf = a.bsvf = (long long)TL * kvld; a.bso = (long long)Lq * C;
-        a.scale = scale; a.dtype = DF_BF16; a.scr = scr;
-        timed(PC_CROSS_ATTN, 4.0 * M * TL * C, 2.0 * (2.0 * M * C + 2.0 * B() * TL * C),
-              [&] { return launch_attention(a, st); });
-      }
-      gemm_packed(ao, C, p + ".attn2.o", true, false, h, C, h, C, M, C, C, DF_F32, hb);
-      // GEGLU feed-forward
-      {
-        GemmArgs ex = {};
-        ex.geglu = 1;
-        gemm_packed(hb, C, p + ".ff1", false, true, nullptr, 0, fg, 4 * C, M, 8 * C, C, DF_BF16, nullptr, &ex);
-      }
-      gemm_packed(fg, 4 * C, p + ".ff2", true, false, h, C, h, C, M, C, 4 * C, DF_F32, hb);
-    }
-    gemm_packed(hb, C, b.name + ".pout", true, false, x, C, out, C, M, C, C, DF_F32, nullptr);
-  }
-
   void transformer(const BlockDesc& b, const float* x, const bf16_t* text, float* out) {
     const int R = rows(b.level), W = width(b.level), C = b.cin;
     const int Lq = R * W, L = (c.H >> b.level) * (c.W >> b.level), heads = C / c.head_dim;
     const int M = B() * Lq;
     const int TL = c.text_len;
     const size_t mark = top;
+    if (fold_ok(C)) {
+      transformer_frag(b, x, out, R, W);
+      top = mark;
+      return;
+    }
     bf16_t* nb = (bf16_t*)alloc((size_t)M * C * 2);          // normalised input of the next GEMM
     float* h = (float*)alloc((size_t)M * C * 4);             // hidden state (residual stream)
     bf16_t* qkv = (bf16_t*)alloc((size_t)M * 3 * C * 2);
@@ -841,19 +723,8 @@ struct Exec {
     bf16_t* ff = (bf16_t*)alloc((size_t)M * 8 * C * 2);
     bf16_t* fg = (bf16_t*)alloc((size_t)M * 4 * C * 2);
     const float scale = 1.0f / sqrtf((float)c.head_dim);
-    if (fold_ok(C) && M <= kFragMaxRows && frag_path()) {
-      top = mark;
-      transformer_frag(b, x, out, R, W);
-      top = mark;
-      return;
-    }
-    if (cols() && b.depth > 0 && !fold_ok(C)) { err = DF_ESHAPE; return; }   // (cfg_ok rejects such plans up front)
+    if (cols() && b.depth > 0) { err = DF_ESHAPE; return; }   // (cfg_ok rejects such plans up front)
     groupnorm(b.name + ".gn", x, DF_F32, R, W, C, 1e-6f, 0, nb);
-    if (fold_ok(C)) {
-      transformer_folded(b, x, out, nb, h, qkv, ao, fg, R, W);
-      top = mark;
-      return;
-    }
     gemm(nb, C, b.name + ".pin", true, nullptr, 0, h, C, M, C, C, DF_F32);
     for (int d = 0; d < b.depth; ++d) {
       const std::string p = b.name + ".b" + std::to_string(d);
@@ -1083,8 +954,7 @@ std::vector<PackSpec> build_pack_specs(const df_unet_cfg& c, const std::vector<B
   std::vector<PackSpec> v;
   size_t off = base;
   auto add = [&](const std::string& name, int N, int K, const std::string& norm, bool has_bias) {
-    PackSpec sp{name, N, K, norm, has_bias, 0, 0, 0, 0};
-    sp.w_off = off; off += align256((size_t)N * K * sizeof(bf16_t));
+    PackSpec sp{name, N, K, norm, has_bias, 0, 0, 0};
     sp.f_off = off; off += align256((size_t)N * K * sizeof(bf16_t));
     if (!norm.empty()) {
       sp.s_off = off; off += align256((size_t)N * sizeof(float));
@@ -1245,11 +1115,8 @@ int df_unet_create(df_unet** out, const df_unet_cfg* cfg, const void* const* wei
       base = u->kv_off[lv] + align256((size_t)u->kv_count[lv] * 2 * cfg->levels[lv] * cfg->text_dim * sizeof(bf16_t));
     for (const PackSpec& sp : build_pack_specs(u->cfg, u->blocks, base, &end)) {
       PackedW pw;
-      bf16_t* dst = (bf16_t*)(u->ws + sp.w_off);
       const bf16_t* src = (const bf16_t*)u->w[sp.name + ".w"];
       const float* gamma = sp.norm.empty() ? nullptr : (const float*)u->w[sp.norm + ".g"];
-      if (launch_pack_weight(src, gamma, dst, sp.N, sp.K, 0) != DF_OK) { delete u; return DF_EHIP; }
-      pw.w = dst;
       {
         bf16_t* fdst = (bf16_t*)(u->ws + sp.f_off);
         if (launch_pack_wfrag(src, gamma, fdst, sp.N, sp.K, 0) != DF_OK) { delete u; return DF_EHIP; }

@@ -1,0 +1,80 @@
+// Shared by the two kernels for linear layers on fragment-packed operands (wgemm.hip: wave-level, few tokens;
+// bgemm.hip: workgroup tiles through LDS, many tokens): the kernel arguments and the store of one output unit.
+#pragma once
+#include "kernels.h"
+
+namespace df {
+
+struct WParams {
+  const bf16x8* Xp;
+  const bf16x8* Wp;
+  int M, N, K;          // N: rows of W that produce outputs (geglu: F value rows; the gate rows follow at row F)
+  const float* bias;
+  const float* ln_s;
+  const float* ln_t;
+  float ln_eps;
+  const float* residual;
+  long long ldr;
+  float* out_f32;
+  long long ldo;
+  bf16_t* out_packed;
+  bf16_t* out_rows;
+  long long ld_rows;
+  int geglu;
+  int nseg, seg_w;
+  bf16_t* seg_out[3];
+  long long seg_ld[3], seg_rows_out[3], seg_row0[3];
+  int seg_rows_in[3];
+  int seg_tr[3];
+  int seg_pin[3], seg_pout[3];
+  // fused cross-attention (XA > 0): per (batch item, head) 8*XA key fragments then 4*XA value fragments
+  const bf16x8* xkv;
+  int xa_keys;          // valid text tokens
+  long long xa_bstride; // fragments between batch items
+  int xa_rows;          // token rows per batch item
+  float xa_scale;
+  int group_m;          // bgemm: token tiles of a panel in the tile order (see there)
+};
+
+// One output unit: 8 consecutive features n .. n+7 of token m = mt*32 + lane%32, written in every requested form.
+__device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, int n, int lane, const float* v) {
+  const bool row_ok = m < p.M;
+  if (p.out_f32 && row_ok) {
+    st_vec(p.out_f32 + (long long)m * p.ldo + n, v);
+    st_vec(p.out_f32 + (long long)m * p.ldo + n + 4, v + 4);
+  }
+  if (p.out_packed) {
+    // fragment (mt, n/16) of the [M, N] result as the next layer's activation operand; padded token rows are
+    // written too (they only ever feed padded rows)
+    const int KFo = p.N >> 4;
+    st_vec(p.out_packed + (((size_t)mt * KFo + (n >> 4)) * 64 + lane) * 8, v);
+  }
+  if (row_ok) {
+    if (p.nseg > 0) {
+      // 8 features never straddle a segment (seg_w % 32 == 0); at most three segments, usually one batch item:
+      // comparisons instead of integer divisions
+      const int sg = (n >= p.seg_w ? 1 : 0) + (n >= 2 * p.seg_w ? 1 : 0);
+      const int bi = m < p.seg_rows_in[sg] ? 0 : m / p.seg_rows_in[sg];
+      if (p.seg_tr[sg]) {
+        // feature-major output: the 32 tokens of a half wave are consecutive in memory for each feature
+        bf16_t* o = p.seg_out[sg] + ((long long)bi * p.seg_w + (n - sg * p.seg_w)) * p.seg_ld[sg] + p.seg_row0[sg] +
+                    seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o[q * p.seg_ld[sg]] = f2bf(v[q]);
+      } else {
+        const long long orow = (long long)bi * p.seg_rows_out[sg] + p.seg_row0[sg] +
+                               seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
+        st_vec(p.seg_out[sg] + orow * p.seg_ld[sg] + (n - sg * p.seg_w), v);
+      }
+    } else if (p.out_rows) {
+      st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);
+    }
+  }
+}
+
+// Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.
+int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
+// Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1.
+int pick_bgemm(const WParams& p, double other_us);
+
+}  // namespace df

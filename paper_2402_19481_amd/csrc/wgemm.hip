@@ -15,44 +15,13 @@
 // makes those 16 features two runs of 8 consecutive ones: exactly the 16 bytes that the same lane of the *next*
 // layer's activation fragment holds.  The epilogue therefore writes the next layer's packed operand with one
 // 16-byte store per lane and no data exchange.
-#include "kernels.h"
+#include "wgemm.h"
 
 namespace df {
 
 namespace {
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_w;
-
-struct WParams {
-  const bf16x8* Xp;
-  const bf16x8* Wp;
-  int M, N, K;          // N: rows of W that produce outputs (geglu: F value rows; the gate rows follow at row F)
-  const float* bias;
-  const float* ln_s;
-  const float* ln_t;
-  float ln_eps;
-  const float* residual;
-  long long ldr;
-  float* out_f32;
-  long long ldo;
-  bf16_t* out_packed;
-  bf16_t* out_rows;
-  long long ld_rows;
-  int geglu;
-  int nseg, seg_w;
-  bf16_t* seg_out[3];
-  long long seg_ld[3], seg_rows_out[3], seg_row0[3];
-  int seg_rows_in[3];
-  int seg_tr[3];
-  int seg_pin[3], seg_pout[3];
-  // fused cross-attention (XA > 0): per (batch item, head) 8*XA key fragments then 4*XA value fragments
-  const bf16x8* xkv;
-  int xa_keys;          // valid text tokens
-  long long xa_bstride; // fragments between batch items
-  int xa_rows;          // token rows per batch item
-  float xa_scale;
-};
-
 
 // XA > 0 (TM = 1, TN = 2, KSPLIT = 4, N = one head per workgroup): the 64 output features are the query of one
 // attention head; cross-attention against XA 32-key tiles of packed text keys / values runs in the epilogue and the
@@ -364,37 +333,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += e.r[q];
     }
-    if (p.out_f32 && row_ok) {
-      st_vec(p.out_f32 + (long long)m * p.ldo + n, v);
-      st_vec(p.out_f32 + (long long)m * p.ldo + n + 4, v + 4);
-    }
-    if (p.out_packed) {
-      // fragment (mt, n/16) of the [M, N] result as the next layer's activation operand; padded token rows are
-      // written too (they only ever feed padded rows)
-      const int KFo = p.N >> 4;
-      st_vec(p.out_packed + (((size_t)mt * KFo + (n >> 4)) * 64 + lane) * 8, v);
-    }
-    if (row_ok) {
-      if (p.nseg > 0) {
-        // 8 features never straddle a segment (seg_w % 32 == 0); at most three segments, usually one batch item:
-        // comparisons instead of integer divisions
-        const int sg = (n >= p.seg_w ? 1 : 0) + (n >= 2 * p.seg_w ? 1 : 0);
-        const int bi = m < p.seg_rows_in[sg] ? 0 : m / p.seg_rows_in[sg];
-        if (p.seg_tr[sg]) {
-          // feature-major output: the 32 tokens of a half wave are consecutive in memory for each feature
-          bf16_t* o = p.seg_out[sg] + ((long long)bi * p.seg_w + (n - sg * p.seg_w)) * p.seg_ld[sg] + p.seg_row0[sg] +
-                      seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
-#pragma unroll
-          for (int q = 0; q < 8; ++q) o[q * p.seg_ld[sg]] = f2bf(v[q]);
-        } else {
-          const long long orow = (long long)bi * p.seg_rows_out[sg] + p.seg_row0[sg] +
-                                 seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
-          st_vec(p.seg_out[sg] + orow * p.seg_ld[sg] + (n - sg * p.seg_w), v);
-        }
-      } else if (p.out_rows) {
-        st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);
-      }
-    }
+    wg_store_unit(p, mt, m, n, lane, v);
   }
   DF_WTRACE(9 + 2 * (i0 / RP < 4 ? i0 / RP : 3), __builtin_readcyclecounter());
   }
@@ -560,11 +499,6 @@ __global__ void pack_text_kv_kernel(const bf16_t* __restrict__ kv, long long ld,
   out[idx] = v;
 }
 
-int tune_cfg() {
-  static const int v = [] { const char* e = tune_env("DF_WGEMM_CFG"); return e ? atoi(e) : 0; }();
-  return v;
-}
-
 template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0>
 int launch_one(const WParams& p, hipStream_t st) {
   const int MT = (p.M + 31) / 32, MG = (MT + TM - 1) / TM;
@@ -686,6 +620,35 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
       return DF_ESHAPE;
     p.xkv = (const bf16x8*)a.xa_kv; p.xa_keys = a.xa_keys; p.xa_rows = a.xa_rows; p.xa_scale = a.xa_scale;
     p.xa_bstride = a.xa_bstride / 8;
+  }
+  const int nfrag = Nout / 32;
+  // Measured on the patch step (kernel trace, cold weights).  A wave tile of 32 tokens x 64 features keeps the most waves
+  // in flight and wins while the problem has few tiles; from ~320 workgroups on, the 64 x 64 tile's lower operand
+  // traffic per flop wins; and where a still larger tile (64 x 96 without GEGLU) covers the output with at most one
+  // workgroup per unit, its single round of workgroups wins again, provided the reduction is long enough to amortise
+  // the row-by-row epilogue.
+  const int MT = (a.M + 31) / 32;
+  const long long wg12 = (long long)MT * (p.geglu ? nfrag : nfrag / 2);
+  const bool long_k = a.K / 16 / 4 >= 16;
+  const bool wide = wg12 >= 320 && long_k && !p.geglu && nfrag % 3 == 0 && (long long)((MT + 1) / 2) * (nfrag / 3) <= 256 && !a.xa_kv;
+  {
+    // Predicted time of the wave-level kernel (microseconds: launch + rounds of workgroups x (K loop + epilogue), fitted
+    // like the tile kernel's table): it keeps the problems whose token count does not fill the tiles of bgemm.hip.
+    const double kt = a.K / 64.0;
+    const bool two = wg12 >= 320 && !a.xa_kv;
+    const double n = wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)wg12;
+    const double r = n / 256.0 > 0.6 ? n / 256.0 : 0.6;
+    const double us = wide ? 11.0 : two ? 3.1 + r * (0.257 * kt + (p.geglu ? 0.6 : p.nseg ? 1.4 : 2.4))
+                                        : 4.6 + r * (0.198 * kt + (a.xa_kv || p.geglu ? 0.1 : p.nseg ? -1.1 : -1.6));
+    const char* e = tune_env("DF_BGEMM");
+    const int c = e ? atoi(e) : pick_bgemm(p, us);
+    if (c >= 0) {
+      const int rc = launch_bgemm(p, c, st);
+      if (rc != DF_ESHAPE || e) return rc;
+    }
+  }
+  if (a.xa_kv) {
+    const int XA = (a.xa_keys + 31) / 32;
     const int KFw = a.K / 16 / 4;
 #define DF_XA(PFV)                                                             \
   switch (XA) {                                                                \
@@ -700,31 +663,8 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     DF_XA(1)
 #undef DF_XA
   }
-  switch (tune_cfg()) {                                  // DF_WGEMM_CFG: tuning aid
-    case 1: return launch_cfg<1, 2, 4, 5>(p, st);
-    case 2: return launch_cfg<2, 2, 4, 5>(p, st);
-    case 3: return launch_cfg<1, 2, 4, 10>(p, st);
-    case 5: return launch_cfg<1, 2, 8, 5>(p, st);
-    case 6: return launch_cfg<2, 3, 4, 5>(p, st);
-    case 9: return launch_cfg<4, 4, 4, 2>(p, st);
-    default: break;
-  }
-  const int nfrag = Nout / 32;
   if (!p.geglu && nfrag % 2) return launch_cfg<1, 1, 4, 5>(p, st);
-  // Measured on the patch step (kernel trace, cold weights).  A compute unit feeds its waves about one 1 KB operand
-  // fragment per 32 cycles, whatever the L2 hit rate, so a kernel's K loop lasts (fragment loads of the busiest unit)
-  // x 32 cycles, and every workgroup adds a fixed ramp and epilogue.  A wave tile of 32 tokens x 64 features keeps
-  // the most waves in flight and wins while the problem has few tiles; from ~320 workgroups on, the 64 x 64 tile's
-  // lower operand traffic per flop wins; and where a still larger tile (128 x 128 for the GEGLU projection, 64 x 96
-  // otherwise) covers the output with at most one workgroup per unit, its traffic per flop and its single round of
-  // workgroups win again, provided the reduction is long enough to amortise the row-by-row epilogue.
-  const int MT = (a.M + 31) / 32;
-  const long long wg12 = (long long)MT * (p.geglu ? nfrag : nfrag / 2);
-  const bool long_k = a.K / 16 / 4 >= 16;
-  if (wg12 >= 320 && long_k) {
-    if (p.geglu && nfrag % 2 == 0 && (long long)((MT + 3) / 4) * (nfrag / 2) <= 256) return launch_cfg<4, 4, 4, 2>(p, st);
-    if (!p.geglu && nfrag % 3 == 0 && (long long)((MT + 1) / 2) * (nfrag / 3) <= 256) return launch_cfg<2, 3, 4, 5>(p, st);
-  }
+  if (wide) return launch_cfg<2, 3, 4, 5>(p, st);
   if (wg12 >= 320) return launch_cfg<2, 2, 4, 5>(p, st);
   return launch_cfg<1, 2, 4, 5>(p, st);
 }
