@@ -39,6 +39,7 @@ struct AttnParams {
   long long ldq, ldkf, ldvf, ldks, ldvs, ldo;
   long long bsq, bskf, bsvf, bsks, bsvs, bso;
   float scale;
+  float sc_log2;   // factor of the scores in log2 units (transposed-V variants): scale * log2(e), or 1 for scaled queries
   int nsplit, keys_per_split;
   int out_packed;
   // transposed-V variant: vs is V^T [B][heads*64][vt_ld] (keys contiguous), every key comes from ks / vs
@@ -360,22 +361,30 @@ __device__ long long g_attn_trace[512 * 32];
 #define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
-// NGR = 2: eight waves in two groups of four.  Both groups hold the same 128 queries; of every 128 consecutive keys
-// group 0 takes the first 64 and group 1 the last 64, and the two running (max, sum, O) states are merged through LDS
-// at the end.  A SIMD then always has two waves in different phases of their tile, so one wave's softmax (vector ALU)
-// runs under the other's matrix instructions and LDS waits, which a single wave per SIMD leaves exposed.
-template <int NST, int NGR>
-__global__ __launch_bounds__(256 * NGR, NGR == 1 ? 2 : 1) void attn_vt_d64(AttnParams p) {
-  constexpr int D = 64, TK = 64;
-  constexpr int KB = TK * D * 2, STAGE = 2 * KB * NGR;     // bytes: K tiles of all groups, then their V^T tiles
+// Self-attention of the UNet step for many queries: the matrix pipe and the vector ALU of a SIMD work at the same time only
+// where one wave's instruction stream mixes the two (measured: 16 MFMAs then 64 exponentials 1030-1600 cycles with any
+// number of waves, interleaved one by one 660), so the loop is software-pipelined inside the wave.  Iteration t issues the
+// matrix instructions of S_{t+1} = K_{t+1} Q^T and of O += V_{t-1} P_{t-1} between the exponentials of tile t; nothing
+// in an iteration waits for anything the same iteration started.
+//   - PRE: the queries already carry scale * log2(e) (the projection applies it to its float accumulators before rounding).
+//     S then starts from -m instead of zero (the first MFMA of a tile reads the register tuple that holds it), so the
+//     exponential's argument is the accumulator itself; otherwise one fma per score.
+//   - The running maximum m only moves when a score exceeds it by more than 8 (a factor of 256: P stays far inside
+//     float and bf16 range, relative precision is that of any other scaling).  That happens in the first tile and hardly
+//     again; the lanes' maxima are compared, not exchanged, and the exchange and rescaling sit in a branch beside the loop.
+//   - Row sums come from the packed probabilities (v_dot2 with ones): half the instructions of adding floats.
+// K and V^T tiles go global -> LDS through two rings of three 8 KB tiles; K_{t+3} and V_{t+1} are requested in iteration t.
+// Bound by the exponentials (64 of 8.3 cycles per wave and tile against 16 MFMAs of 32) and what the power limit leaves of
+// the clock.  Measured against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10 heads
+// 1435 -> 1105 us (961 TFLOP/s), 4096 x 4096 x 10 88 -> 66, 1024 x 4096 x 20 51.6 -> 38, 1200 x 9600 x 10 66 -> 46.
+// Three workgroups per unit instead of two (168 registers) gain 2 % on the largest of these and lose 3-5 % below.
+template <bool PRE>
+__global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
+  constexpr int D = 64, TK = 64, KB = TK * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
-  DF_ATRACE(0, wall_clock64());
-  DF_ATRACE(1, __builtin_readcyclecounter());
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: what depends on it (key range, masks of the
-                                                               // ragged tile, LDS addresses) stays off the vector ALU
-  const int grp = wave >> 2, wq = wave & 3;
-  const int xor32 = (lane ^ 32) << 2;                          // byte index of the partner lane for ds_bpermute
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int xor32 = (lane ^ 32) << 2;
   const int g = lane >> 5, c = lane & 31;
   const int csig = (c & 0x13) | ((c & 4) << 1) | ((c & 8) >> 1);
   int t = blockIdx.x;
@@ -390,15 +399,32 @@ __global__ __launch_bounds__(256 * NGR, NGR == 1 ? 2 : 1) void attn_vt_d64(AttnP
   const int h = (t / nqb) % p.heads;
   const int zz = t / (nqb * p.heads);
   const int b = zz / p.nsplit, split = zz % p.nsplit;
-  const int q0 = qb * 128 + wq * 32;
+  const int q0 = qb * 128 + wave * 32;
   const int kv_lo = split * p.keys_per_split;              // multiple of 64
   int kv_hi = kv_lo + p.keys_per_split;
   if (kv_hi > p.L) kv_hi = p.L;
-  const int ntiles = (kv_hi - kv_lo + TK * NGR - 1) / (TK * NGR);   // iterations: one 64-key tile per group each
+  const int ntiles = (kv_hi - kv_lo + TK - 1) / TK;
 
   const bf16_t* kg = (const bf16_t*)p.ks + (long long)b * p.bsks + h * D;
   const bf16_t* vg = (const bf16_t*)p.vs + (long long)b * p.bsvs + (long long)h * D * p.vt_ld;
 
+  // direct loads: instruction j of a wave covers tile rows (2*wave + j)*8 + lane/8, 16-byte slot lane%8
+  const int lr = lane >> 3, slot8 = lane & 7;
+  unsigned int kofs[2], vofs[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = (2 * wave + j) * 8 + lr;
+    kofs[j] = (unsigned int)row * (unsigned int)p.ldks + (unsigned int)((slot8 ^ ((row >> 1) & 7)) * 8);
+    vofs[j] = (unsigned int)row * (unsigned int)p.vt_ld + (unsigned int)((slot8 ^ (row & 7) ^ (row >> 3)) * 8);
+  }
+  // LDS: three K tiles [key][d], then three V^T tiles [d][key].  kofr: the offsets inside the last tile when it is ragged
+  // (rows beyond the last key re-read it and are masked)
+  unsigned int kofr[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int row = (2 * wave + j) * 8 + lr, left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
+    kofr[j] = (unsigned int)(row < left ? row : left) * (unsigned int)p.ldks + (unsigned int)((slot8 ^ ((row >> 1) & 7)) * 8);
+  }
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
@@ -410,212 +436,190 @@ __global__ __launch_bounds__(256 * NGR, NGR == 1 ? 2 : 1) void attn_vt_d64(AttnP
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
-
-  // direct loads: instruction j of a wave covers tile rows (2*wave + j)*8 + lane/8, 16-byte slot lane%8.  A lane's
-  // offsets inside a tile never change (32-bit, the launcher bounds the pitches); a tile adds a scalar base.
-  const int lr = lane >> 3, slot = lane & 7;
-  unsigned int kofs[2], vofs[2];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int row = (2 * wave + j) * 8 + lr;               // key within the iteration's K tiles
-    const int f = (row >> 1) & 7;                          // swizzle key: conflict-free 16-byte reads on 64 banks
-    kofs[j] = (unsigned int)row * (unsigned int)p.ldks + (unsigned int)((slot ^ f) * 8);
-    const int d = ((2 * wave + j) & 7) * 8 + lr;           // feature row of the V^T tile (waves 4-7: second group's tile)
-    const int ch = slot ^ (d & 7) ^ (d >> 3);              // 8-key chunk; the buffer is padded to whole tiles
-    vofs[j] = (unsigned int)d * (unsigned int)p.vt_ld + (unsigned int)(ch * 8);
-  }
-  auto issue = [&](int tl, int stage) {
-    if (tl > ntiles - 1) tl = ntiles - 1;                  // past the end: re-read the last tile (keeps vmcnt uniform)
-    const int key0 = kv_lo + tl * TK * NGR;
-    char* sk = smem + stage * STAGE;
-    char* sv = sk + KB * NGR;
-    if (key0 + TK * NGR <= p.L) {                          // (uniform) every key row of the iteration exists
-      const bf16_t* kb = kg + (long long)key0 * p.ldks;
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kb + kofs[j]), DF_LPTR(sk + (2 * wave + j) * 1024), 16, 0, 0);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int row = (2 * wave + j) * 8 + lr;
-        int key = key0 + row;
-        if (key > p.L - 1) key = p.L - 1;                  // rows beyond the last key are masked below
-        const int f = (row >> 1) & 7;
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kg + (long long)key * p.ldks + ((slot ^ f) * 8)),
-                                         DF_LPTR(sk + (2 * wave + j) * 1024), 16, 0, 0);
-      }
-    }
-    long long vkey0 = key0 + TK * grp;
-    if (vkey0 > p.vt_ld - TK) vkey0 = p.vt_ld - TK;        // a tile wholly beyond the padded buffer: masked below
-    const bf16_t* vb = vg + vkey0;
+  for (int i = 0; i < 3; ++i) {
+    const int ti = i < ntiles ? i : ntiles - 1;            // past the end: the last tile again (keeps vmcnt uniform)
+    const bool rag = kv_lo + ti * TK + TK > p.L;
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds(DF_GPTR(vb + vofs[j]), DF_LPTR(sv + (2 * wave + j) * 1024), 16, 0, 0);
-  };
+      __builtin_amdgcn_global_load_lds(DF_GPTR(kg + (long long)(kv_lo + ti * TK) * p.ldks + (rag ? kofr[j] : kofs[j])),
+                                       DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j)
+    __builtin_amdgcn_global_load_lds(DF_GPTR(vg + kv_lo + vofs[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
 
-  f32x16 o_acc[2];
+  // LDS byte offsets of this lane's fragments inside a tile.  K: MFMA row c of key block kb, k-step s; V^T: feature csig of
+  // feature block db, key step ts.  The second block is 4096 bytes on in both (for V^T with the key steps ts ^ 2).
+  int kof[4], vof[4];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < 4; ++i) {
+    const int row = key_of_mfma_row(c), kchunk = 4 * (i >> 1) + 2 * (i & 1) + g;
+    kof[i] = row * (D * 2) + (((2 * i + g) ^ ((row >> 1) & 7)) * 16);
+    vof[i] = csig * (TK * 2) + ((kchunk ^ (csig & 7) ^ (csig >> 3)) * 16);
+  }
+  const char* const lds = smem;
+
+  f32x16 o_acc[2], sa[2], cinit;
 #pragma unroll
-    for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
+  for (int e = 0; e < 16; ++e) { o_acc[0][e] = 0.f; o_acc[1][e] = 0.f; cinit[e] = 0.f; }
   float m_run = -INFINITY, l_run = 0.f;
-  const float sc = p.scale * kLog2e;
-
+  const float sc = PRE ? 1.0f : p.sc_log2;
+  u32x4 pk[4];                                             // packed probabilities of the previous tile
 #pragma unroll
-  for (int i = 0; i < NST - 1; ++i) issue(i, i);
-  DF_ATRACE(2, __builtin_readcyclecounter());
-  int stage = 0, nstage = NST - 1;
-  for (int tl = 0; tl < ntiles; ++tl) {
-    if (tl < 8) DF_ATRACE(3 + 3 * tl, __builtin_readcyclecounter());
-    // tile tl has landed once at most the loads of the NST-2 younger tiles (4 each) are outstanding
-    {
-      constexpr int VM = 4 * (NST - 2);
-      __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4) | (0 << 8));   // vmcnt(VM) lgkmcnt(0)
-    }
+  for (int i = 0; i < 4; ++i) pk[i] = u32x4{0u, 0u, 0u, 0u};
+
+  auto max8 = [&](const f32x16& s, int h, float a) {       // maximum with accumulators 8h .. 8h+7
+    a = fmaxf(fmaxf(a, s[8 * h]), s[8 * h + 1]);
+    a = fmaxf(fmaxf(a, s[8 * h + 2]), s[8 * h + 3]);
+    a = fmaxf(fmaxf(a, s[8 * h + 4]), s[8 * h + 5]);
+    return fmaxf(fmaxf(a, s[8 * h + 6]), s[8 * h + 7]);
+  };
+  auto vfrag = [&](int vbase, int ts, int db) { return *reinterpret_cast<const u32x4*>(lds + vbase + vof[db ? ts ^ 2 : ts] + 4096 * db); };
+  auto kfrag = [&](int kbase, int s, int kb) { return *reinterpret_cast<const u32x4*>(lds + kbase + kof[s] + 4096 * kb); };
+  auto pv_mfma = [&](u32x4 v, int ts, int db) {
+    o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pk[ts]), o_acc[db], 0, 0, 0);
+  };
+  auto s_mfma = [&](u32x4 k, int s, int kb) {
+    sa[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), qreg[s], s == 0 ? cinit : sa[kb], 0, 0, 0);
+  };
+  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+  auto sync_tile = [&](auto vmc) {
+    constexpr int VM = decltype(vmc)::value;
+    __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4) | (0 << 8));   // vmcnt(VM) lgkmcnt(0)
     asm volatile("" ::: "memory");
-    if (tl < 8) DF_ATRACE(4 + 3 * tl, __builtin_readcyclecounter());
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (tl < 8) DF_ATRACE(5 + 3 * tl, __builtin_readcyclecounter());
-    issue(tl + NST - 1, nstage);                           // the stage every wave finished reading before the barrier
-    const bf16_t* Ks = reinterpret_cast<const bf16_t*>(smem + stage * STAGE + grp * KB);
-    const bf16_t* Vt = reinterpret_cast<const bf16_t*>(smem + stage * STAGE + KB * NGR + grp * KB);
-    const int tile_base = kv_lo + tl * TK * NGR + grp * TK;
-    // The tile's work in two copies: full tiles carry no mask code at all (written as one body with a run-time flag,
-    // the compiler evaluates the masks' comparisons ahead of the branch in every tile: a third of the loop's vector
-    // instructions).
-    auto tile = [&](auto raggedc) {
-    constexpr bool ragged = decltype(raggedc)::value;
-    // All LDS fragment reads of a phase are issued before its MFMAs (one read per MFMA would put an LDS round trip
-    // between every pair of matrix instructions), and the V^T fragments are requested before the softmax so that
-    // they arrive while the vector ALU works.
-    bf16x8 kfr[2][4];
+  };
+#define DF_FENCE __builtin_amdgcn_sched_barrier(0)
+
+  // S_0
+  sync_tile(std::integral_constant<int, 0>{});
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const int row = 32 * kb + key_of_mfma_row(c);
-      const int f = (row >> 1) & 7;
+  for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) kfr[kb][s] = *reinterpret_cast<const bf16x8*>(&Ks[row * D + (((2 * s + g) ^ f) * 8)]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    f32x16 s_acc[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s_acc[kb][e] = 0.f;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-        s_acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[kb][s], qreg[s], s_acc[kb], 0, 0, 0);
-    u32x4 vfr[4][2];
-#pragma unroll
-    for (int ts = 0; ts < 4; ++ts) {
-      const int kchunk = 4 * (ts >> 1) + 2 * (ts & 1) + g;
-#pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        const int d = 32 * db + csig;
-        vfr[ts][db] = *reinterpret_cast<const u32x4*>(&Vt[d * TK + (kchunk ^ (d & 7) ^ (d >> 3)) * 8]);
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (ragged) {
+    for (int kb = 0; kb < 2; ++kb) s_mfma(kfrag(0, s, kb), s, kb);
+
+  int kbase = KB, vbase = 2 * KB;                          // K_{tl+1}; V_{tl-1} (tile 0: K_2 as a finite stand-in, P is 0)
+  int kdst = 0, vdst = 4 * KB;                             // slots of K_{tl+3}, V_{tl+1}
+  int tl = 0;
+  const bool ragged = (kv_hi - kv_lo) % TK != 0;
+  const int nfull = ragged ? ntiles - 1 : ntiles;
+  float m_base = 0.f;                                      // what the scores in sa are relative to (PRE)
+  for (;;) {
+    // First tile, a tile with a score beyond the window, or the ragged last tile: settle the pending tile's values, mask
+    // the keys beyond the range, move the running maximum and rescale everything to it.
+    if (ragged && tl == ntiles - 1) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int j = e >> 2, r = e & 3;
-          const int key = tile_base + 32 * kb + 16 * (j >> 1) + 8 * g + 4 * (j & 1) + r;
-          if (key >= kv_hi) s_acc[kb][e] = -INFINITY;
-        }
+        for (int e = 0; e < 16; ++e)
+          if (kv_lo + tl * TK + 32 * kb + 16 * (e >> 3) + 8 * g + (e & 7) >= kv_hi) sa[kb][e] = -INFINITY;
     }
-    float mx = -INFINITY;
+    {
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+      for (int i = 0; i < 8; ++i) pv_mfma(vfrag(vbase, i >> 1, i & 1), i >> 1, i & 1);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s_acc[kb][e]);
-    mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)))) * sc;
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    float rs = 0.f;
+      for (int i = 0; i < 4; ++i) pk[i] = u32x4{0u, 0u, 0u, 0u};
+      const float mx = max8(sa[1], 1, max8(sa[1], 0, max8(sa[0], 1, max8(sa[0], 0, -INFINITY))));
+      const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)));
+      const float m_new = fmaxf(m_run, PRE ? fmaxf(mx, part) + m_base : fmaxf(mx, part) * sc);
+      if constexpr (PRE) {
+        const float shift = m_base - m_new;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][e], sc, -m_new));
-        s_acc[kb][e] = pv;
-        rs += pv;
+        for (int e = 0; e < 16; ++e) { sa[0][e] += shift; sa[1][e] += shift; cinit[e] = -m_new; }
+        m_base = m_new;
       }
-    rs += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(rs)));
-    l_run = l_run * alpha + rs;
-    m_run = m_new;
-    // the running maximum rarely moves after the first tiles: rescale only when some query of the wave needs it
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o_acc[i][e] *= alpha;
+      for (int e = 0; e < 16; ++e) { o_acc[0][e] *= alpha; o_acc[1][e] *= alpha; }
+      l_run *= alpha;
+      m_run = m_new;
     }
+    bool move;
+    do {
+      // Tile tl: its probabilities from the scores in sa (in place: a key block's registers take S of tile tl+1 as soon as
+      // its exponentials are done), O += V P of tile tl-1, S of tile tl+1.  One matrix instruction and its share of
+      // vector instructions per slot; operand fragments are read from LDS five slots ahead.
+      u32x4 f[16];
 #pragma unroll
-    for (int ts = 0; ts < 4; ++ts) {
-      const int kb = ts >> 1, half = ts & 1;
-      u32x4 pk;
-      pk.x = pack_bf2(s_acc[kb][8 * half + 0], s_acc[kb][8 * half + 1]);
-      pk.y = pack_bf2(s_acc[kb][8 * half + 2], s_acc[kb][8 * half + 3]);
-      pk.z = pack_bf2(s_acc[kb][8 * half + 4], s_acc[kb][8 * half + 5]);
-      pk.w = pack_bf2(s_acc[kb][8 * half + 6], s_acc[kb][8 * half + 7]);
-      const bf16x8 pfrag = __builtin_bit_cast(bf16x8, pk);
-      const int kchunk = 4 * kb + 2 * half + g;            // keys 32*kb + 16*half + 8*g .. +7
+      for (int i = 0; i < 5; ++i) f[i] = vfrag(vbase, i >> 1, i & 1);
+      float ex[2][8];
+      auto E = [&](int u, int h) {                         // four exponentials of key step u
 #pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        u32x4 vraw = vfr[ts][db];
-        if constexpr (ragged) {                            // keys beyond the range: P is 0, V must be finite
-          const int key = tile_base + kchunk * 8;
-          if (key + 0 >= kv_hi) vraw.x = 0u; else if (key + 1 >= kv_hi) vraw.x &= 0xffffu;
-          if (key + 2 >= kv_hi) vraw.y = 0u; else if (key + 3 >= kv_hi) vraw.y &= 0xffffu;
-          if (key + 4 >= kv_hi) vraw.z = 0u; else if (key + 5 >= kv_hi) vraw.z &= 0xffffu;
-          if (key + 6 >= kv_hi) vraw.w = 0u; else if (key + 7 >= kv_hi) vraw.w &= 0xffffu;
+        for (int q = 0; q < 4; ++q) {
+          const float x = sa[u >> 1][8 * (u & 1) + 4 * h + q];
+          ex[u & 1][4 * h + q] = __builtin_amdgcn_exp2f(PRE ? x : fmaf(x, sc, -m_run));
         }
-        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vraw), pfrag, o_acc[db], 0, 0, 0);
-      }
-    }
-    };
-    if (tile_base + TK <= kv_hi) tile(std::false_type{});          // (wave-uniform branches)
-    else if (tile_base < kv_hi) tile(std::true_type{});            // the last iteration may hold one tile only
-    stage = (stage + 1 == NST) ? 0 : stage + 1;
-    nstage = (nstage + 1 == NST) ? 0 : nstage + 1;
+      };
+      unsigned int w[2][4];
+      auto C = [&](int u) {                                // packing (after the matrix instructions of key step u read pk[u])
+#pragma unroll
+        for (int q = 0; q < 4; ++q) w[u & 1][q] = pack_bf2(ex[u & 1][2 * q], ex[u & 1][2 * q + 1]);
+        pk[u] = u32x4{w[u & 1][0], w[u & 1][1], w[u & 1][2], w[u & 1][3]};
+      };
+      auto S = [&](int u) {                                // row sums
+#pragma unroll
+        for (int q = 0; q < 4; ++q) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[u & 1][q]), ones, l_run, false);
+      };
+      const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
+      const bf16_t* kb3 = kg + (long long)(kv_lo + tk3 * TK) * p.ldks;
+      const bf16_t* vb1 = vg + kv_lo + tv1 * TK;
+      const bool krag = kv_lo + tk3 * TK + TK > p.L;
+      auto dma_k = [&](int j) {
+        __builtin_amdgcn_global_load_lds(DF_GPTR(kb3 + (krag ? kofr[j] : kofs[j])), DF_LPTR(smem + kdst + (2 * wave + j) * 1024), 16, 0, 0);
+      };
+      auto dma_v = [&](int j) {
+        __builtin_amdgcn_global_load_lds(DF_GPTR(vb1 + vofs[j]), DF_LPTR(smem + vdst + (2 * wave + j) * 1024), 16, 0, 0);
+      };
+      DF_FENCE;
+      pv_mfma(f[0], 0, 0); f[5] = vfrag(vbase, 2, 1); E(0, 0); DF_FENCE;
+      pv_mfma(f[1], 0, 1); f[6] = kfrag(kbase, 0, 0); E(0, 1); dma_k(0); DF_FENCE;
+      pv_mfma(f[2], 1, 0); f[7] = vfrag(vbase, 3, 0); C(0); dma_k(1); DF_FENCE;
+      pv_mfma(f[3], 1, 1); f[8] = kfrag(kbase, 1, 0); E(1, 0); DF_FENCE;
+      pv_mfma(f[4], 2, 0); f[9] = vfrag(vbase, 3, 1); E(1, 1); DF_FENCE;
+      pv_mfma(f[5], 2, 1); f[10] = kfrag(kbase, 2, 0); C(1); S(0); DF_FENCE;
+      s_mfma(f[6], 0, 0); f[11] = kfrag(kbase, 3, 0); E(2, 0); DF_FENCE;
+      pv_mfma(f[7], 3, 0); f[12] = kfrag(kbase, 0, 1); E(2, 1); S(1); DF_FENCE;
+      s_mfma(f[8], 1, 0); f[13] = kfrag(kbase, 1, 1); C(2); dma_v(0); DF_FENCE;
+      pv_mfma(f[9], 3, 1); f[14] = kfrag(kbase, 2, 1); E(3, 0); DF_FENCE;
+      s_mfma(f[10], 2, 0); f[15] = kfrag(kbase, 3, 1); E(3, 1); dma_v(1); DF_FENCE;
+      s_mfma(f[11], 3, 0); S(2); DF_FENCE;
+      s_mfma(f[12], 0, 1); C(3); DF_FENCE;
+      s_mfma(f[13], 1, 1); S(3); DF_FENCE;
+      s_mfma(f[14], 2, 1); DF_FENCE;
+      s_mfma(f[15], 3, 1);
+      float mx = max8(sa[0], 1, max8(sa[0], 0, -INFINITY));
+      DF_FENCE;
+      mx = max8(sa[1], 1, max8(sa[1], 0, mx));
+      kbase = kbase == 2 * KB ? 0 : kbase + KB;
+      kdst = kdst == 2 * KB ? 0 : kdst + KB;
+      vbase = vbase == 5 * KB ? 3 * KB : vbase + KB;
+      vdst = vdst == 5 * KB ? 3 * KB : vdst + KB;
+      ++tl;
+      sync_tile(std::integral_constant<int, 4>{});         // K_{tl+1} and V_{tl-1} of the next tile have landed, for every wave
+      move = __builtin_amdgcn_ballot_w64(PRE ? mx > 8.0f : fmaf(mx, sc, -m_run) > 8.0f) != 0;
+    } while (tl < nfull && !move);
+    if (tl >= ntiles) break;
   }
-  __builtin_amdgcn_s_waitcnt((0 & 0xF) | (0x7 << 4) | (0 << 8));     // drain the clamped tail loads
-  DF_ATRACE(28, __builtin_readcyclecounter());
-  DF_ATRACE(31, ntiles);
-
-  if constexpr (NGR == 2) {
-    // group 1 hands its state to group 0 (the ring is free once every wave has drained its loads)
-    __syncthreads();
-    float* mrg = reinterpret_cast<float*>(smem);           // [4 waves][34][64]: 32 accumulators, max, sum per lane
-    if (grp == 1) {
+  // the last tile's values
+  sync_tile(std::integral_constant<int, 0>{});
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) mrg[(wq * 34 + i * 16 + e) * 64 + lane] = o_acc[i][e];
-      mrg[(wq * 34 + 32) * 64 + lane] = m_run;
-      mrg[(wq * 34 + 33) * 64 + lane] = l_run;
+  for (int i = 0; i < 8; ++i) {
+    const int ts = i >> 1;
+    u32x4 v = vfrag(vbase, ts, i & 1);
+    if (ragged) {                                          // keys beyond the range: P is 0, V must be finite
+      const int key = kv_lo + (ntiles - 1) * TK + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
+      if (key + 0 >= kv_hi) v.x = 0u; else if (key + 1 >= kv_hi) v.x &= 0xffffu;
+      if (key + 2 >= kv_hi) v.y = 0u; else if (key + 3 >= kv_hi) v.y &= 0xffffu;
+      if (key + 4 >= kv_hi) v.z = 0u; else if (key + 5 >= kv_hi) v.z &= 0xffffu;
+      if (key + 6 >= kv_hi) v.w = 0u; else if (key + 7 >= kv_hi) v.w &= 0xffffu;
     }
-    __syncthreads();
-    if (grp == 1) return;
-    const float m1 = mrg[(wq * 34 + 32) * 64 + lane], l1 = mrg[(wq * 34 + 33) * 64 + lane];
-    const float m_new = fmaxf(m_run, m1);                  // group 0 always holds at least one key: finite
-    const float a0 = __builtin_amdgcn_exp2f(m_run - m_new), a1 = __builtin_amdgcn_exp2f(m1 - m_new);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) o_acc[i][e] = o_acc[i][e] * a0 + mrg[(wq * 34 + i * 16 + e) * 64 + lane] * a1;
-    l_run = l_run * a0 + l1 * a1;
-    m_run = m_new;
+    pv_mfma(v, ts, i & 1);
   }
+#undef DF_FENCE
+  l_run += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(l_run)));
 
-  DF_ATRACE(29, __builtin_readcyclecounter());
-  DF_ATRACE(30, wall_clock64());
   const int qi = q0 + c;
   if (qi >= p.Lq) return;
   if (p.nsplit == 1) {
@@ -661,7 +665,7 @@ __global__ __launch_bounds__(256 * NGR, NGR == 1 ? 2 : 1) void attn_vt_d64(AttnP
 // direct loads, 1 KB contiguous per instruction; a wave reading its MFMA operands straight from the row-major buffers
 // touches 32 cache lines per instruction and ran at a quarter of the rate) in a private 16 KB of LDS, so the loop has no
 // barrier: a tile's fragments go LDS -> registers, then the next tile's loads are issued into the same LDS while the
-// tile computes.  Same operand conventions and swizzles as attn_vt_d64.
+// tile computes.  Same operand conventions and swizzles as attn_pipe_d64.
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   constexpr int D = 64, TK = 64;
@@ -757,7 +761,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
 #pragma unroll
     for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
-  const float sc = p.scale * kLog2e;
+  const float sc = p.sc_log2;
 
   auto tile = [&](int tl, auto raggedc) {
     constexpr bool ragged = decltype(raggedc)::value;
@@ -997,23 +1001,30 @@ __global__ __launch_bounds__(256) void attn_f32(AttnParams p) {
   }
 }
 
-// Number of key-range splits.  Cost model from the kernel traces of the patch step: a compute unit works through its
-// workgroups' 64-key tiles at a roughly constant rate whether one or three of them are resident, so the time follows
-// the most loaded unit, ceil(workgroups / 256) x (tiles per workgroup + a fixed part); the merge kernel grows with the
-// number of partials.  (Plain "at least 512 workgroups" picked 800 for the 1200-query level: 768 run at once and
-// the last 32 had the chip to themselves for a full workgroup lifetime, +35 %.)
-int pick_splits(int B, int Lq, int L, int heads) {
-  static const int forced = tune_env("DF_ATTN_SPLITS") ? atoi(tune_env("DF_ATTN_SPLITS")) : 0;   // tuning aid
-  if (forced > 0) return (L / forced >= 64) ? forced : 1;
+// Predicted time (microseconds) of attn_pipe_d64 with the keys in `ns` ranges, fitted on 22 shapes between 64 x 256 and
+// 7200 x 57600 with 1 to 12 ranges each.  A compute unit works through its workgroups' 64-key tiles at nearly the same
+// rate whether one or two are resident (0.65 and 0.53 us per tile), so the time follows the most loaded unit; ranges
+// even out the load, and cost a second kernel and the float partials (written and read at 2.9 TB/s together).
+double pipe_us(int B, int Lq, int L, int heads, int ns) {
   const long long blocks = (long long)cdiv(Lq, 128) * heads * B;
+  const long long per_cu = (blocks * ns + 255) / 256;
+  const double tiles = cdiv(cdiv(L, ns), 64);
+  return 4.5 + tiles * (per_cu == 1 ? 0.65 : 0.53 * per_cu) +
+         (ns > 1 ? 2.5 + (double)B * heads * Lq * ns * 512.0 / 2.9e6 : 0.0);
+}
+
+// Number of key ranges
+int pick_splits(int B, int Lq, int L, int heads) {
+#ifdef DF_TUNING
+  const int forced = tune_env("DF_ATTN_SPLITS") ? atoi(tune_env("DF_ATTN_SPLITS")) : 0;
+  if (forced > 0) return (L / forced >= 64) ? forced : 1;
+#endif
   int best = 1;
-  double best_cost = 1e30;
+  double best_us = 1e30;
   for (int ns = 1; ns <= 16; ++ns) {
     if (ns > 1 && L / ns < 128) break;
-    const int tiles = cdiv(cdiv(L, ns), 64);
-    const long long per_cu = (blocks * ns + 255) / 256;
-    const double cost = (double)per_cu * (tiles + 2) + (ns > 1 ? 1.0 + 0.5 * ns : 0.0);
-    if (cost < best_cost - 1e-9) { best_cost = cost; best = ns; }
+    const double us = pipe_us(B, Lq, L, heads, ns);
+    if (us < best_us - 1e-9) { best_us = us; best = ns; }
   }
   return best;
 }
@@ -1050,6 +1061,8 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   p.ldq = a.ldq; p.ldkf = a.ldkf; p.ldvf = a.ldvf; p.ldks = a.ldks; p.ldvs = a.ldvs; p.ldo = a.ldo;
   p.bsq = a.bsq; p.bskf = a.bskf; p.bsvf = a.bsvf; p.bsks = a.bsks; p.bsvs = a.bsvs; p.bso = a.bso;
   p.scale = a.scale;
+  p.sc_log2 = a.q_scaled ? 1.0f : a.scale * kLog2e;
+  if (a.q_scaled && !a.v_transposed) return DF_EINVAL;
   p.nsplit = 1; p.keys_per_split = a.L;
   p.out_packed = a.out_packed;
   if (a.out_packed && (a.dtype != DF_BF16 || ((uintptr_t)a.out % 16))) return DF_EINVAL;
@@ -1067,15 +1080,21 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   for (long long v : lds) if (v % 8) return DF_EINVAL;
   const void* ptrs[] = {a.q, a.k_fresh, a.v_fresh, a.k_stale, a.v_stale, a.out};
   for (const void* q : ptrs) if ((uintptr_t)q % 16) return DF_EINVAL;
-  // Few queries against many keys (the patch at the deepest level): one workgroup per 32-query block and head whose
-  // waves split the keys; no partials, no merge kernel.  Each block streams the head's whole K / V^T, so this pays
-  // only while the query blocks are few: a compute unit then pulls Lq / 32 x the head's keys through its load path where
-  // the LDS-tiled kernel pulls Lq / 128 x.  Measured: 300 queries x 2400 keys 17.9 -> 16.6 us (both launches of the
-  // split form counted), 1024 x 4096 49.2 -> 56.4 us.
-  // It also wants its workgroups in one round (at most one per compute unit): two batch items of 300 queries make 400
-  // workgroups, 144 units run two of them in turn, and the split form wins again (2.48 vs 3.02 ms per step).
-  static const int wave_lq = tune_env("DF_ATTN_WAVE_LQ") ? atoi(tune_env("DF_ATTN_WAVE_LQ")) : 512;   // tuning aid
-  if (a.v_transposed && a.Lq <= wave_lq && a.L >= 512 && (long long)cdiv(a.Lq, 32) * a.heads * a.B <= 256) {
+  // Few queries (the patch at the deepest level): one workgroup per 32-query block and head whose eight waves split the
+  // keys; no partials, no merge kernel.  Each block streams the head's whole K / V^T, so a compute unit pulls Lq / 32 x
+  // the head's keys through its load path where the LDS-shared kernel pulls Lq / 128 x: taken where its time, a launch
+  // and 1.93 us per 64-key tile of a wave, is below the other's, and only with its workgroups in one round (at most one
+  // per compute unit).  300 queries x 2400 keys x 20 heads 15.1 us (split form 17.9), 256 x 1024 x 10 8.6 (11.9),
+  // 256 x 4096 x 10 20.1 (17.4).
+#ifdef DF_TUNING
+  const char* wave_env = tune_env("DF_ATTN_WAVE");
+#else
+  const char* wave_env = nullptr;
+#endif
+  const bool wave_fits = a.v_transposed && a.L >= 512 && (long long)cdiv(a.Lq, 32) * a.heads * a.B <= 256;
+  if (wave_fits && (wave_env ? atoi(wave_env) != 0
+                             : 4.7 + 1.93 * cdiv(cdiv(a.L, 64), 8) <
+                                   pipe_us(a.B, a.Lq, a.L, a.heads, pick_splits(a.B, a.Lq, a.L, a.heads)))) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
@@ -1098,7 +1117,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   if ((long long)a.B * ns > 65535) return DF_ESHAPE;
   if ((long long)a.B * a.heads * a.Lq * 16 >= (1LL << 31)) return DF_ESHAPE;   // the merge kernel indexes with 32 bits
   if (ns > 1) {
-    const int kps = cdiv(cdiv(a.L, ns), 128) * 128;      // whole 128-key iterations of the two-group kernel
+    const int kps = cdiv(cdiv(a.L, ns), 128) * 128;      // whole pairs of tiles
     ns = cdiv(a.L, kps);                                 // rounding up may leave the last ranges empty: drop them
     if (ns > 1) {
       char* scr = scratch_region(a.scr, attention_scratch_bytes(a.B, a.Lq, a.L, a.heads, a.d));
@@ -1116,31 +1135,9 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
-    // Up to ~600 workgroups (at most two per compute unit): two groups of four waves and a two-stage ring (64 KB of
-    // LDS); measured on the patch step, the second group gains ~9 % over one group with a three-stage ring.  Larger
-    // launches keep one group and three stages (48 KB, three workgroups per unit), which is faster there (the
-    // 480 x 480-latent share: 27.4 vs 31.5 ms of self-attention).  Deeper rings lose in both forms: the kernel is not
-    // bound by the latency of the K / V^T stream.
-    static const int forced_st = tune_env("DF_ATTN_STAGES") ? atoi(tune_env("DF_ATTN_STAGES")) : 0;   // tuning aid
-    static const int forced_gr = tune_env("DF_ATTN_GROUPS") ? atoi(tune_env("DF_ATTN_GROUPS")) : 0;   // tuning aid
-    static const long long g2max = tune_env("DF_ATTN_G2MAX") ? atoll(tune_env("DF_ATTN_G2MAX")) : 600;   // tuning aid
-    const int ngr = forced_gr ? forced_gr : (nwg <= g2max ? 2 : 1);
-    const int nst = forced_st ? forced_st : (ngr == 2 ? 2 : 3);
-#define DF_ATTN_VT(NSTV, NGRV)                                                                                      \
-  {                                                                                                                 \
-    constexpr int smem = NSTV * 2 * 64 * 64 * 2 * NGRV;                                                             \
-    static bool attr_set = false;                                                                                   \
-    if (!attr_set) {                                                                                                \
-      if (hipFuncSetAttribute((const void*)attn_vt_d64<NSTV, NGRV>, hipFuncAttributeMaxDynamicSharedMemorySize,     \
-                              smem) != hipSuccess)                                                                  \
-        return DF_EHIP;                                                                                             \
-      attr_set = true;                                                                                              \
-    }                                                                                                               \
-    hipLaunchKernelGGL((attn_vt_d64<NSTV, NGRV>), dim3((unsigned)nwg), dim3(256 * NGRV), smem, st, p);              \
-  }
-    if (ngr == 2) { if (nst <= 2) DF_ATTN_VT(2, 2) else if (nst == 3) DF_ATTN_VT(3, 2) else DF_ATTN_VT(4, 2) }
-    else if (nst <= 3) DF_ATTN_VT(3, 1) else if (nst == 4) DF_ATTN_VT(4, 1) else DF_ATTN_VT(6, 1)
-#undef DF_ATTN_VT
+    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V^T tiles
+    if (a.q_scaled) hipLaunchKernelGGL((attn_pipe_d64<true>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    else hipLaunchKernelGGL((attn_pipe_d64<false>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   } else {
     // 32-bit row offsets inside a 64-key tile
     if (a.ldkf >= (1 << 24) || a.ldvf >= (1 << 24) || a.ldks >= (1 << 24) || a.ldvs >= (1 << 24)) return DF_ESHAPE;

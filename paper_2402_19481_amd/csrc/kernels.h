@@ -167,6 +167,7 @@ struct WGemmArgs {
   int seg_rows_in[3];
   int seg_tr[3];          // transposed segments, as in GemmArgs
   int seg_pin[3], seg_pout[3];   // strip-of-a-grid row mapping, as in GemmArgs
+  float seg0_scale;       // segment 0's values are multiplied by this before they are rounded (0: not)
   // Fused cross-attention: the layer is a query projection with N = heads * 64 and a folded LayerNorm; instead of
   // the projection the kernel writes out_packed = softmax(q k^T * xa_scale) v per head, against xa_keys text tokens
   // whose keys / values were packed by launch_pack_text_kv (xa_kv: this block's fragments, batch stride
@@ -207,6 +208,7 @@ struct AttnArgs {
   // bsvs) and every key is read from k_stale / v_stale (own_n must be 0; k_fresh / v_fresh are ignored); bf16, d = 64
   int v_transposed;
   long long vt_ld;
+  int q_scaled;         // q already holds query * scale * log2(e) (v_transposed only)
   const Scratch* scr;   // see GnArgs
 };
 int launch_attention(const AttnArgs& a, hipStream_t st);

@@ -630,6 +630,7 @@ struct Exec {
         ex.seg_out[1] = ks; ex.seg_ld[1] = C; ex.seg_rows_in[1] = Lq; ex.seg_rows_out[1] = L; ex.seg_row0[1] = (long long)row0;
         ex.seg_out[2] = vs; ex.seg_ld[2] = Lpad; ex.seg_rows_in[2] = Lq; ex.seg_rows_out[2] = 0; ex.seg_row0[2] = (long long)row0;
         ex.seg_tr[2] = 1;
+        ex.seg0_scale = scale * 1.4426950408889634f;   // exponents of the softmax leave the attention's loop ready for exp2
         ex.seg_pin[1] = ex.seg_pin[2] = pin; ex.seg_pout[1] = ex.seg_pout[2] = pout;
         wg(hp, p + ".attn1.qkv", false, true, nullptr, nullptr, nullptr, nullptr, 0, M, 3 * C, C, &ex);
       }
@@ -641,7 +642,7 @@ struct Exec {
         AttnArgs a = {};
         a.k_stale = ks; a.v_stale = vs; a.out = aop; a.q = qkv; a.out_packed = 1;
         a.k_fresh = ks; a.v_fresh = vs; a.own_lo = 0; a.own_n = 0;
-        a.v_transposed = 1; a.vt_ld = Lpad;
+        a.v_transposed = 1; a.vt_ld = Lpad; a.q_scaled = 1;
         a.B = B(); a.Lq = Lq; a.L = L; a.heads = heads; a.d = c.head_dim;
         a.ldq = C; a.ldkf = a.ldvf = C; a.ldks = C; a.ldvs = C; a.ldo = C;
         a.bsq = (long long)Lq * C; a.bskf = a.bsvf = (long long)L * C;

@@ -27,6 +27,7 @@ struct WParams {
   int seg_rows_in[3];
   int seg_tr[3];
   int seg_pin[3], seg_pout[3];
+  float seg0_scale;     // factor of segment 0 (the attention queries), 1 without one; segment 0 is never transposed
   // fused cross-attention (XA > 0): per (batch item, head) 8*XA key fragments then 4*XA value fragments
   const bf16x8* xkv;
   int xa_keys;          // valid text tokens
@@ -64,7 +65,9 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
       } else {
         const long long orow = (long long)bi * p.seg_rows_out[sg] + p.seg_row0[sg] +
                                seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
-        st_vec(p.seg_out[sg] + orow * p.seg_ld[sg] + (n - sg * p.seg_w), v);
+        const float sc = sg == 0 ? p.seg0_scale : 1.0f;
+        const float w[8] = {v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc, v[4] * sc, v[5] * sc, v[6] * sc, v[7] * sc};
+        st_vec(p.seg_out[sg] + orow * p.seg_ld[sg] + (n - sg * p.seg_w), w);
       }
     } else if (p.out_rows) {
       st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);

@@ -605,6 +605,8 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   if (a.nseg > 0) {
     if (a.nseg > 3 || a.seg_w % 32 || a.seg_w * a.nseg != a.N || a.geglu) return DF_ESHAPE;
     p.nseg = a.nseg; p.seg_w = a.seg_w;
+    if (a.seg0_scale != 0.f && a.seg_tr[0]) return DF_EINVAL;
+    p.seg0_scale = a.seg0_scale != 0.f ? a.seg0_scale : 1.0f;
     for (int i = 0; i < a.nseg; ++i) {
       if (!a.seg_out[i] || a.seg_rows_in[i] <= 0 || (!a.seg_tr[i] && (a.seg_ld[i] % 8 || !al(a.seg_out[i], 16))))
         return DF_EINVAL;

@@ -461,6 +461,33 @@ def test_attn_stale_vt(B, Lq, L, heads, packed):
     np.testing.assert_array_equal(got, got2)            # reproducible (padding rows of a packed output are not written)
 
 
+@pytest.mark.parametrize("Lq,L,heads", [(128, 64, 1), (129, 65, 2), (31, 127, 1), (257, 129, 1), (128, 192, 2), (640, 1000, 5),
+                                        (1024, 2496, 3)])
+@pytest.mark.parametrize("shape", ["rising", "falling", "spike"])
+def test_attn_stale_vt_running_maximum(Lq, L, heads, shape):
+    """Scores that leave the kernel's rescaling window: rising from tile to tile, falling, one far above all others in
+    the last (ragged) tile."""
+    say("attn_stale_vt_running_maximum", Lq, L, heads, shape)
+    C = heads * 64
+    q = normal(53, "q", (1, Lq, C))
+    k = 0.3 * normal(53, "k", (1, L, C))
+    v = round_bf16(normal(53, "v", (1, L, C)))
+    ramp = np.arange(L, dtype=np.float32) / L
+    grow = {"rising": ramp, "falling": 1.0 - ramp, "spike": (np.arange(L) == L - 1).astype(np.float32)}[shape]
+    u = np.ones(C, dtype=np.float32)
+    q = round_bf16(q + u)
+    k = round_bf16(k + 8.0 * grow[None, :, None] * u)       # score of key j grows by 64 * grow[j] (times 1 + noise)
+    ref = ops.attention_dense(q, k, v, heads)
+    Lp = (L + 63) // 64 * 64
+    vt = np.zeros((1, C, Lp), dtype=np.float32)
+    vt[:, :, :L] = v.transpose(0, 2, 1)
+    vt_d = dev(vt, True)
+    if Lp > L:
+        vt_d[:, :, L:] = float("nan")
+    got = host(df.attn_stale_vt(dev(q, True), dev(k, True), vt_d, heads, L))
+    check(got, ref, True, "attn_stale_vt_running_maximum", say=say)
+
+
 @pytest.mark.parametrize("B,rows,C,TL,count,block", [
     (1, 300, 1280, 77, 3, 1),       # level 2 of the benchmark step
     (1, 1200, 640, 77, 2, 0),       # level 1
