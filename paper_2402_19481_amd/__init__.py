@@ -139,7 +139,9 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    """The current stream's handle.  (torch.cuda.current_stream() builds a Stream object around it: 2.8 us per call against
+    0.2, more than half of what a small operation spends on the host outside its launch.)"""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def copy_bytes(dst, src):
