@@ -827,10 +827,76 @@ __global__ __launch_bounds__(256) void conv3x3_direct(const T* __restrict__ x, c
   Elem<OutT>::st(y + idx, acc);
 }
 
+// f32, Cin % 4 == 0: a workgroup owns 4 pixels x 32 output channels, its four waves every fourth 16-byte chunk of the channels
+// of each tap; a lane owns one output channel of two pixels.  Latency-bound at the sizes it is used at: all loads of
+// a tap are independent, and the weights of a channel are read along its row (one thread per output before, a serial
+// loop over 9 x Cin with the lanes' weights a row apart: 128 pixels x 32 channels, Cin = 32: 37.9 -> 4 us).
+__global__ __launch_bounds__(256) void conv3x3_f32(const float* __restrict__ x, const float* __restrict__ top,
+                                                   const float* __restrict__ bot, long long halo_bs,
+                                                   const float* __restrict__ left, const float* __restrict__ right,
+                                                   long long side_bs, long long side_rs, const float* __restrict__ w,
+                                                   const float* __restrict__ bias, const float* __restrict__ chan_add,
+                                                   const float* __restrict__ residual, float* __restrict__ y, int B, int R,
+                                                   int W, int Cin, int Cout, int Ro, int Wo, int stride, int act) {
+  __shared__ float red[4][4][32];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int nct = (Cout + 31) >> 5;
+  const long long total = (long long)B * Ro * Wo;
+  const long long p0 = (long long)(blockIdx.x / nct) * 4;
+  const int c0 = (int)(blockIdx.x % nct) * 32;
+  const int co = c0 + (lane & 31) < Cout ? c0 + (lane & 31) : Cout - 1;
+  int pr[2], pc[2], pb[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    long long pix = p0 + 2 * (lane >> 5) + i;
+    if (pix >= total) pix = total - 1;
+    pc[i] = (int)(pix % Wo) * stride;
+    pr[i] = (int)((pix / Wo) % Ro) * stride;
+    pb[i] = (int)(pix / ((long long)Wo * Ro));
+  }
+  float acc[2] = {0.f, 0.f};
+#pragma unroll
+  for (int tap = 0; tap < 9; ++tap) {
+    const float* xp[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      xp[i] = conv_tap_src(x, top, bot, halo_bs, left, right, side_bs, side_rs, pb[i], pr[i] + tap / 3 - 1,
+                           pc[i] + tap % 3 - 1, R, W, Cin);
+    const float* wp = w + ((long long)co * 9 + tap) * Cin;
+    for (int k = wave * 4; k < Cin; k += 16) {
+      const f32x4 wv = *reinterpret_cast<const f32x4*>(wp + k);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        f32x4 xv = {0.f, 0.f, 0.f, 0.f};
+        if (xp[i]) xv = *reinterpret_cast<const f32x4*>(xp[i] + k);
+        acc[i] = fmaf(xv.x, wv.x, acc[i]); acc[i] = fmaf(xv.y, wv.y, acc[i]);
+        acc[i] = fmaf(xv.z, wv.z, acc[i]); acc[i] = fmaf(xv.w, wv.w, acc[i]);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) red[wave][2 * (lane >> 5) + i][lane & 31] = acc[i];
+  __syncthreads();
+  if (threadIdx.x < 128) {
+    const int px = threadIdx.x >> 5, n = c0 + (threadIdx.x & 31);
+    const long long pix = p0 + px;
+    if (pix >= total || n >= Cout) return;
+    float v = (red[0][px][threadIdx.x & 31] + red[1][px][threadIdx.x & 31]) +
+              (red[2][px][threadIdx.x & 31] + red[3][px][threadIdx.x & 31]);
+    if (bias) v += bias[n];
+    if (chan_add) v += chan_add[pix / ((long long)Ro * Wo) * Cout + n];
+    if (residual) v += residual[pix * Cout + n];
+    if (act == 1) v = silu_f(v);
+    y[pix * Cout + n] = v;
+  }
+}
+
 // One wave per output pixel, lanes split the 9*Cin reduction; for wide inputs and few outputs (Cout <= 8).
 template <typename T, typename OutT, int CO>
 __global__ __launch_bounds__(256) void conv3x3_wave(const T* __restrict__ x, const T* __restrict__ top,
                                                     const T* __restrict__ bot, long long halo_bs,
+                                                    const T* __restrict__ left, const T* __restrict__ right,
+                                                    long long side_bs, long long side_rs,
                                                     const T* __restrict__ w, const float* __restrict__ bias,
                                                     const float* __restrict__ residual, OutT* __restrict__ y, int B,
                                                     int R, int W, int Cin, int Cout, int Ro, int Wo, int stride,
@@ -846,20 +912,10 @@ __global__ __launch_bounds__(256) void conv3x3_wave(const T* __restrict__ x, con
   for (int o = 0; o < CO; ++o) acc[o] = 0.f;
   for (int ky = 0; ky < 3; ++ky) {
     const int ri = r * stride + ky - 1;
-    const T* rowp;
-    if (ri < 0) {
-      if (!top) continue;
-      rowp = top + b * halo_bs;
-    } else if (ri >= R) {
-      if (!bot) continue;
-      rowp = bot + b * halo_bs;
-    } else {
-      rowp = x + ((long long)b * R + ri) * W * Cin;
-    }
     for (int kx = 0; kx < 3; ++kx) {
       const int ci = c * stride + kx - 1;
-      if (ci < 0 || ci >= W) continue;
-      const T* xp = rowp + (long long)ci * Cin;
+      const T* xp = conv_tap_src(x, top, bot, halo_bs, left, right, side_bs, side_rs, b, ri, ci, R, W, Cin);
+      if (!xp) continue;
       for (int i = lane; i < Cin; i += 64) {
         const float xv = Elem<T>::ld(xp + i);
 #pragma unroll
@@ -887,6 +943,8 @@ __global__ __launch_bounds__(256) void conv3x3_wave(const T* __restrict__ x, con
 template <typename OutT>
 __global__ __launch_bounds__(256) void conv3x3_cin4(const bf16_t* __restrict__ x, const bf16_t* __restrict__ top,
                                                     const bf16_t* __restrict__ bot, long long halo_bs,
+                                                    const bf16_t* __restrict__ left, const bf16_t* __restrict__ right,
+                                                    long long side_bs, long long side_rs,
                                                     const bf16_t* __restrict__ w, const float* __restrict__ bias,
                                                     const float* __restrict__ residual, OutT* __restrict__ y, int B, int R,
                                                     int W, int Cout, int Ro, int Wo, int stride, int act) {
@@ -903,15 +961,12 @@ __global__ __launch_bounds__(256) void conv3x3_cin4(const bf16_t* __restrict__ x
 #pragma unroll
   for (int ky = 0; ky < 3; ++ky) {
     const int ri = r * stride + ky - 1;
-    const bf16_t* rowp = nullptr;
-    if (ri < 0) { if (top) rowp = top + b * halo_bs; }
-    else if (ri >= R) { if (bot) rowp = bot + b * halo_bs; }
-    else rowp = x + ((long long)b * R + ri) * W * 4;
 #pragma unroll
     for (int kx = 0; kx < 3; ++kx) {
       const int ci = c * stride + kx - 1;
+      const bf16_t* xp = conv_tap_src(x, top, bot, halo_bs, left, right, side_bs, side_rs, b, ri, ci, R, W, 4);
       u32x2 t = {0u, 0u};
-      if (rowp && ci >= 0 && ci < W) t = *reinterpret_cast<const u32x2*>(rowp + (long long)ci * 4);
+      if (xp) t = *reinterpret_cast<const u32x2*>(xp);
       xin[ky * 3 + kx][0] = __uint_as_float(t.x << 16); xin[ky * 3 + kx][1] = __uint_as_float(t.x & 0xffff0000u);
       xin[ky * 3 + kx][2] = __uint_as_float(t.y << 16); xin[ky * 3 + kx][3] = __uint_as_float(t.y & 0xffff0000u);
     }
@@ -952,6 +1007,8 @@ __global__ __launch_bounds__(256) void conv3x3_cin4(const bf16_t* __restrict__ x
 template <typename OutT, int CO>
 __global__ __launch_bounds__(256) void conv3x3_fewout(const bf16_t* __restrict__ x, const bf16_t* __restrict__ top,
                                                       const bf16_t* __restrict__ bot, long long halo_bs,
+                                                      const bf16_t* __restrict__ left, const bf16_t* __restrict__ right,
+                                                      long long side_bs, long long side_rs,
                                                       const bf16_t* __restrict__ w, const float* __restrict__ bias,
                                                       const float* __restrict__ residual, OutT* __restrict__ y, int B,
                                                       int R, int W, int Cin, int Cout, int act) {
@@ -972,10 +1029,6 @@ __global__ __launch_bounds__(256) void conv3x3_fewout(const bf16_t* __restrict__
     const int tp = ch / cpt, k8 = (ch - tp * cpt) * 8;
     const int ky = tp / 3, kx = tp - ky * 3;
     const int ri = r + ky - 1;
-    const bf16_t* rowp = nullptr;
-    if (ri < 0) { if (top) rowp = top + b * halo_bs; }
-    else if (ri >= R) { if (bot) rowp = bot + b * halo_bs; }
-    else rowp = x + ((long long)b * R + ri) * W * Cin;
     float wv[CO][8];
 #pragma unroll
     for (int o = 0; o < CO; ++o) {
@@ -987,10 +1040,12 @@ __global__ __launch_bounds__(256) void conv3x3_fewout(const bf16_t* __restrict__
     }
 #pragma unroll
     for (int px = 0; px < 4; ++px) {
-      const int ci = c0 + px + kx - 1;
-      if (!rowp || ci < 0 || ci >= W) continue;
+      // pixels beyond the row's end read its last pixel (nothing is stored for them)
+      const int ci = (c0 + px < W ? c0 + px : W - 1) + kx - 1;
+      const bf16_t* xp = conv_tap_src(x, top, bot, halo_bs, left, right, side_bs, side_rs, b, ri, ci, R, W, Cin);
+      if (!xp) continue;
       float xv[8];
-      ld_vec(rowp + (long long)ci * Cin + k8, xv);
+      ld_vec(xp + k8, xv);
 #pragma unroll
       for (int o = 0; o < CO; ++o)
 #pragma unroll
@@ -1341,17 +1396,23 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t st) {
                      a.residual, (OT*)a.y, a.B, a.R, a.W, a.Cin, a.Cout, Ro, Wo, a.stride, a.act)
 #define DF_WAVE(T, OT)                                                                                                \
   hipLaunchKernelGGL((conv3x3_wave<T, OT, 8>), dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, (const T*)a.x,        \
-                     (const T*)a.halo_top, (const T*)a.halo_bot, a.halo_bstride, (const T*)a.w, a.bias, a.residual,  \
+                     (const T*)a.halo_top, (const T*)a.halo_bot, a.halo_bstride, (const T*)a.halo_left,               \
+                     (const T*)a.halo_right, a.side_bstride, a.side_rstride, (const T*)a.w, a.bias, a.residual,       \
                      (OT*)a.y, a.B, a.R, a.W, a.Cin, a.Cout, Ro, Wo, a.stride, a.act)
   if ((total + 255) / 256 > 0x7fffffffLL) return DF_ESHAPE;
-  if (!sides && a.dtype == DF_BF16 && !a.chan_add && ((uintptr_t)a.x % 16 == 0) && ((uintptr_t)a.w % 16 == 0) &&
-      ((uintptr_t)a.halo_top % 16 == 0) && ((uintptr_t)a.halo_bot % 16 == 0)) {
+  // 16-byte loads; the pixels of four channels are loaded with 8-byte ones
+  const int pa = a.Cin == 4 && a.dtype == DF_BF16 ? 8 : 16;
+  const bool al16 = ((uintptr_t)a.x % 16 == 0) && ((uintptr_t)a.w % 16 == 0) && ((uintptr_t)a.halo_top % 16 == 0) &&
+                    ((uintptr_t)a.halo_bot % 16 == 0) && ((uintptr_t)a.halo_left % pa == 0) && ((uintptr_t)a.halo_right % pa == 0);
+  const int pe = pa / (a.dtype == DF_BF16 ? 2 : 4);              // elements per aligned access
+  if (a.dtype == DF_BF16 && !a.chan_add && al16 && a.side_bstride % pe == 0 && a.side_rstride % pe == 0) {
     if (a.Cin == 4 && a.Cout % 8 == 0 && a.halo_bstride % 4 == 0 && ((uintptr_t)a.y % 16 == 0) &&
         ((uintptr_t)a.residual % 16 == 0)) {
       const long long n = M * (a.Cout / 8);
 #define DF_C4(OT)                                                                                                  \
   hipLaunchKernelGGL((conv3x3_cin4<OT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const bf16_t*)a.x,     \
-                     (const bf16_t*)a.halo_top, (const bf16_t*)a.halo_bot, a.halo_bstride, (const bf16_t*)a.w, a.bias, \
+                     (const bf16_t*)a.halo_top, (const bf16_t*)a.halo_bot, a.halo_bstride, (const bf16_t*)a.halo_left, \
+                     (const bf16_t*)a.halo_right, a.side_bstride, a.side_rstride, (const bf16_t*)a.w, a.bias,         \
                      a.residual, (OT*)a.y, a.B, a.R, a.W, a.Cout, Ro, Wo, a.stride, a.act)
       if (a.out_dtype == DF_BF16) DF_C4(bf16_t); else DF_C4(float);
 #undef DF_C4
@@ -1362,7 +1423,8 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t st) {
       const long long quads = (long long)a.B * a.R * ((a.W + 3) / 4);
 #define DF_FEW(OT)                                                                                                 \
   hipLaunchKernelGGL((conv3x3_fewout<OT, 4>), dim3((unsigned)((quads + 3) / 4)), dim3(256), 0, st, (const bf16_t*)a.x, \
-                     (const bf16_t*)a.halo_top, (const bf16_t*)a.halo_bot, a.halo_bstride, (const bf16_t*)a.w, a.bias, \
+                     (const bf16_t*)a.halo_top, (const bf16_t*)a.halo_bot, a.halo_bstride, (const bf16_t*)a.halo_left, \
+                     (const bf16_t*)a.halo_right, a.side_bstride, a.side_rstride, (const bf16_t*)a.w, a.bias,         \
                      a.residual, (OT*)a.y, a.B, a.R, a.W, a.Cin, a.Cout, a.act)
       if (a.out_dtype == DF_BF16) DF_FEW(bf16_t); else DF_FEW(float);
 #undef DF_FEW
@@ -1370,10 +1432,18 @@ int launch_conv3x3(const ConvArgs& a, hipStream_t st) {
       return DF_OK;
     }
   }
-  const bool wave = a.Cout <= 8 && a.Cin >= 64 && !a.chan_add && !sides;   // the wave kernel knows row halos only
+  const bool wave = a.Cout <= 8 && a.Cin >= 64 && !a.chan_add;
   if (a.dtype == DF_F32) {
     if (a.out_dtype != DF_F32) return DF_ESHAPE;
-    if (wave) DF_WAVE(float, float); else DF_DIRECT(float, float);
+    if (!wave && al16 && a.Cin % 4 == 0 && a.halo_bstride % 4 == 0 && a.side_bstride % 4 == 0 && a.side_rstride % 4 == 0) {
+      // outputs per workgroup: 4 pixels x 32 channels
+      const long long nwg = cdiv(M, 4) * (long long)cdiv(a.Cout, 32);
+      if (nwg > 0x7fffffffLL) return DF_ESHAPE;
+      hipLaunchKernelGGL(conv3x3_f32, dim3((unsigned)nwg), dim3(256), 0, st, (const float*)a.x, (const float*)a.halo_top,
+                         (const float*)a.halo_bot, a.halo_bstride, (const float*)a.halo_left, (const float*)a.halo_right,
+                         a.side_bstride, a.side_rstride, (const float*)a.w, a.bias, a.chan_add, a.residual, (float*)a.y, a.B,
+                         a.R, a.W, a.Cin, a.Cout, Ro, Wo, a.stride, a.act);
+    } else if (wave) DF_WAVE(float, float); else DF_DIRECT(float, float);
   } else {
     if (a.out_dtype == DF_BF16) { if (wave) DF_WAVE(bf16_t, bf16_t); else DF_DIRECT(bf16_t, bf16_t); }
     else { if (wave) DF_WAVE(bf16_t, float); else DF_DIRECT(bf16_t, float); }

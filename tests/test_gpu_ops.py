@@ -190,6 +190,26 @@ def test_conv_halo_all_patches(B, H, W, Cin, Cout, N, stride, bf16):
     check(host(y), ref, bf16, "conv N=1", say=say)
 
 
+@pytest.mark.parametrize("axis", ["rows", "cols"])
+@pytest.mark.parametrize("B,H,W,Cin,Cout,N,stride,bf16", [
+    (1, 6, 10, 4, 33, 2, 1, False),      # float32: one 16-byte chunk of channels, a channel tile of one
+    (2, 10, 6, 20, 31, 2, 1, False),     # pixels and channels not multiples of the 4 x 32 tile
+    (1, 12, 12, 64, 64, 3, 2, False),
+    (1, 6, 10, 4, 8, 2, 1, True),        # four input channels: strip width not a multiple of four
+    (2, 10, 6, 320, 3, 2, 1, True),      # few outputs: pixel quads that end beyond a row
+    (1, 6, 6, 72, 8, 2, 1, True),        # one wave per pixel
+])
+def test_conv_small_kernels(B, H, W, Cin, Cout, N, stride, bf16, axis):
+    say("conv small", B, H, W, Cin, Cout, N, stride, bf16, axis)
+    full, stale, w, b = _conv_case(13, B, H, W, Cin, Cout, bf16)
+    ax = 1 if axis == "rows" else 2
+    conv = df.conv3x3_halo if ax == 1 else df.conv3x3_halo_cols
+    for i, xf in enumerate(np.split(full, N, ax)):
+        ref = ops.conv3x3_halo(xf, stale, w, b, i, N, stride, 1, split_axis=ax)
+        y = conv(dev(np.ascontiguousarray(xf), bf16), dev(stale, bf16), dev(w, bf16), dev(b), i, N, stride, 1)
+        check(host(y), ref, bf16, "conv small patch %d" % i, say=say)
+
+
 def test_conv_config3_full_size():
     t = configs.conv_gn_stage()
     m = t["meta"]
@@ -213,6 +233,16 @@ def _attn_case(seed, B, L, C, N, patch, bf16, stale_std=0.5):
     return dict(q=rnd(normal(seed, "q", (B, Lq, C))), kf=rnd(kfull[:, sl].copy()), vf=rnd(vfull[:, sl].copy()),
                 ks=rnd(kfull + normal(seed, "kn", (B, L, C), std=stale_std)),
                 vs=rnd(vfull + normal(seed, "vn", (B, L, C), std=stale_std)))
+
+
+@pytest.mark.parametrize("Lq_total,N,C,heads", [(3, 1, 32, 1), (66, 2, 64, 1), (254, 2, 64, 2), (2050, 2, 64, 2), (1026, 1, 128, 2)])
+def test_attention_f32_edges(Lq_total, N, C, heads):
+    """Fewer keys than a wave's step, ragged steps, and the form with four queries per workgroup (ragged last four)."""
+    say("attn f32", Lq_total, N, C, heads)
+    t = _attn_case(22, 1, Lq_total, C, N, N - 1, False)
+    ref = ops.attn_displaced(t["q"], t["kf"], t["vf"], t["ks"], t["vs"], heads, N - 1, N)
+    o = df.attn_displaced(*(dev(t[n]) for n in ("q", "kf", "vf", "ks", "vs")), heads, N - 1, N)
+    check(host(o), ref, False, "attn f32", say=say)
 
 
 @pytest.mark.parametrize("B,L,C,heads,N,patch,bf16", [
