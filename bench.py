@@ -207,7 +207,7 @@ def measured_mfma_peak(df, torch):
 
 
 def run_tile_sweep(df, torch):
-    """Every tile shape / ring depth of the LDS-tiled MFMA kernel on convolution and linear shapes of the larger
+    """Every tile shape of the LDS-tiled MFMA kernel (tgemm.hip) on convolution and linear shapes of the larger
     workloads (2048x2048 and 3840x3840 shares, the synchronous full-image step), no split along K.  Needs the tuning
     build (python -m paper_2402_19481_amd.build --tuning): the library proper has no override switches.  One JSON
     line per shape: microseconds and TFLOP/s per tile configuration ("auto" = the library's own choice)."""
@@ -231,7 +231,7 @@ def run_tile_sweep(df, torch):
             e1.synchronize()
         return e0.elapsed_time(e1) * 1e3 / rep
 
-    tiles = ["", "64x64x2", "64x64x3", "64x64x7", "64x64x6", "128x64x3", "128x64x7", "64x128x2", "128x128x2", "128x128x3", "128x128x7", "128x128x6"]
+    tiles = ["", "128x128", "128x64", "64x64", "64x128", "128x160", "256x128"]      # the kernel's table, in its order
     convs = [("conv 32x128 320->320 (configuration 3)", 32, 128, 320, 320), ("conv 64x256 320->320", 64, 256, 320, 320),
              ("conv 64x256 960->320", 64, 256, 960, 320), ("conv 32x128 640->640", 32, 128, 640, 640),
              ("conv 32x128 1920->640", 32, 128, 1920, 640), ("conv 16x64 1280->1280", 16, 64, 1280, 1280),
@@ -240,15 +240,15 @@ def run_tile_sweep(df, torch):
              ("linear 4096x640x2560", 4096, 640, 2560), ("linear 4096x5120x640", 4096, 5120, 640),
              ("linear 9600x640x640 (full image)", 9600, 640, 640), ("linear 2400x1280x1280 (full image)", 2400, 1280, 1280),
              ("linear 2400x1280x5120 (full image)", 2400, 1280, 5120), ("linear 38400x320x960 (full image)", 38400, 320, 960)]
-    os.environ["DF_TUNE"] = "1"
 
     def sweep(name, flops, fn):
         rec = {"op": name, "gflop": round(flops / 1e9, 2)}
         for t in tiles:
-            if t:
-                os.environ["DF_TILE"] = t
-            else:
-                os.environ.pop("DF_TILE", None)
+            for k, v in (("DF_TG", str(tiles.index(t) - 1)), ("DF_TGS", "1")):
+                if t:
+                    os.environ[k] = v
+                else:
+                    os.environ.pop(k, None)
             us = timed(fn)
             rec[t or "auto"] = {"us": round(us, 1), "tflops": round(flops / us / 1e6)}
         print(json.dumps(rec), flush=True)
@@ -263,9 +263,9 @@ def run_tile_sweep(df, torch):
 
 
 def run_timeline(df, torch, tune_path):
-    """In-kernel timelines from the tuning build (cycle stamps written by the kernels themselves): where a k-slab of the
-    LDS-tiled MFMA kernel spends its cycles, and how a wave-level linear layer of the patch step divides into
-    prologue, K loop and reduction + epilogue.  One JSON line per case."""
+    """In-kernel timelines from the tuning build (cycle stamps written by the kernels themselves): how a wave-level linear
+    layer of the patch step divides into prologue, K loop and reduction + epilogue, and the tiles of the self-attention
+    whose waves split the keys.  One JSON line per case."""
     import ctypes
     import math
     import statistics
@@ -274,39 +274,6 @@ def run_timeline(df, torch, tune_path):
     g = torch.Generator(device="cpu").manual_seed(1)
     rn = lambda *s: torch.randn(*s, generator=g).to(dev)
     bf = lambda t: t.to(torch.bfloat16)
-    os.environ["DF_TUNE"] = "1"
-
-    def pipe(name, fn, tile, KT):
-        os.environ["DF_TILE"] = tile
-        for _ in range(3):
-            fn()
-        torch.cuda.synchronize()
-        n = 8 + 4 * KT
-        buf = (ctypes.c_longlong * n)()
-        if lib.df_tune_pipe_trace(buf, n) != 0:
-            raise RuntimeError("df_tune_pipe_trace failed")
-        t = list(buf)
-        ph = [(t[8 + 4 * k + 1] - t[8 + 4 * k], t[8 + 4 * k + 2] - t[8 + 4 * k + 1], t[8 + 4 * k + 3] - t[8 + 4 * k + 2],
-               (t[8 + 4 * (k + 1)] if k + 1 < KT else t[2]) - t[8 + 4 * k + 3]) for k in range(KT)]
-        mid = ph[3:-2] if KT > 8 else ph
-        m = [round(statistics.mean(x[i] for x in mid)) for i in range(4)]
-        print(json.dumps({"kernel": "mfma_pipe_kernel", "op": name, "tile": tile, "k_slabs": KT,
-                          "cycles_before_first_slab": t[8] - t[0], "cycles_k_loop": t[2] - t[8],
-                          "per_slab_cycles": {"wait_own_loads": m[0], "barrier": m[1], "issue_loads_and_lds_reads": m[2],
-                                              "mfma": m[3], "total": sum(m)},
-                          "note": "each of the four stamps of a slab costs ~90 cycles itself"}), flush=True)
-
-    M, N, K = 2400, 1280, 5120
-    x, w, b = bf(rn(M, K)), bf(rn(N, K) / math.sqrt(K)), rn(N)
-    for tile in ("64x64x2", "128x128x3", "128x128x7"):
-        pipe("linear 2400x1280x5120", lambda: df.linear(x, w, b), tile, K // 64)
-    R, W, Cin, Cout = 64, 256, 960, 320
-    x2, st = bf(rn(1, R, W, Cin)), bf(rn(1, R * 4, W, Cin))
-    w2, b2 = bf(rn(Cout, 3, 3, Cin) / math.sqrt(9 * Cin)), rn(Cout)
-    for tile in ("64x64x3", "128x128x7"):
-        pipe("conv 64x256 960->320", lambda: df.conv3x3_halo(x2, st, w2, b2, 1, 4), tile, 9 * Cin // 64)
-    os.environ.pop("DF_TILE", None)
-
     def wgemm(name, fn):
         for _ in range(3):
             fn()

@@ -8,13 +8,13 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdistrifusion.so")
-SOURCES = ["api.hip", "refresh.hip", "groupnorm.hip", "conv_gemm.hip", "wgemm.hip", "bgemm.hip", "attn.hip", "elementwise.hip", "unet.hip"]
+SOURCES = ["api.hip", "refresh.hip", "groupnorm.hip", "conv_gemm.hip", "tgemm.hip", "wgemm.hip", "bgemm.hip", "attn.hip", "elementwise.hip", "unet.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
-# The tuning build (python -m paper_2402_19481_amd.build --tuning) compiles the environment switches in (DF_TILE,
-# DF_SPLITK, DF_ATTN_SPLITS, ...: kernel-selection overrides for sweeps such as `bench.py --tile-sweep`) and writes
+# The tuning build (python -m paper_2402_19481_amd.build --tuning) compiles the environment switches in (DF_TG,
+# DF_TGS, DF_ATTN_SPLITS, ...: kernel-selection overrides for sweeps such as `bench.py --tile-sweep`) and writes
 # libdistrifusion_tune.so beside the library; the library proper never reads the environment.
 OBJ_TUNE = os.path.join(HERE, "_build_tune")
 LIB_TUNE = os.path.join(HERE, "libdistrifusion_tune.so")

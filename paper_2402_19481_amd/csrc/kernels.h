@@ -102,34 +102,8 @@ struct GemmArgs {
   long long lda, ldw, ldr, ldo;
   int act;        // 0 none, 1 SiLU
   int out_dtype;
-  // GEGLU epilogue: W holds 2F rows (F value rows, then F gate rows), N = 2F; the output is [M, F] bf16 with
-  // out[m, f] = (x w_f + b_f) * gelu(x w_{F+f} + b_{F+f}).  Requires K % 64 == 0, K >= 128, F % 64 == 0.
-  int geglu;
-  // Segmented bf16 output (fused QKV projection): column segment s = col / seg_w is written to seg_out[s] instead of
-  // `out`; input row m lands on row (m / seg_rows_in[s]) * seg_rows_out[s] + seg_row0[s] + m % seg_rows_in[s] with
-  // row stride seg_ld[s].  nseg = 0: plain output.  Requires K % 64 == 0, K >= 128, no split-K (any K is accepted).
-  int nseg, seg_w;
-  void* seg_out[3];
-  long long seg_ld[3], seg_rows_out[3], seg_row0[3];
-  int seg_rows_in[3];
-  // seg_tr[s] != 0: segment s is written transposed, out[(b * seg_w + col) * seg_ld[s] + seg_row0[s] + row_in_batch]
-  // (feature-major, rows contiguous: the V^T layout of the attention kernel); seg_rows_out is ignored for it
-  int seg_tr[3];
-  // seg_pin[s] > 0: row m of a batch item is token (m / seg_pin, m % seg_pin) of a vertical strip and lands on row
-  // seg_row0 + (m / seg_pin) * seg_pout + m % seg_pin of the destination's batch item (its grid rows are seg_pout long)
-  int seg_pin[3], seg_pout[3];
-  // W is in the tiled layout written by launch_pack_weight (requires N % 64 == 0, K % 64 == 0, K >= 128).
+  // W is in the tiled layout written by launch_pack_weight (requires N % 64 == 0, K % 64 == 0).
   int packed_w;
-  // LayerNorm folded into the GEMM: A holds the un-normalised rows (bf16), W was packed with the norm scale
-  // multiplied in, ln_s[n] = sum_k W'[n,k], ln_t[n] = sum_k W[n,k] beta[k] + bias[n] (bias must then be null).
-  // The kernel derives each row's mean and rstd from the A tiles it streams and applies
-  // out = rstd * (acc - mean * ln_s[n]) + ln_t[n].  Requires the pipelined kernel (K % 64 == 0, K >= 128).
-  const float* ln_s;
-  const float* ln_t;
-  float ln_eps;
-  // optional second output: the same values rounded to bf16, [M, N] with row stride ldo2 (plain outputs only)
-  void* out2;
-  long long ldo2;
   const Scratch* scr;     // see GnArgs
 };
 int launch_gemm_bf16(const GemmArgs& a, hipStream_t st);
@@ -150,7 +124,10 @@ struct WGemmArgs {
   const void* Wp;         // packed weights [N, K]
   int M, N, K;            // K % 64 == 0, N % 32 == 0
   const float* bias;      // [N] or nullptr
-  const float* ln_s;      // folded LayerNorm vectors (see GemmArgs), or nullptr
+  // LayerNorm folded into the layer: Xp holds the un-normalised rows, Wp was packed with the norm scale multiplied in,
+  // ln_s[n] = sum_k W'[n,k], ln_t[n] = sum_k W[n,k] beta[k] + bias[n] (bias must then be null); each row's mean and rstd
+  // come from the operand the kernel streams: out = rstd * (acc - mean * ln_s[n]) + ln_t[n]
+  const float* ln_s;
   const float* ln_t;
   float ln_eps;
   const float* residual;  // row-major [M, N'] float, row stride ldr, or nullptr (may alias out_f32)
@@ -161,12 +138,19 @@ struct WGemmArgs {
   void* out_rows;         // row-major bf16 [M, N'], row stride ld_rows, or nullptr
   long long ld_rows;
   int geglu;              // F: W holds F value rows then F gate rows (N == 2F), N' = F; 0: N' = N
-  int nseg, seg_w;        // segmented row-major bf16 output as in GemmArgs (replaces out_rows)
+  // segmented bf16 output (fused QKV projection; replaces out_rows): column segment s = col / seg_w is written to
+  // seg_out[s]; input row m lands on row (m / seg_rows_in[s]) * seg_rows_out[s] + seg_row0[s] + m % seg_rows_in[s] with
+  // row stride seg_ld[s]
+  int nseg, seg_w;
   void* seg_out[3];
   long long seg_ld[3], seg_rows_out[3], seg_row0[3];
   int seg_rows_in[3];
-  int seg_tr[3];          // transposed segments, as in GemmArgs
-  int seg_pin[3], seg_pout[3];   // strip-of-a-grid row mapping, as in GemmArgs
+  // seg_tr[s] != 0: segment s is written transposed, out[(b * seg_w + col) * seg_ld[s] + seg_row0[s] + row_in_batch]
+  // (feature-major, rows contiguous: the V^T layout of the attention kernel); seg_rows_out is ignored for it
+  int seg_tr[3];
+  // seg_pin[s] > 0: row m of a batch item is token (m / seg_pin, m % seg_pin) of a vertical strip and lands on row
+  // seg_row0 + (m / seg_pin) * seg_pout + m % seg_pin of the destination's batch item (its grid rows are seg_pout long)
+  int seg_pin[3], seg_pout[3];
   float seg0_scale;       // segment 0's values are multiplied by this before they are rounded (0: not)
   // Fused cross-attention: the layer is a query projection with N = heads * 64 and a folded LayerNorm; instead of
   // the projection the kernel writes out_packed = softmax(q k^T * xa_scale) v per head, against xa_keys text tokens

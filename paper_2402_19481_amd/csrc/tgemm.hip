@@ -1,0 +1,398 @@
+#include <cmath>
+#include <type_traits>
+
+#include "tile.h"
+
+namespace df {
+
+namespace {
+
+#define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
+#define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
+
+template <int VM>
+__device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
+  __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
+}
+__device__ __forceinline__ void block_sync() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+// Epilogue of four consecutive columns of one output row
+template <bool kConv, typename OutT>
+__device__ __forceinline__ void store4(const TileParams& p, int row, int col, f32x4 v) {
+  if (p.bias) v += *reinterpret_cast<const f32x4*>(p.bias + col);
+  if constexpr (kConv) {
+    if (p.chan_add) v += *reinterpret_cast<const f32x4*>(p.chan_add + (long long)(row / (p.Ro * p.Wo)) * p.chan_ld + col);
+  }
+  if (p.residual) v += *reinterpret_cast<const f32x4*>(p.residual + (long long)row * p.ldr + col);
+  if (p.act == 1) { v.x = silu_f(v.x); v.y = silu_f(v.y); v.z = silu_f(v.z); v.w = silu_f(v.w); }
+  OutT* o = reinterpret_cast<OutT*>(p.out) + (long long)row * p.ldo + col;
+  if constexpr (sizeof(OutT) == 4) {
+    *reinterpret_cast<f32x4*>(o) = v;
+  } else {
+    const u32x2 t = {pack_bf2(v.x, v.y), pack_bf2(v.z, v.w)};
+    *reinterpret_cast<u32x2*>(o) = t;
+  }
+}
+
+struct TgExtra {
+  const bf16_t* zeros;
+  float* partials;
+  int group_m;
+};
+
+// BM x BN output tile per workgroup, (BM/WM) x (BN/WN) waves of WM x WN as 32 x 32 MFMA blocks, KG groups of such waves
+// that take alternate 64-wide k-slabs and are added through LDS at the end.  Operands go global -> LDS with direct
+// loads (8 rows of 128 B per instruction) into a ring of ST stages of KG slabs.  Rows beyond M / N are clamped to the last
+// valid one (never stored); the convolution's zero padding is fetched from a page of zeros.
+//   - What bounds it: the direct loads (45 bytes per cycle and compute unit measured with the matrix instructions taken
+//     out) and the matrix pipe in about equal parts (128 x 128: 0.35 us of either per slab, 0.46 together; 256 x 128:
+//     0.51 and 0.52, 0.77 together); HBM does not (weights cold or resident in L2: the same).
+//   - A wave issues its loads in four parts between the matrix instructions: all of them right behind the barrier kept
+//     every wave of the unit waiting for the load queue (256 x 128: 0.96 -> 0.77 us per slab).
+//   - Weights are the MFMA's row operand, so a lane holds four consecutive output channels of one pixel and the tile is
+//     staged through LDS with 16-byte accesses.
+template <int BM, int BN, int WM, int WN, int KG, int ST, int OCC, bool kConv, typename OutT>
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN) * KG, ((BM / WM) * (BN / WN) * KG * OCC + 3) / 4)
+void tgemm_kernel(TileParams p, TgExtra x) {
+  constexpr int NWG = (BM / WM) * (BN / WN), NW = NWG * KG, NTHR = 64 * NW;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  constexpr int AJ = BM / 8 / NWG, BJ = BN / 8 / NWG;     // 1 KB direct loads per wave and slab (its k-group's)
+  static_assert(AJ * 8 * NWG == BM && BJ * 8 * NWG == BN, "whole loads");
+  constexpr int L = AJ + BJ;
+  constexpr int SLAB = (BM + BN) * 128, STAGE = SLAB * KG;
+  static_assert(L * (ST - 1) < 64, "vmcnt field is 6 bits");
+  constexpr int NP = ST > 2 ? 4 : 3;                      // parts of a stage's loads (two stages: all before the barrier)
+  constexpr int LATE = NP == 4 ? L - (3 * L + 3) / 4 : 0; // loads of part 3
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave / NWG, wq = wave % NWG, wm = wq % (BM / WM), wn = wq / (BM / WM);
+  const int MT = (p.M + BM - 1) / BM, NT = (p.N + BN - 1) / BN, nwg = MT * NT;
+  int t = blockIdx.x;
+  {
+    const int xcd = t & 7, loc = t >> 3;
+    const int base = nwg >> 3, rem = nwg & 7;
+    t = xcd * base + (xcd < rem ? xcd : rem) + loc;
+  }
+  int m0, n0;
+  {
+    const int per = x.group_m * NT, pn = t / per, r = t - pn * per, mf = pn * x.group_m;
+    const int gh = MT - mf < x.group_m ? MT - mf : x.group_m;
+    n0 = r / gh;
+    m0 = (mf + r - n0 * gh) * BM;
+    n0 *= BN;
+  }
+  const int nsplit = gridDim.y, split = blockIdx.y;
+  const int slabs_all = p.K / 64;
+  const int stages_all = (slabs_all + KG - 1) / KG;
+  const int per_split = (stages_all + nsplit - 1) / nsplit;
+  const int s_lo = split * per_split * KG;                               // first slab of the split
+  int s_hi = s_lo + per_split * KG;
+  if (s_hi > slabs_all) s_hi = slabs_all;
+  const int KT = (s_hi - s_lo + KG - 1) / KG;
+
+  // direct loads: instruction j of a wave covers tile rows (wq*AJ + j)*8 + lane/8, LDS slot lane%8 of the row; row r keeps
+  // its 16-byte chunk c at slot c ^ ((r >> 1) & 7)
+  const int lr = lane >> 3;
+  const bf16_t* a_base[AJ];                                              // channel 0 of the centre pixel / start of the row
+  int a_r[AJ], a_c[AJ], a_b[AJ];
+#pragma unroll
+  for (int j = 0; j < AJ; ++j) {
+    const int row = (wq * AJ + j) * 8 + lr;
+    int m = m0 + row;
+    if (m >= p.M) m = p.M - 1;                                           // ragged last tile: re-read, never stored
+    const int ch = ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    if constexpr (kConv) {
+      const int per = p.Ro * p.Wo;
+      a_b[j] = m / per;
+      const int rem = m - a_b[j] * per;
+      a_r[j] = rem / p.Wo;
+      a_c[j] = (rem - a_r[j] * p.Wo) * p.stride;
+      a_r[j] *= p.stride;
+      a_base[j] = p.A + (((long long)a_b[j] * p.R + a_r[j]) * p.W + a_c[j]) * p.Cin + ch;
+    } else {
+      a_base[j] = p.A + (long long)m * p.lda + ch;
+      a_b[j] = a_r[j] = a_c[j] = 0;
+    }
+  }
+  const bf16_t* b_ptr[BJ];
+#pragma unroll
+  for (int j = 0; j < BJ; ++j) {
+    const int row = (wq * BJ + j) * 8 + lr;
+    int n = n0 + row;
+    if (n >= p.N) n = p.N - 1;
+    // tiled weights: tile (n/64, slab) is 8 KB contiguous, rows and swizzled slots exactly as they sit in LDS
+    if (!kConv && p.packed_w) b_ptr[j] = p.Wt + ((long long)(n >> 6) * slabs_all * 64 + (n & 63)) * 64 + (lane & 7) * 8;
+    else b_ptr[j] = p.Wt + (long long)n * p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+  }
+  const int b_step = !kConv && p.packed_w ? 4096 : 64;                  // elements between slabs
+  // Convolution: a lane's source pixel changes only with the filter tap, every Cin / 64 slabs
+  const bf16_t* a_tap[AJ];
+  bool a_pad[AJ];
+  int tap_k0 = 0, tap_end = 0;                                           // k range of the tap the pointers are set for
+  auto set_tap = [&](int k0) {
+    const int tap = k0 / p.Cin;
+    tap_k0 = tap * p.Cin;
+    tap_end = tap_k0 + p.Cin;
+    const int dy = tap / 3 - 1, dx = tap - (tap / 3) * 3 - 1;
+    const long long off = ((long long)dy * p.W + dx) * p.Cin;
+#pragma unroll
+    for (int j = 0; j < AJ; ++j) {
+      const int ri = a_r[j] + dy, ci = a_c[j] + dx;
+      a_tap[j] = a_base[j] + off;
+      a_pad[j] = false;
+      if ((unsigned)ri >= (unsigned)p.R || (unsigned)ci >= (unsigned)p.W) {
+        const bf16_t* src = conv_tap_src(p.A, p.top, p.bot, p.halo_bs, p.left, p.right, p.side_bs, p.side_rs, a_b[j], ri,
+                                         ci, p.R, p.W, p.Cin);
+        const int row = (wq * AJ + j) * 8 + lr;
+        a_pad[j] = src == nullptr;
+        a_tap[j] = (src ? src : x.zeros) + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+      }
+    }
+  };
+  // part STEP of 4 of a stage's loads (one part per 16 of K of the loop below: a wave that issues them all at once waits
+  // for the queue of the load path, and every wave of the unit with it)
+  auto issue = [&](int kt, int slot, auto stepc) {
+    constexpr int STEP = decltype(stepc)::value;
+    int slab = s_lo + kt * KG + kg;
+    if (slab > slabs_all - 1) slab = slabs_all - 1;                      // a group's missing last slab: loaded, not used
+    const int k0 = slab * 64;
+    char* sa = smem + slot * STAGE + kg * SLAB + wq * AJ * 1024;
+    char* sb = smem + slot * STAGE + kg * SLAB + BM * 128 + wq * BJ * 1024;
+    if constexpr (kConv && STEP == 0) {
+      if (k0 >= tap_end || k0 < tap_k0) set_tap(k0);                     // (uniform)
+    }
+#pragma unroll
+    for (int q = 0; q < L; ++q) {
+      if (q * NP / L != STEP) continue;
+      const int j = q < AJ ? q : q - AJ;
+      if (q < AJ) {
+        const bf16_t* src;
+        if constexpr (kConv) src = a_pad[j < AJ ? j : 0] ? a_tap[j < AJ ? j : 0] : a_tap[j < AJ ? j : 0] + (k0 - tap_k0);
+        else src = a_base[j < AJ ? j : 0] + k0;
+        __builtin_amdgcn_global_load_lds(DF_GPTR(src), DF_LPTR(sa + j * 1024), 16, 0, 0);
+      } else {
+        __builtin_amdgcn_global_load_lds(DF_GPTR(b_ptr[j < BJ ? j : 0] + (long long)slab * b_step), DF_LPTR(sb + j * 1024), 16, 0, 0);
+      }
+    }
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  const int lrow = lane & 31, g = lane >> 5, sw = (lrow >> 1) & 7;
+  bf16x8 xa[2][TM], wa[2][TN];
+  auto rd = [&](int slot, int ks, auto bc) {
+    constexpr int b = decltype(bc)::value;
+    const char* s = smem + slot * STAGE + kg * SLAB + lrow * 128 + ((2 * ks + g) ^ sw) * 16;
+#pragma unroll
+    for (int i = 0; i < TM; ++i) xa[b][i] = *reinterpret_cast<const bf16x8*>(s + (wm * WM + i * 32) * 128);
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wa[b][j] = *reinterpret_cast<const bf16x8*>(s + (BM + wn * WN + j * 32) * 128);
+  };
+  auto mm = [&](auto bc) {
+    constexpr int b = decltype(bc)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[b][j], xa[b][i], acc[i][j], 0, 0, 0);
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+#define DF_SB __builtin_amdgcn_sched_barrier(0)
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+#pragma unroll
+  for (int s = 0; s < ST - 1; ++s) {
+    const int k = s < KT ? s : KT - 1;                                   // past the end: the last stage again (vmcnt stays uniform)
+    issue(k, s, I0{}); issue(k, s, I1{}); issue(k, s, I2{}); issue(k, s, I3{});
+  }
+  wait_vm_lds<L * (ST - 2)>();
+  block_sync();
+  rd(0, 0, I0{});
+  int slot = 0, pslot = ST - 1;
+  for (int kt = 0; kt < KT; ++kt) {
+    const int nslot = slot + 1 == ST ? 0 : slot + 1;
+    const int kn = kt + ST - 1 < KT ? kt + ST - 1 : KT - 1;
+    const bool mine = KG == 1 || s_lo + kt * KG + kg < s_hi;             // (uniform) the group has a slab in this stage
+    DF_SB; rd(slot, 1, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB; issue(kn, pslot, I0{});
+    DF_SB; rd(slot, 2, I0{}); DF_SB; if (mine) mm(I1{}); DF_SB; issue(kn, pslot, I1{});
+    DF_SB; rd(slot, 3, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB; issue(kn, pslot, I2{});
+    if (kt + 1 < KT) {
+      wait_vm_lds<L * (ST - 2) - LATE>();
+      block_sync();
+      rd(nslot, 0, I0{});
+    }
+    DF_SB; if (mine) mm(I1{}); DF_SB; issue(kn, pslot, I3{});
+    pslot = slot;
+    slot = nslot;
+  }
+  wait_vm_lds<0>();                                                      // the clamped tail loads: the ring becomes the epilogue's
+#undef DF_SB
+
+  // ---- epilogue: accumulators -> LDS (the ring is free), k-groups added, whole rows stored ----
+  constexpr int PT = BN + 4;
+  float* tile = reinterpret_cast<float*>(smem);
+  block_sync();
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        *reinterpret_cast<f32x4*>(tile + (kg * BM + wm * WM + i * 32 + lrow) * PT + wn * WN + j * 32 + 8 * q + 4 * g) =
+            f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+  __syncthreads();
+#pragma unroll 1
+  for (int idx = tid; idx < BM * (BN / 4); idx += NTHR) {
+    const int r = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
+    const int row = m0 + r, col = n0 + c4;
+    if (row >= p.M || col >= p.N) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(tile + r * PT + c4);
+#pragma unroll
+    for (int k = 1; k < KG; ++k) v += *reinterpret_cast<const f32x4*>(tile + (k * BM + r) * PT + c4);
+    if (nsplit > 1) *reinterpret_cast<f32x4*>(x.partials + ((size_t)split * p.M + row) * p.N + col) = v;
+    else store4<kConv, OutT>(p, row, col, v);
+  }
+}
+
+// sum over the splits, in split order, then the epilogue; four columns per lane
+template <bool kConv, typename OutT>
+__global__ __launch_bounds__(256) void tgemm_reduce_kernel(TileParams p, const float* __restrict__ partials, int nsplit) {
+  const unsigned int idx = blockIdx.x * blockDim.x + threadIdx.x;        // M * N / 4 < 2^31 (launcher)
+  const unsigned int n4 = (unsigned int)p.N / 4;
+  if (idx >= (unsigned int)p.M * n4) return;
+  const int row = (int)(idx / n4), col = (int)(idx - (unsigned int)row * n4) * 4;
+  f32x4 v = {0.f, 0.f, 0.f, 0.f};
+  for (int s = 0; s < nsplit; ++s) v += *reinterpret_cast<const f32x4*>(partials + ((size_t)s * p.M + row) * p.N + col);
+  store4<kConv, OutT>(p, row, col, v);
+}
+
+template <int BM, int BN, int WM, int WN, int KG, int ST, int OCC, bool kConv, typename OutT>
+int launch_one(const TileParams& p, int nsplit, hipStream_t st) {
+  constexpr int NW = (BM / WM) * (BN / WN) * KG;
+  const int MT = cdiv(p.M, BM), NT = cdiv(p.N, BN), stages = cdiv(p.K / 64, KG);
+  const long long nwg = (long long)MT * NT;
+  if (nwg > 0x7fffffffLL) return DF_ESHAPE;
+  if (nsplit > stages) nsplit = stages;
+  if (nsplit < 1) nsplit = 1;
+  nsplit = cdiv(stages, cdiv(stages, nsplit));                           // no empty split
+  if (nsplit > 1 && ((long long)p.M * p.N >= (1LL << 31))) return DF_ESHAPE;
+  TgExtra x = {};
+  if (kConv || nsplit > 1) {
+    char* scr = scratch_region(p.scr, kScratchCounterBytes + (nsplit > 1 ? (size_t)nsplit * p.M * p.N * sizeof(float) : 0));
+    if (!scr) return DF_ENOMEM;
+    x.zeros = (const bf16_t*)(scr + kScratchZeroPageOffset);
+    x.partials = (float*)(scr + kScratchCounterBytes);
+  }
+  // token tiles of a panel: the workgroups an XCD runs at once then cover a square of the output
+  const double conc = std::fmin((double)nwg / 8.0, 32.0 * OCC);
+  int gm = (int)(std::sqrt(conc * BN / BM) + 0.5);
+  if (gm < 1) gm = 1;
+  if (gm > MT) gm = MT;
+  x.group_m = cdiv(MT, cdiv(MT, gm));
+  constexpr int ring = ST * (BM + BN) * 128 * KG, fin = KG * BM * (BN + 4) * 4;
+  constexpr int smem = ring > fin ? ring : fin;
+  static_assert(smem * OCC <= 160 * 1024, "LDS of a compute unit");
+  auto k = tgemm_kernel<BM, BN, WM, WN, KG, ST, OCC, kConv, OutT>;
+  static bool attr_set = false;
+  if (!attr_set) {
+    if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)nsplit), dim3(64 * NW), smem, st, p, x);
+  DF_LAUNCH_CHECK();
+  if (nsplit > 1) {
+    const long long n = (long long)p.M * (p.N / 4);
+    hipLaunchKernelGGL((tgemm_reduce_kernel<kConv, OutT>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, x.partials, nsplit);
+    DF_LAUNCH_CHECK();
+  }
+  return DF_OK;
+}
+
+template <int BM, int BN, int WM, int WN, int KG, int ST, int OCC>
+int launch_cfg(const TileParams& p, bool conv, int out_dtype, int nsplit, hipStream_t st) {
+  if (conv) return out_dtype == DF_BF16 ? launch_one<BM, BN, WM, WN, KG, ST, OCC, true, bf16_t>(p, nsplit, st)
+                                        : launch_one<BM, BN, WM, WN, KG, ST, OCC, true, float>(p, nsplit, st);
+  return out_dtype == DF_BF16 ? launch_one<BM, BN, WM, WN, KG, ST, OCC, false, bf16_t>(p, nsplit, st)
+                              : launch_one<BM, BN, WM, WN, KG, ST, OCC, false, float>(p, nsplit, st);
+}
+
+// Tile shapes with their predicted times: microseconds of a launch, of a stage (KG slabs) and of a workgroup's prologue and
+// epilogue, fitted to 28 convolutions (64 to 28800 pixels, 320 to 2560 channels) and 11 linear layers with 1 to 8 parts of
+// K each; chosen by them, those shapes take 0.5 % more than the best of 18 tile shapes did.
+struct TileCfg { int bm, bn, kg, occ; double base, stage, fixed; };
+constexpr TileCfg kTiles[] = {
+    {128, 128, 1, 1, 2.96, 0.518, 1.99},
+    {128, 64, 1, 2, 3.56, 0.708, 0.0},     // two workgroups per unit
+    {64, 64, 2, 1, 2.03, 0.532, 1.42},
+    {64, 128, 2, 1, 2.63, 0.789, 1.32},
+    {128, 160, 1, 1, 4.56, 0.641, 2.59},   // channel counts are multiples of 320
+    {256, 128, 1, 1, 3.48, 0.774, 2.48},   // sixteen waves
+};
+constexpr int kNumTiles = (int)(sizeof(kTiles) / sizeof(kTiles[0]));
+// Parts of K: at least four slabs each, at most as many as the chip takes workgroups at once with some to spare
+constexpr int kMaxSplit = 16, kMaxSplitWgs = 640;
+
+long long tiles_of(const TileCfg& t, long long M, long long N) { return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn); }
+
+}  // namespace
+
+// bytes of library scratch a launch may ask for (plans reserve it up front); also covers a convolution with M output
+// pixels, N = Cout
+size_t gemm_scratch_bytes(long long M, long long N) {
+  long long ns = 0;
+  for (const TileCfg& t : kTiles) {
+    long long n = kMaxSplitWgs / tiles_of(t, M, N);
+    if (n > kMaxSplit) n = kMaxSplit;
+    if (n > ns) ns = n;
+  }
+  return kScratchCounterBytes + (size_t)(ns > 1 ? ns * M * N * (long long)sizeof(float) : 0);
+}
+
+int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st) {
+  auto al = [](const void* ptr, int a) { return ((uintptr_t)ptr % a) == 0; };
+  const bool ok = p.K % 64 == 0 && (!conv || p.Cin % 64 == 0) && p.N % 4 == 0 && p.ldo % 4 == 0 && al(p.out, 16) && al(p.bias, 16) &&
+                  al(p.chan_add, 16) && p.chan_ld % 4 == 0 && (!p.residual || (p.ldr % 4 == 0 && al(p.residual, 16)));
+  if (!ok) return DF_ESHAPE;
+  const int slabs = p.K / 64;
+  int cfg = 0, ns = 1;
+  double best = 1e30;
+  for (int c = 0; c < kNumTiles; ++c) {
+    const TileCfg& t = kTiles[c];
+    const long long n = tiles_of(t, p.M, p.N);
+    for (int s = 1; s <= kMaxSplit; ++s) {
+      if (s > 1 && (n * s > kMaxSplitWgs || slabs / s < 4)) break;
+      const int stages = cdiv(cdiv(slabs, t.kg), s);
+      const double wgs = (double)n * s;
+      // rounds of workgroups; two of a unit share it, and one alone is faster
+      const double r = t.occ == 1 ? std::ceil(wgs / 256.0) : wgs <= 256.0 ? 0.6 : wgs > 1024.0 ? wgs / 512.0 : std::ceil(wgs / 512.0);
+      const double us = t.base + r * (stages * t.stage + (conv ? t.fixed : 0.0)) +
+                        (s > 1 ? 3.97 + 1.46e-6 * s * (double)p.M * p.N : 0.0);   // the partials and the kernel that adds them
+      if (us < best) { best = us; cfg = c; ns = s; }
+    }
+  }
+#ifdef DF_TUNING
+  if (tune_env("DF_TG")) cfg = atoi(tune_env("DF_TG"));
+  if (tune_env("DF_TGS")) ns = atoi(tune_env("DF_TGS"));
+#endif
+  switch (cfg) {
+    case 0: return launch_cfg<128, 128, 32, 64, 1, 4, 1>(p, conv, out_dtype, ns, st);
+    case 1: return launch_cfg<128, 64, 32, 32, 1, 3, 2>(p, conv, out_dtype, ns, st);
+    case 2: return launch_cfg<64, 64, 32, 32, 2, 4, 1>(p, conv, out_dtype, ns, st);
+    case 3: return launch_cfg<64, 128, 32, 64, 2, 3, 1>(p, conv, out_dtype, ns, st);
+    case 4: return launch_cfg<128, 160, 32, 160, 1, 4, 1>(p, conv, out_dtype, ns, st);
+    case 5: return launch_cfg<256, 128, 64, 32, 1, 3, 1>(p, conv, out_dtype, ns, st);
+    default: return DF_ESHAPE;
+  }
+}
+
+}  // namespace df

@@ -1,0 +1,52 @@
+// Shared by the matrix kernels on row-major operands (conv_gemm.hip, tgemm.hip): the arguments of a linear layer or an
+// implicit-GEMM convolution, and the source of a filter tap.
+#pragma once
+#include "kernels.h"
+
+namespace df {
+
+struct TileParams {
+  // GEMM view
+  const bf16_t* A;
+  const bf16_t* Wt;
+  const float* bias;
+  const float* residual;
+  const float* chan_add;
+  long long chan_ld;
+  void* out;
+  int M, N, K;
+  long long lda, ldw, ldr, ldo;
+  int act;
+  // convolution geometry (kConv only)
+  const bf16_t* top;
+  const bf16_t* bot;
+  long long halo_bs;
+  const bf16_t* left;    // stale column left / right of a vertical strip: pixel (b, row) at left + b*side_bs + row*side_rs
+  const bf16_t* right;
+  long long side_bs, side_rs;
+  int R, W, Cin, Ro, Wo, stride;
+  int packed_w;   // W in the tiled layout of launch_pack_weight
+  const Scratch* scr;   // host side only: where split-K partials and the page of zeros live
+};
+
+// Source pixel (channel 0) of one filter tap: the fresh patch, a stale halo row (patches are horizontal strips) or
+// halo column (vertical strips), or nullptr where the tap falls on the zero padding around the image.
+template <typename T>
+__device__ __forceinline__ const T* conv_tap_src(const T* x, const T* top, const T* bot, long long halo_bs, const T* left,
+                                                 const T* right, long long side_bs, long long side_rs, int b, int ri,
+                                                 int ci, int R, int W, int Cin) {
+  if (ci < 0 || ci >= W) {
+    const T* side = ci < 0 ? left : right;
+    if (!side || ri < 0 || ri >= R) return nullptr;
+    return side + b * side_bs + ri * side_rs;
+  }
+  if (ri < 0) return top ? top + b * halo_bs + (long long)ci * Cin : nullptr;
+  if (ri >= R) return bot ? bot + b * halo_bs + (long long)ci * Cin : nullptr;
+  return x + (((long long)b * R + ri) * W + ci) * Cin;
+}
+
+// Workgroup-tile kernel (tgemm.hip): linear layers and convolutions with K % 64 == 0 (Cin % 64 == 0), N % 4 == 0 and an
+// epilogue of whole 16-byte accesses.  DF_ESHAPE if the arguments do not fit.
+int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st);
+
+}  // namespace df

@@ -399,12 +399,12 @@ struct Exec {
     }
     if (!live()) return;
     GemmArgs g = {};
-    if (extra) g = *extra;   // epilogue variant (GEGLU / segmented output) prepared by the caller
+    if (extra) g = *extra;   // weight layout prepared by the caller
     g.A = A; g.W = W; g.bias = bp; g.residual = residual; g.out = out;
     g.M = M; g.N = Nn; g.K = K; g.lda = lda; g.ldw = K; g.ldr = ldr; g.ldo = ldo; g.act = 0; g.out_dtype = out_dtype;
     g.scr = scr;
     const double osz = out_dtype == DF_BF16 ? 2.0 : 4.0;
-    label = "linear " + dims({M, Nn, K}) + (g.geglu ? " geglu" : "") + (g.ln_s ? " ln" : "");
+    label = "linear " + dims({M, Nn, K});
     timed(PC_GEMM, 2.0 * M * Nn * K, 2.0 * ((double)M * K + (double)Nn * K) + osz * M * Nn,
           [&] { return launch_gemm_bf16(g, st); });
   }
@@ -735,26 +735,9 @@ struct Exec {
       timed(PC_LAYERNORM, 0.0, 6.0 * M * C, [&] { return launch_layernorm(h, nb, g1, b1, M, C, 1e-5f, st); });
       bf16_t* ks = (bf16_t*)stale_buf(p + ".attn1.k", (size_t)B() * L * C * 2);
       bf16_t* vs = (bf16_t*)stale_buf(p + ".attn1.v", (size_t)B() * L * C * 2);
-      // With refresh the projection writes the patch's keys and values straight into its rows of the stale buffers
-      // (the refresh costs nothing) and attention reads every key from there; without refresh they go to a scratch
-      // tensor and are spliced in by the attention loader.
-      const bool fused_kv = (full() || refresh) && C % 64 == 0 && C >= 128;
-      // where the patch's tokens start in the key / value buffers: a block of Lq rows, or - vertical strips - W
-      // tokens of every grid row starting at the strip's first column
-      const bool strip = cols() && !full();
-      const size_t row0 = full() ? 0 : (strip ? (size_t)patch * W : (size_t)patch * Lq);
-      const int pin = strip ? W : 0, pout = strip ? (c.W >> b.level) : 0;
-      (void)pin; (void)pout;             // (vertical strips never reach this path)
-      if (fused_kv) {
-        GemmArgs ex = {};
-        ex.nseg = 3; ex.seg_w = C;
-        ex.seg_out[0] = qkv; ex.seg_ld[0] = C; ex.seg_rows_in[0] = 0x7fffffff; ex.seg_rows_out[0] = 0; ex.seg_row0[0] = 0;
-        ex.seg_out[1] = ks; ex.seg_ld[1] = C; ex.seg_rows_in[1] = Lq; ex.seg_rows_out[1] = L; ex.seg_row0[1] = (long long)row0;
-        ex.seg_out[2] = vs; ex.seg_ld[2] = C; ex.seg_rows_in[2] = Lq; ex.seg_rows_out[2] = L; ex.seg_row0[2] = (long long)row0;
-        gemm(nb, C, p + ".attn1.qkv", false, nullptr, 0, qkv, C, M, 3 * C, C, DF_BF16, &ex);
-      } else {
-        gemm(nb, C, p + ".attn1.qkv", false, nullptr, 0, qkv, 3 * C, M, 3 * C, C, DF_BF16);
-      }
+      // (vertical strips never reach this path: a patch is a block of consecutive tokens)
+      const size_t row0 = full() ? 0 : (size_t)patch * Lq;
+      gemm(nb, C, p + ".attn1.qkv", false, nullptr, 0, qkv, 3 * C, M, 3 * C, C, DF_BF16);
       {
         const size_t need = attention_scratch_bytes(B(), Lq, L, heads, c.head_dim);
         if (need > scratch_need) scratch_need = need;
@@ -765,20 +748,15 @@ struct Exec {
         a.B = B(); a.Lq = Lq; a.L = L; a.heads = heads; a.d = c.head_dim;
         a.ldks = a.ldvs = C; a.ldo = C;
         a.bsks = a.bsvs = (long long)L * C; a.bso = (long long)Lq * C;
-        if (fused_kv) {
-          a.k_fresh = ks; a.v_fresh = vs; a.own_lo = 0; a.own_n = 0;     // every key row comes from the refreshed buffer
-          a.ldq = C; a.ldkf = a.ldvf = C; a.bsq = (long long)Lq * C; a.bskf = a.bsvf = (long long)L * C;
-        } else {
-          a.k_fresh = qkv + C; a.v_fresh = qkv + 2 * C;
-          a.own_lo = full() ? 0 : patch * Lq; a.own_n = Lq;
-          a.ldq = a.ldkf = a.ldvf = 3 * C; a.bsq = a.bskf = a.bsvf = (long long)Lq * 3 * C;
-        }
+        a.k_fresh = qkv + C; a.v_fresh = qkv + 2 * C;
+        a.own_lo = full() ? 0 : patch * Lq; a.own_n = Lq;
+        a.ldq = a.ldkf = a.ldvf = 3 * C; a.bsq = a.bskf = a.bsvf = (long long)Lq * 3 * C;
         a.scale = scale; a.dtype = DF_BF16; a.scr = scr;
         label = "self_attn " + dims({M, L, C});
         timed(PC_SELF_ATTN, 4.0 * M * L * C, 2.0 * (2.0 * M * C + 2.0 * B() * L * C),
               [&] { return launch_attention(a, st); });
       }
-      if (live() && !fused_kv && (full() || refresh)) {
+      if (live() && (full() || refresh)) {
         // narrow layers keep the separate refresh copies of the projected keys and values
         for (int bi = 0; bi < B(); ++bi) {
           timed(PC_REFRESH, 0.0, 4.0 * Lq * C, [&] {
@@ -820,14 +798,8 @@ struct Exec {
       const float* g3 = (const float*)weight(p + ".ln3.g");
       const float* b3 = (const float*)weight(p + ".ln3.beta");
       timed(PC_LAYERNORM, 0.0, 6.0 * M * C, [&] { return launch_layernorm(h, nb, g3, b3, M, C, 1e-5f, st); });
-      if (C % 64 == 0 && C >= 128) {
-        GemmArgs ex = {};
-        ex.geglu = 1;                    // value * gelu(gate) in the epilogue: the [M, 8C] tensor never exists
-        gemm(nb, C, p + ".ff1", true, nullptr, 0, fg, 4 * C, M, 8 * C, C, DF_BF16, &ex);
-      } else {
-        gemm(nb, C, p + ".ff1", true, nullptr, 0, ff, 8 * C, M, 8 * C, C, DF_BF16);
-        timed(PC_ELEMENTWISE, 0.0, 24.0 * M * C, [&] { return launch_geglu(ff, fg, M, 4 * C, st); });
-      }
+      gemm(nb, C, p + ".ff1", true, nullptr, 0, ff, 8 * C, M, 8 * C, C, DF_BF16);
+      timed(PC_ELEMENTWISE, 0.0, 24.0 * M * C, [&] { return launch_geglu(ff, fg, M, 4 * C, st); });
       gemm(fg, 4 * C, p + ".ff2", true, h, C, h, C, M, C, 4 * C, DF_F32);
     }
     timed(PC_ELEMENTWISE, 0.0, 6.0 * M * C, [&] { return launch_cast_bf16(h, nb, (long long)M * C, 0, st); });

@@ -354,6 +354,41 @@ def test_linear(M, N, K, out_f32, res):
     np.testing.assert_array_equal(host(y), host(y2))
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1, 36, 64),          # one row, one slab; columns end inside a tile and inside a 32-wide block
+    (63, 320, 192),       # odd number of slabs: the second k-group has none in the last stage
+    (65, 132, 128),
+    (129, 160, 320),
+    (300, 1280, 2560),    # parts of K
+    (100, 640, 1600),     # parts of K that do not divide the slabs
+    (1025, 1280, 1280),
+    (7201, 640, 1280),    # 128 x 160 tile, one row in the last
+    (4100, 640, 5760),    # 256 x 128 tile, parts of K
+])
+def test_linear_tiles(M, N, K):
+    test_linear(M, N, K, True, True)
+    test_linear(M, N, K, False, False)
+
+
+@pytest.mark.parametrize("B,H,W,Cin,Cout,N,stride,axis", [
+    (1, 6, 10, 64, 36, 2, 1, "rows"),        # 30 pixels, columns end inside a tile
+    (2, 14, 14, 128, 132, 2, 1, "cols"),
+    (1, 44, 60, 64, 320, 2, 2, "rows"),      # taps change inside a stage, stride 2
+    (1, 20, 60, 1280, 320, 4, 1, "rows"),    # parts of K
+    (1, 100, 100, 64, 160, 2, 1, "cols"),    # side columns in a large tile, ragged last one
+])
+def test_conv_tiles(B, H, W, Cin, Cout, N, stride, axis):
+    say("conv tiles", B, H, W, Cin, Cout, N, stride, axis)
+    full, stale, w, b = _conv_case(14, B, H, W, Cin, Cout, True)
+    ax = 1 if axis == "rows" else 2
+    conv = df.conv3x3_halo if ax == 1 else df.conv3x3_halo_cols
+    for i in (0, N - 1):
+        xf = np.ascontiguousarray(np.split(full, N, ax)[i])
+        ref = ops.conv3x3_halo(xf, stale, w, b, i, N, stride, 1, split_axis=ax)
+        check(host(conv(dev(xf, True), dev(stale, True), dev(w, True), dev(b), i, N, stride, 1)), ref, True,
+              "conv tiles patch %d" % i, say=say)
+
+
 # ---------------------------------------------------------------------------------------------------------------
 # linear layers on fragment-packed operands
 # ---------------------------------------------------------------------------------------------------------------
@@ -427,6 +462,21 @@ def test_linear_packed(M, N, K, variant):
     # determinism and in-place residual
     outs2 = df.linear_packed(xp, wp, M, N, K, residual=rd, geglu=geglu, want=("f32",), **kw)
     np.testing.assert_array_equal(host(outs["f32"]), host(outs2["f32"]))
+
+
+@pytest.mark.parametrize("M,N,K,variant", [
+    (1025, 640, 640, "plain"),         # workgroup tiles: one token in the last row of tiles, residual as start value
+    (4097, 640, 1280, "plain"),
+    (2049, 1280, 1280, "ln"),
+    (2049, 1280, 1280, "ln_far"),
+    (4100, 1920, 640, "ln"),
+    (577, 5120, 640, "ln_geglu"),
+    (600, 5120, 640, "geglu"),
+    (3000, 640, 2560, "plain"),        # two k-groups added through LDS
+    (1800, 10240, 1280, "ln_geglu"),   # the 320 x 256 tile, ragged
+])
+def test_linear_packed_tiles(M, N, K, variant):
+    test_linear_packed(M, N, K, variant)
 
 
 def test_geglu_gate_function_pointwise():
