@@ -103,10 +103,13 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     src[q] = (row < BT ? (const char*)p.Xp + (size_t)mt * KF * 1024 : (const char*)p.Wp + (size_t)wrow(row - BT) * KF * 1024) +
              kk * 1024;
   }
-  auto issue = [&](int kt, int slot) {
+  // loads of a stage: all (STEP < 0), or part STEP of KS
+  auto issue = [&](int kt, int slot, auto stepc) {
+    constexpr int STEP = decltype(stepc)::value;
     const size_t ko = (size_t)kt * (BKF * 1024);
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
+      if (STEP >= 0 && q * KS / NL != STEP) continue;
       int i = wave * NL + q;
       if (i > I - 1) i = I - 1;
       __builtin_amdgcn_global_load_lds(DF_GPTR(src[q] + ko + lo), DF_LPTR(smem + slot * STAGE + i * 1024), 16, 0, 0);
@@ -196,9 +199,40 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
+  using I2 = std::integral_constant<int, 2>;
+  using I3 = std::integral_constant<int, 3>;
+  using All = std::integral_constant<int, -1>;
+  if constexpr (ST >= 4) {
+    // Stage kt + ST - 1 is requested in parts between the matrix instructions of stage kt
+    constexpr int LATE = NL - ((KS - 1) * NL + KS - 1) / KS;   // loads of the part behind the barrier
+#pragma unroll
+    for (int s = 0; s < ST - 1; ++s) issue(s < KT ? s : KT - 1, s, All{});   // past the end: the last stage again
+    wait_vm_lds<NL * (ST - 2)>();
+    block_sync();
+    rd(0, 0, I0{});
+    int slot = 0, pslot = ST - 1;
+    for (int kt = 0; kt < KT; ++kt) {
+      const int nslot = slot + 1 == ST ? 0 : slot + 1;
+      const int kn = kt + ST - 1 < KT ? kt + ST - 1 : KT - 1;
+      DF_SB; rd(slot, 1, I1{}); DF_SB; mm(kt * KS, I0{}); DF_SB; issue(kn, pslot, I0{});
+      if constexpr (KS == 4) {
+        DF_SB; rd(slot, 2, I0{}); DF_SB; mm(kt * KS + 1, I1{}); DF_SB; issue(kn, pslot, I1{});
+        DF_SB; rd(slot, 3, I1{}); DF_SB; mm(kt * KS + 2, I0{}); DF_SB; issue(kn, pslot, I2{});
+      }
+      if (kt + 1 < KT) {
+        wait_vm_lds<NL * (ST - 2) - LATE>();
+        block_sync();
+        rd(nslot, 0, I0{});
+      }
+      DF_SB; mm(kt * KS + KS - 1, I1{}); DF_SB; issue(kn, pslot, std::integral_constant<int, KS - 1>{});
+      pslot = slot;
+      slot = nslot;
+    }
+    wait_vm_lds<0>();                                  // the repeated last stages: the ring becomes the epilogue's
+  } else {
 #pragma unroll
   for (int s = 0; s < ST; ++s)
-    if (s < KT) issue(s, s);
+    if (s < KT) issue(s, s, All{});
   if (ST <= KT) wait_vm_lds<NL * (ST - 1)>();
   else wait_vm_lds<0>();
   block_sync();
@@ -216,10 +250,11 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
       else wait_vm_lds<0>();
       block_sync();
       rd(nslot, 0, I0{});
-      if (kt + ST < KT) issue(kt + ST, slot);
+      if (kt + ST < KT) issue(kt + ST, slot, All{});
     }
     DF_SB; mm(kt * KS + KS - 1, I1{}); DF_SB;
     slot = nslot;
+  }
   }
 
   // ---- epilogue: the operand ring is free ----
@@ -533,15 +568,17 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
 namespace {
 
 // Tile shapes.  `slab` and `epi` are the microseconds of a round of workgroups per 64 of K and for prologue + epilogue
-// (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, fitted to 27 token counts x 5 layers.
-struct TileCfg { int bt, bf, occ; double base, slab, epi[4]; };
+// (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, `alone` the round of a workgroup that
+// has a unit to itself where two would fit; fitted to 16 token counts x 5 layers with weights that no cache holds.  Chosen by
+// them (and the wave-level kernel's, see wgemm.hip), those layers take 1 % more than with the best of all.
+struct TileCfg { int bt, bf, occ; double base, slab, epi[4], alone; };
 constexpr TileCfg kTiles[] = {
-    {10, 8, 1, 0.08, 1.677, {21.4, 28.8, 24.5, 39.2}},   // 320 x 256, eight waves of 160 x 64
-    {4, 4, 2, 2.42, 1.036, {5.5, 7.5, 6.5, 6.2}},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
-    {4, 4, 1, 0.74, 0.502, {6.0, 7.9, 7.0, 7.7}},        // 128 x 128, four ring stages
-    {2, 4, 2, 2.53, 0.588, {4.3, 6.9, 4.5, 6.2}},        // 64 x 128, two k-groups, two workgroups per unit
-    {2, 2, 2, 2.73, 0.425, {1e9, 3.4, 2.3, 5.1}},        // 64 x 64, two k-groups, two workgroups per unit
-    {2, 2, 1, 1.14, 0.218, {1e9, 3.8, 2.8, 5.5}},        // 64 x 64, two k-groups, four stages of 128
+    {10, 8, 1, 2.34, 1.670, {18.4, 26.7, 22.7, 38.1}, 1.0},   // 320 x 256, eight waves of 160 x 64
+    {4, 4, 2, 3.77, 1.078, {3.3, 5.7, 4.2, 7.4}, 0.70},       // 128 x 128, eight waves of 32 x 64, two workgroups per unit
+    {4, 4, 1, 1.80, 0.474, {5.3, 7.1, 6.0, 8.4}, 1.0},        // 128 x 128, four ring stages
+    {2, 4, 2, 3.90, 0.620, {3.0, 5.7, 2.9, 8.3}, 0.62},       // 64 x 128, two k-groups, two workgroups per unit
+    {2, 2, 2, 2.30, 0.432, {1e9, 3.3, 1.7, 7.3}, 0.86},       // 64 x 64, two k-groups, two workgroups per unit
+    {2, 2, 1, 2.50, 0.227, {1e9, 3.0, 1.9, 6.6}, 1.0},        // 64 x 64, two k-groups, four stages of 128
 };
 
 }  // namespace
@@ -570,10 +607,12 @@ int pick_bgemm(const WParams& p, double other_us) {
     if ((p.K / 64) % (c == 5 || c == 4 ? 2 : 1)) continue;          // two k-groups of 64 per stage
     const int bfo = p.geglu ? t.bf / 2 : t.bf;
     const long long n = (long long)((MT + t.bt - 1) / t.bt) * ((NF + bfo - 1) / bfo);
-    // rounds of workgroups; two workgroups of a unit share it, so their rounds are continuous beyond the first few, and a
-    // workgroup with the unit to itself is faster
+    // rounds of workgroups; two workgroups of a unit share it, so their rounds are continuous beyond the first few
     double r = (double)((n + 255) / 256);
-    if (t.occ == 2) r = n <= 256 ? 0.62 : n > 768 ? n / 512.0 : (double)((n + 511) / 512);
+    if (t.occ == 2) {
+      const long long rem = n % 512;
+      r = n > 1536 ? n / 512.0 : (double)(n / 512) + (rem == 0 ? 0.0 : rem <= 256 ? t.alone : 1.0);
+    }
     const double us = t.base + r * (kt * t.slab + t.epi[mode]);
     if (us < best) { best = us; pick = c; }
   }

@@ -624,13 +624,15 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     p.xa_bstride = a.xa_bstride / 8;
   }
   const int nfrag = Nout / 32;
-  // Measured on the patch step (kernel trace, cold weights).  A wave tile of 32 tokens x 64 features keeps the most waves
-  // in flight and wins while the problem has few tiles; from ~320 workgroups on, the 64 x 64 tile's lower operand
-  // traffic per flop wins; and where a still larger tile (64 x 96 without GEGLU) covers the output with at most one
-  // workgroup per unit, its single round of workgroups wins again, provided the reduction is long enough to amortise
-  // the row-by-row epilogue.
+  // Measured with cold weights.  Up to 128 wave tiles of 32 tokens x 64 features the 32 x 32 tile puts twice the
+  // workgroups on the chip: such a layer waits for its weights, which a compute unit pulls from HBM at no more than 25
+  // bytes per cycle (64 x 1280 x 5120 18.4 -> 13.1 us, 150 x 1280 x 1280 6.4 -> 5.2; at 140 tiles it loses).  Up to ~320
+  // the 32 x 64 tile keeps the most waves in flight; from there on the 64 x 64 tile's lower operand traffic per flop wins;
+  // and where a still larger tile (64 x 96 without GEGLU) covers the output with at most one workgroup per unit, its single
+  // round of workgroups wins again, provided the reduction is long enough to amortise the row-by-row epilogue.
   const int MT = (a.M + 31) / 32;
   const long long wg12 = (long long)MT * (p.geglu ? nfrag : nfrag / 2);
+  const bool few = wg12 <= 128;
   const bool long_k = a.K / 16 / 4 >= 16;
   const bool wide = wg12 >= 320 && long_k && !p.geglu && nfrag % 3 == 0 && (long long)((MT + 1) / 2) * (nfrag / 3) <= 256 && !a.xa_kv;
   {
@@ -640,10 +642,12 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     const bool two = wg12 >= 320 && !a.xa_kv;
     const double n = wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)wg12;
     const double r = n / 256.0 > 0.6 ? n / 256.0 : 0.6;
-    const double us = wide ? 11.0 : two ? 3.1 + r * (0.257 * kt + (p.geglu ? 0.6 : p.nseg ? 1.4 : 2.4))
-                                        : 4.6 + r * (0.198 * kt + (a.xa_kv || p.geglu ? 0.1 : p.nseg ? -1.1 : -1.6));
+    const double us = wide ? 9.7 + 0.125 * kt
+                      : two ? 4.6 + r * (0.286 * kt + (p.geglu ? 0.15 : p.nseg ? 0.88 : 1.16))
+                            : 5.3 + r * (0.189 * kt + (p.geglu ? -1.0 : p.nseg ? 0.35 : a.xa_kv ? 0.1 : -2.2));
     const char* e = tune_env("DF_BGEMM");
-    const int c = e ? atoi(e) : pick_bgemm(p, us);
+    // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
+    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.94 * us);
     if (c >= 0) {
       const int rc = launch_bgemm(p, c, st);
       if (rc != DF_ESHAPE || e) return rc;
@@ -665,7 +669,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     DF_XA(1)
 #undef DF_XA
   }
-  if (!p.geglu && nfrag % 2) return launch_cfg<1, 1, 4, 5>(p, st);
+  if (!p.geglu && (nfrag % 2 || few)) return launch_cfg<1, 1, 4, 5>(p, st);
   if (wide) return launch_cfg<2, 3, 4, 5>(p, st);
   if (wg12 >= 320) return launch_cfg<2, 2, 4, 5>(p, st);
   return launch_cfg<1, 2, 4, 5>(p, st);
