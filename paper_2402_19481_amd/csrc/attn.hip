@@ -3,19 +3,13 @@
 // rows are read from the fresh tensors and every other row from the stale
 // buffers.  The splice happens in the tile loader; no scattered copy exists.
 //
-// bf16 kernel (head dim 64): flash-style, one workgroup = 4 waves x 32 queries,
-// 64-key K/V tiles staged through LDS and shared by the 4 waves.  Each wave
-// computes S^T = K Q^T with v_mfma_f32_32x32x16_bf16 so that a lane owns one
-// query column: the online-softmax row statistics are lane-local plus one
-// exchange with lane^32.  The rows of the K tile are assigned to MFMA rows in
-// a permuted order chosen so that the exponentiated accumulators are, without
-// any data movement, the B operand (P^T) of O^T = V^T P^T, and the matching
-// V^T operand is one 16-byte read from a transposed, XOR-swizzled V tile.
-// Small query counts are spread over the chip by splitting the key range
-// across workgroups; partial (O, m, l) are merged by a second kernel.
-//
-// f32 kernel: one wave per query, lanes stride over keys; for the small
-// full-precision configuration only.
+// bf16 (head dim 64): attn_pipe_d64 and, for few queries, attn_wave_d64.  Both compute S^T = K Q^T with
+// v_mfma_f32_32x32x16_bf16 so that a lane owns one query column: the softmax's row statistics are lane-local plus one
+// exchange with lane^32.  The rows of the K tile are assigned to MFMA rows in a permuted order chosen so that the
+// exponentiated accumulators are, without any data movement, the B operand (P^T) of O^T = V^T P^T.
+// In the UNet step every key comes from the (already refreshed) stale buffers and V is stored transposed ([feature][key],
+// written that way by the projection), so a V^T operand is one 16-byte read of an LDS tile.
+// f32: d / 4 lanes share a key (attn_f32); for the small full-precision configuration only.
 #include <cstdlib>
 #include <type_traits>
 
@@ -36,6 +30,7 @@ struct AttnParams {
   int own_lo, own_n;
   int own_period;  // 0: keys [own_lo, own_lo + own_n) are fresh; P > 0: key j is fresh iff j % P lies in that range
                    // (a vertical strip of a token grid with P columns) and is row (j / P) * own_n + j % P - own_lo
+  unsigned int own_magic;   // floor(2^32 / own_period), at most 2^32 - 1
   long long ldq, ldkf, ldvf, ldks, ldvs, ldo;
   long long bsq, bskf, bsvf, bsks, bsvs, bso;
   float scale;
@@ -57,294 +52,12 @@ __device__ __forceinline__ long long fresh_row(int own_lo, int own_n, int period
   return (rel >= 0 && rel < own_n) ? (long long)rel : -1;
 }
 
-__device__ __forceinline__ const bf16_t* key_row(const bf16_t* fresh, const bf16_t* stale, long long ldf, long long lds,
-                                                 int own_lo, int own_n, int period, int j) {
-  const long long fr = fresh_row(own_lo, own_n, period, j);
-  return fr >= 0 ? fresh + fr * ldf : stale + (long long)j * lds;
-}
-
 // physical key (0..31) loaded into MFMA row rho of a 32-key block
 __device__ __forceinline__ int key_of_mfma_row(int rho) {
   const int j = rho >> 3, g = (rho >> 2) & 1, r = rho & 3;
   return 16 * (j >> 1) + 8 * g + 4 * (j & 1) + r;
 }
 
-// PERIODIC: the fresh keys are a vertical strip of the token grid (own_period > 0); a separate instantiation, so that
-// the contiguous split keeps its tile-level fast paths and carries none of the per-key index arithmetic.
-template <bool PERIODIC>
-__global__ __launch_bounds__(256, 2) void attn_bf16_d64(AttnParams p) {
-  const int period = PERIODIC ? p.own_period : 0;
-  constexpr int D = 64, TK = 64;
-  __shared__ __attribute__((aligned(16))) bf16_t Ks[2][TK * D];   // [key][d], 16-byte chunks XOR-swizzled by row
-  __shared__ __attribute__((aligned(16))) bf16_t Vt[2][D * TK];   // [d][key], swizzled
-
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // scalar: the query rows, hence the key ranges and the
-                                                               // ragged-tile test, stay off the vector ALU
-  const int g = lane >> 5, c = lane & 31;
-  const int xor32 = (lane ^ 32) << 2;                          // byte index of the partner lane for ds_bpermute
-  const int csig = (c & 0x13) | ((c & 4) << 1) | ((c & 8) >> 1);   // c with bits 2 and 3 swapped
-  // 1-D grid; workgroups go round-robin over the 8 XCDs, so XCD x takes the x-th contiguous chunk of the
-  // (query block fastest, head, batch*split) order: the query blocks that read the same K/V range share an L2
-  int t = blockIdx.x;
-  {
-    const int nwg = gridDim.x;
-    const int xcd = t & 7, loc = t >> 3;
-    const int base = nwg >> 3, rem = nwg & 7;
-    t = xcd * base + (xcd < rem ? xcd : rem) + loc;
-  }
-  const int nqb = (p.Lq + 127) / 128;
-  const int qb = t % nqb;
-  const int h = (t / nqb) % p.heads;
-  const int zz = t / (nqb * p.heads);
-  const int b = zz / p.nsplit, split = zz % p.nsplit;
-  const int q0 = qb * 128 + wave * 32;
-  const int kv_lo = split * p.keys_per_split;
-  int kv_hi = kv_lo + p.keys_per_split;
-  if (kv_hi > p.L) kv_hi = p.L;
-  const int ntiles = (kv_hi - kv_lo + TK - 1) / TK;
-
-  const bf16_t* kf = (const bf16_t*)p.kf + (long long)b * p.bskf + h * D;
-  const bf16_t* vf = (const bf16_t*)p.vf + (long long)b * p.bsvf + h * D;
-  const bf16_t* ks = p.ks ? (const bf16_t*)p.ks + (long long)b * p.bsks + h * D : nullptr;
-  const bf16_t* vs = p.vs ? (const bf16_t*)p.vs + (long long)b * p.bsvs + h * D : nullptr;
-
-  // Q^T operand: lane (g, c) holds Q[q0 + c][16*ks + 8*g .. +7] for ks = 0..3
-  bf16x8 qreg[4];
-  {
-    const int qi = q0 + c;
-    const bf16_t* qp = (const bf16_t*)p.q + (long long)b * p.bsq + (long long)qi * p.ldq + h * D;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      u32x4 t = {0u, 0u, 0u, 0u};
-      if (qi < p.Lq) t = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * g);
-      qreg[s] = __builtin_bit_cast(bf16x8, t);
-    }
-  }
-
-  // cooperative tile loads: K: lane -> (key = tid/8 (+32), chunk = tid%8); V: keys 2*kap, 2*kap+1, chunk = tid%8
-  const int ld_key = tid >> 3, ld_ch = tid & 7;
-  // The K/V rows come from HBM or the Infinity Cache with microseconds of latency and a tile's compute is a fraction
-  // of that, so three tiles of loads are kept in flight in a register ring (slot = tile % 3, loop unrolled by 3).
-  constexpr int PF = 3;
-  u32x4 kreg[PF][2], vreg[PF][2];
-  const u32x4 zero4 = {0u, 0u, 0u, 0u};
-  // a lane's row offsets inside a tile (32-bit: the launcher bounds the pitches); a tile that lies wholly in the
-  // stale buffer or wholly in the fresh rows only adds a scalar base (the generic path below redoes a select and a
-  // 64-bit multiply per row and tile)
-  unsigned int kof_s[2], vof_s[2], kof_f[2], vof_f[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    kof_s[i] = (unsigned int)(ld_key + 32 * i) * (unsigned int)p.ldks + ld_ch * 8;
-    vof_s[i] = (unsigned int)(2 * ld_key + i) * (unsigned int)p.ldvs + ld_ch * 8;
-    kof_f[i] = (unsigned int)(ld_key + 32 * i) * (unsigned int)p.ldkf + ld_ch * 8;
-    vof_f[i] = (unsigned int)(2 * ld_key + i) * (unsigned int)p.ldvf + ld_ch * 8;
-  }
-  auto load_tile = [&](int t, auto slot) {
-    constexpr int S = decltype(slot)::value;
-    const int base = kv_lo + t * TK;
-    if (!PERIODIC && base + TK <= kv_hi) {         // (uniform) a full tile of a contiguous split
-      const int rel = base - p.own_lo;
-      if (rel >= 0 && rel + TK <= p.own_n) {               // all rows fresh
-        const bf16_t* kb = kf + (long long)rel * p.ldkf;
-        const bf16_t* vb = vf + (long long)rel * p.ldvf;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          kreg[S][i] = *reinterpret_cast<const u32x4*>(kb + kof_f[i]);
-          vreg[S][i] = *reinterpret_cast<const u32x4*>(vb + vof_f[i]);
-        }
-        return;
-      }
-      if (rel + TK <= 0 || rel >= p.own_n) {               // all rows stale
-        const bf16_t* kb = ks + (long long)base * p.ldks;
-        const bf16_t* vb = vs + (long long)base * p.ldvs;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          kreg[S][i] = *reinterpret_cast<const u32x4*>(kb + kof_s[i]);
-          vreg[S][i] = *reinterpret_cast<const u32x4*>(vb + vof_s[i]);
-        }
-        return;
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int jk = base + ld_key + 32 * i;
-      kreg[S][i] = jk < kv_hi ? *reinterpret_cast<const u32x4*>(key_row(kf, ks, p.ldkf, p.ldks, p.own_lo, p.own_n, period, jk) + ld_ch * 8)
-                              : zero4;
-      const int jv = base + 2 * ld_key + i;
-      vreg[S][i] = jv < kv_hi ? *reinterpret_cast<const u32x4*>(key_row(vf, vs, p.ldvf, p.ldvs, p.own_lo, p.own_n, period, jv) + ld_ch * 8)
-                              : zero4;
-    }
-  };
-  auto store_tile = [&](int buf, auto slot) {
-    constexpr int S = decltype(slot)::value;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int row = ld_key + 32 * i;
-      const int f = (row & 3) | (((row >> 3) & 1) << 2);
-      *reinterpret_cast<u32x4*>(&Ks[buf][row * D + ((ld_ch ^ f) * 8)]) = kreg[S][i];
-    }
-    // V transposed: dword (keys 2*kap, 2*kap+1) of row d goes to chunk (kap/4) ^ (d%8) ^ (d/8), dword kap%4
-    const int kap = ld_key;
-    unsigned int* vt = reinterpret_cast<unsigned int*>(&Vt[buf][0]);
-    const unsigned int a[4] = {vreg[S][0].x, vreg[S][0].y, vreg[S][0].z, vreg[S][0].w};
-    const unsigned int bq[4] = {vreg[S][1].x, vreg[S][1].y, vreg[S][1].z, vreg[S][1].w};
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int d = ld_ch * 8 + e;
-      const unsigned int lo = (e & 1) ? (a[e >> 1] >> 16) : (a[e >> 1] & 0xffffu);
-      const unsigned int hi = (e & 1) ? (bq[e >> 1] & 0xffff0000u) : (bq[e >> 1] << 16);
-      const int chunk = (kap >> 2) ^ (d & 7) ^ (d >> 3);
-      vt[d * 32 + chunk * 4 + (kap & 3)] = lo | hi;
-    }
-  };
-
-  f32x16 o_acc[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) o_acc[i][e] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-  const float sc = p.scale * kLog2e;
-
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  using I2 = std::integral_constant<int, 2>;
-  if (ntiles > 0) load_tile(0, I0{});
-  if (ntiles > 1) load_tile(1, I1{});
-  if (ntiles > 2) load_tile(2, I2{});
-  // one tile: ring slot -> LDS buffer t&1, barrier, refill the slot with tile t+3, compute from LDS.  A buffer is
-  // rewritten two tiles later, after the barrier of the tile in between, which every wave reaches only after it has
-  // finished reading it.
-  auto do_tile = [&](int t, auto slot) {
-    const int buf = t & 1;
-    store_tile(buf, slot);
-    __syncthreads();
-    if (t + PF < ntiles) load_tile(t + PF, slot);
-    // ---- S^T = K Q^T for two 32-key blocks ----
-    f32x16 s_acc[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) s_acc[kb][e] = 0.f;
-      const int row = 32 * kb + key_of_mfma_row(c);
-      const int f = (row & 3) | (((row >> 3) & 1) << 2);
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const bf16x8 kfrag = *reinterpret_cast<const bf16x8*>(&Ks[buf][row * D + (((2 * s + g) ^ f) * 8)]);
-        s_acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfrag, qreg[s], s_acc[kb], 0, 0, 0);
-      }
-    }
-    // accumulator e = 4*j + r of block kb is key  base + 32*kb + 16*(j/2) + 8*g + 4*(j%2) + r  for query c
-    const int tile_base = kv_lo + t * TK;
-    float mx = -INFINITY;
-    if (tile_base + TK > kv_hi) {   // ragged last tile: keys beyond the range get no weight
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int j = e >> 2, r = e & 3;
-          const int key = tile_base + 32 * kb + 16 * (j >> 1) + 8 * g + 4 * (j & 1) + r;
-          if (key >= kv_hi) s_acc[kb][e] = -INFINITY;
-        }
-    }
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s_acc[kb][e]);
-    mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)))) * sc;   // scale > 0
-    const float m_new = fmaxf(m_run, mx);           // finite: every tile holds at least one valid key
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);   // exp2(-inf) = 0 on the first tile
-    float rs = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][e], sc, -m_new));   // raw v_exp_f32: arguments are <= 0
-        s_acc[kb][e] = pv;
-        rs += pv;
-      }
-    rs += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(rs)));
-    l_run = l_run * alpha + rs;
-    m_run = m_new;
-    // the running maximum rarely moves after the first tiles: rescale only when some query of the wave needs it
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o_acc[i][e] *= alpha;
-    }
-
-    // ---- O^T += V^T P^T : four 16-key steps; lane supplies P for its query and key slots 8g..8g+7 ----
-#pragma unroll
-    for (int ts = 0; ts < 4; ++ts) {
-      const int kb = ts >> 1, half = ts & 1;
-      u32x4 pk;
-      pk.x = pack_bf2(s_acc[kb][8 * half + 0], s_acc[kb][8 * half + 1]);
-      pk.y = pack_bf2(s_acc[kb][8 * half + 2], s_acc[kb][8 * half + 3]);
-      pk.z = pack_bf2(s_acc[kb][8 * half + 4], s_acc[kb][8 * half + 5]);
-      pk.w = pack_bf2(s_acc[kb][8 * half + 6], s_acc[kb][8 * half + 7]);
-      const bf16x8 pfrag = __builtin_bit_cast(bf16x8, pk);
-      const int kchunk = 4 * kb + 2 * half + g;     // keys 32*kb + 16*half + 8*g .. +7
-#pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        const int d = 32 * db + csig;                 // MFMA row c computes feature row sigma(c) (see the write below)
-        const int chunk = kchunk ^ (d & 7) ^ (d >> 3);
-        const bf16x8 vfrag = *reinterpret_cast<const bf16x8*>(&Vt[buf][d * TK + chunk * 8]);
-        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfrag, pfrag, o_acc[db], 0, 0, 0);
-      }
-    }
-  };
-  for (int t = 0; t < ntiles; t += PF) {
-    do_tile(t, I0{});
-    if (t + 1 < ntiles) do_tile(t + 1, I1{});
-    if (t + 2 < ntiles) do_tile(t + 2, I2{});
-  }
-
-  // ---- write: V^T rows were taken in the order sigma (bits 2 and 3 of the row index swapped), so accumulator
-  // elements 8f .. 8f+7 of lane (g, c) are O[q0 + c][32*db + 16*f + 8*g .. +7]: eight consecutive features ----
-  const int qi = q0 + c;
-  if (qi >= p.Lq) return;
-  if (p.nsplit == 1) {
-    const float inv = 1.0f / l_run;
-    bf16_t* op = (bf16_t*)p.out + (long long)b * p.bso + (long long)qi * p.ldo + h * D;
-    const long long m = (long long)b * p.Lq + qi;     // token row of the packed operand
-    bf16_t* pp = (bf16_t*)p.out + (((m >> 5) * (long long)(p.heads * D / 16) + h * (D / 16)) * 64 + (m & 31) + 32 * g) * 8;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        u32x4 t;
-        t.x = pack_bf2(o_acc[db][8 * f + 0] * inv, o_acc[db][8 * f + 1] * inv);
-        t.y = pack_bf2(o_acc[db][8 * f + 2] * inv, o_acc[db][8 * f + 3] * inv);
-        t.z = pack_bf2(o_acc[db][8 * f + 4] * inv, o_acc[db][8 * f + 5] * inv);
-        t.w = pack_bf2(o_acc[db][8 * f + 6] * inv, o_acc[db][8 * f + 7] * inv);
-        if (p.out_packed) *reinterpret_cast<u32x4*>(pp + (2 * db + f) * 512) = t;
-        else *reinterpret_cast<u32x4*>(op + 32 * db + 16 * f + 8 * g) = t;
-      }
-  } else {
-    const long long row = (((long long)split * p.B + b) * p.heads + h) * p.Lq + qi;
-    float* po = p.part_o + row * D;
-#pragma unroll
-    for (int db = 0; db < 2; ++db)
-#pragma unroll
-      for (int f = 0; f < 2; ++f) {
-        f32x4 t0 = {o_acc[db][8 * f], o_acc[db][8 * f + 1], o_acc[db][8 * f + 2], o_acc[db][8 * f + 3]};
-        f32x4 t1 = {o_acc[db][8 * f + 4], o_acc[db][8 * f + 5], o_acc[db][8 * f + 6], o_acc[db][8 * f + 7]};
-        *reinterpret_cast<f32x4*>(po + 32 * db + 16 * f + 8 * g) = t0;
-        *reinterpret_cast<f32x4*>(po + 32 * db + 16 * f + 8 * g + 4) = t1;
-      }
-    if (g == 0) {
-      p.part_ml[row * 2] = m_run;      // in log2 units
-      p.part_ml[row * 2 + 1] = l_run;
-    }
-  }
-}
-
-// ---- variant for the UNet step: every key row comes from the (already refreshed) stale buffers, V is stored
-// transposed ([feature][key], written that way by the projection), so K and V^T tiles go global -> LDS with direct
-// loads (no registers, no transposing stores) through a 3-stage ring awaited with an explicit vmcnt.  The swizzles
-// of the LDS tiles are applied on the source side: LDS slot s of row r receives global chunk s ^ key(r). ----
 #ifdef DF_TUNING
 // Tuning build only: per workgroup (waves 0 and 5; wave 5's rows follow at +256), 32 stamps: the constant-rate clock at entry and exit, cycle stamps between.
 __device__ long long g_attn_trace[512 * 32];
@@ -378,7 +91,14 @@ __device__ long long g_attn_trace[512 * 32];
 // the clock.  Measured against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10 heads
 // 1435 -> 1105 us (961 TFLOP/s), 4096 x 4096 x 10 88 -> 66, 1024 x 4096 x 20 51.6 -> 38, 1200 x 9600 x 10 66 -> 46.
 // Three workgroups per unit instead of two (168 registers) gain 2 % on the largest of these and lose 3-5 % below.
-template <bool PRE>
+// Fresh and stale rows (kSrcRows, kSrcPeriodic): the splice is resolved in the source addresses of the direct loads, tile by tile
+// where a tile lies on one side, lane by lane else; V is transposed by ds_read_b64_tr_b16 on its way from LDS to the registers.
+// 1024 of 4096 tokens x 10 heads: 35 -> 29 us with the merge, against staging through registers.
+// Where K and V come from: all stale, V transposed (V^T); rows of the fresh and the stale tensors, the fresh ones a range of keys
+// (kSrcRows) or periodic (kSrcPeriodic)
+enum { kSrcVt = 0, kSrcRows = 1, kSrcPeriodic = 2 };
+
+template <bool PRE, int SRC>
 __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   constexpr int D = 64, TK = 64, KB = TK * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -406,25 +126,78 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   const int ntiles = (kv_hi - kv_lo + TK - 1) / TK;
 
   const bf16_t* kg = (const bf16_t*)p.ks + (long long)b * p.bsks + h * D;
-  const bf16_t* vg = (const bf16_t*)p.vs + (long long)b * p.bsvs + (long long)h * D * p.vt_ld;
+  const bf16_t* vg = (const bf16_t*)p.vs + (long long)b * p.bsvs + (SRC == kSrcVt ? (long long)h * D * p.vt_ld : (long long)h * D);
+  const bf16_t* kfr = (const bf16_t*)p.kf + (long long)b * p.bskf + h * D;
+  const bf16_t* vfr = (const bf16_t*)p.vf + (long long)b * p.bsvf + h * D;
 
-  // direct loads: instruction j of a wave covers tile rows (2*wave + j)*8 + lane/8, 16-byte slot lane%8
+  // direct loads: instruction j of a wave covers tile rows (2*wave + j)*8 + lane/8, 16-byte slot lane%8.  K tiles are
+  // [key][d], row r holding chunk c at slot c ^ ((r >> 1) & 7).  V^T tiles are [d][key]; V tiles (fresh and stale rows) [key][d]
+  // with a swizzle for the transposing reads.
   const int lr = lane >> 3, slot8 = lane & 7;
-  unsigned int kofs[2], vofs[2];
+  int trow[2], kch[2], vch[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
     const int row = (2 * wave + j) * 8 + lr;
-    kofs[j] = (unsigned int)row * (unsigned int)p.ldks + (unsigned int)((slot8 ^ ((row >> 1) & 7)) * 8);
-    vofs[j] = (unsigned int)row * (unsigned int)p.vt_ld + (unsigned int)((slot8 ^ (row & 7) ^ (row >> 3)) * 8);
+    trow[j] = row;
+    kch[j] = (slot8 ^ ((row >> 1) & 7)) * 8;
+    vch[j] = SRC == kSrcVt ? (slot8 ^ (row & 7) ^ (row >> 3)) * 8 : (slot8 ^ (((row >> 1) & 1) * 2) ^ (((row >> 3) & 1) * 4)) * 8;
   }
-  // LDS: three K tiles [key][d], then three V^T tiles [d][key].  kofr: the offsets inside the last tile when it is ragged
-  // (rows beyond the last key re-read it and are masked)
+  // offsets inside a tile whose rows are consecutive in one tensor (32-bit, the launcher bounds the pitches)
+  unsigned int kofs[2], vofs[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    kofs[j] = (unsigned int)trow[j] * (unsigned int)p.ldks + (unsigned int)kch[j];
+    vofs[j] = (unsigned int)trow[j] * (unsigned int)(SRC == kSrcVt ? p.vt_ld : p.ldvs) + (unsigned int)vch[j];
+  }
+  // SRC != kSrcVt: a lane's source row for tile row trow[j] of the tile at key0; rows beyond the last key re-read it (masked)
+  struct Rows { const bf16_t* k[2]; const bf16_t* v[2]; };
+  auto rows_of = [&](int key0) {
+    Rows r;
+    if (SRC == kSrcRows && (key0 + TK <= p.own_lo || key0 >= p.own_lo + p.own_n) && key0 + TK <= p.L) {   // (uniform) all stale
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        r.k[j] = kg + (long long)key0 * p.ldks + kofs[j];
+        r.v[j] = vg + (long long)key0 * p.ldvs + vofs[j];
+      }
+      return r;
+    }
+    if (SRC == kSrcRows && key0 >= p.own_lo && key0 + TK <= p.own_lo + p.own_n && key0 + TK <= p.L) {     // (uniform) all fresh
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        r.k[j] = kfr + (long long)(key0 - p.own_lo) * p.ldkf + ((unsigned int)trow[j] * (unsigned int)p.ldkf + (unsigned int)kch[j]);
+        r.v[j] = vfr + (long long)(key0 - p.own_lo) * p.ldvf + ((unsigned int)trow[j] * (unsigned int)p.ldvf + (unsigned int)vch[j]);
+      }
+      return r;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      unsigned int key = (unsigned int)(key0 + trow[j] < p.L ? key0 + trow[j] : p.L - 1), row = key - (unsigned int)p.own_lo;
+      bool own = row < (unsigned int)p.own_n;
+      if constexpr (SRC == kSrcPeriodic) {
+        // key = q * P + r, q from the rounded-down reciprocal (at most one too small)
+        unsigned int q = __umulhi(key, p.own_magic), rr = key - q * (unsigned int)p.own_period;
+        if (rr >= (unsigned int)p.own_period) { ++q; rr -= (unsigned int)p.own_period; }
+        row = rr - (unsigned int)p.own_lo;
+        own = row < (unsigned int)p.own_n;
+        row += q * (unsigned int)p.own_n;
+      }
+      row = own ? row : key;
+      r.k[j] = (own ? kfr : kg) + (unsigned long long)row * (unsigned int)(own ? p.ldkf : p.ldks) + kch[j];
+      r.v[j] = (own ? vfr : vg) + (unsigned long long)row * (unsigned int)(own ? p.ldvf : p.ldvs) + vch[j];
+    }
+    return r;
+  };
+  // kSrcVt: kofr are the offsets inside the last tile when it is ragged
   unsigned int kofr[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int row = (2 * wave + j) * 8 + lr, left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
-    kofr[j] = (unsigned int)(row < left ? row : left) * (unsigned int)p.ldks + (unsigned int)((slot8 ^ ((row >> 1) & 7)) * 8);
+    const int left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
+    kofr[j] = (unsigned int)(trow[j] < left ? trow[j] : left) * (unsigned int)p.ldks + (unsigned int)kch[j];
   }
+  auto kptr = [&](int ti, int j) {
+    const int key0 = kv_lo + ti * TK;
+    return kg + (long long)key0 * p.ldks + (key0 + TK > p.L ? kofr[j] : kofs[j]);
+  };
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
@@ -436,18 +209,31 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
+  // LDS: three K tiles, then three V tiles
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int ti = i < ntiles ? i : ntiles - 1;            // past the end: the last tile again (keeps vmcnt uniform)
-    const bool rag = kv_lo + ti * TK + TK > p.L;
+    if constexpr (SRC == kSrcVt) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_global_load_lds(DF_GPTR(kptr(ti, j)), DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+    } else {
+      const Rows r = rows_of(kv_lo + ti * TK);
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        __builtin_amdgcn_global_load_lds(DF_GPTR(r.k[j]), DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+      if (i == 0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          __builtin_amdgcn_global_load_lds(DF_GPTR(r.v[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
+      }
+    }
+  }
+  if constexpr (SRC == kSrcVt) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds(DF_GPTR(kg + (long long)(kv_lo + ti * TK) * p.ldks + (rag ? kofr[j] : kofs[j])),
-                                       DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds(DF_GPTR(vg + kv_lo + vofs[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
   }
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-    __builtin_amdgcn_global_load_lds(DF_GPTR(vg + kv_lo + vofs[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
 
   // LDS byte offsets of this lane's fragments inside a tile.  K: MFMA row c of key block kb, k-step s; V^T: feature csig of
   // feature block db, key step ts.  The second block is 4096 bytes on in both (for V^T with the key steps ts ^ 2).
@@ -458,6 +244,10 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     kof[i] = row * (D * 2) + (((2 * i + g) ^ ((row >> 1) & 7)) * 16);
     vof[i] = csig * (TK * 2) + ((kchunk ^ (csig & 7) ^ (csig >> 3)) * 16);
   }
+  // V rows: a transposing read hands 16 lanes four keys of 16 features: lane i supplies the address of key i / 4, features 4 * (i
+  // % 4) .., and receives feature i.  Chunks 1 and 2 are exchanged (csig), key + 8 g; the second feature block is slot ^ 4.
+  const int tri = lane & 15;
+  const int vtr = (8 * g + (tri >> 2)) * (D * 2) + (((2 * (c >> 4) + (tri & 1)) ^ (2 * ((tri >> 3) & 1)) ^ (4 * g)) * 16) + ((tri >> 1) & 1) * 8;
   const char* const lds = smem;
 
   f32x16 o_acc[2], sa[2], cinit;
@@ -476,6 +266,34 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     return fmaxf(fmaxf(a, s[8 * h + 6]), s[8 * h + 7]);
   };
   auto vfrag = [&](int vbase, int ts, int db) { return *reinterpret_cast<const u32x4*>(lds + vbase + vof[db ? ts ^ 2 : ts] + 4096 * db); };
+  // The eight V fragments of a tile of rows ([2 * ts + db], low and high half), requested by vrequest() and there after
+  // varrive<1>() (key steps 0 and 1) and varrive<2>() (2 and 3), which name every register again: the compiler's own
+  // transposing read waits for all global loads in flight (it takes them for possible writers of the tile).
+  struct VTile { u32x2 r[16]; };
+  auto vrequest = [&](int vbase, VTile& v) {
+    const unsigned int a0 = (unsigned int)(uintptr_t)DF_LPTR(lds + vbase + vtr), a1 = (unsigned int)(uintptr_t)DF_LPTR(lds + vbase + (vtr ^ 64));
+#define DF_TR(o, a, off) "ds_read_b64_tr_b16 %" #o ", %" #a " offset:" #off "\n\t"
+    asm volatile(DF_TR(0, 16, 0) DF_TR(1, 16, 512) DF_TR(2, 17, 0) DF_TR(3, 17, 512)
+                 DF_TR(4, 16, 2048) DF_TR(5, 16, 2560) DF_TR(6, 17, 2048) DF_TR(7, 17, 2560)
+                 DF_TR(8, 16, 4096) DF_TR(9, 16, 4608) DF_TR(10, 17, 4096) DF_TR(11, 17, 4608)
+                 DF_TR(12, 16, 6144) DF_TR(13, 16, 6656) DF_TR(14, 17, 6144) DF_TR(15, 17, 6656)
+                 : "=&v"(v.r[0]), "=&v"(v.r[1]), "=&v"(v.r[2]), "=&v"(v.r[3]), "=&v"(v.r[4]), "=&v"(v.r[5]), "=&v"(v.r[6]), "=&v"(v.r[7]),
+                   "=&v"(v.r[8]), "=&v"(v.r[9]), "=&v"(v.r[10]), "=&v"(v.r[11]), "=&v"(v.r[12]), "=&v"(v.r[13]), "=&v"(v.r[14]), "=&v"(v.r[15])
+                 : "v"(a0), "v"(a1) : "memory");
+#undef DF_TR
+  };
+  auto varrive = [&](VTile& v, auto half) {
+    if constexpr (decltype(half)::value == 1)
+      asm volatile("s_waitcnt lgkmcnt(8)" : "+v"(v.r[0]), "+v"(v.r[1]), "+v"(v.r[2]), "+v"(v.r[3]), "+v"(v.r[4]), "+v"(v.r[5]), "+v"(v.r[6]), "+v"(v.r[7]) :: "memory");
+    else
+      asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v.r[8]), "+v"(v.r[9]), "+v"(v.r[10]), "+v"(v.r[11]), "+v"(v.r[12]), "+v"(v.r[13]), "+v"(v.r[14]), "+v"(v.r[15]) :: "memory");
+  };
+  auto vof8 = [&](const VTile& v, int ts, int db) {
+    const u32x2 lo = v.r[4 * ts + 2 * db], hi = v.r[4 * ts + 2 * db + 1];
+    return u32x4{lo.x, lo.y, hi.x, hi.y};
+  };
+  using H1 = std::integral_constant<int, 1>;
+  using H2 = std::integral_constant<int, 2>;
   auto kfrag = [&](int kbase, int s, int kb) { return *reinterpret_cast<const u32x4*>(lds + kbase + kof[s] + 4096 * kb); };
   auto pv_mfma = [&](u32x4 v, int ts, int db) {
     o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pk[ts]), o_acc[db], 0, 0, 0);
@@ -517,8 +335,10 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
           if (kv_lo + tl * TK + 32 * kb + 16 * (e >> 3) + 8 * g + (e & 7) >= kv_hi) sa[kb][e] = -INFINITY;
     }
     {
+      VTile vt;
+      if constexpr (SRC != kSrcVt) { vrequest(vbase, vt); varrive(vt, H1{}); varrive(vt, H2{}); }
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pv_mfma(vfrag(vbase, i >> 1, i & 1), i >> 1, i & 1);
+      for (int i = 0; i < 8; ++i) pv_mfma(SRC == kSrcVt ? vfrag(vbase, i >> 1, i & 1) : vof8(vt, i >> 1, i & 1), i >> 1, i & 1);
 #pragma unroll
       for (int i = 0; i < 4; ++i) pk[i] = u32x4{0u, 0u, 0u, 0u};
       const float mx = max8(sa[1], 1, max8(sa[1], 0, max8(sa[0], 1, max8(sa[0], 0, -INFINITY))));
@@ -542,8 +362,15 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       // its exponentials are done), O += V P of tile tl-1, S of tile tl+1.  One matrix instruction and its share of
       // vector instructions per slot; operand fragments are read from LDS five slots ahead.
       u32x4 f[16];
+      VTile vt;
+      if constexpr (SRC == kSrcVt) {
 #pragma unroll
-      for (int i = 0; i < 5; ++i) f[i] = vfrag(vbase, i >> 1, i & 1);
+        for (int i = 0; i < 5; ++i) f[i] = vfrag(vbase, i >> 1, i & 1);
+      } else {
+        vrequest(vbase, vt);
+      }
+      auto vnext = [&](int ts, int db) { return SRC == kSrcVt ? vfrag(vbase, ts, db) : u32x4{0u, 0u, 0u, 0u}; };
+      auto vuse = [&](const u32x4& ahead, int ts, int db) { return SRC == kSrcVt ? ahead : vof8(vt, ts, db); };
       float ex[2][8];
       auto E = [&](int u, int h) {                         // four exponentials of key step u
 #pragma unroll
@@ -563,26 +390,35 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
         for (int q = 0; q < 4; ++q) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[u & 1][q]), ones, l_run, false);
       };
       const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
-      const bf16_t* kb3 = kg + (long long)(kv_lo + tk3 * TK) * p.ldks;
-      const bf16_t* vb1 = vg + kv_lo + tv1 * TK;
-      const bool krag = kv_lo + tk3 * TK + TK > p.L;
+      const bf16_t *kp[2], *vp[2];
+      if constexpr (SRC == kSrcVt) {
+        const bf16_t* vb1 = vg + kv_lo + tv1 * TK;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) { kp[j] = kptr(tk3, j); vp[j] = vb1 + vofs[j]; }
+      } else {
+        const Rows r3 = rows_of(kv_lo + tk3 * TK), r1 = rows_of(kv_lo + tv1 * TK);
+#pragma unroll
+        for (int j = 0; j < 2; ++j) { kp[j] = r3.k[j]; vp[j] = r1.v[j]; }
+      }
       auto dma_k = [&](int j) {
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kb3 + (krag ? kofr[j] : kofs[j])), DF_LPTR(smem + kdst + (2 * wave + j) * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(DF_GPTR(kp[j]), DF_LPTR(smem + kdst + (2 * wave + j) * 1024), 16, 0, 0);
       };
       auto dma_v = [&](int j) {
-        __builtin_amdgcn_global_load_lds(DF_GPTR(vb1 + vofs[j]), DF_LPTR(smem + vdst + (2 * wave + j) * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(DF_GPTR(vp[j]), DF_LPTR(smem + vdst + (2 * wave + j) * 1024), 16, 0, 0);
       };
       DF_FENCE;
-      pv_mfma(f[0], 0, 0); f[5] = vfrag(vbase, 2, 1); E(0, 0); DF_FENCE;
-      pv_mfma(f[1], 0, 1); f[6] = kfrag(kbase, 0, 0); E(0, 1); dma_k(0); DF_FENCE;
-      pv_mfma(f[2], 1, 0); f[7] = vfrag(vbase, 3, 0); C(0); dma_k(1); DF_FENCE;
-      pv_mfma(f[3], 1, 1); f[8] = kfrag(kbase, 1, 0); E(1, 0); DF_FENCE;
-      pv_mfma(f[4], 2, 0); f[9] = vfrag(vbase, 3, 1); E(1, 1); DF_FENCE;
-      pv_mfma(f[5], 2, 1); f[10] = kfrag(kbase, 2, 0); C(1); S(0); DF_FENCE;
+      if constexpr (SRC != kSrcVt) { E(0, 0); E(0, 1); DF_FENCE; varrive(vt, H1{}); DF_FENCE; }
+      pv_mfma(vuse(f[0], 0, 0), 0, 0); f[5] = vnext(2, 1); if constexpr (SRC == kSrcVt) E(0, 0); DF_FENCE;
+      pv_mfma(vuse(f[1], 0, 1), 0, 1); f[6] = kfrag(kbase, 0, 0); if constexpr (SRC == kSrcVt) E(0, 1); dma_k(0); DF_FENCE;
+      pv_mfma(vuse(f[2], 1, 0), 1, 0); f[7] = vnext(3, 0); C(0); dma_k(1); DF_FENCE;
+      pv_mfma(vuse(f[3], 1, 1), 1, 1); f[8] = kfrag(kbase, 1, 0); E(1, 0); DF_FENCE;
+      if constexpr (SRC != kSrcVt) { varrive(vt, H2{}); DF_FENCE; }
+      pv_mfma(vuse(f[4], 2, 0), 2, 0); f[9] = vnext(3, 1); E(1, 1); DF_FENCE;
+      pv_mfma(vuse(f[5], 2, 1), 2, 1); f[10] = kfrag(kbase, 2, 0); C(1); S(0); DF_FENCE;
       s_mfma(f[6], 0, 0); f[11] = kfrag(kbase, 3, 0); E(2, 0); DF_FENCE;
-      pv_mfma(f[7], 3, 0); f[12] = kfrag(kbase, 0, 1); E(2, 1); S(1); DF_FENCE;
+      pv_mfma(vuse(f[7], 3, 0), 3, 0); f[12] = kfrag(kbase, 0, 1); E(2, 1); S(1); DF_FENCE;
       s_mfma(f[8], 1, 0); f[13] = kfrag(kbase, 1, 1); C(2); dma_v(0); DF_FENCE;
-      pv_mfma(f[9], 3, 1); f[14] = kfrag(kbase, 2, 1); E(3, 0); DF_FENCE;
+      pv_mfma(vuse(f[9], 3, 1), 3, 1); f[14] = kfrag(kbase, 2, 1); E(3, 0); DF_FENCE;
       s_mfma(f[10], 2, 0); f[15] = kfrag(kbase, 3, 1); E(3, 1); dma_v(1); DF_FENCE;
       s_mfma(f[11], 3, 0); S(2); DF_FENCE;
       s_mfma(f[12], 0, 1); C(3); DF_FENCE;
@@ -604,11 +440,13 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   }
   // the last tile's values
   sync_tile(std::integral_constant<int, 0>{});
+  VTile vlast;
+  if constexpr (SRC != kSrcVt) { vrequest(vbase, vlast); varrive(vlast, H1{}); varrive(vlast, H2{}); }
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
     const int ts = i >> 1;
-    u32x4 v = vfrag(vbase, ts, i & 1);
-    if (ragged) {                                          // keys beyond the range: P is 0, V must be finite
+    u32x4 v = SRC == kSrcVt ? vfrag(vbase, ts, i & 1) : vof8(vlast, ts, i & 1);
+    if (SRC == kSrcVt && ragged) {                         // keys beyond the range: P is 0, V must be finite
       const int key = kv_lo + (ntiles - 1) * TK + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
       if (key + 0 >= kv_hi) v.x = 0u; else if (key + 1 >= kv_hi) v.x &= 0xffffu;
       if (key + 2 >= kv_hi) v.y = 0u; else if (key + 3 >= kv_hi) v.y &= 0xffffu;
@@ -1061,18 +899,19 @@ __global__ __launch_bounds__(256) void attn_f32(AttnParams p) {
 
 // Predicted time (microseconds) of attn_pipe_d64 with the keys in `ns` ranges, fitted on 22 shapes between 64 x 256 and
 // 7200 x 57600 with 1 to 12 ranges each.  A compute unit works through its workgroups' 64-key tiles at nearly the same
-// rate whether one or two are resident (0.65 and 0.53 us per tile), so the time follows the most loaded unit; ranges
-// even out the load, and cost a second kernel and the float partials (written and read at 2.9 TB/s together).
-double pipe_us(int B, int Lq, int L, int heads, int ns) {
+// rate whether one or two are resident (0.65 and 0.53 us per tile; with the row gather, `rows`, 0.76 and 0.58), so the time
+// follows the most loaded unit; ranges even out the load, and cost a second kernel and the float partials (written and read
+// at 2.9 TB/s together).
+double pipe_us(int B, int Lq, int L, int heads, bool rows, int ns) {
   const long long blocks = (long long)cdiv(Lq, 128) * heads * B;
   const long long per_cu = (blocks * ns + 255) / 256;
   const double tiles = cdiv(cdiv(L, ns), 64);
-  return 4.5 + tiles * (per_cu == 1 ? 0.65 : 0.53 * per_cu) +
+  return 4.5 + tiles * (per_cu == 1 ? (rows ? 0.76 : 0.65) : (rows ? 0.58 : 0.53) * per_cu) +
          (ns > 1 ? 2.5 + (double)B * heads * Lq * ns * 512.0 / 2.9e6 : 0.0);
 }
 
 // Number of key ranges
-int pick_splits(int B, int Lq, int L, int heads) {
+int pick_splits(int B, int Lq, int L, int heads, bool rows) {
 #ifdef DF_TUNING
   const int forced = tune_env("DF_ATTN_SPLITS") ? atoi(tune_env("DF_ATTN_SPLITS")) : 0;
   if (forced > 0) return (L / forced >= 64) ? forced : 1;
@@ -1081,7 +920,7 @@ int pick_splits(int B, int Lq, int L, int heads) {
   double best_us = 1e30;
   for (int ns = 1; ns <= 16; ++ns) {
     if (ns > 1 && L / ns < 128) break;
-    const double us = pipe_us(B, Lq, L, heads, ns);
+    const double us = pipe_us(B, Lq, L, heads, rows, ns);
     if (us < best_us - 1e-9) { best_us = us; best = ns; }
   }
   return best;
@@ -1100,7 +939,7 @@ extern "C" __attribute__((visibility("default"))) int df_tune_attn_trace(long lo
 #endif
 
 size_t attention_scratch_bytes(int B, int Lq, int L, int heads, int d) {
-  const int ns = pick_splits(B, Lq, L, heads);
+  const int n0 = pick_splits(B, Lq, L, heads, false), n1 = pick_splits(B, Lq, L, heads, true), ns = n0 > n1 ? n0 : n1;
   if (ns == 1) return kScratchCounterBytes;
   return kScratchCounterBytes + (size_t)ns * B * heads * Lq * (d + 2) * sizeof(float) + 256;
 }
@@ -1116,6 +955,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   p.q = a.q; p.kf = a.k_fresh; p.vf = a.v_fresh; p.ks = a.k_stale; p.vs = a.v_stale; p.out = a.out;
   p.B = a.B; p.Lq = a.Lq; p.L = a.L; p.heads = a.heads; p.own_lo = a.own_lo; p.own_n = a.own_n;
   p.own_period = a.own_period;
+  p.own_magic = a.own_period > 1 ? (unsigned int)((1ULL << 32) / (unsigned int)a.own_period) : 0xffffffffu;
   p.ldq = a.ldq; p.ldkf = a.ldkf; p.ldvf = a.ldvf; p.ldks = a.ldks; p.ldvs = a.ldvs; p.ldo = a.ldo;
   p.bsq = a.bsq; p.bskf = a.bskf; p.bsvf = a.bsvf; p.bsks = a.bsks; p.bsvs = a.bsvs; p.bso = a.bso;
   p.scale = a.scale;
@@ -1157,7 +997,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   const bool wave_fits = a.v_transposed && a.L >= 512 && (long long)cdiv(a.Lq, 32) * a.heads * a.B <= 256;
   if (wave_fits && (wave_env ? atoi(wave_env) != 0
                              : 4.7 + 1.93 * cdiv(cdiv(a.L, 64), 8) <
-                                   pipe_us(a.B, a.Lq, a.L, a.heads, pick_splits(a.B, a.Lq, a.L, a.heads)))) {
+                                   pipe_us(a.B, a.Lq, a.L, a.heads, false, pick_splits(a.B, a.Lq, a.L, a.heads, false)))) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
@@ -1176,7 +1016,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     DF_LAUNCH_CHECK();
     return DF_OK;
   }
-  int ns = pick_splits(a.B, a.Lq, a.L, a.heads);
+  int ns = pick_splits(a.B, a.Lq, a.L, a.heads, !a.v_transposed);
   if ((long long)a.B * ns > 65535) return DF_ESHAPE;
   if ((long long)a.B * a.heads * a.Lq * 16 >= (1LL << 31)) return DF_ESHAPE;   // the merge kernel indexes with 32 bits
   if (ns > 1) {
@@ -1199,13 +1039,14 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
     constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V^T tiles
-    if (a.q_scaled) hipLaunchKernelGGL((attn_pipe_d64<true>), dim3((unsigned)nwg), dim3(256), smem, st, p);
-    else hipLaunchKernelGGL((attn_pipe_d64<false>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    if (a.q_scaled) hipLaunchKernelGGL((attn_pipe_d64<true, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   } else {
     // 32-bit row offsets inside a 64-key tile
     if (a.ldkf >= (1 << 24) || a.ldvf >= (1 << 24) || a.ldks >= (1 << 24) || a.ldvs >= (1 << 24)) return DF_ESHAPE;
-    if (a.own_period > 0) hipLaunchKernelGGL(attn_bf16_d64<true>, dim3((unsigned)nwg), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL(attn_bf16_d64<false>, dim3((unsigned)nwg), dim3(256), 0, st, p);
+    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V tiles
+    if (a.own_period > 0) hipLaunchKernelGGL((attn_pipe_d64<false, kSrcPeriodic>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcRows>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   }
   DF_LAUNCH_CHECK();
   if (ns > 1) {

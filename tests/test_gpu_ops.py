@@ -235,6 +235,33 @@ def _attn_case(seed, B, L, C, N, patch, bf16, stale_std=0.5):
                 vs=rnd(vfull + normal(seed, "vn", (B, L, C), std=stale_std)))
 
 
+@pytest.mark.parametrize("axis", ["rows", "cols"])
+@pytest.mark.parametrize("B,H,W,C,N", [
+    (1, 3, 4, 64, 1),            # fewer keys than a tile, every key fresh
+    (1, 5, 26, 64, 2),           # 65 / 130 keys: a second tile of one / two keys
+    (2, 9, 21, 128, 3),          # own range starts and ends inside tiles, two batch items
+    (1, 16, 64, 64, 4),          # own ranges of whole tiles
+    (1, 40, 104, 192, 8),        # parts of the key range, ragged last one
+])
+def test_attention_displaced_tiles(B, H, W, C, N, axis):
+    say("attn tiles", B, H, W, C, N, axis)
+    if (H if axis == "rows" else W) % N:
+        H, W = W, H
+    heads, L = C // 64, H * W
+    rnd = lambda n, *sh: round_bf16(normal(23, n, sh))
+    ks, vs = rnd("ks", B, L, C), rnd("vs", B, L, C)
+    for i in sorted({0, N // 2, N - 1}):
+        q, kf, vf = rnd("q%d" % i, B, L // N, C), rnd("kf%d" % i, B, L // N, C), rnd("vf%d" % i, B, L // N, C)
+        args = (dev(q, True), dev(kf, True), dev(vf, True), dev(ks, True), dev(vs, True), heads)
+        if axis == "rows":
+            ref = ops.attn_displaced(q, kf, vf, ks, vs, heads, i, N)
+            o = df.attn_displaced(*args, i, N)
+        else:
+            ref = ops.attn_displaced(q, kf, vf, ks, vs, heads, i, N, split_axis=2, hw=(H, W))
+            o = df.attn_displaced_cols(*args, H, W, i, N)
+        check(host(o), ref, True, "attn tiles patch %d" % i, say=say)
+
+
 @pytest.mark.parametrize("Lq_total,N,C,heads", [(3, 1, 32, 1), (66, 2, 64, 1), (254, 2, 64, 2), (2050, 2, 64, 2), (1026, 1, 128, 2)])
 def test_attention_f32_edges(Lq_total, N, C, heads):
     """Fewer keys than a wave's step, ragged steps, and the form with four queries per workgroup (ragged last four)."""
