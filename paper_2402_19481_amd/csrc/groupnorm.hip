@@ -40,7 +40,7 @@ struct GnHalo {
   int cols, rows;   // cols != 0: vertical strips of rpp columns, the state holds boundary columns of `rows` pixels
 };
 
-// stores 4 or 8 bf16 values of pixel p (within its batch item), channels c0.., into the boundary-row state if the
+// stores 2, 4 or 8 bf16 values of pixel p (within its batch item), channels c0.., into the boundary-row state if the
 // pixel lies on the first or last row of its patch
 template <int V>
 __device__ __forceinline__ void halo_store(const GnHalo& h, int b, long long p, int C, int c0, const float* v) {
@@ -57,9 +57,11 @@ __device__ __forceinline__ void halo_store(const GnHalo& h, int b, long long p, 
       bf16_t* o = h.out + ((((long long)b * h.npatch + (h.patch0 + q)) * 2 + which) * h.rows + row) * C + c0;
       if constexpr (V == 8) {
         st_vec(o, v);
-      } else {
+      } else if constexpr (V == 4) {
         u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
         *reinterpret_cast<u32x2*>(o) = t;
+      } else {
+        *reinterpret_cast<unsigned int*>(o) = pack_bf2(v[0], v[1]);
       }
     }
     return;
@@ -82,9 +84,11 @@ __device__ __forceinline__ void halo_store(const GnHalo& h, int b, long long p, 
     bf16_t* o = h.out + ((((long long)b * h.npatch + patch) * 2 + which) * h.W + col) * C + c0;
     if constexpr (V == 8) {
       st_vec(o, v);
-    } else {
+    } else if constexpr (V == 4) {
       u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
       *reinterpret_cast<u32x2*>(o) = t;
+    } else {
+      *reinterpret_cast<unsigned int*>(o) = pack_bf2(v[0], v[1]);
     }
   }
 }
@@ -544,10 +548,40 @@ __global__ __launch_bounds__(1024) void gn_group_kernel(const Tin* __restrict__ 
   }
 }
 
+// V consecutive channels from / to memory
+template <int V, typename T>
+__device__ __forceinline__ void ld_chan(const T* p, float* v) {
+  if constexpr (sizeof(T) == 4) {
+    if constexpr (V == 4) ld_vec(p, v);
+    else { const float2 t = *reinterpret_cast<const float2*>(p); v[0] = t.x; v[1] = t.y; }
+  } else if constexpr (V == 4) {
+    const u32x2 t = *reinterpret_cast<const u32x2*>(p);
+    v[0] = __uint_as_float(t.x << 16); v[1] = __uint_as_float(t.x & 0xffff0000u);
+    v[2] = __uint_as_float(t.y << 16); v[3] = __uint_as_float(t.y & 0xffff0000u);
+  } else {
+    const unsigned int t = *reinterpret_cast<const unsigned int*>(p);
+    v[0] = __uint_as_float(t << 16); v[1] = __uint_as_float(t & 0xffff0000u);
+  }
+}
+template <int V, typename T>
+__device__ __forceinline__ void st_chan(T* p, const float* v) {
+  if constexpr (sizeof(T) == 4) {
+    if constexpr (V == 4) st_vec(p, v);
+    else *reinterpret_cast<float2*>(p) = make_float2(v[0], v[1]);
+  } else if constexpr (V == 4) {
+    const u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+    *reinterpret_cast<u32x2*>(p) = t;
+  } else {
+    *reinterpret_cast<unsigned int*>(p) = pack_bf2(v[0], v[1]);
+  }
+}
+
 // The same for one segment whose share per lane is at most NV pixels: every lane requests all its pixels at once
 // (one memory round trip instead of one per pass) and keeps them in registers for the normalisation, so x is read
-// once.
-template <typename Tin, typename Tout, int NV>
+// once.  V channels per lane: 4, or 2 where the group's channel count allows no more (320 channels in 32 groups).
+// Bound by two round trips and a workgroup's share of the load path; the two-launch path costs ~11 us however small the
+// tensor is: 16 x 64 x 320 12.1 -> 6.7 us, 16 x 64 x 1280 11.6 -> 10.0.
+template <typename Tin, typename Tout, int NV, int V>
 __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restrict__ x, Tout* __restrict__ y,
                                                             const float* stale, float* sums_out,
                                                             const float* __restrict__ gamma, const float* __restrict__ beta,
@@ -557,43 +591,38 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   __shared__ float s_mr[3];
   const int g = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
-  const int cg = C / G, cgv = cg >> 2;
+  const int cg = C / G, cgv = cg / V;
   const int ppass = blockDim.x / cgv;
   const int cv = tid % cgv, psub = tid / cgv;
   const bool active = psub < ppass;
-  const int c0 = g * cg + cv * 4;
+  const int c0 = g * cg + cv * V;
   const long long base = (long long)b * pix;
   const float piv = Elem<Tin>::ld(x + base * C + g * cg);     // sums are taken of x - piv
   // everything that does not depend on x is requested first: affine parameters and the cached sums
-  float gm[4] = {0.f, 0.f, 0.f, 0.f}, bt[4] = {0.f, 0.f, 0.f, 0.f};
-  if (active) { ld_vec(gamma + c0, gm); ld_vec(beta + c0, bt); }
+  float gm[V], bt[V];
+#pragma unroll
+  for (int i = 0; i < V; ++i) { gm[i] = 0.f; bt[i] = 0.f; }
+  if (active) { ld_chan<V>(gamma + c0, gm); ld_chan<V>(beta + c0, bt); }
   double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
   if (tid < 64)
     gn_stale_wave((N == 1 && stat_mode != DF_GN_STALE) ? nullptr : stale, b, g, B, G, N, patch_idx, lane, st_s, st_q,
                   own_s, own_q);
-  float v[NV][4];
+  float v[NV][V];
   float a = 0.f, q = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int p = psub + k * ppass;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[k][i] = 0.f;
+    for (int i = 0; i < V; ++i) v[k][i] = 0.f;
     if (active && p < pix) {
-      const Tin* src = x + (base + p) * C + c0;
-      if constexpr (sizeof(Tin) == 4) {
-        ld_vec(src, v[k]);
-      } else {
-        const u32x2 t = *reinterpret_cast<const u32x2*>(src);
-        v[k][0] = __uint_as_float(t.x << 16); v[k][1] = __uint_as_float(t.x & 0xffff0000u);
-        v[k][2] = __uint_as_float(t.y << 16); v[k][3] = __uint_as_float(t.y & 0xffff0000u);
-      }
+      ld_chan<V>(x + (base + p) * C + c0, v[k]);
     }
   }
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     if (!(active && psub + k * ppass < pix)) continue;          // absent pixels hold zeros, not the pivot
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { const float d = v[k][i] - piv; a += d; q = fmaf(d, d, q); }
+    for (int i = 0; i < V; ++i) { const float d = v[k][i] - piv; a += d; q = fmaf(d, d, q); }
   }
   s_s[tid] = a; s_q[tid] = q;
   __syncthreads();
@@ -616,9 +645,9 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   __syncthreads();
   if (!active) return;
   const float mean = s_mr[0], mean_lo = s_mr[1], rstd = s_mr[2];
-  float sc[4], sh[4];
+  float sc[V], sh[V];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < V; ++i) {
     sc[i] = rstd * gm[i];
     sh[i] = bt[i];
   }
@@ -626,21 +655,18 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   for (int k = 0; k < NV; ++k) {
     const int p = psub + k * ppass;
     if (p >= pix) continue;
-    float o4[4];
+    float o4[V];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < V; ++i) {
       const float t = fmaf((v[k][i] - mean) - mean_lo, sc[i], sh[i]);
       o4[i] = silu ? silu_f(t) : t;
     }
     const long long m = base + p;
     Tout* o = y + m * C + c0;
     if (packed) o = y + (((m >> 5) * (C >> 4) + (c0 >> 4)) * 64 + (m & 31) + 32 * ((c0 >> 3) & 1)) * 8 + (c0 & 7);
-    if constexpr (sizeof(Tout) == 4) {
-      st_vec(o, o4);
-    } else {
-      u32x2 t = {pack_bf2(o4[0], o4[1]), pack_bf2(o4[2], o4[3])};
-      *reinterpret_cast<u32x2*>(o) = t;
-      if (halo.out) halo_store<4>(halo, b, p, C, c0, o4);
+    st_chan<V>(o, o4);
+    if constexpr (sizeof(Tout) == 2) {
+      if (halo.out) halo_store<V>(halo, b, p, C, c0, o4);
     }
   }
 }
@@ -700,19 +726,28 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
     const int cg = a.C / a.G;
     const long long per_group = pix_seg * a.nseg * cg;
     static const bool no_fused = tune_env("DF_GN_3K") != nullptr;   // tuning aid
-    const int ppass = (cg % 4 == 0 && cg / 4 <= 1024) ? 1024 / (cg / 4) : 0;
-    const bool fits_regs = a.nseg == 1 && pix_seg <= (long long)ppass * 8;
-    if (!no_fused && cg % 4 == 0 && cg / 4 <= 1024 && (fits_regs || per_group <= kGnGroupMaxElems)) {
+    // channels per lane of the form that keeps its pixels in registers, and pixels per pass of its 1024 lanes
+    const int v = cg % 4 == 0 ? 4 : cg % 2 == 0 ? 2 : 0;
+    const int ppass = (v && cg / v <= 1024) ? 1024 / (cg / v) : 0;
+    // up to 16 pixels per lane (a workgroup's loads then take as long as the second launch would)
+    const int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? (pix_seg <= (long long)ppass * 8 ? 8 : 16) : 0;
+    if (!no_fused && (nv || (cg % 4 == 0 && cg / 4 <= 1024 && per_group <= kGnGroupMaxElems))) {
       dim3 grid(a.G, a.B);
-      if (fits_regs) {
-        // one patch, at most 8 pixels per lane: single read of x
-#define DF_GN_REG(TI, TO)                                                                                             \
-  hipLaunchKernelGGL((gn_group_reg_kernel<TI, TO, 8>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale,     \
+      if (nv) {
+        // one patch: single read of x
+#define DF_GN_REG(TI, TO, NVV, VV)                                                                                    \
+  hipLaunchKernelGGL((gn_group_reg_kernel<TI, TO, NVV, VV>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,  \
                      a.silu, a.y_packed, halo)
-        if (a.in_dtype == DF_BF16) DF_GN_REG(bf16_t, bf16_t);
-        else if (a.out_dtype == DF_BF16) DF_GN_REG(float, bf16_t);
-        else DF_GN_REG(float, float);
+#define DF_GN_REG_T(NVV, VV)                                                                                          \
+  {                                                                                                                   \
+    if (a.in_dtype == DF_BF16) DF_GN_REG(bf16_t, bf16_t, NVV, VV);                                                    \
+    else if (a.out_dtype == DF_BF16) DF_GN_REG(float, bf16_t, NVV, VV);                                               \
+    else DF_GN_REG(float, float, NVV, VV);                                                                            \
+  }
+        if (v == 4) { if (nv == 8) DF_GN_REG_T(8, 4) else DF_GN_REG_T(16, 4) }
+        else { if (nv == 8) DF_GN_REG_T(8, 2) else DF_GN_REG_T(16, 2) }
+#undef DF_GN_REG_T
 #undef DF_GN_REG
         DF_LAUNCH_CHECK();
         return DF_OK;

@@ -108,6 +108,26 @@ def test_groupnorm_shapes(B, H, W, C, G, N, patch, bf16):
         assert rel_l2(host(fs), ref_fs) < 1e-5
 
 
+@pytest.mark.parametrize("R,W,C,G,bf16", [
+    (1, 1, 320, 32, True),       # ten channels per group, two per lane: a single pixel
+    (8, 204, 320, 32, True),     # the most pixels of eight per lane
+    (23, 71, 320, 32, False),    # one more: sixteen per lane
+    (16, 204, 320, 32, True),    # the most of sixteen
+    (5, 653, 320, 32, True),     # one more: two launches
+    (17, 48, 1280, 32, False),   # four channels per lane: the most of eight, ..
+    (19, 43, 1280, 32, True),    # .. one more
+    (1, 1632, 1280, 32, False),
+    (3, 5, 12, 2, False),        # six channels per group
+])
+def test_groupnorm_pixels_in_registers(R, W, C, G, bf16):
+    say("gn registers", R, W, C, G, bf16)
+    full, st, gamma, beta = _gn_case(5, 2, 2 * R, W, C, G, 2, bf16)
+    ref, ref_fs = ops.groupnorm_stale(full[:, R:], st, gamma, beta, G, 1, 2, 1e-5, 0, True)
+    y, fs = df.groupnorm_stale(dev(full[:, R:], bf16), dev(st), dev(gamma), dev(beta), G, 1, 2, 1e-5, 0, True)
+    check(host(y), ref, bf16, "gn registers", say=say)
+    assert rel_l2(host(fs), ref_fs) < 1e-5
+
+
 @pytest.mark.parametrize("R,W,C,G,N,patch", [
     (8, 16, 64, 8, 2, 1),        # one launch, pixels held in registers
     (32, 128, 64, 4, 4, 2),      # one launch per group, two passes over the patch
