@@ -24,23 +24,35 @@ __device__ __forceinline__ void block_sync() {
 
 enum { EPI_PLAIN = 0, EPI_GEGLU = 1, EPI_QKV = 2, EPI_XA = 3 };
 
-// Geometry of a tile's epilogue: the accumulators go through LDS in passes of PI token fragment rows per wave.
+// Geometry of a tile's epilogue: the accumulators go through LDS in passes of R token fragment rows of the tile (row
+// i * WT + wt of the order is row i of the waves at wt).
 template <int WT, int WF, int TT, int TF, int KG, int OCC, bool LN>
 struct Epi {
   static constexpr int BT = WT * TT, BF = WF * TF;
   static constexpr int kStats = LN ? (KG * WF + 1) * BT * 32 * 2 * 4 : 0;
   static constexpr int kVecs = (LN ? 2 : 1) * BF * 32 * 4;
   static constexpr int kCap = 160 * 1024 / OCC - kStats - kVecs;
-  static constexpr int pass_bytes(int pi) { return KG * WT * pi * BF * 4096; }
+  static constexpr int pass_bytes(int r) { return KG * r * BF * 4096; }
   static constexpr int pick() {
-    for (int pi = TT; pi > 1; --pi)
-      if (TT % pi == 0 && pass_bytes(pi) <= kCap) return pi;
+    for (int r = BT; r > 1; --r)
+      if (BT % r == 0 && (r % WT == 0 || WT % r == 0) && pass_bytes(r) <= kCap) return r;
     return 1;
   }
-  static constexpr int PI = pick();
-  static constexpr int kBytes = pass_bytes(PI) + kStats + kVecs;
+  static constexpr int R = pick();
+  static constexpr int kBytes = pass_bytes(R) + kStats + kVecs;
 };
 
+// Linear layer on fragment-packed operands, a workgroup per output tile: BT x 32 tokens by BF x 32 features, the waves WT x WF
+// over it and KG over the k-steps of a stage.  The operands' 1 KB fragments go from memory to an LDS ring of ST stages by direct
+// loads, and from there to the waves without conflicts, since a fragment is in lane order.
+// What bounds it: a compute unit receives 25 - 33 bytes per cycle by direct loads (128 x 320 tile, K = 1280: 1750 cycles
+// per 64 of K by the loads alone, 1530 by the matrix instructions and LDS reads alone, 2230 together), so a tile is as fast
+// as its operand bytes per flop and the number of compute units that have one; then the epilogue (a quarter of the time at
+// K = 1280), which in the smaller tiles runs beside the other workgroup of the unit.  Hence a set of tiles, from 64 x 64 to
+// 256 x 320 with 320 a divisor of most layers' widths, and the choice by predicted time below.  With the stages requested
+// in parts between the matrix instructions and the 320-wide tiles, 1024 x 10240 x 1280 with GEGLU 46.6 -> 36.3 us, 1800
+// x 10240 x 1280 68 -> 62, 4096 x 5120 x 640 43.5 -> 39.9, 14400 x 640 x 2560 with residual 78 -> 61.  Four waves of 64 x
+// 160 instead of eight of 32 x 160: 40 us (one wave per SIMD issues the epilogue half as fast).
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
 __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(WParams p) {
   using E = Epi<WT, WF, TT, TF, KG, OCC, LN>;
@@ -60,8 +72,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   const int tok = lane & 31, g = lane >> 5;
   const int kg = wave / (WT * WF), wq = wave % (WT * WF), wt = wq % WT, wf = wq / WT;
   const int MT = (p.M + 31) >> 5, NF = p.N >> 5;
-  constexpr int JO = EPI == EPI_GEGLU ? TF / 2 : TF;   // output fragments per wave along the features
-  constexpr int BFO = WF * JO;
+  constexpr int BFO = EPI == EPI_GEGLU ? BF / 2 : BF;  // output fragments of the tile along the features
   const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO, nwg = MG * NG;
   int t = blockIdx.x;
   {
@@ -78,15 +89,14 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   }
   const int KF = p.K >> 4, KT = KF / BKF;
 
-  // fragment row of the weights behind row r (0 .. BF-1) of the tile (geglu: of a wave's TF rows the first half are
-  // value rows, the second half their gates)
+  // fragment row of the weights behind row r (0 .. BF-1) of the tile (geglu: the first half are value rows, the second
+  // half their gates)
   auto wrow = [&](int r) {
     int nt;
     if constexpr (EPI == EPI_GEGLU) {
-      const int w = r / TF, j = r - w * TF;
-      nt = ng * BFO + w * JO + (j < JO ? j : j - JO);
+      nt = ng * BFO + (r < BFO ? r : r - BFO);
       if (nt > NF - 1) nt = NF - 1;
-      return j < JO ? nt : NF + nt;
+      return r < BFO ? nt : NF + nt;
     }
     nt = ng * BF + r;
     return nt < NF ? nt : NF - 1;
@@ -117,7 +127,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   };
 
   // per-feature vectors of the tile (norm scale / shift, or bias): requested now, parked in LDS for the epilogue
-  constexpr int NV = BF * 32 / (64 * NW) > 0 ? BF * 32 / (64 * NW) : 1;
+  constexpr int NV = (BF * 32 + 64 * NW - 1) / (64 * NW);
   float vs[NV], vt[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) {
@@ -200,7 +210,6 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   using I1 = std::integral_constant<int, 1>;
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
   using I2 = std::integral_constant<int, 2>;
-  using I3 = std::integral_constant<int, 3>;
   using All = std::integral_constant<int, -1>;
   if constexpr (ST >= 4) {
     // Stage kt + ST - 1 is requested in parts between the matrix instructions of stage kt
@@ -258,9 +267,9 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   }
 
   // ---- epilogue: the operand ring is free ----
-  constexpr int PI = E::PI;
-  f32x4* red = reinterpret_cast<f32x4*>(smem);         // [KG][WT*PI rows][BF][2 f][2 halves][64 lanes]
-  float* s_part = reinterpret_cast<float*>(smem + E::pass_bytes(PI));   // [KG*WF][BT*32][2] partial (sum, sum of squares)
+  constexpr int R = E::R;
+  f32x4* red = reinterpret_cast<f32x4*>(smem);         // [KG][R rows][BF][2 f][2 halves][64 lanes]
+  float* s_part = reinterpret_cast<float*>(smem + E::pass_bytes(R));   // [KG*WF][BT*32][2] partial (sum, sum of squares)
   float* s_mr = s_part + (LN ? KG * WF * BT * 64 : 0);  // [BT*32][2] mean, rstd
   float* s_t = s_part + E::kStats / 4;                 // [BF*32] shift / bias
   float* s_s = s_t + BF * 32;                          // [BF*32] scale sums (folded LayerNorm)
@@ -282,16 +291,17 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     }
   }
 #pragma unroll 1
-  for (int pass = 0; pass < TT / PI; ++pass) {
+  for (int pass = 0; pass < BT / R; ++pass) {
     if (pass > 0) __syncthreads();                     // the previous pass has been read
 #pragma unroll
     for (int i = 0; i < TT; ++i) {
-      if (i / PI != pass) continue;                    // (uniform; accumulator indices stay compile-time)
+      const int row = i * WT + wt - pass * R;          // (uniform; accumulator indices stay compile-time)
+      if (row < 0 || row >= R) continue;
 #pragma unroll
       for (int j = 0; j < TF; ++j)
 #pragma unroll
         for (int h = 0; h < 4; ++h)
-          red[(((kg * WT * PI + wt * PI + i % PI) * BF + wf * TF + j) * 4 + h) * 64 + lane] =
+          red[(((kg * R + row) * BF + wf * TF + j) * 4 + h) * 64 + lane] =
               f32x4{acc[i][j][4 * h], acc[i][j][4 * h + 1], acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]};
     }
     __syncthreads();
@@ -312,12 +322,12 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     }
     // 8 consecutive features 16f + 8g .. of tile fragment (row r of the pass, weight row jf), token tk of the row
     auto value8 = [&](int r, int trow, int jf, int f, int gg, int tk, float* v) {
-      f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+      f32x4 a, b;
 #pragma unroll
       for (int k = 0; k < KG; ++k) {
-        const f32x4* q = red + (((k * WT * PI + r) * BF + jf) * 4 + 2 * f) * 64 + tk + 32 * gg;
-        a += q[0];
-        b += q[64];
+        const f32x4* q = red + (((k * R + r) * BF + jf) * 4 + 2 * f) * 64 + tk + 32 * gg;
+        a = k ? a + q[0] : q[0];
+        b = k ? b + q[64] : q[64];
       }
       const float* tv = s_t + jf * 32 + 16 * f + 8 * gg;
       const f32x4 t0 = *reinterpret_cast<const f32x4*>(tv), t1 = *reinterpret_cast<const f32x4*>(tv + 4);
@@ -338,9 +348,9 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
       // items (token row of the pass, head): the head's normalised, rounded query is the B operand of S^T = K Q^T
       constexpr int HW = BF / 2;
 #pragma unroll 1
-      for (int it = wave; it < WT * PI * HW; it += NW) {
+      for (int it = wave; it < R * HW; it += NW) {
         const int hd = it % HW, r = it / HW;
-        const int trow = (r / PI) * TT + pass * PI + r % PI, mt = mg * BT + trow, head = ng * HW + hd;
+        const int q0 = pass * R + r, trow = (q0 % WT) * TT + q0 / WT, mt = mg * BT + trow, head = ng * HW + hd;
         if (mt >= MT || head * 2 >= NF) continue;
         const int bi = mt * 32 < p.xa_rows ? 0 : mt * 32 / p.xa_rows;
         const bf16x8* kv = p.xkv + (size_t)bi * p.xa_bstride + (size_t)head * (12 * XA) * 64 + lane;
@@ -421,11 +431,11 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
       // items (token row, output fragment, half of the row's tokens): lane -> token it*16 + lane%16, features 8*(lane/16) ..
       const int tl = lane & 15, f = lane >> 5, gg = (lane >> 4) & 1;
 #pragma unroll 1
-      for (int it = wave; it < WT * PI * BFO * 2; it += NW) {
+      for (int it = wave; it < R * BFO * 2; it += NW) {
         const int half = it & 1, jo = (it >> 1) % BFO, r = (it >> 1) / BFO;
-        const int trow = (r / PI) * TT + pass * PI + r % PI, mt = mg * BT + trow, nt = ng * BFO + jo;
+        const int q0 = pass * R + r, trow = (q0 % WT) * TT + q0 / WT, mt = mg * BT + trow, nt = ng * BFO + jo;
         if (mt >= MT || nt >= NF) continue;
-        const int jf = EPI == EPI_GEGLU ? (jo / JO) * TF + jo % JO : jo;
+        const int jf = jo;
         if constexpr (EPI == EPI_QKV) {
           const int n0 = nt * 32, sg = (n0 >= p.seg_w ? 1 : 0) + (n0 >= 2 * p.seg_w ? 1 : 0);
           if (p.seg_tr[sg]) {
@@ -437,7 +447,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
               float x = 0.f;
 #pragma unroll
               for (int k = 0; k < KG; ++k)
-                x += reinterpret_cast<const float*>(red + (((k * WT * PI + r) * BF + jf) * 4 + 2 * half + ((fe >> 2) & 1)) * 64 + tk2 +
+                x += reinterpret_cast<const float*>(red + (((k * R + r) * BF + jf) * 4 + 2 * half + ((fe >> 2) & 1)) * 64 + tk2 +
                                                     32 * ((fe >> 3) & 1))[fe & 3];
               if constexpr (LN) {
                 const float* mr = s_mr + (trow * 32 + tk2) * 2;
@@ -480,7 +490,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         value8(r, trow, jf, f, gg, tk, v);
         if constexpr (EPI == EPI_GEGLU) {
           float gt[8];
-          value8(r, trow, jf + JO, f, gg, tk, gt);
+          value8(r, trow, jf + BFO, f, gg, tk, gt);
 #pragma unroll
           for (int q = 0; q < 8; ++q) v[q] *= gelu_erf(gt[q]);
         }
@@ -532,7 +542,7 @@ template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC>
 int launch_tile_cfg(const WParams& p, hipStream_t st) {
   constexpr int BF = WF * TF;
   if (p.xkv) {
-    if constexpr (BF % 2 == 0) {
+    if constexpr (BF % 2 == 0 && WT * TT * BF <= 16) {   // (the registers of a larger tile's wave do not hold keys and values too)
       switch ((p.xa_keys + 31) / 32) {
         case 1: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 1>(p, st);
         case 2: return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_XA, true, 2>(p, st);
@@ -543,7 +553,7 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
     return DF_ESHAPE;
   }
   if (p.geglu) {
-    if constexpr (TF % 2 == 0) {
+    if constexpr (BF % 2 == 0) {
       if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, true, 0>(p, st);
       return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, false, 0>(p, st);
     }
@@ -569,28 +579,30 @@ namespace {
 
 // Tile shapes.  `slab` and `epi` are the microseconds of a round of workgroups per 64 of K and for prologue + epilogue
 // (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, `alone` the round of a workgroup that
-// has a unit to itself where two would fit; fitted to 16 token counts x 5 layers with weights that no cache holds.  Chosen by
-// them (and the wave-level kernel's, see wgemm.hip), those layers take 1 % more than with the best of all.
+// has a unit to itself where two would fit; fitted to 24 token counts x 5 layers with weights that no cache holds.  Chosen by
+// them (and the wave-level kernel's, see wgemm.hip), those layers take 1.5 % more than with the best of all.
 struct TileCfg { int bt, bf, occ; double base, slab, epi[4], alone; };
 constexpr TileCfg kTiles[] = {
-    {10, 8, 1, 2.34, 1.670, {18.4, 26.7, 22.7, 38.1}, 1.0},   // 320 x 256, eight waves of 160 x 64
+    {8, 10, 1, 0.00, 1.603, {17.3, 28.6, 26.3, 1e9}, 1.0},    // 256 x 320, eight waves of 64 x 160
     {4, 4, 2, 3.77, 1.078, {3.3, 5.7, 4.2, 7.4}, 0.70},       // 128 x 128, eight waves of 32 x 64, two workgroups per unit
     {4, 4, 1, 1.80, 0.474, {5.3, 7.1, 6.0, 8.4}, 1.0},        // 128 x 128, four ring stages
     {2, 4, 2, 3.90, 0.620, {3.0, 5.7, 2.9, 8.3}, 0.62},       // 64 x 128, two k-groups, two workgroups per unit
     {2, 2, 2, 2.30, 0.432, {1e9, 3.3, 1.7, 7.3}, 0.86},       // 64 x 64, two k-groups, two workgroups per unit
     {2, 2, 1, 2.50, 0.227, {1e9, 3.0, 1.9, 6.6}, 1.0},        // 64 x 64, two k-groups, four stages of 128
+    {4, 10, 1, 1.43, 0.947, {10.4, 15.4, 13.8, 1e9}, 1.0},    // 128 x 320, eight waves of 32 x 160
 };
 
 }  // namespace
 
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
   switch (cfg) {
-    case 0: return launch_tile_cfg<2, 4, 5, 2, 1, 4, 2, 1>(p, st);
+    case 0: return launch_tile_cfg<4, 2, 2, 5, 1, 2, 4, 1>(p, st);
     case 1: return launch_tile_cfg<4, 2, 1, 2, 1, 4, 2, 2>(p, st);
     case 2: return launch_tile_cfg<4, 2, 1, 2, 1, 4, 4, 1>(p, st);
     case 3: return launch_tile_cfg<2, 2, 1, 2, 2, 2, 3, 2>(p, st);
     case 4: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 2, 2>(p, st);
     case 5: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 4, 1>(p, st);
+    case 6: return launch_tile_cfg<4, 2, 1, 5, 1, 2, 5, 1>(p, st);
     default: return DF_ESHAPE;
   }
 }

@@ -35,19 +35,20 @@ __device__ __forceinline__ float silu_f(float x) {
 }
 
 // GELU in its exact (erf) form, 0.5 x (1 + erf(x / sqrt 2)).  erfc(|z|) = t (a1 + t (a2 + t (a3 + t (a4 + t a5))))
-// exp(-z^2) with t = 1 / (1 + p |z|) (Abramowitz & Stegun 7.1.26: absolute error below 1.5e-7, the size of float
-// rounding of the result); for negative arguments 1 + erf(z) is erfc(|z|) itself, so nothing cancels.  A dozen
-// instructions per value where the library erff takes several times that; the GEGLU epilogues are otherwise bounded
-// by this function.
+// exp(-z^2) with z = x / sqrt 2, t = 1 / (1 + p |z|) (Abramowitz & Stegun 7.1.26: absolute error below 1.5e-7, the size of
+// float rounding of the result).  With e = erfc(|z|) / 2 the result is max(x, 0) - |x| e for both signs, and for negative
+// arguments nothing cancels.  The constants below have the 1/2, the 1/sqrt 2 and log2(e) in them: thirteen instructions per
+// value, where the library erff takes several times that; the GEGLU epilogues are otherwise bounded by this function.
 __device__ __forceinline__ float gelu_erf(float x) {
-  const float z = fabsf(x) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-  float poly = fmaf(t, 1.061405429f, -1.453152027f);
-  poly = fmaf(poly, t, 1.421413741f);
-  poly = fmaf(poly, t, -0.284496736f);
-  poly = fmaf(poly, t, 0.254829592f);
-  const float erfc_abs = poly * t * __builtin_amdgcn_exp2f(-z * z * 1.4426950408889634f);
-  return 0.5f * x * (x >= 0.f ? 2.0f - erfc_abs : erfc_abs);
+  const float ax = fabsf(x);
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.23164189f, ax, 1.0f));
+  float poly = fmaf(t, 0.5307027145f, -0.7265760135f);
+  poly = fmaf(poly, t, 0.7107068705f);
+  poly = fmaf(poly, t, -0.1422483685f);
+  poly = fmaf(poly, t, 0.127414796f);
+  const float u = x * 0.84932180f;
+  const float e = poly * t * __builtin_amdgcn_exp2f(-(u * u));
+  return fmaf(-ax, e, fmaxf(x, 0.f));
 }
 
 template <typename T> struct Elem;

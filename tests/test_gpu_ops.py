@@ -520,7 +520,9 @@ def test_linear_packed(M, N, K, variant):
     (577, 5120, 640, "ln_geglu"),
     (600, 5120, 640, "geglu"),
     (3000, 640, 2560, "plain"),        # two k-groups added through LDS
-    (1800, 10240, 1280, "ln_geglu"),   # the 320 x 256 tile, ragged
+    (1800, 10240, 1280, "ln_geglu"),   # the 256 x 320 tile, ragged
+    (993, 10240, 1280, "ln_geglu"),    # the 128 x 320 tile, one token in the last row
+    (14367, 640, 640, "plain"),        # the 128 x 320 tile, ragged, residual
 ])
 def test_linear_packed_tiles(M, N, K, variant):
     test_linear_packed(M, N, K, variant)
