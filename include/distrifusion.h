@@ -191,6 +191,10 @@ int df_linear(const void* x, const void* w, const float* bias, const float* resi
  *     geglu != 0: w holds N/2 value rows then N/2 gate rows; y [M, N/2] = value * gelu(gate).
  *     Outputs (any subset, at least one): y_f32 row-major float (residual may alias it), y_packed packed bf16 (all
  *     ceil(M/32)*32 rows are written), y_rows row-major bf16.
+ *   df_linear_packed_scratch  df_linear_packed (no LayerNorm, no GEGLU) with a region of the caller, 256-byte aligned,
+ *     in which a layer of few tiles and long K keeps the sums of its parts of K, as the step does; such a layer returns
+ *     DF_ENOMEM if the region is too small.  df_linear_packed_scratch_bytes always suffices.  Calls that overlap need
+ *     regions of their own.
  */
 size_t df_packed_bytes(long long rows, long long K);
 int df_pack_rows(const void* x, void* packed, int M, int K, void* stream);
@@ -198,6 +202,10 @@ int df_pack_linear_weight(const void* w, const float* gamma, void* packed, int N
 int df_linear_packed(const void* xp, const void* wp, const float* bias, const float* ln_s, const float* ln_t,
                      float ln_eps, const float* residual, float* y_f32, void* y_packed, void* y_rows, int M, int N,
                      int K, int geglu, void* stream);
+size_t df_linear_packed_scratch_bytes(int M, int N);
+int df_linear_packed_scratch(const void* xp, const void* wp, const float* bias, const float* residual, float* y_f32,
+                             void* y_packed, void* y_rows, int M, int N, int K, void* scratch, size_t scratch_bytes,
+                             void* stream);
 
 /*
  * The two attention forms the UNet step runs internally, exposed for tests and measurements.

@@ -77,6 +77,9 @@ def lib():
     L.df_pack_rows.argtypes = [vp, vp, i, i, vp]
     L.df_pack_linear_weight.argtypes = [vp, vp, vp, i, i, vp]
     L.df_linear_packed.argtypes = [vp, vp, vp, vp, vp, f, vp, vp, vp, vp, i, i, i, i, vp]
+    L.df_linear_packed_scratch.argtypes = [vp, vp, vp, vp, vp, vp, vp, i, i, i, vp, sz, vp]
+    L.df_linear_packed_scratch_bytes.restype = sz
+    L.df_linear_packed_scratch_bytes.argtypes = [i, i]
     cfgp = ctypes.POINTER(UNetCfgC)
     if not hasattr(L, "df_patch_unet_step"):
         raise DfError("libdistrifusion.so is stale: rebuild it")
@@ -108,7 +111,7 @@ def lib():
     L.df_unet_profile_kernel.restype = i
     for name in ("df_copy_bytes", "df_buffer_refresh", "df_groupnorm_stale", "df_conv3x3_halo", "df_attn_displaced",
                  "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv",
-                 "df_cross_attn_packed", "df_packed_bytes", "df_pack_rows", "df_pack_linear_weight", "df_linear_packed", "df_unet_num_weights", "df_unet_weight_info", "df_unet_create",
+                 "df_cross_attn_packed", "df_packed_bytes", "df_pack_rows", "df_pack_linear_weight", "df_linear_packed", "df_linear_packed_scratch", "df_unet_num_weights", "df_unet_weight_info", "df_unet_create",
                  "df_unet_stale_lookup", "df_unet_num_stale", "df_unet_stale_name", "df_patch_unet_step",
                  "df_unet_profile_enable", "df_unet_set_graph", "df_unet_profile_reset", "df_unet_profile_num_classes",
                  "df_unet_profile_read"):
@@ -315,10 +318,15 @@ def pack_linear_weight(w, gamma=None):
     return out
 
 
+def linear_packed_scratch(M, N, device):
+    return torch.empty(lib().df_linear_packed_scratch_bytes(M, N), dtype=torch.uint8, device=device)
+
+
 def linear_packed(xp, wp, M, N, K, bias=None, ln_s=None, ln_t=None, ln_eps=1e-5, residual=None, geglu=False,
-                  want=("f32",)):
+                  want=("f32",), scratch=None):
     """Linear layer on packed operands; returns a dict of the requested outputs: "f32" [M,N'] float row-major,
-    "packed" packed bf16, "rows" [M,N'] bf16 row-major (N' = N/2 with geglu)."""
+    "packed" packed bf16, "rows" [M,N'] bf16 row-major (N' = N/2 with geglu).
+    scratch: uint8 tensor of the caller (linear_packed_scratch) for a plain layer that may add parts of K in it."""
     No = N // 2 if geglu else N
     dev = xp.device
     outs = {}
@@ -328,6 +336,13 @@ def linear_packed(xp, wp, M, N, K, bias=None, ln_s=None, ln_t=None, ln_eps=1e-5,
         outs["packed"] = torch.empty(lib().df_packed_bytes(M, No) // 2, dtype=torch.bfloat16, device=dev)
     if "rows" in want:
         outs["rows"] = torch.empty(M, No, dtype=torch.bfloat16, device=dev)
+    if scratch is not None:
+        if ln_s is not None or geglu:
+            raise DfError("linear_packed: scratch is for plain layers")
+        _check(lib().df_linear_packed_scratch(_ptr(xp), _ptr(wp), _ptr(bias), _ptr(residual), _ptr(outs.get("f32")),
+                                              _ptr(outs.get("packed")), _ptr(outs.get("rows")), M, N, K, _ptr(scratch),
+                                              scratch.numel(), _stream()))
+        return outs
     _check(lib().df_linear_packed(_ptr(xp), _ptr(wp), _ptr(bias), _ptr(ln_s), _ptr(ln_t), ln_eps, _ptr(residual),
                                   _ptr(outs.get("f32")), _ptr(outs.get("packed")), _ptr(outs.get("rows")), M, N, K,
                                   1 if geglu else 0, _stream()))

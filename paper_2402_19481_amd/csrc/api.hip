@@ -279,6 +279,19 @@ int df_linear_packed(const void* xp, const void* wp, const float* bias, const fl
   return launch_wgemm(a, (hipStream_t)stream);
 }
 
+size_t df_linear_packed_scratch_bytes(int M, int N) { return M > 0 && N > 0 ? wgemm_scratch_bytes(M, N) : 0; }
+
+int df_linear_packed_scratch(const void* xp, const void* wp, const float* bias, const float* residual, float* y_f32,
+                             void* y_packed, void* y_rows, int M, int N, int K, void* scratch, size_t scratch_bytes,
+                             void* stream) {
+  if (!xp || !wp || !scratch || ((uintptr_t)scratch % 256) || (!y_f32 && !y_packed && !y_rows)) return DF_EINVAL;
+  const Scratch s = {(char*)scratch, scratch_bytes};
+  WGemmArgs a = {};
+  a.Xp = xp; a.Wp = wp; a.M = M; a.N = N; a.K = K; a.bias = bias; a.residual = residual; a.ldr = N; a.out_f32 = y_f32;
+  a.ldo = N; a.out_packed = y_packed; a.out_rows = y_rows; a.ld_rows = N; a.scr = &s;
+  return launch_wgemm(a, (hipStream_t)stream);
+}
+
 int df_euler_update(float* x, const float* eps, float sigma, float sigma_next, long long n, void* stream) {
   if (!x || !eps) return DF_EINVAL;
   if (n < 0) return DF_ESHAPE;

@@ -22,7 +22,7 @@ __device__ __forceinline__ void block_sync() {
   asm volatile("" ::: "memory");
 }
 
-enum { EPI_PLAIN = 0, EPI_GEGLU = 1, EPI_QKV = 2, EPI_XA = 3 };
+enum { EPI_PLAIN = 0, EPI_GEGLU = 1, EPI_QKV = 2, EPI_XA = 3, EPI_PART = 4 };
 
 // Geometry of a tile's epilogue: the accumulators go through LDS in passes of R token fragment rows of the tile (row
 // i * WT + wt of the order is row i of the waves at wt).
@@ -87,7 +87,12 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     ng = r / gh;
     mg = m0 + r - ng * gh;
   }
-  const int KF = p.K >> 4, KT = KF / BKF;
+  const int KF = p.K >> 4;
+  int KT = KF / BKF, kt0 = 0;                          // stages of this workgroup, the first of them
+  if constexpr (EPI == EPI_PART) {
+    kt0 = (int)((long long)KT * blockIdx.y / gridDim.y);
+    KT = (int)((long long)KT * (blockIdx.y + 1) / gridDim.y) - kt0;
+  }
 
   // fragment row of the weights behind row r (0 .. BF-1) of the tile (geglu: the first half are value rows, the second
   // half their gates)
@@ -111,7 +116,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     int mt = mg * BT + row;
     if (mt > MT - 1) mt = MT - 1;                      // ragged last tile: re-read, never stored
     src[q] = (row < BT ? (const char*)p.Xp + (size_t)mt * KF * 1024 : (const char*)p.Wp + (size_t)wrow(row - BT) * KF * 1024) +
-             kk * 1024;
+             ((size_t)kt0 * BKF + kk) * 1024;
   }
   // loads of a stage: all (STEP < 0), or part STEP of KS
   auto issue = [&](int kt, int slot, auto stepc) {
@@ -136,7 +141,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     if (r < BF * 32) {
       const int n = wrow(r >> 5) * 32 + (r & 31);
       if constexpr (LN) { vs[q] = p.ln_s[n]; vt[q] = p.ln_t[n]; }
-      else if (p.bias) vt[q] = p.bias[n];
+      else if (EPI != EPI_PART && p.bias) vt[q] = p.bias[n];
     }
   }
   f32x16 acc[TT][TF];
@@ -264,6 +269,23 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     DF_SB; mm(kt * KS + KS - 1, I1{}); DF_SB;
     slot = nslot;
   }
+  }
+
+  if constexpr (EPI == EPI_PART) {
+    // the part's sums as they are: [part][token row][feature row][quarter][lane], 1 KB per store
+    static_assert(KG == 1, "one wave holds the sum of a part");
+    f32x4* d = p.partials + (size_t)blockIdx.y * MT * NF * 256 + lane;
+#pragma unroll
+    for (int i = 0; i < TT; ++i)
+#pragma unroll
+      for (int j = 0; j < TF; ++j) {
+        const int mt = mg * BT + wt * TT + i, nt = ng * BF + wf * TF + j;
+        if (mt >= MT || nt >= NF) continue;
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+          d[((size_t)mt * NF + nt) * 256 + h * 64] = f32x4{acc[i][j][4 * h], acc[i][j][4 * h + 1], acc[i][j][4 * h + 2], acc[i][j][4 * h + 3]};
+      }
+    return;
   }
 
   // ---- epilogue: the operand ring is free ----
@@ -509,6 +531,34 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   }
 }
 
+// Adds the parts of K in their order and finishes the layer: a wave per half of a fragment (token row, 16 features).
+// 1024 x 1280 in three parts: 6 us, bound by the 16 MB of sums.
+__global__ __launch_bounds__(256) void bgemm_sum_kernel(WParams p, int parts) {
+  const int MT = (p.M + 31) >> 5, NF = p.N >> 5, lane = threadIdx.x & 63;
+  const int u = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (u >= MT * NF * 2) return;
+  const int fr = u >> 1, f = u & 1, mt = fr / NF, nt = fr - mt * NF;
+  const int m = mt * 32 + (lane & 31), n = nt * 32 + 16 * f + 8 * (lane >> 5);
+  const f32x4* s = p.partials + (size_t)fr * 256 + f * 128 + lane;
+  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+  if (p.residual && m < p.M) {
+    a = *reinterpret_cast<const f32x4*>(p.residual + (long long)m * p.ldr + n);
+    b = *reinterpret_cast<const f32x4*>(p.residual + (long long)m * p.ldr + n + 4);
+  }
+#pragma unroll 4
+  for (int i = 0; i < parts; ++i) {
+    a += s[0];
+    b += s[64];
+    s += (size_t)MT * NF * 256;
+  }
+  if (p.bias) {
+    a += *reinterpret_cast<const f32x4*>(p.bias + n);
+    b += *reinterpret_cast<const f32x4*>(p.bias + n + 4);
+  }
+  const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+  wg_store_unit(p, mt, m, n, lane, v);
+}
+
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
 int launch_one(const WParams& pin, hipStream_t st) {
   constexpr int BT = WT * TT, BF = WF * TF, BFO = EPI == EPI_GEGLU ? BF / 2 : BF, NW = WT * WF * KG;
@@ -517,7 +567,8 @@ int launch_one(const WParams& pin, hipStream_t st) {
   const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO;
   const long long nwg = (long long)MG * NG;
   if ((p.K / 16) % (KS * KG)) return DF_ESHAPE;
-  const double conc = std::fmin((double)nwg / 8.0, 32.0 * OCC);
+  const int parts = EPI == EPI_PART ? p.parts : 1;
+  const double conc = std::fmin((double)nwg / 8.0, 32.0 * OCC / parts);
   int gm = (int)(std::sqrt(conc * BF / BT) + 0.5);
   if (gm < 1) gm = 1;
   if (gm > MG) gm = MG;
@@ -533,8 +584,12 @@ int launch_one(const WParams& pin, hipStream_t st) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)nwg), dim3(64 * NW), smem, st, p);
+  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)parts), dim3(64 * NW), smem, st, p);
   DF_LAUNCH_CHECK();
+  if constexpr (EPI == EPI_PART) {
+    hipLaunchKernelGGL(bgemm_sum_kernel, dim3((unsigned)((MT * NF * 2 + 3) / 4)), dim3(256), 0, st, p, parts);
+    DF_LAUNCH_CHECK();
+  }
   return DF_OK;
 }
 
@@ -568,6 +623,10 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
     }
     if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
     return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, false, 0>(q, st);
+  }
+  if (p.parts > 1) {
+    if constexpr (KG == 1 && OCC == 1) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);
+    return DF_ESHAPE;
   }
   if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, true, 0>(p, st);
   return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, false, 0>(p, st);
@@ -607,8 +666,34 @@ int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
   }
 }
 
-// The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.
-int pick_bgemm(const WParams& p, double other_us) {
+namespace {
+// Parts of K, for plain layers whose tiles cover part of the chip: one round of workgroups in all.  `fixed` is the time of
+// the second launch and of what the parts do beside their stages; each part's sums cost a write and a read.
+struct SplitCfg { int tile; double fixed; };
+constexpr SplitCfg kSplits[] = {{2, 4.3}, {6, 5.0}};
+constexpr int kMaxParts = 8;
+constexpr double kPartUs = 2.2e-6;                     // microseconds per output value and part
+
+int max_parts(const TileCfg& t, long long MT, long long NF) {
+  const long long n = ((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf);
+  return n > 256 ? 1 : 256 / n > kMaxParts ? kMaxParts : (int)(256 / n);
+}
+}  // namespace
+
+// bytes of scratch that a plain layer's parts of K may take
+size_t wgemm_scratch_bytes(long long M, long long N) {
+  const long long MT = (M + 31) / 32, NF = N / 32;
+  int parts = 1;
+  for (const SplitCfg& q : kSplits) {
+    const int n = max_parts(kTiles[q.tile], MT, NF);
+    if (n > parts) parts = n;
+  }
+  return kScratchCounterBytes + (parts > 1 ? (size_t)parts * MT * NF * 4096 : 0);
+}
+
+// The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.  With
+// `scr`, `parts` receives the number of parts to split K into.
+int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts) {
   const int mode = p.xkv ? 3 : p.geglu ? 0 : p.nseg ? 1 : 2;
   const int MT = (p.M + 31) / 32, NF = p.N / 32;
   const double kt = p.K / 64.0;
@@ -627,6 +712,20 @@ int pick_bgemm(const WParams& p, double other_us) {
     }
     const double us = t.base + r * (kt * t.slab + t.epi[mode]);
     if (us < best) { best = us; pick = c; }
+  }
+  // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts; 3600: 79 -> 70.  At 640 features and K = 2560 and
+  // below the sums cost what the parts gain.
+  *parts = 1;
+  if (mode == 2 && !p.ln_s && scr) {
+    for (const SplitCfg& q : kSplits) {
+      const TileCfg& t = kTiles[q.tile];
+      const int most = max_parts(t, MT, NF);
+      for (int s = 2; s <= most; ++s) {
+        if (kt / s < 8) break;
+        const double us = t.base + std::ceil(kt / s) * t.slab + q.fixed + kPartUs * s * (32.0 * MT) * p.N;
+        if (us < 0.97 * best) { best = us / 0.97; pick = q.tile; *parts = s; }
+      }
+    }
   }
   return pick;
 }

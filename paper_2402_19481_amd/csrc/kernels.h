@@ -160,8 +160,10 @@ struct WGemmArgs {
   int xa_keys, xa_rows;
   long long xa_bstride;
   float xa_scale;
+  const Scratch* scr;     // scratch region of the caller (a plan's) for layers that split K; nullptr: none does
 };
 int launch_wgemm(const WGemmArgs& a, hipStream_t st);
+size_t wgemm_scratch_bytes(long long M, long long N);
 size_t packed_rows_bytes(long long M, long long K);
 int launch_pack_rows(const bf16_t* x, long long ldx, bf16_t* out, int M, int K, hipStream_t st);
 int launch_pack_wfrag(const bf16_t* w, const float* gamma, bf16_t* out, int N, int K, hipStream_t st);

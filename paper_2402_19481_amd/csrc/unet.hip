@@ -564,9 +564,14 @@ struct Exec {
   // Linear layer on fragment-packed operands (wgemm.hip); `ln` applies the folded LayerNorm of that weight.
   void wg(const bf16_t* Xp, const std::string& wn, bool bias, bool ln, const float* residual, float* out_f32,
           bf16_t* out_packed, bf16_t* out_rows, long long ld_rows, int M, int Nn, int K, const WGemmArgs* extra = nullptr) {
+    if (!ln && !extra) {
+      const size_t need = wgemm_scratch_bytes(M, Nn);
+      if (need > scratch_need) scratch_need = need;
+    }
     if (!live()) return;
     WGemmArgs g = {};
     if (extra) g = *extra;
+    else if (!ln) g.scr = scr;
     auto it = packed->find(wn);
     if (it == packed->end()) { err = DF_EINVAL; return; }
     g.Xp = Xp; g.Wp = it->second.f; g.M = M; g.N = Nn; g.K = K;

@@ -34,6 +34,8 @@ struct WParams {
   long long xa_bstride; // fragments between batch items
   int xa_rows;          // token rows per batch item
   float xa_scale;
+  f32x4* partials;      // bgemm with `parts` > 1 parts of K: their sums
+  int parts;
   int group_m;          // bgemm: token tiles of a panel in the tile order (see there)
 };
 
@@ -78,6 +80,6 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
 // Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
 // Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1.
-int pick_bgemm(const WParams& p, double other_us);
+int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts);
 
 }  // namespace df

@@ -647,7 +647,15 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
                             : 5.3 + r * (0.189 * kt + (p.geglu ? -1.0 : p.nseg ? 0.35 : a.xa_kv ? 0.1 : -2.2));
     const char* e = tune_env("DF_BGEMM");
     // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
-    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.94 * us);
+    int parts = 1;
+    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.94 * us, a.scr, &parts);
+    if (e && a.scr && tune_env("DF_PARTS")) parts = atoi(tune_env("DF_PARTS"));
+    if (parts > 1) {
+      char* scr = scratch_region(a.scr, kScratchCounterBytes + (size_t)parts * MT * nfrag * 4096);
+      if (!scr) return DF_ENOMEM;
+      p.parts = parts;
+      p.partials = (f32x4*)(scr + kScratchCounterBytes);
+    }
     if (c >= 0) {
       const int rc = launch_bgemm(p, c, st);
       if (rc != DF_ESHAPE || e) return rc;

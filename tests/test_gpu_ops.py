@@ -528,6 +528,33 @@ def test_linear_packed_tiles(M, N, K, variant):
     test_linear_packed(M, N, K, variant)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (1024, 1280, 5120),                # parts of K on the 128 x 320 or 128 x 128 tile
+    (993, 1280, 5120),                 # one token in the last row of tiles
+    (993, 1280, 4160),                 # stages that do not divide into the parts
+    (3600, 1280, 5120),
+])
+def test_linear_packed_parts(M, N, K):
+    say("linear_packed_parts", M, N, K)
+    x, w = round_bf16(normal(43, "x", (M, K)) + 0.3), round_bf16(normal(43, "w", (N, K), std=1.0 / math.sqrt(K)))
+    b, r = normal(43, "b", (N,), std=0.1), normal(43, "r", (M, N))
+    xp, wp, bd = df.pack_rows(dev(x, True)), df.pack_linear_weight(dev(w, True)), dev(b)
+    scratch = df.linear_packed_scratch(M, N, xp.device)
+    with pytest.raises(df.DfError):    # refused before any launch: the layer does split
+        df.linear_packed(xp, wp, M, N, K, bias=bd, residual=dev(r), scratch=scratch[:16384])
+    ref = ops.linear(x, w, b)
+    for res in (None, r):
+        kw = dict(bias=bd, residual=None if res is None else dev(res), scratch=scratch)
+        scratch.fill_(255)             # NaN where a sum would be missing
+        outs = df.linear_packed(xp, wp, M, N, K, want=("f32", "packed", "rows"), **kw)
+        want = ref if res is None else ref + res
+        check(host(outs["f32"]), want, True, "linear_packed_parts f32", tol=2e-3, row_tol=8e-3, elt_tol=8e-3, say=say)
+        got, _ = unpack_rows(host(outs["packed"]), M, N)
+        np.testing.assert_array_equal(got, host(outs["rows"]))
+        again = df.linear_packed(xp, wp, M, N, K, want=("f32",), **kw)
+        np.testing.assert_array_equal(host(outs["f32"]), host(again["f32"]))
+
+
 def test_geglu_gate_function_pointwise():
     """The kernels' GELU against the erf definition, value by value: identity weights turn the GEGLU layer into
     out[m, f] = x[m, f] * gelu(x[m, f]) with exact products, on a grid of bf16-representable arguments."""
