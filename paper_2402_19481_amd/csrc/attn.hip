@@ -87,6 +87,10 @@ __device__ long long g_attn_trace[512 * 32];
 //     again; the lanes' maxima are compared, not exchanged, and the exchange and rescaling sit in a branch beside the loop.
 //   - Row sums come from the packed probabilities (v_dot2 with ones): half the instructions of adding floats.
 // K and V^T tiles go global -> LDS through two rings of three 8 KB tiles; K_{t+3} and V_{t+1} are requested in iteration t.
+// Order of a slot: iteration t reads K_{t+1} and V_{t-1} (S_0 before the loop reads K_0) and ends with a barrier that every wave
+// reaches with its reads done (lgkmcnt(0)).  K_{t+3} goes to the slot of K_t, last read in iteration t-1; V_{t+1} to the slot of
+// V_{t-2}, last read in iteration t-1: the barrier at that iteration's end lies between.  K_0 is read before the loop, so
+// S_0 has a barrier of its own before iteration 0 requests K_3.
 // Bound by the exponentials (64 of 8.3 cycles per wave and tile against 16 MFMAs of 32) and what the power limit leaves of
 // the clock.  Measured against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10 heads
 // 1435 -> 1105 us (961 TFLOP/s), 4096 x 4096 x 10 88 -> 66, 1024 x 4096 x 20 51.6 -> 38, 1200 x 9600 x 10 66 -> 46.
@@ -317,6 +321,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) s_mfma(kfrag(0, s, kb), s, kb);
+  sync_tile(std::integral_constant<int, 0>{});             // every wave has read K_0: its slot takes K_3
 
   int kbase = KB, vbase = 2 * KB;                          // K_{tl+1}; V_{tl-1} (tile 0: K_2 as a finite stand-in, P is 0)
   int kdst = 0, vdst = 4 * KB;                             // slots of K_{tl+3}, V_{tl+1}
