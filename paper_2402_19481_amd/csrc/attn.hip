@@ -85,7 +85,10 @@ __device__ long long g_attn_trace[512 * 32];
 //   - The running maximum m only moves when a score exceeds it by more than 8 (a factor of 256: P stays far inside
 //     float and bf16 range, relative precision is that of any other scaling).  That happens in the first tile and hardly
 //     again; the lanes' maxima are compared, not exchanged, and the exchange and rescaling sit in a branch beside the loop.
-//   - Row sums come from the packed probabilities (v_dot2 with ones): half the instructions of adding floats.
+//   - Row sums add the float probabilities, not the rounded ones the matrix instructions take: the rounding of a heavy key
+//     would otherwise enter every feature of the row (a key of weight 0.9 with values near zero: 2.0e-3 of error against 1.4e-3,
+//     where the rounding of the result alone is 1.4e-3; random scores differ by less than 7 % in either direction).  Sums
+//     of the packed pairs by v_dot2 are half the instructions and 0.6 % faster on the largest shape.
 // K and V^T tiles go global -> LDS through two rings of three 8 KB tiles; K_{t+3} and V_{t+1} are requested in iteration t.
 // Order of a slot: iteration t reads K_{t+1} and V_{t-1} (S_0 before the loop reads K_0) and ends with a barrier that every wave
 // reaches with its reads done (lgkmcnt(0)).  K_{t+3} goes to the slot of K_t, last read in iteration t-1; V_{t+1} to the slot of
@@ -305,7 +308,6 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   auto s_mfma = [&](u32x4 k, int s, int kb) {
     sa[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, k), qreg[s], s == 0 ? cinit : sa[kb], 0, 0, 0);
   };
-  const bf16x2 ones = __builtin_bit_cast(bf16x2, 0x3f803f80u);
   auto sync_tile = [&](auto vmc) {
     constexpr int VM = decltype(vmc)::value;
     __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4) | (0 << 8));   // vmcnt(VM) lgkmcnt(0)
@@ -391,8 +393,8 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
         pk[u] = u32x4{w[u & 1][0], w[u & 1][1], w[u & 1][2], w[u & 1][3]};
       };
       auto S = [&](int u) {                                // row sums
-#pragma unroll
-        for (int q = 0; q < 4; ++q) l_run = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[u & 1][q]), ones, l_run, false);
+        const float* e = ex[u & 1];
+        l_run += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
       };
       const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
       const bf16_t *kp[2], *vp[2];

@@ -617,6 +617,38 @@ def test_attn_stale_vt(B, Lq, L, heads, packed):
     np.testing.assert_array_equal(got, got2)            # reproducible (padding rows of a packed output are not written)
 
 
+@pytest.mark.parametrize("form", ["vt", "rows"])
+def test_attention_row_sums_are_not_rounded(form):
+    """One key takes most of the weight with a value of zero, so the result is the small remainder over the row sum and a row sum
+    of bf16 terms (2^-9 each way on the heavy term) would shift a whole row of it.  The keys before it keep the running
+    maximum below its score by less than the rescaling window, so that its probability is not a power of two.  The
+    values are c_d = 1 + d/64 for every other key: the mean over d of out_d / (c_d w) - 1 averages the rounding of the
+    64 results (2^-9 / sqrt(3) / 8 = 1.4e-4 at most) and of the other keys' weights (2^-9 / sqrt(3) over the root of some 100 that count), a
+    rounded sum would leave 2^-9 / sqrt(3) x 0.9 = 1e-3."""
+    say("attention_row_sums", form)
+    heads, Lq, L, N = 2, 1024, 4096, 4
+    C = heads * 64
+    q, k = normal(57, "q", (1, Lq, heads, 64)), normal(57, "k", (1, L, heads, 64))
+    v = np.broadcast_to(1.0 + np.arange(64, dtype=np.float32) / 64, (1, L, heads, 64)).copy()
+    q[..., 0] = 8.0 + 0.5 * np.clip(q[..., 0], -3, 3)
+    k[..., 0] = 0.0
+    for key, score in ((3, 0.6), (100, 1.0)):             # the first and the second tile of a key range
+        k[:, key] = 0.0
+        k[:, key, :, 0] = score * 10.5                      # 10.5 nats for q = 8: exp(10.5) / (4096 sqrt(e)) ~ 5
+    v[:, 100] = 0.0
+    q, k, v = (round_bf16(t.reshape(1, -1, C)) for t in (q, k, v))
+    ref = ops.attention_dense(q, k, v, heads)
+    if form == "vt":
+        out = df.attn_stale_vt(dev(q, True), dev(k, True), dev(v.transpose(0, 2, 1), True), heads, L)
+    else:
+        out = df.attn_displaced(dev(q, True), dev(k[:, Lq:2 * Lq], True), dev(v[:, Lq:2 * Lq], True), dev(k, True), dev(v, True),
+                                heads, 1, N)
+    shift = (host(out) / ref - 1.0).reshape(Lq, heads, 64).mean(2)
+    say("   weight of the heavy key", 1.0 - ref[0, :, 0].mean(), "row shift rms", np.sqrt((shift ** 2).mean()))
+    assert ref[0, :, 0].mean() < 0.3
+    assert np.sqrt((shift ** 2).mean()) < 3.5e-4
+
+
 @pytest.mark.parametrize("Lq,L,heads", [(128, 64, 1), (129, 65, 2), (31, 127, 1), (257, 129, 1), (128, 192, 2), (640, 1000, 5),
                                         (1024, 2496, 3)])
 @pytest.mark.parametrize("shape", ["rising", "falling", "spike"])
