@@ -216,7 +216,11 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
-  // LDS: three K tiles, then three V tiles
+  // LDS: three K tiles, three V tiles, and a tile of zeros: the values behind probabilities that are zero by construction (a tile
+  // that has none yet, or whose values are already added), where a tile in use could hold infinities
+  constexpr int ZERO = 6 * KB;
+  *reinterpret_cast<u32x4*>(smem + ZERO + tid * 32) = u32x4{0u, 0u, 0u, 0u};
+  *reinterpret_cast<u32x4*>(smem + ZERO + tid * 32 + 16) = u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int ti = i < ntiles ? i : ntiles - 1;            // past the end: the last tile again (keeps vmcnt uniform)
@@ -325,7 +329,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     for (int kb = 0; kb < 2; ++kb) s_mfma(kfrag(0, s, kb), s, kb);
   sync_tile(std::integral_constant<int, 0>{});             // every wave has read K_0: its slot takes K_3
 
-  int kbase = KB, vbase = 2 * KB;                          // K_{tl+1}; V_{tl-1} (tile 0: K_2 as a finite stand-in, P is 0)
+  int kbase = KB, vnext = 3 * KB, vbase = ZERO;            // K_{tl+1}; V_tl; V_{tl-1}, or zeros where P is
   int kdst = 0, vdst = 4 * KB;                             // slots of K_{tl+3}, V_{tl+1}
   int tl = 0;
   const bool ragged = (kv_hi - kv_lo) % TK != 0;
@@ -348,6 +352,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       for (int i = 0; i < 8; ++i) pv_mfma(SRC == kSrcVt ? vfrag(vbase, i >> 1, i & 1) : vof8(vt, i >> 1, i & 1), i >> 1, i & 1);
 #pragma unroll
       for (int i = 0; i < 4; ++i) pk[i] = u32x4{0u, 0u, 0u, 0u};
+      vbase = ZERO;
       const float mx = max8(sa[1], 1, max8(sa[1], 0, max8(sa[0], 1, max8(sa[0], 0, -INFINITY))));
       const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)));
       const float m_new = fmaxf(m_run, PRE ? fmaxf(mx, part) + m_base : fmaxf(mx, part) * sc);
@@ -376,7 +381,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       } else {
         vrequest(vbase, vt);
       }
-      auto vnext = [&](int ts, int db) { return SRC == kSrcVt ? vfrag(vbase, ts, db) : u32x4{0u, 0u, 0u, 0u}; };
+      auto vread = [&](int ts, int db) { return SRC == kSrcVt ? vfrag(vbase, ts, db) : u32x4{0u, 0u, 0u, 0u}; };
       auto vuse = [&](const u32x4& ahead, int ts, int db) { return SRC == kSrcVt ? ahead : vof8(vt, ts, db); };
       float ex[2][8];
       auto E = [&](int u, int h) {                         // four exponentials of key step u
@@ -415,12 +420,12 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       };
       DF_FENCE;
       if constexpr (SRC != kSrcVt) { E(0, 0); E(0, 1); DF_FENCE; varrive(vt, H1{}); DF_FENCE; }
-      pv_mfma(vuse(f[0], 0, 0), 0, 0); f[5] = vnext(2, 1); if constexpr (SRC == kSrcVt) E(0, 0); DF_FENCE;
+      pv_mfma(vuse(f[0], 0, 0), 0, 0); f[5] = vread(2, 1); if constexpr (SRC == kSrcVt) E(0, 0); DF_FENCE;
       pv_mfma(vuse(f[1], 0, 1), 0, 1); f[6] = kfrag(kbase, 0, 0); if constexpr (SRC == kSrcVt) E(0, 1); dma_k(0); DF_FENCE;
-      pv_mfma(vuse(f[2], 1, 0), 1, 0); f[7] = vnext(3, 0); C(0); dma_k(1); DF_FENCE;
+      pv_mfma(vuse(f[2], 1, 0), 1, 0); f[7] = vread(3, 0); C(0); dma_k(1); DF_FENCE;
       pv_mfma(vuse(f[3], 1, 1), 1, 1); f[8] = kfrag(kbase, 1, 0); E(1, 0); DF_FENCE;
       if constexpr (SRC != kSrcVt) { varrive(vt, H2{}); DF_FENCE; }
-      pv_mfma(vuse(f[4], 2, 0), 2, 0); f[9] = vnext(3, 1); E(1, 1); DF_FENCE;
+      pv_mfma(vuse(f[4], 2, 0), 2, 0); f[9] = vread(3, 1); E(1, 1); DF_FENCE;
       pv_mfma(vuse(f[5], 2, 1), 2, 1); f[10] = kfrag(kbase, 2, 0); C(1); S(0); DF_FENCE;
       s_mfma(f[6], 0, 0); f[11] = kfrag(kbase, 3, 0); E(2, 0); DF_FENCE;
       pv_mfma(vuse(f[7], 3, 0), 3, 0); f[12] = kfrag(kbase, 0, 1); E(2, 1); S(1); DF_FENCE;
@@ -437,7 +442,8 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       mx = max8(sa[1], 1, max8(sa[1], 0, mx));
       kbase = kbase == 2 * KB ? 0 : kbase + KB;
       kdst = kdst == 2 * KB ? 0 : kdst + KB;
-      vbase = vbase == 5 * KB ? 3 * KB : vbase + KB;
+      vbase = vnext;
+      vnext = vnext == 5 * KB ? 3 * KB : vnext + KB;
       vdst = vdst == 5 * KB ? 3 * KB : vdst + KB;
       ++tl;
       sync_tile(std::integral_constant<int, 4>{});         // K_{tl+1} and V_{tl-1} of the next tile have landed, for every wave
@@ -453,7 +459,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   for (int i = 0; i < 8; ++i) {
     const int ts = i >> 1;
     u32x4 v = SRC == kSrcVt ? vfrag(vbase, ts, i & 1) : vof8(vlast, ts, i & 1);
-    if (SRC == kSrcVt && ragged) {                         // keys beyond the range: P is 0, V must be finite
+    if (ragged) {                                          // keys beyond the range: P is 0, V must be finite
       const int key = kv_lo + (ntiles - 1) * TK + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
       if (key + 0 >= kv_hi) v.x = 0u; else if (key + 1 >= kv_hi) v.x &= 0xffffu;
       if (key + 2 >= kv_hi) v.y = 0u; else if (key + 3 >= kv_hi) v.y &= 0xffffu;
@@ -1045,13 +1051,13 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
-    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V^T tiles
+    constexpr int smem = 7 * 64 * 64 * 2;                // three K and three V^T tiles, zeros
     if (a.q_scaled) hipLaunchKernelGGL((attn_pipe_d64<true, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
     else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   } else {
     // 32-bit row offsets inside a 64-key tile
     if (a.ldkf >= (1 << 24) || a.ldvf >= (1 << 24) || a.ldks >= (1 << 24) || a.ldvs >= (1 << 24)) return DF_ESHAPE;
-    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V tiles
+    constexpr int smem = 7 * 64 * 64 * 2;                // three K and three V tiles, zeros
     if (a.own_period > 0) hipLaunchKernelGGL((attn_pipe_d64<false, kSrcPeriodic>), dim3((unsigned)nwg), dim3(256), smem, st, p);
     else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcRows>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   }

@@ -649,6 +649,47 @@ def test_attention_row_sums_are_not_rounded(form):
     assert np.sqrt((shift ** 2).mean()) < 3.5e-4
 
 
+@pytest.mark.parametrize("form", ["vt", "rows", "cols"])
+@pytest.mark.parametrize("what", ["value", "last value", "key"])
+def test_attention_infinities_stay_where_they_belong(what, form):
+    """An infinite value is infinite in its own feature and nowhere else, whether its tile is followed by a rescaling (scores rise
+    from tile to tile) or is the ragged last one; a key whose scores are all -inf has no weight.  Six tiles, one
+    key in the last."""
+    say("attention_infinities", what, form)
+    H, N, heads = 107, 3, 2
+    L, Lq, C = 3 * H, H, heads * 64
+    q, k, v = normal(58, "q", (1, Lq, C)), 0.3 * normal(58, "k", (1, L, C)), normal(58, "v", (1, L, C))
+    q, k = np.abs(q) + 0.5, k + (4.0 * np.arange(L, dtype=np.float32) / L)[None, :, None]
+    q, k, v = (round_bf16(t.astype(np.float32)) for t in (q, k, v))
+    if what == "key":
+        k[0, 150, 70] = -np.inf
+    else:
+        v[0, 150 if what == "value" else L - 1, 70] = np.inf
+    ref = np.empty((1, Lq, C))
+    with np.errstate(invalid="ignore"):
+        for h in range(heads):
+            c = slice(64 * h, 64 * h + 64)
+            sc = q[0, :, c].astype(np.float64) @ k[0, :, c].astype(np.float64).T / 8.0
+            w = np.exp(sc - sc.max(1, keepdims=True))
+            ref[0, :, c] = w @ v[0, :, c].astype(np.float64) / w.sum(1, keepdims=True)
+    assert np.isinf(ref).sum() == (0 if what == "key" else Lq)
+    qd, kd, vd = dev(q, True), dev(k, True), dev(v, True)
+    if form == "vt":
+        Lp = (L + 63) // 64 * 64
+        vt = torch.full((1, C, Lp), float("nan"), dtype=torch.bfloat16, device=DEV)
+        vt[:, :, :L] = vd.transpose(1, 2)
+        out = df.attn_stale_vt(qd, kd, vt, heads, L)
+    elif form == "rows":
+        own = slice(2 * Lq, 3 * Lq)
+        out = df.attn_displaced(qd, kd[:, own].contiguous(), vd[:, own].contiguous(), kd, vd, heads, 2, N)
+    else:                               # the last of three columns of a grid with 107 rows
+        out = df.attn_displaced_cols(qd, kd[:, 2::3].contiguous(), vd[:, 2::3].contiguous(), kd, vd, heads, H, 3, 2, N)
+    got = host(out)
+    np.testing.assert_array_equal(got[np.isinf(ref)], ref[np.isinf(ref)])
+    got[np.isinf(ref)] = ref[np.isinf(ref)] = 0.0
+    check(got, ref, True, "attention_infinities", say=say)
+
+
 @pytest.mark.parametrize("Lq,L,heads", [(128, 64, 1), (129, 65, 2), (31, 127, 1), (257, 129, 1), (128, 192, 2), (640, 1000, 5),
                                         (1024, 2496, 3)])
 @pytest.mark.parametrize("shape", ["rising", "falling", "spike"])
