@@ -37,8 +37,9 @@ __device__ __forceinline__ float silu_f(float x) {
 // GELU in its exact (erf) form, 0.5 x (1 + erf(x / sqrt 2)).  erfc(|z|) = t (a1 + t (a2 + t (a3 + t (a4 + t a5))))
 // exp(-z^2) with z = x / sqrt 2, t = 1 / (1 + p |z|) (Abramowitz & Stegun 7.1.26: absolute error below 1.5e-7, the size of
 // float rounding of the result).  With e = erfc(|z|) / 2 the result is max(x, 0) - |x| e for both signs, and for negative
-// arguments nothing cancels.  The constants below have the 1/2, the 1/sqrt 2 and log2(e) in them: thirteen instructions per
+// arguments nothing cancels.  The constants below have the 1/2, the 1/sqrt 2 and log2(e) in them: fourteen instructions per
 // value, where the library erff takes several times that; the GEGLU epilogues are otherwise bounded by this function.
+// The factor of e is kept finite, so that +inf stays +inf (e is 0 there).
 __device__ __forceinline__ float gelu_erf(float x) {
   const float ax = fabsf(x);
   const float t = __builtin_amdgcn_rcpf(fmaf(0.23164189f, ax, 1.0f));
@@ -48,7 +49,7 @@ __device__ __forceinline__ float gelu_erf(float x) {
   poly = fmaf(poly, t, 0.127414796f);
   const float u = x * 0.84932180f;
   const float e = poly * t * __builtin_amdgcn_exp2f(-(u * u));
-  return fmaf(-ax, e, fmaxf(x, 0.f));
+  return fmaf(-fabsf(fminf(x, 3.0e38f)), e, fmaxf(x, 0.f));
 }
 
 template <typename T> struct Elem;

@@ -576,6 +576,22 @@ def test_geglu_gate_function_pointwise():
     assert (err <= 4e-6 * np.maximum(1.0, xd * xd)).all()
 
 
+@pytest.mark.parametrize("M,K", [(40, 64), (2048, 1280)])      # the wave-level kernel and a tile of the LDS kernel
+def test_geglu_gate_of_infinity_and_nan(M, K):
+    """gelu at the ends of its range, delivered by the gates' bias: +inf and the largest floats are returned as they are,
+    finite negative ones give 0, -inf (-inf x 0 in the definition) and NaN give NaN."""
+    say("geglu gate of infinity", M, K)
+    F = 512
+    gate = np.zeros(F, dtype=np.float32)
+    gate[:6] = [np.inf, 3.3e38, 1e30, -3.3e38, -np.inf, np.nan]
+    want = np.array([np.inf, 3.3e38, 1e30, 0.0, np.nan, np.nan], dtype=np.float32)
+    xp = df.pack_rows(torch.zeros(M, K, dtype=torch.bfloat16, device=DEV))
+    wp = df.pack_linear_weight(torch.zeros(2 * F, K, dtype=torch.bfloat16, device=DEV))
+    bias = dev(np.concatenate([np.ones(F, dtype=np.float32), gate]))
+    out = host(df.linear_packed(xp, wp, M, 2 * F, K, bias=bias, geglu=True, want=("f32",))["f32"])
+    np.testing.assert_array_equal(out, np.broadcast_to(np.concatenate([want, np.zeros(F - 6)]), (M, F)))
+
+
 # ---------------------------------------------------------------------------------------------------------------
 # the attention forms of the UNet step: transposed values in the stale buffer; cross-attention fused into its
 # query projection
