@@ -850,6 +850,11 @@ __global__ __launch_bounds__(256) void attn_f32(AttnParams p) {
       kv[u] = ld(fr >= 0 ? kf + fr * p.ldkf : ks + (long long)j * p.ldks);
       vv[u] = ld(fr >= 0 ? vf + fr * p.ldvf : vs + (long long)j * p.ldvs);
     }
+    if (j0 + U * KPS > p.L) {                              // (uniform) keys beyond the last: weight 0, the value must be finite
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (j0 + u * KPS + grp >= p.L) vv[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
 #pragma unroll
     for (int q = 0; q < QN; ++q) {
       float s[U], mn = m[q];
@@ -861,17 +866,16 @@ __global__ __launch_bounds__(256) void attn_f32(AttnParams p) {
         s[u] = j0 + u * KPS + grp < p.L ? t * p.scale : -INFINITY;
         mn = fmaxf(mn, s[u]);
       }
-      if (mn > -INFINITY) {                                // a group may have no key in its first step
-        const float a = expf(m[q] - mn);
-        l[q] *= a; acc[q] *= a;
+      // a maximum of -inf (no key in the group's first step, scores of -inf, or NaN, which fmaxf passes over) is no reference
+      const float ref = mn == -INFINITY ? 0.f : mn, a = expf(m[q] - ref);
+      l[q] *= a; acc[q] *= a;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          const float e = expf(s[u] - mn);
-          l[q] += e;
-          acc[q] += vv[u] * e;
-        }
-        m[q] = mn;
+      for (int u = 0; u < U; ++u) {
+        const float e = expf(s[u] - ref);
+        l[q] += e;
+        acc[q] += vv[u] * e;
       }
+      m[q] = mn;
     }
   }
 #pragma unroll

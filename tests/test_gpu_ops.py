@@ -292,6 +292,31 @@ def test_attention_f32_edges(Lq_total, N, C, heads):
     check(host(o), ref, False, "attn f32", say=say)
 
 
+@pytest.mark.parametrize("L,C,heads", [(5, 32, 1), (37, 32, 1), (37, 64, 1), (2053, 128, 2)])
+def test_attention_f32_infinities_and_nan(L, C, heads):
+    """A NaN score makes its query's result NaN (also where it is the only score a group of lanes sees), a key whose scores
+    are -inf has no weight, an infinite value of the last key (re-read by the lanes behind it) is infinite in its own
+    feature and nowhere else."""
+    say("attention_f32_infinities", L, C, heads)
+    q, k, v = (normal(59, n, (1, L, C)).astype(np.float32) for n in ("q", "k", "v"))
+    q = np.abs(q) + 0.5
+    run = lambda kk, vv: host(df.attn_displaced(dev(q), dev(kk), dev(vv), dev(kk), dev(vv), heads, 0, 1))
+    bad = k.copy()
+    bad[0, 2, :C // heads] = np.nan                         # the first head's scores of key 2
+    got = run(bad, v)
+    assert np.isnan(got[..., :C // heads]).all() and np.isfinite(got[..., C // heads:]).all()
+    off = k.copy()
+    off[0, 2] = -np.inf                                     # without key 2
+    ref = ops.attention_dense(q, np.delete(k, 2, 1), np.delete(v, 2, 1), heads)
+    check(run(off, v), ref, False, "attention_f32 -inf", say=say)
+    big = v.copy()
+    big[0, L - 1, 7] = np.inf
+    got, ref = run(k, big), ops.attention_dense(q, k, v, heads)
+    assert (got[..., 7] == np.inf).all()
+    got[..., 7] = ref[..., 7] = 0.0
+    check(got, ref, False, "attention_f32 inf value", say=say)
+
+
 @pytest.mark.parametrize("B,L,C,heads,N,patch,bf16", [
     (1, 256, 32, 1, 2, 0, False),       # configuration 1
     (2, 96, 128, 2, 3, 1, False),       # d = 64 in float32, fewer keys than two waves' stride
