@@ -64,6 +64,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   constexpr int NL = (I + NW - 1) / NW;                // per wave (the last wave repeats the last fragment)
   static_assert(NL * (ST - 1) < 64, "vmcnt field is 6 bits");
   static_assert((WF & (WF - 1)) == 0, "");
+  static_assert(EPI != EPI_QKV || LN, "the segmented epilogue applies the folded LayerNorm");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
   asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.group_m), "s"(p.residual), "s"(p.ldr));
@@ -471,11 +472,8 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
               for (int k = 0; k < KG; ++k)
                 x += reinterpret_cast<const float*>(red + (((k * R + r) * BF + jf) * 4 + 2 * half + ((fe >> 2) & 1)) * 64 + tk2 +
                                                     32 * ((fe >> 3) & 1))[fe & 3];
-              if constexpr (LN) {
-                const float* mr = s_mr + (trow * 32 + tk2) * 2;
-                return mr[1] * (x - mr[0] * s_s[jf * 32 + fe]) + s_t[jf * 32 + fe];
-              }
-              return x + s_t[jf * 32 + fe];
+              const float* mr = s_mr + (trow * 32 + tk2) * 2;
+              return mr[1] * (x - mr[0] * s_s[jf * 32 + fe]) + s_t[jf * 32 + fe];
             };
             auto at = [&](int fe, int m) {
               const int bi = m < rin ? 0 : m / rin;
@@ -608,24 +606,24 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
     return DF_ESHAPE;
   }
   if (p.geglu) {
-    if constexpr (BF % 2 == 0) {
+    if constexpr (BF % 2 == 0 && BF > 2) {               // (64 x 64 tiles: one value fragment per wave row, never the choice)
       if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, true, 0>(p, st);
       return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_GEGLU, false, 0>(p, st);
     }
     return DF_ESHAPE;
   }
   if (p.nseg) {
+    if (!p.ln_s) return DF_ESHAPE;                       // (the segmented projections of the step fold a LayerNorm)
     WParams q = p;
     for (int i = 0; i < p.nseg; ++i) {
       // transposed segments: how many consecutive tokens stay together and aligned in the destination
       const long long al = p.seg_ld[i] | p.seg_row0[i] | p.seg_pin[i] | p.seg_pout[i] | p.seg_rows_in[i] | p.M;
       if (p.seg_tr[i]) q.seg_tr[i] = (al % 8 == 0 && (uintptr_t)p.seg_out[i] % 16 == 0) ? 8 : (al % 2 == 0 && (uintptr_t)p.seg_out[i] % 4 == 0) ? 2 : 1;
     }
-    if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
-    return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, false, 0>(q, st);
+    return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
   }
   if (p.parts > 1) {
-    if constexpr (KG == 1 && OCC == 1) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);
+    if constexpr (TT == 1 && KG == 1 && OCC == 1) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);
     return DF_ESHAPE;
   }
   if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, true, 0>(p, st);

@@ -90,13 +90,8 @@ __device__ __forceinline__ float wave_sum(float v) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
-// Kernel-selection overrides from the environment (DF_TILE, DF_SPLITK, DF_ATTN_*, ...) exist only in builds with
+// Kernel-selection overrides from the environment (DF_TG, DF_TGS, DF_BGEMM, DF_PARTS, DF_ATTN_*) exist only in builds with
 // -DDF_TUNING; in the library as shipped every choice is a function of the call's arguments alone.
 #ifdef DF_TUNING
 static inline const char* tune_env(const char* name) { return getenv(name); }

@@ -13,15 +13,13 @@ namespace df {
 // per-operation entry points use one region per device that the library allocates on first use.  That region is
 // never freed or moved while the process lives: a larger request allocates a further buffer and the old one stays
 // valid for anything that still holds its address.
-// The first 16 KiB of a region are reserved: [0, 8 KiB) counters that every kernel leaves at zero,
-// [8 KiB, 16 KiB) a page of zeros nobody writes.
+// The first 16 KiB of a region are reserved and start at zero; [8 KiB, 16 KiB) is a page of zeros nobody writes.
 struct Scratch {
   char* ptr;
   size_t bytes;
 };
 constexpr size_t kScratchCounterBytes = 16384;
 constexpr size_t kScratchZeroPageOffset = 8192;
-constexpr int kScratchNumCounters = 2048;
 // Region of at least `bytes` for a launch: `given` if non-null (nullptr result if it is too small), else the
 // library's per-device region.  Returns nullptr on failure.
 char* scratch_region(const Scratch* given, size_t bytes);

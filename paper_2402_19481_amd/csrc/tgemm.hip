@@ -64,9 +64,8 @@ void tgemm_kernel(TileParams p, TgExtra x) {
   static_assert(AJ * 8 * NWG == BM && BJ * 8 * NWG == BN, "whole loads");
   constexpr int L = AJ + BJ;
   constexpr int SLAB = (BM + BN) * 128, STAGE = SLAB * KG;
-  static_assert(L * (ST - 1) < 64, "vmcnt field is 6 bits");
-  constexpr int NP = ST > 2 ? 4 : 3;                      // parts of a stage's loads (two stages: all before the barrier)
-  constexpr int LATE = NP == 4 ? L - (3 * L + 3) / 4 : 0; // loads of part 3
+  static_assert(ST > 2 && L * (ST - 1) < 64, "part 3 is requested behind the barrier; the vmcnt field is 6 bits");
+  constexpr int LATE = L - (3 * L + 3) / 4;               // loads of part 3
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -168,7 +167,7 @@ void tgemm_kernel(TileParams p, TgExtra x) {
     }
 #pragma unroll
     for (int q = 0; q < L; ++q) {
-      if (q * NP / L != STEP) continue;
+      if (q * 4 / L != STEP) continue;
       const int j = q < AJ ? q : q - AJ;
       if (q < AJ) {
         const bf16_t* src;
