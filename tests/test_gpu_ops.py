@@ -130,8 +130,8 @@ def test_groupnorm_pixels_in_registers(R, W, C, G, bf16):
 
 @pytest.mark.parametrize("R,W,C,G,N,patch", [
     (8, 16, 64, 8, 2, 1),        # one launch, pixels held in registers
-    (32, 128, 64, 4, 4, 2),      # one launch per group, two passes over the patch
-    (64, 128, 64, 4, 2, 0),      # statistics / finalize / apply kernels
+    (32, 128, 64, 4, 4, 2),      # one launch, sixteen pixels per lane
+    (64, 128, 64, 4, 2, 0),      # two launches
 ])
 @pytest.mark.parametrize("mode", [0, 1])
 def test_groupnorm_mean_far_from_zero_f32(R, W, C, G, N, patch, mode):
@@ -187,8 +187,8 @@ def _conv_case(seed, B, H, W, Cin, Cout, bf16, noise=0.5):
     (1, 16, 16, 32, 32, 2, 1, False),    # configuration 1
     (2, 12, 6, 5, 7, 3, 1, False),       # odd channel counts
     (1, 16, 8, 8, 12, 4, 2, False),      # stride 2
-    (1, 8, 8, 4, 64, 2, 1, True),        # conv_in-like: 4 input channels (direct kernel)
-    (1, 8, 8, 128, 4, 2, 1, True),       # conv_out-like: 4 output channels (wave kernel)
+    (1, 8, 8, 4, 64, 2, 1, True),        # conv_in-like: 4 input channels
+    (1, 8, 8, 128, 4, 2, 1, True),       # conv_out-like: 4 output channels (four pixels per wave)
     (2, 16, 12, 64, 96, 4, 1, True),     # MFMA tile path, ragged M and N tiles
     (1, 16, 24, 96, 64, 4, 2, True),     # MFMA, stride 2
     (1, 32, 40, 64, 320, 2, 1, True),    # MFMA, several N tiles
@@ -322,7 +322,7 @@ def test_attention_f32_infinities_and_nan(L, C, heads):
     (2, 96, 128, 2, 3, 1, False),       # d = 64 in float32, fewer keys than two waves' stride
     (1, 512, 128, 2, 4, 2, True),       # bf16 MFMA kernel
     (2, 600, 64, 1, 4, 3, True),        # ragged: 150 queries, 600 keys (partial tiles), batch 2
-    (1, 2400, 192, 3, 8, 5, True),      # level-2 shape of the 1280x1920 share: 300 queries, split keys
+    (1, 2400, 192, 3, 8, 5, True),      # level-2 shape of the 1280x1920 share: 300 queries, parts of the key range
     (1, 77 * 1, 128, 2, 1, 0, True),    # 77 keys, everything fresh (cross-attention shape)
 ])
 def test_attention_displaced(B, L, C, heads, N, patch, bf16):
@@ -395,8 +395,8 @@ def test_tiny_block_chain_f32():
 # ------------------------------------------------------------------ linear layers (per-token, fresh rows only)
 
 @pytest.mark.parametrize("M,N,K,out_f32,res", [
-    (300, 1280, 1280, True, True),     # level-2 projection of the 1280x1920 share: few tiles, split along K
-    (300, 1280, 5120, True, True),     # feed-forward output: deep K
+    (300, 1280, 1280, True, True),     # level-2 projection of the 1280x1920 share
+    (300, 1280, 5120, True, True),     # feed-forward output: parts of K
     (300, 3840, 1280, False, False),   # fused QKV
     (77, 2560, 2048, False, False),    # text K/V projection: ragged rows
     (1200, 640, 2560, True, True),
@@ -494,8 +494,8 @@ def test_pack_rows_layout():
     (130, 512, 128, "ln_geglu"),
     (1200, 640, 640, "plain"),
     (300, 3840, 1280, "ln"),           # 64 x 96 wave tile: a single round of workgroups, reduced row by row
-    (300, 10240, 1280, "ln_geglu"),    # 128 x 128 wave tile (two value / gate fragment pairs), ragged third row group
-    (270, 1024, 1024, "geglu"),        # 128 x 128 tile without the folded norm; 9 token fragments
+    (300, 10240, 1280, "ln_geglu"),    # 128 x 128 tile through LDS, ragged third row of tiles
+    (270, 1024, 1024, "geglu"),        # 32 x 64 wave tile without the folded norm; 9 token fragments
     (270, 3840, 1280, "plain"),        # 64 x 96 tile, odd number of token fragments (last row group half empty)
     (300, 1280, 1280, "ln_far"),       # folded LayerNorm on rows whose mean is 50 standard deviations from zero
 ])
@@ -623,19 +623,24 @@ def test_geglu_gate_of_infinity_and_nan(M, K):
 # ---------------------------------------------------------------------------------------------------------------
 
 @pytest.mark.parametrize("B,Lq,L,heads,packed", [
-    (1, 300, 2400, 20, True),       # level 2 of the benchmark step: ragged last key tile, 2.3 query blocks
-    (1, 1200, 9600, 10, False),     # level 1
+    # attn_wave_d64: one workgroup per 32 queries and head, its waves split the keys
+    (1, 300, 2400, 20, True),       # level 2 of the benchmark step: ragged last key tile, ragged last query block
+    (2, 300, 2400, 8, True),        # two batch items
+    (2, 70, 1003, 3, False),        # ragged queries, 43 valid keys in the last tile, two batch items
+    (1, 300, 515, 1, True),         # 9 tiles on 8 waves, 3 valid keys in the last tile
+    (1, 32, 512, 1, True),          # one tile per wave
+    (1, 40, 600, 2, False),
+    (1, 512, 1003, 16, False),      # a workgroup on every compute unit: the most this form takes
+    # attn_pipe_d64: 128 queries per workgroup, key tiles through LDS
+    (1, 1200, 9600, 10, False),     # level 1 of the benchmark step: five key ranges
     (2, 96, 200, 2, True),          # two batch items, key count not a multiple of 8
-    (1, 33, 64, 1, False),          # a single full tile, ragged queries: the second wave group has no keys
-    (1, 40, 600, 2, False),         # key ranges rounded up to 128: fewer ranges than first chosen, last one ragged
-    (1, 130, 1100, 3, True),        # odd number of 64-key tiles in a range: the second group's last tile is missing
-    (2, 300, 2400, 4, True),        # two batch items in the form whose waves split the keys (80 workgroups)
-    (2, 300, 2400, 20, True),       # two batch items of the benchmark level: 400 blocks, so split key ranges in the two-group kernel
-    (1, 4096, 8192, 10, False),     # > 600 workgroups: the single-group, three-stage form
-    (1, 512, 4096, 2, False),       # the largest query count of the form whose waves split the keys
-    (2, 70, 1003, 3, False),        # that form: ragged queries, 11 valid keys in the last tile, two batch items
-    (1, 300, 515, 1, True),         # that form: 9 tiles on 8 waves, 3 valid keys in the last tile
-    (1, 32, 512, 1, True),          # that form: one tile per wave
+    (1, 33, 64, 1, False),          # a single full tile: every load past it repeats it; two waves without queries
+    (1, 40, 450, 2, False),         # key ranges rounded up to 256: fewer ranges than first chosen, last one ragged
+    (1, 130, 1100, 3, True),        # the last of five ranges has two tiles, one of them ragged
+    (2, 300, 2400, 4, True),        # two batch items, seven ranges
+    (2, 300, 2400, 20, True),       # two batch items of the benchmark level: 400 query blocks, too many for the other form
+    (1, 512, 4096, 2, False),       # the largest number of ranges
+    (1, 4096, 8192, 10, False),     # several rounds of workgroups
 ])
 def test_attn_stale_vt(B, Lq, L, heads, packed):
     say("attn_stale_vt", B, Lq, L, heads, packed)
@@ -732,7 +737,7 @@ def test_attention_infinities_stay_where_they_belong(what, form):
 
 
 @pytest.mark.parametrize("Lq,L,heads", [(128, 64, 1), (129, 65, 2), (31, 127, 1), (257, 129, 1), (128, 192, 2), (640, 1000, 5),
-                                        (1024, 2496, 3)])
+                                        (1024, 2496, 3), (300, 449, 2), (1024, 4096, 3)])   # (640 and 2496: attn_wave_d64)
 @pytest.mark.parametrize("shape", ["rising", "falling", "spike"])
 def test_attn_stale_vt_running_maximum(Lq, L, heads, shape):
     """Scores that leave the kernel's rescaling window: rising from tile to tile, falling, one far above all others in
@@ -763,6 +768,10 @@ def test_attn_stale_vt_running_maximum(Lq, L, heads, shape):
     (1, 1200, 640, 77, 2, 0),       # level 1
     (2, 64, 128, 13, 2, 1),         # two batch items, one key tile
     (1, 40, 256, 128, 1, 0),        # the longest supported text
+    (1, 1345, 1280, 77, 2, 1),      # 64 x 128 tile through LDS, one token in the last row of tiles
+    (2, 864, 1280, 13, 2, 1),       # 128 x 128 tile, two batch items that meet inside a tile
+    (1, 1700, 1280, 128, 1, 0),     # 128 x 128 tile, the longest text
+    (1, 3300, 1280, 33, 1, 0),      # 128 x 128 tile, two workgroups per unit
 ])
 def test_cross_attn_packed(B, rows, C, TL, count, block):
     say("cross_attn_packed", B, rows, C, TL, count, block)

@@ -177,6 +177,47 @@ def test_small_unet_vertical_strips(H, W, N, B):
     net.close()
 
 
+@pytest.mark.parametrize("H,W,B,cols", [
+    (124, 62, 1, False),      # 961 tokens per patch, 1922 in the synchronous step: single tokens / pairs of V^T
+    (132, 30, 2, False),      # 2 x 495 tokens: a batch item ends inside a fragment
+    (62, 124, 1, True),       # strips of 31 columns
+    (64, 120, 1, True),       # strips of 30 columns: pairs
+    (60, 128, 1, True),       # strips of 32 columns: eight tokens at a time
+])
+def test_unet_qkv_projection_on_tiles(H, W, B, cols):
+    """The fused query / key / value projection on the LDS tiles of bgemm.hip (864 tokens and more at 640 channels) with every
+    grouping of the transposed values: FULL and each patch's DISPLACED eps, and the keys and values they leave."""
+    say("qkv on tiles", H, W, B, cols)
+    cfg = ut.UNetCfg(H=H, W=W, N=2, levels=(64, 640), depths=(0, 1), groups=32, emb_dim=128, text_len=13, text_dim=96,
+                     res_per_level=1)
+    weights = configs.unet_weights(cfg, seed=9, threads=8)
+    t = configs.unet_inputs(cfg, seed=9, stale_std=0.5)
+    scale = np.arange(1, B + 1).reshape(B, 1, 1, 1)
+    x_prev, x = np.concatenate([t["x_prev"]] * B) * scale, np.concatenate([t["x"]] * B) * scale
+    emb, text = np.concatenate([t["emb"]] * B), np.concatenate([t["text"]] * B)
+    bl, P, ostale, ax = ut.blocks(cfg), ounet.Params(weights), {}, 2 if cols else 1
+    net = df.PatchUNet(cfg, _upload(weights), B=B, device=DEV, split_axis=df.SPLIT_COLS if cols else df.SPLIT_ROWS)
+    emb_d, text_d = dev(emb), dev(text, True)
+
+    def kv(o):
+        for nm in net.stale_names():
+            if nm.endswith((".k", ".v")):
+                check(*_stale_as_oracle(net, nm, cfg, B, o, cols), True, nm, say=say)
+
+    o_full = ounet.unet_step(cfg, bl, P, x_prev, emb, text, ostale, mode=ounet.FULL, split_axis=ax)
+    check_eps(host(net.step(dev(x_prev), emb_d, text_d, mode=df.MODE_FULL)), o_full, "FULL eps")
+    kv(ostale)
+    stale0 = net.stale.clone()
+    for i in range(2):
+        net.stale.copy_(stale0)
+        snap = {k: v.copy() for k, v in ostale.items()}
+        xs = np.ascontiguousarray(np.split(x, 2, ax)[i])
+        o_disp = ounet.unet_step(cfg, bl, P, xs, emb, text, snap, i, ounet.DISPLACED, split_axis=ax)
+        check_eps(host(net.step(dev(xs), emb_d, text_d, patch_idx=i, mode=df.MODE_DISPLACED)), o_disp, "patch %d eps" % i)
+        kv(snap)
+    net.close()
+
+
 def test_euler_update():
     x = torch.randn(1, 20, 240, 4, device=DEV)
     e = torch.randn(1, 20, 240, 4, device=DEV)

@@ -29,7 +29,7 @@ def _case(seed, R, W, C, G, N, bf16):
 @pytest.mark.parametrize("bf16", [True, False])
 def test_noalloc_groupnorm_matches_allocating_entry_point(bf16):
     G, N, patch = 32, 2, 1
-    # both shapes take the statistics / finalize / apply kernels (more than 80 K values per group), i.e. use scratch
+    # the first two take two launches (more than 3264 pixels of ten channels per group), i.e. use scratch
     shapes = [(72, 128, 320), (66, 128, 320), (4, 8, 64)]        # then a tiny one that needs no scratch at all
     for k, (R, W, C) in enumerate(shapes):
         print("noalloc groupnorm", bf16, R, W, C, flush=True)
