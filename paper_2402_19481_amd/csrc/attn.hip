@@ -95,8 +95,9 @@ __device__ long long g_attn_trace[512 * 32];
 // V_{t-2}, last read in iteration t-1: the barrier at that iteration's end lies between.  K_0 is read before the loop, so
 // S_0 has a barrier of its own before iteration 0 requests K_3.
 // Bound by the exponentials (64 of 8.3 cycles per wave and tile against 16 MFMAs of 32) and what the power limit leaves of
-// the clock.  Measured against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10 heads
-// 1435 -> 1105 us (961 TFLOP/s), 4096 x 4096 x 10 88 -> 66, 1024 x 4096 x 20 51.6 -> 38, 1200 x 9600 x 10 66 -> 46.
+// the clock.  Measured in the step (PRE) against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10
+// heads 1435 -> 1100 us (965 TFLOP/s), 1024 x 4096 x 20 51.6 -> 37, 1200 x 9600 x 10 66 -> 46.4 with the merge; queries without
+// the scale: 4096 x 4096 x 10 88 -> 69.
 // Three workgroups per unit instead of two (168 registers) gain 2 % on the largest of these and lose 3-5 % below.
 // Fresh and stale rows (kSrcRows, kSrcPeriodic): the splice is resolved in the source addresses of the direct loads, tile by tile
 // where a tile lies on one side, lane by lane else; V is transposed by ds_read_b64_tr_b16 on its way from LDS to the registers.
@@ -810,7 +811,7 @@ __global__ __launch_bounds__(256) void attn_combine_d64(AttnParams p) {
 // key (16-byte loads, the score is summed over them), so a wave's step covers 256/D keys, four of them per lane in flight;
 // every group of lanes keeps its own (max, sum, O) and the groups, then the waves, are merged at the end.
 // Latency-bound at the sizes it is used at (whole keys per lane and 6 x D shuffles at the end before: 128 queries x
-// 256 keys, d = 32: 18.3 -> 5 us).  QN = 4 reuses the loads of a key for four queries and is taken where one query
+// 256 keys, d = 32: 18.3 -> 5.3 us; 2304 x 9216, d = 64: 513).  QN = 4 reuses the loads of a key for four queries and is taken where one query
 // per workgroup would already give every compute unit eight workgroups.
 template <int D, int QN>
 __global__ __launch_bounds__(256) void attn_f32(AttnParams p) {
@@ -1004,8 +1005,8 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   // keys; no partials, no merge kernel.  Each block streams the head's whole K / V^T, so a compute unit pulls Lq / 32 x
   // the head's keys through its load path where the LDS-shared kernel pulls Lq / 128 x: taken where its time, a launch
   // and 1.93 us per 64-key tile of a wave, is below the other's, and only with its workgroups in one round (at most one
-  // per compute unit).  300 queries x 2400 keys x 20 heads 15.1 us (split form 17.9), 256 x 1024 x 10 8.6 (11.9),
-  // 256 x 4096 x 10 20.1 (17.4).
+  // per compute unit).  Cold keys, one box: 300 queries x 2400 keys x 20 heads 17.7 us (split form 19.2), 256 x 1024 x 10 9.6
+  // (12.6), 256 x 4096 x 10 21.7 (18.6); boxes differ by a tenth (16.2 - 18.0 us for the first inside the step).
 #ifdef DF_TUNING
   const char* wave_env = tune_env("DF_ATTN_WAVE");
 #else
