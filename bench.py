@@ -29,13 +29,27 @@ PEAK_HBM_GBS = 8000.0
 TRAFFIC_PROFILE = os.path.join("profiles", "unet_step_cfg4_hbm_traffic.md")
 
 
+def kernel_sources_digest():
+    """Digest of the kernel sources, by which a committed counter profile says which kernels it measured."""
+    import hashlib
+    h = hashlib.sha256()
+    src = os.path.join(ROOT, "paper_2402_19481_amd", "csrc")
+    for name in sorted(n for n in os.listdir(src) if n.endswith((".hip", ".h"))):
+        h.update(name.encode())
+        h.update(open(os.path.join(src, name), "rb").read())
+    return h.hexdigest()[:16]
+
+
 def traffic_from_profile(cls=None, kernel=None):
     """HBM bytes of a kernel class per step, or of one kernel per launch, as the committed rocprofv3 --pmc summary of
     this command states them (FETCH_SIZE + WRITE_SIZE, calibrated with `bench.py --calibrate-copy`), or None.  Counter
-    runs are separate profiler runs by nature, so this is never a measurement of the present run and is labelled so."""
+    runs are separate profiler runs by nature, so this is never a measurement of the present run and is labelled so;
+    a summary of other kernel sources than the present ones is not reported at all."""
     try:
-        for line in open(os.path.join(ROOT, TRAFFIC_PROFILE)):
-            f = line.split()
+        lines = [line.split() for line in open(os.path.join(ROOT, TRAFFIC_PROFILE))]
+        if ["kernel_sources_digest", kernel_sources_digest()] not in lines:
+            return None
+        for f in lines:
             if cls and len(f) == 3 and f[0] == "traffic_per_step_bytes" and f[1] == cls:
                 return float(f[2])
             if kernel and len(f) > 2 and f[0] == "traffic_per_launch_bytes" and " ".join(f[2:]) == kernel:
@@ -264,7 +278,7 @@ def run_tile_sweep(df, torch):
 
 def run_timeline(df, torch, tune_path):
     """In-kernel timelines from the tuning build (cycle stamps written by the kernels themselves): how a wave-level linear
-    layer of the patch step divides into prologue, K loop and reduction + epilogue, and the tiles of the self-attention
+    layer of the patch step (the shapes that stay on wgemm.hip) divides into prologue, K loop and reduction + epilogue, and the tiles of the self-attention
     whose waves split the keys.  One JSON line per case."""
     import ctypes
     import math
@@ -302,13 +316,12 @@ def run_timeline(df, torch, tune_path):
                                      "epilogue_later_passes": mean([r[4] - r[9] for r in t])}}), flush=True)
 
     M = 300
-    for name, N, K, geglu, ln in (("linear_packed 300x10240x1280 geglu ln", 10240, 1280, True, True),
-                                  ("linear_packed 300x1280x5120", 1280, 5120, False, False),
-                                  ("linear_packed 300x1280x1280", 1280, 1280, False, False),
-                                  ("linear_packed 300x3840x1280 ln", 3840, 1280, False, True)):
+    for name, N, K, ln in (("linear_packed 300x1280x5120", 1280, 5120, False),
+                           ("linear_packed 300x1280x1280", 1280, 1280, False),
+                           ("linear_packed 300x3840x1280 ln", 3840, 1280, True)):
         xw, ww, bw = bf(rn(M, K)), bf(rn(N, K) / math.sqrt(K)), rn(N)
         xp, wp = df.pack_rows(xw), df.pack_linear_weight(ww)
-        kw = dict(geglu=geglu, want=("packed",))
+        kw = dict(want=("packed",))
         if ln:
             kw.update(ln_s=rn(N), ln_t=rn(N))
         else:
@@ -500,7 +513,7 @@ def main():
     ap.add_argument("--tile-sweep", action="store_true",
                     help="tile-shape sweep of the LDS-tiled MFMA kernel on large shapes (needs the tuning build)")
     ap.add_argument("--timeline", action="store_true",
-                    help="in-kernel cycle stamps of the tiled MFMA kernel and the wave-level linear layers (needs the tuning build)")
+                    help="in-kernel cycle stamps of the wave-level linear layers and the few-query attention (needs the tuning build)")
     ap.add_argument("--ops", action="store_true",
                     help="single-operation measurements at the shapes of the other configurations instead of the step")
     args = ap.parse_args()
