@@ -518,7 +518,7 @@ def main():
                     help="single-operation measurements at the shapes of the other configurations instead of the step")
     args = ap.parse_args()
     if args.gpus != 1:
-        print("bench.py: this build runs on one GPU only (no collectives, no sharding); use --gpus 1", file=sys.stderr)
+        print("bench.py: the library runs on one GPU only (no collectives, no sharding); use --gpus 1", file=sys.stderr)
         sys.exit(2)
 
     import torch

@@ -344,7 +344,7 @@ int df_mfma_probe(float* out, int blocks, int iters, double* flops, void* stream
 
 /* Measurement support: the cost of making every workgroup wait for all others, which decides between one launch per
  * layer and a persistent kernel for the step (Section 5.1 removes launch overhead with CUDAGraph; this is the
- * measurement behind this build's choice of graph-replayed separate launches).  `iters` dependent phases over `blocks`
+ * measurement behind the choice of graph-replayed separate launches).  `iters` dependent phases over `blocks`
  * workgroups (34 <= blocks <= number of compute units), each phase = write 1 KB per workgroup, then read what another
  * workgroup wrote: mode 0 one kernel per phase, mode 1 one kernel with a fenced counter barrier per phase, mode 2 one
  * kernel exchanging 32 tagged words per workgroup through relaxed device-scope atomics (no fences).  Every wait is

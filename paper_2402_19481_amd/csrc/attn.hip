@@ -1005,8 +1005,8 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   // keys; no partials, no merge kernel.  Each block streams the head's whole K / V^T, so a compute unit pulls Lq / 32 x
   // the head's keys through its load path where the LDS-shared kernel pulls Lq / 128 x: taken where its time, a launch
   // and 1.93 us per 64-key tile of a wave, is below the other's, and only with its workgroups in one round (at most one
-  // per compute unit).  Cold keys, one box: 300 queries x 2400 keys x 20 heads 17.7 us (split form 19.2), 256 x 1024 x 10 9.6
-  // (12.6), 256 x 4096 x 10 21.7 (18.6); boxes differ by a tenth (16.2 - 18.0 us for the first inside the step).
+  // per compute unit).  Cold keys, one machine: 300 queries x 2400 keys x 20 heads 17.7 us (split form 19.2), 256 x 1024 x 10
+  // 9.6 (12.6), 256 x 4096 x 10 21.7 (18.6); machines differ by a tenth (16.1 - 18.0 us for the first inside the step).
 #ifdef DF_TUNING
   const char* wave_env = tune_env("DF_ATTN_WAVE");
 #else
