@@ -71,7 +71,6 @@ __device__ long long g_attn_trace[512 * 32];
 #define DF_ATRACE(slot, expr) do {} while (0)
 #endif
 
-#define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
 #define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 // Self-attention of the UNet step for many queries: the matrix pipe and the vector ALU of a SIMD work at the same time only
@@ -202,10 +201,11 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     const int left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
     kofr[j] = (unsigned int)(trow[j] < left ? trow[j] : left) * (unsigned int)p.ldks + (unsigned int)kch[j];
   }
-  auto kptr = [&](int ti, int j) {
+  auto load_k = [&](int ti, int j, const char* dst) {
     const int key0 = kv_lo + ti * TK;
-    return kg + (long long)key0 * p.ldks + (key0 + TK > p.L ? kofr[j] : kofs[j]);
+    lds_load16(kg + (long long)key0 * p.ldks, 2u * (key0 + TK > p.L ? kofr[j] : kofs[j]), dst);
   };
+  auto load_v = [&](int ti, int j, const char* dst) { lds_load16(vg + kv_lo + ti * TK, 2u * vofs[j], dst); };
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
@@ -228,23 +228,23 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     if constexpr (SRC == kSrcVt) {
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kptr(ti, j)), DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+        load_k(ti, j, smem + i * KB + (2 * wave + j) * 1024);
     } else {
       const Rows r = rows_of(kv_lo + ti * TK);
 #pragma unroll
       for (int j = 0; j < 2; ++j)
-        __builtin_amdgcn_global_load_lds(DF_GPTR(r.k[j]), DF_LPTR(smem + i * KB + (2 * wave + j) * 1024), 16, 0, 0);
+        lds_load16(r.k[j], smem + i * KB + (2 * wave + j) * 1024);
       if (i == 0) {
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          __builtin_amdgcn_global_load_lds(DF_GPTR(r.v[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
+          lds_load16(r.v[j], smem + 3 * KB + (2 * wave + j) * 1024);
       }
     }
   }
   if constexpr (SRC == kSrcVt) {
 #pragma unroll
     for (int j = 0; j < 2; ++j)
-      __builtin_amdgcn_global_load_lds(DF_GPTR(vg + kv_lo + vofs[j]), DF_LPTR(smem + 3 * KB + (2 * wave + j) * 1024), 16, 0, 0);
+      load_v(0, j, smem + 3 * KB + (2 * wave + j) * 1024);
   }
 
   // LDS byte offsets of this lane's fragments inside a tile.  K: MFMA row c of key block kb, k-step s; V^T: feature csig of
@@ -404,20 +404,20 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       };
       const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
       const bf16_t *kp[2], *vp[2];
-      if constexpr (SRC == kSrcVt) {
-        const bf16_t* vb1 = vg + kv_lo + tv1 * TK;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { kp[j] = kptr(tk3, j); vp[j] = vb1 + vofs[j]; }
-      } else {
+      if constexpr (SRC != kSrcVt) {
         const Rows r3 = rows_of(kv_lo + tk3 * TK), r1 = rows_of(kv_lo + tv1 * TK);
 #pragma unroll
         for (int j = 0; j < 2; ++j) { kp[j] = r3.k[j]; vp[j] = r1.v[j]; }
       }
       auto dma_k = [&](int j) {
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kp[j]), DF_LPTR(smem + kdst + (2 * wave + j) * 1024), 16, 0, 0);
+        const char* dst = smem + kdst + (2 * wave + j) * 1024;
+        if constexpr (SRC == kSrcVt) load_k(tk3, j, dst);
+        else lds_load16(kp[j], dst);
       };
       auto dma_v = [&](int j) {
-        __builtin_amdgcn_global_load_lds(DF_GPTR(vp[j]), DF_LPTR(smem + vdst + (2 * wave + j) * 1024), 16, 0, 0);
+        const char* dst = smem + vdst + (2 * wave + j) * 1024;
+        if constexpr (SRC == kSrcVt) load_v(tv1, j, dst);
+        else lds_load16(vp[j], dst);
       };
       DF_FENCE;
       if constexpr (SRC != kSrcVt) { E(0, 0); E(0, 1); DF_FENCE; varrive(vt, H1{}); DF_FENCE; }
@@ -569,20 +569,19 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
     if (key0 + TK <= p.L) {                                  // (uniform) every key row of the tile exists
       const bf16_t* kb0 = kg + (long long)key0 * p.ldks;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) __builtin_amdgcn_global_load_lds(DF_GPTR(kb0 + kofs[j]), DF_LPTR(sk + j * 1024), 16, 0, 0);
+      for (int j = 0; j < 8; ++j) lds_load16(kb0, 2u * kofs[j], sk + j * 1024);
     } else {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int row = j * 8 + lr;
         int key = key0 + row;
         if (key > p.L - 1) key = p.L - 1;                    // rows beyond the last key are masked in the tile body
-        __builtin_amdgcn_global_load_lds(DF_GPTR(kg + (long long)key * p.ldks + ((slot ^ ((row >> 1) & 7)) * 8)),
-                                         DF_LPTR(sk + j * 1024), 16, 0, 0);
+        lds_load16(kg + (long long)key * p.ldks + ((slot ^ ((row >> 1) & 7)) * 8), sk + j * 1024);
       }
     }
     const bf16_t* vb0 = vg + key0;                           // the V^T buffer is padded to whole tiles
 #pragma unroll
-    for (int j = 0; j < 8; ++j) __builtin_amdgcn_global_load_lds(DF_GPTR(vb0 + vofs[j]), DF_LPTR(sv + j * 1024), 16, 0, 0);
+    for (int j = 0; j < 8; ++j) lds_load16(vb0, 2u * vofs[j], sv + j * 1024);
   };
   bf16x8 kfr[2][4];
   u32x4 vfr[4][2];

@@ -9,9 +9,6 @@ namespace {
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_b;
 
-#define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
-#define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
 template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
@@ -52,7 +49,9 @@ struct Epi {
 // 256 x 320 with 320 a divisor of most layers' widths, and the choice by predicted time below.  With the stages requested
 // in parts between the matrix instructions and the 320-wide tiles, 1024 x 10240 x 1280 with GEGLU 46.6 -> 36.3 us, 1800
 // x 10240 x 1280 68 -> 62, 4096 x 5120 x 640 43.5 -> 39.9, 14400 x 640 x 2560 with residual 78 -> 61.  Four waves of 64 x
-// 160 instead of eight of 32 x 160: 40 us (one wave per SIMD issues the epilogue half as fast).
+// 160 instead of eight of 32 x 160: 40 us (one wave per SIMD issues the epilogue half as fast).  With loads that leave the waits
+// for LDS reads exact (lds_load_buf): 1800 x 1280 x 5120 48.9 -> 41.4 us, 1800 x 3840 x 1280 30.4 -> 27.5, 4096 x 1280 x 1280 27.2
+// -> 24.7; 1800 x 10240 x 1280 with GEGLU, bound by its epilogue, 65 -> 64.
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
 __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(WParams p) {
   using E = Epi<WT, WF, TT, TF, KG, OCC, LN>;
@@ -122,13 +121,13 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   // loads of a stage: all (STEP < 0), or part STEP of KS
   auto issue = [&](int kt, int slot, auto stepc) {
     constexpr int STEP = decltype(stepc)::value;
-    const size_t ko = (size_t)kt * (BKF * 1024);
+    const unsigned int ko = (unsigned int)kt * (BKF * 1024);
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
       if (STEP >= 0 && q * KS / NL != STEP) continue;
       int i = wave * NL + q;
       if (i > I - 1) i = I - 1;
-      __builtin_amdgcn_global_load_lds(DF_GPTR(src[q] + ko + lo), DF_LPTR(smem + slot * STAGE + i * 1024), 16, 0, 0);
+      lds_load_buf(src[q], lo, ko, smem + slot * STAGE + i * 1024);
     }
   };
 

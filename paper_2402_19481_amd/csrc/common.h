@@ -85,6 +85,35 @@ __device__ __forceinline__ void st_vec(bf16_t* p, const float* v) {
   *reinterpret_cast<u32x4*>(p) = t;
 }
 
+// Direct loads, memory -> LDS: lane i's 16 bytes go to dst + 16 i (`dst` the same for the whole wave).  They count in vmcnt, and
+// the caller waits (s_waitcnt, then a barrier if other waves read).  Two forms, neither of them the compiler's global_load_lds
+// builtin: it takes that for an access to LDS in flight and turns every wait for an LDS read behind one into lgkmcnt(0), so
+// operands requested for the next matrix instructions were waited for at once.
+//   - lds_load_buf: from base + sofs (uniform) + ofs bytes.  The form to use where 32-bit lane offsets do.
+//   - lds_load16: from a lane's own pointer, or base (uniform) + ofs bytes, as instructions the compiler does not count: keep it
+//     out of loops that are entered with other loads in flight (it waits for those with vmcnt(0) in every pass).  M0, which
+//     holds the LDS address, is named as clobbered: the compiler warns that it is a reserved register, and orders its own writes
+//     of M0 (for lds_load_buf) by it.
+// 1800 x 1280 x 5120 on 128 x 128 tiles (bgemm.hip): 50 us with the global builtin, 52 - 54 with lds_load16 (the residual's
+// loads are in flight there), 40.4 with lds_load_buf; attention 7200 x 57600 x 10 heads: 1227, 1194, 1215 us.
+__device__ __forceinline__ unsigned int lds_offset(const void* p) {
+  return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+__device__ __forceinline__ void lds_load_buf(const void* base, unsigned int ofs, unsigned int sofs, void* dst) {
+  // raw buffer descriptor: stride 0, no bound, data format 32
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(__builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, -1, 0x00020000),
+                                           (__attribute__((address_space(3))) void*)dst, 16, ofs, sofs, 0, 0);
+}
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
+__device__ __forceinline__ void lds_load16(const void* src, const void* dst) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_offset(dst)) : "memory", "m0");
+}
+__device__ __forceinline__ void lds_load16(const void* base, unsigned int ofs, const void* dst) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(ofs), "s"(base), "s"(lds_offset(dst)) : "memory", "m0");
+}
+#pragma clang diagnostic pop
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

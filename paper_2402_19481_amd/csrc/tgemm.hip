@@ -7,9 +7,6 @@ namespace df {
 
 namespace {
 
-#define DF_GPTR(p) ((const __attribute__((address_space(1))) void*)(p))
-#define DF_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
-
 template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
@@ -53,6 +50,8 @@ struct TgExtra {
 //     0.51 and 0.52, 0.77 together); HBM does not (weights cold or resident in L2: the same).
 //   - A wave issues its loads in four parts between the matrix instructions: all of them right behind the barrier kept
 //     every wave of the unit waiting for the load queue (256 x 128: 0.96 -> 0.77 us per slab).
+//   - Waits for LDS reads are exact (see the direct loads in common.h): 4096 pixels x 320 x 320 channels 22.7 -> 21.3 us, 1200 x 640
+//     x 640 22.7 -> 20.8, 4096 x 1280 x 1280 142 -> 134.
 //   - Weights are the MFMA's row operand, so a lane holds four consecutive output channels of one pixel and the tile is
 //     staged through LDS with 16-byte accesses.
 template <int BM, int BN, int WM, int WN, int KG, int ST, int OCC, bool kConv, typename OutT>
@@ -97,7 +96,9 @@ void tgemm_kernel(TileParams p, TgExtra x) {
   // direct loads: instruction j of a wave covers tile rows (wq*AJ + j)*8 + lane/8, LDS slot lane%8 of the row; row r keeps
   // its 16-byte chunk c at slot c ^ ((r >> 1) & 7)
   const int lr = lane >> 3;
-  const bf16_t* a_base[AJ];                                              // channel 0 of the centre pixel / start of the row
+  const bf16_t* a_base[AJ];                                              // convolution: channel 0 of the centre pixel
+  const char* const a_tile = (const char*)(p.A + (long long)m0 * (kConv ? 0 : p.lda));   // linear layer: the tile's first row,
+  unsigned int a_ofs[AJ];                                                // and the lane's bytes from there (launcher: below 2^31)
   int a_r[AJ], a_c[AJ], a_b[AJ];
 #pragma unroll
   for (int j = 0; j < AJ; ++j) {
@@ -113,22 +114,25 @@ void tgemm_kernel(TileParams p, TgExtra x) {
       a_c[j] = (rem - a_r[j] * p.Wo) * p.stride;
       a_r[j] *= p.stride;
       a_base[j] = p.A + (((long long)a_b[j] * p.R + a_r[j]) * p.W + a_c[j]) * p.Cin + ch;
+      a_ofs[j] = 0;
     } else {
-      a_base[j] = p.A + (long long)m * p.lda + ch;
+      a_base[j] = nullptr;
       a_b[j] = a_r[j] = a_c[j] = 0;
+      a_ofs[j] = 2u * ((unsigned int)(m - m0) * (unsigned int)p.lda + (unsigned int)ch);
     }
   }
-  const bf16_t* b_ptr[BJ];
+  // tiled weights: tile (n/64, slab) is 8 KB contiguous, rows and swizzled slots exactly as they sit in LDS
+  const bool tiled = !kConv && p.packed_w;
+  const char* const b_tile = (const char*)(p.Wt + (tiled ? (long long)(n0 >> 6) * slabs_all * 4096 : (long long)n0 * p.ldw));
+  unsigned int b_ofs[BJ];
 #pragma unroll
   for (int j = 0; j < BJ; ++j) {
     const int row = (wq * BJ + j) * 8 + lr;
-    int n = n0 + row;
-    if (n >= p.N) n = p.N - 1;
-    // tiled weights: tile (n/64, slab) is 8 KB contiguous, rows and swizzled slots exactly as they sit in LDS
-    if (!kConv && p.packed_w) b_ptr[j] = p.Wt + ((long long)(n >> 6) * slabs_all * 64 + (n & 63)) * 64 + (lane & 7) * 8;
-    else b_ptr[j] = p.Wt + (long long)n * p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8;
+    const int n = (n0 + row < p.N ? n0 + row : p.N - 1) - n0;
+    b_ofs[j] = 2u * (tiled ? ((unsigned int)(n >> 6) * (unsigned int)slabs_all * 64u + (unsigned int)(n & 63)) * 64u + (lane & 7) * 8
+                           : (unsigned int)n * (unsigned int)p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8);
   }
-  const int b_step = !kConv && p.packed_w ? 4096 : 64;                  // elements between slabs
+  const unsigned int b_step = tiled ? 8192 : 128;                       // bytes between slabs
   // Convolution: a lane's source pixel changes only with the filter tap, every Cin / 64 slabs
   const bf16_t* a_tap[AJ];
   bool a_pad[AJ];
@@ -170,12 +174,13 @@ void tgemm_kernel(TileParams p, TgExtra x) {
       if (q * 4 / L != STEP) continue;
       const int j = q < AJ ? q : q - AJ;
       if (q < AJ) {
-        const bf16_t* src;
-        if constexpr (kConv) src = a_pad[j < AJ ? j : 0] ? a_tap[j < AJ ? j : 0] : a_tap[j < AJ ? j : 0] + (k0 - tap_k0);
-        else src = a_base[j < AJ ? j : 0] + k0;
-        __builtin_amdgcn_global_load_lds(DF_GPTR(src), DF_LPTR(sa + j * 1024), 16, 0, 0);
+        if constexpr (kConv) {
+          lds_load16(a_pad[j < AJ ? j : 0] ? a_tap[j < AJ ? j : 0] : a_tap[j < AJ ? j : 0] + (k0 - tap_k0), sa + j * 1024);
+        } else {
+          lds_load_buf(a_tile, a_ofs[j < AJ ? j : 0], (unsigned int)k0 * 2u, sa + j * 1024);
+        }
       } else {
-        __builtin_amdgcn_global_load_lds(DF_GPTR(b_ptr[j < BJ ? j : 0] + (long long)slab * b_step), DF_LPTR(sb + j * 1024), 16, 0, 0);
+        lds_load_buf(b_tile, b_ofs[j < BJ ? j : 0], (unsigned int)slab * b_step, sb + j * 1024);
       }
     }
   };
@@ -361,7 +366,7 @@ int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st) 
   auto al = [](const void* ptr, int a) { return ((uintptr_t)ptr % a) == 0; };
   const bool ok = p.K % 64 == 0 && (!conv || p.Cin % 64 == 0) && p.N % 4 == 0 && p.ldo % 4 == 0 && al(p.out, 16) && al(p.bias, 16) &&
                   al(p.chan_add, 16) && p.chan_ld % 4 == 0 && (!p.residual || (p.ldr % 4 == 0 && al(p.residual, 16)));
-  if (!ok) return DF_ESHAPE;
+  if (!ok || p.ldw >= (1 << 22) || (!conv && p.lda >= (1 << 22)) || p.K >= (1 << 22)) return DF_ESHAPE;   // 32-bit offsets inside a tile
   const int slabs = p.K / 64;
   int cfg = 0, ns = 1;
   double best = 1e30;

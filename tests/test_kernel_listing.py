@@ -25,3 +25,26 @@ def test_attention_ring_has_a_barrier_between_the_first_reads_and_the_first_refi
             if op:
                 order += "B" if op[0] == "s_barrier" else "L" if op[0].startswith("global_load_lds") else "r" if op[0].startswith("ds_read") else ""
         assert re.match(r"L+Br+B[^L]*L", order), (name, order)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs the compiler")
+@pytest.mark.parametrize("source", [s for s in build.SOURCES if "lds_load" in open(os.path.join(build.CSRC, s)).read()])
+def test_every_direct_load_follows_its_own_write_of_m0(source, tmp_path):
+    """A direct load takes its LDS address from M0.  Loads written as instructions set M0 themselves, the compiler's are preceded
+    by a write of the compiler's: the last write before a load must be of the load's own kind."""
+    out = tmp_path / "k.s"
+    subprocess.run(["hipcc", *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
+                   check=True, capture_output=True)
+    inside, last, loads = False, None, 0
+    for line in out.read_text().splitlines():
+        if line.startswith("_Z"):
+            last = None
+        if "#ASMSTART" in line or "#ASMEND" in line:
+            inside = "#ASMSTART" in line
+        op = line.split(";")[0].split()
+        if len(op) > 1 and op[0].startswith("s_") and op[1] == "m0,":
+            last = inside
+        if op and (op[0].startswith("global_load_lds") or (op[0].startswith("buffer_load") and op[-1] == "lds")):
+            loads += 1
+            assert last is inside, (loads, line)
+    assert loads > 0
