@@ -362,11 +362,27 @@ size_t gemm_scratch_bytes(long long M, long long N) {
   return kScratchCounterBytes + (size_t)(ns > 1 ? ns * M * N * (long long)sizeof(float) : 0);
 }
 
+int launch_conv_reduce(const TileParams& p, const float* partials, int nsplit, int out_dtype, hipStream_t st) {
+  const long long n = (long long)p.M * (p.N / 4);
+  const dim3 grid((unsigned)((n + 255) / 256));
+  if (out_dtype == DF_BF16) hipLaunchKernelGGL((tgemm_reduce_kernel<true, bf16_t>), grid, dim3(256), 0, st, p, partials, nsplit);
+  else hipLaunchKernelGGL((tgemm_reduce_kernel<true, float>), grid, dim3(256), 0, st, p, partials, nsplit);
+  DF_LAUNCH_CHECK();
+  return DF_OK;
+}
+
 int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st) {
   auto al = [](const void* ptr, int a) { return ((uintptr_t)ptr % a) == 0; };
   const bool ok = p.K % 64 == 0 && (!conv || p.Cin % 64 == 0) && p.N % 4 == 0 && p.ldo % 4 == 0 && al(p.out, 16) && al(p.bias, 16) &&
                   al(p.chan_add, 16) && p.chan_ld % 4 == 0 && (!p.residual || (p.ldr % 4 == 0 && al(p.residual, 16)));
   if (!ok || p.ldw >= (1 << 22) || (!conv && p.lda >= (1 << 22)) || p.K >= (1 << 22)) return DF_ESHAPE;   // 32-bit offsets inside a tile
+  // (the tiles below serve linear layers and the convolutions of stride 2, where a pixel is used by a quarter of the taps)
+#ifdef DF_TUNING
+  const bool tap_wise = tune_env("DF_TG") != nullptr;
+#else
+  const bool tap_wise = false;
+#endif
+  if (conv && p.stride == 1 && !tap_wise) return launch_rconv(p, out_dtype, st);
   const int slabs = p.K / 64;
   int cfg = 0, ns = 1;
   double best = 1e30;

@@ -48,5 +48,9 @@ __device__ __forceinline__ const T* conv_tap_src(const T* x, const T* top, const
 // Workgroup-tile kernel (tgemm.hip): linear layers and convolutions with K % 64 == 0 (Cin % 64 == 0), N % 4 == 0 and an
 // epilogue of whole 16-byte accesses.  DF_ESHAPE if the arguments do not fit.
 int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st);
+// Convolution of stride 1 with the input pixels kept in LDS over the taps (rconv.hip); the arguments are those launch_tgemm accepts.
+int launch_rconv(const TileParams& p, int out_dtype, hipStream_t st);
+// Adds the parts of a convolution in their order and finishes it (tgemm.hip).
+int launch_conv_reduce(const TileParams& p, const float* partials, int nsplit, int out_dtype, hipStream_t st);
 
 }  // namespace df
