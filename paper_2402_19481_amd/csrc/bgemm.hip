@@ -622,7 +622,7 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
     return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
   }
   if (p.parts > 1) {
-    if constexpr (TT == 1 && KG == 1 && OCC == 1) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);
+    if constexpr (TT == 1 && KG == 1 && OCC == 1 && TF != 3) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);
     return DF_ESHAPE;
   }
   if (p.ln_s) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PLAIN, true, 0>(p, st);
@@ -635,17 +635,25 @@ namespace {
 
 // Tile shapes.  `slab` and `epi` are the microseconds of a round of workgroups per 64 of K and for prologue + epilogue
 // (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, `alone` the round of a workgroup that
-// has a unit to itself where two would fit; fitted to 24 token counts x 5 layers with weights that no cache holds.  Chosen by
-// them (and the wave-level kernel's, see wgemm.hip), those layers take 1.5 % more than with the best of all.
-struct TileCfg { int bt, bf, occ; double base, slab, epi[4], alone; };
+// has a unit to itself where two would fit, `kf` the k-fragments of a stage; fitted to 38 token counts x 8 layers with weights
+// that no cache holds.  Chosen by them (and the wave-level kernel's, see wgemm.hip), those layers take 1.3 % more than with the
+// best of 18 shapes.  The 96-, 160- and 192-wide tiles and 256 x 256 are there because a round of workgroups over 256 units is
+// rarely full: 7200 x 640 x 2560 44.9 -> 33.2 us, 4096 x 1280 x 1280 28.8 -> 24.7, 1976 x 640 x 2560 23.3 -> 18.1, 4096 x 3840 x
+// 1280 55.7 -> 44.2, 494 x 10240 x 1280 with GEGLU 27.3 -> 24.7, 1024 x 1280 x 1280 12.7 -> 12.0.
+struct TileCfg { int bt, bf, occ, kf; double base, slab, epi[4], alone; };
 constexpr TileCfg kTiles[] = {
-    {8, 10, 1, 0.00, 1.603, {17.3, 28.6, 26.3, 1e9}, 1.0},    // 256 x 320, eight waves of 64 x 160
-    {4, 4, 2, 3.77, 1.078, {3.3, 5.7, 4.2, 7.4}, 0.70},       // 128 x 128, eight waves of 32 x 64, two workgroups per unit
-    {4, 4, 1, 1.80, 0.474, {5.3, 7.1, 6.0, 8.4}, 1.0},        // 128 x 128, four ring stages
-    {2, 4, 2, 3.90, 0.620, {3.0, 5.7, 2.9, 8.3}, 0.62},       // 64 x 128, two k-groups, two workgroups per unit
-    {2, 2, 2, 2.30, 0.432, {1e9, 3.3, 1.7, 7.3}, 0.86},       // 64 x 64, two k-groups, two workgroups per unit
-    {2, 2, 1, 2.50, 0.227, {1e9, 3.0, 1.9, 6.6}, 1.0},        // 64 x 64, two k-groups, four stages of 128
-    {4, 10, 1, 1.43, 0.947, {10.4, 15.4, 13.8, 1e9}, 1.0},    // 128 x 320, eight waves of 32 x 160
+    {8, 10, 1, 2, 1.51, 1.886, {13.8, 28.6, 19.2, 1e9}, 1.0},     // 256 x 320, eight waves of 64 x 160
+    {4, 4, 2, 4, 3.00, 0.982, {4.7, 5.7, 8.0, 7.4}, 0.71},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
+    {4, 4, 1, 4, 1.59, 0.468, {5.0, 7.1, 6.5, 8.4}, 1.0},         // 128 x 128, four ring stages
+    {2, 4, 2, 4, 3.11, 0.602, {3.4, 5.7, 4.8, 8.3}, 0.63},        // 64 x 128, two k-groups, two workgroups per unit
+    {2, 2, 2, 8, 2.52, 0.407, {1e9, 3.3, 2.4, 7.3}, 0.78},        // 64 x 64, two k-groups, two workgroups per unit
+    {2, 2, 1, 8, 2.31, 0.224, {1e9, 3.0, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128
+    {4, 10, 1, 2, 1.43, 1.056, {9.0, 15.4, 13.3, 1e9}, 1.0},      // 128 x 320, eight waves of 32 x 160
+    {2, 3, 1, 8, 2.83, 0.281, {1e9, 4.6, 3.2, 1e9}, 1.0},         // 64 x 96, four k-groups of 32 x 96
+    {4, 5, 1, 4, 1.88, 0.551, {1e9, 11.0, 8.6, 1e9}, 1.0},        // 128 x 160, two k-groups of 32 x 160
+    {8, 8, 1, 2, 1.04, 1.429, {12.9, 24.0, 17.7, 1e9}, 1.0},      // 256 x 256, eight waves of 64 x 128
+    {4, 3, 1, 4, 2.11, 0.412, {1e9, 7.0, 5.1, 1e9}, 1.0},         // 128 x 96, two k-groups of 32 x 96
+    {4, 6, 1, 2, 2.24, 0.690, {6.7, 10.5, 7.6, 1e9}, 1.0},        // 128 x 192, eight waves of 32 x 96
 };
 
 }  // namespace
@@ -659,6 +667,11 @@ int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
     case 4: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 2, 2>(p, st);
     case 5: return launch_tile_cfg<2, 2, 1, 1, 2, 4, 4, 1>(p, st);
     case 6: return launch_tile_cfg<4, 2, 1, 5, 1, 2, 5, 1>(p, st);
+    case 7: return launch_tile_cfg<2, 1, 1, 3, 4, 2, 4, 1>(p, st);
+    case 8: return launch_tile_cfg<4, 1, 1, 5, 2, 2, 4, 1>(p, st);
+    case 9: return launch_tile_cfg<4, 2, 2, 4, 1, 2, 4, 1>(p, st);
+    case 10: return launch_tile_cfg<4, 1, 1, 3, 2, 2, 5, 1>(p, st);
+    case 11: return launch_tile_cfg<4, 2, 1, 3, 1, 2, 6, 1>(p, st);
     default: return DF_ESHAPE;
   }
 }
@@ -668,7 +681,7 @@ namespace {
 // the second launch and of what the parts do beside their stages; each part's sums cost a write and a read.
 struct SplitCfg { int tile; double fixed; };
 constexpr SplitCfg kSplits[] = {{2, 4.3}, {6, 5.0}};
-constexpr int kMaxParts = 8;
+constexpr int kMaxParts = 8, kSplitFamily = 7;          // (the first tiles: those that parts of K were weighed against)
 constexpr double kPartUs = 2.2e-6;                     // microseconds per output value and part
 
 int max_parts(const TileCfg& t, long long MT, long long NF) {
@@ -689,16 +702,16 @@ size_t wgemm_scratch_bytes(long long M, long long N) {
 }
 
 // The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.  With
-// `scr`, `parts` receives the number of parts to split K into.
+// `scr`, `parts` receives the number of parts to split K into, 0 if `scr` is too small for them.
 int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts) {
   const int mode = p.xkv ? 3 : p.geglu ? 0 : p.nseg ? 1 : 2;
   const int MT = (p.M + 31) / 32, NF = p.N / 32;
   const double kt = p.K / 64.0;
   double best = other_us;
   int pick = -1;
-  for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
+  auto consider = [&](int c) {
     const TileCfg& t = kTiles[c];
-    if ((p.K / 64) % (c == 5 || c == 4 ? 2 : 1)) continue;          // two k-groups of 64 per stage
+    if ((p.K / 16) % t.kf) return;
     const int bfo = p.geglu ? t.bf / 2 : t.bf;
     const long long n = (long long)((MT + t.bt - 1) / t.bt) * ((NF + bfo - 1) / bfo);
     // rounds of workgroups; two workgroups of a unit share it, so their rounds are continuous beyond the first few
@@ -708,11 +721,12 @@ int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts
       r = n > 1536 ? n / 512.0 : (double)(n / 512) + (rem == 0 ? 0.0 : rem <= 256 ? t.alone : 1.0);
     }
     const double us = t.base + r * (kt * t.slab + t.epi[mode]);
-    if (us < best) { best = us; pick = c; }
-  }
-  // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts; 3600: 79 -> 70.  At 640 features and K = 2560 and
-  // below the sums cost what the parts gain.
+    if (us < best) { best = us; pick = c; *parts = 1; }
+  };
   *parts = 1;
+  for (int c = 0; c < kSplitFamily; ++c) consider(c);
+  // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts.  At 640 features and K = 2560 and below the sums cost what
+  // the parts gain.
   if (mode == 2 && !p.ln_s && scr) {
     for (const SplitCfg& q : kSplits) {
       const TileCfg& t = kTiles[q.tile];
@@ -723,7 +737,10 @@ int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts
         if (us < 0.97 * best) { best = us / 0.97; pick = q.tile; *parts = s; }
       }
     }
+    // a layer that splits here needs its scratch, also where one of the tiles below is faster in the end
+    if (*parts > 1 && !scratch_region(scr, kScratchCounterBytes + (size_t)*parts * MT * NF * 4096)) { *parts = 0; return -1; }
   }
+  for (int c = kSplitFamily; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) consider(c);
   return pick;
 }
 

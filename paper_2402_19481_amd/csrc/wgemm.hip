@@ -643,13 +643,15 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     const double n = wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)wg12;
     const double r = n / 256.0 > 0.6 ? n / 256.0 : 0.6;
     const double us = wide ? 9.7 + 0.125 * kt
-                      : two ? 4.6 + r * (0.286 * kt + (p.geglu ? 0.15 : p.nseg ? 0.88 : 1.16))
-                            : 5.3 + r * (0.189 * kt + (p.geglu ? -1.0 : p.nseg ? 0.35 : a.xa_kv ? 0.1 : -2.2));
+                      : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : p.ln_s ? 0.23 : 0.9))
+                      : a.xa_kv ? 5.3 + r * (0.189 * kt + 0.1)
+                                : 3.46 + r * (0.201 * kt + (p.geglu ? 2.1 : p.nseg ? 2.2 : p.ln_s ? 0.49 : 0.34));
     const char* e = tune_env("DF_BGEMM");
     // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
     int parts = 1;
-    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.94 * us, a.scr, &parts);
+    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.98 * us, a.scr, &parts);
     if (e && a.scr && tune_env("DF_PARTS")) parts = atoi(tune_env("DF_PARTS"));
+    if (parts < 1) return DF_ENOMEM;
     if (parts > 1) {
       char* scr = scratch_region(a.scr, kScratchCounterBytes + (size_t)parts * MT * nfrag * 4096);
       if (!scr) return DF_ENOMEM;
