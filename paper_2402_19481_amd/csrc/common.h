@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <stdlib.h>
+#include <type_traits>
 #include "../../include/distrifusion.h"
 
 namespace df {
@@ -118,6 +119,21 @@ __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
   return v;
+}
+
+// The wave's sum, the same for every lane, added in a fixed order: within rows of 16 lanes, then over the rows, by lane moves of the
+// vector ALU (six of them; a step through LDS costs a round trip).
+__device__ __forceinline__ float wave_total(float v) {
+  auto add = [&](auto ctrl, auto rows) {
+    v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, decltype(rows)::value, 0xf, true));
+  };
+  add(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});   // row_shr:1, 2, 4, 8: lane 15 of a row has its sum
+  add(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});
+  add(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});
+  add(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});
+  add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});   // row_bcast:15 into rows 1 and 3
+  add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});   // row_bcast:31 into rows 2 and 3
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
 // Kernel-selection overrides from the environment (DF_TG, DF_TGS, DF_BGEMM, DF_PARTS, DF_ATTN_*) exist only in builds with

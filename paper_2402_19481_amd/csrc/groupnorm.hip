@@ -238,42 +238,50 @@ struct GnMoments { float mean_hi, mean_lo, rstd; };
 // Mean and variance of one (batch item, group) from the fresh sums of this launch and the cached per-patch sums,
 // according to the statistic mode (Section 4, Eq. 2; Section 5.3).  Runs once per group, in double.
 // `st_*`: sums of the cached entries of the other patches, `own_*`: the cached entry of this patch.
-__device__ __forceinline__ GnMoments gn_combine_pre(double tot_s, double tot_q, double n_loc, int nseg, int N,
+// `inv_loc` = 1 / n_loc and `inv_all` = 1 / (n_loc * nseg * N) come from the host: this runs on one wave while the others wait, and
+// a division or a square root in double is some twenty dependent instructions.
+struct GnCount { double n_loc, inv_loc, inv_all; };
+__device__ __forceinline__ GnMoments gn_combine_pre(double tot_s, double tot_q, const GnCount& n, int nseg, int N,
                                                     int stat_mode, double st_s, double st_q, double own_s,
                                                     double own_q, float eps) {
   double mean, var;
   if (nseg > 1 || (N == 1 && stat_mode != DF_GN_STALE)) {
     // the whole image is fresh: exact statistics
-    const double n = n_loc * (double)nseg;
-    mean = tot_s / n;
-    var = fmax(tot_q / n - mean * mean, 0.0);
+    mean = tot_s * n.inv_all;
+    var = fmax(tot_q * n.inv_all - mean * mean, 0.0);
   } else {
-    const double n_glob = n_loc * (double)N;
-    const double loc_m = tot_s / n_loc, loc_m2 = tot_q / n_loc;
+    const double loc_m = tot_s * n.inv_loc, loc_m2 = tot_q * n.inv_loc;
     if (stat_mode == DF_GN_SUMS) {
-      mean = (tot_s + st_s) / n_glob;
-      var = fmax((tot_q + st_q) / n_glob - mean * mean, 0.0);
+      mean = (tot_s + st_s) * n.inv_all;
+      var = fmax((tot_q + st_q) * n.inv_all - mean * mean, 0.0);
     } else if (stat_mode == DF_GN_EQ2) {
-      mean = (st_s + own_s) / n_glob + (loc_m - own_s / n_loc);
-      const double m2 = (st_q + own_q) / n_glob + (loc_m2 - own_q / n_loc);
+      mean = (st_s + own_s) * n.inv_all + (loc_m - own_s * n.inv_loc);
+      const double m2 = (st_q + own_q) * n.inv_all + (loc_m2 - own_q * n.inv_loc);
       var = m2 - mean * mean;
       if (var < 0.0) var = loc_m2 - loc_m * loc_m;
     } else if (stat_mode == DF_GN_SEPARATE) {
       mean = loc_m;
       var = fmax(loc_m2 - loc_m * loc_m, 0.0);
     } else {
-      mean = (st_s + own_s) / n_glob;
-      var = fmax((st_q + own_q) / n_glob - mean * mean, 0.0);
+      mean = (st_s + own_s) * n.inv_all;
+      var = fmax((st_q + own_q) * n.inv_all - mean * mean, 0.0);
     }
   }
   GnMoments m;
   m.mean_hi = (float)mean;
   m.mean_lo = (float)(mean - (double)m.mean_hi);
-  m.rstd = (float)(1.0 / sqrt(var + (double)eps));
+  // one Newton step on the hardware's float estimate (1 ulp) leaves a relative error of 1e-14; outside float range the long way
+  const double v = var + (double)eps;
+  if (v > 1e-30 && v < 1e30) {
+    const double r = (double)__builtin_amdgcn_rsqf((float)v);
+    m.rstd = (float)(r * (1.5 - 0.5 * v * r * r));
+  } else {
+    m.rstd = (float)(1.0 / sqrt(v));
+  }
   return m;
 }
 
-__device__ __forceinline__ GnMoments gn_combine(double tot_s, double tot_q, double n_loc, int nseg, int N, int stat_mode,
+__device__ __forceinline__ GnMoments gn_combine(double tot_s, double tot_q, const GnCount& n_loc, int nseg, int N, int stat_mode,
                                                 const float* stale, int b, int g, int B, int G, int patch_idx,
                                                 float eps) {
   double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
@@ -316,7 +324,7 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
                                                  float* sums_out, const float* __restrict__ gamma,
                                                  const float* __restrict__ beta, int pix_seg, int C, int G, int nblk,
                                                  int nseg, int B, int patch_idx, int N, float eps, int stat_mode, int tp,
-                                                 int ppb, int pix_per_blk, int silu, int packed, GnHalo halo) {
+                                                 int ppb, int pix_per_blk, int silu, int packed, GnHalo halo, GnCount cnt) {
   constexpr int V = Elem<Tin>::kVec;
   __shared__ float s_red[2][32][kMaxG];
   __shared__ float s_mom[kMaxG][3];
@@ -347,7 +355,7 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
     double tot_s = 0.0, tot_q = 0.0;  // sums of x over all segments (valid where part == 0)
     // the partials are sums of x - pivot, the pivot being the group's first value of the batch item
     const float piv = folds ? Elem<Tin>::ld(x + (long long)b * nseg * pix_seg * C + g * cg) : 0.f;
-    const double n_seg = (double)pix_seg * (double)cg;
+    const double n_seg = cnt.n_loc;
     for (int sg = 0; sg < nseg; ++sg) {
       float a = 0.f, c = 0.f;
       if (folds) {
@@ -389,7 +397,7 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
           if (j == patch_idx) { own_s = av; own_q = cv; } else { st_s += av; st_q += cv; }
         }
       }
-      const GnMoments mo = gn_combine_pre(tot_s, tot_q, n_seg, nseg, N, stat_mode, st_s, st_q, own_s, own_q, eps);
+      const GnMoments mo = gn_combine_pre(tot_s, tot_q, cnt, nseg, N, stat_mode, st_s, st_q, own_s, own_q, eps);
       if (nseg == 1 && sums_out != nullptr && blk == 0) {   // may alias the patch's slot of the cache: every block reads
         float* o = sums_out + ((long long)b * G + g) * 2;   // the snapshot, never the cache itself
         o[0] = (float)tot_s; o[1] = (float)tot_q;
@@ -455,7 +463,7 @@ __global__ __launch_bounds__(1024) void gn_group_kernel(const Tin* __restrict__ 
                                                         const float* stale, float* sums_out,
                                                         const float* __restrict__ gamma, const float* __restrict__ beta,
                                                         int pix_seg, int C, int G, int nseg, int B, int patch_idx, int N,
-                                                        float eps, int stat_mode, int silu, int packed, GnHalo halo) {
+                                                        float eps, int stat_mode, int silu, int packed, GnHalo halo, GnCount cnt) {
   __shared__ float s_s[1024], s_q[1024];
   __shared__ float s_mr[3];
   const int g = blockIdx.x, b = blockIdx.y;
@@ -466,7 +474,7 @@ __global__ __launch_bounds__(1024) void gn_group_kernel(const Tin* __restrict__ 
   const bool active = psub < ppass;
   const int c0 = g * cg + cv * 4;
   const float piv = Elem<Tin>::ld(x + (long long)b * nseg * pix_seg * C + g * cg);   // sums are taken of x - piv
-  const double n_seg = (double)pix_seg * (double)cg;
+  const double n_seg = cnt.n_loc;
   double tot_s = 0.0, tot_q = 0.0;
   for (int sg = 0; sg < nseg; ++sg) {
     const long long base = ((long long)b * nseg + sg) * pix_seg;
@@ -502,7 +510,7 @@ __global__ __launch_bounds__(1024) void gn_group_kernel(const Tin* __restrict__ 
     __syncthreads();
   }
   if (tid == 0) {
-    const GnMoments mo = gn_combine(tot_s, tot_q, n_seg, nseg, N, stat_mode, stale, b, g, B, G, patch_idx, eps);
+    const GnMoments mo = gn_combine(tot_s, tot_q, cnt, nseg, N, stat_mode, stale, b, g, B, G, patch_idx, eps);
     if (nseg == 1 && sums_out != nullptr) {          // after the stale sums were read: may alias the own slot
       float* o = sums_out + ((long long)b * G + g) * 2;
       o[0] = (float)tot_s; o[1] = (float)tot_q;
@@ -579,18 +587,22 @@ __device__ __forceinline__ void st_chan(T* p, const float* v) {
 // The same for one segment whose share per lane is at most NV pixels: every lane requests all its pixels at once
 // (one memory round trip instead of one per pass) and keeps them in registers for the normalisation, so x is read
 // once.  V channels per lane: 4, or 2 where the group's channel count allows no more (320 channels in 32 groups).
-// Bound by two round trips and a workgroup's share of the load path; the two-launch path costs ~11 us however small the
-// tensor is: 16 x 64 x 320 12.1 -> 6.7 us, 16 x 64 x 1280 11.6 -> 10.0.
+// Bound by two round trips, the kernel's start and a workgroup's share of the load path.  Requests carry no branch (a lane without
+// a pixel repeats the last one and leaves it out of the sums), a wave adds its lanes without LDS, and the one wave that combines
+// the moments multiplies where it divided: 300 x 1280 float32 6.4 -> 5.5 us, 64 x 1280 4.5 -> 3.9, 494 x 1280 bf16 8.2 -> 7.1, 1200 x 640
+// float32 10.5 -> 9.4, 1024 x 1280 bf16 12.6 -> 11.0 (a launch after another, 1.5 us of each the boundary).  Two launches cost ~11 us however
+// small the tensor is.
 template <typename Tin, typename Tout, int NV, int V>
 __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restrict__ x, Tout* __restrict__ y,
                                                             const float* stale, float* sums_out,
                                                             const float* __restrict__ gamma, const float* __restrict__ beta,
                                                             int pix, int C, int G, int B, int patch_idx, int N, float eps,
-                                                            int stat_mode, int silu, int packed, GnHalo halo) {
-  __shared__ float s_s[1024], s_q[1024];
+                                                            int stat_mode, int silu, int packed, GnHalo halo, GnCount cnt) {
+  __shared__ float s_s[16], s_q[16];
   __shared__ float s_mr[3];
   const int g = blockIdx.x, b = blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = (int)blockDim.x >> 6;   // (16 waves)
   const int cg = C / G, cgv = cg / V;
   const int ppass = blockDim.x / cgv;
   const int cv = tid % cgv, psub = tid / cgv;
@@ -598,43 +610,50 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   const int c0 = g * cg + cv * V;
   const long long base = (long long)b * pix;
   const float piv = Elem<Tin>::ld(x + base * C + g * cg);     // sums are taken of x - piv
-  // everything that does not depend on x is requested first: affine parameters and the cached sums
+  // everything that does not depend on x is requested first: affine parameters and, in the first wave, the cached sums (lane j:
+  // patch j; added only after x has been requested - waited for here they held up the wave's share of x)
   float gm[V], bt[V];
 #pragma unroll
   for (int i = 0; i < V; ++i) { gm[i] = 0.f; bt[i] = 0.f; }
   if (active) { ld_chan<V>(gamma + c0, gm); ld_chan<V>(beta + c0, bt); }
-  double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
-  if (tid < 64)
-    gn_stale_wave((N == 1 && stat_mode != DF_GN_STALE) ? nullptr : stale, b, g, B, G, N, patch_idx, lane, st_s, st_q,
-                  own_s, own_q);
+  const bool cached = stale != nullptr && !(N == 1 && stat_mode != DF_GN_STALE);
+  float2 st = make_float2(0.f, 0.f);
+  if (cached && tid < 64 && lane < N) {
+    const float* sp = stale + (((long long)lane * B + b) * G + g) * 2;
+    st.x = sp[0]; st.y = sp[1];
+  }
   float v[NV][V];
   float a = 0.f, q = 0.f;
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int p = psub + k * ppass;
-#pragma unroll
-    for (int i = 0; i < V; ++i) v[k][i] = 0.f;
-    if (active && p < pix) {
-      ld_chan<V>(x + (base + p) * C + c0, v[k]);
-    }
+    ld_chan<V>(x + (base + (p < pix ? p : pix - 1)) * C + c0, v[k]);      // (without branches; absent pixels are not added)
   }
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    if (!(active && psub + k * ppass < pix)) continue;          // absent pixels hold zeros, not the pivot
+    const bool here = active && psub + k * ppass < pix;
 #pragma unroll
-    for (int i = 0; i < V; ++i) { const float d = v[k][i] - piv; a += d; q = fmaf(d, d, q); }
+    for (int i = 0; i < V; ++i) { const float d = here ? v[k][i] - piv : 0.f; a += d; q = fmaf(d, d, q); }
   }
-  s_s[tid] = a; s_q[tid] = q;
+  a = wave_total(a); q = wave_total(q);
+  if (lane == 0) { s_s[wave] = a; s_q[wave] = q; }
   __syncthreads();
   if (tid < 64) {
-    float fs = 0.f, fq = 0.f;
-    for (int k = lane; k < (int)blockDim.x; k += 64) { fs += s_s[k]; fq += s_q[k]; }
-    fs = wave_sum(fs); fq = wave_sum(fq);
+    const float fs = wave_total(lane < nw ? s_s[lane] : 0.f), fq = wave_total(lane < nw ? s_q[lane] : 0.f);
+    double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
+    if (cached && N > 64) {
+      gn_stale_wave(stale, b, g, B, G, N, patch_idx, lane, st_s, st_q, own_s, own_q);
+    } else if (cached) {
+      for (int j = 0; j < N; ++j) {                             // patch order fixes the order of the additions
+        const float aj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st.x), j));
+        const float cj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st.y), j));
+        if (j == patch_idx) { own_s = aj; own_q = cj; } else { st_s += aj; st_q += cj; }
+      }
+    }
     if (tid == 0) {
-      const double n_loc = (double)pix * (double)cg;
       double S, SS;
-      gn_unshift(fs, fq, n_loc, piv, S, SS);
-      const GnMoments mo = gn_combine_pre(S, SS, n_loc, 1, N, stat_mode, st_s, st_q, own_s, own_q, eps);
+      gn_unshift(fs, fq, cnt.n_loc, piv, S, SS);
+      const GnMoments mo = gn_combine_pre(S, SS, cnt, 1, N, stat_mode, st_s, st_q, own_s, own_q, eps);
       if (sums_out != nullptr) {                     // after the stale sums were read: may alias the own slot
         float* o = sums_out + ((long long)b * G + g) * 2;
         o[0] = (float)S; o[1] = (float)SS;
@@ -721,6 +740,8 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
     halo.single = ((long long)a.Rseg * a.nseg == a.halo_rpp) ? 1 : 0;
   }
   if (pix_seg <= 0 || pix_seg * a.nseg > 0x7fffffffLL) return DF_ESHAPE;
+  const double n_loc = (double)pix_seg * (double)(a.C / a.G);
+  const GnCount cnt = {n_loc, 1.0 / n_loc, 1.0 / (n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1))};
   // small tensors: the whole GroupNorm in one launch, one workgroup per (group, batch item)
   {
     const int cg = a.C / a.G;
@@ -729,8 +750,10 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
     // channels per lane of the form that keeps its pixels in registers, and pixels per pass of its 1024 lanes
     const int v = cg % 4 == 0 ? 4 : cg % 2 == 0 ? 2 : 0;
     const int ppass = (v && cg / v <= 1024) ? 1024 / (cg / v) : 0;
-    // up to 16 pixels per lane (a workgroup's loads then take as long as the second launch would)
-    const int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? (pix_seg <= (long long)ppass * 8 ? 8 : 16) : 0;
+    // up to 16 pixels per lane (a workgroup's loads then take as long as the second launch would); the kernel requests nv of them
+    // whether they are there or not, so nv is the power of two from 2 on that holds the lane's share
+    int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? 2 : 0;
+    while (nv && (long long)ppass * nv < pix_seg) nv *= 2;
     if (!no_fused && (nv || (cg % 4 == 0 && cg / 4 <= 1024 && per_group <= kGnGroupMaxElems))) {
       dim3 grid(a.G, a.B);
       if (nv) {
@@ -738,15 +761,20 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
 #define DF_GN_REG(TI, TO, NVV, VV)                                                                                    \
   hipLaunchKernelGGL((gn_group_reg_kernel<TI, TO, NVV, VV>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,  \
-                     a.silu, a.y_packed, halo)
+                     a.silu, a.y_packed, halo, cnt)
 #define DF_GN_REG_T(NVV, VV)                                                                                          \
   {                                                                                                                   \
     if (a.in_dtype == DF_BF16) DF_GN_REG(bf16_t, bf16_t, NVV, VV);                                                    \
     else if (a.out_dtype == DF_BF16) DF_GN_REG(float, bf16_t, NVV, VV);                                               \
     else DF_GN_REG(float, float, NVV, VV);                                                                            \
   }
-        if (v == 4) { if (nv == 8) DF_GN_REG_T(8, 4) else DF_GN_REG_T(16, 4) }
-        else { if (nv == 8) DF_GN_REG_T(8, 2) else DF_GN_REG_T(16, 2) }
+#define DF_GN_REG_V(VV)                                                                                               \
+  {                                                                                                                   \
+    if (nv == 2) DF_GN_REG_T(2, VV) else if (nv == 4) DF_GN_REG_T(4, VV)                                              \
+    else if (nv == 8) DF_GN_REG_T(8, VV) else DF_GN_REG_T(16, VV)                                                     \
+  }
+        if (v == 4) DF_GN_REG_V(4) else DF_GN_REG_V(2)
+#undef DF_GN_REG_V
 #undef DF_GN_REG_T
 #undef DF_GN_REG
         DF_LAUNCH_CHECK();
@@ -755,7 +783,7 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
 #define DF_GN_GROUP(TI, TO)                                                                                         \
   hipLaunchKernelGGL((gn_group_kernel<TI, TO>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, a.sums_out, \
                      a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode, a.silu, \
-                     a.y_packed, halo)
+                     a.y_packed, halo, cnt)
       if (a.in_dtype == DF_BF16) DF_GN_GROUP(bf16_t, bf16_t);
       else if (a.out_dtype == DF_BF16) DF_GN_GROUP(float, bf16_t);
       else DF_GN_GROUP(float, float);
@@ -788,7 +816,7 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
 #define DF_GN_APPLY(TI, TO, NCHV)                                                                                     \
   hipLaunchKernelGGL((gn_apply<TI, TO, NCHV>), gs, dim3(thr_apply), 0, st, (const TI*)a.x, (TO*)a.y, partial,         \
                      stale_copy, a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, L.nblk, a.nseg, a.B, a.patch_idx, \
-                     a.N, a.eps, a.stat_mode, L.tp, L.ppb, L.pix_per_blk, a.silu, a.y_packed, halo)
+                     a.N, a.eps, a.stat_mode, L.tp, L.ppb, L.pix_per_blk, a.silu, a.y_packed, halo, cnt)
 #define DF_GN_BOTH(NCHV)                                                                                              \
   {                                                                                                                   \
     if (a.in_dtype == DF_BF16) DF_GN_STATS(bf16_t, NCHV); else DF_GN_STATS(float, NCHV);                              \
