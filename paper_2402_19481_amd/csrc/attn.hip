@@ -510,14 +510,19 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   }
 }
 
-// Self-attention of a patch with few queries (the deepest level: 300-1024 query rows against the whole image's keys).
+// Self-attention of a patch with few queries (the deepest levels: 32-1024 query rows against the whole image's keys).
 // One workgroup = one 32-query block of one head; its NW waves take contiguous runs of 64-key tiles and merge their
 // (max, sum, O) states through LDS at the end, so nothing is split across workgroups and no second kernel runs.
 // Nothing is shared between waves inside the loop: every wave stages its own K and V^T tiles (global -> LDS with
 // direct loads, 1 KB contiguous per instruction; a wave reading its MFMA operands straight from the row-major buffers
 // touches 32 cache lines per instruction and ran at a quarter of the rate) in a private 16 KB of LDS, so the loop has no
-// barrier: a tile's fragments go LDS -> registers, then the next tile's loads are issued into the same LDS while the
-// tile computes.  Same operand conventions and swizzles as attn_pipe_d64.
+// barrier: the fragments of V of tile i and of K of tile i + 1 go LDS -> registers, then the loads of V of tile i + 1 and K
+// of tile i + 2 are issued into the same LDS while the scores of tile i + 1 are on the matrix cores and the
+// exponentials of tile i on the vector ALU.  Same operand conventions and swizzles as attn_pipe_d64.
+// Two waves share a SIMD, and the one launched first took the issue slots: the later half carries the higher wave
+// priority.  300 queries x 2400 keys x 20 heads, cold keys: 17.7 us; scores a tile ahead 16.5; priority 15.5.  Of these the
+// launch takes 1.5, the first tiles' way from HBM 3 (12 MB of keys for all heads), the merge 1; a round of eight tiles takes
+// 1.3 us where its 128 KB need 1.2 at the rate that L2 fills a compute unit (52 B per clock).
 template <int NW>
 __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   constexpr int D = 64, TK = 64;
@@ -564,7 +569,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   }
   char* sk = smem + wave * (2 * TK * D * 2);                 // this wave's K tile [key][d], then its V^T tile [d][key]
   char* sv = sk + TK * D * 2;
-  auto issue = [&](int tl) {
+  auto issue_k = [&](int tl) {
     const int key0 = tl * TK;
     if (key0 + TK <= p.L) {                                  // (uniform) every key row of the tile exists
       const bf16_t* kb0 = kg + (long long)key0 * p.ldks;
@@ -579,15 +584,16 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
         lds_load16(kg + (long long)key * p.ldks + ((slot ^ ((row >> 1) & 7)) * 8), sk + j * 1024);
       }
     }
-    const bf16_t* vb0 = vg + key0;                           // the V^T buffer is padded to whole tiles
+  };
+  auto issue_v = [&](int tl) {
+    const bf16_t* vb0 = vg + tl * TK;                        // the V^T buffer is padded to whole tiles
 #pragma unroll
     for (int j = 0; j < 8; ++j) lds_load16(vb0, 2u * vofs[j], sv + j * 1024);
   };
   bf16x8 kfr[2][4];
   u32x4 vfr[4][2];
-  auto read_frags = [&]() {
+  auto read_k = [&]() {
     const bf16_t* Ks = reinterpret_cast<const bf16_t*>(sk);
-    const bf16_t* Vt = reinterpret_cast<const bf16_t*>(sv);
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb) {
       const int row = 32 * kb + key_of_mfma_row(c);
@@ -595,6 +601,9 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) kfr[kb][s] = *reinterpret_cast<const bf16x8*>(&Ks[row * D + (((2 * s + g) ^ f) * 8)]);
     }
+  };
+  auto read_v = [&]() {
+    const bf16_t* Vt = reinterpret_cast<const bf16_t*>(sv);
 #pragma unroll
     for (int ts = 0; ts < 4; ++ts) {
       const int kchunk = 4 * (ts >> 1) + 2 * (ts & 1) + g;
@@ -614,10 +623,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   float m_run = -INFINITY, l_run = 0.f;
   const float sc = p.sc_log2;
 
-  auto tile = [&](int tl, auto raggedc) {
-    constexpr bool ragged = decltype(raggedc)::value;
-    const int tile_base = tl * TK;
-    f32x16 s_acc[2];
+  auto scores = [&](f32x16 (&s_acc)[2]) {                    // S^T of the tile whose K fragments are in registers
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -627,91 +633,146 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
         s_acc[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[kb][s], qreg[s], s_acc[kb], 0, 0, 0);
-    if constexpr (ragged) {
+  };
+  auto new_max = [&](const f32x16 (&s_acc)[2]) {
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s_acc[kb][e]);
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(halves[0]), __uint_as_float(halves[1])) * sc;
+    return fmaxf(m_run, mx);                                 // finite: a tile holds at least one key
+  };
+  // P of 16 keys (MFMA operand) from their scores, the row sums on the way
+  auto probs = [&](f32x16 (&s_acc)[2], int ts, float m_new, float& rs) {
+    const int kb = ts >> 1, half = ts & 1;
+    float e8[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      e8[i] = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][8 * half + i], sc, -m_new));
+      rs += e8[i];
+    }
+    const u32x4 pk = {pack_bf2(e8[0], e8[1]), pack_bf2(e8[2], e8[3]), pack_bf2(e8[4], e8[5]), pack_bf2(e8[6], e8[7])};
+    return __builtin_bit_cast(bf16x8, pk);
+  };
+  auto rescale = [&](float m_new) {
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    m_run = m_new;
+    l_run *= alpha;                                          // this lane's half of the keys; the halves meet at the end
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o_acc[i][e] *= alpha;     // (without a branch: a jump here costs copies of all 32)
+  };
+  // The query blocks of a head read the same keys; started on the same tile they would all wait for the same cache
+  // lines while the rest of the head's K / V^T (cold: other patches' rows, last touched a step ago) is not even
+  // requested.  Block qb therefore walks each wave's run of tiles from a different starting tile, wrapping around:
+  // ten blocks keep ten tiles per wave slot in flight and find the others' tiles in L2.  The order is a fixed
+  // function of the indices, so results stay reproducible.  A tile with fewer than 64 keys stays the last.
+  const int nt = t_hi - t_lo;
+  const int nrot = t_hi * TK > p.L ? nt - 1 : nt;
+  const int rot = ((qb & 7) * nrot) >> 3;                    // < nrot, spread over the run
+  auto tile_at = [&](int i) { const int k = i + rot; return t_lo + (i >= nrot ? i : k < nrot ? k : k - nrot); };
+  // The scores run one tile ahead: while the exponentials and sums of tile i are on the vector ALU, the matrix cores take
+  // the scores of tile i + 1 and the product with V of tile i.
+  auto landed = [&]() {
+    __builtin_amdgcn_s_waitcnt((0 & 0xF) | (0x7 << 4) | (0xF << 8));   // vmcnt(0): this wave's loads are in its LDS
+    asm volatile("" ::: "memory");
+  };
+  auto in_registers = [&]() {
+    __builtin_amdgcn_s_waitcnt((0x3F & 0xF) | ((0x3F >> 4) << 14) | (0x7 << 4) | (0 << 8));   // lgkmcnt(0)
+    asm volatile("" ::: "memory");
+  };
+  auto step = [&](int i, f32x16 (&cur)[2], f32x16 (&nxt)[2]) {
+    landed();                                                // V of tile i, K of tile i + 1
+    DF_ATRACE(3 + 3 * i, __builtin_readcyclecounter());
+    read_k();
+    read_v();
+    const float m_new = new_max(cur);
+    in_registers();
+    DF_ATRACE(4 + 3 * i, __builtin_readcyclecounter());
+    issue_v(tile_at(i + 1));                                 // into the LDS just read, under this tile's work
+    if (i + 2 < nt) issue_k(tile_at(i + 2));                 // (uniform)
+    __builtin_amdgcn_sched_barrier(0);
+    scores(nxt);
+    rescale(m_new);
+    float rs = 0.f;
+#pragma unroll
+    for (int ts = 0; ts < 4; ++ts) {
+      const bf16x8 pfrag = probs(cur, ts, m_new, rs);
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfr[ts][db]), pfrag, o_acc[db], 0, 0, 0);
+    }
+    l_run += rs;
+    asm volatile("" : "+v"(l_run));                        // (here, not sunk into a later block)
+    __builtin_amdgcn_sched_barrier(0);
+    DF_ATRACE(5 + 3 * i, __builtin_readcyclecounter());
+  };
+  f32x16 s_a[2], s_b[2];
+  if (wave >= NW / 2) __builtin_amdgcn_s_setprio(1);
+  if (nt > 0) {
+    issue_k(tile_at(0));
+    issue_v(tile_at(0));
+    __builtin_amdgcn_s_waitcnt((8 & 0xF) | (0x7 << 4) | (0xF << 8));   // vmcnt(8): K is there
+    asm volatile("" ::: "memory");
+    read_k();
+    in_registers();
+    if (nt > 1) issue_k(tile_at(1));
+    scores(s_a);
+    DF_ATRACE(2, __builtin_readcyclecounter());
+    int i = 0;
+    for (; i + 2 < nt; i += 2) {
+      step(i, s_a, s_b);
+      step(i + 1, s_b, s_a);
+    }
+    if (i + 1 < nt) {
+      step(i, s_a, s_b);
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) s_a[kb] = s_b[kb];
+      ++i;
+    }
+    // the last tile: no scores ahead, and it may hold fewer than 64 keys
+    const int tile_base = tile_at(i) * TK;
+    landed();
+    DF_ATRACE(3 + 3 * i, __builtin_readcyclecounter());
+    read_v();
+    if (tile_base + TK > p.L) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int j = e >> 2, r = e & 3;
           const int key = tile_base + 32 * kb + 16 * (j >> 1) + 8 * g + 4 * (j & 1) + r;
-          if (key >= p.L) s_acc[kb][e] = -INFINITY;
+          if (key >= p.L) s_a[kb][e] = -INFINITY;
         }
-    }
-    float mx = -INFINITY;
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
+      for (int ts = 0; ts < 4; ++ts)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) mx = fmaxf(mx, s_acc[kb][e]);
-    mx = fmaxf(mx, __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)))) * sc;
-    const float m_new = fmaxf(m_run, mx);                    // finite: a tile holds at least one key
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-    float rs = 0.f;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(s_acc[kb][e], sc, -m_new));
-        s_acc[kb][e] = pv;
-        rs += pv;
-      }
-    l_run = l_run * alpha + rs;                              // this lane's half of the keys; the halves meet at the end
-    m_run = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) o_acc[i][e] *= alpha;
-    }
-#pragma unroll
-    for (int ts = 0; ts < 4; ++ts) {
-      const int kb = ts >> 1, half = ts & 1;
-      u32x4 pk;
-      pk.x = pack_bf2(s_acc[kb][8 * half + 0], s_acc[kb][8 * half + 1]);
-      pk.y = pack_bf2(s_acc[kb][8 * half + 2], s_acc[kb][8 * half + 3]);
-      pk.z = pack_bf2(s_acc[kb][8 * half + 4], s_acc[kb][8 * half + 5]);
-      pk.w = pack_bf2(s_acc[kb][8 * half + 6], s_acc[kb][8 * half + 7]);
-      const bf16x8 pfrag = __builtin_bit_cast(bf16x8, pk);
-#pragma unroll
-      for (int db = 0; db < 2; ++db) {
-        u32x4 vraw = vfr[ts][db];
-        if constexpr (ragged) {                              // keys beyond the range: P is 0, V must be finite
-          const int key = tile_base + (4 * kb + 2 * half + g) * 8;
+        for (int db = 0; db < 2; ++db) {                     // keys beyond the range: P is 0, V must be finite
+          const int key = tile_base + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
+          u32x4& vraw = vfr[ts][db];
           if (key + 0 >= p.L) vraw.x = 0u; else if (key + 1 >= p.L) vraw.x &= 0xffffu;
           if (key + 2 >= p.L) vraw.y = 0u; else if (key + 3 >= p.L) vraw.y &= 0xffffu;
           if (key + 4 >= p.L) vraw.z = 0u; else if (key + 5 >= p.L) vraw.z &= 0xffffu;
           if (key + 6 >= p.L) vraw.w = 0u; else if (key + 7 >= p.L) vraw.w &= 0xffffu;
         }
-        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vraw), pfrag, o_acc[db], 0, 0, 0);
-      }
     }
-  };
-  // The query blocks of a head read the same keys; started on the same tile they would all wait for the same cache
-  // lines while the rest of the head's K / V^T (cold: other patches' rows, last touched a step ago) is not even
-  // requested.  Block qb therefore walks each wave's run of tiles from a different starting tile, wrapping around:
-  // ten blocks keep ten tiles per wave slot in flight and find the others' tiles in L2.  The order is a fixed
-  // function of the indices, so results stay reproducible.
-  const int nt = t_hi - t_lo;
-  const int rot = ((qb & 7) * nt) >> 3;                      // < nt, spread over the run
-  auto tile_at = [&](int i) { const int k = i + rot; return t_lo + (k < nt ? k : k - nt); };
-  if (nt > 0) issue(tile_at(0));
-  DF_ATRACE(2, __builtin_readcyclecounter());
-  for (int i = 0; i < nt; ++i) {
-    const int tl = tile_at(i);
-    __builtin_amdgcn_s_waitcnt((0 & 0xF) | (0x7 << 4) | (0xF << 8));   // vmcnt(0): the tile has landed in LDS
-    asm volatile("" ::: "memory");
-    DF_ATRACE(3 + 3 * i, __builtin_readcyclecounter());
-    read_frags();
-    __builtin_amdgcn_s_waitcnt((0x3F & 0xF) | ((0x3F >> 4) << 14) | (0x7 << 4) | (0 << 8));   // lgkmcnt(0): fragments in registers
-    asm volatile("" ::: "memory");
+    const float m_new = new_max(s_a);
     DF_ATRACE(4 + 3 * i, __builtin_readcyclecounter());
-    if (i + 1 < nt) issue(tile_at(i + 1));                   // (uniform) into the LDS just read, under this tile's work
-    __builtin_amdgcn_sched_barrier(0);
-    if (tl * TK + TK <= p.L) tile(tl, std::false_type{});
-    else tile(tl, std::true_type{});
-    __builtin_amdgcn_sched_barrier(0);
+    rescale(m_new);
+    float rs = 0.f;
+#pragma unroll
+    for (int ts = 0; ts < 4; ++ts) {
+      const bf16x8 pfrag = probs(s_a, ts, m_new, rs);
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vfr[ts][db]), pfrag, o_acc[db], 0, 0, 0);
+    }
+    l_run += rs;
     DF_ATRACE(5 + 3 * i, __builtin_readcyclecounter());
   }
-  __builtin_amdgcn_s_waitcnt((0 & 0xF) | (0x7 << 4) | (0 << 8));
   l_run += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(l_run)));
 
   // ---- merge the NW states in wave order ----
@@ -1000,26 +1061,30 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   for (long long v : lds) if (v % 8) return DF_EINVAL;
   const void* ptrs[] = {a.q, a.k_fresh, a.v_fresh, a.k_stale, a.v_stale, a.out};
   for (const void* q : ptrs) if ((uintptr_t)q % 16) return DF_EINVAL;
-  // Few queries (the patch at the deepest level): one workgroup per 32-query block and head whose eight waves split the
+  // Few queries (the patch at the deepest levels): one workgroup per 32-query block and head whose eight waves split the
   // keys; no partials, no merge kernel.  Each block streams the head's whole K / V^T, so a compute unit pulls Lq / 32 x
-  // the head's keys through its load path where the LDS-shared kernel pulls Lq / 128 x: taken where its time, a launch
-  // and 1.93 us per 64-key tile of a wave, is below the other's, and only with its workgroups in one round (at most one
-  // per compute unit).  Cold keys, one machine: 300 queries x 2400 keys x 20 heads 17.7 us (split form 19.2), 256 x 1024 x 10
-  // 9.6 (12.6), 256 x 4096 x 10 21.7 (18.6); machines differ by a tenth (16.1 - 18.0 us for the first inside the step).
+  // the head's keys through its load path where the LDS-shared kernel pulls Lq / 128 x: it is only taken with its workgroups
+  // in one round (at most one per compute unit), and where a wave's rounds of 64 keys are few.  The more query blocks share a
+  // head's keys, the sooner they come from L2, and the more rounds it stays ahead: by measurement on 134 shapes, cold keys, up
+  // to 3 + 3/4 of the blocks, at most 10 (beyond, where the model of the split form says that it is slower still).
+  // Microseconds, split form against this: 64 queries x 256 keys x 10 heads 6.8 / 5.7, 128 x 512 x 20 10.7 / 7.4,
+  // 256 x 1024 x 10 13.3 / 9.1, 300 x 2400 x 20 20.7 / 15.7, 256 x 4096 x 10 19.8 / 18.6, 128 x 3072 x 20 19.2 / 18.7; the other way
+  // 32 x 2048 x 20 14.7 / 15.7, 128 x 4096 x 20 20.7 / 23.2, 300 x 9600 x 20 40.5 / 48.6.
 #ifdef DF_TUNING
   const char* wave_env = tune_env("DF_ATTN_WAVE");
 #else
   const char* wave_env = nullptr;
 #endif
-  const bool wave_fits = a.v_transposed && a.L >= 512 && (long long)cdiv(a.Lq, 32) * a.heads * a.B <= 256;
-  if (wave_fits && (wave_env ? atoi(wave_env) != 0
-                             : 4.7 + 1.93 * cdiv(cdiv(a.L, 64), 8) <
-                                   pipe_us(a.B, a.Lq, a.L, a.heads, false, pick_splits(a.B, a.Lq, a.L, a.heads, false)))) {
+  const long long qblocks = cdiv(a.Lq, 32), rounds = cdiv(cdiv(a.L, 64), 8);
+  const bool wave_fits = a.v_transposed && a.L >= 64 && qblocks * a.heads * a.B <= 256;
+  const bool wave_over_split = wave_fits && a.L >= 512 && (wave_env ? atoi(wave_env) != 0
+      : 4.7 + 1.93 * (double)rounds < pipe_us(a.B, a.Lq, a.L, a.heads, false, pick_splits(a.B, a.Lq, a.L, a.heads, false)));
+  const bool wave_few_rounds = wave_fits && (wave_env ? atoi(wave_env) != 0 : rounds <= 3 + 3 * qblocks / 4 && rounds <= 10);
+  auto launch_wave = [&]() -> int {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
-    p.vt_ld = a.vt_ld;
-    if (a.B > 65535 || cdiv(a.Lq, 32) > 65535) return DF_ESHAPE;
-    const dim3 grid((unsigned)(cdiv(a.heads, 8) * 8), (unsigned)cdiv(a.Lq, 32), (unsigned)a.B);
+    p.vt_ld = a.vt_ld; p.nsplit = 1; p.keys_per_split = a.L;
+    const dim3 grid((unsigned)(cdiv(a.heads, 8) * 8), (unsigned)qblocks, (unsigned)a.B);
     constexpr int NW = 8;
     constexpr int smem = NW * 2 * 64 * 64 * 2;          // a K and a V^T tile per wave; the merge reuses it
     static_assert(NW * 34 * 64 * 4 <= smem, "the merge fits");
@@ -1032,7 +1097,8 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(attn_wave_d64<NW>, grid, dim3(64 * NW), smem, st, p);
     DF_LAUNCH_CHECK();
     return DF_OK;
-  }
+  };
+  if (wave_over_split) return launch_wave();
   int ns = pick_splits(a.B, a.Lq, a.L, a.heads, !a.v_transposed);
   if ((long long)a.B * ns > 65535) return DF_ESHAPE;
   if ((long long)a.B * a.heads * a.Lq * 16 >= (1LL << 31)) return DF_ESHAPE;   // the merge kernel indexes with 32 bits
@@ -1048,6 +1114,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
       p.part_ml = p.part_o + (size_t)ns * a.B * a.heads * a.Lq * 64;
     }
   }
+  if (wave_few_rounds) return launch_wave();             // (what the caller has to provide stays that of the split form)
   const long long nwg = (long long)cdiv(a.Lq, 128) * a.heads * a.B * p.nsplit;
   if (nwg > 0x7fffffffLL) return DF_ESHAPE;
   if (a.v_transposed) {
