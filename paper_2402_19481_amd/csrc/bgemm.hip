@@ -584,8 +584,7 @@ int launch_one(const WParams& pin, hipStream_t st) {
   hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)parts), dim3(64 * NW), smem, st, p);
   DF_LAUNCH_CHECK();
   if constexpr (EPI == EPI_PART) {
-    hipLaunchKernelGGL(bgemm_sum_kernel, dim3((unsigned)((MT * NF * 2 + 3) / 4)), dim3(256), 0, st, p, parts);
-    DF_LAUNCH_CHECK();
+    return launch_part_sums(p, st);
   }
   return DF_OK;
 }
@@ -657,6 +656,14 @@ constexpr TileCfg kTiles[] = {
 };
 
 }  // namespace
+
+// Adds the parts of K, with bias and residual, and writes the layer's outputs.
+int launch_part_sums(const WParams& p, hipStream_t st) {
+  const int units = ((p.M + 31) / 32) * (p.N / 32) * 2;
+  hipLaunchKernelGGL(bgemm_sum_kernel, dim3((unsigned)((units + 3) / 4)), dim3(256), 0, st, p, p.parts);
+  DF_LAUNCH_CHECK();
+  return DF_OK;
+}
 
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
   switch (cfg) {

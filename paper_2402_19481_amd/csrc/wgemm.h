@@ -81,5 +81,6 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
 // Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1.
 int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts);
+int launch_part_sums(const WParams& p, hipStream_t st);
 
 }  // namespace df

@@ -37,7 +37,7 @@ __device__ long long g_wg_trace[1024 * 16];
 #define DF_WTRACE(slot, expr) do {} while (0)
 #endif
 
-template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA>
+template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA, bool PART>
 __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   DF_WTRACE(0, wall_clock64());
@@ -74,8 +74,8 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     t = xcd * base + (xcd < rem ? xcd : rem) + loc;
   }
   const int mg = t % MG, ng = t / MG;
-  const int KF = p.K >> 4, KFw = KF / KSPLIT;
-  const int kf0 = wave * KFw;
+  const int KF = p.K >> 4, KFw = PART ? KF / KSPLIT / (int)gridDim.y : KF / KSPLIT;   // (whole, by the launcher)
+  const int kf0 = ((PART ? (int)blockIdx.y * KSPLIT : 0) + wave) * KFw;
 #ifdef DF_TUNING
   asm volatile("" ::"s"(kf0), "s"(mg), "s"(ng));
 #endif
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const float* src = nullptr;                        // (uniform)
     if (ln) src = wave == 0 ? p.ln_s + n0 : wave == 1 ? p.ln_t + n0 : (gg && wave == 2) ? p.ln_s + p.N + n0
                                                           : (gg && wave == 3) ? p.ln_t + p.N + n0 : nullptr;
-    else if (p.bias) src = wave == 0 ? p.bias + n0 : (gg && wave == 2) ? p.bias + p.N + n0 : nullptr;
+    else if (!PART && p.bias) src = wave == 0 ? p.bias + n0 : (gg && wave == 2) ? p.bias + p.N + n0 : nullptr;
     if (src && lane * 4 < JO * 32) vec_pre = *reinterpret_cast<const f32x4*>(src + 4 * lane);
   }
   struct Epi { float r[8]; };
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int mt = mg * TM + i0 + (p.geglu ? (pu >> 1) / GP : (pu >> 1) / TN);
     const int m = mt * 32 + tok;
     const int n = (ng * JO + j) * 32 + 16 * f + 8 * g;
-    if (p.residual && m < p.M) {
+    if (!PART && p.residual && m < p.M) {
       ld_vec(p.residual + (long long)m * p.ldr + n, e.r); ld_vec(p.residual + (long long)m * p.ldr + n + 4, e.r + 4);
     }
   };
@@ -270,6 +270,13 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       for (int w = 0; w < KSPLIT; ++w) {
         a += red[(w * U + (il * TN + j) * 4 + 2 * f) * 64 + lane];
         b += red[(w * U + (il * TN + j) * 4 + 2 * f + 1) * 64 + lane];
+      }
+      if constexpr (PART) {
+        // the part's sums as they are, in the layout of bgemm_sum_kernel: [part][token row][feature row][quarter][lane]
+        f32x4* d = p.partials + (((size_t)blockIdx.y * MT + mt) * NTo + ng * TN + j) * 256 + f * 128 + lane;
+        d[0] = a;
+        d[64] = b;
+        continue;
       }
       v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
     }
@@ -499,7 +506,7 @@ __global__ void pack_text_kv_kernel(const bf16_t* __restrict__ kv, long long ld,
   out[idx] = v;
 }
 
-template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0>
+template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0, bool PART = false>
 int launch_one(const WParams& p, hipStream_t st) {
   const int MT = (p.M + 31) / 32, MG = (MT + TM - 1) / TM;
   const int NTo = p.N / 32;
@@ -511,14 +518,15 @@ int launch_one(const WParams& p, hipStream_t st) {
   if (KF % KSPLIT) return DF_ESHAPE;
   constexpr int RP = (KSPLIT * TM * TN * 4 <= 128) ? TM : (TM % 2 == 0 && KSPLIT * (TM / 2) * TN * 4 <= 128) ? TM / 2 : 1;
   constexpr int smem = KSPLIT * RP * TN * 4 * 1024 + KSPLIT * TM * 32 * 2 * 4 + (XA > 0 ? 4096 : 0) + 4 * 128 * 4;
-  auto k = wgemm_kernel<TM, TN, KSPLIT, PF, LN, XA>;
+  auto k = wgemm_kernel<TM, TN, KSPLIT, PF, LN, XA, PART>;
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)(MG * NG)), dim3(64 * KSPLIT), smem, st, p);
+  hipLaunchKernelGGL(k, dim3((unsigned)(MG * NG), PART ? (unsigned)p.parts : 1u), dim3(64 * KSPLIT), smem, st, p);
   DF_LAUNCH_CHECK();
+  if constexpr (PART) return launch_part_sums(p, st);
   return DF_OK;
 }
 
@@ -527,7 +535,14 @@ template <int TM, int TN, int KSPLIT, int PFMAX>
 int launch_cfg(const WParams& p, hipStream_t st) {
   const int KF = p.K / 16;
   if (KF % KSPLIT) return DF_ESHAPE;
-  const int KFw = KF / KSPLIT;
+  const int KFw = KF / KSPLIT / p.parts;
+  if (p.parts > 1) {
+    if constexpr (TM == 1 && TN == 2) {
+      if (KFw % PFMAX == 0) return launch_one<TM, TN, KSPLIT, PFMAX, false, 0, true>(p, st);
+      return launch_one<TM, TN, KSPLIT, 4, false, 0, true>(p, st);
+    }
+    return DF_ESHAPE;
+  }
   const bool ln = p.ln_s != nullptr;
 #define DF_WG(PFV)                                                                     \
   return ln ? launch_one<TM, TN, KSPLIT, PFV, true>(p, st) : launch_one<TM, TN, KSPLIT, PFV, false>(p, st)
@@ -601,7 +616,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   p.Xp = (const bf16x8*)a.Xp; p.Wp = (const bf16x8*)a.Wp; p.M = a.M; p.N = Nout; p.K = a.K;
   p.bias = a.bias; p.ln_s = a.ln_s; p.ln_t = a.ln_t; p.ln_eps = a.ln_eps; p.residual = a.residual; p.ldr = a.ldr;
   p.out_f32 = a.out_f32; p.ldo = a.ldo; p.out_packed = (bf16_t*)a.out_packed; p.out_rows = (bf16_t*)a.out_rows;
-  p.ld_rows = a.ld_rows; p.geglu = a.geglu ? 1 : 0;
+  p.ld_rows = a.ld_rows; p.geglu = a.geglu ? 1 : 0; p.parts = 1;
   if (a.nseg > 0) {
     if (a.nseg > 3 || a.seg_w % 32 || a.seg_w * a.nseg != a.N || a.geglu) return DF_ESHAPE;
     p.nseg = a.nseg; p.seg_w = a.seg_w;
@@ -662,6 +677,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
       const int rc = launch_bgemm(p, c, st);
       if (rc != DF_ESHAPE || e) return rc;
     }
+    p.parts = 1;
   }
   if (a.xa_kv) {
     const int XA = (a.xa_keys + 31) / 32;
@@ -678,6 +694,19 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     if (KFw % 2 == 0) { DF_XA(2) }
     DF_XA(1)
 #undef DF_XA
+  }
+  // So few tokens and so long a K that a workgroup waits for its run of the weights: four parts of K, 32 x 64 tiles, at most one
+  // workgroup per unit, and a second launch for the sums.  Against the 32 x 32 tile, cold weights: 32 x 1280 x 5120 14.3 -> 10.2 us, 64 x
+  // 1280 x 5120 13.2 -> 11.3, 96 x 1280 x 5120 12.6 -> 11.3; with K = 2560 8.1 against 9.3, with 128 tokens (320 workgroups) 12.1
+  // against 14.6.  Without enough scratch the layer stays whole.
+  if (few && a.scr && !a.ln_s && !p.geglu && !p.nseg && !a.xa_kv && nfrag % 2 == 0 && a.K >= 4096 &&
+      (a.K % 1280 == 0 || a.K % 1024 == 0) && 4 * wg12 <= 256 && !tune_env("DF_BGEMM")) {
+    char* scr = scratch_region(a.scr, kScratchCounterBytes + (size_t)4 * MT * nfrag * 4096);
+    if (scr) {
+      p.parts = 4;
+      p.partials = (f32x4*)(scr + kScratchCounterBytes);
+      return launch_cfg<1, 2, 4, 5>(p, st);
+    }
   }
   if (!p.geglu && (nfrag % 2 || few)) return launch_cfg<1, 1, 4, 5>(p, st);
   if (wide) return launch_cfg<2, 3, 4, 5>(p, st);
