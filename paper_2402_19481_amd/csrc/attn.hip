@@ -39,6 +39,8 @@ struct AttnParams {
   int out_packed;
   // transposed-V variant: vs is V^T [B][heads*64][vt_ld] (keys contiguous), every key comes from ks / vs
   long long vt_ld;
+  NextReads next;
+  int qblocks;     // attn_wave_d64: blocks of 32 queries; the rows of the grid beyond them read ahead
 };
 
 // Row of the fresh tensor that holds key j, or -1 if the key comes from the stale buffer (Section 4: the keys and
@@ -510,6 +512,30 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   }
 }
 
+// Workgroups of attn_wave_d64's launch beyond its query blocks: each XCD's read that XCD's eighth of every region once and drop it.
+template <int NW>
+__device__ __forceinline__ void read_ahead(const AttnParams& p, int row) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int xcd = blockIdx.x & 7, rows = (int)gridDim.y - p.qblocks, cols = (int)gridDim.x >> 3;   // (gridDim.x: a multiple of 8)
+  const int first = (((int)blockIdx.z * rows + row) * cols + ((int)blockIdx.x >> 3)) * NW + wave;
+  const int stride = (int)gridDim.z * rows * cols * NW;
+  for (int r = 0; r < p.next.n; ++r) {
+    const long long kb = p.next.bytes[r] >> 10, lo = kb * xcd / 8;
+    const int n = (int)(kb * (xcd + 1) / 8 - lo);
+    const char* base = (const char*)p.next.p[r] + (lo << 10) + lane * 16;
+    for (int i = first; i < n; i += 4 * stride) {
+      u32x4 t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int k = i + u * stride;
+        t[u] = *reinterpret_cast<const u32x4*>(base + ((long long)(k < n ? k : i) << 10));
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(t[u]));
+    }
+  }
+}
+
 // Self-attention of a patch with few queries (the deepest levels: 32-1024 query rows against the whole image's keys).
 // One workgroup = one 32-query block of one head; its NW waves take contiguous runs of 64-key tiles and merge their
 // (max, sum, O) states through LDS at the end, so nothing is split across workgroups and no second kernel runs.
@@ -538,6 +564,7 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   // x-fastest order, so every query block of head h runs on XCD h % 8 and the blocks of a head, which read the same
   // K / V^T, share an L2 - without any index arithmetic (the divisions of a linear index were a tenth of this kernel).
   const int h = blockIdx.x, qb = blockIdx.y, b = blockIdx.z;
+  if (qb >= p.qblocks) { read_ahead<NW>(p, qb - p.qblocks); return; }
   if (h >= p.heads) return;
   const int q0 = qb * 32;
   const int NT = (p.L + TK - 1) / TK;
@@ -1084,7 +1111,26 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld; p.nsplit = 1; p.keys_per_split = a.L;
-    const dim3 grid((unsigned)(cdiv(a.heads, 8) * 8), (unsigned)qblocks, (unsigned)a.B);
+    // Compute units without a workgroup read ahead what the next launches of the stream read (packed weights; from HBM into the
+    // last-level cache).  A layer of few tokens waits for its weights: 64 x 1280 x 1280 5.4 us with them in HBM, 4.0 with them
+    // read before.  The amount is what these units read (20 GB/s each, 3 TB/s together) while the others attend; more makes
+    // this launch longer (26 MB: 5.9 -> 9.8 us), and with few idle units, or long keys that come from HBM themselves, it
+    // takes more from them than it gives (300 x 2400 x 20, 48 units: 17.0 -> 23.5 us): nothing below 80 units.  512 x 512 step of
+    // four patches 5150 -> 5000 us, 1024 x 1024 of eight with guidance 7205 -> 7135.
+    const int cols = cdiv(a.heads, 8) * 8;
+    const long long idle = 256 - qblocks * a.heads * a.B;
+    long long rows = a.next.n > 0 ? idle / ((long long)cols * a.B) : 0;
+    if (rows * cols * a.B < 80) rows = 0;
+    const double us = 1.0 + 1.93 * (double)rounds, rate = 0.02e6 * (double)(rows * cols * a.B);
+    long long kb = (long long)(us * (rate < 3.0e6 ? rate : 3.0e6) / 1024.0);
+    p.next.n = 0;
+    for (int i = 0; i < a.next.n && rows > 0 && kb > 0; ++i) {
+      const long long n = a.next.bytes[i] >> 10 < kb ? a.next.bytes[i] >> 10 : kb;
+      p.next.p[p.next.n] = a.next.p[i]; p.next.bytes[p.next.n++] = n << 10;
+      kb -= n;
+    }
+    p.qblocks = (int)qblocks;
+    const dim3 grid((unsigned)cols, (unsigned)(qblocks + (p.next.n ? rows : 0)), (unsigned)a.B);
     constexpr int NW = 8;
     constexpr int smem = NW * 2 * 64 * 64 * 2;          // a K and a V^T tile per wave; the merge reuses it
     static_assert(NW * 34 * 64 * 4 <= smem, "the merge fits");

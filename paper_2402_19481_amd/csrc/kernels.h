@@ -172,6 +172,14 @@ size_t packed_text_kv_bytes(int B, int TL, int count, int C);
 int launch_pack_text_kv(const bf16_t* kv, long long ld, bf16_t* out, int B, int TL, int count, int C, hipStream_t st);
 
 // ---- attn.hip ----
+// Read-only memory that the next launches of the stream will read (their weights), in the order of use.
+constexpr int kNextMax = 6;
+struct NextReads {
+  const void* p[kNextMax];
+  long long bytes[kNextMax];                   // whole KB
+  int n;
+};
+
 struct AttnArgs {
   const void* q;        // [B, Lq, heads*d], row stride ldq, batch stride bsq
   const void* k_fresh;  // rows [own_lo, own_lo + own_n) of the key set
@@ -194,6 +202,7 @@ struct AttnArgs {
   long long vt_ld;
   int q_scaled;         // q already holds query * scale * log2(e) (v_transposed only)
   const Scratch* scr;   // see GnArgs
+  NextReads next;       // read ahead by compute units that the launch leaves idle; n = 0: nothing
 };
 int launch_attention(const AttnArgs& a, hipStream_t st);
 size_t attention_scratch_bytes(int B, int Lq, int L, int heads, int d);

@@ -586,6 +586,13 @@ struct Exec {
           [&] { return launch_wgemm(g, st); });
   }
 
+  // Adds the packed weights of a linear layer to what a launch may read ahead.
+  void read_next(NextReads& r, const std::string& wn, int Nn, int K) {
+    auto it = packed->find(wn);
+    if (it == packed->end() || r.n >= kNextMax) return;
+    r.p[r.n] = it->second.f; r.bytes[r.n++] = (long long)Nn * K * 2;
+  }
+
   // Transformer on fragment-packed activations: every linear layer reads its operands in
   // MFMA order straight into registers and writes the next layer's operand in that order; LayerNorms are folded into
   // the consuming layers; attention reads row-major Q/K/V and writes its output packed.
@@ -653,6 +660,11 @@ struct Exec {
         a.bsq = (long long)Lq * C; a.bskf = a.bsvf = (long long)L * C;
         a.bsks = (long long)L * C; a.bsvs = (long long)C * Lpad; a.bso = (long long)Lq * C;
         a.scale = scale; a.dtype = DF_BF16; a.scr = scr;
+        read_next(a.next, p + ".attn2.q", C, C);
+        read_next(a.next, p + ".attn1.o", C, C);
+        read_next(a.next, p + ".attn2.o", C, C);
+        read_next(a.next, p + ".ff2", C, 4 * C);
+        read_next(a.next, p + ".ff1", 8 * C, C);
         label = "self_attn " + dims({M, L, C});
         timed(PC_SELF_ATTN, 4.0 * M * L * C, 2.0 * (2.0 * M * C + 2.0 * B() * L * C),
               [&] { return launch_attention(a, st); });
