@@ -121,18 +121,12 @@ void tgemm_kernel(TileParams p, TgExtra x) {
       a_ofs[j] = 2u * ((unsigned int)(m - m0) * (unsigned int)p.lda + (unsigned int)ch);
     }
   }
-  // tiled weights: tile (n/64, slab) is 8 KB contiguous, rows and swizzled slots exactly as they sit in LDS
-  const bool tiled = !kConv && p.packed_w;
-  const char* const b_tile = (const char*)(p.Wt + (tiled ? (long long)(n0 >> 6) * slabs_all * 4096 : (long long)n0 * p.ldw));
+  const bool tiled = !kConv && p.packed_w;                              // (see tile.h)
+  const char* const b_tile = (const char*)(p.Wt + w_tile_base(tiled, n0, slabs_all, p.ldw));
   unsigned int b_ofs[BJ];
 #pragma unroll
-  for (int j = 0; j < BJ; ++j) {
-    const int row = (wq * BJ + j) * 8 + lr;
-    const int n = (n0 + row < p.N ? n0 + row : p.N - 1) - n0;
-    b_ofs[j] = 2u * (tiled ? ((unsigned int)(n >> 6) * (unsigned int)slabs_all * 64u + (unsigned int)(n & 63)) * 64u + (lane & 7) * 8
-                           : (unsigned int)n * (unsigned int)p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8);
-  }
-  const unsigned int b_step = tiled ? 8192 : 128;                       // bytes between slabs
+  for (int j = 0; j < BJ; ++j) b_ofs[j] = w_lane_bytes(tiled, n0, (wq * BJ + j) * 8 + lr, lane & 7, p.N, slabs_all, p.ldw);
+  const unsigned int b_step = w_slab_bytes(tiled);
   // Convolution: a lane's source pixel changes only with the filter tap, every Cin / 64 slabs
   const bf16_t* a_tap[AJ];
   bool a_pad[AJ];

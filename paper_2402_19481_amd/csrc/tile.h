@@ -45,6 +45,22 @@ __device__ __forceinline__ const T* conv_tap_src(const T* x, const T* top, const
   return x + (((long long)b * R + ri) * W + ci) * Cin;
 }
 
+// Where an output tile that starts at weight row n0 (a multiple of 32) takes its weights from: elements from the weights to the tile's
+// base, bytes from there to the 16 that LDS slot `slot` of tile row `row` receives (rows beyond the last of N: that one, re-read and
+// never stored), and bytes from one slab of 64 columns to the next.  LDS row r keeps its 16-byte chunk c at slot c ^ ((r >> 1) & 7).
+// Tiled weights hold the rows of a 64 x 64 tile just so, but tile (n / 64, slab) begins at a multiple of 64 rows where a 160-wide output
+// tile need not: the base is that of the tile that holds row n0, and the lane counts its rows from there (a tile row 32 further
+// has the same swizzle).  The launcher keeps K and ldw below 2^22: the bytes fit 32 bits up to 320 rows row-major, four tiles tiled.
+__host__ __device__ inline long long w_tile_base(bool tiled, int n0, int slabs, long long ldw) {
+  return tiled ? (long long)(n0 >> 6) * slabs * 4096 : (long long)n0 * ldw;
+}
+__host__ __device__ inline unsigned int w_lane_bytes(bool tiled, int n0, int row, int slot, int N, int slabs, long long ldw) {
+  const unsigned int n = (unsigned int)((n0 + row < N ? n0 + row : N - 1) - (tiled ? n0 & ~63 : n0));
+  return 2u * (tiled ? ((n >> 6) * (unsigned int)slabs * 64u + (n & 63u)) * 64u + (unsigned int)slot * 8u
+                     : n * (unsigned int)ldw + (unsigned int)(slot ^ ((row >> 1) & 7)) * 8u);
+}
+__host__ __device__ inline unsigned int w_slab_bytes(bool tiled) { return tiled ? 8192 : 128; }
+
 // Workgroup-tile kernel (tgemm.hip): linear layers and convolutions with K % 64 == 0 (Cin % 64 == 0), N % 4 == 0 and an
 // epilogue of whole 16-byte accesses.  DF_ESHAPE if the arguments do not fit.
 int launch_tgemm(const TileParams& p, bool conv, int out_dtype, hipStream_t st);
