@@ -192,9 +192,12 @@ int df_linear(const void* x, const void* w, const float* bias, const float* resi
  *     Outputs (any subset, at least one): y_f32 row-major float (residual may alias it), y_packed packed bf16 (all
  *     ceil(M/32)*32 rows are written), y_rows row-major bf16.
  *   df_linear_packed_scratch  df_linear_packed (no LayerNorm, no GEGLU) with a region of the caller, 256-byte aligned,
- *     in which a layer of few tiles and long K keeps the sums of its parts of K, as the step does; such a layer returns
- *     DF_ENOMEM if the region is too small.  df_linear_packed_scratch_bytes always suffices.  Calls that overlap need
- *     regions of their own.
+ *     in which a layer of few tiles and long K keeps the sums of its parts of K, as the step does.
+ *     df_linear_packed_scratch_bytes always suffices.  With less, a layer of more than 128 tiles of 32 x 64 outputs whose
+ *     parts save enough (1024 x 1280 x 5120, say; the set of such shapes is fixed) returns DF_ENOMEM, before any launch.
+ *     Every other layer runs with any region: in no more parts than fit, down to the whole K.  The parts are added in
+ *     order, so equal calls with regions of equal size give equal bits; the last bits may differ between regions of
+ *     different size.  Calls that overlap need regions of their own.
  */
 size_t df_packed_bytes(long long rows, long long K);
 int df_pack_rows(const void* x, void* packed, int M, int K, void* stream);

@@ -708,9 +708,8 @@ size_t wgemm_scratch_bytes(long long M, long long N) {
   return kScratchCounterBytes + (parts > 1 ? (size_t)parts * MT * NF * 4096 : 0);
 }
 
-// The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.  With
-// `scr`, `parts` receives the number of parts to split K into, 0 if `scr` is too small for them.
-int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts) {
+// The tile shape with the least predicted time, if that is below the wave-level kernel's `other_us`; else -1.
+int pick_bgemm(const WParams& p, double other_us, long long room, int* parts) {
   const int mode = p.xkv ? 3 : p.geglu ? 0 : p.nseg ? 1 : 2;
   const int MT = (p.M + 31) / 32, NF = p.N / 32;
   const double kt = p.K / 64.0;
@@ -734,18 +733,16 @@ int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts
   for (int c = 0; c < kSplitFamily; ++c) consider(c);
   // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts.  At 640 features and K = 2560 and below the sums cost what
   // the parts gain.
-  if (mode == 2 && !p.ln_s && scr) {
+  if (mode == 2 && !p.ln_s && room > 1) {
     for (const SplitCfg& q : kSplits) {
       const TileCfg& t = kTiles[q.tile];
       const int most = max_parts(t, MT, NF);
-      for (int s = 2; s <= most; ++s) {
+      for (int s = 2; s <= most && s <= room; ++s) {
         if (kt / s < 8) break;
         const double us = t.base + std::ceil(kt / s) * t.slab + q.fixed + kPartUs * s * (32.0 * MT) * p.N;
         if (us < 0.97 * best) { best = us / 0.97; pick = q.tile; *parts = s; }
       }
     }
-    // a layer that splits here needs its scratch, also where one of the tiles below is faster in the end
-    if (*parts > 1 && !scratch_region(scr, kScratchCounterBytes + (size_t)*parts * MT * NF * 4096)) { *parts = 0; return -1; }
   }
   for (int c = kSplitFamily; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) consider(c);
   return pick;

@@ -79,8 +79,46 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
 
 // Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
-// Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1.
-int pick_bgemm(const WParams& p, double other_us, const Scratch* scr, int* parts);
+// Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1, and the parts to split K into: at most `room`,
+// which the caller's scratch holds.
+int pick_bgemm(const WParams& p, double other_us, long long room, int* parts);
 int launch_part_sums(const WParams& p, hipStream_t st);
+
+// Parts of K that the scratch handed to a plain layer (MT token rows of 32, NF feature rows of 32, K) has to hold; 1: any scratch
+// will do.  This decides which calls return DF_ENOMEM and nothing else.  It is the choice of parts as it was when that became
+// part of the entry point, with the predicted times of then (a launch, a round of workgroups per 64 of K, its prologue and
+// epilogue, the round of a workgroup alone on a unit), so that a later fit of the tiles does not move the set of calls that
+// are refused.  Layers that it leaves out split as far as their scratch allows.
+inline int parts_due(int MT, int NF, int K) {
+  struct Tile { int bt, bf, occ; double base, slab, epi, alone; };
+  constexpr Tile tiles[] = {{8, 10, 1, 0.00, 1.603, 26.3, 1.0}, {4, 4, 2, 3.77, 1.078, 4.2, 0.70}, {4, 4, 1, 1.80, 0.474, 6.0, 1.0},
+                            {2, 4, 2, 3.90, 0.620, 2.9, 0.62},  {2, 2, 2, 2.30, 0.432, 1.7, 0.86}, {2, 2, 1, 2.50, 0.227, 1.9, 1.0},
+                            {4, 10, 1, 1.43, 0.947, 13.8, 1.0}};
+  const double kt = K / 64.0;
+  const long long wave_tiles = (long long)MT * (NF / 2), pairs = (MT + 1) / 2;
+  if (wave_tiles <= 128) return 1;
+  const bool two = wave_tiles >= 320, wide = two && K >= 1024 && NF % 3 == 0 && pairs * (NF / 3) <= 256;
+  const double waves = (two ? (double)(pairs * (NF / 2)) : (double)wave_tiles) / 256.0, rw = waves > 0.6 ? waves : 0.6;
+  double best = 0.94 * (wide ? 9.7 + 0.125 * kt : two ? 4.6 + rw * (0.286 * kt + 1.16) : 5.3 + rw * (0.189 * kt - 2.2));
+  for (int c = 0; c < 7; ++c) {
+    const Tile& t = tiles[c];
+    if ((c == 4 || c == 5) && K / 64 % 2) continue;
+    const long long n = (long long)((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf), rem = n % 512;
+    const double r = t.occ == 1 ? (double)((n + 255) / 256)
+                     : n > 1536 ? n / 512.0 : (double)(n / 512) + (rem == 0 ? 0.0 : rem <= 256 ? t.alone : 1.0);
+    const double us = t.base + r * (kt * t.slab + t.epi);
+    if (us < best) best = us;
+  }
+  int parts = 1;
+  for (int c = 2; c <= 6; c += 4) {
+    const Tile& t = tiles[c];
+    const long long n = (long long)((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf);
+    for (int s = 2; s <= 8 && n * s <= 256 && kt / s >= 8; ++s) {
+      const double us = t.base + (K / 64 + s - 1) / s * t.slab + (c == 2 ? 4.3 : 5.0) + 2.2e-6 * s * (32.0 * MT) * (32.0 * NF);
+      if (us < 0.97 * best) { best = us / 0.97; parts = s; }
+    }
+  }
+  return parts;
+}
 
 }  // namespace df

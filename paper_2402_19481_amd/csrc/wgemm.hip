@@ -651,6 +651,15 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   const bool few = wg12 <= 128;
   const bool long_k = a.K / 16 / 4 >= 16;
   const bool wide = wg12 >= 320 && long_k && !p.geglu && nfrag % 3 == 0 && (long long)((MT + 1) / 2) * (nfrag / 3) <= 256 && !a.xa_kv;
+  // Parts of K that the caller's scratch holds.  Only plain layers split.
+  const bool plain = !a.ln_s && !p.geglu && !p.nseg && !a.xa_kv;
+  const size_t part_bytes = (size_t)MT * nfrag * 4096;
+  const long long room = plain && a.scr && a.scr->ptr && a.scr->bytes > kScratchCounterBytes
+                             ? (long long)((a.scr->bytes - kScratchCounterBytes) / part_bytes) : 0;
+  if (plain && a.scr) {
+    const int due = parts_due(MT, nfrag, a.K);
+    if (due > 1 && due > room) return DF_ENOMEM;
+  }
   {
     // Predicted time of the wave-level kernel (microseconds: launch + rounds of workgroups x (K loop + epilogue), fitted
     // like the tile kernel's table): it keeps the problems whose token count does not fill the tiles of bgemm.hip.
@@ -665,14 +674,12 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     const char* e = tune_env("DF_BGEMM");
     // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
     int parts = 1;
-    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.98 * us, a.scr, &parts);
+    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.98 * us, room, &parts);
     if (e && a.scr && tune_env("DF_PARTS")) parts = atoi(tune_env("DF_PARTS"));
-    if (parts < 1) return DF_ENOMEM;
     if (parts > 1) {
-      char* scr = scratch_region(a.scr, kScratchCounterBytes + (size_t)parts * MT * nfrag * 4096);
-      if (!scr) return DF_ENOMEM;
+      if (parts > room) return DF_ENOMEM;                // (an override's)
       p.parts = parts;
-      p.partials = (f32x4*)(scr + kScratchCounterBytes);
+      p.partials = (f32x4*)(a.scr->ptr + kScratchCounterBytes);
     }
     if (c >= 0) {
       const int rc = launch_bgemm(p, c, st);
@@ -699,15 +706,12 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   // So few tokens and so long a K that a workgroup waits for its run of the weights: four parts of K, 32 x 64 tiles, at most one
   // workgroup per unit, and a second launch for the sums.  Against the 32 x 32 tile, cold weights: 32 x 1280 x 5120 14.3 -> 10.2 us, 64 x
   // 1280 x 5120 13.2 -> 11.3, 96 x 1280 x 5120 12.6 -> 11.3; with K = 2560 8.1 against 9.3, with 128 tokens (320 workgroups) 12.1
-  // against 14.6.  Without enough scratch the layer stays whole.
-  if (few && a.scr && !a.ln_s && !p.geglu && !p.nseg && !a.xa_kv && nfrag % 2 == 0 && a.K >= 4096 &&
-      (a.K % 1280 == 0 || a.K % 1024 == 0) && 4 * wg12 <= 256 && !tune_env("DF_BGEMM")) {
-    char* scr = scratch_region(a.scr, kScratchCounterBytes + (size_t)4 * MT * nfrag * 4096);
-    if (scr) {
-      p.parts = 4;
-      p.partials = (f32x4*)(scr + kScratchCounterBytes);
-      return launch_cfg<1, 2, 4, 5>(p, st);
-    }
+  // against 14.6.  Without enough scratch the layer stays whole (parts_due has none of these).
+  if (few && plain && room >= 4 && nfrag % 2 == 0 && a.K >= 4096 && (a.K % 1280 == 0 || a.K % 1024 == 0) && 4 * wg12 <= 256 &&
+      !tune_env("DF_BGEMM")) {
+    p.parts = 4;
+    p.partials = (f32x4*)(a.scr->ptr + kScratchCounterBytes);
+    return launch_cfg<1, 2, 4, 5>(p, st);
   }
   if (!p.geglu && (nfrag % 2 || few)) return launch_cfg<1, 1, 4, 5>(p, st);
   if (wide) return launch_cfg<2, 3, 4, 5>(p, st);
