@@ -238,46 +238,43 @@ struct GnMoments { float mean_hi, mean_lo, rstd; };
 // Mean and variance of one (batch item, group) from the fresh sums of this launch and the cached per-patch sums,
 // according to the statistic mode (Section 4, Eq. 2; Section 5.3).  Runs once per group, in double.
 // `st_*`: sums of the cached entries of the other patches, `own_*`: the cached entry of this patch.
-// `inv_loc` = 1 / n_loc and `inv_all` = 1 / (n_loc * nseg * N) come from the host: this runs on one wave while the others wait, and
-// a division or a square root in double is some twenty dependent instructions.
-struct GnCount { double n_loc, inv_loc, inv_all; };
+// The reciprocals come from the host: this runs on one wave while the others wait, and a division or a square root in double is some
+// twenty dependent instructions.  The quotients are those of a division all the same (div_by).
+struct GnCount { double n_loc, inv_loc, n_all, inv_all; };   // values of a group in the patch, and in the image
 __device__ __forceinline__ GnMoments gn_combine_pre(double tot_s, double tot_q, const GnCount& n, int nseg, int N,
                                                     int stat_mode, double st_s, double st_q, double own_s,
                                                     double own_q, float eps) {
+  auto loc = [&](double s) { return div_by(s, n.n_loc, n.inv_loc); };
+  auto all = [&](double s) { return div_by(s, n.n_all, n.inv_all); };
   double mean, var;
   if (nseg > 1 || (N == 1 && stat_mode != DF_GN_STALE)) {
     // the whole image is fresh: exact statistics
-    mean = tot_s * n.inv_all;
-    var = fmax(tot_q * n.inv_all - mean * mean, 0.0);
+    mean = all(tot_s);
+    var = fmax(all(tot_q) - mean * mean, 0.0);
   } else {
-    const double loc_m = tot_s * n.inv_loc, loc_m2 = tot_q * n.inv_loc;
+    const double loc_m = loc(tot_s), loc_m2 = loc(tot_q);
     if (stat_mode == DF_GN_SUMS) {
-      mean = (tot_s + st_s) * n.inv_all;
-      var = fmax((tot_q + st_q) * n.inv_all - mean * mean, 0.0);
+      mean = all(tot_s + st_s);
+      var = fmax(all(tot_q + st_q) - mean * mean, 0.0);
     } else if (stat_mode == DF_GN_EQ2) {
-      mean = (st_s + own_s) * n.inv_all + (loc_m - own_s * n.inv_loc);
-      const double m2 = (st_q + own_q) * n.inv_all + (loc_m2 - own_q * n.inv_loc);
+      mean = all(st_s + own_s) + (loc_m - loc(own_s));
+      const double m2 = all(st_q + own_q) + (loc_m2 - loc(own_q));
       var = m2 - mean * mean;
       if (var < 0.0) var = loc_m2 - loc_m * loc_m;
     } else if (stat_mode == DF_GN_SEPARATE) {
       mean = loc_m;
       var = fmax(loc_m2 - loc_m * loc_m, 0.0);
     } else {
-      mean = (st_s + own_s) * n.inv_all;
-      var = fmax((st_q + own_q) * n.inv_all - mean * mean, 0.0);
+      mean = all(st_s + own_s);
+      var = fmax(all(st_q + own_q) - mean * mean, 0.0);
     }
   }
   GnMoments m;
   m.mean_hi = (float)mean;
   m.mean_lo = (float)(mean - (double)m.mean_hi);
-  // one Newton step on the hardware's float estimate (1 ulp) leaves a relative error of 1e-14; outside float range the long way
   const double v = var + (double)eps;
-  if (v > 1e-30 && v < 1e30) {
-    const double r = (double)__builtin_amdgcn_rsqf((float)v);
-    m.rstd = (float)(r * (1.5 - 0.5 * v * r * r));
-  } else {
-    m.rstd = (float)(1.0 / sqrt(v));
-  }
+  // the hardware's float estimate (1 ulp), refined; outside float range the long way
+  m.rstd = v > 1e-30 && v < 1e30 ? (float)rsqrt_from(v, __builtin_amdgcn_rsqf((float)v)) : (float)(1.0 / sqrt(v));
   return m;
 }
 
@@ -741,7 +738,8 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   }
   if (pix_seg <= 0 || pix_seg * a.nseg > 0x7fffffffLL) return DF_ESHAPE;
   const double n_loc = (double)pix_seg * (double)(a.C / a.G);
-  const GnCount cnt = {n_loc, 1.0 / n_loc, 1.0 / (n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1))};
+  const double n_all = n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1);
+  const GnCount cnt = {n_loc, 1.0 / n_loc, n_all, 1.0 / n_all};
   // small tensors: the whole GroupNorm in one launch, one workgroup per (group, batch item)
   {
     const int cg = a.C / a.G;
