@@ -323,27 +323,34 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
 }
 
 // Tile of th x tw pixels for a patch of R x W: the fewest tiles, then the fewest input pixels, over heights of up to 24 rows and
-// the one that takes the whole width (this runs at every launch)
+// the one that takes the whole width.  This runs at every launch: a height with as many rows of tiles as the one before it is
+// left out, since it is never wider.
 struct Geo { int th, tw, tr, tc; };
 Geo pick_geo(int R, int W, int bm, int cap) {
   Geo best = {0, 0, 0, 0};
-  unsigned long long bc = ~0ULL;
+  unsigned int fewest = ~0u, pixels = 0;
   auto cd = [](unsigned int a, unsigned int b) { return (a + b - 1) / b; };
-  auto consider = [&](unsigned int th) {
+  auto consider = [&](unsigned int th, unsigned int tr) {
     unsigned int tw = (unsigned int)bm / th;
     if ((th + 2) * (tw + 2) > (unsigned int)cap) tw = (unsigned int)cap / (th + 2) > 2 ? cap / (th + 2) - 2 : 0;
     if (tw > (unsigned int)W) tw = W;
     if (tw < 1) return;
-    const unsigned int tr = cd(R, th), tc = cd(W, tw), h = cd(R, tr), w = cd(W, tc);
-    const unsigned long long c = ((unsigned long long)tr * tc << 16) + (h + 2) * (w + 2);
-    if (c < bc) { bc = c; best = Geo{(int)h, (int)w, (int)tr, (int)tc}; }
+    const unsigned int tc = cd(W, tw), n = tr * tc;
+    if (n > fewest) return;
+    const unsigned int h = cd(R, tr), w = cd(W, tc), in = (h + 2) * (w + 2);
+    if (n < fewest || in < pixels) { fewest = n; pixels = in; best = Geo{(int)h, (int)w, (int)tr, (int)tc}; }
   };
-  for (int th = 1; th <= R && th <= 24; ++th) consider(th);
+  unsigned int last = 0;
+  for (int th = 1; th <= R && th <= 24; ++th) {
+    const unsigned int tr = cd(R, th);
+    if (tr != last) consider(th, tr);
+    last = tr;
+  }
   if (W < bm) {
     int th = bm / W;
     if ((th + 2) * (W + 2) > cap) th = cap / (W + 2) - 2;
     if (th > R) th = R;
-    if (th > 24) consider(th);
+    if (th > 24) consider(th, cd(R, th));
   }
   return best;
 }
@@ -384,9 +391,8 @@ int launch_one(const TileParams& p, const Geo& g, int nsplit, hipStream_t st) {
 }
 
 template <int PM, int PN, int TM, int TN, int KG, int TAPS, int ST, int NIN>
-int launch_cfg(const TileParams& p, int out_dtype, int nsplit, hipStream_t st) {
-  const Geo g = pick_geo(p.R, p.W, PM * TM * 32, NIN * 64);
-  if (g.th <= 0) return DF_ESHAPE;
+int launch_cfg(const TileParams& p, const Geo& g, int out_dtype, int nsplit, hipStream_t st) {
+  if (g.th <= 0 || g.th * g.tw > PM * TM * 32 || (g.th + 2) * (g.tw + 2) > NIN * 64) return DF_ESHAPE;   // (the table's row is another tile's)
   return out_dtype == DF_BF16 ? launch_one<PM, PN, TM, TN, KG, TAPS, ST, NIN, bf16_t>(p, g, nsplit, st)
                               : launch_one<PM, PN, TM, TN, KG, TAPS, ST, NIN, float>(p, g, nsplit, st);
 }
@@ -419,7 +425,7 @@ int launch_rconv(const TileParams& p, int out_dtype, hipStream_t st) {
   const long long room = (long long)((gemm_scratch_bytes(p.M, p.N) - kScratchCounterBytes) / ((size_t)p.M * p.N * sizeof(float)));
   int cfg = -1, ns = 1;
   double best = 1e30;
-  Geo g = {};
+  Geo g = {}, chosen = {};
   for (int c = 0; c < (int)(sizeof(kTiles) / sizeof(kTiles[0])); ++c) {
     const TileCfg& t = kTiles[c];
     if (c == 0 || t.bm != kTiles[c - 1].bm || t.nin != kTiles[c - 1].nin) g = pick_geo(p.R, p.W, t.bm, t.nin * 64);
@@ -429,22 +435,25 @@ int launch_rconv(const TileParams& p, int out_dtype, hipStream_t st) {
       if (s > 1 && (n * s > kMaxSplitWgs || s > room)) break;
       const double us = t.base + std::ceil(n * s / 256.0) * (cdiv(slabs, s) * t.slab + t.fixed) +
                         (s > 1 ? kSplitUs + kPartUs * s * (double)p.M * p.N : 0.0);
-      if (us < best) { best = us; cfg = c; ns = s; }
+      if (us < best) { best = us; cfg = c; ns = s; chosen = g; }
     }
   }
 #ifdef DF_TUNING
-  if (tune_env("DF_RC")) cfg = atoi(tune_env("DF_RC"));
+  if (tune_env("DF_RC")) {
+    cfg = atoi(tune_env("DF_RC"));
+    if (cfg >= 0 && cfg < (int)(sizeof(kTiles) / sizeof(kTiles[0]))) chosen = pick_geo(p.R, p.W, kTiles[cfg].bm, kTiles[cfg].nin * 64);
+  }
   if (tune_env("DF_RCS")) ns = atoi(tune_env("DF_RCS"));
 #endif
   switch (cfg) {
-    case 0: return launch_cfg<8, 1, 1, 5, 1, 1, 3, 6>(p, out_dtype, ns, st);
-    case 1: return launch_cfg<4, 2, 2, 2, 1, 1, 3, 6>(p, out_dtype, ns, st);
-    case 2: return launch_cfg<8, 1, 1, 2, 1, 3, 2, 6>(p, out_dtype, ns, st);
-    case 3: return launch_cfg<4, 1, 1, 5, 2, 1, 4, 4>(p, out_dtype, ns, st);
-    case 4: return launch_cfg<4, 2, 1, 2, 1, 1, 4, 3>(p, out_dtype, ns, st);
-    case 5: return launch_cfg<4, 1, 1, 2, 2, 3, 3, 3>(p, out_dtype, ns, st);
-    case 6: return launch_cfg<2, 1, 1, 5, 4, 1, 4, 3>(p, out_dtype, ns, st);
-    case 7: return launch_cfg<2, 1, 1, 2, 4, 3, 3, 2>(p, out_dtype, ns, st);
+    case 0: return launch_cfg<8, 1, 1, 5, 1, 1, 3, 6>(p, chosen, out_dtype, ns, st);
+    case 1: return launch_cfg<4, 2, 2, 2, 1, 1, 3, 6>(p, chosen, out_dtype, ns, st);
+    case 2: return launch_cfg<8, 1, 1, 2, 1, 3, 2, 6>(p, chosen, out_dtype, ns, st);
+    case 3: return launch_cfg<4, 1, 1, 5, 2, 1, 4, 4>(p, chosen, out_dtype, ns, st);
+    case 4: return launch_cfg<4, 2, 1, 2, 1, 1, 4, 3>(p, chosen, out_dtype, ns, st);
+    case 5: return launch_cfg<4, 1, 1, 2, 2, 3, 3, 3>(p, chosen, out_dtype, ns, st);
+    case 6: return launch_cfg<2, 1, 1, 5, 4, 1, 4, 3>(p, chosen, out_dtype, ns, st);
+    case 7: return launch_cfg<2, 1, 1, 2, 4, 3, 3, 2>(p, chosen, out_dtype, ns, st);
     default: return DF_ESHAPE;
   }
 }
