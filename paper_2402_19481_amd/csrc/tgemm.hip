@@ -325,8 +325,11 @@ int launch_cfg(const TileParams& p, bool conv, int out_dtype, int nsplit, hipStr
 }
 
 // Tile shapes with their predicted times: microseconds of a launch, of a stage (KG slabs) and of a workgroup's prologue and
-// epilogue, fitted to 28 convolutions (64 to 28800 pixels, 320 to 2560 channels) and 11 linear layers with 1 to 8 parts of
-// K each; chosen by them, those shapes take 0.5 % more than the best of 18 tile shapes did.
+// epilogue.  They come from 28 convolutions, most of which are rconv.hip's now, and 11 linear layers with the loads of then; what still
+// holds is which tile they choose, not the times (0.4 to 1.1 of a launch with nothing in a cache).  Measured so with the present
+// loads, the chosen tile and parts against the best of these six in 1 to 16 parts: 54 linear layers (256 to 38400 tokens, 320 to
+// 1920 features, K 320 to 5120) take 1.8 % more in the mean, 14 % at worst (2400 x 1920 x 640: 16.5 us, 14.4 on 256 x 128), nine
+// convolutions of stride 2 0.9 %.
 struct TileCfg { int bm, bn, kg, occ; double base, stage, fixed; };
 constexpr TileCfg kTiles[] = {
     {128, 128, 1, 1, 2.96, 0.518, 1.99},
