@@ -83,25 +83,29 @@ __device__ long long g_attn_trace[512 * 32];
 //   - PRE: the queries already carry scale * log2(e) (the projection applies it to its float accumulators before rounding).
 //     S then starts from -m instead of zero (the first MFMA of a tile reads the register tuple that holds it), so the
 //     exponential's argument is the accumulator itself; otherwise one fma per score.
-//   - The running maximum m only moves when a score exceeds it by more than 8 (a factor of 256: P stays far inside
-//     float and bf16 range, relative precision is that of any other scaling).  That happens in the first tile and hardly
-//     again; the lanes' maxima are compared, not exchanged, and the exchange and rescaling sit in a branch beside the loop.
+//   - The running maximum m is that of a range's first tile and moves only when a tile has probabilities far above 1 (so P stays
+//     far inside float and bf16 range; relative precision is that of any other scaling).  The sum of a lane's 32 probabilities,
+//     which it needs anyway, tells: beyond 256, at the latest where one of them overflows, the wave drops the tile's probabilities
+//     (nothing has read them yet) and does the tile again from memory in a branch beside the loop.  Watching the maximum of the
+//     scores instead took 16 instructions per tile, and their latency between the last matrix instruction and the barrier.
 //   - Row sums add the float probabilities, not the rounded ones the matrix instructions take: the rounding of a heavy key
 //     would otherwise enter every feature of the row (a key of weight 0.9 with values near zero: 2.0e-3 of error against 1.4e-3,
 //     where the rounding of the result alone is 1.4e-3; random scores differ by less than 7 % in either direction).  Sums
 //     of the packed pairs by v_dot2 are half the instructions and 0.6 % faster on the largest shape.
-// K and V^T tiles go global -> LDS through two rings of three 8 KB tiles; K_{t+3} and V_{t+1} are requested in iteration t.
+// K and V^T tiles go global -> LDS through a ring of three slots of an 8 KB tile each; K_{t+3} and V_{t+1} are requested in
+// iteration t.  Slot i holds K_i, K_{i+3}, .. and V_{i+1}, V_{i+4}, ..: what an iteration reads lies in one slot, in the same order
+// in both tiles, so four address registers serve its sixteen reads.
 // Order of a slot: iteration t reads K_{t+1} and V_{t-1} (S_0 before the loop reads K_0) and ends with a barrier that every wave
 // reaches with its reads done (lgkmcnt(0)).  K_{t+3} goes to the slot of K_t, last read in iteration t-1; V_{t+1} to the slot of
 // V_{t-2}, last read in iteration t-1: the barrier at that iteration's end lies between.  K_0 is read before the loop, so
-// S_0 has a barrier of its own before iteration 0 requests K_3.
-// Bound by the exponentials (64 of 8.3 cycles per wave and tile against 16 MFMAs of 32) and what the power limit leaves of
-// the clock.  Measured in the step (PRE) against the kernel with the phases one after the other: 7200 queries x 57600 keys x 10
-// heads 1435 -> 1100 us (965 TFLOP/s), 1024 x 4096 x 20 51.6 -> 37, 1200 x 9600 x 10 66 -> 46.4 with the merge; queries without
-// the scale: 4096 x 4096 x 10 88 -> 69.
-// Three workgroups per unit instead of two (168 registers) gain 2 % on the largest of these and lose 3-5 % below.
-// Fresh and stale rows (kSrcRows, kSrcPeriodic): the splice is resolved in the source addresses of the direct loads, tile by tile
-// where a tile lies on one side, lane by lane else; V is transposed by ds_read_b64_tr_b16 on its way from LDS to the registers.
+// S_0 has a barrier of its own before iteration 0 requests K_3.  A tile done again reads no LDS and passes no barrier.
+// Bound by the vector instructions of the softmax (85 per wave and tile: 32 exponentials of 8.3 cycles, 32 additions, 16 packings)
+// beside 16 MFMAs of 32 cycles, and by what the power limit leaves of the clock (1.6 - 1.8 GHz): every instruction that goes
+// counts.  Measured in the step (PRE), against 109 vector instructions per tile (maxima of the scores, separate addresses of K and
+// V): 7200 queries x 57600 keys x 10 heads 1088 -> 1010 us (1050 TFLOP/s), 1800 x 14400 x 20 160 -> 147, 4096 x 16384 x 10 (strips)
+// 189 -> 175; queries without the scale, fresh and stale rows: the layer of 1024 of 4096 tokens x 10 heads 51.3 -> 49.5.
+// Fresh and stale rows (kSrcRows, kSrcPeriodic): the splice is resolved in the source addresses of the direct loads, lane by
+// lane; V is transposed by ds_read_b64_tr_b16 on its way from LDS to the registers.
 // 1024 of 4096 tokens x 10 heads: 35 -> 29 us with the merge, against staging through registers.
 // Where K and V come from: all stale, V transposed (V^T); rows of the fresh and the stale tensors, the fresh ones a range of keys
 // (kSrcRows) or periodic (kSrcPeriodic)
@@ -149,7 +153,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     const int row = (2 * wave + j) * 8 + lr;
     trow[j] = row;
     kch[j] = (slot8 ^ ((row >> 1) & 7)) * 8;
-    vch[j] = SRC == kSrcVt ? (slot8 ^ (row & 7) ^ (row >> 3)) * 8 : (slot8 ^ (((row >> 1) & 1) * 2) ^ (((row >> 3) & 1) * 4)) * 8;
+    vch[j] = SRC == kSrcVt ? kch[j] : (slot8 ^ (((row >> 1) & 1) * 2) ^ (((row >> 3) & 1) * 4)) * 8;
   }
   // offsets inside a tile whose rows are consecutive in one tensor (32-bit, the launcher bounds the pitches)
   unsigned int kofs[2], vofs[2];
@@ -158,44 +162,6 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     kofs[j] = (unsigned int)trow[j] * (unsigned int)p.ldks + (unsigned int)kch[j];
     vofs[j] = (unsigned int)trow[j] * (unsigned int)(SRC == kSrcVt ? p.vt_ld : p.ldvs) + (unsigned int)vch[j];
   }
-  // SRC != kSrcVt: a lane's source row for tile row trow[j] of the tile at key0; rows beyond the last key re-read it (masked)
-  struct Rows { const bf16_t* k[2]; const bf16_t* v[2]; };
-  auto rows_of = [&](int key0) {
-    Rows r;
-    if (SRC == kSrcRows && (key0 + TK <= p.own_lo || key0 >= p.own_lo + p.own_n) && key0 + TK <= p.L) {   // (uniform) all stale
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        r.k[j] = kg + (long long)key0 * p.ldks + kofs[j];
-        r.v[j] = vg + (long long)key0 * p.ldvs + vofs[j];
-      }
-      return r;
-    }
-    if (SRC == kSrcRows && key0 >= p.own_lo && key0 + TK <= p.own_lo + p.own_n && key0 + TK <= p.L) {     // (uniform) all fresh
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        r.k[j] = kfr + (long long)(key0 - p.own_lo) * p.ldkf + ((unsigned int)trow[j] * (unsigned int)p.ldkf + (unsigned int)kch[j]);
-        r.v[j] = vfr + (long long)(key0 - p.own_lo) * p.ldvf + ((unsigned int)trow[j] * (unsigned int)p.ldvf + (unsigned int)vch[j]);
-      }
-      return r;
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      unsigned int key = (unsigned int)(key0 + trow[j] < p.L ? key0 + trow[j] : p.L - 1), row = key - (unsigned int)p.own_lo;
-      bool own = row < (unsigned int)p.own_n;
-      if constexpr (SRC == kSrcPeriodic) {
-        // key = q * P + r, q from the rounded-down reciprocal (at most one too small)
-        unsigned int q = __umulhi(key, p.own_magic), rr = key - q * (unsigned int)p.own_period;
-        if (rr >= (unsigned int)p.own_period) { ++q; rr -= (unsigned int)p.own_period; }
-        row = rr - (unsigned int)p.own_lo;
-        own = row < (unsigned int)p.own_n;
-        row += q * (unsigned int)p.own_n;
-      }
-      row = own ? row : key;
-      r.k[j] = (own ? kfr : kg) + (unsigned long long)row * (unsigned int)(own ? p.ldkf : p.ldks) + kch[j];
-      r.v[j] = (own ? vfr : vg) + (unsigned long long)row * (unsigned int)(own ? p.ldvf : p.ldvs) + vch[j];
-    }
-    return r;
-  };
   // kSrcVt: kofr are the offsets inside the last tile when it is ragged
   unsigned int kofr[2];
 #pragma unroll
@@ -203,11 +169,35 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     const int left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
     kofr[j] = (unsigned int)(trow[j] < left ? trow[j] : left) * (unsigned int)p.ldks + (unsigned int)kch[j];
   }
-  auto load_k = [&](int ti, int j, const char* dst) {
+  // Byte offsets of the K loads (kSrcVt) of the tile requested next; those of the last tile from the iteration that requests it on
+  unsigned int kcur[2];
+  // Direct load j of the wave, of tile ti of K (V: of V or V^T), to LDS.  Fresh and stale rows are told apart lane by lane: with
+  // branches for tiles that lie on one side the layer of 1024 of 4096 tokens took 52.1 us instead of 49.5 (a wave that has its
+  // SIMD to itself waits out every branch).
+  auto load_tile = [&](auto isv, int ti, int j, const char* to) {
+    constexpr bool V = decltype(isv)::value;
     const int key0 = kv_lo + ti * TK;
-    lds_load16(kg + (long long)key0 * p.ldks, 2u * (key0 + TK > p.L ? kofr[j] : kofs[j]), dst);
+    if constexpr (SRC == kSrcVt) {
+      lds_load16(V ? vg + key0 : kg + (long long)key0 * p.ldks, V ? 2u * vofs[j] : kcur[j], to);
+      return;
+    }
+    // rows beyond the last key re-read it (masked)
+    unsigned int key = (unsigned int)(key0 + trow[j] < p.L ? key0 + trow[j] : p.L - 1), row = key - (unsigned int)p.own_lo;
+    bool own = row < (unsigned int)p.own_n;
+    if constexpr (SRC == kSrcPeriodic) {
+      // key = q * P + r, q from the rounded-down reciprocal (at most one too small)
+      unsigned int q = __umulhi(key, p.own_magic), rr = key - q * (unsigned int)p.own_period;
+      if (rr >= (unsigned int)p.own_period) { ++q; rr -= (unsigned int)p.own_period; }
+      row = rr - (unsigned int)p.own_lo;
+      own = row < (unsigned int)p.own_n;
+      row += q * (unsigned int)p.own_n;
+    }
+    row = own ? row : key;
+    if constexpr (V) lds_load16((own ? vfr : vg) + (unsigned long long)row * (unsigned int)(own ? p.ldvf : p.ldvs) + vch[j], to);
+    else lds_load16((own ? kfr : kg) + (unsigned long long)row * (unsigned int)(own ? p.ldkf : p.ldks) + kch[j], to);
   };
-  auto load_v = [&](int ti, int j, const char* dst) { lds_load16(vg + kv_lo + ti * TK, 2u * vofs[j], dst); };
+  using IsK = std::false_type;
+  using IsV = std::true_type;
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
@@ -219,45 +209,29 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
-  // LDS: three K tiles, three V tiles, and a tile of zeros: the values behind probabilities that are zero by construction (a tile
-  // that has none yet, or whose values are already added), where a tile in use could hold infinities
-  constexpr int ZERO = 6 * KB;
-  *reinterpret_cast<u32x4*>(smem + ZERO + tid * 32) = u32x4{0u, 0u, 0u, 0u};
-  *reinterpret_cast<u32x4*>(smem + ZERO + tid * 32 + 16) = u32x4{0u, 0u, 0u, 0u};
+  // LDS: a ring of three slots, a K tile and a V tile each.  Slot i % 3 takes K_i and V_{i+1}, so an iteration reads its K and its V
+  // in one slot and refills another.
+  constexpr int SLOT = 2 * KB;
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int ti = i < ntiles ? i : ntiles - 1;            // past the end: the last tile again (keeps vmcnt uniform)
-    if constexpr (SRC == kSrcVt) {
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
-        load_k(ti, j, smem + i * KB + (2 * wave + j) * 1024);
-    } else {
-      const Rows r = rows_of(kv_lo + ti * TK);
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-        lds_load16(r.k[j], smem + i * KB + (2 * wave + j) * 1024);
-      if (i == 0) {
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          lds_load16(r.v[j], smem + 3 * KB + (2 * wave + j) * 1024);
-      }
+    for (int j = 0; j < 2; ++j) {
+      kcur[j] = 2u * (ti == ntiles - 1 ? kofr[j] : kofs[j]);
+      load_tile(IsK{}, ti, j, smem + i * SLOT + (2 * wave + j) * 1024);
     }
   }
-  if constexpr (SRC == kSrcVt) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-      load_v(0, j, smem + 3 * KB + (2 * wave + j) * 1024);
+  for (int j = 0; j < 2; ++j) {
+    load_tile(IsV{}, 0, j, smem + 2 * SLOT + KB + (2 * wave + j) * 1024);
+    kcur[j] = 2u * (ntiles - 1 <= 3 ? kofr[j] : kofs[j]);
   }
 
-  // LDS byte offsets of this lane's fragments inside a tile.  K: MFMA row c of key block kb, k-step s; V^T: feature csig of
-  // feature block db, key step ts.  The second block is 4096 bytes on in both (for V^T with the key steps ts ^ 2).
-  int kof[4], vof[4];
+  // LDS byte offsets of this lane's fragments inside a tile, the same for K (MFMA row c, which is key csig, of key block kb; k-step s)
+  // and V^T (feature csig of feature block db; key step ts).  The second block is 4096 bytes on.
+  int kof[4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = key_of_mfma_row(c), kchunk = 4 * (i >> 1) + 2 * (i & 1) + g;
-    kof[i] = row * (D * 2) + (((2 * i + g) ^ ((row >> 1) & 7)) * 16);
-    vof[i] = csig * (TK * 2) + ((kchunk ^ (csig & 7) ^ (csig >> 3)) * 16);
-  }
+  for (int i = 0; i < 4; ++i) kof[i] = csig * (D * 2) + (((2 * i + g) ^ ((csig >> 1) & 7)) * 16);
   // V rows: a transposing read hands 16 lanes four keys of 16 features: lane i supplies the address of key i / 4, features 4 * (i
   // % 4) .., and receives feature i.  Chunks 1 and 2 are exchanged (csig), key + 8 g; the second feature block is slot ^ 4.
   const int tri = lane & 15;
@@ -279,13 +253,13 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     a = fmaxf(fmaxf(a, s[8 * h + 4]), s[8 * h + 5]);
     return fmaxf(fmaxf(a, s[8 * h + 6]), s[8 * h + 7]);
   };
-  auto vfrag = [&](int vbase, int ts, int db) { return *reinterpret_cast<const u32x4*>(lds + vbase + vof[db ? ts ^ 2 : ts] + 4096 * db); };
+  auto vfrag = [&](int base, int ts, int db) { return *reinterpret_cast<const u32x4*>(lds + (base + kof[ts]) + KB + 4096 * db); };
   // The eight V fragments of a tile of rows ([2 * ts + db], low and high half), requested by vrequest() and there after
   // varrive<1>() (key steps 0 and 1) and varrive<2>() (2 and 3), which name every register again: the compiler's own
   // transposing read waits for all global loads in flight (it takes them for possible writers of the tile).
   struct VTile { u32x2 r[16]; };
-  auto vrequest = [&](int vbase, VTile& v) {
-    const unsigned int a0 = (unsigned int)(uintptr_t)DF_LPTR(lds + vbase + vtr), a1 = (unsigned int)(uintptr_t)DF_LPTR(lds + vbase + (vtr ^ 64));
+  auto vrequest = [&](int base, VTile& v) {
+    const unsigned int a0 = (unsigned int)(uintptr_t)DF_LPTR(lds + base + KB + vtr), a1 = (unsigned int)(uintptr_t)DF_LPTR(lds + base + KB + (vtr ^ 64));
 #define DF_TR(o, a, off) "ds_read_b64_tr_b16 %" #o ", %" #a " offset:" #off "\n\t"
     asm volatile(DF_TR(0, 16, 0) DF_TR(1, 16, 512) DF_TR(2, 17, 0) DF_TR(3, 17, 512)
                  DF_TR(4, 16, 2048) DF_TR(5, 16, 2560) DF_TR(6, 17, 2048) DF_TR(7, 17, 2560)
@@ -308,7 +282,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   };
   using H1 = std::integral_constant<int, 1>;
   using H2 = std::integral_constant<int, 2>;
-  auto kfrag = [&](int kbase, int s, int kb) { return *reinterpret_cast<const u32x4*>(lds + kbase + kof[s] + 4096 * kb); };
+  auto kfrag = [&](int base, int s, int kb) { return *reinterpret_cast<const u32x4*>(lds + (base + kof[s]) + 4096 * kb); };
   auto pv_mfma = [&](u32x4 v, int ts, int db) {
     o_acc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v), __builtin_bit_cast(bf16x8, pk[ts]), o_acc[db], 0, 0, 0);
   };
@@ -332,145 +306,187 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     for (int kb = 0; kb < 2; ++kb) s_mfma(kfrag(0, s, kb), s, kb);
   sync_tile(std::integral_constant<int, 0>{});             // every wave has read K_0: its slot takes K_3
 
-  int kbase = KB, vnext = 3 * KB, vbase = ZERO;            // K_{tl+1}; V_tl; V_{tl-1}, or zeros where P is
-  int kdst = 0, vdst = 4 * KB;                             // slots of K_{tl+3}, V_{tl+1}
+  int base = SLOT, dst = 0;                                // slots: of K_{tl+1} and V_{tl-1}, of K_{tl+3} and V_{tl+1}
   int tl = 0;
+  auto advance = [&] {
+    dst = base;
+    base = base == 2 * SLOT ? 0 : base + SLOT;
+    ++tl;
+  };
   const bool ragged = (kv_hi - kv_lo) % TK != 0;
   const int nfull = ragged ? ntiles - 1 : ntiles;
   float m_base = 0.f;                                      // what the scores in sa are relative to (PRE)
+  // Maximum of 32 scores per lane and of the other half of the query's: the running maximum that covers them.
+  auto settle = [&](const f32x16& s0, const f32x16& s1) {
+    const float mx = max8(s1, 1, max8(s1, 0, max8(s0, 1, max8(s0, 0, -INFINITY))));
+    const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)));
+    return fmaxf(m_run, PRE ? fmaxf(mx, part) + m_base : fmaxf(mx, part) * sc);
+  };
+  // Everything to the new maximum; returns what is to be added to scores that are relative to the old one (PRE)
+  auto move_to = [&](float m_new) {
+    const float shift = m_base - m_new;
+    if constexpr (PRE) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) { sa[0][e] += shift; sa[1][e] += shift; cinit[e] = -m_new; }
+      m_base = m_new;
+    }
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { o_acc[0][e] *= alpha; o_acc[1][e] *= alpha; }
+    l_run *= alpha;
+    m_run = m_new;
+    return shift;
+  };
+
+  // Tile tl: its probabilities from the scores in sa (in place: a key block's registers take S of tile tl+1 as soon as
+  // its exponentials are done), O += V P of tile tl-1 (PV), S of tile tl+1.  One matrix instruction and its share of
+  // vector instructions per slot; operand fragments are read from LDS five slots ahead.  Returns the tile's row sums.
+  auto tile = [&](auto pvc) {
+    constexpr bool PV = decltype(pvc)::value;
+    u32x4 f[16];
+    VTile vt;
+    if constexpr (PV && SRC == kSrcVt) {
+#pragma unroll
+      for (int i = 0; i < 5; ++i) f[i] = vfrag(base, i >> 1, i & 1);
+    }
+    if constexpr (PV && SRC != kSrcVt) vrequest(base, vt);
+    auto vread = [&](int ts, int db) { return PV && SRC == kSrcVt ? vfrag(base, ts, db) : u32x4{0u, 0u, 0u, 0u}; };
+    auto pv = [&](const u32x4& ahead, int ts, int db) {
+      if constexpr (PV) pv_mfma(SRC == kSrcVt ? ahead : vof8(vt, ts, db), ts, db);
+    };
+    float ex[2][8];
+    auto E = [&](int u, int h) {                           // four exponentials of key step u
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float x = sa[u >> 1][8 * (u & 1) + 4 * h + q];
+        ex[u & 1][4 * h + q] = __builtin_amdgcn_exp2f(PRE ? x : fmaf(x, sc, -m_run));
+      }
+    };
+    unsigned int w[2][4];
+    auto C = [&](int u) {                                  // packing (after the matrix instructions of key step u read pk[u])
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[u & 1][q] = pack_bf2(ex[u & 1][2 * q], ex[u & 1][2 * q + 1]);
+      pk[u] = u32x4{w[u & 1][0], w[u & 1][1], w[u & 1][2], w[u & 1][3]};
+      asm volatile("" : "+v"(pk[u]));                    // (stays here: the branch behind the tile may replace it)
+    };
+    float tsum = 0.f;
+    auto S = [&](int u) {                                  // row sums
+      const float* e = ex[u & 1];
+      const float t = ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
+      tsum = u == 0 ? t : tsum + t;
+      asm volatile("" : "+v"(tsum));
+    };
+    const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
+    auto dma_k = [&](int j) { load_tile(IsK{}, tk3, j, smem + dst + (2 * wave + j) * 1024); };
+    auto dma_v = [&](int j) { load_tile(IsV{}, tv1, j, smem + dst + KB + (2 * wave + j) * 1024); };
+    DF_FENCE;
+    if constexpr (SRC != kSrcVt && PV) { E(0, 0); E(0, 1); DF_FENCE; varrive(vt, H1{}); DF_FENCE; }
+    pv(f[0], 0, 0); f[5] = vread(2, 1); if constexpr (SRC == kSrcVt || !PV) E(0, 0); DF_FENCE;
+    pv(f[1], 0, 1); f[6] = kfrag(base, 0, 0); if constexpr (SRC == kSrcVt || !PV) E(0, 1); dma_k(0); DF_FENCE;
+    pv(f[2], 1, 0); f[7] = vread(3, 0); C(0); dma_k(1); DF_FENCE;
+    pv(f[3], 1, 1); f[8] = kfrag(base, 1, 0); E(1, 0); DF_FENCE;
+    if constexpr (SRC != kSrcVt && PV) { varrive(vt, H2{}); DF_FENCE; }
+    pv(f[4], 2, 0); f[9] = vread(3, 1); E(1, 1); DF_FENCE;
+    pv(f[5], 2, 1); f[10] = kfrag(base, 2, 0); C(1); S(0); DF_FENCE;
+    s_mfma(f[6], 0, 0); f[11] = kfrag(base, 3, 0); E(2, 0); DF_FENCE;
+    pv(f[7], 3, 0); f[12] = kfrag(base, 0, 1); E(2, 1); S(1); DF_FENCE;
+    s_mfma(f[8], 1, 0); f[13] = kfrag(base, 1, 1); C(2); dma_v(0); DF_FENCE;
+    pv(f[9], 3, 1); f[14] = kfrag(base, 2, 1); E(3, 0); DF_FENCE;
+    s_mfma(f[10], 2, 0); f[15] = kfrag(base, 3, 1); E(3, 1); dma_v(1); DF_FENCE;
+    s_mfma(f[11], 3, 0); S(2); DF_FENCE;
+    s_mfma(f[12], 0, 1); C(3); DF_FENCE;
+    s_mfma(f[13], 1, 1); S(3); DF_FENCE;
+    s_mfma(f[14], 2, 1); DF_FENCE;
+    s_mfma(f[15], 3, 1);
+    if (SRC == kSrcVt && tl + 4 == ntiles - 1) {           // the next iteration requests the last tile
+#pragma unroll
+      for (int j = 0; j < 2; ++j) { kcur[j] = 2u * kofr[j]; asm volatile("" : "+v"(kcur[j])); }
+    }
+    sync_tile(std::integral_constant<int, 4>{});           // K_{tl+1} and V_{tl-1} of the next tile have landed, for every wave
+    return tsum;
+  };
+  // A tile with probabilities far above 1: its scores once more, from memory (K's slot is taken), and its probabilities and the
+  // sums relative to a maximum that covers them.  Nothing has read them yet.
+  auto redo = [&]() {
+    f32x16 t[2];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) {
+      const int key = kv_lo + tl * TK + 32 * kb + key_of_mfma_row(c);
+      const long long fr = SRC == kSrcVt ? -1 : fresh_row(p.own_lo, p.own_n, SRC == kSrcPeriodic ? p.own_period : 0, key);
+      const bf16_t* kr = (fr >= 0 ? kfr + fr * p.ldkf : kg + (long long)key * p.ldks) + 8 * g;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        t[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kr + 16 * s)), qreg[s],
+                                                        s == 0 ? cinit : t[kb], 0, 0, 0);
+    }
+    const float shift = move_to(settle(t[0], t[1]));
+    float tsum = 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float e[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const float x = t[u >> 1][8 * (u & 1) + q];
+        e[q] = __builtin_amdgcn_exp2f(PRE ? x + shift : fmaf(x, sc, -m_run));
+        tsum += e[q];
+      }
+      pk[u] = u32x4{pack_bf2(e[0], e[1]), pack_bf2(e[2], e[3]), pack_bf2(e[4], e[5]), pack_bf2(e[6], e[7])};
+    }
+    return tsum;
+  };
+
+  bool again = false;                                      // tile tl has to be done again (NaN passes on as it is)
+  auto values = [&](bool last) {                           // O += V P of the pending tile
+    VTile vt;
+    if constexpr (SRC != kSrcVt) { vrequest(base, vt); varrive(vt, H1{}); varrive(vt, H2{}); }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int ts = i >> 1;
+      u32x4 v = SRC == kSrcVt ? vfrag(base, ts, i & 1) : vof8(vt, ts, i & 1);
+      if (last && ragged) {                                // keys beyond the range: P is 0, V must be finite
+        const int key = kv_lo + (ntiles - 1) * TK + (2 * ts + g) * 8;
+        if (key + 0 >= kv_hi) v.x = 0u; else if (key + 1 >= kv_hi) v.x &= 0xffffu;
+        if (key + 2 >= kv_hi) v.y = 0u; else if (key + 3 >= kv_hi) v.y &= 0xffffu;
+        if (key + 4 >= kv_hi) v.z = 0u; else if (key + 5 >= kv_hi) v.z &= 0xffffu;
+        if (key + 6 >= kv_hi) v.w = 0u; else if (key + 7 >= kv_hi) v.w &= 0xffffu;
+      }
+      pv_mfma(v, ts, i & 1);
+    }
+  };
   for (;;) {
-    // First tile, a tile with a score beyond the window, or the ragged last tile: settle the pending tile's values, mask
-    // the keys beyond the range, move the running maximum and rescale everything to it.
-    if (ragged && tl == ntiles - 1) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (kv_lo + tl * TK + 32 * kb + 16 * (e >> 3) + 8 * g + (e & 7) >= kv_hi) sa[kb][e] = -INFINITY;
+    if (again) {
+      l_run += redo();
+      advance();
+      if (tl >= ntiles) break;
     }
-    {
-      VTile vt;
-      if constexpr (SRC != kSrcVt) { vrequest(vbase, vt); varrive(vt, H1{}); varrive(vt, H2{}); }
+    if (tl == 0 || tl >= nfull) {
+      // First tile, or the ragged last one: settle the pending tile's values, mask the keys beyond the range, move the running
+      // maximum and rescale everything to it.
+      if (ragged && tl == ntiles - 1) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) pv_mfma(SRC == kSrcVt ? vfrag(vbase, i >> 1, i & 1) : vof8(vt, i >> 1, i & 1), i >> 1, i & 1);
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pk[i] = u32x4{0u, 0u, 0u, 0u};
-      vbase = ZERO;
-      const float mx = max8(sa[1], 1, max8(sa[1], 0, max8(sa[0], 1, max8(sa[0], 0, -INFINITY))));
-      const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(mx)));
-      const float m_new = fmaxf(m_run, PRE ? fmaxf(mx, part) + m_base : fmaxf(mx, part) * sc);
-      if constexpr (PRE) {
-        const float shift = m_base - m_new;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) { sa[0][e] += shift; sa[1][e] += shift; cinit[e] = -m_new; }
-        m_base = m_new;
+          for (int e = 0; e < 16; ++e)
+            if (kv_lo + tl * TK + 32 * kb + 16 * (e >> 3) + 8 * g + (e & 7) >= kv_hi) sa[kb][e] = -INFINITY;
       }
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) { o_acc[0][e] *= alpha; o_acc[1][e] *= alpha; }
-      l_run *= alpha;
-      m_run = m_new;
+      if (tl > 0) values(false);
+      move_to(settle(sa[0], sa[1]));
+      l_run += tile(std::false_type{});
+      advance();
     }
-    bool move;
-    do {
-      // Tile tl: its probabilities from the scores in sa (in place: a key block's registers take S of tile tl+1 as soon as
-      // its exponentials are done), O += V P of tile tl-1, S of tile tl+1.  One matrix instruction and its share of
-      // vector instructions per slot; operand fragments are read from LDS five slots ahead.
-      u32x4 f[16];
-      VTile vt;
-      if constexpr (SRC == kSrcVt) {
-#pragma unroll
-        for (int i = 0; i < 5; ++i) f[i] = vfrag(vbase, i >> 1, i & 1);
-      } else {
-        vrequest(vbase, vt);
-      }
-      auto vread = [&](int ts, int db) { return SRC == kSrcVt ? vfrag(vbase, ts, db) : u32x4{0u, 0u, 0u, 0u}; };
-      auto vuse = [&](const u32x4& ahead, int ts, int db) { return SRC == kSrcVt ? ahead : vof8(vt, ts, db); };
-      float ex[2][8];
-      auto E = [&](int u, int h) {                         // four exponentials of key step u
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float x = sa[u >> 1][8 * (u & 1) + 4 * h + q];
-          ex[u & 1][4 * h + q] = __builtin_amdgcn_exp2f(PRE ? x : fmaf(x, sc, -m_run));
-        }
-      };
-      unsigned int w[2][4];
-      auto C = [&](int u) {                                // packing (after the matrix instructions of key step u read pk[u])
-#pragma unroll
-        for (int q = 0; q < 4; ++q) w[u & 1][q] = pack_bf2(ex[u & 1][2 * q], ex[u & 1][2 * q + 1]);
-        pk[u] = u32x4{w[u & 1][0], w[u & 1][1], w[u & 1][2], w[u & 1][3]};
-      };
-      auto S = [&](int u) {                                // row sums
-        const float* e = ex[u & 1];
-        l_run += ((e[0] + e[1]) + (e[2] + e[3])) + ((e[4] + e[5]) + (e[6] + e[7]));
-      };
-      const int tk3 = tl + 3 < ntiles ? tl + 3 : ntiles - 1, tv1 = tl + 1 < ntiles ? tl + 1 : ntiles - 1;
-      const bf16_t *kp[2], *vp[2];
-      if constexpr (SRC != kSrcVt) {
-        const Rows r3 = rows_of(kv_lo + tk3 * TK), r1 = rows_of(kv_lo + tv1 * TK);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { kp[j] = r3.k[j]; vp[j] = r1.v[j]; }
-      }
-      auto dma_k = [&](int j) {
-        const char* dst = smem + kdst + (2 * wave + j) * 1024;
-        if constexpr (SRC == kSrcVt) load_k(tk3, j, dst);
-        else lds_load16(kp[j], dst);
-      };
-      auto dma_v = [&](int j) {
-        const char* dst = smem + vdst + (2 * wave + j) * 1024;
-        if constexpr (SRC == kSrcVt) load_v(tv1, j, dst);
-        else lds_load16(vp[j], dst);
-      };
-      DF_FENCE;
-      if constexpr (SRC != kSrcVt) { E(0, 0); E(0, 1); DF_FENCE; varrive(vt, H1{}); DF_FENCE; }
-      pv_mfma(vuse(f[0], 0, 0), 0, 0); f[5] = vread(2, 1); if constexpr (SRC == kSrcVt) E(0, 0); DF_FENCE;
-      pv_mfma(vuse(f[1], 0, 1), 0, 1); f[6] = kfrag(kbase, 0, 0); if constexpr (SRC == kSrcVt) E(0, 1); dma_k(0); DF_FENCE;
-      pv_mfma(vuse(f[2], 1, 0), 1, 0); f[7] = vread(3, 0); C(0); dma_k(1); DF_FENCE;
-      pv_mfma(vuse(f[3], 1, 1), 1, 1); f[8] = kfrag(kbase, 1, 0); E(1, 0); DF_FENCE;
-      if constexpr (SRC != kSrcVt) { varrive(vt, H2{}); DF_FENCE; }
-      pv_mfma(vuse(f[4], 2, 0), 2, 0); f[9] = vread(3, 1); E(1, 1); DF_FENCE;
-      pv_mfma(vuse(f[5], 2, 1), 2, 1); f[10] = kfrag(kbase, 2, 0); C(1); S(0); DF_FENCE;
-      s_mfma(f[6], 0, 0); f[11] = kfrag(kbase, 3, 0); E(2, 0); DF_FENCE;
-      pv_mfma(vuse(f[7], 3, 0), 3, 0); f[12] = kfrag(kbase, 0, 1); E(2, 1); S(1); DF_FENCE;
-      s_mfma(f[8], 1, 0); f[13] = kfrag(kbase, 1, 1); C(2); dma_v(0); DF_FENCE;
-      pv_mfma(vuse(f[9], 3, 1), 3, 1); f[14] = kfrag(kbase, 2, 1); E(3, 0); DF_FENCE;
-      s_mfma(f[10], 2, 0); f[15] = kfrag(kbase, 3, 1); E(3, 1); dma_v(1); DF_FENCE;
-      s_mfma(f[11], 3, 0); S(2); DF_FENCE;
-      s_mfma(f[12], 0, 1); C(3); DF_FENCE;
-      s_mfma(f[13], 1, 1); S(3); DF_FENCE;
-      s_mfma(f[14], 2, 1); DF_FENCE;
-      s_mfma(f[15], 3, 1);
-      float mx = max8(sa[0], 1, max8(sa[0], 0, -INFINITY));
-      DF_FENCE;
-      mx = max8(sa[1], 1, max8(sa[1], 0, mx));
-      kbase = kbase == 2 * KB ? 0 : kbase + KB;
-      kdst = kdst == 2 * KB ? 0 : kdst + KB;
-      vbase = vnext;
-      vnext = vnext == 5 * KB ? 3 * KB : vnext + KB;
-      vdst = vdst == 5 * KB ? 3 * KB : vdst + KB;
-      ++tl;
-      sync_tile(std::integral_constant<int, 4>{});         // K_{tl+1} and V_{tl-1} of the next tile have landed, for every wave
-      move = __builtin_amdgcn_ballot_w64(PRE ? mx > 8.0f : fmaf(mx, sc, -m_run) > 8.0f) != 0;
-    } while (tl < nfull && !move);
-    if (tl >= ntiles) break;
+    again = false;
+    while (tl < nfull) {
+      const float tsum = tile(std::true_type{});
+      again = __builtin_amdgcn_ballot_w64(tsum > 256.f) != 0;
+      if (again) break;
+      l_run += tsum;
+      advance();
+    }
+    if (!again && tl >= ntiles) break;
   }
   // the last tile's values
   sync_tile(std::integral_constant<int, 0>{});
-  VTile vlast;
-  if constexpr (SRC != kSrcVt) { vrequest(vbase, vlast); varrive(vlast, H1{}); varrive(vlast, H2{}); }
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int ts = i >> 1;
-    u32x4 v = SRC == kSrcVt ? vfrag(vbase, ts, i & 1) : vof8(vlast, ts, i & 1);
-    if (ragged) {                                          // keys beyond the range: P is 0, V must be finite
-      const int key = kv_lo + (ntiles - 1) * TK + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
-      if (key + 0 >= kv_hi) v.x = 0u; else if (key + 1 >= kv_hi) v.x &= 0xffffu;
-      if (key + 2 >= kv_hi) v.y = 0u; else if (key + 3 >= kv_hi) v.y &= 0xffffu;
-      if (key + 4 >= kv_hi) v.z = 0u; else if (key + 5 >= kv_hi) v.z &= 0xffffu;
-      if (key + 6 >= kv_hi) v.w = 0u; else if (key + 7 >= kv_hi) v.w &= 0xffffu;
-    }
-    pv_mfma(v, ts, i & 1);
-  }
+  values(true);
 #undef DF_FENCE
   l_run += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(l_run)));
 
@@ -1065,6 +1081,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   p.bsq = a.bsq; p.bskf = a.bskf; p.bsvf = a.bsvf; p.bsks = a.bsks; p.bsvs = a.bsvs; p.bso = a.bso;
   p.scale = a.scale;
   p.sc_log2 = a.q_scaled ? 1.0f : a.scale * kLog2e;
+  const bool scaled = a.v_transposed && p.sc_log2 == 1.0f;             // (a caller's own scaling and scale = ln 2 do as well)
   if (a.q_scaled && !a.v_transposed) return DF_EINVAL;
   p.nsplit = 1; p.keys_per_split = a.L;
   p.out_packed = a.out_packed;
@@ -1168,13 +1185,13 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
-    constexpr int smem = 7 * 64 * 64 * 2;                // three K and three V^T tiles, zeros
-    if (a.q_scaled) hipLaunchKernelGGL((attn_pipe_d64<true, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V^T tiles
+    if (scaled) hipLaunchKernelGGL((attn_pipe_d64<true, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
     else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   } else {
     // 32-bit row offsets inside a 64-key tile
     if (a.ldkf >= (1 << 24) || a.ldvf >= (1 << 24) || a.ldks >= (1 << 24) || a.ldvs >= (1 << 24)) return DF_ESHAPE;
-    constexpr int smem = 7 * 64 * 64 * 2;                // three K and three V tiles, zeros
+    constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V tiles
     if (a.own_period > 0) hipLaunchKernelGGL((attn_pipe_d64<false, kSrcPeriodic>), dim3((unsigned)nwg), dim3(256), smem, st, p);
     else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcRows>), dim3((unsigned)nwg), dim3(256), smem, st, p);
   }

@@ -736,6 +736,46 @@ def test_attention_infinities_stay_where_they_belong(what, form):
     check(got, ref, True, "attention_infinities", say=say)
 
 
+@pytest.mark.parametrize("form", ["vt", "vt scaled", "rows", "cols"])
+@pytest.mark.parametrize("H,N,keys", [
+    (257, 3, (70, 130, 200, 700)),           # 771 keys: the second tile, consecutive tiles, the last whole one
+    (256, 3, (64, 127, 191, 767)),           # 768 keys, no ragged tile: first and last key of a tile, the very last
+    (43, 3, (3, 66, 128)),                   # 129 keys: one whole tile behind the first, one key in the ragged one
+])
+def test_attention_scores_that_jump(H, N, keys, form):
+    """Scores that rise from one key to the next by 19, then by 109 nats (2^157, beyond float) above what the tiles before
+    held: the tile's probabilities are taken again relative to the new maximum.  Later keys at the same level share the weight; every third query sees
+    the opposite sign, so lanes of a wave differ."""
+    say("attention_scores_that_jump", H, N, keys, form)
+    heads, L, Lq = 8, H * N, H
+    C = heads * 64
+    q, k = normal(59, "q", (1, Lq, C)), 0.3 * normal(59, "k", (1, L, C))
+    v = round_bf16(normal(59, "v", (1, L, C)))
+    q = q + np.where(np.arange(Lq) % 3 == 2, -1.0, 1.0)[None, :, None].astype(np.float32)
+    for i, key in enumerate(keys):
+        k[:, key] += 2.4 if i == 0 else 16.0
+    unit = 0.125 * np.log2(np.e) if form == "vt scaled" else 1.0
+    q, k = round_bf16((q * unit).astype(np.float32)), round_bf16(k.astype(np.float32))
+    ref = ops.attention_dense(q.astype(np.float64) / unit, k, v, heads)
+    qd, kd, vd = dev(q, True), dev(k, True), dev(v, True)
+    if form.startswith("vt"):
+        # (more query blocks than the form for few queries takes)
+        qd = qd.repeat(1, -(-33 * 32 // Lq), 1)
+        Lp = (L + 63) // 64 * 64
+        vt = torch.full((1, C, Lp), float("nan"), dtype=torch.bfloat16, device=DEV)
+        vt[:, :, :L] = vd.transpose(1, 2)
+        got = host(df.attn_stale_vt(qd, kd, vt, heads, L, scale=float(np.log(2)) if form == "vt scaled" else None))
+        for part in range(0, got.shape[1], Lq):
+            check(got[:, part:part + Lq], ref, True, "attention_scores_that_jump", say=say)
+    elif form == "rows":
+        own = slice(Lq, 2 * Lq)
+        got = host(df.attn_displaced(qd, kd[:, own].contiguous(), vd[:, own].contiguous(), kd, vd, heads, 1, N))
+        check(got, ref, True, "attention_scores_that_jump", say=say)
+    else:
+        got = host(df.attn_displaced_cols(qd, kd[:, 1::3].contiguous(), vd[:, 1::3].contiguous(), kd, vd, heads, H, 3, 1, N))
+        check(got, ref, True, "attention_scores_that_jump", say=say)
+
+
 @pytest.mark.parametrize("Lq,L,heads", [(128, 64, 1), (129, 65, 2), (31, 127, 1), (257, 129, 1), (128, 192, 2), (640, 1000, 5),
                                         (1024, 2496, 3), (300, 449, 2), (1024, 4096, 3)])   # (640 and 2496: attn_wave_d64)
 @pytest.mark.parametrize("shape", ["rising", "falling", "spike"])
