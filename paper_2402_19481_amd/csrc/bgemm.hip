@@ -39,6 +39,84 @@ struct Epi {
   static constexpr int kBytes = pass_bytes(R) + kStats + kVecs;
 };
 
+// Cross-attention of one head and 32 tokens (row mt) in one wave: S^T = K Q^T against XA 32-key tiles of packed text keys (lane = token),
+// softmax over the valid keys, O^T = V^T P^T, packed output.  LATE: the values are requested here, behind the scores (they and the keys do
+// not fit the registers of a unit's second workgroup).
+template <int XA, bool LATE>
+__device__ __forceinline__ void xa_head(const WParams& p, int mt, int head, int g, int lane, const bf16x8 (&qf)[4],
+                                        const bf16x8 (&kf)[XA][4], const bf16x8 (&vpre)[2 * XA][2], const bf16x8* kv) {
+  f32x16 sa[XA];
+#pragma unroll
+  for (int kt = 0; kt < XA; ++kt) {
+#pragma unroll
+    for (int e = 0; e < 16; ++e) sa[kt][e] = 0.f;
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt][ds], qf[ds], sa[kt], 0, 0, 0);
+  }
+  bf16x8 vf[2 * XA][2];
+#pragma unroll
+  for (int ks = 0; ks < 2 * XA; ++ks)
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) vf[ks][dt] = LATE ? kv[(size_t)(4 * XA + dt * 2 * XA + ks) * 64] : vpre[ks][dt];
+  const float sc = p.xa_scale * 1.4426950408889634f;
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int key = kt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
+      if (key >= p.xa_keys) sa[kt][e] = -INFINITY;
+      mx = fmaxf(mx, sa[kt][e]);
+    }
+  mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;
+  float l = 0.f;
+#pragma unroll
+  for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float pv = __builtin_amdgcn_exp2f(fmaf(sa[kt][e], sc, -mx));
+      sa[kt][e] = pv;
+      l += pv;
+    }
+  l += __shfl_xor(l, 32, 64);
+  f32x16 oa[2];
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) oa[dt][e] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < 2 * XA; ++ks) {
+    const int kt = ks >> 1, hf = ks & 1;
+    const u32x4 pk = {pack_bf2(sa[kt][8 * hf + 0], sa[kt][8 * hf + 1]), pack_bf2(sa[kt][8 * hf + 2], sa[kt][8 * hf + 3]),
+                      pack_bf2(sa[kt][8 * hf + 4], sa[kt][8 * hf + 5]), pack_bf2(sa[kt][8 * hf + 6], sa[kt][8 * hf + 7])};
+    const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
+#pragma unroll
+    for (int dt = 0; dt < 2; ++dt) oa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][dt], pf, oa[dt], 0, 0, 0);
+  }
+  const float inv = __builtin_amdgcn_rcpf(l);
+  const int KFo = p.N >> 4;
+#pragma unroll
+  for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+    for (int f2 = 0; f2 < 2; ++f2) {
+      float o8[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) o8[q] = oa[dt][8 * f2 + q] * inv;
+      st_vec(p.out_packed + (((size_t)mt * KFo + head * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
+    }
+}
+
+// LDS of the epilogue of one k-group, which leaves the accumulators where they are: the waves' partial row sums, the
+// per-feature vectors, and (GEGLU on an odd number of fragments per wave) the halves that two waves exchange.
+template <int WT, int WF, int TT, int TF, bool LN, bool GEGLU>
+struct Direct {
+  static constexpr int BT = WT * TT, BF = WF * TF;
+  static constexpr int kXch = GEGLU && TF % 2 ? BT * 4096 : 0;
+  static constexpr int kStats = LN ? WF * BT * 32 * 2 * 4 : 0;
+  static constexpr int kVecs = (LN ? 2 : 1) * BF * 32 * 4;
+  static constexpr int kBytes = kXch + kStats + kVecs;
+};
+
 // Linear layer on fragment-packed operands, a workgroup per output tile: BT x 32 tokens by BF x 32 features, the waves WT x WF
 // over it and KG over the k-steps of a stage.  The operands' 1 KB fragments go from memory to an LDS ring of ST stages by direct
 // loads, and from there to the waves without conflicts, since a fragment is in lane order.
@@ -94,14 +172,25 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     KT = (int)((long long)KT * (blockIdx.y + 1) / gridDim.y) - kt0;
   }
 
-  // fragment row of the weights behind row r (0 .. BF-1) of the tile (geglu: the first half are value rows, the second
-  // half their gates)
+  // fragment row of the weights behind row r (0 .. BF-1) of the tile.  GEGLU, several k-groups: the first half are value rows, the
+  // second half their gates.  GEGLU, one k-group: a wave holds pairs, values in front; an odd fragment in the middle is
+  // the value (first wave) or the gate (second) of a pair that the two waves share.
+  constexpr int HP = TF / 2;                           // pairs of a wave
   auto wrow = [&](int r) {
     int nt;
     if constexpr (EPI == EPI_GEGLU) {
-      nt = ng * BFO + (r < BFO ? r : r - BFO);
+      bool gate;
+      if constexpr (KG == 1) {
+        static_assert(TF % 2 == 0 || WF == 2, "two waves share the odd pair");
+        const int w = r / TF, j = r - w * TF;
+        gate = TF % 2 && j == HP ? w == 1 : j >= TF - HP;
+        nt = ng * BFO + (TF % 2 && j == HP ? HP : w * (TF - HP) + (gate ? j - (TF - HP) : j));
+      } else {
+        gate = r >= BFO;
+        nt = ng * BFO + (gate ? r - BFO : r);
+      }
       if (nt > NF - 1) nt = NF - 1;
-      return r < BFO ? nt : NF + nt;
+      return gate ? NF + nt : nt;
     }
     nt = ng * BF + r;
     return nt < NF ? nt : NF - 1;
@@ -216,11 +305,17 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
   using I2 = std::integral_constant<int, 2>;
   using All = std::integral_constant<int, -1>;
+  auto request_args = [&] {                            // (behind the first loads)
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (EPI == EPI_QKV) wg_request_segments(p);
+    else if constexpr (EPI != EPI_PART) wg_request_outputs(p);
+  };
   if constexpr (ST >= 4) {
     // Stage kt + ST - 1 is requested in parts between the matrix instructions of stage kt
     constexpr int LATE = NL - ((KS - 1) * NL + KS - 1) / KS;   // loads of the part behind the barrier
 #pragma unroll
     for (int s = 0; s < ST - 1; ++s) issue(s < KT ? s : KT - 1, s, All{});   // past the end: the last stage again
+    request_args();
     wait_vm_lds<NL * (ST - 2)>();
     block_sync();
     rd(0, 0, I0{});
@@ -247,6 +342,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 #pragma unroll
   for (int s = 0; s < ST; ++s)
     if (s < KT) issue(s, s, All{});
+  request_args();
   if (ST <= KT) wait_vm_lds<NL * (ST - 1)>();
   else wait_vm_lds<0>();
   block_sync();
@@ -289,6 +385,189 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   }
 
   // ---- epilogue: the operand ring is free ----
+  // One k-group: a wave finishes its own tile where it stands, in the accumulators.  A lane holds one token's 2 x 8 consecutive
+  // features of every fragment, which is the unit of the packed output.  The folded LayerNorm, rstd (x - mean s) + t, is a
+  // product with rstd and then one v_mfma_f32_32x32x2_f32 per fragment, whose two k's are s x (-mean rstd) and t x 1 (a plain layer:
+  // bias x 1): float throughout, on the matrix unit beside the vector ALU, which bounds these epilogues, and two LDS reads per
+  // fragment instead of four per eight values.  Through LDS as below, with the norm on the vector ALU, 1024 x 10240 x 1280 with GEGLU
+  // spent 11.1 us here.
+  if constexpr (KG == 1 && (EPI != EPI_XA || TF == 2)) {
+    using D = Direct<WT, WF, TT, TF, LN, EPI == EPI_GEGLU>;
+    constexpr bool kOdd = EPI == EPI_GEGLU && TF % 2;
+    f32x4* xch = reinterpret_cast<f32x4*>(smem);       // [from wave row 0 / 1][BT][2][64 lanes]
+    float* s_part = reinterpret_cast<float*>(smem + D::kXch);            // [WF][BT*32][2]
+    float* s_t = reinterpret_cast<float*>(smem + D::kXch + D::kStats);   // [BF*32] shift / bias
+    float* s_s = s_t + BF * 32;                        // [BF*32] scale sums
+    bf16x8 xkf[XA > 0 ? XA : 1][4], xvf[XA > 0 ? 2 * XA : 1][2];
+    const bf16x8* kv = nullptr;
+    if constexpr (EPI == EPI_XA) {
+      // the wave's features are one head: its keys and values are on their way while the row sums meet
+      const int mt = mg * BT + wt * TT, head = ng * WF + wf;
+      const int bi = mt * 32 < p.xa_rows || mt >= MT ? 0 : mt * 32 / p.xa_rows;
+      kv = p.xkv + (size_t)bi * p.xa_bstride + (size_t)(head * 2 < NF ? head : 0) * (12 * XA) * 64 + lane;
+#pragma unroll
+      for (int kt = 0; kt < XA; ++kt)
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds) xkf[kt][ds] = kv[(size_t)(kt * 4 + ds) * 64];
+      if constexpr (OCC == 1)
+#pragma unroll
+        for (int ks = 0; ks < 2 * XA; ++ks)
+#pragma unroll
+          for (int dt = 0; dt < 2; ++dt) xvf[ks][dt] = kv[(size_t)(4 * XA + dt * 2 * XA + ks) * 64];
+    }
+    block_sync();
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const int r = tid + q * 64 * NW;
+      if (r < BF * 32) { s_t[r] = vt[q]; if constexpr (LN) s_s[r] = vs[q]; }
+    }
+    if constexpr (LN) {
+#pragma unroll
+      for (int i = 0; i < TT; ++i) {
+        const float sm = ln_sum[i] + __shfl_xor(ln_sum[i], 32, 64);
+        const float sq = ln_sq[i] + __shfl_xor(ln_sq[i], 32, 64);
+        if (g == 0) {
+          float* d = s_part + ((wf * BT + wt * TT + i) * 32 + tok) * 2;
+          d[0] = sm; d[1] = sq;
+        }
+      }
+    }
+    if constexpr (kOdd) {
+      // of the shared pair the first wave finishes features 0 - 7 of either half, the second 8 - 15 (register order)
+#pragma unroll
+      for (int i = 0; i < TT; ++i) {
+        const f32x16& a = acc[i][HP];
+        f32x4* d = xch + ((wf * BT + wt * TT + i) * 2) * 64 + lane;
+        if (wf == 0) {
+          d[0] = f32x4{a[8], a[9], a[10], a[11]};
+          d[64] = f32x4{a[12], a[13], a[14], a[15]};
+        } else {
+          d[0] = f32x4{a[0], a[1], a[2], a[3]};
+          d[64] = f32x4{a[4], a[5], a[6], a[7]};
+        }
+      }
+    }
+    __syncthreads();
+    // weight row tok of a fragment is its feature sigma(tok) (bits 2 and 3 swapped)
+    const int sig = (tok & 0x13) | ((tok & 4) << 1) | ((tok & 8) >> 1);
+    auto vec_of = [&](int r) { return LN ? (g ? s_t : s_s)[r * 32 + sig] : g ? s_t[r * 32 + sig] : 0.f; };
+    auto rows_out = [&](auto po) {
+      constexpr bool packed_only = decltype(po)::value;  // (the step's GEGLU: short code, it is cold in every launch)
+#pragma unroll
+    for (int i = 0; i < TT; ++i) {
+      const int mt = mg * BT + wt * TT + i, m = mt * 32 + tok;
+      float rstd = 1.f, bm = g ? 1.f : 0.f;
+      if constexpr (LN) {
+        float sm = 0.f, sq = 0.f;
+#pragma unroll
+        for (int w = 0; w < WF; ++w) {
+          const float* q = s_part + ((w * BT + wt * TT + i) * 32 + tok) * 2;
+          sm += q[0]; sq += q[1];
+        }
+        const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+        const float mean = sm * inv_k;
+        const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
+        rstd = __builtin_amdgcn_rsqf(var + p.ln_eps);
+        bm = g ? 1.f : -mean * rstd;
+      }
+      auto finish = [&](f32x16& a, int r) {            // tile row r: norm and shift, or bias
+        if constexpr (LN) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) a[e] *= rstd;
+        }
+        a = __builtin_amdgcn_mfma_f32_32x32x2f32(vec_of(r), bm, a, 0, 0, 0);
+      };
+      auto store = [&](int nt, int f, float* v) {
+        if (mt >= MT || nt >= NF) return;
+        const int n = nt * 32 + 16 * f + 8 * g;
+        if constexpr (!kResInit) {
+          if (p.residual && m < p.M) {
+            float r8[8];
+            ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += r8[q];
+          }
+        }
+        wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+      };
+      if constexpr (EPI == EPI_GEGLU) {
+        if (mt >= MT) continue;
+        auto unit = [&](int nt, int f, const f32x16& a, const f32x16& gt) {
+          if (nt >= NF) return;
+          float v[8];
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[q] = a[8 * f + q] * gelu_erf(gt[8 * f + q]);
+          if (packed_only) st_vec(p.out_packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
+          else store(nt, f, v);
+        };
+#pragma unroll
+        for (int j = 0; j < HP; ++j) {
+          finish(acc[i][j], wf * TF + j);
+          finish(acc[i][TF - HP + j], wf * TF + TF - HP + j);
+#pragma unroll
+          for (int f = 0; f < 2; ++f) unit(ng * BFO + wf * (TF - HP) + j, f, acc[i][j], acc[i][TF - HP + j]);
+        }
+        if constexpr (kOdd) {
+          const f32x4* d = xch + (((1 - wf) * BT + wt * TT + i) * 2) * 64 + lane;
+          const f32x4 lo = d[0], hi = d[64];
+          f32x16 o;
+#pragma unroll
+          for (int e = 0; e < 16; ++e) o[e] = (e & 4 ? hi : lo)[e & 3];
+          finish(acc[i][HP], wf * TF + HP);
+          finish(o, (1 - wf) * TF + HP);
+          if (wf == 0) unit(ng * BFO + HP, 0, acc[i][HP], o);
+          else unit(ng * BFO + HP, 1, o, acc[i][HP]);
+        }
+      } else if constexpr (EPI == EPI_XA) {
+        finish(acc[i][0], wf * TF);
+        finish(acc[i][1], wf * TF + 1);
+        const int head = ng * WF + wf;
+        if (mt >= MT || head * 2 >= NF) continue;
+        // the head's normalised, rounded query is the B operand of S^T = K Q^T
+        bf16x8 qf[4];
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds) {
+          const f32x16& a = acc[i][ds >> 1];
+          const int e = 8 * (ds & 1);
+          qf[ds] = __builtin_bit_cast(bf16x8, u32x4{pack_bf2(a[e], a[e + 1]), pack_bf2(a[e + 2], a[e + 3]), pack_bf2(a[e + 4], a[e + 5]),
+                                                    pack_bf2(a[e + 6], a[e + 7])});
+        }
+        xa_head<XA, (OCC > 1)>(p, mt, head, g, lane, qf, xkf, xvf, kv);
+      } else if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+        for (int j = 0; j < TF; ++j) {
+          finish(acc[i][j], wf * TF + j);
+          const int nt = ng * BF + wf * TF + j;
+          if (mt >= MT || nt >= NF) continue;
+#pragma unroll
+          for (int f = 0; f < 2; ++f) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
+            wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < TF; ++j) {
+          finish(acc[i][j], wf * TF + j);
+#pragma unroll
+          for (int f = 0; f < 2; ++f) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
+            store(ng * BF + wf * TF + j, f, v);
+          }
+        }
+      }
+    }
+    };
+    if (EPI == EPI_GEGLU && p.out_packed && !p.out_f32 && !p.out_rows && !p.residual) rows_out(std::true_type{});
+    else rows_out(std::false_type{});
+    return;
+  }
+
+  // Several k-groups: their accumulators meet in LDS.
   constexpr int R = E::R;
   f32x4* red = reinterpret_cast<f32x4*>(smem);         // [KG][R rows][BF][2 f][2 halves][64 lanes]
   float* s_part = reinterpret_cast<float*>(smem + E::pass_bytes(R));   // [KG*WF][BT*32][2] partial (sum, sum of squares)
@@ -389,65 +668,8 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
           const u32x4 qv = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
           qf[ds] = __builtin_bit_cast(bf16x8, qv);
         }
-        f32x16 sa[XA];
-#pragma unroll
-        for (int kt = 0; kt < XA; ++kt) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) sa[kt][e] = 0.f;
-#pragma unroll
-          for (int ds = 0; ds < 4; ++ds) sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt][ds], qf[ds], sa[kt], 0, 0, 0);
-        }
-        bf16x8 vf[2 * XA][2];
-#pragma unroll
-        for (int ks = 0; ks < 2 * XA; ++ks)
-#pragma unroll
-          for (int dt = 0; dt < 2; ++dt) vf[ks][dt] = kv[(size_t)(4 * XA + dt * 2 * XA + ks) * 64];
-        const float sc = p.xa_scale * 1.4426950408889634f;
-        float mx = -INFINITY;
-#pragma unroll
-        for (int kt = 0; kt < XA; ++kt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int key = kt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
-            if (key >= p.xa_keys) sa[kt][e] = -INFINITY;
-            mx = fmaxf(mx, sa[kt][e]);
-          }
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;
-        float l = 0.f;
-#pragma unroll
-        for (int kt = 0; kt < XA; ++kt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const float pv = __builtin_amdgcn_exp2f(fmaf(sa[kt][e], sc, -mx));
-            sa[kt][e] = pv;
-            l += pv;
-          }
-        l += __shfl_xor(l, 32, 64);
-        f32x16 oa[2];
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) oa[dt][e] = 0.f;
-#pragma unroll
-        for (int ks = 0; ks < 2 * XA; ++ks) {
-          const int kt = ks >> 1, hf = ks & 1;
-          const u32x4 pk = {pack_bf2(sa[kt][8 * hf + 0], sa[kt][8 * hf + 1]), pack_bf2(sa[kt][8 * hf + 2], sa[kt][8 * hf + 3]),
-                            pack_bf2(sa[kt][8 * hf + 4], sa[kt][8 * hf + 5]), pack_bf2(sa[kt][8 * hf + 6], sa[kt][8 * hf + 7])};
-          const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
-#pragma unroll
-          for (int dt = 0; dt < 2; ++dt) oa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks][dt], pf, oa[dt], 0, 0, 0);
-        }
-        const float inv = __builtin_amdgcn_rcpf(l);
-        const int KFo = p.N >> 4;
-#pragma unroll
-        for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-          for (int f2 = 0; f2 < 2; ++f2) {
-            float o8[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) o8[q] = oa[dt][8 * f2 + q] * inv;
-            st_vec(p.out_packed + (((size_t)mt * KFo + head * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
-          }
+        const bf16x8 none[2 * XA][2] = {};
+        xa_head<XA, true>(p, mt, head, g, lane, qf, kf, none, kv);
       }
     } else {
       // items (token row, output fragment, half of the row's tokens): lane -> token it*16 + lane%16, features 8*(lane/16) ..
@@ -458,52 +680,6 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         const int q0 = pass * R + r, trow = (q0 % WT) * TT + q0 / WT, mt = mg * BT + trow, nt = ng * BFO + jo;
         if (mt >= MT || nt >= NF) continue;
         const int jf = jo;
-        if constexpr (EPI == EPI_QKV) {
-          const int n0 = nt * 32, sg = (n0 >= p.seg_w ? 1 : 0) + (n0 >= 2 * p.seg_w ? 1 : 0);
-          if (p.seg_tr[sg]) {
-            // transposed segment (V^T), features 16*half .. +15 of the fragment, the row's 32 tokens
-            bf16_t* seg = p.seg_out[sg] + p.seg_row0[sg];
-            const long long sld = p.seg_ld[sg];
-            const int rin = p.seg_rows_in[sg], pin = p.seg_pin[sg], pout = p.seg_pout[sg];
-            auto one = [&](int fe, int tk2) {          // feature fe of the fragment, token tk2 of the row
-              float x = 0.f;
-#pragma unroll
-              for (int k = 0; k < KG; ++k)
-                x += reinterpret_cast<const float*>(red + (((k * R + r) * BF + jf) * 4 + 2 * half + ((fe >> 2) & 1)) * 64 + tk2 +
-                                                    32 * ((fe >> 3) & 1))[fe & 3];
-              const float* mr = s_mr + (trow * 32 + tk2) * 2;
-              return mr[1] * (x - mr[0] * s_s[jf * 32 + fe]) + s_t[jf * 32 + fe];
-            };
-            auto at = [&](int fe, int m) {
-              const int bi = m < rin ? 0 : m / rin;
-              return seg + ((long long)bi * p.seg_w + (n0 + fe - sg * p.seg_w)) * sld + seg_pos(m - bi * rin, pin, pout);
-            };
-            if (p.seg_tr[sg] == 8) {                   // eight tokens stay together and 16-byte aligned (launcher)
-              const int fe = 16 * half + tl, t0 = 8 * (lane >> 4);
-              float v[8];
-#pragma unroll
-              for (int q = 0; q < 8; ++q) v[q] = one(fe, t0 + q);
-              if (mt * 32 + t0 < p.M) st_vec(at(fe, mt * 32 + t0), v);
-            } else if (p.seg_tr[sg] == 2) {            // token pairs stay together: 64 contiguous bytes per feature and store
-              const int t0 = 2 * tl;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                const int fe = 16 * half + 4 * q + (lane >> 4);
-                const unsigned int w = pack_bf2(one(fe, t0), one(fe, t0 + 1));
-                if (mt * 32 + t0 < p.M) *reinterpret_cast<unsigned int*>(at(fe, mt * 32 + t0)) = w;
-              }
-            } else {
-              const int t0 = lane & 31;
-#pragma unroll
-              for (int q = 0; q < 8; ++q) {
-                const int fe = 16 * half + 2 * q + (lane >> 5);
-                const bf16_t w = f2bf(one(fe, t0));
-                if (mt * 32 + t0 < p.M) *at(fe, mt * 32 + t0) = w;
-              }
-            }
-            continue;
-          }
-        }
         const int tk = half * 16 + tl;
         float v[8];
         value8(r, trow, jf, f, gg, tk, v);
@@ -522,7 +698,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
             for (int q = 0; q < 8; ++q) v[q] += r8[q];
           }
         }
-        wg_store_unit(p, mt, m, n, tk + 32 * gg, v);
+        wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
       }
     }
   }
@@ -567,7 +743,7 @@ __global__ __launch_bounds__(256) void bgemm_sum_kernel(WParams p) {
     b += bb;
   }
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  wg_store_unit(p, mt, m, n, lane, v);
+  wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * (lane >> 5), lane, v);
 }
 
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
@@ -586,7 +762,8 @@ int launch_one(const WParams& pin, hipStream_t st) {
   const int np = (MG + gm - 1) / gm;
   p.group_m = (MG + np - 1) / np;
   constexpr int ring = ST * (BT + BF) * KS * KG * 1024;
-  constexpr int fin = Epi<WT, WF, TT, TF, KG, OCC, LN>::kBytes;
+  constexpr bool direct = KG == 1 && (EPI != EPI_XA || TF == 2);
+  constexpr int fin = direct ? Direct<WT, WF, TT, TF, LN, EPI == EPI_GEGLU>::kBytes : Epi<WT, WF, TT, TF, KG, OCC, LN>::kBytes;
   constexpr int smem = ring > fin ? ring : fin;
   static_assert(smem <= 160 * 1024, "LDS of a compute unit");
   auto k = bgemm_kernel<WT, WF, TT, TF, KG, KS, ST, OCC, EPI, LN, XA>;
@@ -626,13 +803,7 @@ int launch_tile_cfg(const WParams& p, hipStream_t st) {
   }
   if (p.nseg) {
     if (!p.ln_s) return DF_ESHAPE;                       // (the segmented projections of the step fold a LayerNorm)
-    WParams q = p;
-    for (int i = 0; i < p.nseg; ++i) {
-      // transposed segments: how many consecutive tokens stay together and aligned in the destination
-      const long long al = p.seg_ld[i] | p.seg_row0[i] | p.seg_pin[i] | p.seg_pout[i] | p.seg_rows_in[i] | p.M;
-      if (p.seg_tr[i]) q.seg_tr[i] = (al % 8 == 0 && (uintptr_t)p.seg_out[i] % 16 == 0) ? 8 : (al % 2 == 0 && (uintptr_t)p.seg_out[i] % 4 == 0) ? 2 : 1;
-    }
-    return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(q, st);
+    return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_QKV, true, 0>(p, st);
   }
   if (p.parts > 1) {
     if constexpr (TT == 1 && KG == 1 && OCC == 1 && TF != 3) return launch_one<WT, WF, TT, TF, KG, KS, ST, OCC, EPI_PART, false, 0>(p, st);

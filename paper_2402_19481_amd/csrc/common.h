@@ -35,22 +35,24 @@ __device__ __forceinline__ float silu_f(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
 }
 
-// GELU in its exact (erf) form, 0.5 x (1 + erf(x / sqrt 2)).  erfc(|z|) = t (a1 + t (a2 + t (a3 + t (a4 + t a5))))
-// exp(-z^2) with z = x / sqrt 2, t = 1 / (1 + p |z|) (Abramowitz & Stegun 7.1.26: absolute error below 1.5e-7, the size of
-// float rounding of the result).  With e = erfc(|z|) / 2 the result is max(x, 0) - |x| e for both signs, and for negative
-// arguments nothing cancels.  The constants below have the 1/2, the 1/sqrt 2 and log2(e) in them: fourteen instructions per
-// value, where the library erff takes several times that; the GEGLU epilogues are otherwise bounded by this function.
-// The factor of e is kept finite, so that +inf stays +inf (e is 0 there).
+// GELU in its exact (erf) form, 0.5 x (1 + erf(x / sqrt 2)) = max(x, 0) - |x| Q(|x|) for both signs, Q(a) = erfc(a / sqrt 2) / 2: for
+// negative arguments nothing cancels.  log2 Q is so smooth that a polynomial of degree 8 in a holds it: fitted here by reweighted least
+// squares on [0, 5.6] to |error of a Q| <= 1e-7 and |error of Q| <= 1e-4 Q (0.61 of either bound reached; Q < 1e-8 beyond, where the
+// polynomial goes on falling to -infinity).  Against 64 bits the float function is off by 2.4e-7 at most and 2.8e-8 rms over N(0, 1)
+// (Abramowitz & Stegun 7.1.26, with a reciprocal besides: 3.3e-7 and 3.6e-8), 6e-5 of the value at arguments around -5 (2.5e-3).
+// Twelve instructions per value, one of them at a quarter of the rate: the GEGLU epilogues are bounded by them.
+// The factor of Q is kept finite, so that +inf stays +inf (Q is 0 there).
 __device__ __forceinline__ float gelu_erf(float x) {
-  const float ax = fabsf(x);
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.23164189f, ax, 1.0f));
-  float poly = fmaf(t, 0.5307027145f, -0.7265760135f);
-  poly = fmaf(poly, t, 0.7107068705f);
-  poly = fmaf(poly, t, -0.1422483685f);
-  poly = fmaf(poly, t, 0.127414796f);
-  const float u = x * 0.84932180f;
-  const float e = poly * t * __builtin_amdgcn_exp2f(-(u * u));
-  return fmaf(-fabsf(fminf(x, 3.0e38f)), e, fmaxf(x, 0.f));
+  const float a = fabsf(x);
+  float q = fmaf(-6.546825e-07f, a, 1.1150935e-05f);
+  q = fmaf(q, a, -4.1239004e-05f);
+  q = fmaf(q, a, -0.00051439233f);
+  q = fmaf(q, a, 0.007592879f);
+  q = fmaf(q, a, -0.05288758f);
+  q = fmaf(q, a, -0.45907083f);
+  q = fmaf(q, a, -1.1511227f);
+  q = fmaf(q, a, -0.99999964f);
+  return fmaf(-fabsf(fminf(x, 3.0e38f)), __builtin_amdgcn_exp2f(q), fmaxf(x, 0.f));
 }
 
 template <typename T> struct Elem;

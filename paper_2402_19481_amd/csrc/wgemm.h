@@ -25,7 +25,7 @@ struct WParams {
   bf16_t* seg_out[3];
   long long seg_ld[3], seg_rows_out[3], seg_row0[3];
   int seg_rows_in[3];
-  int seg_tr[3];
+  int seg_tr[3];        // 0: rows; 1: transposed; 2: transposed, token pairs stay together and 4-byte aligned
   int seg_pin[3], seg_pout[3];
   float seg0_scale;     // factor of segment 0 (the attention queries), 1 without one; segment 0 is never transposed
   // fused cross-attention (XA > 0): per (batch item, head) 8*XA key fragments then 4*XA value fragments
@@ -39,9 +39,58 @@ struct WParams {
   int group_m;          // bgemm: token tiles of a panel in the tile order (see there)
 };
 
-// One output unit: 8 consecutive features n .. n+7 of token m = mt*32 + lane%32, written in every requested form.
-__device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, int n, int lane, const float* v) {
+// Arguments of the segment that a fragment of 32 features lies in (seg_w % 32 == 0).  `n0`, its first feature, is the same for the
+// whole wave and the three are chosen by scalar selects: indexed by a lane's feature number the arguments came by four dependent
+// vector loads per unit, most of the 3.5 us that the epilogue of a 128 x 128 query / key / value tile took.
+struct WSegment {
+  bf16_t* out;
+  long long ld, rows_out, row0;
+  int rows_in, tr, pin, pout, first;   // first: feature 0 of the segment
+  float scale;
+};
+__device__ __forceinline__ WSegment wg_segment(const WParams& p, int n0) {
+  const bool s1 = n0 >= p.seg_w, s2 = n0 >= 2 * p.seg_w;
+  auto pick = [&](const auto& v) { return s2 ? v[2] : s1 ? v[1] : v[0]; };
+  return {pick(p.seg_out), pick(p.seg_ld),  pick(p.seg_rows_out), pick(p.seg_row0), pick(p.seg_rows_in),
+          pick(p.seg_tr),  pick(p.seg_pin), pick(p.seg_pout),     s2 ? 2 * p.seg_w : s1 ? p.seg_w : 0,
+          s1 ? 1.0f : p.seg0_scale};
+}
+
+// One output unit: features n0 + fo .. + 7 of token m, written in every requested form.  n0 is uniform, the first of a fragment; `lane`
+// is the lane of that token and feature group in the packed layout (m % 32 + 32 (fo / 8 % 2)); lane ^ 1 of the wave holds token m ^ 1.
+__device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, int n0, int fo, int lane, const float* v) {
   const bool row_ok = m < p.M;
+  const int n = n0 + fo;
+  if (p.nseg > 0) {
+    const WSegment s = wg_segment(p, n0);
+    const int mp = s.tr > 1 ? m & ~1 : m;
+    const int bi = mp < s.rows_in ? 0 : mp / s.rows_in;   // (usually one batch item: a comparison instead of a division)
+    const long long pos = s.row0 + seg_pos(mp - bi * s.rows_in, s.pin, s.pout);
+    if (s.tr > 1) {
+      // feature-major, token pairs stay together and aligned (launcher): neighbouring lanes exchange, the even one keeps feature 2q of
+      // both tokens and the odd one 2q + 1; a store covers the 32 tokens of four features
+      bf16_t* o = s.out + ((long long)bi * p.seg_w + (n - s.first) + (m & 1)) * s.ld + pos;
+      const unsigned int sel = m & 1 ? 0x07060302u : 0x01000504u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const unsigned int u = pack_bf2(v[2 * q], v[2 * q + 1]);
+        const unsigned int w = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)u, 0xb1, 0xf, 0xf, true);   // lane ^ 1
+        const unsigned int x = __builtin_amdgcn_perm(u, w, sel);
+        if (row_ok) *reinterpret_cast<unsigned int*>(o + 2 * q * s.ld) = x;
+      }
+    } else if (s.tr) {
+      bf16_t* o = s.out + ((long long)bi * p.seg_w + (n - s.first)) * s.ld + pos;
+      if (row_ok) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) o[q * s.ld] = f2bf(v[q]);
+      }
+    } else if (row_ok) {
+      const float w[8] = {v[0] * s.scale, v[1] * s.scale, v[2] * s.scale, v[3] * s.scale,
+                          v[4] * s.scale, v[5] * s.scale, v[6] * s.scale, v[7] * s.scale};
+      st_vec(s.out + ((long long)bi * s.rows_out + pos) * s.ld + (n - s.first), w);
+    }
+    return;
+  }
   if (p.out_f32 && row_ok) {
     st_vec(p.out_f32 + (long long)m * p.ldo + n, v);
     st_vec(p.out_f32 + (long long)m * p.ldo + n + 4, v + 4);
@@ -52,29 +101,20 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
     const int KFo = p.N >> 4;
     st_vec(p.out_packed + (((size_t)mt * KFo + (n >> 4)) * 64 + lane) * 8, v);
   }
-  if (row_ok) {
-    if (p.nseg > 0) {
-      // 8 features never straddle a segment (seg_w % 32 == 0); at most three segments, usually one batch item:
-      // comparisons instead of integer divisions
-      const int sg = (n >= p.seg_w ? 1 : 0) + (n >= 2 * p.seg_w ? 1 : 0);
-      const int bi = m < p.seg_rows_in[sg] ? 0 : m / p.seg_rows_in[sg];
-      if (p.seg_tr[sg]) {
-        // feature-major output: the 32 tokens of a half wave are consecutive in memory for each feature
-        bf16_t* o = p.seg_out[sg] + ((long long)bi * p.seg_w + (n - sg * p.seg_w)) * p.seg_ld[sg] + p.seg_row0[sg] +
-                    seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) o[q * p.seg_ld[sg]] = f2bf(v[q]);
-      } else {
-        const long long orow = (long long)bi * p.seg_rows_out[sg] + p.seg_row0[sg] +
-                               seg_pos(m - bi * p.seg_rows_in[sg], p.seg_pin[sg], p.seg_pout[sg]);
-        const float sc = sg == 0 ? p.seg0_scale : 1.0f;
-        const float w[8] = {v[0] * sc, v[1] * sc, v[2] * sc, v[3] * sc, v[4] * sc, v[5] * sc, v[6] * sc, v[7] * sc};
-        st_vec(p.seg_out[sg] + orow * p.seg_ld[sg] + (n - sg * p.seg_w), w);
-      }
-    } else if (p.out_rows) {
-      st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);
-    }
-  }
+  if (p.out_rows && row_ok) st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);
+}
+
+// Every argument that an epilogue needs is requested while the first operands are on their way: fetched where it is first used, a
+// batch of them costs that epilogue a round trip to memory (they are cold in every launch).
+__device__ __forceinline__ void wg_request_outputs(const WParams& p) {
+  asm volatile("" ::"s"(p.out_f32), "s"(p.ldo), "s"(p.out_packed), "s"(p.out_rows), "s"(p.ld_rows), "s"(p.nseg), "s"(p.ln_eps));
+}
+__device__ __forceinline__ void wg_request_segments(const WParams& p) {
+  asm volatile("" ::"s"(p.seg_w), "s"(p.seg_out[0]), "s"(p.seg_out[1]), "s"(p.seg_out[2]), "s"(p.seg_ld[0]), "s"(p.seg_ld[1]), "s"(p.seg_ld[2]),
+               "s"(p.seg_rows_out[0]), "s"(p.seg_rows_out[1]), "s"(p.seg_rows_out[2]));
+  asm volatile("" ::"s"(p.seg_row0[0]), "s"(p.seg_row0[1]), "s"(p.seg_row0[2]), "s"(p.seg_rows_in[0]), "s"(p.seg_rows_in[1]), "s"(p.seg_rows_in[2]),
+               "s"(p.seg_tr[0]), "s"(p.seg_tr[1]), "s"(p.seg_tr[2]), "s"(p.seg_pin[0]), "s"(p.seg_pin[1]), "s"(p.seg_pin[2]),
+               "s"(p.seg_pout[0]), "s"(p.seg_pout[1]), "s"(p.seg_pout[2]), "s"(p.seg0_scale));
 }
 
 // Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.

@@ -182,6 +182,9 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     for (int j = 0; j < TN; ++j) wr[s][j] = wb[j][o];
   }
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (!PART && XA == 0) wg_request_outputs(p);
+  if constexpr (LN && XA == 0) wg_request_segments(p);
+  __builtin_amdgcn_sched_barrier(0);
   DF_WTRACE(2, __builtin_readcyclecounter());
   for (int kf = 0; kf < KFw; kf += PF) {
 #pragma unroll
@@ -292,7 +295,6 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     }
     const int m = mt * 32 + tok;
     const int nfrag = ng * JO + j;                     // output fragment along the feature axis
-    const int n = nfrag * 32 + 16 * f + 8 * g;         // first of this lane's 8 consecutive features
     if (ln) {
       float sm = 0.f, sq = 0.f;
 #pragma unroll
@@ -341,7 +343,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += e.r[q];
     }
-    wg_store_unit(p, mt, m, n, lane, v);
+    wg_store_unit(p, mt, m, nfrag * 32, 16 * f + 8 * g, lane, v);
   }
   DF_WTRACE(9 + 2 * (i0 / RP < 4 ? i0 / RP : 3), __builtin_readcyclecounter());
   }
@@ -626,7 +628,8 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     for (int i = 0; i < a.nseg; ++i) {
       if (!a.seg_out[i] || a.seg_rows_in[i] <= 0 || (!a.seg_tr[i] && (a.seg_ld[i] % 8 || !al(a.seg_out[i], 16))))
         return DF_EINVAL;
-      p.seg_tr[i] = a.seg_tr[i]; p.seg_pin[i] = a.seg_pin[i]; p.seg_pout[i] = a.seg_pout[i];
+      const long long even = a.seg_ld[i] | a.seg_row0[i] | a.seg_pin[i] | a.seg_pout[i] | a.seg_rows_in[i] | a.M;
+      p.seg_tr[i] = a.seg_tr[i] ? (even % 2 == 0 && al(a.seg_out[i], 4) ? 2 : 1) : 0; p.seg_pin[i] = a.seg_pin[i]; p.seg_pout[i] = a.seg_pout[i];
       p.seg_out[i] = (bf16_t*)a.seg_out[i]; p.seg_ld[i] = a.seg_ld[i]; p.seg_rows_out[i] = a.seg_rows_out[i];
       p.seg_row0[i] = a.seg_row0[i]; p.seg_rows_in[i] = a.seg_rows_in[i];
     }
