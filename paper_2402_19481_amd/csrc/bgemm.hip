@@ -44,7 +44,7 @@ struct Epi {
 // not fit the registers of a unit's second workgroup).
 template <int XA, bool LATE>
 __device__ __forceinline__ void xa_head(const WParams& p, int mt, int head, int g, int lane, const bf16x8 (&qf)[4],
-                                        const bf16x8 (&kf)[XA][4], const bf16x8 (&vpre)[2 * XA][2], const bf16x8* kv) {
+                                        const bf16x8 (&kf)[XA][4], const bf16x8 (*vpre)[2], const bf16x8* kv) {
   f32x16 sa[XA];
 #pragma unroll
   for (int kt = 0; kt < XA; ++kt) {
@@ -122,14 +122,15 @@ struct Direct {
 // loads, and from there to the waves without conflicts, since a fragment is in lane order.
 // What bounds it: a compute unit receives 25 - 33 bytes per cycle by direct loads (128 x 320 tile, K = 1280: 1750 cycles
 // per 64 of K by the loads alone, 1530 by the matrix instructions and LDS reads alone, 2230 together), so a tile is as fast
-// as its operand bytes per flop and the number of compute units that have one; then the epilogue (a quarter of the time at
+// as its operand bytes per flop and the number of compute units that have one; then the epilogue (with GEGLU a sixth of the time at
 // K = 1280), which in the smaller tiles runs beside the other workgroup of the unit.  Hence a set of tiles, from 64 x 64 to
 // 256 x 320 with 320 a divisor of most layers' widths, and the choice by predicted time below.  With the stages requested
 // in parts between the matrix instructions and the 320-wide tiles, 1024 x 10240 x 1280 with GEGLU 46.6 -> 36.3 us, 1800
 // x 10240 x 1280 68 -> 62, 4096 x 5120 x 640 43.5 -> 39.9, 14400 x 640 x 2560 with residual 78 -> 61.  Four waves of 64 x
 // 160 instead of eight of 32 x 160: 40 us (one wave per SIMD issues the epilogue half as fast).  With loads that leave the waits
 // for LDS reads exact (lds_load_buf): 1800 x 1280 x 5120 48.9 -> 41.4 us, 1800 x 3840 x 1280 30.4 -> 27.5, 4096 x 1280 x 1280 27.2
-// -> 24.7; 1800 x 10240 x 1280 with GEGLU, bound by its epilogue, 65 -> 64.
+// -> 24.7.  With the epilogue of a single k-group in the accumulators and its arguments requested early: 1024 x 10240 x 1280 with GEGLU
+// 35.4 -> 31.4 us, 1800 x 10240 x 1280 61 -> 53, 1024 x 3840 x 1280 split into queries, keys and values 20 -> 17.5.
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
 __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(WParams p) {
   using E = Epi<WT, WF, TT, TF, KG, OCC, LN>;
@@ -389,8 +390,8 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   // features of every fragment, which is the unit of the packed output.  The folded LayerNorm, rstd (x - mean s) + t, is a
   // product with rstd and then one v_mfma_f32_32x32x2_f32 per fragment, whose two k's are s x (-mean rstd) and t x 1 (a plain layer:
   // bias x 1): float throughout, on the matrix unit beside the vector ALU, which bounds these epilogues, and two LDS reads per
-  // fragment instead of four per eight values.  Through LDS as below, with the norm on the vector ALU, 1024 x 10240 x 1280 with GEGLU
-  // spent 11.1 us here.
+  // fragment instead of four per eight values.  4096 x 5120 x 640 with GEGLU (256 x 320 tile): 11.1 us of epilogue through LDS as below
+  // with the norm on the vector ALU, 5.2 now, which is what the vector ALU takes for the gates.
   if constexpr (KG == 1 && (EPI != EPI_XA || TF == 2)) {
     using D = Direct<WT, WF, TT, TF, LN, EPI == EPI_GEGLU>;
     constexpr bool kOdd = EPI == EPI_GEGLU && TF % 2;
@@ -454,113 +455,113 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     auto rows_out = [&](auto po) {
       constexpr bool packed_only = decltype(po)::value;  // (the step's GEGLU: short code, it is cold in every launch)
 #pragma unroll
-    for (int i = 0; i < TT; ++i) {
-      const int mt = mg * BT + wt * TT + i, m = mt * 32 + tok;
-      float rstd = 1.f, bm = g ? 1.f : 0.f;
-      if constexpr (LN) {
-        float sm = 0.f, sq = 0.f;
-#pragma unroll
-        for (int w = 0; w < WF; ++w) {
-          const float* q = s_part + ((w * BT + wt * TT + i) * 32 + tok) * 2;
-          sm += q[0]; sq += q[1];
-        }
-        const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
-        const float mean = sm * inv_k;
-        const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
-        rstd = __builtin_amdgcn_rsqf(var + p.ln_eps);
-        bm = g ? 1.f : -mean * rstd;
-      }
-      auto finish = [&](f32x16& a, int r) {            // tile row r: norm and shift, or bias
+      for (int i = 0; i < TT; ++i) {
+        const int mt = mg * BT + wt * TT + i, m = mt * 32 + tok;
+        float rstd = 1.f, bm = g ? 1.f : 0.f;
         if constexpr (LN) {
+          float sm = 0.f, sq = 0.f;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) a[e] *= rstd;
-        }
-        a = __builtin_amdgcn_mfma_f32_32x32x2f32(vec_of(r), bm, a, 0, 0, 0);
-      };
-      auto store = [&](int nt, int f, float* v) {
-        if (mt >= MT || nt >= NF) return;
-        const int n = nt * 32 + 16 * f + 8 * g;
-        if constexpr (!kResInit) {
-          if (p.residual && m < p.M) {
-            float r8[8];
-            ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] += r8[q];
+          for (int w = 0; w < WF; ++w) {
+            const float* q = s_part + ((w * BT + wt * TT + i) * 32 + tok) * 2;
+            sm += q[0]; sq += q[1];
           }
+          const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+          const float mean = sm * inv_k;
+          const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
+          rstd = __builtin_amdgcn_rsqf(var + p.ln_eps);
+          bm = g ? 1.f : -mean * rstd;
         }
-        wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
-      };
-      if constexpr (EPI == EPI_GEGLU) {
-        if (mt >= MT) continue;
-        auto unit = [&](int nt, int f, const f32x16& a, const f32x16& gt) {
-          if (nt >= NF) return;
-          float v[8];
+        auto finish = [&](f32x16& a, int r) {            // tile row r: norm and shift, or bias
+          if constexpr (LN) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) v[q] = a[8 * f + q] * gelu_erf(gt[8 * f + q]);
-          if (packed_only) st_vec(p.out_packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
-          else store(nt, f, v);
+            for (int e = 0; e < 16; ++e) a[e] *= rstd;
+          }
+          a = __builtin_amdgcn_mfma_f32_32x32x2f32(vec_of(r), bm, a, 0, 0, 0);
         };
+        auto store = [&](int nt, int f, float* v) {
+          if (mt >= MT || nt >= NF) return;
+          const int n = nt * 32 + 16 * f + 8 * g;
+          if constexpr (!kResInit) {
+            if (p.residual && m < p.M) {
+              float r8[8];
+              ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
 #pragma unroll
-        for (int j = 0; j < HP; ++j) {
-          finish(acc[i][j], wf * TF + j);
-          finish(acc[i][TF - HP + j], wf * TF + TF - HP + j);
-#pragma unroll
-          for (int f = 0; f < 2; ++f) unit(ng * BFO + wf * (TF - HP) + j, f, acc[i][j], acc[i][TF - HP + j]);
-        }
-        if constexpr (kOdd) {
-          const f32x4* d = xch + (((1 - wf) * BT + wt * TT + i) * 2) * 64 + lane;
-          const f32x4 lo = d[0], hi = d[64];
-          f32x16 o;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) o[e] = (e & 4 ? hi : lo)[e & 3];
-          finish(acc[i][HP], wf * TF + HP);
-          finish(o, (1 - wf) * TF + HP);
-          if (wf == 0) unit(ng * BFO + HP, 0, acc[i][HP], o);
-          else unit(ng * BFO + HP, 1, o, acc[i][HP]);
-        }
-      } else if constexpr (EPI == EPI_XA) {
-        finish(acc[i][0], wf * TF);
-        finish(acc[i][1], wf * TF + 1);
-        const int head = ng * WF + wf;
-        if (mt >= MT || head * 2 >= NF) continue;
-        // the head's normalised, rounded query is the B operand of S^T = K Q^T
-        bf16x8 qf[4];
-#pragma unroll
-        for (int ds = 0; ds < 4; ++ds) {
-          const f32x16& a = acc[i][ds >> 1];
-          const int e = 8 * (ds & 1);
-          qf[ds] = __builtin_bit_cast(bf16x8, u32x4{pack_bf2(a[e], a[e + 1]), pack_bf2(a[e + 2], a[e + 3]), pack_bf2(a[e + 4], a[e + 5]),
-                                                    pack_bf2(a[e + 6], a[e + 7])});
-        }
-        xa_head<XA, (OCC > 1)>(p, mt, head, g, lane, qf, xkf, xvf, kv);
-      } else if constexpr (EPI == EPI_QKV) {
-#pragma unroll
-        for (int j = 0; j < TF; ++j) {
-          finish(acc[i][j], wf * TF + j);
-          const int nt = ng * BF + wf * TF + j;
-          if (mt >= MT || nt >= NF) continue;
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
-            float v[8];
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
-            wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+              for (int q = 0; q < 8; ++q) v[q] += r8[q];
+            }
           }
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < TF; ++j) {
-          finish(acc[i][j], wf * TF + j);
-#pragma unroll
-          for (int f = 0; f < 2; ++f) {
+          wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+        };
+        if constexpr (EPI == EPI_GEGLU) {
+          if (mt >= MT) continue;
+          auto unit = [&](int nt, int f, const f32x16& a, const f32x16& gt) {
+            if (nt >= NF) return;
             float v[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
-            store(ng * BF + wf * TF + j, f, v);
+            for (int q = 0; q < 8; ++q) v[q] = a[8 * f + q] * gelu_erf(gt[8 * f + q]);
+            if (packed_only) st_vec(p.out_packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
+            else store(nt, f, v);
+          };
+#pragma unroll
+          for (int j = 0; j < HP; ++j) {
+            finish(acc[i][j], wf * TF + j);
+            finish(acc[i][TF - HP + j], wf * TF + TF - HP + j);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) unit(ng * BFO + wf * (TF - HP) + j, f, acc[i][j], acc[i][TF - HP + j]);
+          }
+          if constexpr (kOdd) {
+            const f32x4* d = xch + (((1 - wf) * BT + wt * TT + i) * 2) * 64 + lane;
+            const f32x4 lo = d[0], hi = d[64];
+            f32x16 o;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) o[e] = (e & 4 ? hi : lo)[e & 3];
+            finish(acc[i][HP], wf * TF + HP);
+            finish(o, (1 - wf) * TF + HP);
+            if (wf == 0) unit(ng * BFO + HP, 0, acc[i][HP], o);
+            else unit(ng * BFO + HP, 1, o, acc[i][HP]);
+          }
+        } else if constexpr (EPI == EPI_XA) {
+          finish(acc[i][0], wf * TF);
+          finish(acc[i][1], wf * TF + 1);
+          const int head = ng * WF + wf;
+          if (mt >= MT || head * 2 >= NF) continue;
+          // the head's normalised, rounded query is the B operand of S^T = K Q^T
+          bf16x8 qf[4];
+#pragma unroll
+          for (int ds = 0; ds < 4; ++ds) {
+            const f32x16& a = acc[i][ds >> 1];
+            const int e = 8 * (ds & 1);
+            qf[ds] = __builtin_bit_cast(bf16x8, u32x4{pack_bf2(a[e], a[e + 1]), pack_bf2(a[e + 2], a[e + 3]), pack_bf2(a[e + 4], a[e + 5]),
+                                                      pack_bf2(a[e + 6], a[e + 7])});
+          }
+          xa_head<XA, (OCC > 1)>(p, mt, head, g, lane, qf, xkf, xvf, kv);
+        } else if constexpr (EPI == EPI_QKV) {
+#pragma unroll
+          for (int j = 0; j < TF; ++j) {
+            finish(acc[i][j], wf * TF + j);
+            const int nt = ng * BF + wf * TF + j;
+            if (mt >= MT || nt >= NF) continue;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              float v[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
+              wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int j = 0; j < TF; ++j) {
+            finish(acc[i][j], wf * TF + j);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+              float v[8];
+#pragma unroll
+              for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
+              store(ng * BF + wf * TF + j, f, v);
+            }
           }
         }
       }
-    }
     };
     if (EPI == EPI_GEGLU && p.out_packed && !p.out_f32 && !p.out_rows && !p.residual) rows_out(std::true_type{});
     else rows_out(std::false_type{});
@@ -668,8 +669,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
           const u32x4 qv = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]), pack_bf2(v[4], v[5]), pack_bf2(v[6], v[7])};
           qf[ds] = __builtin_bit_cast(bf16x8, qv);
         }
-        const bf16x8 none[2 * XA][2] = {};
-        xa_head<XA, true>(p, mt, head, g, lane, qf, kf, none, kv);
+        xa_head<XA, true>(p, mt, head, g, lane, qf, kf, nullptr, kv);
       }
     } else {
       // items (token row, output fragment, half of the row's tokens): lane -> token it*16 + lane%16, features 8*(lane/16) ..
@@ -821,23 +821,25 @@ namespace {
 // (GEGLU, QKV, plain / residual, fused cross-attention), `base` those of a launch, `alone` the round of a workgroup that
 // has a unit to itself where two would fit, `kf` the k-fragments of a stage; fitted to 38 token counts x 8 layers with weights
 // that no cache holds.  Chosen by them (and the wave-level kernel's, see wgemm.hip), those layers take 1.3 % more than with the
-// best of 18 shapes.  The 96-, 160- and 192-wide tiles and 256 x 256 are there because a round of workgroups over 256 units is
+// best of 18 shapes.  The columns of GEGLU, QKV and cross-attention are from after the epilogues in the accumulators: GEGLU layers of 256 -
+// 7200 tokens (18 counts x 2) take 1.4 % more than with the best of the nine shapes that have it, QKV and cross-attention layers in the
+// step (7 images x 2 levels) were fitted to the step's time.  The 96-, 160- and 192-wide tiles and 256 x 256 are there because a round of workgroups over 256 units is
 // rarely full: 7200 x 640 x 2560 44.9 -> 33.2 us, 4096 x 1280 x 1280 28.8 -> 24.7, 1976 x 640 x 2560 23.3 -> 18.1, 4096 x 3840 x
 // 1280 55.7 -> 44.2, 494 x 10240 x 1280 with GEGLU 27.3 -> 24.7, 1024 x 1280 x 1280 12.7 -> 12.0.
 struct TileCfg { int bt, bf, occ, kf; double base, slab, epi[4], alone; };
 constexpr TileCfg kTiles[] = {
-    {8, 10, 1, 2, 1.51, 1.886, {13.8, 28.6, 19.2, 1e9}, 1.0},     // 256 x 320, eight waves of 64 x 160
-    {4, 4, 2, 4, 3.00, 0.982, {4.7, 5.7, 8.0, 7.4}, 0.71},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
-    {4, 4, 1, 4, 1.59, 0.468, {5.0, 7.1, 6.5, 8.4}, 1.0},         // 128 x 128, four ring stages
-    {2, 4, 2, 4, 3.11, 0.602, {3.4, 5.7, 4.8, 8.3}, 0.63},        // 64 x 128, two k-groups, two workgroups per unit
-    {2, 2, 2, 8, 2.52, 0.407, {1e9, 3.3, 2.4, 7.3}, 0.78},        // 64 x 64, two k-groups, two workgroups per unit
-    {2, 2, 1, 8, 2.31, 0.224, {1e9, 3.0, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128
-    {4, 10, 1, 2, 1.43, 1.056, {9.0, 15.4, 13.3, 1e9}, 1.0},      // 128 x 320, eight waves of 32 x 160
-    {2, 3, 1, 8, 2.83, 0.281, {1e9, 4.6, 3.2, 1e9}, 1.0},         // 64 x 96, four k-groups of 32 x 96
-    {4, 5, 1, 4, 1.88, 0.551, {1e9, 11.0, 8.6, 1e9}, 1.0},        // 128 x 160, two k-groups of 32 x 160
-    {8, 8, 1, 2, 1.04, 1.429, {12.9, 24.0, 17.7, 1e9}, 1.0},      // 256 x 256, eight waves of 64 x 128
-    {4, 3, 1, 4, 2.11, 0.412, {1e9, 7.0, 5.1, 1e9}, 1.0},         // 128 x 96, two k-groups of 32 x 96
-    {4, 6, 1, 2, 2.24, 0.690, {6.7, 10.5, 7.6, 1e9}, 1.0},        // 128 x 192, eight waves of 32 x 96
+    {8, 10, 1, 2, 1.51, 1.886, {8.5, 28.6, 19.2, 1e9}, 1.0},      // 256 x 320, eight waves of 64 x 160
+    {4, 4, 2, 4, 3.00, 0.982, {2.2, 3.6, 8.0, 3.2}, 0.71},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
+    {4, 4, 1, 4, 1.59, 0.468, {4.0, 3.6, 6.5, 6.0}, 1.0},         // 128 x 128, four ring stages
+    {2, 4, 2, 4, 3.11, 0.602, {3.4, 3.0, 4.8, 8.3}, 0.63},        // 64 x 128, two k-groups, two workgroups per unit
+    {2, 2, 2, 8, 2.52, 0.407, {1e9, 2.9, 2.4, 7.3}, 0.78},        // 64 x 64, two k-groups, two workgroups per unit
+    {2, 2, 1, 8, 2.31, 0.224, {1e9, 2.8, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128
+    {4, 10, 1, 2, 1.43, 1.056, {6.0, 7.5, 13.3, 1e9}, 1.0},       // 128 x 320, eight waves of 32 x 160
+    {2, 3, 1, 8, 2.83, 0.281, {1e9, 4.3, 3.2, 1e9}, 1.0},         // 64 x 96, four k-groups of 32 x 96
+    {4, 5, 1, 4, 1.88, 0.551, {1e9, 9.5, 8.6, 1e9}, 1.0},         // 128 x 160, two k-groups of 32 x 160
+    {8, 8, 1, 2, 1.04, 1.429, {8.5, 10.0, 17.7, 1e9}, 1.0},       // 256 x 256, eight waves of 64 x 128
+    {4, 3, 1, 4, 2.11, 0.412, {1e9, 4.5, 5.1, 1e9}, 1.0},         // 128 x 96, two k-groups of 32 x 96
+    {4, 6, 1, 2, 2.24, 0.690, {5.3, 8.0, 7.6, 1e9}, 1.0},         // 128 x 192, eight waves of 32 x 96
 };
 
 }  // namespace
