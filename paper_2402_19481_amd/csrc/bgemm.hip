@@ -145,7 +145,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   static_assert(EPI != EPI_QKV || LN, "the segmented epilogue applies the folded LayerNorm");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.group_m), "s"(p.residual), "s"(p.ldr));
+  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.group_m), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tok = lane & 31, g = lane >> 5;
@@ -247,10 +247,12 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         f32x4 r[4];
 #pragma unroll
         for (int f = 0; f < 4; ++f) r[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (m < p.M && nt < NF) {
-          const float* rp = p.residual + (long long)m * p.ldr + nt * 32 + 8 * g;
+        if ((p.res_frag ? m < MT * 32 : m < p.M) && nt < NF) {
+          int next;
+          const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, m >> 5, m, nt * 32, 8 * g, lane, &next);
+          const int half = p.res_frag ? 512 : 16;      // from the first eight features to the others
 #pragma unroll
-          for (int f = 0; f < 4; ++f) r[f] = *reinterpret_cast<const f32x4*>(rp + 16 * (f >> 1) + 4 * (f & 1));
+          for (int f = 0; f < 4; ++f) r[f] = *reinterpret_cast<const f32x4*>(rp + half * (f >> 1) + next * (f & 1));
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[i][j][e] = r[e >> 2][e & 3];
@@ -385,6 +387,15 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     return;
   }
 
+  auto add_residual = [&](int mt, int m, int n0, int fo, int ln, float* v) {
+    int next;
+    const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, n0, fo, ln, &next);
+    float r8[8];
+    ld_vec(rp, r8); ld_vec(rp + next, r8 + 4);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] += r8[q];
+  };
+
   // ---- epilogue: the operand ring is free ----
   // One k-group: a wave finishes its own tile where it stands, in the accumulators.  A lane holds one token's 2 x 8 consecutive
   // features of every fragment, which is the unit of the packed output.  The folded LayerNorm, rstd (x - mean s) + t, is a
@@ -480,14 +491,8 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         };
         auto store = [&](int nt, int f, float* v) {
           if (mt >= MT || nt >= NF) return;
-          const int n = nt * 32 + 16 * f + 8 * g;
           if constexpr (!kResInit) {
-            if (p.residual && m < p.M) {
-              float r8[8];
-              ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
-#pragma unroll
-              for (int q = 0; q < 8; ++q) v[q] += r8[q];
-            }
+            if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * g, lane, v);
           }
           wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
         };
@@ -689,14 +694,9 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 #pragma unroll
           for (int q = 0; q < 8; ++q) v[q] *= gelu_erf(gt[q]);
         }
-        const int m = mt * 32 + tk, n = nt * 32 + 16 * f + 8 * gg;
+        const int m = mt * 32 + tk;
         if constexpr (!kResInit) {
-          if (p.residual && m < p.M) {
-            float r8[8];
-            ld_vec(p.residual + (long long)m * p.ldr + n, r8); ld_vec(p.residual + (long long)m * p.ldr + n + 4, r8 + 4);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] += r8[q];
-          }
+          if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
         }
         wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
       }
@@ -710,7 +710,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 template <int NP>
 __global__ __launch_bounds__(256) void bgemm_sum_kernel(WParams p) {
   asm volatile("" ::"s"(p.partials), "s"(p.M), "s"(p.N), "s"(p.bias), "s"(p.residual), "s"(p.ldr), "s"(p.out_f32), "s"(p.ldo), "s"(p.out_packed),
-               "s"(p.out_rows), "s"(p.nseg));              // (one batch of argument loads, see wgemm.hip)
+               "s"(p.out_rows), "s"(p.nseg), "s"(p.res_frag), "s"(p.f32_frag));   // (one batch of argument loads, see wgemm.hip)
   const int MT = (p.M + 31) >> 5, NF = p.N >> 5, lane = threadIdx.x & 63;
   const int u = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (u >= MT * NF * 2) return;
@@ -729,9 +729,11 @@ __global__ __launch_bounds__(256) void bgemm_sum_kernel(WParams p) {
     ba = *reinterpret_cast<const f32x4*>(p.bias + n);
     bb = *reinterpret_cast<const f32x4*>(p.bias + n + 4);
   }
-  if (p.residual && m < p.M) {
-    a = *reinterpret_cast<const f32x4*>(p.residual + (long long)m * p.ldr + n);
-    b = *reinterpret_cast<const f32x4*>(p.residual + (long long)m * p.ldr + n + 4);
+  if (p.residual && (m < p.M || p.res_frag)) {
+    int next;
+    const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, nt * 32, 16 * f + 8 * (lane >> 5), lane, &next);
+    a = *reinterpret_cast<const f32x4*>(rp);
+    b = *reinterpret_cast<const f32x4*>(rp + next);
   }
 #pragma unroll
   for (int i = 0; i < NP; ++i) {

@@ -132,6 +132,7 @@ struct WGemmArgs {
   long long ldr;
   float* out_f32;         // row-major [M, N'] float, row stride ldo, or nullptr
   long long ldo;
+  int res_frag, f32_frag; // not 0: residual / out_f32 is in fragments (below) instead of row-major
   void* out_packed;       // packed bf16 [M, N'] (the next layer's activation operand), or nullptr
   void* out_rows;         // row-major bf16 [M, N'], row stride ld_rows, or nullptr
   long long ld_rows;

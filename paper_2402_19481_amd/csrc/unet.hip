@@ -562,8 +562,10 @@ struct Exec {
 
 
   // Linear layer on fragment-packed operands (wgemm.hip); `ln` applies the folded LayerNorm of that weight.
+  // `frag`: the residual (kResFrag) and the float output (kOutFrag) are in fragments, row-major otherwise.
+  enum { kResFrag = 1, kOutFrag = 2 };
   void wg(const bf16_t* Xp, const std::string& wn, bool bias, bool ln, const float* residual, float* out_f32,
-          bf16_t* out_packed, bf16_t* out_rows, long long ld_rows, int M, int Nn, int K, const WGemmArgs* extra = nullptr) {
+          bf16_t* out_packed, bf16_t* out_rows, long long ld_rows, int M, int Nn, int K, const WGemmArgs* extra = nullptr, int frag = 0) {
     if (!ln && !extra) {
       const size_t need = wgemm_scratch_bytes(M, Nn);
       if (need > scratch_need) scratch_need = need;
@@ -579,6 +581,7 @@ struct Exec {
     else if (bias) g.bias = (const float*)weight(wn + ".b");
     const int No = g.geglu ? g.geglu : Nn;
     g.residual = residual; g.ldr = No; g.out_f32 = out_f32; g.ldo = No; g.out_packed = out_packed;
+    g.res_frag = frag & kResFrag; g.f32_frag = frag & kOutFrag;
     g.out_rows = out_rows; g.ld_rows = ld_rows;
     const double ob = (out_f32 ? 4.0 : 0.0) + (out_packed ? 2.0 : 0.0) + ((out_rows || g.nseg) ? 2.0 : 0.0);
     label = "linear_packed " + dims({M, Nn, K}) + (g.geglu ? " geglu" : "") + (ln ? " ln" : "") + (g.nseg ? " qkv" : "");
@@ -603,7 +606,7 @@ struct Exec {
     const float scale = 1.0f / sqrtf((float)c.head_dim);
     const size_t pC = packed_rows_bytes(M, C);
     bf16_t* nbp = (bf16_t*)alloc(pC);                       // GroupNorm output
-    float* h = (float*)alloc((size_t)M * C * 4);            // hidden state (residual stream), row-major
+    float* h = (float*)alloc(2 * pC);                       // hidden state (residual stream), fragments of floats
     bf16_t* hp = (bf16_t*)alloc(pC);                        // its bf16 copy, packed
     bf16_t* qkv = (bf16_t*)alloc((size_t)M * 3 * C * 2);    // row-major queries (and fresh K/V without refresh)
     bf16_t* aop = (bf16_t*)alloc(pC);                       // attention output, packed
@@ -615,7 +618,7 @@ struct Exec {
       vs_tmp = (bf16_t*)alloc((size_t)B() * C * Lpad * 2);
     }
     groupnorm(b.name + ".gn", x, DF_F32, R, W, C, 1e-6f, 0, nbp, 1);
-    wg(nbp, b.name + ".pin", true, false, nullptr, h, hp, nullptr, 0, M, C, C);
+    wg(nbp, b.name + ".pin", true, false, nullptr, b.depth ? h : nullptr, hp, nullptr, 0, M, C, C, nullptr, kOutFrag);
     for (int d = 0; d < b.depth; ++d) {
       const std::string p = b.name + ".b" + std::to_string(d);
       bf16_t* ks = (bf16_t*)stale_buf(p + ".attn1.k", (size_t)B() * L * C * 2);
@@ -669,7 +672,7 @@ struct Exec {
         timed(PC_SELF_ATTN, 4.0 * M * L * C, 2.0 * (2.0 * M * C + 2.0 * B() * L * C),
               [&] { return launch_attention(a, st); });
       }
-      wg(aop, p + ".attn1.o", true, false, h, h, hp, nullptr, 0, M, C, C);
+      wg(aop, p + ".attn1.o", true, false, h, h, hp, nullptr, 0, M, C, C, nullptr, kResFrag | kOutFrag);
       // cross-attention to the text tokens
       const long long kvld = (long long)kv_count[b.level] * 2 * C;
       const int kvi = kv_cursor[b.level];
@@ -711,14 +714,15 @@ struct Exec {
                 [&] { return launch_attention(a, st); });
         }
       }
-      wg(aop, p + ".attn2.o", true, false, h, h, hp, nullptr, 0, M, C, C);
+      wg(aop, p + ".attn2.o", true, false, h, h, hp, nullptr, 0, M, C, C, nullptr, kResFrag | kOutFrag);
       // GEGLU feed-forward
       {
         WGemmArgs ex = {};
         ex.geglu = 4 * C;
         wg(hp, p + ".ff1", false, true, nullptr, nullptr, fgp, nullptr, 0, M, 8 * C, C, &ex);
       }
-      wg(fgp, p + ".ff2", true, false, h, h, hp, nullptr, 0, M, C, 4 * C);
+      // (behind the last block only the packed copy is read)
+      wg(fgp, p + ".ff2", true, false, h, d + 1 < b.depth ? h : nullptr, hp, nullptr, 0, M, C, 4 * C, nullptr, kResFrag | kOutFrag);
     }
     wg(hp, b.name + ".pout", true, false, x, out, nullptr, nullptr, 0, M, C, C);
   }

@@ -17,6 +17,7 @@ struct WParams {
   long long ldr;
   float* out_f32;
   long long ldo;
+  int res_frag, f32_frag;
   bf16_t* out_packed;
   bf16_t* out_rows;
   long long ld_rows;
@@ -56,6 +57,16 @@ __device__ __forceinline__ WSegment wg_segment(const WParams& p, int n0) {
           s1 ? 1.0f : p.seg0_scale};
 }
 
+// Eight consecutive floats of a unit (see wg_store_unit) of the residual or the float output: the first four, and how far on the others
+// are.  Row-major, or in fragments [token row][feature row][4][64 lanes] of four, quarter 2 f + h of a fragment holding
+// features 16 f + 8 (lane / 32) + 4 h .. of token lane % 32: the accumulators' own order, a kilobyte per access where a row-major one
+// touches a line for every lane (the address unit takes one a cycle: 64 cycles against 16).
+template <typename T>
+__device__ __forceinline__ T* wg_float_unit(T* base, int frag, long long ld, int N, int mt, int m, int n0, int fo, int lane, int* next) {
+  *next = frag ? 256 : 4;
+  return frag ? base + (((size_t)mt * (N >> 5) + (n0 >> 5)) * 4 + 2 * (fo >> 4)) * 256 + lane * 4 : base + (long long)m * ld + n0 + fo;
+}
+
 // One output unit: features n0 + fo .. + 7 of token m, written in every requested form.  n0 is uniform, the first of a fragment; `lane`
 // is the lane of that token and feature group in the packed layout (m % 32 + 32 (fo / 8 % 2)); lane ^ 1 of the wave holds token m ^ 1.
 __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, int n0, int fo, int lane, const float* v) {
@@ -91,9 +102,11 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
     }
     return;
   }
-  if (p.out_f32 && row_ok) {
-    st_vec(p.out_f32 + (long long)m * p.ldo + n, v);
-    st_vec(p.out_f32 + (long long)m * p.ldo + n + 4, v + 4);
+  if (p.out_f32 && (row_ok || p.f32_frag)) {
+    int next;
+    float* o = wg_float_unit(p.out_f32, p.f32_frag, p.ldo, p.N, mt, m, n0, fo, lane, &next);
+    st_vec(o, v);
+    st_vec(o + next, v + 4);
   }
   if (p.out_packed) {
     // fragment (mt, n/16) of the [M, N] result as the next layer's activation operand; padded token rows are
@@ -107,7 +120,7 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
 // Every argument that an epilogue needs is requested while the first operands are on their way: fetched where it is first used, a
 // batch of them costs that epilogue a round trip to memory (they are cold in every launch).
 __device__ __forceinline__ void wg_request_outputs(const WParams& p) {
-  asm volatile("" ::"s"(p.out_f32), "s"(p.ldo), "s"(p.out_packed), "s"(p.out_rows), "s"(p.ld_rows), "s"(p.nseg), "s"(p.ln_eps));
+  asm volatile("" ::"s"(p.out_f32), "s"(p.ldo), "s"(p.f32_frag), "s"(p.out_packed), "s"(p.out_rows), "s"(p.ld_rows), "s"(p.nseg), "s"(p.ln_eps));
 }
 __device__ __forceinline__ void wg_request_segments(const WParams& p) {
   asm volatile("" ::"s"(p.seg_w), "s"(p.seg_out[0]), "s"(p.seg_out[1]), "s"(p.seg_out[2]), "s"(p.seg_ld[0]), "s"(p.seg_ld[1]), "s"(p.seg_ld[2]),

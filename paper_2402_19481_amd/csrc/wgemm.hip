@@ -56,7 +56,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // code starts, and the prologue of these few-microsecond kernels became a chain of four or five dependent round
   // trips to the scalar cache.
   asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.bias), "s"(p.ln_s), "s"(p.ln_t),
-               "s"(p.residual), "s"(p.ldr), "s"(p.geglu));
+               "s"(p.residual), "s"(p.ldr), "s"(p.geglu), "s"(p.res_frag));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the k-walk and tile addresses stay off the vector ALU
   const int tok = lane & 31, g = lane >> 5;
@@ -134,9 +134,10 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int j = p.geglu ? (pu >> 1) % GP : (pu >> 1) % TN;          // compile-time divisors (JO is a run-time value)
     const int mt = mg * TM + i0 + (p.geglu ? (pu >> 1) / GP : (pu >> 1) / TN);
     const int m = mt * 32 + tok;
-    const int n = (ng * JO + j) * 32 + 16 * f + 8 * g;
-    if (!PART && p.residual && m < p.M) {
-      ld_vec(p.residual + (long long)m * p.ldr + n, e.r); ld_vec(p.residual + (long long)m * p.ldr + n + 4, e.r + 4);
+    if (!PART && p.residual && (p.res_frag ? mt < MT : m < p.M)) {
+      int next;
+      const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, (ng * JO + j) * 32, 16 * f + 8 * g, lane, &next);
+      ld_vec(rp, e.r); ld_vec(rp + next, e.r + 4);
     }
   };
   constexpr int MAXU = (RP * TN * 2 + KSPLIT - 1) / KSPLIT;   // pair units of a pass per wave
@@ -339,7 +340,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       continue;
     }
     const bool row_ok = m < p.M;
-    if (p.residual && row_ok) {
+    if (p.residual && (row_ok || p.res_frag)) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += e.r[q];
     }
@@ -618,7 +619,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   WParams p = {};
   p.Xp = (const bf16x8*)a.Xp; p.Wp = (const bf16x8*)a.Wp; p.M = a.M; p.N = Nout; p.K = a.K;
   p.bias = a.bias; p.ln_s = a.ln_s; p.ln_t = a.ln_t; p.ln_eps = a.ln_eps; p.residual = a.residual; p.ldr = a.ldr;
-  p.out_f32 = a.out_f32; p.ldo = a.ldo; p.out_packed = (bf16_t*)a.out_packed; p.out_rows = (bf16_t*)a.out_rows;
+  p.out_f32 = a.out_f32; p.ldo = a.ldo; p.res_frag = a.res_frag; p.f32_frag = a.f32_frag; p.out_packed = (bf16_t*)a.out_packed; p.out_rows = (bf16_t*)a.out_rows;
   p.ld_rows = a.ld_rows; p.geglu = a.geglu ? 1 : 0; p.parts = 1;
   if (a.nseg > 0) {
     if (a.nseg > 3 || a.seg_w % 32 || a.seg_w * a.nseg != a.N || a.geglu) return DF_ESHAPE;
