@@ -308,10 +308,12 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
   using I2 = std::integral_constant<int, 2>;
   using All = std::integral_constant<int, -1>;
+  constexpr bool SEG = EPI == EPI_QKV;
+  WOut out = {};
   auto request_args = [&] {                            // (behind the first loads)
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (EPI == EPI_QKV) wg_request_segments(p);
-    else if constexpr (EPI != EPI_PART) wg_request_outputs(p);
+    if constexpr (EPI != EPI_PART && EPI != EPI_XA) out = wg_outputs<SEG>(p);
+    if constexpr (EPI == EPI_XA) asm volatile("" ::"s"(p.out_packed), "s"(p.ln_eps), "s"(p.xkv), "s"(p.xa_rows), "s"(p.xa_bstride));
   };
   if constexpr (ST >= 4) {
     // Stage kt + ST - 1 is requested in parts between the matrix instructions of stage kt
@@ -494,7 +496,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
           if constexpr (!kResInit) {
             if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * g, lane, v);
           }
-          wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+          wg_store_unit<SEG>(p, out, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
         };
         if constexpr (EPI == EPI_GEGLU) {
           if (mt >= MT) continue;
@@ -503,7 +505,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
             float v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = a[8 * f + q] * gelu_erf(gt[8 * f + q]);
-            if (packed_only) st_vec(p.out_packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
+            if (packed_only) st_vec(out.packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
             else store(nt, f, v);
           };
 #pragma unroll
@@ -550,7 +552,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
               float v[8];
 #pragma unroll
               for (int q = 0; q < 8; ++q) v[q] = acc[i][j][8 * f + q];
-              wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+              wg_store_unit<SEG>(p, out, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
             }
           }
         } else {
@@ -568,7 +570,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         }
       }
     };
-    if (EPI == EPI_GEGLU && p.out_packed && !p.out_f32 && !p.out_rows && !p.residual) rows_out(std::true_type{});
+    if (EPI == EPI_GEGLU && out.packed && !out.f32 && !out.rows && !p.residual) rows_out(std::true_type{});
     else rows_out(std::false_type{});
     return;
   }
@@ -698,7 +700,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         if constexpr (!kResInit) {
           if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
         }
-        wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
+        wg_store_unit<SEG>(p, out, mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
       }
     }
   }
@@ -745,7 +747,7 @@ __global__ __launch_bounds__(256) void bgemm_sum_kernel(WParams p) {
     b += bb;
   }
   const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  wg_store_unit(p, mt, m, nt * 32, 16 * f + 8 * (lane >> 5), lane, v);
+  wg_store_unit<false>(p, wg_outputs<false>(p), mt, m, nt * 32, 16 * f + 8 * (lane >> 5), lane, v);
 }
 
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>

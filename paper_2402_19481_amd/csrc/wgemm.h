@@ -37,6 +37,8 @@ struct WParams {
   float xa_scale;
   f32x4* partials;      // bgemm with `parts` > 1 parts of K: their sums
   int parts;
+  int mgroups, kfw;     // wgemm: groups of token rows, k-fragments of a wave, and the reciprocals of both
+  unsigned int mg_magic, kfw_magic;
   int group_m;          // bgemm: token tiles of a panel in the tile order (see there)
 };
 
@@ -57,6 +59,36 @@ __device__ __forceinline__ WSegment wg_segment(const WParams& p, int n0) {
           s1 ? 1.0f : p.seg0_scale};
 }
 
+// What the epilogues need of the arguments is requested while the first operands are on their way: fetched where it is first used, a
+// batch of them costs that epilogue a round trip to memory (they are cold in every launch).  The outputs stay in registers from here on
+// (left alone, the compiler fetches them again); the segments' are too many for that and come from the scalar cache later.
+struct WOut {
+  float* f32;
+  bf16_t *packed, *rows;
+  long long ldo, ld_rows;
+  int f32_frag;
+};
+template <typename T>
+__device__ __forceinline__ T wg_pin(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+template <bool SEG>
+__device__ __forceinline__ WOut wg_outputs(const WParams& p) {
+  WOut o = {};
+  if constexpr (SEG) {
+    asm volatile("" ::"s"(p.seg_w), "s"(p.seg_out[0]), "s"(p.seg_out[1]), "s"(p.seg_out[2]), "s"(p.seg_ld[0]), "s"(p.seg_ld[1]), "s"(p.seg_ld[2]),
+                 "s"(p.seg_rows_out[0]), "s"(p.seg_rows_out[1]), "s"(p.seg_rows_out[2]));
+    asm volatile("" ::"s"(p.seg_row0[0]), "s"(p.seg_row0[1]), "s"(p.seg_row0[2]), "s"(p.seg_rows_in[0]), "s"(p.seg_rows_in[1]), "s"(p.seg_rows_in[2]),
+                 "s"(p.seg_tr[0]), "s"(p.seg_tr[1]), "s"(p.seg_tr[2]), "s"(p.seg_pin[0]), "s"(p.seg_pin[1]), "s"(p.seg_pin[2]),
+                 "s"(p.seg_pout[0]), "s"(p.seg_pout[1]), "s"(p.seg_pout[2]), "s"(p.seg0_scale));
+  } else {
+    o.f32 = wg_pin(p.out_f32); o.ldo = wg_pin(p.ldo); o.f32_frag = wg_pin(p.f32_frag);
+    o.packed = wg_pin(p.out_packed); o.rows = wg_pin(p.out_rows); o.ld_rows = wg_pin(p.ld_rows);
+  }
+  return o;
+}
+
 // Eight consecutive floats of a unit (see wg_store_unit) of the residual or the float output: the first four, and how far on the others
 // are.  Row-major, or in fragments [token row][feature row][4][64 lanes] of four, quarter 2 f + h of a fragment holding
 // features 16 f + 8 (lane / 32) + 4 h .. of token lane % 32: the accumulators' own order, a kilobyte per access where a row-major one
@@ -69,10 +101,11 @@ __device__ __forceinline__ T* wg_float_unit(T* base, int frag, long long ld, int
 
 // One output unit: features n0 + fo .. + 7 of token m, written in every requested form.  n0 is uniform, the first of a fragment; `lane`
 // is the lane of that token and feature group in the packed layout (m % 32 + 32 (fo / 8 % 2)); lane ^ 1 of the wave holds token m ^ 1.
-__device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, int n0, int fo, int lane, const float* v) {
+template <bool SEG>
+__device__ __forceinline__ void wg_store_unit(const WParams& p, const WOut& o, int mt, int m, int n0, int fo, int lane, const float* v) {
   const bool row_ok = m < p.M;
   const int n = n0 + fo;
-  if (p.nseg > 0) {
+  if constexpr (SEG) {
     const WSegment s = wg_segment(p, n0);
     const int mp = s.tr > 1 ? m & ~1 : m;
     const int bi = mp < s.rows_in ? 0 : mp / s.rows_in;   // (usually one batch item: a comparison instead of a division)
@@ -80,20 +113,20 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
     if (s.tr > 1) {
       // feature-major, token pairs stay together and aligned (launcher): neighbouring lanes exchange, the even one keeps feature 2q of
       // both tokens and the odd one 2q + 1; a store covers the 32 tokens of four features
-      bf16_t* o = s.out + ((long long)bi * p.seg_w + (n - s.first) + (m & 1)) * s.ld + pos;
+      bf16_t* d = s.out + ((long long)bi * p.seg_w + (n - s.first) + (m & 1)) * s.ld + pos;
       const unsigned int sel = m & 1 ? 0x07060302u : 0x01000504u;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const unsigned int u = pack_bf2(v[2 * q], v[2 * q + 1]);
         const unsigned int w = (unsigned int)__builtin_amdgcn_update_dpp(0, (int)u, 0xb1, 0xf, 0xf, true);   // lane ^ 1
         const unsigned int x = __builtin_amdgcn_perm(u, w, sel);
-        if (row_ok) *reinterpret_cast<unsigned int*>(o + 2 * q * s.ld) = x;
+        if (row_ok) *reinterpret_cast<unsigned int*>(d + 2 * q * s.ld) = x;
       }
     } else if (s.tr) {
-      bf16_t* o = s.out + ((long long)bi * p.seg_w + (n - s.first)) * s.ld + pos;
+      bf16_t* d = s.out + ((long long)bi * p.seg_w + (n - s.first)) * s.ld + pos;
       if (row_ok) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) o[q * s.ld] = f2bf(v[q]);
+        for (int q = 0; q < 8; ++q) d[q * s.ld] = f2bf(v[q]);
       }
     } else if (row_ok) {
       const float w[8] = {v[0] * s.scale, v[1] * s.scale, v[2] * s.scale, v[3] * s.scale,
@@ -102,32 +135,19 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, int mt, int m, i
     }
     return;
   }
-  if (p.out_f32 && (row_ok || p.f32_frag)) {
+  if (o.f32 && (row_ok || o.f32_frag)) {
     int next;
-    float* o = wg_float_unit(p.out_f32, p.f32_frag, p.ldo, p.N, mt, m, n0, fo, lane, &next);
-    st_vec(o, v);
-    st_vec(o + next, v + 4);
+    float* d = wg_float_unit(o.f32, o.f32_frag, o.ldo, p.N, mt, m, n0, fo, lane, &next);
+    st_vec(d, v);
+    st_vec(d + next, v + 4);
   }
-  if (p.out_packed) {
+  if (o.packed) {
     // fragment (mt, n/16) of the [M, N] result as the next layer's activation operand; padded token rows are
     // written too (they only ever feed padded rows)
     const int KFo = p.N >> 4;
-    st_vec(p.out_packed + (((size_t)mt * KFo + (n >> 4)) * 64 + lane) * 8, v);
+    st_vec(o.packed + (((size_t)mt * KFo + (n >> 4)) * 64 + lane) * 8, v);
   }
-  if (p.out_rows && row_ok) st_vec(p.out_rows + (long long)m * p.ld_rows + n, v);
-}
-
-// Every argument that an epilogue needs is requested while the first operands are on their way: fetched where it is first used, a
-// batch of them costs that epilogue a round trip to memory (they are cold in every launch).
-__device__ __forceinline__ void wg_request_outputs(const WParams& p) {
-  asm volatile("" ::"s"(p.out_f32), "s"(p.ldo), "s"(p.f32_frag), "s"(p.out_packed), "s"(p.out_rows), "s"(p.ld_rows), "s"(p.nseg), "s"(p.ln_eps));
-}
-__device__ __forceinline__ void wg_request_segments(const WParams& p) {
-  asm volatile("" ::"s"(p.seg_w), "s"(p.seg_out[0]), "s"(p.seg_out[1]), "s"(p.seg_out[2]), "s"(p.seg_ld[0]), "s"(p.seg_ld[1]), "s"(p.seg_ld[2]),
-               "s"(p.seg_rows_out[0]), "s"(p.seg_rows_out[1]), "s"(p.seg_rows_out[2]));
-  asm volatile("" ::"s"(p.seg_row0[0]), "s"(p.seg_row0[1]), "s"(p.seg_row0[2]), "s"(p.seg_rows_in[0]), "s"(p.seg_rows_in[1]), "s"(p.seg_rows_in[2]),
-               "s"(p.seg_tr[0]), "s"(p.seg_tr[1]), "s"(p.seg_tr[2]), "s"(p.seg_pin[0]), "s"(p.seg_pin[1]), "s"(p.seg_pin[2]),
-               "s"(p.seg_pout[0]), "s"(p.seg_pout[1]), "s"(p.seg_pout[2]), "s"(p.seg0_scale));
+  if (o.rows && row_ok) st_vec(o.rows + (long long)m * o.ld_rows + n, v);
 }
 
 // Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.

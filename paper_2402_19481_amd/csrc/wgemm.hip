@@ -10,6 +10,12 @@
 //     workgroup add their partial tiles through LDS in wave order at the end (fixed order: results are
 //     reproducible), so even a 300 x 1280 output puts ~800 waves on the chip;
 //   - loads run PF k-steps ahead in a register ring; there is no barrier inside the K loop.
+// What bounds it: half of such a launch is not its K loop but the way to the first operands and the sum of the waves' tiles and epilogue
+// behind it (300 x 1280 x 1280: 2300, 4100 and 2200 cycles), where a wave has its SIMD to itself and waits out every
+// instruction.  Hence one kernel per kind of output, arguments that stay in registers, indices from reciprocals, and a
+// loop that requests nothing past its end.  In the step, against branches for the kinds, arguments fetched again and refills of
+// the last fragment: 64 x 1280 x 1280 5.6 -> 4.9 us, 64 x 10240 x 1280 with GEGLU 10.9 -> 10.2, 256 x 1280 in K = 1280 and 5120 (160
+// workgroups) 9.1 -> 8.7 on average, 1024 x 1280 x 1280 with cross-attention 14.8 -> 14.0.
 // The product is computed transposed (weights as the A operand, tokens as the B operand), so a lane ends up with
 // one token and 16 features.  Weight rows are stored with bits 2 and 3 of the in-fragment row index swapped, which
 // makes those 16 features two runs of 8 consecutive ones: exactly the 16 bytes that the same lane of the *next*
@@ -37,8 +43,14 @@ __device__ long long g_wg_trace[1024 * 16];
 #define DF_WTRACE(slot, expr) do {} while (0)
 #endif
 
-template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA, bool PART>
+// MODE: plain layer, GEGLU, or segmented output (with branches in their place an epilogue of few instructions was four times as long
+// and fetched its arguments again).
+enum { MODE_PLAIN = 0, MODE_GEGLU = 1, MODE_SEG = 2 };
+
+template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA, bool PART, int MODE>
 __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
+  constexpr bool GEGLU = MODE == MODE_GEGLU, SEG = MODE == MODE_SEG;
+  static_assert(!GEGLU || (TN % 2 == 0 && XA == 0 && !PART), "");
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   DF_WTRACE(0, wall_clock64());
   DF_WTRACE(1, __builtin_readcyclecounter());
@@ -50,21 +62,21 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   u32x4* qlds = reinterpret_cast<u32x4*>(smem_raw + KSPLIT * U * 1024 + KSPLIT * TM * 32 * 2 * 4);   // [4][64] (XA)
   float* vecs = reinterpret_cast<float*>(smem_raw + KSPLIT * U * 1024 + KSPLIT * TM * 32 * 2 * 4 + (XA > 0 ? 4096 : 0));   // [4][128]
   constexpr int GP = TN >= 2 ? TN / 2 : 1;   // geglu: the tile's first GP fragments are value rows, the last GP their gates
+  constexpr int JO = GEGLU ? GP : TN;        // output fragments per row of the tile
 
   // Every kernel argument the prologue needs is requested here, in one batch: left to the compiler, the scalar loads
   // of arguments first used under a condition (norm vectors, bias, residual, operand pointers) are issued where that
   // code starts, and the prologue of these few-microsecond kernels became a chain of four or five dependent round
   // trips to the scalar cache.
-  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.bias), "s"(p.ln_s), "s"(p.ln_t),
-               "s"(p.residual), "s"(p.ldr), "s"(p.geglu), "s"(p.res_frag));
+  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.mg_magic), "s"(p.kfw_magic), "s"(p.mgroups), "s"(p.kfw),
+               "s"(p.bias), "s"(p.ln_s), "s"(p.ln_t), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the k-walk and tile addresses stay off the vector ALU
   const int tok = lane & 31, g = lane >> 5;
   const int MT = (p.M + 31) >> 5;                      // 32-token fragments rows
-  const int MG = (MT + TM - 1) / TM;                   // tile groups along M
+  const int MG = p.mgroups;                            // tile groups along M
   const int NTo = p.N >> 5;                            // 32-feature output fragments
-  const int NG = p.geglu ? NTo / GP : NTo / TN;        // geglu: fragment j < GP is paired with gate fragment j + GP
-  const int nwg = MG * NG;
+  const int nwg = gridDim.x;
   int t = blockIdx.x;
   {
     // workgroups go round-robin over the 8 XCDs; give each XCD a contiguous run of tiles, token tiles fastest, so
@@ -73,8 +85,9 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int base = nwg >> 3, rem = nwg & 7;
     t = xcd * base + (xcd < rem ? xcd : rem) + loc;
   }
-  const int mg = t % MG, ng = t / MG;
-  const int KF = p.K >> 4, KFw = PART ? KF / KSPLIT / (int)gridDim.y : KF / KSPLIT;   // (whole, by the launcher)
+  // t / MG (the launcher: t MG < 2^32; the reciprocal of 1 does not fit)
+  const int ng = MG == 1 ? t : (int)(((unsigned long long)(unsigned int)t * p.mg_magic) >> 32), mg = t - ng * MG;
+  const int KF = p.K >> 4, KFw = p.kfw;                // k-fragments of a wave
   const int kf0 = ((PART ? (int)blockIdx.y * KSPLIT : 0) + wave) * KFw;
 #ifdef DF_TUNING
   asm volatile("" ::"s"(kf0), "s"(mg), "s"(ng));
@@ -91,10 +104,30 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
-    const int nt = p.geglu ? (j < GP ? ng * GP + j : NTo + ng * GP + (j - GP)) : ng * TN + j;
+    const int nt = GEGLU ? (j < GP ? ng * GP + j : NTo + ng * GP + (j - GP)) : ng * TN + j;
     wb[j] = p.Wp + ((size_t)nt * KF + kf0) * 64 + lane;
   }
 
+  bf16x8 xr[PF][TM], wr[PF][TN];
+  // The loop body is straight-line code (no branches): KFw % PF == 0 (launcher), and the last PF steps refill nothing (a refill of
+  // the last fragment again was a fifth of the loads at K = 1280, and the epilogue's stores queued behind them).  Every wave walks its k-range from a different starting fragment (wrapping around): the
+  // streams of all waves are otherwise aligned modulo the fragment-row pitch and hit the same few L2 / memory
+  // channels at any moment.  The order is a fixed function of the tile, so results stay reproducible.
+  const unsigned int rsum = (unsigned int)(mg * 7 + ng * 3 + wave * 5);
+  const int rot = KFw == 1 ? 0 : (int)(rsum - (unsigned int)KFw * (unsigned int)(((unsigned long long)rsum * p.kfw_magic) >> 32));   // rsum % KFw
+  auto pos = [&](int step) {
+    const int k = step + rot;
+    return (size_t)(k < KFw ? k : k - KFw) * 64;
+  };
+#pragma unroll
+  for (int s = 0; s < PF; ++s) {
+    const size_t o = pos(s);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) xr[s][i] = xb[i][o];
+#pragma unroll
+    for (int j = 0; j < TN; ++j) wr[s][j] = wb[j][o];
+  }
+  __builtin_amdgcn_sched_barrier(0);
   f32x16 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -107,7 +140,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   for (int i = 0; i < TM; ++i) { ln_sum[i] = 0.f; ln_sq[i] = 0.f; }
   constexpr bool ln = LN;
 
-  // Epilogue operands are requested before the K loop: their latency would otherwise sit, un-overlapped, at the end
+  // Epilogue operands are requested between the first operands and the K loop: their latency would otherwise sit, un-overlapped, at the end
   // of every one of these short kernels.  A pair unit = (token fragment row i, output fragment j, half f): 8
   // consecutive features per lane.  The tile is reduced and written in passes of RP rows; the pair units of a pass go
   // round-robin over the waves, which run the epilogue for them.
@@ -115,13 +148,12 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // token: wave v < 4 fetches vector v for the tile's whole feature range with ONE load (<= 128 floats) and parks it
   // in LDS for the epilogue.  Fetched per unit and lane they were 8-32 extra vector-memory instructions per wave, each
   // of which costs the compute unit's load path as much as a 1 KB operand fragment.
-  const int JO = p.geglu ? GP : TN;                    // output fragments per row of the tile
-  const int npu = RP * JO * 2;
+  constexpr int npu = RP * JO * 2;
   static_assert(KSPLIT >= 4, "one wave per parked vector");
   f32x4 vec_pre = {0.f, 0.f, 0.f, 0.f};
   {
     const int n0 = ng * JO * 32;
-    const bool gg = TN >= 2 && p.geglu;
+    constexpr bool gg = GEGLU;
     const float* src = nullptr;                        // (uniform)
     if (ln) src = wave == 0 ? p.ln_s + n0 : wave == 1 ? p.ln_t + n0 : (gg && wave == 2) ? p.ln_s + p.N + n0
                                                           : (gg && wave == 3) ? p.ln_t + p.N + n0 : nullptr;
@@ -131,16 +163,16 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   struct Epi { float r[8]; };
   auto load_epi = [&](int i0, int pu, Epi& e) {
     const int f = pu & 1;
-    const int j = p.geglu ? (pu >> 1) % GP : (pu >> 1) % TN;          // compile-time divisors (JO is a run-time value)
-    const int mt = mg * TM + i0 + (p.geglu ? (pu >> 1) / GP : (pu >> 1) / TN);
+    const int j = (pu >> 1) % JO;
+    const int mt = mg * TM + i0 + (pu >> 1) / JO;
     const int m = mt * 32 + tok;
-    if (!PART && p.residual && (p.res_frag ? mt < MT : m < p.M)) {
+    if (!PART && !SEG && XA == 0 && p.residual && (p.res_frag ? mt < MT : m < p.M)) {
       int next;
       const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, (ng * JO + j) * 32, 16 * f + 8 * g, lane, &next);
       ld_vec(rp, e.r); ld_vec(rp + next, e.r + 4);
     }
   };
-  constexpr int MAXU = (RP * TN * 2 + KSPLIT - 1) / KSPLIT;   // pair units of a pass per wave
+  constexpr int MAXU = (npu + KSPLIT - 1) / KSPLIT;    // pair units of a pass per wave
   constexpr int NPRE = MAXU < 3 ? MAXU : 3;
   Epi epre[NPRE];
 #pragma unroll
@@ -163,55 +195,38 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  bf16x8 xr[PF][TM], wr[PF][TN];
-  // The loop body is straight-line code (no branches): KFw % PF == 0 (launcher), refills past the end re-read the
-  // wave's last fragment.  Every wave walks its k-range from a different starting fragment (wrapping around): the
-  // streams of all waves are otherwise aligned modulo the fragment-row pitch and hit the same few L2 / memory
-  // channels at any moment.  The order is a fixed function of the tile, so results stay reproducible.
-  const int rot = (int)((unsigned)(mg * 7 + ng * 3 + wave * 5) % (unsigned)KFw);
-  auto pos = [&](int step) {
-    if (step > KFw - 1) step = KFw - 1;
-    const int k = step + rot;
-    return (size_t)(k < KFw ? k : k - KFw) * 64;
-  };
-#pragma unroll
-  for (int s = 0; s < PF; ++s) {
-    const size_t o = pos(s);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) xr[s][i] = xb[i][o];
-#pragma unroll
-    for (int j = 0; j < TN; ++j) wr[s][j] = wb[j][o];
-  }
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (!PART && XA == 0) wg_request_outputs(p);
-  if constexpr (LN && XA == 0) wg_request_segments(p);
+  const WOut out = wg_outputs<SEG>(p);
   __builtin_amdgcn_sched_barrier(0);
   DF_WTRACE(2, __builtin_readcyclecounter());
-  for (int kf = 0; kf < KFw; kf += PF) {
+  auto step = [&](int s) {
 #pragma unroll
-    for (int s = 0; s < PF; ++s) {
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[s][j], xr[s][i], acc[i][j], 0, 0, 0);
+    if constexpr (ln) {
+      // row sums of the tokens for the folded LayerNorm.  v_dot2c is executed by the matrix unit (7.6 cycles each); unpacked to plain
+      // float operations of the vector ALU the layers took as long or longer (300 x 3840 x 1280 11.7 -> 11.9 us)
+      const bf16x2_w ones = __builtin_bit_cast(bf16x2_w, 0x3f803f80u);
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wr[s][j], xr[s][i], acc[i][j], 0, 0, 0);
-      if constexpr (ln) {
-        // row sums of the tokens for the folded LayerNorm.  v_dot2c is executed by the matrix unit (7.6 cycles each); unpacked to plain
-        // float operations of the vector ALU the layers took as long or longer (300 x 3840 x 1280 11.7 -> 11.9 us)
-        const bf16x2_w ones = __builtin_bit_cast(bf16x2_w, 0x3f803f80u);
+      for (int i = 0; i < TM; ++i) {
+        const u32x4 raw = __builtin_bit_cast(u32x4, xr[s][i]);
+        const unsigned int wds[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const u32x4 raw = __builtin_bit_cast(u32x4, xr[s][i]);
-          const unsigned int wds[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const bf16x2_w v2 = __builtin_bit_cast(bf16x2_w, wds[q]);
-            ln_sum[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, ones, ln_sum[i], false);
-            ln_sq[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, v2, ln_sq[i], false);
-          }
+        for (int q = 0; q < 4; ++q) {
+          const bf16x2_w v2 = __builtin_bit_cast(bf16x2_w, wds[q]);
+          ln_sum[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, ones, ln_sum[i], false);
+          ln_sq[i] = __builtin_amdgcn_fdot2_f32_bf16(v2, v2, ln_sq[i], false);
         }
       }
-      const size_t o = pos(kf + s + PF);
+    }
+  };
+  for (int kf = PF; kf < KFw; kf += PF) {
+#pragma unroll
+    for (int s = 0; s < PF; ++s) {
+      step(s);
+      const size_t o = pos(kf + s);
 #pragma unroll
       for (int i = 0; i < TM; ++i) xr[s][i] = xb[i][o];
 #pragma unroll
@@ -219,6 +234,8 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       __builtin_amdgcn_sched_barrier(0);               // keep the refill here, PF steps ahead of its use
     }
   }
+#pragma unroll
+  for (int s = 0; s < PF; ++s) step(s);
 
   DF_WTRACE(3, __builtin_readcyclecounter());
   // ---- add the KSPLIT partial tiles in wave order, one token-fragment row at a time ----
@@ -255,8 +272,8 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int pu = wave + t * KSPLIT;
     if (pu >= npu) break;
     const int f = pu & 1;
-    const int j = p.geglu ? (pu >> 1) % GP : (pu >> 1) % TN;
-    const int il = p.geglu ? (pu >> 1) / GP : (pu >> 1) / TN;
+    const int j = (pu >> 1) % JO;
+    const int il = (pu >> 1) / JO;
     const int i = i0 + il;
     const int mt = mg * TM + i;
     if (mt >= MT) continue;
@@ -285,7 +302,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       }
       v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
     }
-    if (TN >= 2 && p.geglu) {
+    if constexpr (GEGLU) {
       f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
 #pragma unroll
       for (int w = 0; w < KSPLIT; ++w) {
@@ -313,7 +330,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       vec8(0, ea); vec8(1, eb);
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] = rstd * (v[q] - mean * ea[q]) + eb[q];
-      if (TN >= 2 && p.geglu) {
+      if constexpr (GEGLU) {
         vec8(2, ea); vec8(3, eb);
 #pragma unroll
         for (int q = 0; q < 8; ++q) gt[q] = rstd * (gt[q] - mean * ea[q]) + eb[q];
@@ -323,13 +340,13 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       vec8(0, ea);
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += ea[q];
-      if (TN >= 2 && p.geglu) {
+      if constexpr (GEGLU) {
         vec8(2, ea);
 #pragma unroll
         for (int q = 0; q < 8; ++q) gt[q] += ea[q];
       }
     }
-    if (TN >= 2 && p.geglu) {
+    if constexpr (GEGLU) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] *= gelu_erf(gt[q]);
     }
@@ -340,11 +357,11 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       continue;
     }
     const bool row_ok = m < p.M;
-    if (p.residual && (row_ok || p.res_frag)) {
+    if (!SEG && p.residual && (row_ok || p.res_frag)) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += e.r[q];
     }
-    wg_store_unit(p, mt, m, nfrag * 32, 16 * f + 8 * g, lane, v);
+    wg_store_unit<SEG>(p, out, mt, m, nfrag * 32, 16 * f + 8 * g, lane, v);
   }
   DF_WTRACE(9 + 2 * (i0 / RP < 4 ? i0 / RP : 3), __builtin_readcyclecounter());
   }
@@ -510,8 +527,9 @@ __global__ void pack_text_kv_kernel(const bf16_t* __restrict__ kv, long long ld,
   out[idx] = v;
 }
 
-template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0, bool PART = false>
-int launch_one(const WParams& p, hipStream_t st) {
+template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0, bool PART = false, int MODE = MODE_PLAIN>
+int launch_one(const WParams& pin, hipStream_t st) {
+  WParams p = pin;
   const int MT = (p.M + 31) / 32, MG = (MT + TM - 1) / TM;
   const int NTo = p.N / 32;
   if (!p.geglu && NTo % TN) return DF_ESHAPE;
@@ -522,7 +540,12 @@ int launch_one(const WParams& p, hipStream_t st) {
   if (KF % KSPLIT) return DF_ESHAPE;
   constexpr int RP = (KSPLIT * TM * TN * 4 <= 128) ? TM : (TM % 2 == 0 && KSPLIT * (TM / 2) * TN * 4 <= 128) ? TM / 2 : 1;
   constexpr int smem = KSPLIT * RP * TN * 4 * 1024 + KSPLIT * TM * 32 * 2 * 4 + (XA > 0 ? 4096 : 0) + 4 * 128 * 4;
-  auto k = wgemm_kernel<TM, TN, KSPLIT, PF, LN, XA, PART>;
+  // reciprocals for the tile indices and for the waves' first fragments (x / d = x * magic >> 32 while x d < 2^32)
+  p.mgroups = MG; p.kfw = KF / KSPLIT / (PART ? p.parts : 1);
+  if (p.kfw < 1 || (long long)MG * NG * MG >= (1LL << 32) || (7LL * MG + 3LL * NG + 20) * p.kfw >= (1LL << 32)) return DF_ESHAPE;
+  p.mg_magic = (unsigned int)(((1ULL << 32) + MG - 1) / MG);
+  p.kfw_magic = (unsigned int)(((1ULL << 32) + p.kfw - 1) / p.kfw);
+  auto k = wgemm_kernel<TM, TN, KSPLIT, PF, LN, XA, PART, MODE>;
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
@@ -548,7 +571,13 @@ int launch_cfg(const WParams& p, hipStream_t st) {
     return DF_ESHAPE;
   }
   const bool ln = p.ln_s != nullptr;
-#define DF_WG(PFV)                                                                     \
+#define DF_WG(PFV)                                                                                                        \
+  if (p.nseg) return ln ? launch_one<TM, TN, KSPLIT, PFV, true, 0, false, MODE_SEG>(p, st) : DF_ESHAPE;   /* (as bgemm) */  \
+  if constexpr (TN == 2) {                                                                                                \
+    if (p.geglu) return ln ? launch_one<TM, TN, KSPLIT, PFV, true, 0, false, MODE_GEGLU>(p, st)                            \
+                           : launch_one<TM, TN, KSPLIT, PFV, false, 0, false, MODE_GEGLU>(p, st);                          \
+  }                                                                                                                       \
+  if (p.geglu) return DF_ESHAPE;                                                                                          \
   return ln ? launch_one<TM, TN, KSPLIT, PFV, true>(p, st) : launch_one<TM, TN, KSPLIT, PFV, false>(p, st)
   if (KFw % PFMAX == 0) { DF_WG(PFMAX); }
   if (KFw % 4 == 0) { DF_WG(4); }
