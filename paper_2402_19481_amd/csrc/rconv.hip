@@ -11,6 +11,11 @@ template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
 }
+template <int MOST = 40>
+__device__ __forceinline__ void wait_vm_lds(int n) {   // the same with a count that unrolling makes known
+  if (n == MOST) wait_vm_lds<MOST>();
+  else if constexpr (MOST > 0) wait_vm_lds<MOST - 1>(n);
+}
 __device__ __forceinline__ void block_sync() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
@@ -178,17 +183,28 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
       for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wa[b][j], xa[b][i], acc[i][j], 0, 0, 0);
   };
   // part `part` of NSUB of the loads requested during stage st of the channels `slab`: the weights ST - 1 stages on, and the
-  // next channels' pixels.  Past the end the last channels are loaded again: the counts behind the waits stay uniform.
+  // next channels' pixels.  The last channels (LAST) request what is left of their own weights and nothing else: loaded once more to
+  // keep the counts behind the waits they were a fifth of the loads of 320 channels.
   auto in_loads = [&](int st) { return st * IPS >= NIN ? 0 : (NIN - st * IPS < IPS ? NIN - st * IPS : IPS); };
-  auto issue = [&](int slab, int buf, int wslot, int st, int part) {
-    const int ws = st + ST - 1, nin = in_loads(st), n = WL + nin;
-    const int sw = slab + ws / NST < s_hi ? slab + ws / NST : s_hi - 1, sn = slab + 1 < s_hi ? slab + 1 : s_hi - 1;
+  auto issue = [&](auto lastc, int slab, int buf, int wslot, int st, int part) {
+    constexpr bool LAST = decltype(lastc)::value;
+    const int ws = st + ST - 1, nw = LAST && ws >= NST ? 0 : WL, nin = LAST ? 0 : in_loads(st), n = nw + nin;
 #pragma unroll
     for (int l = 0; l < WL + IPS; ++l) {
       if (l >= n || l * NSUB / n != part) continue;
-      if (l < WL) load_w(sw, ws % NST, wslot, l);
-      else load_in(sn, buf ^ 1, st * IPS + l - WL);
+      if (l < nw) load_w(slab + ws / NST, ws % NST, wslot, l);
+      else load_in(slab + 1, buf ^ 1, st * IPS + l - nw);
     }
+  };
+  // loads that may still be in flight at the end of stage st: those requested in the last ST - 2 stages
+  auto in_flight = [&](auto lastc, int st) {
+    int n = 0;
+#pragma unroll
+    for (int k = 0; k < ST - 2; ++k) {
+      const int j = st - k;
+      n += decltype(lastc)::value ? (j < 0 || j + ST - 1 < NST ? WL : 0) : WL + in_loads((j + NST) % NST);
+    }
+    return n;
   };
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
   // prologue
@@ -200,12 +216,18 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
 #pragma unroll
     for (int l = 0; l < WL; ++l) load_w(sw, s % NST, s, l);
   }
+  // the epilogue's arguments (cold in every launch) come beside the first operands
+  asm volatile("" ::"s"(p.bias), "s"(p.chan_add), "s"(p.chan_ld), "s"(p.residual), "s"(p.ldr), "s"(p.out), "s"(p.ldo), "s"(p.act), "s"(x.partials));
   wait_vm_lds<(ST - 2) * WL>();
   block_sync();
   rd(0, 0, 0, 0, 0);
   int slot = 0, wslot = ST - 1, buf = 0;
-  issue(s_lo, 0, wslot, 0, 0);
-  for (int slab = s_lo; slab < s_hi; ++slab) {
+  using Last = std::true_type;
+  using More = std::false_type;
+  if (s_lo + 1 < s_hi) issue(More{}, s_lo, 0, wslot, 0, 0);
+  else issue(Last{}, s_lo, 0, wslot, 0, 0);
+  auto channels = [&](auto lastc, int slab) {
+    constexpr bool LAST = decltype(lastc)::value;
 #pragma unroll
     for (int st = 0; st < NST; ++st) {
       const int nslot = slot + 1 == ST ? 0 : slot + 1;
@@ -214,58 +236,44 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
         const int b = (st * NSUB + u) % NB, bn = (st * NSUB + u + 1) % NB;
         if (u + 1 < NSUB) {
           DF_SB; rd(slot, buf, st, u + 1, bn); DF_SB; mm(b); DF_SB;
-          issue(slab, buf, wslot, st, u + 1);
-        } else if (st + 1 == NST && slab + 1 == s_hi) {
-          wait_vm_lds<0>();
+          issue(lastc, slab, buf, wslot, st, u + 1);
+        } else if (LAST && st + 1 == NST) {
           DF_SB; mm(b); DF_SB;
         } else {
-          // loads requested in the last ST - 2 stages may still be in flight
-          if constexpr (ST == 3) {
-            if (in_loads(st) == 0) wait_vm_lds<WL>();
-            else if (in_loads(st) == IPS) wait_vm_lds<WL + IPS>();
-            else wait_vm_lds<WL + (NIN % IPS)>();
-          } else {
-            int fl = 0;
-#pragma unroll
-            for (int k = 0; k < ST - 2; ++k) fl += WL + in_loads((st - k + NST) % NST);
-            switch (fl - (ST - 2) * WL) {                  // (compile-time after unrolling)
-              case 0: wait_vm_lds<(ST - 2) * WL>(); break;
-              case 1: wait_vm_lds<(ST - 2) * WL + 1>(); break;
-              case 2: wait_vm_lds<(ST - 2) * WL + 2>(); break;
-              case 3: wait_vm_lds<(ST - 2) * WL + 3>(); break;
-              case 4: wait_vm_lds<(ST - 2) * WL + 4>(); break;
-              case 5: wait_vm_lds<(ST - 2) * WL + 5>(); break;
-              case 6: wait_vm_lds<(ST - 2) * WL + 6>(); break;
-              default: wait_vm_lds<(ST - 2) * WL>(); break;
-            }
-          }
+          wait_vm_lds(in_flight(lastc, st));
           block_sync();
           const bool wrap = st + 1 == NST;
           rd(nslot, wrap ? buf ^ 1 : buf, wrap ? 0 : st + 1, 0, bn);
           DF_SB; mm(b); DF_SB;
           // the next stage's first part goes to the slot of the stage that has just ended
-          issue(wrap ? slab + 1 : slab, wrap ? buf ^ 1 : buf, slot, wrap ? 0 : st + 1, 0);
+          if (!wrap) issue(lastc, slab, buf, slot, st + 1, 0);
+          else if (slab + 2 < s_hi) issue(More{}, slab + 1, buf ^ 1, slot, 0, 0);
+          else issue(Last{}, slab + 1, buf ^ 1, slot, 0, 0);
         }
       }
       wslot = slot;
       slot = nslot;
     }
     buf ^= 1;
+  };
+  for (int slab = s_lo; slab + 1 < s_hi; ++slab) channels(More{}, slab);
+  // What the epilogue adds per channel is requested where only weights are left to request.
+  constexpr int RS = 512 / (BN / 4);                       // rows per round of the epilogue; a thread keeps its columns
+  const bool part = gridDim.y > 1;
+  const int c4 = (tid % (BN / 4)) * 4, col = n0 + c4;
+  const bool mine = tid < RS * (BN / 4) && col < p.N;
+  f32x4 add = {0.f, 0.f, 0.f, 0.f}, add_image = add;
+  if (!part && mine) {
+    if (p.bias) add = *reinterpret_cast<const f32x4*>(p.bias + col);
+    if (p.chan_add) add_image = *reinterpret_cast<const f32x4*>(p.chan_add + (long long)bi * p.chan_ld + col);
   }
+  channels(Last{}, s_hi - 1);
 #undef DF_SB
 
   // ---- epilogue: accumulators -> LDS in passes of RP fragment rows of the tile, k-groups added, rows of the output stored ----
   constexpr int RP = pass_rows(PM * TM, KG, BN), PT = BN + 4;
   float* tile = reinterpret_cast<float*>(smem);
-  constexpr int U = 4, RS = 512 / (BN / 4);                // rows in flight per thread, rows per round
-  const bool part = gridDim.y > 1;
-  const int c4 = (tid % (BN / 4)) * 4, col = n0 + c4;      // a thread keeps its columns
-  const bool mine = tid < RS * (BN / 4) && col < p.N;
-  f32x4 add = {0.f, 0.f, 0.f, 0.f};
-  if (!part && mine) {
-    if (p.bias) add = *reinterpret_cast<const f32x4*>(p.bias + col);
-    if (p.chan_add) add += *reinterpret_cast<const f32x4*>(p.chan_add + (long long)bi * p.chan_ld + col);
-  }
+  constexpr int U = 4;                                     // rows in flight per thread
 #pragma unroll 1
   for (int f0 = 0; f0 < PM * TM; f0 += RP) {
     block_sync();                                          // the ring, or the previous pass, has been read
@@ -306,7 +314,7 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
             *reinterpret_cast<f32x4*>(x.partials + ((size_t)blockIdx.y * p.M + row[k]) * p.N + col) = v;
             continue;
           }
-          v += add;
+          v += add + add_image;
           v += res[k];
           if (p.act == 1) { v.x = silu_f(v.x); v.y = silu_f(v.y); v.z = silu_f(v.z); v.w = silu_f(v.w); }
           OutT* o = reinterpret_cast<OutT*>(p.out) + row[k] * p.ldo + col;
