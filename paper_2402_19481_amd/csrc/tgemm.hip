@@ -225,27 +225,49 @@ void tgemm_kernel(TileParams p, TgExtra x) {
     const int k = s < KT ? s : KT - 1;                                   // past the end: the last stage again (vmcnt stays uniform)
     issue(k, s, I0{}); issue(k, s, I1{}); issue(k, s, I2{}); issue(k, s, I3{});
   }
+  // the epilogue's arguments (cold in every launch) come beside the first operands
+  asm volatile("" ::"s"(p.bias), "s"(p.chan_add), "s"(p.chan_ld), "s"(p.residual), "s"(p.ldr), "s"(p.out), "s"(p.ldo), "s"(p.act), "s"(x.partials));
   wait_vm_lds<L * (ST - 2)>();
   block_sync();
   rd(0, 0, I0{});
-  int slot = 0, pslot = ST - 1;
-  for (int kt = 0; kt < KT; ++kt) {
-    const int nslot = slot + 1 == ST ? 0 : slot + 1;
-    const int kn = kt + ST - 1 < KT ? kt + ST - 1 : KT - 1;
-    const bool mine = KG == 1 || s_lo + kt * KG + kg < s_hi;             // (uniform) the group has a slab in this stage
+  int slot = 0, pslot = ST - 1, kt = 0;
+  auto has_slab = [&] { return KG == 1 || s_lo + kt * KG + kg < s_hi; };   // (uniform) the group has a slab in stage kt
+  for (; kt + ST - 1 < KT; ++kt) {
+    const int nslot = slot + 1 == ST ? 0 : slot + 1, kn = kt + ST - 1;
+    const bool mine = has_slab();
     DF_SB; rd(slot, 1, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB; issue(kn, pslot, I0{});
     DF_SB; rd(slot, 2, I0{}); DF_SB; if (mine) mm(I1{}); DF_SB; issue(kn, pslot, I1{});
     DF_SB; rd(slot, 3, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB; issue(kn, pslot, I2{});
-    if (kt + 1 < KT) {
-      wait_vm_lds<L * (ST - 2) - LATE>();
-      block_sync();
-      rd(nslot, 0, I0{});
-    }
+    wait_vm_lds<L * (ST - 2) - LATE>();
+    block_sync();
+    rd(nslot, 0, I0{});
     DF_SB; if (mine) mm(I1{}); DF_SB; issue(kn, pslot, I3{});
     pslot = slot;
     slot = nslot;
   }
-  wait_vm_lds<0>();                                                      // the clamped tail loads: the ring becomes the epilogue's
+  // the last ST - 1 stages have been requested (as in bgemm.hip)
+  auto last = [&](auto uc) {                                             // stage kt, uc stages into the tail: false behind the last one
+    constexpr int U = decltype(uc)::value;
+    const int nslot = slot + 1 == ST ? 0 : slot + 1;
+    const bool mine = has_slab(), more = U < ST - 2 && kt + 1 < KT;
+    DF_SB; rd(slot, 1, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB;
+    rd(slot, 2, I0{}); DF_SB; if (mine) mm(I1{}); DF_SB;
+    rd(slot, 3, I1{}); DF_SB; if (mine) mm(I0{}); DF_SB;
+    if (more) {
+      wait_vm_lds<U < ST - 2 ? L * (ST - 3 - U) : 0>();                  // (stages of a short K that were requested twice count too)
+      block_sync();
+      rd(nslot, 0, I0{});
+    }
+    DF_SB; if (mine) mm(I1{}); DF_SB;
+    slot = nslot;
+    ++kt;
+    return more;
+  };
+  static_assert(ST == 3 || ST == 4, "");
+  if (last(I0{}))
+    if (last(I1{}))
+      if constexpr (ST == 4) last(I2{});
+  if (KT < ST - 1) wait_vm_lds<0>();                                     // the ring becomes the epilogue's
 #undef DF_SB
 
   // ---- epilogue: accumulators -> LDS (the ring is free), k-groups added, whole rows stored ----
@@ -261,17 +283,28 @@ void tgemm_kernel(TileParams p, TgExtra x) {
         *reinterpret_cast<f32x4*>(tile + (kg * BM + wm * WM + i * 32 + lrow) * PT + wn * WN + j * 32 + 8 * q + 4 * g) =
             f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
   __syncthreads();
+  // (four rows' additions requested together: one by one each waited for the one before it)
+  constexpr int ITEMS = BM * (BN / 4) / NTHR, U = ITEMS % 4 == 0 ? 4 : ITEMS % 2 == 0 ? 2 : 1;
+  static_assert(ITEMS * NTHR == BM * (BN / 4), "");
 #pragma unroll 1
-  for (int idx = tid; idx < BM * (BN / 4); idx += NTHR) {
-    const int r = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
-    const int row = m0 + r, col = n0 + c4;
-    if (row >= p.M || col >= p.N) continue;
-    const Added add = nsplit > 1 ? Added{} : added4<kConv>(p, row, col);
-    f32x4 v = *reinterpret_cast<const f32x4*>(tile + r * PT + c4);
+  for (int i0 = 0; i0 < ITEMS; i0 += U) {
+    Added add[U];
 #pragma unroll
-    for (int k = 1; k < KG; ++k) v += *reinterpret_cast<const f32x4*>(tile + (k * BM + r) * PT + c4);
-    if (nsplit > 1) *reinterpret_cast<f32x4*>(x.partials + ((size_t)split * p.M + row) * p.N + col) = v;
-    else store4<kConv, OutT>(p, row, col, v, add);
+    for (int k = 0; k < U; ++k) {
+      const int idx = tid + (i0 + k) * NTHR, row = m0 + idx / (BN / 4), col = n0 + (idx % (BN / 4)) * 4;
+      add[k] = nsplit > 1 || row >= p.M || col >= p.N ? Added{} : added4<kConv>(p, row, col);
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int idx = tid + (i0 + k) * NTHR, r = idx / (BN / 4), c4 = (idx % (BN / 4)) * 4;
+      const int row = m0 + r, col = n0 + c4;
+      if (row >= p.M || col >= p.N) continue;
+      f32x4 v = *reinterpret_cast<const f32x4*>(tile + r * PT + c4);
+#pragma unroll
+      for (int h = 1; h < KG; ++h) v += *reinterpret_cast<const f32x4*>(tile + (h * BM + r) * PT + c4);
+      if (nsplit > 1) *reinterpret_cast<f32x4*>(x.partials + ((size_t)split * p.M + row) * p.N + col) = v;
+      else store4<kConv, OutT>(p, row, col, v, add[k]);
+    }
   }
 }
 
