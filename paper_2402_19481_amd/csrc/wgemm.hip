@@ -179,22 +179,19 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   for (int t = 0; t < NPRE; ++t)
     if (wave + t * KSPLIT < npu) load_epi(0, wave + t * KSPLIT, epre[t]);
   DF_WTRACE(7, __builtin_readcyclecounter());
-  // fused cross-attention: the wave that runs it also requests the head's key fragments now
-  bf16x8 xkf[XA > 0 ? XA : 1][4];
+  // fused cross-attention: wave w takes the w-th 32 text tokens of the head, and requests their keys now
+  bf16x8 xkf[4];
   const bf16x8* xkv_ptr = nullptr;
   if constexpr (XA > 0) {
-    const int bi = (int)(((long long)mg * 32) / p.xa_rows);   // TM == 1; a fragment row never straddles batch items when
+    static_assert(XA <= KSPLIT && TM == 1 && TN == 2, "");
+    const int bi = (int)(((long long)mg * 32) / p.xa_rows);   // a fragment row never straddles batch items when
                                                               // rows % 32 == 0, otherwise the launcher requires one item
     xkv_ptr = p.xkv + (size_t)bi * p.xa_bstride + (size_t)ng * (12 * XA) * 64 + lane;
-    if (wave == 0) {
+    if (wave < XA) {
 #pragma unroll
-      for (int kt = 0; kt < XA; ++kt)
-#pragma unroll
-        for (int ds = 0; ds < 4; ++ds) xkf[kt][ds] = xkv_ptr[(size_t)(kt * 4 + ds) * 64];
+      for (int ds = 0; ds < 4; ++ds) xkf[ds] = xkv_ptr[(size_t)(wave * 4 + ds) * 64];
     }
   }
-  __builtin_amdgcn_sched_barrier(0);
-
   __builtin_amdgcn_sched_barrier(0);
   const WOut out = wg_outputs<SEG>(p);
   __builtin_amdgcn_sched_barrier(0);
@@ -238,6 +235,15 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   for (int s = 0; s < PF; ++s) step(s);
 
   DF_WTRACE(3, __builtin_readcyclecounter());
+  bf16x8 vf[2][2];                                     // the values, on their way while the partial tiles are added
+  if constexpr (XA > 0) {
+    if (wave < XA) {
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) vf[dt][ks] = xkv_ptr[(size_t)(4 * XA + dt * 2 * XA + 2 * wave + ks) * 64];
+    }
+  }
   // ---- add the KSPLIT partial tiles in wave order, one token-fragment row at a time ----
   if (ln) {
 #pragma unroll
@@ -368,79 +374,76 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   DF_WTRACE(4, __builtin_readcyclecounter());
   DF_WTRACE(5, wall_clock64());
   if constexpr (XA > 0) {
+    // Wave w: S^T = K Q^T over its key tile (lane = token, 16 keys in natural order thanks to the row permutation of the packed keys), the
+    // probabilities relative to the maximum of all tiles, O^T = V^T P^T of its keys.  The waves then add a quarter of the features
+    // each.  One wave with all tiles took 1900 cycles behind the projection, and its keys held up its share of K.
     __syncthreads();
-    if (wave != 0) return;
-    // one wave: S^T = K Q^T over XA key tiles (lane = token, 16 keys per tile in natural order thanks to the row
-    // permutation of the packed keys), softmax over the valid keys, O^T = V^T P^T, packed output
-    const int mt = mg;                                   // TM == 1
-    const bf16x8* kv = xkv_ptr;
-    bf16x8 qf[4];
+    float* xmax = stat;                                  // [XA][64]; the partial tiles, statistics and vectors have been read
+    float* xsum = vecs;                                  // [XA][64]
+    float pv[16];
+    if (wave < XA) {
+      f32x16 sa;
 #pragma unroll
-    for (int ds = 0; ds < 4; ++ds) qf[ds] = __builtin_bit_cast(bf16x8, qlds[ds * 64 + lane]);
-    auto& kf = xkf;
-    bf16x8 vf[2][2 * XA];
+      for (int e = 0; e < 16; ++e) sa[e] = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int ks = 0; ks < 2 * XA; ++ks) vf[dt][ks] = kv[(size_t)(4 * XA + dt * 2 * XA + ks) * 64];
-    f32x16 sa[XA];
-#pragma unroll
-    for (int kt = 0; kt < XA; ++kt) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) sa[kt][e] = 0.f;
-#pragma unroll
-      for (int ds = 0; ds < 4; ++ds) sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[kt][ds], qf[ds], sa[kt], 0, 0, 0);
-    }
-    const float sc = p.xa_scale * 1.4426950408889634f;
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kt = 0; kt < XA; ++kt)
+      for (int ds = 0; ds < 4; ++ds)
+        sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xkf[ds], __builtin_bit_cast(bf16x8, qlds[ds * 64 + lane]), sa, 0, 0, 0);
+      float mx = -INFINITY;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int key = kt * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
-        if (key >= p.xa_keys) sa[kt][e] = -INFINITY;
-        mx = fmaxf(mx, sa[kt][e]);
+        const int key = wave * 32 + 16 * (e >> 3) + 8 * g + (e & 7);
+        pv[e] = key >= p.xa_keys ? -INFINITY : sa[e];
+        mx = fmaxf(mx, pv[e]);
       }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * sc;
+      xmax[wave * 64 + lane] = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    }
+    __syncthreads();
+    if (wave < XA) {
+      const float sc = p.xa_scale * 1.4426950408889634f;
+      float mx = xmax[lane];
+#pragma unroll
+      for (int w = 1; w < XA; ++w) mx = fmaxf(mx, xmax[w * 64 + lane]);
+      mx *= sc;
+      float l = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        pv[e] = __builtin_amdgcn_exp2f(fmaf(pv[e], sc, -mx));
+        l += pv[e];
+      }
+      xsum[wave * 64 + lane] = l + __shfl_xor(l, 32, 64);
+      f32x16 oa[2];
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) oa[dt][e] = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const u32x4 pk = {pack_bf2(pv[8 * ks + 0], pv[8 * ks + 1]), pack_bf2(pv[8 * ks + 2], pv[8 * ks + 3]),
+                          pack_bf2(pv[8 * ks + 4], pv[8 * ks + 5]), pack_bf2(pv[8 * ks + 6], pv[8 * ks + 7])};
+#pragma unroll
+        for (int dt = 0; dt < 2; ++dt)
+          oa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][ks], __builtin_bit_cast(bf16x8, pk), oa[dt], 0, 0, 0);
+      }
+#pragma unroll
+      for (int dt = 0; dt < 2; ++dt)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          red[((wave * 2 + dt) * 4 + q) * 64 + lane] = f32x4{oa[dt][4 * q], oa[dt][4 * q + 1], oa[dt][4 * q + 2], oa[dt][4 * q + 3]};
+    }
+    __syncthreads();
+    const int dt = wave >> 1, f2 = wave & 1;             // features 32 dt + 16 f2 .. of the head
+    f32x4 a = {0.f, 0.f, 0.f, 0.f}, c = a;
     float l = 0.f;
 #pragma unroll
-    for (int kt = 0; kt < XA; ++kt)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const float pv = __builtin_amdgcn_exp2f(fmaf(sa[kt][e], sc, -mx));
-        sa[kt][e] = pv;
-        l += pv;
-      }
-    l += __shfl_xor(l, 32, 64);
-    f32x16 oa[2];
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) oa[dt][e] = 0.f;
-    }
-#pragma unroll
-    for (int ks = 0; ks < 2 * XA; ++ks) {
-      const int kt = ks >> 1, hf = ks & 1;
-      u32x4 pk;
-      pk.x = pack_bf2(sa[kt][8 * hf + 0], sa[kt][8 * hf + 1]);
-      pk.y = pack_bf2(sa[kt][8 * hf + 2], sa[kt][8 * hf + 3]);
-      pk.z = pack_bf2(sa[kt][8 * hf + 4], sa[kt][8 * hf + 5]);
-      pk.w = pack_bf2(sa[kt][8 * hf + 6], sa[kt][8 * hf + 7]);
-      const bf16x8 pf = __builtin_bit_cast(bf16x8, pk);
-#pragma unroll
-      for (int dt = 0; dt < 2; ++dt) oa[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt][ks], pf, oa[dt], 0, 0, 0);
+    for (int w = 0; w < XA; ++w) {
+      a += red[((w * 2 + dt) * 4 + 2 * f2) * 64 + lane];
+      c += red[((w * 2 + dt) * 4 + 2 * f2 + 1) * 64 + lane];
+      l += xsum[w * 64 + lane];
     }
     const float inv = 1.0f / l;
+    const float o8[8] = {a.x * inv, a.y * inv, a.z * inv, a.w * inv, c.x * inv, c.y * inv, c.z * inv, c.w * inv};
     const int KFo = p.N >> 4;
-#pragma unroll
-    for (int dt = 0; dt < 2; ++dt)
-#pragma unroll
-      for (int f2 = 0; f2 < 2; ++f2) {
-        float o8[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) o8[q] = oa[dt][8 * f2 + q] * inv;
-        st_vec(p.out_packed + (((size_t)mt * KFo + ng * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
-      }
+    st_vec(p.out_packed + (((size_t)mg * KFo + ng * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
   }
 }
 
