@@ -496,38 +496,35 @@ __global__ void pack_wfrag_kernel(const bf16_t* __restrict__ w, const float* __r
 template <int TM, int TN, int KSPLIT, int PFMAX>
 int launch_cfg(const WParams& p, hipStream_t st);
 
-__global__ void pack_text_kv_kernel(const bf16_t* __restrict__ kv, long long ld, u32x4* __restrict__ out, int B, int TL,
-                                    int count, int C, int XA, long long total) {
-  const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx & 63);
-  long long frag = idx >> 6;
-  const int heads = C / 64, per_head = 12 * XA;
-  const int fr = (int)(frag % per_head); frag /= per_head;
-  const int hh = (int)(frag % heads); frag /= heads;
-  const int j = (int)(frag % count);
-  const int b = (int)(frag / count);
+// Keys and values of the text tokens (row-major, per layer C keys then C values) as the fragments of the fused cross-attention.  A
+// workgroup takes four fragments, blockIdx.y, of one (batch item, layer, head), blockIdx.x.  77 x 153600: 22.4 -> 18.0 us against one
+// index over everything, with five 64-bit divisions per lane; what is left are the values, gathered two bytes at a time.
+__global__ __launch_bounds__(256) void pack_text_kv_kernel(const bf16_t* __restrict__ kv, long long ld, u32x4* __restrict__ out, int TL,
+                                                           int heads, int count, int XA) {
+  const int lane = threadIdx.x & 63, fr = blockIdx.y * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const unsigned int bj = blockIdx.x / (unsigned int)heads, hh = blockIdx.x - bj * heads, b = bj / (unsigned int)count, j = bj - b * count;
+  const int C = heads * 64;
+  if (fr >= 12 * XA) return;
+  const bf16_t* src = kv + (long long)b * TL * ld + (long long)j * 2 * C + hh * 64;
   const int i = lane & 31, g = lane >> 5;
   const int sig = (i & 0x13) | ((i & 4) << 1) | ((i & 8) >> 1);
   u32x4 v = {0u, 0u, 0u, 0u};
   if (fr < 4 * XA) {
     const int kt = fr >> 2, ds = fr & 3;
     const int key = kt * 32 + sig;
-    if (key < TL)
-      v = *reinterpret_cast<const u32x4*>(kv + ((long long)b * TL + key) * ld + (long long)j * 2 * C + hh * 64 + ds * 16 + 8 * g);
+    if (key < TL) v = *reinterpret_cast<const u32x4*>(src + key * ld + ds * 16 + 8 * g);
   } else {
-    const int fv = fr - 4 * XA;
-    const int dt = fv / (2 * XA), ks = fv % (2 * XA);
-    const int d = dt * 32 + sig;
+    const int fv = fr - 4 * XA, dt = fv >= 2 * XA ? 1 : 0, ks = fv - dt * 2 * XA;
+    const bf16_t* col = src + C + dt * 32 + sig;
     unsigned int e[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const int key = ks * 16 + 8 * g + q;
-      e[q] = key < TL ? kv[((long long)b * TL + key) * ld + (long long)j * 2 * C + C + hh * 64 + d] : 0u;
+      e[q] = key < TL ? col[key * ld] : 0u;
     }
     v.x = e[0] | (e[1] << 16); v.y = e[2] | (e[3] << 16); v.z = e[4] | (e[5] << 16); v.w = e[6] | (e[7] << 16);
   }
-  out[idx] = v;
+  out[((size_t)blockIdx.x * (12 * XA) + fr) * 64 + lane] = v;
 }
 
 template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA = 0, bool PART = false, int MODE = MODE_PLAIN>
@@ -609,9 +606,10 @@ size_t packed_text_kv_bytes(int B, int TL, int count, int C) {
 int launch_pack_text_kv(const bf16_t* kv, long long ld, bf16_t* out, int B, int TL, int count, int C, hipStream_t st) {
   if (B <= 0 || TL <= 0 || count <= 0 || C % 64 || ld % 8 || ((uintptr_t)kv % 16) || ((uintptr_t)out % 16)) return DF_ESHAPE;
   const int XA = (TL + 31) / 32;
-  const long long total = (long long)B * count * (C / 64) * 12 * XA * 64;
-  hipLaunchKernelGGL(pack_text_kv_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, kv, ld, (u32x4*)out, B, TL,
-                     count, C, XA, total);
+  const long long heads = (long long)B * count * (C / 64);
+  if (heads > 0x7fffffffLL || 3 * XA > 65535) return DF_ESHAPE;
+  hipLaunchKernelGGL(pack_text_kv_kernel, dim3((unsigned)heads, (unsigned)(3 * XA)), dim3(256), 0, st, kv, ld, (u32x4*)out, TL, C / 64,
+                     count, XA);
   DF_LAUNCH_CHECK();
   return DF_OK;
 }
