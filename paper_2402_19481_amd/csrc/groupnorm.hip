@@ -93,6 +93,32 @@ __device__ __forceinline__ void halo_store(const GnHalo& h, int b, long long p, 
   }
 }
 
+// PAIR: x is the concatenation of two tensors along the channels, Ca of `x` and the rest of `b`, which is never stored as floats; the
+// kernel that reads it first leaves the bf16 copy that the shortcut convolution takes.  A lane's channels lie on one side (Ca % 4 == 0).
+// Of the 10 bytes per value that a concatenation kernel moves (floats and bf16 written, both tensors read) 2 remain; 832x1216 step 9703 ->
+// 9637 us, 512x512 step 4654 -> 4644, 2048x2048 in strips 15770 -> 15686.
+struct GnPair {
+  const float* b;
+  int Ca;
+  bf16_t* cat;
+};
+// Where channel c of pixel 0 is, and the values from a pixel to the next
+template <bool PAIR, typename Tin>
+__device__ __forceinline__ const Tin* gn_source(const Tin* x, const GnPair& pr, int C, int c, int* pitch) {
+  if constexpr (PAIR) {
+    *pitch = c < pr.Ca ? pr.Ca : C - pr.Ca;
+    return c < pr.Ca ? x + c : pr.b + (c - pr.Ca);
+  }
+  *pitch = C;
+  return x + c;
+}
+template <bool PAIR, typename Tin>
+__device__ __forceinline__ float gn_value(const Tin* x, const GnPair& pr, int C, long long pix, int c) {
+  int pitch;
+  const Tin* s = gn_source<PAIR>(x, pr, C, c, &pitch);
+  return Elem<Tin>::ld(s + pix * pitch);
+}
+
 // NCH (template parameter of the two-launch kernels): 16-byte loads a lane keeps in flight, 1, 2, 4 or 8
 
 // 16 bytes as loaded -> kVec float values
@@ -116,10 +142,10 @@ struct GnLayout {
   int pix_per_blk;
 };
 
-template <typename Tin, int NCH>
+template <typename Tin, int NCH, bool PAIR>
 __global__ void gn_stats(const Tin* __restrict__ x, float* __restrict__ partial, int pix_seg, int C, int G, int tp,
                          int ppb, int pix_per_blk, int nseg, const float* stale, float* __restrict__ stale_copy,
-                         int stale_n) {
+                         int stale_n, GnPair pr) {
   constexpr int V = Elem<Tin>::kVec;
   __shared__ float s_sum[kMaxG], s_sq[kMaxG], s_piv[kMaxG];
   const int blk = blockIdx.x, seg = blockIdx.y, b = blockIdx.z;
@@ -134,13 +160,15 @@ __global__ void gn_stats(const Tin* __restrict__ x, float* __restrict__ partial,
   if (p_hi > pix_seg) p_hi = pix_seg;
   // a lane requests NCH pixels at once (a strip is usually one chunk: the whole tensor is in flight together);
   // the first chunk goes out before anything else
+  int pitch;
+  const Tin* const xs = gn_source<PAIR>(x, pr, C, c0, &pitch);
   u32x4 raw[NCH];
 #pragma unroll
   for (int k = 0; k < NCH; ++k) {
     const int p = p_lo + psub + k * ppb;
-    raw[k] = *reinterpret_cast<const u32x4*>(x + (seg_base + (p < p_hi ? p : p_lo)) * C + c0);
+    raw[k] = *reinterpret_cast<const u32x4*>(xs + (seg_base + (p < p_hi ? p : p_lo)) * pitch);
   }
-  if (tid < G) s_piv[tid] = Elem<Tin>::ld(x + (long long)b * nseg * pix_seg * C + tid * cg);   // the groups' pivots
+  if (tid < G) s_piv[tid] = gn_value<PAIR>(x, pr, C, (long long)b * nseg * pix_seg, tid * cg);   // the groups' pivots
   // The second launch may overwrite the patch's own slot of the cached sums (in-place refresh) while other blocks of
   // it still need the old value: it reads this snapshot instead.
   if (stale != nullptr && blk == 0 && seg == 0 && b == 0)
@@ -159,7 +187,7 @@ __global__ void gn_stats(const Tin* __restrict__ x, float* __restrict__ partial,
 #pragma unroll
       for (int k = 0; k < NCH; ++k) {
         const int p = p0 + k * ppb;
-        raw[k] = *reinterpret_cast<const u32x4*>(x + (seg_base + (p < p_hi ? p : p0)) * C + c0);
+        raw[k] = *reinterpret_cast<const u32x4*>(xs + (seg_base + (p < p_hi ? p : p0)) * pitch);
       }
     }
 #pragma unroll
@@ -167,6 +195,10 @@ __global__ void gn_stats(const Tin* __restrict__ x, float* __restrict__ partial,
       if (p0 + k * ppb >= p_hi) break;
       float v[V];
       unpack_vec<Tin>(raw[k], v);
+      if constexpr (PAIR) {
+        const u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+        *reinterpret_cast<u32x2*>(pr.cat + (seg_base + p0 + k * ppb) * C + c0) = t;
+      }
 #pragma unroll
       for (int i = 0; i < V; ++i) { const float d = v[i] - piv[i]; s[i] += d; q[i] = fmaf(d, d, q[i]); }
     }
@@ -315,13 +347,14 @@ __device__ __forceinline__ void gn_stale_wave(const float* stale, int b, int g, 
 
 // Second launch of the large path.  Every block adds the partials of its batch item in the same fixed order, combines
 // them with the cached sums and normalises the strip of pixels it was given.
-template <typename Tin, typename Tout, int NCH>
+template <typename Tin, typename Tout, int NCH, bool PAIR>
 __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout* __restrict__ y,
                                                  const float* __restrict__ partial, const float* __restrict__ stale_copy,
                                                  float* sums_out, const float* __restrict__ gamma,
                                                  const float* __restrict__ beta, int pix_seg, int C, int G, int nblk,
                                                  int nseg, int B, int patch_idx, int N, float eps, int stat_mode, int tp,
-                                                 int ppb, int pix_per_blk, int silu, int packed, GnHalo halo, GnCount cnt) {
+                                                 int ppb, int pix_per_blk, int silu, int packed, GnHalo halo, GnCount cnt,
+                                                 GnPair pr) {
   constexpr int V = Elem<Tin>::kVec;
   __shared__ float s_red[2][32][kMaxG];
   __shared__ float s_mom[kMaxG][3];
@@ -337,12 +370,14 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
   const int p_lo = blk * pix_per_blk;
   int p_hi = p_lo + pix_per_blk;
   if (p_hi > pix_seg) p_hi = pix_seg;
+  int pitch;
+  const Tin* const xs = gn_source<PAIR>(x, pr, C, c0, &pitch);
   u32x4 raw[NCH];
   if (works) {
 #pragma unroll
     for (int k = 0; k < NCH; ++k) {
       const int p = p_lo + psub + k * ppb;
-      raw[k] = *reinterpret_cast<const u32x4*>(x + (base + (p < p_hi ? p : p_lo)) * C + c0);
+      raw[k] = *reinterpret_cast<const u32x4*>(xs + (base + (p < p_hi ? p : p_lo)) * pitch);
     }
   }
   {
@@ -351,7 +386,7 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
     const bool folds = part < parts;
     double tot_s = 0.0, tot_q = 0.0;  // sums of x over all segments (valid where part == 0)
     // the partials are sums of x - pivot, the pivot being the group's first value of the batch item
-    const float piv = folds ? Elem<Tin>::ld(x + (long long)b * nseg * pix_seg * C + g * cg) : 0.f;
+    const float piv = folds ? gn_value<PAIR>(x, pr, C, (long long)b * nseg * pix_seg, g * cg) : 0.f;
     const double n_seg = cnt.n_loc;
     for (int sg = 0; sg < nseg; ++sg) {
       float a = 0.f, c = 0.f;
@@ -418,7 +453,7 @@ __global__ __launch_bounds__(1024) void gn_apply(const Tin* __restrict__ x, Tout
 #pragma unroll
       for (int k = 0; k < NCH; ++k) {
         const int p = p0 + k * ppb;
-        raw[k] = *reinterpret_cast<const u32x4*>(x + (base + (p < p_hi ? p : p0)) * C + c0);
+        raw[k] = *reinterpret_cast<const u32x4*>(xs + (base + (p < p_hi ? p : p0)) * pitch);
       }
     }
 #pragma unroll
@@ -589,12 +624,13 @@ __device__ __forceinline__ void st_chan(T* p, const float* v) {
 // the moments multiplies where it divided: 300 x 1280 float32 6.4 -> 5.5 us, 64 x 1280 4.5 -> 3.9, 494 x 1280 bf16 8.2 -> 7.1, 1200 x 640
 // float32 10.5 -> 9.4, 1024 x 1280 bf16 12.6 -> 11.0 (a launch after another, 1.5 us of each the boundary).  Two launches cost ~11 us however
 // small the tensor is.
-template <typename Tin, typename Tout, int NV, int V>
+template <typename Tin, typename Tout, int NV, int V, bool PAIR>
 __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restrict__ x, Tout* __restrict__ y,
                                                             const float* stale, float* sums_out,
                                                             const float* __restrict__ gamma, const float* __restrict__ beta,
                                                             int pix, int C, int G, int B, int patch_idx, int N, float eps,
-                                                            int stat_mode, int silu, int packed, GnHalo halo, GnCount cnt) {
+                                                            int stat_mode, int silu, int packed, GnHalo halo, GnCount cnt,
+                                                            GnPair pr) {
   __shared__ float s_s[16], s_q[16];
   __shared__ float s_mr[3];
   const int g = blockIdx.x, b = blockIdx.y;
@@ -606,7 +642,9 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   const bool active = psub < ppass;
   const int c0 = g * cg + cv * V;
   const long long base = (long long)b * pix;
-  const float piv = Elem<Tin>::ld(x + base * C + g * cg);     // sums are taken of x - piv
+  const float piv = gn_value<PAIR>(x, pr, C, base, g * cg);   // sums are taken of x - piv
+  int pitch;
+  const Tin* const xs = gn_source<PAIR>(x, pr, C, c0, &pitch);
   // everything that does not depend on x is requested first: affine parameters and, in the first wave, the cached sums (lane j:
   // patch j; added only after x has been requested - waited for here they held up the wave's share of x)
   float gm[V], bt[V];
@@ -624,7 +662,7 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     const int p = psub + k * ppass;
-    ld_chan<V>(x + (base + (p < pix ? p : pix - 1)) * C + c0, v[k]);      // (without branches; absent pixels are not added)
+    ld_chan<V>(xs + (base + (p < pix ? p : pix - 1)) * pitch, v[k]);      // (without branches; absent pixels are not added)
   }
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -678,6 +716,7 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
       o4[i] = silu ? silu_f(t) : t;
     }
     const long long m = base + p;
+    if constexpr (PAIR) st_chan<V>(pr.cat + m * C + c0, v[k]);
     Tout* o = y + m * C + c0;
     if (packed) o = y + (((m >> 5) * (C >> 4) + (c0 >> 4)) * 64 + (m & 31) + 32 * ((c0 >> 3) & 1)) * 8 + (c0 & 7);
     st_chan<V>(o, o4);
@@ -714,6 +753,29 @@ size_t groupnorm_scratch_bytes(int B, int nseg, int G, int N) {
   return kScratchCounterBytes + ((size_t)B * kGnMaxStrips * G * 2 + (size_t)N * B * G * 2 + 64) * sizeof(float) + 1024;
 }
 
+namespace {
+// One launch that keeps its pixels in registers (nv > 0: that many per lane), one launch of a workgroup per group (`group`), or two.
+struct GnForm { int v, nv; bool group; };
+GnForm gn_form(const GnArgs& a) {
+  const int cg = a.C / a.G;
+  const long long pix_seg = (long long)a.Rseg * a.W, per_group = pix_seg * a.nseg * cg;
+  static const bool no_fused = tune_env("DF_GN_3K") != nullptr;   // tuning aid
+  // channels per lane of the form that keeps its pixels in registers, and pixels per pass of its 1024 lanes
+  const int v = cg % 4 == 0 ? 4 : cg % 2 == 0 ? 2 : 0;
+  const int ppass = (v && cg / v <= 1024) ? 1024 / (cg / v) : 0;
+  // up to 16 pixels per lane (a workgroup's loads then take as long as the second launch would); the kernel requests nv of them
+  // whether they are there or not, so nv is the power of two from 2 on that holds the lane's share
+  int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? 2 : 0;
+  while (nv && (long long)ppass * nv < pix_seg) nv *= 2;
+  if (no_fused) return {v, 0, false};
+  return {v, nv, !nv && cg % 4 == 0 && cg / 4 <= 1024 && per_group <= kGnGroupMaxElems};
+}
+}  // namespace
+
+bool groupnorm_takes_pair(const GnArgs& a) {
+  return a.G > 0 && a.C % a.G == 0 && a.in_dtype == DF_F32 && a.out_dtype == DF_BF16 && a.x2_from % 4 == 0 && !gn_form(a).group;
+}
+
 int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   const int vec = a.in_dtype == DF_BF16 ? 8 : 4;
   if (a.C % a.G || a.C % vec || a.G > kMaxG || a.C / vec > 1024) return DF_ESHAPE;
@@ -737,34 +799,32 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
     halo.single = ((long long)a.Rseg * a.nseg == a.halo_rpp) ? 1 : 0;
   }
   if (pix_seg <= 0 || pix_seg * a.nseg > 0x7fffffffLL) return DF_ESHAPE;
+  if (a.x2 && (!a.cat_out || a.in_dtype != DF_F32 || a.out_dtype != DF_BF16 || a.x2_from % 4 || a.x2_from <= 0 || a.x2_from >= a.C ||
+               ((uintptr_t)a.x2 % 16) || ((uintptr_t)a.cat_out % 16)))
+    return DF_EINVAL;
+  const GnPair pr = {a.x2, a.x2_from, (bf16_t*)a.cat_out};
   const double n_loc = (double)pix_seg * (double)(a.C / a.G);
   const double n_all = n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1);
   const GnCount cnt = {n_loc, 1.0 / n_loc, n_all, 1.0 / n_all};
   // small tensors: the whole GroupNorm in one launch, one workgroup per (group, batch item)
   {
-    const int cg = a.C / a.G;
-    const long long per_group = pix_seg * a.nseg * cg;
-    static const bool no_fused = tune_env("DF_GN_3K") != nullptr;   // tuning aid
-    // channels per lane of the form that keeps its pixels in registers, and pixels per pass of its 1024 lanes
-    const int v = cg % 4 == 0 ? 4 : cg % 2 == 0 ? 2 : 0;
-    const int ppass = (v && cg / v <= 1024) ? 1024 / (cg / v) : 0;
-    // up to 16 pixels per lane (a workgroup's loads then take as long as the second launch would); the kernel requests nv of them
-    // whether they are there or not, so nv is the power of two from 2 on that holds the lane's share
-    int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? 2 : 0;
-    while (nv && (long long)ppass * nv < pix_seg) nv *= 2;
-    if (!no_fused && (nv || (cg % 4 == 0 && cg / 4 <= 1024 && per_group <= kGnGroupMaxElems))) {
+    const GnForm form = gn_form(a);
+    const int v = form.v, nv = form.nv;
+    if (a.x2 && form.group) return DF_ESHAPE;
+    if (nv || form.group) {
       dim3 grid(a.G, a.B);
       if (nv) {
         // one patch: single read of x
-#define DF_GN_REG(TI, TO, NVV, VV)                                                                                    \
-  hipLaunchKernelGGL((gn_group_reg_kernel<TI, TO, NVV, VV>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
+#define DF_GN_REG(TI, TO, NVV, VV, PR)                                                                                \
+  hipLaunchKernelGGL((gn_group_reg_kernel<TI, TO, NVV, VV, PR>), grid, dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,  \
-                     a.silu, a.y_packed, halo, cnt)
+                     a.silu, a.y_packed, halo, cnt, pr)
 #define DF_GN_REG_T(NVV, VV)                                                                                          \
   {                                                                                                                   \
-    if (a.in_dtype == DF_BF16) DF_GN_REG(bf16_t, bf16_t, NVV, VV);                                                    \
-    else if (a.out_dtype == DF_BF16) DF_GN_REG(float, bf16_t, NVV, VV);                                               \
-    else DF_GN_REG(float, float, NVV, VV);                                                                            \
+    if (a.x2) DF_GN_REG(float, bf16_t, NVV, VV, true);                                                                \
+    else if (a.in_dtype == DF_BF16) DF_GN_REG(bf16_t, bf16_t, NVV, VV, false);                                        \
+    else if (a.out_dtype == DF_BF16) DF_GN_REG(float, bf16_t, NVV, VV, false);                                        \
+    else DF_GN_REG(float, float, NVV, VV, false);                                                                     \
   }
 #define DF_GN_REG_V(VV)                                                                                               \
   {                                                                                                                   \
@@ -808,20 +868,23 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   const size_t lds = (size_t)vec * L.threads * sizeof(float);
   const int thr_apply = L.threads < a.G ? a.G : L.threads;   // the fold needs a lane per group
   const int iters = L.pix_per_blk / L.ppb;              // pixels per lane and strip
-#define DF_GN_STATS(TI, NCHV)                                                                                         \
-  hipLaunchKernelGGL((gn_stats<TI, NCHV>), gs, dim3(L.threads), lds, st, (const TI*)a.x, partial, (int)pix_seg, a.C,  \
-                     a.G, L.tp, L.ppb, L.pix_per_blk, a.nseg, need_stale ? a.stale : nullptr, stale_copy, stale_n)
-#define DF_GN_APPLY(TI, TO, NCHV)                                                                                     \
-  hipLaunchKernelGGL((gn_apply<TI, TO, NCHV>), gs, dim3(thr_apply), 0, st, (const TI*)a.x, (TO*)a.y, partial,         \
+#define DF_GN_STATS(TI, NCHV, PR)                                                                                     \
+  hipLaunchKernelGGL((gn_stats<TI, NCHV, PR>), gs, dim3(L.threads), lds, st, (const TI*)a.x, partial, (int)pix_seg, a.C,  \
+                     a.G, L.tp, L.ppb, L.pix_per_blk, a.nseg, need_stale ? a.stale : nullptr, stale_copy, stale_n, pr)
+#define DF_GN_APPLY(TI, TO, NCHV, PR)                                                                                 \
+  hipLaunchKernelGGL((gn_apply<TI, TO, NCHV, PR>), gs, dim3(thr_apply), 0, st, (const TI*)a.x, (TO*)a.y, partial,         \
                      stale_copy, a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, L.nblk, a.nseg, a.B, a.patch_idx, \
-                     a.N, a.eps, a.stat_mode, L.tp, L.ppb, L.pix_per_blk, a.silu, a.y_packed, halo, cnt)
+                     a.N, a.eps, a.stat_mode, L.tp, L.ppb, L.pix_per_blk, a.silu, a.y_packed, halo, cnt, pr)
 #define DF_GN_BOTH(NCHV)                                                                                              \
   {                                                                                                                   \
-    if (a.in_dtype == DF_BF16) DF_GN_STATS(bf16_t, NCHV); else DF_GN_STATS(float, NCHV);                              \
+    if (a.x2) DF_GN_STATS(float, NCHV, true);                                                                         \
+    else if (a.in_dtype == DF_BF16) DF_GN_STATS(bf16_t, NCHV, false);                                                 \
+    else DF_GN_STATS(float, NCHV, false);                                                                             \
     DF_LAUNCH_CHECK();                                                                                                \
-    if (a.in_dtype == DF_BF16) DF_GN_APPLY(bf16_t, bf16_t, NCHV);                                                     \
-    else if (a.out_dtype == DF_BF16) DF_GN_APPLY(float, bf16_t, NCHV);                                                \
-    else DF_GN_APPLY(float, float, NCHV);                                                                             \
+    if (a.x2) DF_GN_APPLY(float, bf16_t, NCHV, true);                                                                 \
+    else if (a.in_dtype == DF_BF16) DF_GN_APPLY(bf16_t, bf16_t, NCHV, false);                                         \
+    else if (a.out_dtype == DF_BF16) DF_GN_APPLY(float, bf16_t, NCHV, false);                                         \
+    else DF_GN_APPLY(float, float, NCHV, false);                                                                      \
   }
   if (iters <= 1) DF_GN_BOTH(1) else if (iters <= 2) DF_GN_BOTH(2) else if (iters <= 4) DF_GN_BOTH(4) else DF_GN_BOTH(8)
 #undef DF_GN_BOTH

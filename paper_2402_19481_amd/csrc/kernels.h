@@ -55,7 +55,13 @@ struct GnArgs {
   int halo_cols;
   int y_packed;         // bf16 output in the fragment-packed layout of wgemm.hip (rows = B*rows*W pixels, K = C)
   const Scratch* scr;   // scratch region of the caller (a plan's), or nullptr: the library's per-device region
+  // not null: x holds the first x2_from channels of every pixel ([..., x2_from]) and x2 the others ([..., C - x2_from]); cat_out [..., C]
+  // receives all of them in bf16.  Float in, bf16 out, and where groupnorm_takes_pair says so.
+  const float* x2;
+  int x2_from;
+  void* cat_out;
 };
+bool groupnorm_takes_pair(const GnArgs& a);
 int launch_groupnorm(const GnArgs& a, hipStream_t st);
 // Per-strip (sum, sum of squares) of a full image split into N vertical strips: x [B, R, W, C] (float or bf16) ->
 // sums [N, B, G, 2], the content of the GroupNorm cache after a synchronous step on vertical strips.

@@ -409,8 +409,11 @@ struct Exec {
           [&] { return launch_gemm_bf16(g, st); });
   }
 
+  // Concatenation [a, b] along the channels: the GroupNorm that reads it takes the two tensors and leaves the bf16 copy for the shortcut; where
+  // it cannot, both forms are written out first.
+  struct Cat { const float *a, *b; int ca, cb; float* f32; bf16_t* bf; };
   void groupnorm(const std::string& name, const void* x, int in_dtype, int level_rows, int W, int C, float eps, int silu,
-                 bf16_t* y, int y_packed = 0, bf16_t* halo_entry = nullptr) {
+                 bf16_t* y, int y_packed = 0, bf16_t* halo_entry = nullptr, const Cat* cat = nullptr) {
     // level_rows: rows of x in this mode
     const int G = c.groups;
     float* entry = (float*)stale_buf(name + ".stats", (size_t)N() * B() * G * 2 * sizeof(float));
@@ -425,6 +428,12 @@ struct Exec {
     a.stat_mode = gn_mode;
     a.y_packed = y_packed;
     a.scr = scr;
+    const auto whole = [&] {
+      timed(PC_ELEMENTWISE, 0.0, 10.0 * B() * level_rows * W * C, [&] {
+        return launch_concat(cat->a, cat->ca, cat->b, cat->cb, cat->f32, cat->bf, (long long)B() * level_rows * W, st);
+      });
+    };
+    if (cat && full() && cols()) { whole(); cat = nullptr; }   // (the strips' sums take one tensor)
     if (halo_entry && (full() || refresh)) {
       // the consumer convolution's boundary-row (boundary-column) state is refreshed by this kernel's store loop
       a.halo_out = halo_entry; a.halo_npatch = N();
@@ -444,9 +453,18 @@ struct Exec {
       a.nseg = 1; a.Rseg = level_rows; a.N = N(); a.patch_idx = patch; a.stale = entry;
       a.sums_out = refresh ? entry + (size_t)patch * B() * G * 2 : nullptr;
     }
-    const double el = (double)B() * level_rows * W * C;
+    double el = (double)B() * level_rows * W * C;
+    if (cat) {
+      a.x = cat->a; a.x2_from = cat->ca;
+      if (groupnorm_takes_pair(a)) {
+        a.x2 = cat->b; a.cat_out = cat->bf;
+      } else {
+        whole();
+        a.x = x;
+      }
+    }
     label = "groupnorm " + dims({B() * level_rows, W, C}) + (in_dtype == DF_BF16 ? " bf16" : " f32");
-    timed(PC_GROUPNORM, 0.0, el * (in_dtype == DF_BF16 ? 2.0 : 4.0) + el * 2.0, [&] { return launch_groupnorm(a, st); });
+    timed(PC_GROUPNORM, 0.0, el * (in_dtype == DF_BF16 ? 2.0 : 4.0) + el * (a.x2 ? 4.0 : 2.0), [&] { return launch_groupnorm(a, st); });
   }
 
   // x: bf16 [B, R, W, Cin] rows of this mode; out: [B, R/stride, W/stride, Cout]
@@ -530,7 +548,7 @@ struct Exec {
   }
 
   // x_bf: bf16 copy of x if the caller already has one (operand of the 1x1 shortcut), else nullptr
-  void resblock(const BlockDesc& b, const float* x, const bf16_t* emb_act, float* out, const bf16_t* x_bf = nullptr) {
+  void resblock(const BlockDesc& b, const float* x, const bf16_t* emb_act, float* out, const bf16_t* x_bf = nullptr, const Cat* cat = nullptr) {
     const int R = rows(b.level), W = width(b.level);
     const size_t px = (size_t)B() * R * W;
     const size_t mark = top;
@@ -542,7 +560,7 @@ struct Exec {
     bf16_t* e1 = conv_entry(b.name + ".conv1", cols() ? R : W, b.cin);
     bf16_t* e2 = conv_entry(b.name + ".conv2", cols() ? R : W, b.cout);
     const bool hd = dry || e1 != nullptr;      // the GroupNorm kernels refresh the boundary rows of the convolutions
-    groupnorm(b.name + ".gn1", x, DF_F32, R, W, b.cin, 1e-5f, 1, a1, 0, e1);
+    groupnorm(b.name + ".gn1", x, DF_F32, R, W, b.cin, 1e-5f, 1, a1, 0, e1, cat);
     conv(b.name + ".conv1", a1, R, W, b.cin, b.cout, 1, h1, DF_BF16, embp, nullptr, e1, hd, emb_n);
     groupnorm(b.name + ".gn2", h1, DF_BF16, R, W, b.cout, 1e-5f, 1, a2, 0, e2);
     const float* residual = x;
@@ -891,13 +909,20 @@ struct Exec {
             skips.pop_back();
             skip_c.pop_back();
             float* cat = (float*)alloc(px * (size_t)(cur_c + sc) * 4);
-            bf16_t* catb = (bf16_t*)alloc(px * (size_t)(cur_c + sc) * 2);   // the shortcut's operand, written by the same kernel
-            timed(PC_ELEMENTWISE, 0.0, 10.0 * px * (cur_c + sc),
-                  [&] { return launch_concat(cur, cur_c, sk, sc, cat, catb, (long long)px, st); });
+            bf16_t* catb = (bf16_t*)alloc(px * (size_t)(cur_c + sc) * 2);   // the shortcut's operand
             xin = cat;
             xin_bf = dry ? nullptr : catb;
+            const Cat both = {cur, sk, cur_c, sc, cat, catb};
+            if (b.cin != b.cout) {
+              resblock(b, xin, emb_act, out, xin_bf, &both);
+            } else {                                     // (the floats are the block's residual too)
+              timed(PC_ELEMENTWISE, 0.0, 10.0 * px * (cur_c + sc),
+                    [&] { return launch_concat(cur, cur_c, sk, sc, cat, catb, (long long)px, st); });
+              resblock(b, xin, emb_act, out, xin_bf);
+            }
+          } else {
+            resblock(b, xin, emb_act, out, xin_bf);
           }
-          resblock(b, xin, emb_act, out, xin_bf);
           top = mark;
           cur = out; cur_c = b.cout;
           break;
