@@ -868,7 +868,7 @@ constexpr TileCfg kTiles[] = {
     {4, 4, 1, 4, 1.59, 0.468, {4.0, 3.6, 6.5, 6.0}, 1.0},         // 128 x 128, four ring stages
     {2, 4, 2, 4, 3.11, 0.602, {3.4, 3.0, 4.8, 8.3}, 0.63},        // 64 x 128, two k-groups, two workgroups per unit
     {2, 2, 2, 8, 2.52, 0.407, {1e9, 2.9, 2.4, 7.3}, 0.78},        // 64 x 64, two k-groups, two workgroups per unit
-    {2, 2, 1, 8, 2.31, 0.224, {1e9, 2.8, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128
+    {2, 2, 1, 8, 2.31, 0.224, {1e9, 2.8, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128 (plain: kPlain64)
     {4, 10, 1, 2, 1.43, 1.056, {6.0, 7.5, 13.3, 1e9}, 1.0},       // 128 x 320, eight waves of 32 x 160
     {2, 3, 1, 8, 2.83, 0.281, {1e9, 4.3, 3.2, 1e9}, 1.0},         // 64 x 96, four k-groups of 32 x 96
     {4, 5, 1, 4, 1.88, 0.551, {1e9, 9.5, 8.6, 1e9}, 1.0},         // 128 x 160, two k-groups of 32 x 160
@@ -914,10 +914,16 @@ int launch_bgemm(const WParams& p, int cfg, hipStream_t st) {
 namespace {
 // Parts of K, for plain layers whose tiles cover part of the chip: one round of workgroups in all.  `fixed` is the time of
 // the second launch and of what the parts do beside their stages; each part's sums cost a write and a read.
+// `fixed` and kPartUs of the first tile are from a step's layers of 1280 x 5120 with 160 to 1152 tokens (20 counts), against the
+// wave-level kernel; so is kCrowdUs, what parts lose that take more than kCrowd units (576 tokens: four parts of 50 workgroups 1.2 us
+// below the wave-level kernel, five 4 us above; 288: six 0.1 below, seven 0.8 - 3 above, eight 2.5).
 struct SplitCfg { int tile; double fixed; };
-constexpr SplitCfg kSplits[] = {{2, 4.3}, {6, 5.0}};
+constexpr SplitCfg kSplits[] = {{2, 0.9}, {6, 3.0}};
 constexpr int kMaxParts = 8, kSplitFamily = 7;          // (the first tiles: those that parts of K were weighed against)
-constexpr double kPartUs = 2.2e-6;                     // microseconds per output value and part
+constexpr double kPartUs = 2.0e-6;                     // microseconds per output value and part, and per value of the sums
+constexpr double kCrowdUs = 2.5;
+constexpr int kCrowd = 200;
+constexpr double kPlain64 = 0.012;                     // more per slab of the 64 x 64 tile in a plain layer of the step
 
 int max_parts(const TileCfg& t, long long MT, long long NF) {
   const long long n = ((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf);
@@ -954,21 +960,24 @@ int pick_bgemm(const WParams& p, double other_us, long long room, int* parts) {
       const long long rem = n % 512;
       r = n > 1536 ? n / 512.0 : (double)(n / 512) + (rem == 0 ? 0.0 : rem <= 256 ? t.alone : 1.0);
     }
-    const double us = t.base + r * (kt * t.slab + t.epi[mode]);
+    const double us = t.base + r * (kt * (t.slab + (c == 5 && mode == 2 && !p.ln_s ? kPlain64 : 0.0)) + t.epi[mode]);
     if (us < best) { best = us; pick = c; *parts = 1; }
   };
   *parts = 1;
   for (int c = 0; c < kSplitFamily; ++c) consider(c);
+  // In the step, 494 x 1280 x 5120 takes 1.5 us less in five parts than on the wave-level kernel, 256 0.7 less in eight, 576 1.2 less in
+  // four; the error against 64 bits is that of the whole layer (494: 1.19e-7 against 1.29e-7 relative).
   // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts.  At 640 features and K = 2560 and below the sums cost what
   // the parts gain.
   if (mode == 2 && !p.ln_s && room > 1) {
     for (const SplitCfg& q : kSplits) {
       const TileCfg& t = kTiles[q.tile];
       const int most = max_parts(t, MT, NF);
+      const long long tiles = (long long)((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf);
       for (int s = 2; s <= most && s <= room; ++s) {
         if (kt / s < 8) break;
-        const double us = t.base + std::ceil(kt / s) * t.slab + q.fixed + kPartUs * s * (32.0 * MT) * p.N;
-        if (us < 0.97 * best) { best = us / 0.97; pick = q.tile; *parts = s; }
+        const double us = t.base + std::ceil(kt / s) * t.slab + q.fixed + kPartUs * (s + 1) * (32.0 * MT) * p.N + (tiles * s > kCrowd ? kCrowdUs : 0.0);
+        if (us < (pick < 0 || *parts > 1 ? best : 0.97 * best)) { best = us; pick = q.tile; *parts = s; }
       }
     }
   }

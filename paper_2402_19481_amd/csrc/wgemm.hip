@@ -700,7 +700,10 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     const double kt = a.K / 64.0;
     const bool two = wg12 >= 320 && !a.xa_kv;
     const double n = wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)wg12;
-    const double r = n / 256.0 > 0.6 ? n / 256.0 : 0.6;
+    // A plain layer takes the same time for 140 as for 240 workgroups, one per unit: 1280 x 5120 in the step 14.6 - 15.2 us with 224 to
+    // 384 tokens, 19 - 20 with 494 to 768.  By the share of the units 704 and 768 were predicted 24 - 25 and went to the 64 x 64 tiles,
+    // which take 23 (768 tokens, whole step: 10449 -> 10154 us).
+    const double r = plain ? (n <= 256.0 ? (two ? 0.68 : 0.66) : n / 256.0) : n / 256.0 > 0.6 ? n / 256.0 : 0.6;
     const double us = wide ? 9.7 + 0.125 * kt
                       : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : p.ln_s ? 0.23 : 0.9))
                       : a.xa_kv ? 5.3 + r * (0.189 * kt + 0.1)
