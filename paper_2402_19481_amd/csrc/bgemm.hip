@@ -858,14 +858,15 @@ namespace {
 // that no cache holds.  Chosen by them (and the wave-level kernel's, see wgemm.hip), those layers take 1.3 % more than with the
 // best of 18 shapes.  The columns of GEGLU, QKV and cross-attention are from after the epilogues in the accumulators: GEGLU layers of 256 -
 // 7200 tokens (18 counts x 2) take 1.4 % more than with the best of the nine shapes that have it, QKV and cross-attention layers in the
-// step (7 images x 2 levels) were fitted to the step's time.  The 96-, 160- and 192-wide tiles and 256 x 256 are there because a round of workgroups over 256 units is
+// step (7 images x 2 levels) were fitted to the step's time, cross-attention again (20 images) after the wave-level kernel spread it over
+// its waves: 4096 tokens of 640 features 2.3 us less on 128 x 128 with a unit to itself, 1224 of 1280 about 3 less on the wave-level kernel.  The 96-, 160- and 192-wide tiles and 256 x 256 are there because a round of workgroups over 256 units is
 // rarely full: 7200 x 640 x 2560 44.9 -> 33.2 us, 4096 x 1280 x 1280 28.8 -> 24.7, 1976 x 640 x 2560 23.3 -> 18.1, 4096 x 3840 x
 // 1280 55.7 -> 44.2, 494 x 10240 x 1280 with GEGLU 27.3 -> 24.7, 1024 x 1280 x 1280 12.7 -> 12.0.
 struct TileCfg { int bt, bf, occ, kf; double base, slab, epi[4], alone; };
 constexpr TileCfg kTiles[] = {
     {8, 10, 1, 2, 1.51, 1.886, {8.5, 28.6, 19.2, 1e9}, 1.0},      // 256 x 320, eight waves of 64 x 160
     {4, 4, 2, 4, 3.00, 0.982, {2.2, 3.6, 8.0, 3.2}, 0.71},        // 128 x 128, eight waves of 32 x 64, two workgroups per unit
-    {4, 4, 1, 4, 1.59, 0.468, {4.0, 3.6, 6.5, 6.0}, 1.0},         // 128 x 128, four ring stages
+    {4, 4, 1, 4, 1.59, 0.468, {4.0, 3.6, 6.5, 5.2}, 1.0},         // 128 x 128, four ring stages
     {2, 4, 2, 4, 3.11, 0.602, {3.4, 3.0, 4.8, 8.3}, 0.63},        // 64 x 128, two k-groups, two workgroups per unit
     {2, 2, 2, 8, 2.52, 0.407, {1e9, 2.9, 2.4, 7.3}, 0.78},        // 64 x 64, two k-groups, two workgroups per unit
     {2, 2, 1, 8, 2.31, 0.224, {1e9, 2.8, 2.1, 6.6}, 1.0},         // 64 x 64, two k-groups, four stages of 128 (plain: kPlain64)

@@ -706,7 +706,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     const double r = plain ? (n <= 256.0 ? (two ? 0.68 : 0.66) : n / 256.0) : n / 256.0 > 0.6 ? n / 256.0 : 0.6;
     const double us = wide ? 9.7 + 0.125 * kt
                       : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : p.ln_s ? 0.23 : 0.9))
-                      : a.xa_kv ? 5.3 + r * (0.189 * kt + 0.1)
+                      : a.xa_kv ? 5.3 + r * (0.165 * kt + 0.1)
                                 : 3.46 + r * (0.201 * kt + (p.geglu ? 2.1 : p.nseg ? 2.2 : p.ln_s ? 0.49 : 0.34));
     const char* e = tune_env("DF_BGEMM");
     // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
