@@ -420,8 +420,10 @@ constexpr TileCfg kTiles[] = {
     {64, 160, 3, 3.48, 3.270, 4.10},
     {64, 64, 2, 1.30, 1.339, 2.67},
 };
-// a second kernel adds the parts: microseconds of it, and per output value and part
-constexpr double kSplitUs = 4.98, kPartUs = 1.069e-6;
+// A second kernel adds the parts: microseconds of it, and per output value and part.  Refitted to which tile and parts are best on 64 layers
+// after the kernel's last change (by 4.98 and 1.07e-6 layers took too many parts: 24 x 24 pixels x 1280 x 1280 five of 128 x 128, where two of
+// 128 x 64 are faster; one patch of 576 tokens at the deepest level, whole step, 9618 -> 9437 us).
+constexpr double kSplitUs = 3.25, kPartUs = 1.8e-6;
 constexpr int kMaxSplit = 16, kMaxSplitWgs = 640;
 
 }  // namespace
