@@ -68,7 +68,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // of arguments first used under a condition (norm vectors, bias, residual, operand pointers) are issued where that
   // code starts, and the prologue of these few-microsecond kernels became a chain of four or five dependent round
   // trips to the scalar cache.
-  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.mg_magic), "s"(p.kfw_magic), "s"(p.mgroups), "s"(p.kfw),
+  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.mg_recip), "s"(p.kfw_recip), "s"(p.mgroups), "s"(p.kfw),
                "s"(p.bias), "s"(p.ln_s), "s"(p.ln_t), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the k-walk and tile addresses stay off the vector ALU
@@ -85,8 +85,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int base = nwg >> 3, rem = nwg & 7;
     t = xcd * base + (xcd < rem ? xcd : rem) + loc;
   }
-  // t / MG (the launcher: t MG < 2^32; the reciprocal of 1 does not fit)
-  const int ng = MG == 1 ? t : (int)(((unsigned long long)(unsigned int)t * p.mg_magic) >> 32), mg = t - ng * MG;
+  const int ng = (int)quotient_u32((unsigned int)t, (unsigned int)MG, p.mg_recip), mg = t - ng * MG;
   const int KF = p.K >> 4, KFw = p.kfw;                // k-fragments of a wave
   const int kf0 = ((PART ? (int)blockIdx.y * KSPLIT : 0) + wave) * KFw;
 #ifdef DF_TUNING
@@ -114,7 +113,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // streams of all waves are otherwise aligned modulo the fragment-row pitch and hit the same few L2 / memory
   // channels at any moment.  The order is a fixed function of the tile, so results stay reproducible.
   const unsigned int rsum = (unsigned int)(mg * 7 + ng * 3 + wave * 5);
-  const int rot = KFw == 1 ? 0 : (int)(rsum - (unsigned int)KFw * (unsigned int)(((unsigned long long)rsum * p.kfw_magic) >> 32));   // rsum % KFw
+  const int rot = (int)(rsum - (unsigned int)KFw * quotient_u32(rsum, (unsigned int)KFw, p.kfw_recip));   // rsum % KFw
   auto pos = [&](int step) {
     const int k = step + rot;
     return (size_t)(k < KFw ? k : k - KFw) * 64;
@@ -540,11 +539,11 @@ int launch_one(const WParams& pin, hipStream_t st) {
   if (KF % KSPLIT) return DF_ESHAPE;
   constexpr int RP = (KSPLIT * TM * TN * 4 <= 128) ? TM : (TM % 2 == 0 && KSPLIT * (TM / 2) * TN * 4 <= 128) ? TM / 2 : 1;
   constexpr int smem = KSPLIT * RP * TN * 4 * 1024 + KSPLIT * TM * 32 * 2 * 4 + (XA > 0 ? 4096 : 0) + 4 * 128 * 4;
-  // reciprocals for the tile indices and for the waves' first fragments (x / d = x * magic >> 32 while x d < 2^32)
+  // reciprocals for the tile indices and for the waves' first fragments
   p.mgroups = MG; p.kfw = KF / KSPLIT / (PART ? p.parts : 1);
-  if (p.kfw < 1 || (long long)MG * NG * MG >= (1LL << 32) || (7LL * MG + 3LL * NG + 20) * p.kfw >= (1LL << 32)) return DF_ESHAPE;
-  p.mg_magic = (unsigned int)(((1ULL << 32) + MG - 1) / MG);
-  p.kfw_magic = (unsigned int)(((1ULL << 32) + p.kfw - 1) / p.kfw);
+  if (p.kfw < 1) return DF_ESHAPE;
+  p.mg_recip = reciprocal_u32((unsigned int)MG);
+  p.kfw_recip = reciprocal_u32((unsigned int)p.kfw);
   auto k = wgemm_kernel<TM, TN, KSPLIT, PF, LN, XA, PART, MODE>;
   static bool attr_set = false;
   if (!attr_set) {
