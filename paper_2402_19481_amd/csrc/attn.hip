@@ -85,9 +85,13 @@ __device__ long long g_attn_trace[512 * 32];
 //     exponential's argument is the accumulator itself; otherwise one fma per score.
 //   - The running maximum m is that of a range's first tile and moves only when a tile has probabilities far above 1 (so P stays
 //     far inside float and bf16 range; relative precision is that of any other scaling).  The sum of a lane's 32 probabilities,
-//     which it needs anyway, tells: beyond 256, at the latest where one of them overflows, the wave drops the tile's probabilities
-//     (nothing has read them yet) and does the tile again from memory in a branch beside the loop.  Watching the maximum of the
-//     scores instead took 16 instructions per tile, and their latency between the last matrix instruction and the barrier.
+//     which it needs anyway, tells: beyond 2^13 (32 of 2^8) the wave moves m by the power of two above the sum and scales what it has
+//     by it, the tile's packed probabilities exactly; beyond 2^100, at the latest where one of them overflows, it drops them (nothing
+//     has read them yet) and does the tile again from memory, in a branch beside the loop.  Watching the maximum of the scores
+//     instead took 16 instructions per tile, and their latency between the last matrix instruction and the barrier.  A tile from memory
+//     stalls the workgroup for some 2 us: with one for every sum beyond 256, peaked scores took 1024 x 4096 x 10 heads from 25 us
+//     (standard deviation of 0.25 nats) to 33 (4) and 43 (8), 4096 x 16384 x 10 with the scale from 175 to 217 and 273; now 24.6, 25.1 and
+//     30.7, 174, 186 and 222.
 //   - Row sums add the float probabilities, not the rounded ones the matrix instructions take: the rounding of a heavy key
 //     would otherwise enter every feature of the row (a key of weight 0.9 with values near zero: 2.0e-3 of error against 1.4e-3,
 //     where the rounding of the result alone is 1.4e-3; random scores differ by less than 7 % in either direction).  Sums
@@ -405,6 +409,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     sync_tile(std::integral_constant<int, 4>{});           // K_{tl+1} and V_{tl-1} of the next tile have landed, for every wave
     return tsum;
   };
+  constexpr float kMove = 0x1p13f, kRedo = 0x1p100f;
   // A tile with probabilities far above 1: its scores once more, from memory (K's slot is taken), and its probabilities and the
   // sums relative to a maximum that covers them.  Nothing has read them yet.
   auto redo = [&]() {
@@ -435,7 +440,24 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     return tsum;
   };
 
-  bool again = false;                                      // tile tl has to be done again (NaN passes on as it is)
+  // A tile with a large sum that its probabilities and the sum still hold: m up by the power of two above it, for the query's two lanes
+  auto lower = [&](float tsum) {
+    const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(tsum)));
+    const float s = fmaxf(tsum, part);
+    const int k = s > kMove ? __builtin_amdgcn_frexp_expf(s) : 0;
+    const float scale = __builtin_amdgcn_ldexpf(1.0f, -k);
+    move_to(m_run + (float)k);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float lo = __uint_as_float(pk[u][q] << 16) * scale, hi = __uint_as_float(pk[u][q] & 0xffff0000u) * scale;
+        pk[u][q] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+      }
+  };
+
+  bool again = false;                                      // tile tl has a large sum (NaN passes on as it is)
+  float tsum = 0.f;
   auto values = [&](bool last) {                           // O += V P of the pending tile
     VTile vt;
     if constexpr (SRC != kSrcVt) { vrequest(base, vt); varrive(vt, H1{}); varrive(vt, H2{}); }
@@ -455,7 +477,12 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   };
   for (;;) {
     if (again) {
-      l_run += redo();
+      if (__builtin_amdgcn_ballot_w64(tsum > kRedo)) {
+        l_run += redo();
+      } else {
+        l_run += tsum;
+        lower(tsum);
+      }
       advance();
       if (tl >= ntiles) break;
     }
@@ -476,8 +503,8 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     }
     again = false;
     while (tl < nfull) {
-      const float tsum = tile(std::true_type{});
-      again = __builtin_amdgcn_ballot_w64(tsum > 256.f) != 0;
+      tsum = tile(std::true_type{});
+      again = __builtin_amdgcn_ballot_w64(tsum > kMove) != 0;
       if (again) break;
       l_run += tsum;
       advance();
