@@ -160,9 +160,6 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, const WOut& o, i
 
 // Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
-// Tile shape predicted to be faster than the wave-level kernel's `other_us`, or -1, and the parts to split K into: at most `room`,
-// which the caller's scratch holds.
-int pick_bgemm(const WParams& p, double other_us, long long room, int* parts);
 int launch_part_sums(const WParams& p, hipStream_t st);
 
 // Parts of K that the scratch handed to a plain layer (MT token rows of 32, NF feature rows of 32, K) has to hold; 1: any scratch

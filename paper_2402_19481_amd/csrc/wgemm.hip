@@ -21,7 +21,7 @@
 // makes those 16 features two runs of 8 consecutive ones: exactly the 16 bytes that the same lane of the *next*
 // layer's activation fragment holds.  The epilogue therefore writes the next layer's packed operand with one
 // 16-byte store per lane and no data exchange.
-#include "wgemm.h"
+#include "wchoice.h"
 
 namespace df {
 
@@ -672,20 +672,10 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     p.xkv = (const bf16x8*)a.xa_kv; p.xa_keys = a.xa_keys; p.xa_rows = a.xa_rows; p.xa_scale = a.xa_scale;
     p.xa_bstride = a.xa_bstride / 8;
   }
-  const int nfrag = Nout / 32;
-  // Measured with cold weights.  Up to 128 wave tiles of 32 tokens x 64 features the 32 x 32 tile puts twice the
-  // workgroups on the chip: such a layer waits for its weights, which a compute unit pulls from HBM at no more than 25
-  // bytes per cycle (64 x 1280 x 5120 18.4 -> 13.1 us, 150 x 1280 x 1280 6.4 -> 5.2; at 140 tiles it loses).  Up to ~320
-  // the 32 x 64 tile keeps the most waves in flight; from there on the 64 x 64 tile's lower operand traffic per flop wins;
-  // and where a still larger tile (64 x 96 without GEGLU) covers the output with at most one workgroup per unit, its single
-  // round of workgroups wins again, provided the reduction is long enough to amortise the row-by-row epilogue.
-  const int MT = (a.M + 31) / 32;
-  const long long wg12 = (long long)MT * (p.geglu ? nfrag : nfrag / 2);
-  const bool few = wg12 <= 128;
-  const bool long_k = a.K / 16 / 4 >= 16;
-  const bool wide = wg12 >= 320 && long_k && !p.geglu && nfrag % 3 == 0 && (long long)((MT + 1) / 2) * (nfrag / 3) <= 256 && !a.xa_kv;
+  const WaveForm wave = wave_form(p);
+  const int nfrag = Nout / 32, MT = (a.M + 31) / 32;
   // Parts of K that the caller's scratch holds.  Only plain layers split.
-  const bool plain = !a.ln_s && !p.geglu && !p.nseg && !a.xa_kv;
+  const bool plain = is_plain(p);
   const size_t part_bytes = (size_t)MT * nfrag * 4096;
   const long long room = plain && a.scr && a.scr->ptr && a.scr->bytes > kScratchCounterBytes
                              ? (long long)((a.scr->bytes - kScratchCounterBytes) / part_bytes) : 0;
@@ -694,23 +684,9 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
     if (due > 1 && due > room) return DF_ENOMEM;
   }
   {
-    // Predicted time of the wave-level kernel (microseconds: launch + rounds of workgroups x (K loop + epilogue), fitted
-    // like the tile kernel's table): it keeps the problems whose token count does not fill the tiles of bgemm.hip.
-    const double kt = a.K / 64.0;
-    const bool two = wg12 >= 320 && !a.xa_kv;
-    const double n = wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)wg12;
-    // A plain layer takes the same time for 140 as for 240 workgroups, one per unit: 1280 x 5120 in the step 14.6 - 15.2 us with 224 to
-    // 384 tokens, 19 - 20 with 494 to 768.  By the share of the units 704 and 768 were predicted 24 - 25 and went to the 64 x 64 tiles,
-    // which take 23 (768 tokens, whole step: 10449 -> 10154 us).
-    const double r = plain ? (n <= 256.0 ? (two ? 0.68 : 0.66) : n / 256.0) : n / 256.0 > 0.6 ? n / 256.0 : 0.6;
-    const double us = wide ? 9.7 + 0.125 * kt
-                      : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : p.ln_s ? 0.23 : 0.9))
-                      : a.xa_kv ? 5.3 + r * (0.165 * kt + 0.1)
-                                : 3.46 + r * (0.201 * kt + (p.geglu ? 2.1 : p.nseg ? 2.2 : p.ln_s ? 0.49 : 0.34));
-    const char* e = tune_env("DF_BGEMM");
-    // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
     int parts = 1;
-    const int c = e ? atoi(e) : few ? -1 : pick_bgemm(p, 0.98 * us, room, &parts);
+    const char* e = tune_env("DF_BGEMM");
+    const int c = e ? atoi(e) : choose_tile(p, wave, room, &parts);
     if (e && a.scr && tune_env("DF_PARTS")) parts = atoi(tune_env("DF_PARTS"));
     if (parts > 1) {
       if (parts > room) return DF_ENOMEM;                // (an override's)
@@ -743,15 +719,15 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   // workgroup per unit, and a second launch for the sums.  Against the 32 x 32 tile, cold weights: 32 x 1280 x 5120 14.3 -> 10.2 us, 64 x
   // 1280 x 5120 13.2 -> 11.3, 96 x 1280 x 5120 12.6 -> 11.3; with K = 2560 8.1 against 9.3, with 128 tokens (320 workgroups) 12.1
   // against 14.6.  Without enough scratch the layer stays whole (parts_due has none of these).
-  if (few && plain && room >= 4 && nfrag % 2 == 0 && a.K >= 4096 && (a.K % 1280 == 0 || a.K % 1024 == 0) && 4 * wg12 <= 256 &&
+  if (wave.few && plain && room >= 4 && nfrag % 2 == 0 && a.K >= 4096 && (a.K % 1280 == 0 || a.K % 1024 == 0) && 4 * wave.tiles <= 256 &&
       !tune_env("DF_BGEMM")) {
     p.parts = 4;
     p.partials = (f32x4*)(a.scr->ptr + kScratchCounterBytes);
     return launch_cfg<1, 2, 4, 5>(p, st);
   }
-  if (!p.geglu && (nfrag % 2 || few)) return launch_cfg<1, 1, 4, 5>(p, st);
-  if (wide) return launch_cfg<2, 3, 4, 5>(p, st);
-  if (wg12 >= 320) return launch_cfg<2, 2, 4, 5>(p, st);
+  if (!p.geglu && (nfrag % 2 || wave.few)) return launch_cfg<1, 1, 4, 5>(p, st);
+  if (wave.wide) return launch_cfg<2, 3, 4, 5>(p, st);
+  if (wave.tiles >= 320) return launch_cfg<2, 2, 4, 5>(p, st);
   return launch_cfg<1, 2, 4, 5>(p, st);
 }
 

@@ -1,5 +1,5 @@
 """Packed linear layers whose epilogue runs in the accumulators (one k-group): pairs that two waves share, ragged tiles, every output
-form, and the form with a single packed output."""
+form, and the form with a single packed output.  The tile of each row is asserted by test_linear_choice.py."""
 import numpy as np
 import pytest
 
@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (4065, 5120, 640, False),          # bias in place of the norm
     (2590, 5120, 640, True),           # 256 x 256
     (494, 10240, 1280, False),         # 128 x 192: one pair and a share of the next
+    (494, 10240, 1280, True),
+    (1131, 5120, 640, True),
 ])
 def test_geglu_in_the_accumulators(M, N, K, ln):
     say("geglu epilogue", M, N, K, ln)

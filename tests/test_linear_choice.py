@@ -1,0 +1,54 @@
+"""The kernel that each test of a packed linear layer names in its comments is the one that the dispatch gives its size to: a refit of the
+predicted times that moves a test off its tile fails here (wchoice.h on the host; no GPU)."""
+import shutil
+
+import pytest
+
+import test_gpu_k_tails
+import test_gpu_linear_epilogue
+import test_gpu_linear_parts_choice
+import test_gpu_linear_tiles
+import test_gpu_ops
+from linear_choice import WAVE, choices
+
+pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs the compiler")
+
+
+def rows(test):
+    return [tuple(r) for r in test.pytestmark[0].args[1]]
+
+
+def check(layers, want):
+    assert len(layers) == len(want)
+    wrong = [(l, got, w) for l, (got, parts), w in zip(layers, choices(layers), want) if (got, parts) != (w, 1)]
+    assert not wrong, wrong
+
+
+def test_layers_of_few_stages():
+    check(rows(test_gpu_k_tails.test_linear_of_few_stages),
+          ["128x128/2"] * 2 + ["128x192"] * 3 + ["128x96"] + ["64x64"] * 6 + ["128x320"] * 3 + ["256x320", "128x128", WAVE])
+    check([(m, c, c, "xa") for m, c, _ in rows(test_gpu_k_tails.test_cross_attention_of_few_stages)],
+          [WAVE] * 3 + ["128x128/2"] + ["128x128"] * 3)
+
+
+def test_layers_of_the_less_common_tiles():
+    check(rows(test_gpu_linear_tiles.test_linear_packed_more_tiles),
+          ["64x96"] * 2 + ["128x160"] * 2 + ["256x256"] * 2 + ["128x96"] * 2 + ["128x192"] * 2 + ["128x128/2"] * 2)
+
+
+def test_layers_with_the_epilogue_in_the_accumulators():
+    check([(m, n, k, "ln_geglu" if ln else "geglu") for m, n, k, ln in rows(test_gpu_linear_epilogue.test_geglu_in_the_accumulators)],
+          ["128x128"] + ["128x320"] * 2 + ["256x320"] * 2 + ["256x256"] + ["128x192"] * 3)
+
+
+def test_layers_of_the_operation_tests():
+    check([(m, n, k, v.replace("_far", "")) for m, n, k, v in rows(test_gpu_ops.test_linear_packed_tiles)],
+          ["64x64", "128x96", "128x96", "128x96", "128x128/2", "128x128", "128x128", "64x64/2", "256x320", "128x320", "128x320"])
+    check([(b * m, c, c, "xa") for b, m, c, *_ in rows(test_gpu_ops.test_cross_attn_packed)],
+          [WAVE] * 4 + ["64x128/2", "128x128", "128x128", "128x128/2"])
+
+
+def test_parts_of_middle_sizes():
+    """Token counts on either side of each change of the number of parts, with scratch for eight."""
+    counts = test_gpu_linear_parts_choice.test_linear_packed_parts_of_middle_sizes.pytestmark[0].args[1]
+    assert [n for _, n in choices([(m, 1280, 5120, "plain", 8) for m in counts])] == [8, 8, 1, 5, 5, 4, 1, 1, 1]
