@@ -36,16 +36,19 @@ constexpr TileCfg kTiles[] = {
 
 // Parts of K, for plain layers whose tiles cover part of the chip: one round of workgroups in all.  `fixed` is the time of
 // the second launch and of what the parts do beside their stages; each part's sums cost a write and a read.
-// `fixed` and kPartUs of the first tile are from a step's layers of 1280 x 5120 with 160 to 1152 tokens (20 counts), against the
-// wave-level kernel; so is kCrowdUs, what parts lose that take more than kCrowd units (576 tokens: four parts of 50 workgroups 1.2 us
-// below the wave-level kernel, five 4 us above; 288: six 0.1 below, seven 0.8 - 3 above, eight 2.5).
+// kCrowdUs is what parts lose that take more than kCrowd units.  All four are fitted with the wave-level kernel's times of plain layers
+// (choose_tile).  By 0.9, 3.0 and a crowd from 200 units on, which one layer of 1280 x 5120 had given, narrower ones split that should not
+// have: 224 x 1280 x 3840 11.6 -> 13.9 us, 288 x 960 x 3840 11.2 -> 13.0.
 struct SplitCfg { int tile; double fixed; };
-constexpr SplitCfg kSplits[] = {{2, 0.9}, {6, 3.0}};
+constexpr SplitCfg kSplits[] = {{2, 2.0}, {6, 2.2}};
 constexpr int kMaxParts = 8, kSplitFamily = 7;          // (the first tiles: those that parts of K were weighed against)
-constexpr double kPartUs = 2.0e-6;                     // microseconds per output value and part, and per value of the sums
-constexpr double kCrowdUs = 2.5;
-constexpr int kCrowd = 200;
-constexpr double kPlain64 = 0.012;                     // more per slab of the 64 x 64 tile in a plain layer of the step
+constexpr double kPartUs = 1.9e-6;                     // microseconds per output value and part, and per value of the sums
+constexpr double kCrowdUs = 2.0;
+constexpr int kCrowd = 224;
+constexpr double kPlain64 = 0.008;                     // more per slab of the 64 x 64 tile in a plain layer of the step
+// Cross-attention on the 64 x 128 tile: 1224 tokens of 1280 features 11.5, 11.9, 15.2 and 13.7 us against one to four fragments of 32 text
+// tokens.  With the third's time for all, the wave-level kernel had 13.8, 14.2, 14.5 and 15.1.
+constexpr double kXaEpi64x128 = 6.3;
 
 inline int max_parts(const TileCfg& t, long long MT, long long NF) {
   const long long n = ((MT + t.bt - 1) / t.bt) * ((NF + t.bf - 1) / t.bf);
@@ -70,15 +73,16 @@ inline int pick_bgemm(const WParams& p, double other_us, long long room, int* pa
       const long long rem = n % 512;
       r = n > 1536 ? n / 512.0 : (double)(n / 512) + (rem == 0 ? 0.0 : rem <= 256 ? t.alone : 1.0);
     }
-    const double us = t.base + r * (kt * (t.slab + (c == 5 && mode == 2 && !p.ln_s ? kPlain64 : 0.0)) + t.epi[mode]);
+    const double slab = c == 5 && mode == 2 && !p.ln_s ? t.slab + kPlain64 : t.slab;
+    const double epi = c == 3 && mode == 3 && (p.xa_keys + 31) / 32 != 3 ? kXaEpi64x128 : t.epi[mode];
+    const double us = t.base + r * (kt * slab + epi);
     if (us < best) { best = us; pick = c; *parts = 1; }
   };
   *parts = 1;
   for (int c = 0; c < kSplitFamily; ++c) consider(c);
-  // In the step, 494 x 1280 x 5120 takes 1.5 us less in five parts than on the wave-level kernel, 256 0.7 less in eight, 576 1.2 less in
-  // four; the error against 64 bits is that of the whole layer (494: 1.19e-7 against 1.29e-7 relative).
-  // 1024 x 1280 x 5120: 35.5 us with the best tile, 27.5 in three parts.  At 640 features and K = 2560 and below the sums cost what
-  // the parts gain.
+  // Inputs written by the kernel before, weights cold: 494 x 1280 x 5120 21.9 us in five parts, 24.4 on the wave-level kernel; 224 15.7 in
+  // eight against 18.1; 1024 32.1 in three against 33.4 on the best tile.  The error against 64 bits is that of the whole layer (494:
+  // 1.19e-7 against 1.29e-7 relative).  At 640 features and K = 2560 and below the sums cost what the parts gain.
   if (mode == 2 && !p.ln_s && room > 1) {
     for (const SplitCfg& q : kSplits) {
       const TileCfg& t = kTiles[q.tile];
@@ -87,7 +91,7 @@ inline int pick_bgemm(const WParams& p, double other_us, long long room, int* pa
       for (int s = 2; s <= most && s <= room; ++s) {
         if (kt / s < 8) break;
         const double us = t.base + std::ceil(kt / s) * t.slab + q.fixed + kPartUs * (s + 1) * (32.0 * MT) * p.N + (tiles * s > kCrowd ? kCrowdUs : 0.0);
-        if (us < (pick < 0 || *parts > 1 ? best : 0.97 * best)) { best = us; pick = q.tile; *parts = s; }
+        if (us < best) { best = us; pick = q.tile; *parts = s; }
       }
     }
   }
@@ -121,14 +125,24 @@ inline int choose_tile(const WParams& p, const WaveForm& f, long long room, int*
   const double kt = p.K / 64.0;
   const bool two = f.tiles >= 320 && !p.xkv;
   const double n = f.wide ? 0.0 : two ? (double)((MT + 1) / 2) * (p.geglu ? nfrag : nfrag / 2) : (double)f.tiles;
-  // A plain layer takes the same time for 140 as for 240 workgroups, one per unit: 1280 x 5120 in the step 14.6 - 15.2 us with 224 to
-  // 384 tokens, 19 - 20 with 494 to 768.  By the share of the units 704 and 768 were predicted 24 - 25 and went to the 64 x 64 tiles,
-  // which take 23 (768 tokens, whole step: 10449 -> 10154 us).
-  const double r = is_plain(p) ? (n <= 256.0 ? (two ? 0.68 : 0.66) : n / 256.0) : n / 256.0 > 0.6 ? n / 256.0 : 0.6;
-  const double us = f.wide ? 9.7 + 0.125 * kt
-                    : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : p.ln_s ? 0.23 : 0.9))
-                    : p.xkv ? 5.3 + r * (0.165 * kt + 0.1)
-                            : 3.46 + r * (0.201 * kt + (p.geglu ? 2.1 : p.nseg ? 2.2 : p.ln_s ? 0.49 : 0.34));
+  double us;
+  if (is_plain(p)) {
+    // Rounds of 256 workgroups, one per unit, whatever part of the units the last one covers: 1280 x 5120 14.6 - 15.2 us with 224 to 384
+    // tokens, 19 - 20 with 494 to 768.  Every XCD reads all tokens, hence the term in M x K: inputs that the kernel before has just written
+    // instead of ones read before take 1.5 us more at 1024 x 640 x 640 and 3 at 768 x 1280 x 5120.  Fitted to 41 layers (320 to 10240
+    // features, K of 64 to 10240) of 130 to 7200 tokens, weights that no cache holds.  What this chooses takes 0.7 % more than the best of all
+    // tiles and parts with inputs just written, 1.2 % with inputs read again and again, 1.5 % with K below 640.  Constants from 1280 x 5120
+    // alone took 1.9, 1.7 and 2.0, and up to 18 % more than another tile (1500 x 640 x 2560 11.7 -> 13.8 us, 2400 x 320 x 1280 7.5 -> 8.4).
+    const double q = n / 256.0;
+    const double r = q <= 1.0 ? 0.65 : q > 2.0 ? 1.3 * q : two ? 1.2 + 0.5 * (q - 1.0) : 1.0 + 1.35 * (q - 1.0);
+    us = (f.wide ? 6.2 + 0.21 * kt : two ? 4.95 + r * (0.26 * kt + 0.8) : 3.46 + r * (0.201 * kt + 0.34)) + 0.5e-6 * (32.0 * MT) * p.K;
+  } else {
+    const double r = n / 256.0 > 0.6 ? n / 256.0 : 0.6;
+    us = f.wide ? 9.7 + 0.125 * kt
+         : two ? 4.95 + r * (0.261 * kt + (p.geglu ? 0.34 : p.nseg ? 0.7 : 0.23))
+         : p.xkv ? 5.3 + r * (0.165 * kt + 0.1)
+                 : 3.46 + r * (0.201 * kt + (p.geglu ? 2.1 : p.nseg ? 2.2 : 0.49));
+  }
   // (in the step the wave-level kernel keeps its time where the tiles lose a few per cent to what runs before them)
   return pick_bgemm(p, 0.98 * us, room, parts);
 }

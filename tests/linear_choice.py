@@ -13,13 +13,13 @@ TILES = ["256x320", "128x128/2", "128x128", "64x128/2", "64x64/2", "64x64", "128
 SOURCE = r'''#include <cstdio>
 #include "wchoice.h"
 int main() {
-  int M, N, K, ln, geglu, nseg, xa; long long room;
-  while (scanf("%d %d %d %d %d %d %d %lld", &M, &N, &K, &ln, &geglu, &nseg, &xa, &room) == 8) {
+  int M, N, K, ln, geglu, nseg, text; long long room;
+  while (scanf("%d %d %d %d %d %d %d %lld", &M, &N, &K, &ln, &geglu, &nseg, &text, &room) == 8) {
     df::WParams p = {};
     static float one;
     p.M = M; p.K = K; p.geglu = geglu; p.N = geglu ? N / 2 : N; p.nseg = nseg;
     if (ln) p.ln_s = &one;
-    if (xa) p.xkv = reinterpret_cast<const df::bf16x8*>(&one);
+    if (text) { p.xkv = reinterpret_cast<const df::bf16x8*>(&one); p.xa_keys = text; }
     int parts = 1;
     const int tile = df::choose_tile(p, df::wave_form(p), room, &parts);
     printf("%d %d\n", tile, parts);
@@ -39,12 +39,12 @@ def _program():
 
 
 def choices(layers):
-    """layers: (M, N, K, variant[, parts that fit the scratch]); variant: words of ln, geglu, qkv, xa joined by "_", or plain.
-    Returns (tile name or WAVE, parts) of each."""
+    """layers: (M, N, K, variant[, n]); variant: words of ln, geglu, qkv, xa joined by "_", or plain; n: with xa the text tokens (77), else
+    the parts of K that fit the scratch (0).  Returns (tile name or WAVE, parts) of each."""
     lines = []
-    for M, N, K, variant, *room in layers:
+    for M, N, K, variant, *n in layers:
         v = variant.split("_")
-        lines.append("%d %d %d %d %d %d %d %d" % (M, N, K, int("ln" in v or "qkv" in v or "xa" in v), "geglu" in v, 3 * ("qkv" in v), "xa" in v,
-                                                  room[0] if room else 0))
+        ln, text = bool({"ln", "qkv", "xa"} & set(v)), (n[0] if n else 77) if "xa" in v else 0
+        lines.append("%d %d %d %d %d %d %d %d" % (M, N, K, ln, "geglu" in v, 3 * ("qkv" in v), text, n[0] if n and not text else 0))
     out = subprocess.run([_program()], input="\n".join(lines), capture_output=True, text=True, check=True).stdout.split()
     return [(WAVE if int(t) < 0 else TILES[int(t)], int(n)) for t, n in zip(out[::2], out[1::2])]

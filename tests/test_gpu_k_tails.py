@@ -36,8 +36,11 @@ def test_linear_of_few_stages(M, N, K, variant):
     (6000, 128, 77), (6000, 192, 77), (3300, 256, 77),         # the wave-level kernel
     (8250, 256, 77),                   # 128 x 128, two workgroups per unit: four stages in a ring of two
     (4664, 448, 77),                   # 128 x 128 in a ring of four, seven stages; its keys come beside the last one
-    (4012, 512, 33),
+    (4012, 512, 77),
+    (3034, 640, 77),
+    (4012, 512, 33),                   # 64 x 128, two k-groups that add their sums in LDS: eight and ten stages in three
     (3034, 640, 128),
+    (1224, 1280, 50),
 ])
 def test_cross_attention_of_few_stages(rows, C, text):
     run_cross(1, rows, C, text, 2, 1)

@@ -27,8 +27,8 @@ def check(layers, want):
 def test_layers_of_few_stages():
     check(rows(test_gpu_k_tails.test_linear_of_few_stages),
           ["128x128/2"] * 2 + ["128x192"] * 3 + ["128x96"] + ["64x64"] * 6 + ["128x320"] * 3 + ["256x320", "128x128", WAVE])
-    check([(m, c, c, "xa") for m, c, _ in rows(test_gpu_k_tails.test_cross_attention_of_few_stages)],
-          [WAVE] * 3 + ["128x128/2"] + ["128x128"] * 3)
+    check([(m, c, c, "xa", text) for m, c, text in rows(test_gpu_k_tails.test_cross_attention_of_few_stages)],
+          [WAVE] * 3 + ["128x128/2"] + ["128x128"] * 3 + ["64x128/2"] * 3)
 
 
 def test_layers_of_the_less_common_tiles():
@@ -44,7 +44,7 @@ def test_layers_with_the_epilogue_in_the_accumulators():
 def test_layers_of_the_operation_tests():
     check([(m, n, k, v.replace("_far", "")) for m, n, k, v in rows(test_gpu_ops.test_linear_packed_tiles)],
           ["64x64", "128x96", "128x96", "128x96", "128x128/2", "128x128", "128x128", "64x64/2", "256x320", "128x320", "128x320"])
-    check([(b * m, c, c, "xa") for b, m, c, *_ in rows(test_gpu_ops.test_cross_attn_packed)],
+    check([(b * m, c, c, "xa", text) for b, m, c, text, *_ in rows(test_gpu_ops.test_cross_attn_packed)],
           [WAVE] * 4 + ["64x128/2", "128x128", "128x128", "128x128/2"])
 
 
@@ -52,3 +52,12 @@ def test_parts_of_middle_sizes():
     """Token counts on either side of each change of the number of parts, with scratch for eight."""
     counts = test_gpu_linear_parts_choice.test_linear_packed_parts_of_middle_sizes.pytestmark[0].args[1]
     assert [n for _, n in choices([(m, 1280, 5120, "plain", 8) for m in counts])] == [8, 8, 1, 5, 5, 4, 1, 1, 1]
+
+
+def test_layers_of_other_widths():
+    """Layers that constants from 1280 x 5120 alone sent to a slower kernel or split in parts, and those that they were made for."""
+    layers = [(1500, 640, 2560), (2400, 320, 1280), (3000, 320, 2560), (224, 1280, 3840), (288, 960, 3840), (640, 640, 5120),
+              (768, 1280, 5120), (494, 1280, 5120), (1024, 1280, 5120)]
+    assert choices([(*l, "plain", 8) for l in layers]) == [
+        ("64x64", 1), ("64x64", 1), ("64x64", 1), (WAVE, 1), (WAVE, 1), ("128x128", 8), (WAVE, 1), ("128x128", 5), ("128x128", 3)]
+    assert choices([(1224, 1280, 1280, "xa", n) for n in (20, 50, 77, 100)]) == [("64x128/2", 1), ("64x128/2", 1), (WAVE, 1), ("64x128/2", 1)]
