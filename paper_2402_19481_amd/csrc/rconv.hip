@@ -11,8 +11,8 @@ template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
 }
-template <int MOST = 40>
-__device__ __forceinline__ void wait_vm_lds(int n) {   // the same with a count that unrolling makes known
+template <int MOST>
+__device__ __forceinline__ void wait_vm_lds(int n) {   // the same with a count (0 .. MOST) that unrolling makes known
   if (n == MOST) wait_vm_lds<MOST>();
   else if constexpr (MOST > 0) wait_vm_lds<MOST - 1>(n);
 }
@@ -197,6 +197,8 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
     }
   };
   // loads that may still be in flight at the end of stage st: those requested in the last ST - 2 stages
+  constexpr int FLY = (ST - 2) * (WL + IPS);               // (at most)
+  static_assert(FLY <= 63, "vmcnt");
   auto in_flight = [&](auto lastc, int st) {
     int n = 0;
 #pragma unroll
@@ -240,7 +242,7 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
         } else if (LAST && st + 1 == NST) {
           DF_SB; mm(b); DF_SB;
         } else {
-          wait_vm_lds(in_flight(lastc, st));
+          wait_vm_lds<FLY>(in_flight(lastc, st));
           block_sync();
           const bool wrap = st + 1 == NST;
           rd(nslot, wrap ? buf ^ 1 : buf, wrap ? 0 : st + 1, 0, bn);
