@@ -143,7 +143,7 @@ struct WGemmArgs {
   void* out_rows;         // row-major bf16 [M, N'], row stride ld_rows, or nullptr
   long long ld_rows;
   int geglu;              // F: W holds F value rows then F gate rows (N == 2F), N' = F; 0: N' = N
-  // segmented bf16 output (fused QKV projection; replaces out_rows): column segment s = col / seg_w is written to
+  // segmented bf16 output (fused QKV projection; folds a LayerNorm, and is the only output): column segment s = col / seg_w is written to
   // seg_out[s]; input row m lands on row (m / seg_rows_in[s]) * seg_rows_out[s] + seg_row0[s] + m % seg_rows_in[s] with
   // row stride seg_ld[s]
   int nseg, seg_w;

@@ -162,6 +162,11 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, const WOut& o, i
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
 int launch_part_sums(const WParams& p, hipStream_t st);
 
+// A segmented layer folds a LayerNorm and writes its segments: nothing is added to them and no other output comes with them.
+inline bool segments_alone(const WGemmArgs& a) {
+  return a.nseg <= 0 || (a.ln_s && !a.residual && !a.out_f32 && !a.out_packed && !a.out_rows && !a.geglu && !a.xa_kv);
+}
+
 // Parts of K that the scratch handed to a plain layer (MT token rows of 32, NF feature rows of 32, K) has to hold; 1: any scratch
 // will do.  This decides which calls return DF_ENOMEM and nothing else.  It is the choice of parts as it was when that became
 // part of the entry point, with the predicted times of then (a launch, a round of workgroups per 64 of K, its prologue and

@@ -652,6 +652,7 @@ int launch_wgemm(const WGemmArgs& a, hipStream_t st) {
   p.ld_rows = a.ld_rows; p.geglu = a.geglu ? 1 : 0; p.parts = 1;
   if (a.nseg > 0) {
     if (a.nseg > 3 || a.seg_w % 32 || a.seg_w * a.nseg != a.N || a.geglu) return DF_ESHAPE;
+    if (!segments_alone(a)) return DF_EINVAL;
     p.nseg = a.nseg; p.seg_w = a.seg_w;
     if (a.seg0_scale != 0.f && a.seg_tr[0]) return DF_EINVAL;
     p.seg0_scale = a.seg0_scale != 0.f ? a.seg0_scale : 1.0f;
