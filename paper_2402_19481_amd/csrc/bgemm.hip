@@ -385,10 +385,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         if constexpr (ST >= 5)
           if (last(std::integral_constant<int, 3>{}))
             if constexpr (ST >= 6) last(std::integral_constant<int, 4>{});
-    if (KT < ST - 1) {
-      wait_vm_lds<0>();                                  // the ring becomes the epilogue's
-      if constexpr (kDirectXa) request_kv();
-    }
+    if (KT < ST - 1) wait_vm_lds<0>();                   // the ring becomes the epilogue's (cross-attention has more stages, launch_one)
   } else {
 #pragma unroll
   for (int s = 0; s < ST; ++s)
@@ -789,6 +786,8 @@ int launch_one(const WParams& pin, hipStream_t st) {
   const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO;
   const long long nwg = (long long)MG * NG;
   if ((p.K / 16) % (KS * KG)) return DF_ESHAPE;
+  // a tile whose waves hold a head each requests keys and values beside the last of at least ST - 1 stages
+  if (EPI == EPI_XA && KG == 1 && TF == 2 && ST >= 4 && p.K / (16 * KS * KG) < ST - 1) return DF_ESHAPE;
   const int parts = EPI == EPI_PART ? p.parts : 1;
   const double conc = std::fmin((double)nwg / 8.0, 32.0 * OCC / parts);
   int gm = (int)(std::sqrt(conc * BF / BT) + 0.5);

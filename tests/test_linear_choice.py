@@ -61,3 +61,10 @@ def test_layers_of_other_widths():
     assert choices([(*l, "plain", 8) for l in layers]) == [
         ("64x64", 1), ("64x64", 1), ("64x64", 1), (WAVE, 1), (WAVE, 1), ("128x128", 8), (WAVE, 1), ("128x128", 5), ("128x128", 3)]
     assert choices([(1224, 1280, 1280, "xa", n) for n in (20, 50, 77, 100)]) == [("64x128/2", 1), ("64x128/2", 1), (WAVE, 1), ("64x128/2", 1)]
+
+
+def test_cross_attention_of_short_k_stays_off_the_deep_ring():
+    """128 x 128 with a unit to itself (a ring of four) takes cross-attention only with a K of three stages of 64: the launcher refuses it
+    below, and the dispatch never asks."""
+    layers = [(m, c, c, "xa", n) for c in (64, 128) for m in (*range(64, 4096, 96), 10000, 40000, 200000) for n in (20, 77, 128)]
+    assert "128x128" not in {tile for tile, _ in choices(layers)}
