@@ -409,9 +409,24 @@ struct Exec {
           [&] { return launch_gemm_bf16(g, st); });
   }
 
-  // Concatenation [a, b] along the channels: the GroupNorm that reads it takes the two tensors and leaves the bf16 copy for the shortcut; where
-  // it cannot, both forms are written out first.
-  struct Cat { const float *a, *b; int ca, cb; float* f32; bf16_t* bf; };
+  // Concatenation [a, b] along the channels that is not written out: the GroupNorm that reads it takes the two tensors and leaves the bf16 copy
+  // for the shortcut.
+  struct Cat { const float *a, *b; int ca; bf16_t* bf; };
+  // the stretches of pixels that a GroupNorm's statistics are of, in this mode
+  void norm_segments(GnArgs& a, int level_rows, int W, int C, int in_dtype) const {
+    a.B = B(); a.W = W; a.C = C; a.G = c.groups; a.in_dtype = in_dtype; a.out_dtype = DF_BF16;
+    a.nseg = full() && !cols() ? N() : 1;
+    a.Rseg = level_rows / a.nseg;
+  }
+  // whether a block's GroupNorm reads the concatenation from its two tensors, ca channels of the first.  A block that keeps its input as the
+  // residual needs the floats, and the strips' sums of the synchronous step take one tensor.
+  bool reads_pair(const BlockDesc& b, int ca) const {
+    if (b.cin == b.cout || (full() && cols())) return false;
+    GnArgs a = {};
+    norm_segments(a, rows(b.level), width(b.level), b.cin, DF_F32);
+    a.x2_from = ca;
+    return groupnorm_takes_pair(a);
+  }
   void groupnorm(const std::string& name, const void* x, int in_dtype, int level_rows, int W, int C, float eps, int silu,
                  bf16_t* y, int y_packed = 0, bf16_t* halo_entry = nullptr, const Cat* cat = nullptr) {
     // level_rows: rows of x in this mode
@@ -424,16 +439,12 @@ struct Exec {
     if (!live()) return;
     GnArgs a = {};
     a.x = x; a.y = y; a.gamma = gamma; a.beta = beta;
-    a.B = B(); a.W = W; a.C = C; a.G = G; a.eps = eps; a.silu = silu; a.in_dtype = in_dtype; a.out_dtype = DF_BF16;
+    norm_segments(a, level_rows, W, C, in_dtype);
+    a.eps = eps; a.silu = silu;
     a.stat_mode = gn_mode;
     a.y_packed = y_packed;
     a.scr = scr;
-    const auto whole = [&] {
-      timed(PC_ELEMENTWISE, 0.0, 10.0 * B() * level_rows * W * C, [&] {
-        return launch_concat(cat->a, cat->ca, cat->b, cat->cb, cat->f32, cat->bf, (long long)B() * level_rows * W, st);
-      });
-    };
-    if (cat && full() && cols()) { whole(); cat = nullptr; }   // (the strips' sums take one tensor)
+    if (cat) { a.x = cat->a; a.x2 = cat->b; a.x2_from = cat->ca; a.cat_out = cat->bf; }
     if (halo_entry && (full() || refresh)) {
       // the consumer convolution's boundary-row (boundary-column) state is refreshed by this kernel's store loop
       a.halo_out = halo_entry; a.halo_npatch = N();
@@ -444,25 +455,16 @@ struct Exec {
     if (full() && cols()) {
       // vertical strips are not contiguous pixel ranges: the image is normalised as one segment and the per-strip sums
       // of the cache come from a kernel of their own (synchronous step only)
-      a.nseg = 1; a.Rseg = level_rows; a.N = 1; a.patch_idx = 0; a.stale = nullptr; a.sums_out = nullptr;
+      a.N = 1; a.patch_idx = 0; a.stale = nullptr; a.sums_out = nullptr;
       const int Bn = B(), Nn = N();
       timed(PC_GROUPNORM, 0.0, 0.0, [&] { return launch_gn_strip_sums(x, in_dtype, entry, Bn, level_rows, W, C, G, Nn, st); });
     } else if (full()) {
-      a.nseg = N(); a.Rseg = level_rows / N(); a.N = 1; a.patch_idx = 0; a.stale = nullptr; a.sums_out = entry;
+      a.N = 1; a.patch_idx = 0; a.stale = nullptr; a.sums_out = entry;
     } else {
-      a.nseg = 1; a.Rseg = level_rows; a.N = N(); a.patch_idx = patch; a.stale = entry;
+      a.N = N(); a.patch_idx = patch; a.stale = entry;
       a.sums_out = refresh ? entry + (size_t)patch * B() * G * 2 : nullptr;
     }
-    double el = (double)B() * level_rows * W * C;
-    if (cat) {
-      a.x = cat->a; a.x2_from = cat->ca;
-      if (groupnorm_takes_pair(a)) {
-        a.x2 = cat->b; a.cat_out = cat->bf;
-      } else {
-        whole();
-        a.x = x;
-      }
-    }
+    const double el = (double)B() * level_rows * W * C;
     label = "groupnorm " + dims({B() * level_rows, W, C}) + (in_dtype == DF_BF16 ? " bf16" : " f32");
     timed(PC_GROUPNORM, 0.0, el * (in_dtype == DF_BF16 ? 2.0 : 4.0) + el * (a.x2 ? 4.0 : 2.0), [&] { return launch_groupnorm(a, st); });
   }
@@ -908,18 +910,16 @@ struct Exec {
             const int sc = skip_c.back();
             skips.pop_back();
             skip_c.pop_back();
-            float* cat = (float*)alloc(px * (size_t)(cur_c + sc) * 4);
+            const bool pair = reads_pair(b, cur_c);
+            float* cat = pair ? nullptr : (float*)alloc(px * (size_t)(cur_c + sc) * 4);
             bf16_t* catb = (bf16_t*)alloc(px * (size_t)(cur_c + sc) * 2);   // the shortcut's operand
             xin = cat;
             xin_bf = dry ? nullptr : catb;
-            const Cat both = {cur, sk, cur_c, sc, cat, catb};
-            if (b.cin != b.cout) {
-              resblock(b, xin, emb_act, out, xin_bf, &both);
-            } else {                                     // (the floats are the block's residual too)
+            const Cat both = {cur, sk, cur_c, catb};
+            if (!pair)
               timed(PC_ELEMENTWISE, 0.0, 10.0 * px * (cur_c + sc),
                     [&] { return launch_concat(cur, cur_c, sk, sc, cat, catb, (long long)px, st); });
-              resblock(b, xin, emb_act, out, xin_bf);
-            }
+            resblock(b, xin, emb_act, out, xin_bf, pair ? &both : nullptr);
           } else {
             resblock(b, xin, emb_act, out, xin_bf);
           }

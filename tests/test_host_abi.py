@@ -49,3 +49,12 @@ def test_plan_sizes_and_validation():
     assert L.df_unet_num_weights(ctypes.byref(bad)) > 0
     bad = df.make_cfg(ut.UNetCfg(H=12, W=16, N=2, **ut.SMALL))        # coarsest level would have 1.5 rows per patch
     assert L.df_unet_num_weights(ctypes.byref(bad)) == -2
+
+
+def test_workspace_has_no_floats_of_a_concatenation_that_is_not_written():
+    """Vertical strips write the concatenations of their synchronous step out, horizontal ones read them from the two tensors and need no
+    room for them: 1280 channels at the peak of the middle level, 800 floats per pixel of the image less in all."""
+    L = df.lib()
+    cfg = ut.UNetCfg(H=256, W=256, N=4, **ut.SDXL)
+    rows, cols = (L.df_unet_workspace_bytes(ctypes.byref(df.make_cfg(cfg, 1, axis))) for axis in (df.SPLIT_ROWS, df.SPLIT_COLS))
+    assert cols - rows >= 4 * 640 * 256 * 256
