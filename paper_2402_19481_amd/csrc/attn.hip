@@ -96,7 +96,7 @@ __device__ long long g_attn_trace[512 * 32];
 //     would otherwise enter every feature of the row (a key of weight 0.9 with values near zero: 2.0e-3 of error against 1.4e-3,
 //     where the rounding of the result alone is 1.4e-3; random scores differ by less than 7 % in either direction).  Sums
 //     of the packed pairs by v_dot2 are half the instructions and 0.6 % faster on the largest shape.
-// K and V^T tiles go global -> LDS through a ring of three slots of an 8 KB tile each; K_{t+3} and V_{t+1} are requested in
+// K and V^T tiles go global -> LDS through a ring of three slots of an 8 KB tile of each; K_{t+3} and V_{t+1} are requested in
 // iteration t.  Slot i holds K_i, K_{i+3}, .. and V_{i+1}, V_{i+4}, ..: what an iteration reads lies in one slot, in the same order
 // in both tiles, so four address registers serve its sixteen reads.
 // Order of a slot: iteration t reads K_{t+1} and V_{t-1} (S_0 before the loop reads K_0) and ends with a barrier that every wave

@@ -124,7 +124,7 @@ struct Direct {
 // per 64 of K by the loads alone, 1530 by the matrix instructions and LDS reads alone, 2230 together), so a tile is as fast
 // as its operand bytes per flop and the number of compute units that have one; then the epilogue (with GEGLU a sixth of the time at
 // K = 1280), which in the smaller tiles runs beside the other workgroup of the unit.  Hence a set of tiles, from 64 x 64 to
-// 256 x 320 with 320 a divisor of most layers' widths, and the choice by predicted time below.  With the stages requested
+// 256 x 320 with 320 a divisor of most layers' widths, and the choice by predicted time (wchoice.h).  With the stages requested
 // in parts between the matrix instructions and the 320-wide tiles, 1024 x 10240 x 1280 with GEGLU 46.6 -> 36.3 us, 1800
 // x 10240 x 1280 68 -> 62, 4096 x 5120 x 640 43.5 -> 39.9, 14400 x 640 x 2560 with residual 78 -> 61.  Four waves of 64 x
 // 160 instead of eight of 32 x 160: 40 us (one wave per SIMD issues the epilogue half as fast).  With loads that leave the waits

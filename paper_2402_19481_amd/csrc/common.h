@@ -38,8 +38,8 @@ __device__ __forceinline__ float silu_f(float x) {
 // GELU in its exact (erf) form, 0.5 x (1 + erf(x / sqrt 2)) = max(x, 0) - |x| Q(|x|) for both signs, Q(a) = erfc(a / sqrt 2) / 2: for
 // negative arguments nothing cancels.  log2 Q is so smooth that a polynomial of degree 8 in a holds it: fitted here by reweighted least
 // squares on [0, 5.6] to |error of a Q| <= 1e-7 and |error of Q| <= 1e-4 Q (0.61 of either bound reached; Q < 1e-8 beyond, where the
-// polynomial goes on falling to -infinity).  Against 64 bits the float function is off by 2.4e-7 at most and 2.8e-8 rms over N(0, 1)
-// (Abramowitz & Stegun 7.1.26, with a reciprocal besides: 3.3e-7 and 3.6e-8), 6e-5 of the value at arguments around -5 (2.5e-3).
+// polynomial goes on falling to -infinity).  Against 64 bits the float function is off by 2.4e-7 at most and 4.1e-8 rms over N(0, 1)
+// (Abramowitz & Stegun 7.1.26, with a reciprocal besides: 3.3e-7 and 5.4e-8), 6e-5 of the value at arguments around -5 (2.5e-3).
 // Twelve instructions per value, one of them at a quarter of the rate: the GEGLU epilogues are bounded by them.
 // The factor of Q is kept finite, so that +inf stays +inf (Q is 0 there).
 __device__ __forceinline__ float gelu_erf(float x) {

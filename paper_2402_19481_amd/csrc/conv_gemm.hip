@@ -211,9 +211,10 @@ __global__ __launch_bounds__(256) void conv3x3_direct(const T* __restrict__ x, c
 }
 
 // f32, Cin % 4 == 0: a workgroup owns 4 pixels x 32 output channels, its four waves every fourth 16-byte chunk of the channels
-// of each tap; a lane owns one output channel of two pixels.  Latency-bound at the sizes it is used at: all loads of
-// a tap are independent, and the weights of a channel are read along its row (one thread per output before, a serial
-// loop over 9 x Cin with the lanes' weights a row apart: 128 pixels x 32 channels, Cin = 32: 37.9 -> 4 us).
+// of each tap; a lane owns one output channel of two pixels.  Latency-bound at the sizes it is used at: the loads of a tap are
+// independent and the weights of a channel are read along its row, but the branch around absent pixels keeps each tap behind the one
+// before it.  128 pixels x 32 channels, Cin = 32: 9.9 us with its boundary in a graph (one thread per output, a serial loop over 9 x Cin with the
+// lanes' weights a row apart: 37.9).
 __global__ __launch_bounds__(256) void conv3x3_f32(const float* __restrict__ x, const float* __restrict__ top,
                                                    const float* __restrict__ bot, long long halo_bs,
                                                    const float* __restrict__ left, const float* __restrict__ right,

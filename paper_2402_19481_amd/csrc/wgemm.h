@@ -158,7 +158,7 @@ __device__ __forceinline__ void wg_store_unit(const WParams& p, const WOut& o, i
   if (o.rows && row_ok) st_vec(o.rows + (long long)m * o.ld_rows + n, v);
 }
 
-// Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of its table.
+// Workgroup-tile kernel (bgemm.hip), tile shape `cfg` of kTiles (wchoice.h).
 int launch_bgemm(const WParams& p, int cfg, hipStream_t st);
 int launch_part_sums(const WParams& p, hipStream_t st);
 

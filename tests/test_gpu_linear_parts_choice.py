@@ -1,5 +1,5 @@
 """Plain linear layers of a long K where the choice between the wave-level kernel, the tiles and parts of K turns: seven and eight rows of
-fragments (eight parts), nine (whole), thirteen and sixteen (five), eighteen (four), nineteen and more (whole)."""
+fragments (eight parts), nine (whole), thirteen and sixteen (five), seventeen (four), nineteen and more (whole)."""
 import pytest
 
 from test_gpu_linear_parts_few import test_linear_packed_parts_few_tokens as run
