@@ -276,6 +276,10 @@ def run_tile_sweep(df, torch):
         sweep(name, 2.0 * M * N * K, lambda: df.linear(x, w, b))
 
 
+# layers that the choice leaves to the wave-level kernel (wgemm.hip)
+TIMELINE_LAYERS = [(300, 1280, 5120, "plain"), (300, 1280, 1280, "plain"), (300, 1280, 1280, "ln")]
+
+
 def run_timeline(df, torch, tune_path):
     """In-kernel timelines from the tuning build (cycle stamps written by the kernels themselves): how a wave-level linear
     layer of the patch step (the shapes that stay on wgemm.hip) divides into prologue, K loop and reduction + epilogue, and the tiles of the self-attention
@@ -288,16 +292,22 @@ def run_timeline(df, torch, tune_path):
     g = torch.Generator(device="cpu").manual_seed(1)
     rn = lambda *s: torch.randn(*s, generator=g).to(dev)
     bf = lambda t: t.to(torch.bfloat16)
-    def wgemm(name, fn):
-        for _ in range(3):
-            fn()
-        torch.cuda.synchronize()
+    def stamps():
         n = 1024 * 16
         buf = (ctypes.c_longlong * n)()
         if lib.df_tune_wgemm_trace(buf, n) != 0:
             raise RuntimeError("df_tune_wgemm_trace failed")
-        t = [list(buf[i * 16:(i + 1) * 16]) for i in range(1024)]
+        return [list(buf[i * 16:(i + 1) * 16]) for i in range(1024)]
+
+    def wgemm(name, fn):
+        before = max(r[0] for r in stamps())
+        for _ in range(3):
+            fn()
+        torch.cuda.synchronize()
+        t = stamps()
         smax = max(r[0] for r in t)
+        if smax <= before:
+            raise RuntimeError(name + ": not a layer of wgemm_kernel")
         t = [r for r in t if r[0] > smax - 100000 and r[5] >= r[0]]   # this launch's workgroups (100 MHz clock: 1 ms)
         s0 = min(r[0] for r in t)
         mean = lambda v: round(statistics.mean(v))
@@ -306,8 +316,8 @@ def run_timeline(df, torch, tune_path):
                           "last_start_us": round((max(r[0] for r in t) - s0) / 100.0, 2),
                           "cycles": {"prologue": mean([r[2] - r[1] for r in t]),
                                      "prologue_tile_indices": mean([r[6] - r[1] for r in t]),
-                                     "prologue_epilogue_operand_requests": mean([r[7] - r[6] for r in t]),
-                                     "prologue_first_operand_requests": mean([r[2] - r[7] for r in t]),
+                                     "prologue_first_and_epilogue_operand_requests": mean([r[7] - r[6] for r in t]),
+                                     "prologue_output_arguments": mean([r[2] - r[7] for r in t]),
                                      "k_loop": mean([r[3] - r[2] for r in t]),
                                      "reduce_and_epilogue": mean([r[4] - r[3] for r in t]),
                                      # passes of the epilogue: partial tiles to LDS + barrier, then the wave's units
@@ -315,10 +325,9 @@ def run_timeline(df, torch, tune_path):
                                      "epilogue_pass0_units": mean([r[9] - r[8] for r in t]),
                                      "epilogue_later_passes": mean([r[4] - r[9] for r in t])}}), flush=True)
 
-    M = 300
-    for name, N, K, ln in (("linear_packed 300x1280x5120", 1280, 5120, False),
-                           ("linear_packed 300x1280x1280", 1280, 1280, False),
-                           ("linear_packed 300x3840x1280 ln", 3840, 1280, True)):
+    for M, N, K, variant in TIMELINE_LAYERS:
+        ln = variant == "ln"
+        name = "linear_packed %dx%dx%d%s" % (M, N, K, " ln" if ln else "")
         xw, ww, bw = bf(rn(M, K)), bf(rn(N, K) / math.sqrt(K)), rn(N)
         xp, wp = df.pack_rows(xw), df.pack_linear_weight(ww)
         kw = dict(want=("packed",))

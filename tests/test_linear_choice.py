@@ -4,6 +4,7 @@ import shutil
 
 import pytest
 
+import bench
 import test_gpu_k_tails
 import test_gpu_linear_epilogue
 import test_gpu_linear_parts_choice
@@ -46,6 +47,11 @@ def test_layers_of_the_operation_tests():
           ["64x64", "128x96", "128x96", "128x96", "128x128/2", "128x128", "128x128", "64x64/2", "256x320", "128x320", "128x320"])
     check([(b * m, c, c, "xa", text) for b, m, c, text, *_ in rows(test_gpu_ops.test_cross_attn_packed)],
           [WAVE] * 4 + ["64x128/2", "128x128", "128x128", "128x128/2"])
+
+
+def test_layers_whose_timelines_are_read():
+    """`bench.py --timeline` reads stamps that only the wave-level kernel writes."""
+    check(bench.TIMELINE_LAYERS, [WAVE] * len(bench.TIMELINE_LAYERS))
 
 
 def test_parts_of_middle_sizes():
