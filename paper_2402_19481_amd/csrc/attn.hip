@@ -440,7 +440,8 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     return tsum;
   };
 
-  // A tile with a large sum that its probabilities and the sum still hold: m up by the power of two above it, for the query's two lanes
+  // A tile with a large sum that its probabilities and the sum still hold: m up by the power of two above it, for the query's two lanes.
+  // Returns the sum on the scale of the probabilities, by which m moves as well but for rounding (a whole step from 2^24 on).
   auto lower = [&](float tsum) {
     const float part = __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(tsum)));
     const float s = fmaxf(tsum, part);
@@ -454,6 +455,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
         const float lo = __uint_as_float(pk[u][q] << 16) * scale, hi = __uint_as_float(pk[u][q] & 0xffff0000u) * scale;
         pk[u][q] = __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
       }
+    return tsum * scale;
   };
 
   bool again = false;                                      // tile tl has a large sum (NaN passes on as it is)
@@ -477,12 +479,9 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   };
   for (;;) {
     if (again) {
-      if (__builtin_amdgcn_ballot_w64(tsum > kRedo)) {
-        l_run += redo();
-      } else {
-        l_run += tsum;
-        lower(tsum);
-      }
+      // (the sums of the tiles before move with m, so this tile's is added behind)
+      const float sum = __builtin_amdgcn_ballot_w64(tsum > kRedo) ? redo() : lower(tsum);
+      l_run += sum;
       advance();
       if (tl >= ntiles) break;
     }

@@ -40,6 +40,30 @@ def test_attention_peaked_scores(H, N, std, form):
     check(got, ref, True, "attention_peaked", say=say)
 
 
+@pytest.mark.parametrize("form", ["vt", "rows"])
+@pytest.mark.parametrize("top", [25.0, 27.0])
+def test_attention_peaked_scores_beyond_24_bits(form, top):
+    """Scores of 1.7e7 nats (2.4e7 in powers of two, where floats are 2 apart) and one key, in the third tile, 34 or 38 nats above all others:
+    the tile is scaled by 2^-49 or 2^-55, the maximum can only move by 48 or 56.  The result is that key's values.  The products are
+    whole multiples of 16 below 2^27, so their sums are exact."""
+    say("attention_peaked beyond 24 bits", form, top)
+    heads, Lq, N = 8, 257, 3
+    C, L = heads * 64, Lq * N
+    q, k = np.full((1, Lq, C), 2048.0, np.float32), np.full((1, L, C), 1024.0, np.float32)
+    q[:, :, ::64], k[:, :, ::64], k[:, 150, ::64] = 16.0, 8.0, top
+    v = round_bf16(normal(74, "v", (1, L, C)))
+    ref = ops.attention_dense(q, k, v, heads)
+    qd, kd, vd = dev(q, True), dev(k, True), dev(v, True)
+    if form == "vt":
+        vt = torch.zeros((1, C, (L + 63) // 64 * 64), dtype=torch.bfloat16, device=DEV)
+        vt[:, :, :L] = vd.transpose(1, 2)
+        got = host(df.attn_stale_vt(qd.repeat(1, 5, 1), kd, vt, heads, L))[:, :Lq]
+    else:
+        own = slice(Lq, 2 * Lq)
+        got = host(df.attn_displaced(qd, kd[:, own].contiguous(), vd[:, own].contiguous(), kd, vd, heads, 1, N))
+    check(got, ref, True, "attention_peaked", say=say)
+
+
 def test_attention_peaked_scores_take_no_detour():
     """1024 queries x 4096 keys x 10 heads: 25 us with flat scores; 31 where a tile with large probabilities is scaled in registers, 43
     where every such tile is computed again from memory."""
