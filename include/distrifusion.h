@@ -97,6 +97,12 @@ int df_groupnorm_stale(const void* x_fresh, void* y, const float* stale_stats, f
                        const float* gamma, const float* beta, int B, int R, int W, int C, int G,
                        int patch_idx, int N, float eps, int stat_mode, int fuse_silu, int dtype, void* stream);
 
+/* df_groupnorm_stale whose workgroups wait for nobody: where they would hand each other sums inside a launch, each adds up everything itself.
+ * The same result, bit for bit, and slower: what a launch falls back to when a workgroup does not appear, for tests. */
+int df_groupnorm_stale_alone(const void* x_fresh, void* y, const float* stale_stats, float* fresh_stats_out,
+                             const float* gamma, const float* beta, int B, int R, int W, int C, int G, int patch_idx, int N,
+                             float eps, int stat_mode, int fuse_silu, int dtype, void* stream);
+
 /*
  * df_groupnorm_stale for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): same arguments, same kernels, same results, but the statistics pass keeps

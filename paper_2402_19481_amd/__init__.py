@@ -53,6 +53,8 @@ def lib():
     if hasattr(L, "df_groupnorm_stale_noalloc"):
         L.df_groupnorm_stale_noalloc.argtypes = L.df_groupnorm_stale.argtypes
         L.df_groupnorm_stale_noalloc.restype = i
+    L.df_groupnorm_stale_alone.argtypes = L.df_groupnorm_stale.argtypes
+    L.df_groupnorm_stale_alone.restype = i
     L.df_attn_displaced.argtypes = [vp, vp, vp, vp, vp, vp, i, i, i, i, i, i, f, i, vp]
     L.df_buffer_refresh_axis.argtypes = [vp, vp, i, i, ll, i, i, i, i, vp]
     L.df_conv3x3_halo_axis.argtypes = [vp, vp, vp, vp, vp, i, i, i, i, i, i, i, i, i, i, i, vp]
@@ -170,6 +172,16 @@ def groupnorm_stale(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5
                                     _ptr(beta), B, R, W, C, G, patch_idx, N, eps, stat_mode, int(fuse_silu),
                                     _dt(x_fresh), _stream()))
     return y, fresh_stats_out
+
+
+def groupnorm_stale_alone(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS, fuse_silu=False):
+    """groupnorm_stale whose workgroups wait for nobody: the same result, slower (for tests)."""
+    B, R, W, C = x_fresh.shape
+    y = torch.empty_like(x_fresh)
+    fs = torch.empty(B, G, 2, dtype=torch.float32, device=x_fresh.device)
+    _check(lib().df_groupnorm_stale_alone(_ptr(x_fresh), _ptr(y), _ptr(stale_stats), _ptr(fs), _ptr(gamma), _ptr(beta), B, R, W, C, G,
+                                          patch_idx, N, eps, stat_mode, int(fuse_silu), _dt(x_fresh), _stream()))
+    return y, fs
 
 
 def groupnorm_stale_noalloc(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, y, fresh_stats_out, eps=1e-5,

@@ -91,6 +91,13 @@ int df_groupnorm_stale(const void* x_fresh, void* y, const float* stale_stats, f
                          stat_mode, fuse_silu, dtype, nullptr, (hipStream_t)stream);
 }
 
+int df_groupnorm_stale_alone(const void* x_fresh, void* y, const float* stale_stats, float* fresh_stats_out,
+                             const float* gamma, const float* beta, int B, int R, int W, int C, int G, int patch_idx, int N,
+                             float eps, int stat_mode, int fuse_silu, int dtype, void* stream) {
+  return groupnorm_entry(x_fresh, y, stale_stats, fresh_stats_out, gamma, beta, B, R, W, C, G, patch_idx, N, eps,
+                         stat_mode, fuse_silu, dtype, nullptr, (hipStream_t)stream, -1);
+}
+
 int df_conv3x3_halo_axis(const void* x_fresh, const void* stale_full, const void* w, const float* bias, void* y, int B,
                          int H, int W, int Cin, int Cout, int patch_idx, int N, int stride, int act, int dtype,
                          int split_axis, void* stream) {

@@ -10,7 +10,8 @@
 //                sums of the other patches according to the statistic mode, then
 //                y = (x - mean) * rstd * gamma + beta (+ SiLU) on the strip it summed
 //                in the first launch; block 0 also emits the fresh per-patch sums.
-// Small tensors take one launch, one workgroup per (group, batch item).
+// Small tensors take one launch, one workgroup per (group, batch item), and those between one whose workgroups hand each other
+// their sums (gn_meet_kernel).
 // A lane keeps a fixed channel offset for its whole strip, so gamma/beta and
 // the statistics are fetched once per lane.
 //
@@ -19,9 +20,10 @@
 // totals are known: E[x^2] - E[x]^2 of float sums loses (mean / sigma)^2 ulps, which
 // a tensor whose mean is far from zero cannot afford at float32 tolerance.  The
 // normalisation subtracts the mean as a (high, low) float pair before scaling.
+#include <atomic>
 #include <cstdlib>
 #include <mutex>
-#include "kernels.h"
+#include "wgemm.h"
 
 namespace df {
 
@@ -731,6 +733,298 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
   }
 }
 
+// Larger patches in one launch: x is read once and stays in registers, as above, but P workgroups share the groups of an eighth of the
+// channels (a slab), each with a range of pixels, and hand each other their sums.  The workgroups of a slab lie on one XCD
+// (workgroups go round-robin over the eight, so blockIdx % 8 is the slab), and a sum goes through that XCD's L2 as an 8-byte word with the
+// launch's number beside the float, so one store and one poll pass it on: 0.9 us with the wait for the slowest, where an exchange
+// over all XCDs takes 5 and a second launch 2 and another read of x.
+//   - The result depends neither on where the workgroups are nor on all of them being there at once: a word counts only with the right number, and
+//     after `wait` polls a workgroup adds up the other ranges itself, in the same order, with the same bits.  So every wait ends.
+//   - The number is the call's, never the same for two calls that can be under way together, and the how manieth launch on its words this
+//     is (each workgroup takes a ticket as it starts): a graph that is replayed does not take the words of the replay before for its own,
+//     and calls that overlap on the same words find numbers that are not theirs.
+// Bound by two round trips to memory and the exchange (32 x 128 x 320 bf16, us from the first start: requests out 1.6, sums 2.4, all
+// there 3.3, moments 3.8, stored 4.4), by the rates of both beyond some 10 MB.  A launch after another, against two launches or (up to sixteen
+// pixels per lane) a workgroup per group: 1024 x 320 float 7.3 -> 5.0 us, 4096 x 320 bf16 12.1 -> 6.7, 494 x 1280 float 6.5 -> 5.2,
+// 1024 x 1280 bf16 10.8 -> 6.1, 4096 x 640 float 15.1 -> 8.8, 16384 x 960 bf16 27.1 -> 24.7.  One lane-ordered sum in LDS for the
+// eight words of a workgroup (sums through LDS lane by lane, moments with the cached sums behind the exchange) took 2.5 us more.
+constexpr int kGnMeetParts = 32, kGnMeetBatch = 8, kGnMeetGroups = 4, kGnMeetWait = 1024;
+// 8-byte words of a (batch item, slab): a line with the counter of tickets, then 8 per workgroup; and of a launch with P workgroups per slab
+__host__ __device__ constexpr int gn_meet_stride(int P) { return 8 + 8 * P; }
+constexpr size_t gn_meet_words(int P) { return (size_t)kGnMeetBatch * 8 * gn_meet_stride(P); }
+// launches with 2, 4, .. 32 workgroups per slab have words of their own, one after the other
+constexpr size_t gn_meet_offset(int P) {
+  size_t o = 0;
+  for (int q = 2; q < P; q *= 2) o += gn_meet_words(q);
+  return o;
+}
+constexpr size_t kGnMeetWords = gn_meet_offset(2 * kGnMeetParts);
+constexpr int kGnMeetCopies = 4;                         // of the library's own words, for calls that overlap
+__device__ __align__(256) unsigned long long g_gn_words[kGnMeetCopies * kGnMeetWords];
+
+// Indices come from shifts and reciprocals (P, the segments and a slab's groups are powers of two): tp lanes hold a pixel's channels of the
+// slab, ppb pixels go through a workgroup at once.
+struct GnMeet {
+  unsigned long long* words;
+  unsigned int id, tp_recip, cg_recip;
+  int lgP, lgS, tp, ppb, pix_part, wait;                 // lgS: of the workgroups of a segment
+};
+
+// The wave's sums of eight words per lane: word 4 (lane / 32) + 2 (lane / 16 % 2) + lane / 8 % 2 in every eight lanes.  A step adds half of the
+// words in half of the lanes.
+__device__ __forceinline__ float swap_add32(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float swap_add16(float x, float y) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float wave_total8(const float (&w)[8], int lane) {
+  float a[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) a[i] = swap_add32(w[i], w[i + 4]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) c[i] = swap_add16(a[i], a[i + 2]);
+  const bool up = lane & 8;
+  float t = (up ? c[1] : c[0]) + lane_move<0x128>(up ? c[0] : c[1]);   // row_ror:8
+  t += lane_move<0x141>(t);                              // row_half_mirror
+  t += lane_move<0xb1>(t);                               // quad_perm: lane ^ 1
+  t += lane_move<0x4e>(t);                               // lane ^ 2
+  return t;
+}
+// The sum over lanes lane % 8, + 8, + 16, ..: over 8 `over` of them (over = 1, 2, 4, 8)
+__device__ __forceinline__ float eighth_total(float t, int over) {
+  if (over > 1) t += lane_move<0x128>(t);
+  if (over > 2) t = swap_add16(t, t);
+  if (over > 4) t = swap_add32(t, t);
+  return t;
+}
+
+template <typename Tin, typename Tout, int NV, bool PAIR>
+__global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x, Tout* __restrict__ y, const float* stale,
+                                                       float* sums_out, const float* __restrict__ gamma,
+                                                       const float* __restrict__ beta, int pix, int C, int G, int nseg, int B,
+                                                       int patch_idx, int N, float eps, int stat_mode, int silu, int packed,
+                                                       GnHalo halo, GnCount cnt, GnMeet mt, GnFrom<PAIR> pr) {
+  constexpr int V = Elem<Tin>::kVec, NP = kGnMeetParts / 8;
+  __shared__ float s_wave[2][16][8], s_all[kGnMeetParts][8], s_mom[kGnMeetGroups][3];
+  __shared__ int s_met;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slab = blockIdx.x & 7, loc = blockIdx.x >> 3, P = 1 << mt.lgP;
+  const int b = loc >> mt.lgP, part = loc & (P - 1), pps = 1 << mt.lgS;
+  unsigned long long* const words = mt.words + (size_t)(b * 8 + slab) * gn_meet_stride(P);
+  unsigned int ticket = 0;
+  if (tid == 0) ticket = __hip_atomic_fetch_add((unsigned int*)words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int Gs = G >> 3, g0 = slab * Gs, cg = C / G;
+  const int psub = (int)quotient_u32(tid, mt.tp, mt.tp_recip), tc = tid - psub * mt.tp;
+  const int cl = tc * V, la = (int)quotient_u32(cl, cg, mt.cg_recip), nb = (la + 1) * cg - cl;   // group of the slab, and its channels here
+  const int c0 = slab * (C >> 3) + cl;
+  const bool active = psub < mt.ppb;
+  const long long item = (long long)b * nseg * pix;      // the batch item's first pixel
+  const float pa = gn_value<PAIR>(x, pr, C, item, (g0 + la) * cg), pb = gn_value<PAIR>(x, pr, C, item, (g0 + (nb < V ? la + 1 : la)) * cg);
+  // first wave: lane j * Gs + i holds patch j's cached sums of group g0 + i
+  const bool cached = stale != nullptr && !(nseg > 1 || (N == 1 && stat_mode != DF_GN_STALE));
+  float2 st = make_float2(0.f, 0.f);
+  float gpiv = 0.f;
+  if (wave == 0) {
+    const int lg = Gs >> 1;                              // (Gs = 1, 2, 4)
+    if (cached && lane < N * Gs) {
+      const float* sp = stale + (((long long)(lane >> lg) * B + b) * G + g0 + (lane & (Gs - 1))) * 2;
+      st.x = sp[0]; st.y = sp[1];
+    }
+    if (lane < Gs) gpiv = gn_value<PAIR>(x, pr, C, item, (g0 + lane) * cg);
+  }
+  int pitch;
+  const Tin* xs;                                         // where the lane's channels of a batch item's pixels begin
+  unsigned int xo = 0;
+  if constexpr (PAIR) {
+    xs = gn_source<PAIR>(x, pr, C, c0, &pitch);
+    xs += item * pitch;
+  } else {
+    pitch = C;
+    xs = x + item * C;                                   // (uniform: the lane's part is an offset)
+    xo = (unsigned int)c0 * (unsigned int)sizeof(Tin);
+  }
+  u32x4 raw[NV];
+  auto request = [&](int q) {                            // range q of the batch item; pixels that it does not have are others
+    const unsigned int unit = (unsigned int)pitch * (unsigned int)sizeof(Tin), end = (unsigned int)(pix - 1) * unit + xo;
+    const char* const base = (const char*)(xs + (long long)(q >> mt.lgS) * pix * pitch);
+    unsigned int o = (unsigned int)((q & (pps - 1)) * mt.pix_part + psub) * unit + xo;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      raw[k] = *reinterpret_cast<const u32x4*>(base + (o < end ? o : end));
+      o += (unsigned int)mt.ppb * unit;
+    }
+  };
+  auto range = [&](int q, int& lo, int& hi) {
+    lo = (q & (pps - 1)) * mt.pix_part;
+    hi = lo + mt.pix_part < pix ? lo + mt.pix_part : pix;
+  };
+  // sums of range q, which is in the registers, to the first wave: word lane % 8 is the sum (0 - 3) or the sum of squares (4 - 7) of x - pivot
+  // of group lane % 4
+  auto sums = [&](int q, int buf) {
+    int lo, hi;
+    range(q, lo, hi);
+    float s0 = 0.f, q0 = 0.f, s1 = 0.f, q1 = 0.f;
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const bool here = active && lo + psub + k * mt.ppb < hi;
+      float v[V];
+      unpack_vec<Tin>(raw[k], v);
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const bool first = i < nb;
+        const float d = here ? v[i] - (first ? pa : pb) : 0.f;
+        const float d0 = first ? d : 0.f, d1 = first ? 0.f : d;
+        s0 += d0; q0 = fmaf(d0, d0, q0);
+        s1 += d1; q1 = fmaf(d1, d1, q1);
+      }
+      if constexpr (NV > 4) __builtin_amdgcn_sched_barrier(0);          // (a pixel at a time: 128 registers per lane)
+    }
+    float w[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      w[i] = la == i ? s0 : la + 1 == i ? s1 : 0.f;
+      w[i + 4] = la == i ? q0 : la + 1 == i ? q1 : 0.f;
+    }
+    const float t = wave_total8(w, lane);
+    if ((lane & 7) == 0) s_wave[buf][wave][lane >> 3] = t;
+    __syncthreads();
+    float r = 0.f;
+    if (wave == 0) r = eighth_total(s_wave[buf][lane >> 3][lane & 7] + s_wave[buf][8 + (lane >> 3)][lane & 7], 8);
+    return r;
+  };
+  request(part);
+  const float mine = sums(part, 0);
+  float gm[V], bt[V];                                    // (beside the exchange)
+  ld_vec(gamma + c0, gm); ld_vec(beta + c0, bt);
+  if constexpr (V == 8) { ld_vec(gamma + c0 + 4, gm + 4); ld_vec(beta + c0 + 4, bt + 4); }
+  __builtin_amdgcn_sched_barrier(0);
+  bool met = false;
+  float val[NP];                                         // word lane % 8 of range lane / 8 + 8 i
+  double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
+  if (wave == 0) {
+    // the cached sums are here before this workgroup's sums go out: the first one writes the patch's own, which may lie among them
+    asm volatile("" ::"v"(st.x), "v"(st.y));
+    const unsigned int tag = (mt.id << 16) | (((unsigned int)__builtin_amdgcn_readfirstlane((int)ticket) >> mt.lgP) & 0xffffu);
+    if (lane < 8)
+      __hip_atomic_store(words + 8 + part * 8 + lane, (unsigned long long)tag << 32 | __float_as_uint(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (cached)
+      for (int j = 0; j < N; ++j) {                      // patch order fixes the order of the additions
+        const float aj = __shfl(st.x, j * Gs + (lane & (Gs - 1)), 64), cj = __shfl(st.y, j * Gs + (lane & (Gs - 1)), 64);
+        if (j == patch_idx) { own_s = aj; own_q = cj; } else { st_s += aj; st_q += cj; }
+      }
+    for (int n = 0; n < mt.wait && !met; ++n) {
+      bool ok = true;
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        unsigned long long w = (unsigned long long)tag << 32;
+        if ((lane >> 3) + 8 * i < P) w = __hip_atomic_load(words + 8 + lane + 64 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        val[i] = __uint_as_float((unsigned int)w);
+        ok &= (unsigned int)(w >> 32) == tag;
+      }
+      met = __all(ok);
+    }
+    if (lane == 0) s_met = met;
+  }
+  auto moments = [&] {                                   // of the slab's groups, by lanes 0 .. Gs - 1 of the first wave
+    double tot_s = 0.0, tot_q = 0.0;
+    auto add = [&](float t, int sg) {                    // a segment's words
+      double S, SS;
+      gn_unshift(t, lane_move<0x104>(t), cnt.n_loc, gpiv, S, SS);   // row_shl:4
+      tot_s += S; tot_q += SS;
+      if (nseg > 1 && part == 0 && lane < Gs) {
+        float* o = sums_out + (((long long)sg * B + b) * G + g0 + lane) * 2;
+        o[0] = (float)S; o[1] = (float)SS;
+      }
+    };
+    if (nseg == 1) {
+      float t = val[0];
+#pragma unroll
+      for (int i = 1; i < NP; ++i) t += val[i];
+      add(eighth_total(t, 8), 0);
+    } else {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) val[i] = eighth_total(val[i], pps < 8 ? pps : 8);
+      for (int sg = 0; sg < nseg; ++sg) {
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+          if (i >= (sg * pps) >> 3 && 8 * i < (sg + 1) * pps) t += val[i];
+        add(__shfl(t, ((sg * pps) & 7) * 8 + (lane & 7), 64), sg);
+      }
+    }
+    if (lane < Gs) {
+      const GnMoments mo = gn_combine_pre(tot_s, tot_q, cnt, nseg, N, stat_mode, st_s, st_q, own_s, own_q, eps);
+      s_mom[lane][0] = mo.mean_hi; s_mom[lane][1] = mo.mean_lo; s_mom[lane][2] = mo.rstd;
+      if (nseg == 1 && sums_out != nullptr && part == 0) {
+        float* o = sums_out + ((long long)b * G + g0 + lane) * 2;
+        o[0] = (float)tot_s; o[1] = (float)tot_q;
+      }
+    }
+  };
+  if (met) moments();
+  __syncthreads();
+  if (!s_met) {
+    // a range did not appear: this workgroup adds up all of them itself
+#pragma unroll 1
+    for (int q = 0; q < P; ++q) {
+      request(q);
+      const float r = sums(q, (q + 1) & 1);
+      if (wave == 0 && lane < 8) s_all[q][lane] = r;
+    }
+    request(part);
+    if (wave == 0) {
+#pragma unroll
+      for (int i = 0; i < NP; ++i) val[i] = (lane >> 3) + 8 * i < P ? s_all[(lane >> 3) + 8 * i][lane & 7] : 0.f;
+      moments();
+    }
+    __syncthreads();
+  }
+  if (!active) return;
+  const int lb = nb < V ? la + 1 : la;
+  const float ma = s_mom[la][0], mla = s_mom[la][1], ra = s_mom[la][2], mb = s_mom[lb][0], mlb = s_mom[lb][1], rb = s_mom[lb][2];
+  int lo, hi;
+  range(part, lo, hi);
+  const int seg = part >> mt.lgS;
+#pragma unroll
+  for (int i = 0; i < V; ++i) gm[i] *= i < nb ? ra : rb;
+#pragma unroll
+  for (int k = 0; k < NV; ++k) {
+    const int p = lo + psub + k * mt.ppb;
+    if (p >= hi) break;
+    float v[V];
+    unpack_vec<Tin>(raw[k], v);
+    const long long m = item + (long long)seg * pix + p;
+    if constexpr (PAIR) {
+      const u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+      *reinterpret_cast<u32x2*>(pr.cat + m * C + c0) = t;
+    }
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float t = fmaf((v[i] - (i < nb ? ma : mb)) - (i < nb ? mla : mlb), gm[i], bt[i]);
+      v[i] = silu ? silu_f(t) : t;
+    }
+    Tout* o = y + m * C + c0;
+    if (packed) o = y + (((m >> 5) * (C >> 4) + (c0 >> 4)) * 64 + (m & 31) + 32 * ((c0 >> 3) & 1)) * 8 + (c0 & 7);
+    if constexpr (sizeof(Tout) == sizeof(Tin)) {
+      st_vec(o, v);
+    } else {
+      const u32x2 t = {pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3])};
+      *reinterpret_cast<u32x2*>(o) = t;
+    }
+    if constexpr (sizeof(Tout) == 2) {
+      if (halo.out) halo_store<V>(halo, b, (long long)seg * pix + p, C, c0, v);
+    }
+    if constexpr (NV > 4) __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 // Strips of the two-launch path: as close to target_blocks strips as the pixel count allows (the chip has 256
 // compute units and a strip is one block in either launch); a small tensor gets short strips and blocks with few
 // pixel slots rather than few blocks.
@@ -752,6 +1046,8 @@ GnLayout gn_layout(int C, int vec, long long pix, int target_blocks, int max_thr
 
 }  // namespace
 
+size_t groupnorm_meet_bytes() { return kGnMeetWords * sizeof(unsigned long long); }
+
 size_t groupnorm_scratch_bytes(int B, int nseg, int G, int N) {
   // snapshot of the cached sums + partials of at most kGnMaxStrips strips per batch item
   (void)nseg;
@@ -759,8 +1055,35 @@ size_t groupnorm_scratch_bytes(int B, int nseg, int G, int N) {
 }
 
 namespace {
-// One launch that keeps its pixels in registers (nv > 0: that many per lane), one launch of a workgroup per group (`group`), or two.
-struct GnForm { int v, nv; bool group; };
+// One launch that keeps its pixels in registers (nv > 0: that many per lane; P > 0: P workgroups per slab), one launch of a workgroup per
+// group (`group`), or two.
+struct GnForm { int v, nv; bool group; int P, tp, ppb, pix_part; };
+// The form whose workgroups hand each other their sums (P = 0: it does not take the call).  As many workgroups as the compute units of
+// an XCD while each has a pixel per lane: 64 x 64 x 640 float 8.8 us with 32 per slab, 10.5 with 16; two batch items 12.6 with 16 each, 15.6 with 32.
+GnForm gn_meet_form(const GnArgs& a) {
+  GnForm f = {};
+  const int V = a.in_dtype == DF_BF16 ? 8 : 4, Gs = a.G / 8;
+  const long long pix = (long long)a.Rseg * a.W;
+  if (a.G % 8 || (Gs != 1 && Gs != 2 && Gs != 4) || a.C % (8 * V) || a.C / a.G < V || a.N > 16 || a.B > kGnMeetBatch) return f;
+  if (a.nseg != 1 && a.nseg != 2 && a.nseg != 4 && a.nseg != 8) return f;
+  // y over x: a workgroup that has to add up another's range would find results in it
+  const size_t n = (size_t)a.B * a.nseg * pix * a.C;
+  const uintptr_t x = (uintptr_t)a.x, y = (uintptr_t)a.y;
+  if (x && x < y + n * (a.out_dtype == DF_BF16 ? 2 : 4) && y < x + n * (a.in_dtype == DF_BF16 ? 2 : 4)) return f;
+  f.tp = a.C / 8 / V;
+  if (f.tp > 1024) return f;
+  f.ppb = 1024 / f.tp;
+  int P = a.nseg;
+  while (P < 2 || (2 * P <= kGnMeetParts / a.B && pix > (long long)f.ppb * (P / a.nseg))) P *= 2;
+  if (const char* e = tune_env("DF_GN_MEET")) { if (atoi(e) > 1) P = atoi(e); if (P < 2 || P % a.nseg) return f; }
+  const long long part = (pix + P / a.nseg - 1) / (P / a.nseg), nv = (part + f.ppb - 1) / f.ppb;
+  if (nv > 8) return f;                                  // (sixteen do not fit the registers)
+  f.nv = 1;
+  while (f.nv < nv) f.nv *= 2;
+  f.pix_part = (int)part;
+  f.P = P;
+  return f;
+}
 GnForm gn_form(const GnArgs& a) {
   const int cg = a.C / a.G;
   const long long pix_seg = (long long)a.Rseg * a.W, per_group = pix_seg * a.nseg * cg;
@@ -773,6 +1096,14 @@ GnForm gn_form(const GnArgs& a) {
   int nv = a.nseg == 1 && ppass && pix_seg <= (long long)ppass * 16 ? 2 : 0;
   while (nv && (long long)ppass * nv < pix_seg) nv *= 2;
   if (no_fused) return {v, 0, false};
+  // Handing over the sums costs 1 us, which a workgroup per group saves while its lanes have up to four pixels (300 x 1280 float 5.0 us both
+  // ways, bf16 5.2 against 5.6; 494 x 960 5.9 against 5.1 and 6.2 against 5.9, 1024 x 320 7.3 against 5.0 and 6.6 against 5.7).
+  // Of bf16 values, whose lanes hold twice as many channels, it takes more (300 x 960: 5.4 against 5.6).
+  const char* e = tune_env("DF_GN_MEET");
+  if (e ? atoi(e) != 0 : (nv == 0 || nv >= 8) && per_group >= (a.in_dtype == DF_BF16 ? 10000 : 8000)) {
+    const GnForm m = gn_meet_form(a);
+    if (m.P) return m;
+  }
   return {v, nv, !nv && cg % 4 == 0 && cg / 4 <= 1024 && per_group <= kGnGroupMaxElems};
 }
 }  // namespace
@@ -788,6 +1119,29 @@ GnFrom<PAIR> gn_from(const GnArgs& a) {
 bool groupnorm_takes_pair(const GnArgs& a) {
   return a.G > 0 && a.C % a.G == 0 && a.in_dtype == DF_F32 && a.out_dtype == DF_BF16 && a.x2_from % 4 == 0 && !gn_form(a).group;
 }
+
+namespace {
+int ilog2(int n) { return n > 1 ? 1 + ilog2(n / 2) : 0; }
+unsigned int gn_call_number() {
+  static std::atomic<unsigned int> n{0};
+  return n.fetch_add(1, std::memory_order_relaxed) % 0xffffu + 1;   // (never 0: words that nobody has written)
+}
+// The words of a launch: the caller's, or the library's on the current device
+unsigned long long* gn_words(const GnArgs& a, int P, unsigned int call) {
+  if (a.meet) return (unsigned long long*)a.meet + gn_meet_offset(P);
+  static std::atomic<unsigned long long*> at[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+  unsigned long long* w = at[dev].load(std::memory_order_relaxed);
+  if (!w) {
+    void* ptr = nullptr;
+    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_gn_words)) != hipSuccess || !ptr) { (void)hipGetLastError(); return nullptr; }
+    w = (unsigned long long*)ptr;
+    at[dev].store(w, std::memory_order_relaxed);
+  }
+  return w + (call % kGnMeetCopies) * kGnMeetWords + gn_meet_offset(P);
+}
+}  // namespace
 
 int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   const int vec = a.in_dtype == DF_BF16 ? 8 : 4;
@@ -823,6 +1177,29 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
     const GnForm form = gn_form(a);
     const int v = form.v, nv = form.nv;
     if (a.x2 && form.group) return DF_ESHAPE;
+    if (form.P) {
+      const unsigned int call = gn_call_number();
+      const GnMeet mt = {gn_words(a, form.P, call), call, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
+                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : kGnMeetWait};
+      if (!mt.words) return DF_EHIP;
+#define DF_GN_MEET(TI, TO, NVV, PR)                                                                                         \
+  hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
+                     a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,      \
+                     a.silu, a.y_packed, halo, cnt, mt, gn_from<PR>(a))
+#define DF_GN_MEET_T(NVV)                                                                                                    \
+  {                                                                                                                          \
+    if (a.x2) DF_GN_MEET(float, bf16_t, NVV, true);                                                                          \
+    else if (a.in_dtype == DF_BF16) DF_GN_MEET(bf16_t, bf16_t, NVV, false);                                                  \
+    else if (a.out_dtype == DF_BF16) DF_GN_MEET(float, bf16_t, NVV, false);                                                  \
+    else DF_GN_MEET(float, float, NVV, false);                                                                               \
+  }
+      if (form.nv == 1) DF_GN_MEET_T(1) else if (form.nv == 2) DF_GN_MEET_T(2) else if (form.nv == 4) DF_GN_MEET_T(4)
+      else DF_GN_MEET_T(8)
+#undef DF_GN_MEET_T
+#undef DF_GN_MEET
+      DF_LAUNCH_CHECK();
+      return DF_OK;
+    }
     if (nv || form.group) {
       dim3 grid(a.G, a.B);
       if (nv) {
@@ -951,7 +1328,7 @@ int launch_gn_strip_sums(const void* x, int in_dtype, float* sums, int B, int R,
 // Argument validation shared by the two GroupNorm entry points of the C ABI.
 int groupnorm_entry(const void* x_fresh, void* y, const float* stale_stats, float* fresh_stats_out, const float* gamma,
                     const float* beta, int B, int R, int W, int C, int G, int patch_idx, int N, float eps, int stat_mode,
-                    int fuse_silu, int dtype, const Scratch* scr, hipStream_t st) {
+                    int fuse_silu, int dtype, const Scratch* scr, hipStream_t st, int looks) {
   if (!x_fresh || !y || !gamma || !beta || (dtype != DF_F32 && dtype != DF_BF16)) return DF_EINVAL;
   if (stat_mode < DF_GN_SUMS || stat_mode > DF_GN_STALE) return DF_EINVAL;
   if (B <= 0 || R <= 0 || W <= 0 || C <= 0 || G <= 0 || N <= 0 || patch_idx < 0 || patch_idx >= N) return DF_ESHAPE;
@@ -961,7 +1338,7 @@ int groupnorm_entry(const void* x_fresh, void* y, const float* stale_stats, floa
   a.x = x_fresh; a.y = y; a.stale = stale_stats; a.sums_out = fresh_stats_out; a.gamma = gamma; a.beta = beta;
   a.B = B; a.Rseg = R; a.W = W; a.C = C; a.G = G; a.nseg = 1; a.patch_idx = patch_idx; a.N = N; a.eps = eps;
   a.stat_mode = stat_mode; a.silu = fuse_silu ? 1 : 0; a.in_dtype = dtype; a.out_dtype = dtype;
-  a.scr = scr;
+  a.scr = scr; a.looks = looks;
   return launch_groupnorm(a, st);
 }
 

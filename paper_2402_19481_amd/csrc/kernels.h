@@ -60,7 +60,11 @@ struct GnArgs {
   const float* x2;
   int x2_from;
   void* cat_out;
+  // groupnorm_meet_bytes() in which workgroups hand each other sums, zero once and not used by launches that overlap; nullptr: the library's
+  void* meet;
+  int looks;            // -1: workgroups add up everything themselves (the same result; for tests)
 };
+size_t groupnorm_meet_bytes();
 bool groupnorm_takes_pair(const GnArgs& a);
 int launch_groupnorm(const GnArgs& a, hipStream_t st);
 // Per-strip (sum, sum of squares) of a full image split into N vertical strips: x [B, R, W, C] (float or bf16) ->
@@ -69,7 +73,7 @@ int launch_gn_strip_sums(const void* x, int in_dtype, float* sums, int B, int R,
 // df_groupnorm_stale's arguments, validated and launched with the given scratch region (nullptr: the library's)
 int groupnorm_entry(const void* x_fresh, void* y, const float* stale_stats, float* fresh_stats_out, const float* gamma,
                     const float* beta, int B, int R, int W, int C, int G, int patch_idx, int N, float eps, int stat_mode,
-                    int fuse_silu, int dtype, const Scratch* scr, hipStream_t st);
+                    int fuse_silu, int dtype, const Scratch* scr, hipStream_t st, int looks = 0);
 size_t groupnorm_scratch_bytes(int B, int nseg, int G, int N);
 
 // ---- conv.hip / gemm ----

@@ -297,6 +297,7 @@ struct df_unet {
   // scratch region of the step's kernels (GroupNorm partials, split-K / split-key partials, the page of zeros): part
   // of the caller's workspace, right after the plan-owned weights, so recorded graphs hold plan-owned addresses only
   Scratch scr = {nullptr, 0};
+  char* meet = nullptr;          // behind it: where workgroups of the GroupNorms hand each other their sums
 };
 
 namespace {
@@ -323,6 +324,7 @@ struct Exec {
   const std::map<std::string, PackedW>* packed = nullptr;
   int gn_mode = DF_GN_SUMS;      // GroupNorm statistic mode of a DISPLACED step
   const Scratch* scr = nullptr;  // the plan's scratch region
+  void* meet = nullptr;          // where workgroups of its GroupNorms hand each other their sums
   const bf16_t* kv_packed[4] = {nullptr, nullptr, nullptr, nullptr};
   int kv_count[4] = {0, 0, 0, 0};
   int kv_cursor[4] = {0, 0, 0, 0};
@@ -443,7 +445,7 @@ struct Exec {
     a.eps = eps; a.silu = silu;
     a.stat_mode = gn_mode;
     a.y_packed = y_packed;
-    a.scr = scr;
+    a.scr = scr; a.meet = meet;
     if (cat) { a.x = cat->a; a.x2 = cat->b; a.x2_from = cat->ca; a.cat_out = cat->bf; }
     if (halo_entry && (full() || refresh)) {
       // the consumer convolution's boundary-row (boundary-column) state is refreshed by this kernel's store loop
@@ -1041,7 +1043,7 @@ DryResult dry_run(const df_unet_cfg& c, const std::vector<BlockDesc>& blocks) {
   r.packed_bytes = end;
   if (r.scratch < kScratchCounterBytes) r.scratch = kScratchCounterBytes;
   r.scratch = align256(r.scratch);
-  r.ws_bytes += end + r.scratch + 256;
+  r.ws_bytes += end + r.scratch + align256(groupnorm_meet_bytes()) + 256;
   return r;
 }
 
@@ -1169,7 +1171,8 @@ int df_unet_create(df_unet** out, const df_unet_cfg* cfg, const void* const* wei
   }
   u->scr.ptr = u->ws + d.packed_bytes;
   u->scr.bytes = d.scratch;
-  if (scratch_init(u->scr) != DF_OK) { delete u; return DF_EHIP; }
+  u->meet = u->scr.ptr + u->scr.bytes;
+  if (hipMemset(u->meet, 0, groupnorm_meet_bytes()) != hipSuccess || scratch_init(u->scr) != DF_OK) { delete u; return DF_EHIP; }
   *out = u;
   return DF_OK;
 }
@@ -1207,8 +1210,10 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
   if (((uintptr_t)x % 16) || ((uintptr_t)text % 16) || ((uintptr_t)stale % 256) || ((uintptr_t)eps_out % 16))
     return DF_EINVAL;
   Exec e{u->cfg, u->blocks, &u->w, false, mode, mode == DF_MODE_FULL ? 0 : patch_idx, refresh ? 1 : 0,
-         (hipStream_t)stream, u->ws + u->packed_bytes + u->scr.bytes, u->ws_bytes - u->packed_bytes - u->scr.bytes};
+         (hipStream_t)stream, u->meet + align256(groupnorm_meet_bytes()),
+         u->ws_bytes - u->packed_bytes - u->scr.bytes - align256(groupnorm_meet_bytes())};
   e.scr = &u->scr;
+  e.meet = u->meet;
   for (int lv = 0; lv < 4; ++lv) {
     e.kv_count[lv] = u->kv_count[lv];
     e.kv_packed[lv] = (const bf16_t*)(u->ws + u->kv_off[lv]);
