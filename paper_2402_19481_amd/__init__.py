@@ -5,7 +5,8 @@ live on the GPU, passes their device pointers and the current HIP stream to
 the C entry point of the same name, and raises on a non-zero return code.
 PyTorch provides device memory and streams, nothing else.  There is no
 fallback: if the shared library is missing or not built, importing a function
-raises.
+raises.  The operations that are issued one by one go through a native module
+(csrc/binding.cpp), the plan and the rest through ctypes.
 """
 import ctypes
 import os
@@ -153,25 +154,35 @@ def copy_bytes(dst, src):
     _check(lib().df_copy_bytes(_ptr(dst), _ptr(src), src.numel() * src.element_size(), _stream()))
 
 
+_ops = None
+
+
+def _native():
+    """The native binding of the single operations (csrc/binding.cpp), with the entry points of the library that is loaded."""
+    global _ops
+    if _ops is None:
+        L = lib()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise DfError(f"{_HERE}/_binding.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` first") from e
+        _binding.setup(DfError, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
+            "df_strerror", "df_groupnorm_stale", "df_conv3x3_halo_axis", "df_attn_displaced", "df_attn_displaced_axis", "df_linear",
+            "df_buffer_refresh")))
+        _ops = _binding
+    return _ops
+
+
 def buffer_refresh(dst_full, src_patch, patch_idx, N):
     """dst_full [B, ...full...] <- src_patch [B, ...full/N...] at the patch's region (in place)."""
-    B = dst_full.shape[0]
-    _check(lib().df_buffer_refresh(_ptr(dst_full), _ptr(src_patch), B, dst_full.numel() // B, patch_idx, N,
-                                   _dt(dst_full), _stream()))
-    return dst_full
+    return (_ops or _native()).buffer_refresh(dst_full, src_patch, patch_idx, N)
 
 
 def groupnorm_stale(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS,
                     fuse_silu=False, fresh_stats_out=None):
     """Returns (y, fresh_stats [B,G,2])."""
-    B, R, W, C = x_fresh.shape
-    y = torch.empty_like(x_fresh)
-    if fresh_stats_out is None:
-        fresh_stats_out = torch.empty(B, G, 2, dtype=torch.float32, device=x_fresh.device)
-    _check(lib().df_groupnorm_stale(_ptr(x_fresh), _ptr(y), _ptr(stale_stats), _ptr(fresh_stats_out), _ptr(gamma),
-                                    _ptr(beta), B, R, W, C, G, patch_idx, N, eps, stat_mode, int(fuse_silu),
-                                    _dt(x_fresh), _stream()))
-    return y, fresh_stats_out
+    return (_ops or _native()).groupnorm_stale(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps, stat_mode, int(fuse_silu),
+                                               fresh_stats_out)
 
 
 def groupnorm_stale_alone(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS, fuse_silu=False):
@@ -195,26 +206,11 @@ def groupnorm_stale_noalloc(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, 
 
 
 def conv3x3_halo(x_fresh, stale_full, w, bias, patch_idx, N, stride=1, act=0):
-    B, R, W, Cin = x_fresh.shape
-    Cout = w.shape[0]
-    H = R * N
-    y = torch.empty(B, R // stride, W // stride, Cout, dtype=x_fresh.dtype, device=x_fresh.device)
-    _check(lib().df_conv3x3_halo(_ptr(x_fresh), _ptr(stale_full), _ptr(w), _ptr(bias), _ptr(y), B, H, W, Cin, Cout,
-                                 patch_idx, N, stride, act, _dt(x_fresh), _stream()))
-    return y
+    return (_ops or _native()).conv3x3_halo(x_fresh, stale_full, w, bias, patch_idx, N, stride, act, SPLIT_ROWS)
 
 
 def attn_displaced(q, k_fresh, v_fresh, k_stale, v_stale, heads, patch_idx, N, scale=None, out=None):
-    B, Lq, C = q.shape
-    d = C // heads
-    L = Lq * N
-    if scale is None:
-        scale = d ** -0.5
-    if out is None:
-        out = torch.empty_like(q)
-    _check(lib().df_attn_displaced(_ptr(q), _ptr(k_fresh), _ptr(v_fresh), _ptr(k_stale), _ptr(v_stale), _ptr(out), B,
-                                   L, heads, d, patch_idx, N, scale, _dt(q), _stream()))
-    return out
+    return (_ops or _native()).attn_displaced(q, k_fresh, v_fresh, k_stale, v_stale, heads, patch_idx, N, scale, out)
 
 
 def buffer_refresh_cols(dst_full, src_patch, patch_idx, N):
@@ -227,34 +223,19 @@ def buffer_refresh_cols(dst_full, src_patch, patch_idx, N):
 
 def conv3x3_halo_cols(x_fresh, stale_full, w, bias, patch_idx, N, stride=1, act=0):
     """Vertical strip: x_fresh [B, H, W/N, Cin], stale_full [B, H, W, Cin]."""
-    B, H, Wp, Cin = x_fresh.shape
-    Cout = w.shape[0]
-    y = torch.empty(B, H // stride, Wp // stride, Cout, dtype=x_fresh.dtype, device=x_fresh.device)
-    _check(lib().df_conv3x3_halo_axis(_ptr(x_fresh), _ptr(stale_full), _ptr(w), _ptr(bias), _ptr(y), B, H, Wp * N, Cin,
-                                      Cout, patch_idx, N, stride, act, _dt(x_fresh), SPLIT_COLS, _stream()))
-    return y
+    return (_ops or _native()).conv3x3_halo(x_fresh, stale_full, w, bias, patch_idx, N, stride, act, SPLIT_COLS)
 
 
 def attn_displaced_cols(q, k_fresh, v_fresh, k_stale, v_stale, heads, H, W, patch_idx, N, scale=None):
     """Vertical strip of an H x W token grid: q, k_fresh, v_fresh [B, H*W/N, C], k_stale, v_stale [B, H*W, C]."""
-    B, Lq, C = q.shape
-    d = C // heads
-    if scale is None:
-        scale = d ** -0.5
-    out = torch.empty_like(q)
-    _check(lib().df_attn_displaced_axis(_ptr(q), _ptr(k_fresh), _ptr(v_fresh), _ptr(k_stale), _ptr(v_stale), _ptr(out),
-                                        B, H, W, heads, d, patch_idx, N, scale, _dt(q), SPLIT_COLS, _stream()))
-    return out
+    return (_ops or _native()).attn_displaced_axis(q, k_fresh, v_fresh, k_stale, v_stale, heads, H, W, patch_idx, N, scale, SPLIT_COLS)
 
 
 def linear(x, w, bias=None, residual=None, out_dtype=torch.bfloat16, out=None):
     """x [M,K] bf16, w [N,K] bf16 -> [M,N] (+ bias + residual)."""
-    M, K = x.shape
-    N = w.shape[0]
-    if out is None:
-        out = torch.empty(M, N, dtype=out_dtype, device=x.device)
-    _check(lib().df_linear(_ptr(x), _ptr(w), _ptr(bias), _ptr(residual), _ptr(out), M, N, K, _dt(out), _stream()))
-    return out
+    if out is None and out_dtype is not torch.bfloat16 and out_dtype is not torch.float32:
+        raise DfError(f"unsupported dtype {out_dtype}")
+    return (_ops or _native()).linear(x, w, bias, residual, out, DF_BF16 if out_dtype is torch.bfloat16 else DF_F32)
 
 
 def attn_stale_vt(q, k, vt, heads, L, scale=None, packed=False):

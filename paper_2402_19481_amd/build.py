@@ -2,6 +2,7 @@
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,6 +21,26 @@ OBJ_TUNE = os.path.join(HERE, "_build_tune")
 LIB_TUNE = os.path.join(HERE, "libdistrifusion_tune.so")
 
 
+# The native binding of the single operations (csrc/binding.cpp): host code against torch's headers, a Python module beside the library.
+BINDING = os.path.join(HERE, "_binding.so")
+
+
+def _compile_binding():
+    import torch
+    from torch.utils import cpp_extension
+
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI,
+           *("-isystem" + p for p in [*cpp_extension.include_paths(), "/opt/rocm/include", sysconfig.get_paths()["include"]]),
+           os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L" + libs, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for binding.cpp:\n" + r.stderr)
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+
+
 def _compile(src, tuning=False):
     obj = os.path.join(OBJ_TUNE if tuning else OBJ, src.replace(".hip", ".o"))
     cmd = ["hipcc", *FLAGS, *(["-DDF_TUNING"] if tuning else []), "-c", os.path.join(CSRC, src), "-o", obj]
@@ -36,7 +57,10 @@ def build(verbose=True, tuning=False):
     os.makedirs(OBJ_TUNE if tuning else OBJ, exist_ok=True)
     srcs = [s for s in SOURCES if os.path.exists(os.path.join(CSRC, s))]
     with ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
+        binding = None if tuning else ex.submit(_compile_binding)
         objs = list(ex.map(lambda s: _compile(s, tuning), srcs))
+        if binding:
+            binding.result()
     lib = LIB_TUNE if tuning else LIB
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
