@@ -208,10 +208,18 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     src[q] = (row < BT ? (const char*)p.Xp + (size_t)mt * KF * 1024 : (const char*)p.Wp + (size_t)wrow(row - BT) * KF * 1024) +
              ((size_t)kt0 * BKF + kk) * 1024;
   }
+  // Plain layers of whole 1024s of tokens: the XCDs walk K from different stages on, an eighth apart.  Their shares of the tokens then begin
+  // powers of two apart, and in step the eight ask the same channels of the last-level cache: 2048 x 1280 x 5120 46.7 -> 40.5 us,
+  // 4096 x 640 x 2560 27.2 -> 24.6, 1024 x 1280 x 1280 11.2 -> 11.0; 1024 x 1024 full step 12.96 -> 12.78 ms, 2048 x 2048 strips 15.54 ->
+  // 15.36.  Other counts: 1800 x 1280 x 5120 38.7 -> 40.0, 7200 x 1280 x 1280 40.7 -> 41.3, on average of forty 1.000; the layers that
+  // fold a LayerNorm 0 - 3 % slower.  Within an XCD the workgroups stay in step, so that what one has fetched the others find in its L2 (an
+  // offset per tile: steps 2 - 5 % slower).
+  const int rot = EPI == EPI_PLAIN && !LN && MT % 32 == 0 ? (int)((blockIdx.x & 7) * (unsigned int)KT >> 3) : 0;
   // loads of a stage: all (STEP < 0), or part STEP of KS
   auto issue = [&](int kt, int slot, auto stepc) {
     constexpr int STEP = decltype(stepc)::value;
-    const unsigned int ko = (unsigned int)kt * (BKF * 1024);
+    const int kr = EPI == EPI_PLAIN && !LN ? kt + rot : kt;
+    const unsigned int ko = (unsigned int)(kr < KT ? kr : kr - KT) * (BKF * 1024);
 #pragma unroll
     for (int q = 0; q < NL; ++q) {
       if (STEP >= 0 && q * KS / NL != STEP) continue;
