@@ -97,6 +97,13 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   const int slabs_all = p.Cin / 64;
   const int s_lo = (int)((long long)slabs_all * blockIdx.y / gridDim.y), s_hi = (int)((long long)slabs_all * (blockIdx.y + 1) / gridDim.y);
 
+  // First channel of the slab that is being computed and of the one behind it.  The XCDs begin with different slabs: all
+  // of them read the same weights, and in step they ask the same channels of the last-level cache.  64 x 1280 -> 1280 13.9 -> 13.7 us, 494
+  // x 2560 -> 1280 44.8 -> 42.9, 1024 x 1280 -> 1280 40.8 -> 40.2, 4096 x 960 -> 320 31.1 -> 30.5; 300 x 2560 -> 1280 loses, 31.8 -> 33.7;
+  // 32 shapes 0.5 % on average.
+  const int slabs = s_hi - s_lo, rot = (int)((blockIdx.x & 7) * (unsigned int)slabs >> 3);
+  auto behind = [&](int c) { return c + 64 < s_hi * 64 ? c + 64 : s_lo * 64; };
+  int ch = (s_lo + rot) * 64, chn = behind(ch);
   // weight loads: instruction j of a tap covers output channels wrow(j) .. +7 of the tile, lane / 8 one of them
   const int lr = lane >> 3;
   auto wrow = [&](int j) { return (j * 8 + wave < BN / 8 ? j * 8 + wave : BN / 8 - 1) * 8; };
@@ -108,13 +115,13 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
     const int n = (n0 + row < p.N ? n0 + row : p.N - 1) - n0;   // ragged last tile: re-read, never stored
     w_ofs[j] = 2u * ((unsigned int)n * (unsigned int)p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8);
   }
-  auto load_w = [&](int slab, int st, int slot, int l) {   // load l of a stage: tap l / WJ, instruction l % WJ
+  auto load_w = [&](int ch, int st, int slot, int l) {     // load l of a stage: tap l / WJ, instruction l % WJ
     const int tp = l / WJ, j = l % WJ;
-    lds_load_buf(w_tile, w_ofs[j], 2u * ((st * TAPS + tp) * p.Cin + slab * 64), smem + 2 * IB + slot * WB + tp * (BN * 128) + wrow(j) * 128);
+    lds_load_buf(w_tile, w_ofs[j], 2u * ((st * TAPS + tp) * p.Cin + ch), smem + 2 * IB + slot * WB + tp * (BN * 128) + wrow(j) * 128);
   };
   // the first stage's weights, the coldest of what the loop waits for, are requested before the pixels' addresses are known
 #pragma unroll
-  for (int l = 0; l < WL; ++l) load_w(s_lo, 0, 0, l);
+  for (int l = 0; l < WL; ++l) load_w(ch, 0, 0, l);
   // pixel loads: instruction q of a wave covers rows (q * 8 + wave) * 8 + lane / 8 of the buffer, slot lane % 8
   const int RW = x.tw + 2, np = (x.th + 2) * RW;
   const bf16_t* in_ptr[NIN];
@@ -130,8 +137,8 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
     in_zero[q] = src == nullptr;
     in_ptr[q] = (src ? src : x.zeros) + ((lane & 7) ^ ((px >> 1) & 7)) * 8;
   }
-  auto load_in = [&](int slab, int buf, int q) {
-    const bf16_t* src = in_ptr[q] + (in_zero[q] ? 0 : slab * 64);
+  auto load_in = [&](int ch, int buf, int q) {
+    const bf16_t* src = in_ptr[q] + (in_zero[q] ? 0 : ch);
     lds_load16(src, smem + buf * IB + (q * 8 + wave) * 1024);
   };
 
@@ -186,14 +193,14 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   // next channels' pixels.  The last channels (LAST) request what is left of their own weights and nothing else: loaded once more to
   // keep the counts behind the waits they were a fifth of the loads of 320 channels.
   auto in_loads = [&](int st) { return st * IPS >= NIN ? 0 : (NIN - st * IPS < IPS ? NIN - st * IPS : IPS); };
-  auto issue = [&](auto lastc, int slab, int buf, int wslot, int st, int part) {
+  auto issue = [&](auto lastc, int buf, int wslot, int st, int part) {
     constexpr bool LAST = decltype(lastc)::value;
     const int ws = st + ST - 1, nw = LAST && ws >= NST ? 0 : WL, nin = LAST ? 0 : in_loads(st), n = nw + nin;
 #pragma unroll
     for (int l = 0; l < WL + IPS; ++l) {
       if (l >= n || l * NSUB / n != part) continue;
-      if (l < nw) load_w(slab + ws / NST, ws % NST, wslot, l);
-      else load_in(slab + 1, buf ^ 1, st * IPS + l - nw);
+      if (l < nw) load_w(ws / NST ? chn : ch, ws % NST, wslot, l);
+      else load_in(chn, buf ^ 1, st * IPS + l - nw);
     }
   };
   // loads that may still be in flight at the end of stage st: those requested in the last ST - 2 stages
@@ -211,12 +218,11 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
 #define DF_SB __builtin_amdgcn_sched_barrier(0)
   // prologue
 #pragma unroll
-  for (int q = 0; q < NIN; ++q) load_in(s_lo, 0, q);
+  for (int q = 0; q < NIN; ++q) load_in(ch, 0, q);
 #pragma unroll
   for (int s = 1; s < ST - 1; ++s) {
-    const int sw = s_lo + s / NST < s_hi ? s_lo + s / NST : s_hi - 1;
 #pragma unroll
-    for (int l = 0; l < WL; ++l) load_w(sw, s % NST, s, l);
+    for (int l = 0; l < WL; ++l) load_w(s / NST ? chn : ch, s % NST, s, l);
   }
   // the epilogue's arguments (cold in every launch) come beside the first operands
   asm volatile("" ::"s"(p.bias), "s"(p.chan_add), "s"(p.chan_ld), "s"(p.residual), "s"(p.ldr), "s"(p.out), "s"(p.ldo), "s"(p.act), "s"(x.partials));
@@ -226,8 +232,8 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   int slot = 0, wslot = ST - 1, buf = 0;
   using Last = std::true_type;
   using More = std::false_type;
-  if (s_lo + 1 < s_hi) issue(More{}, s_lo, 0, wslot, 0, 0);
-  else issue(Last{}, s_lo, 0, wslot, 0, 0);
+  if (s_lo + 1 < s_hi) issue(More{}, 0, wslot, 0, 0);
+  else issue(Last{}, 0, wslot, 0, 0);
   auto channels = [&](auto lastc, int slab) {
     constexpr bool LAST = decltype(lastc)::value;
 #pragma unroll
@@ -238,7 +244,7 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
         const int b = (st * NSUB + u) % NB, bn = (st * NSUB + u + 1) % NB;
         if (u + 1 < NSUB) {
           DF_SB; rd(slot, buf, st, u + 1, bn); DF_SB; mm(b); DF_SB;
-          issue(lastc, slab, buf, wslot, st, u + 1);
+          issue(lastc, buf, wslot, st, u + 1);
         } else if (LAST && st + 1 == NST) {
           DF_SB; mm(b); DF_SB;
         } else {
@@ -248,9 +254,14 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
           rd(nslot, wrap ? buf ^ 1 : buf, wrap ? 0 : st + 1, 0, bn);
           DF_SB; mm(b); DF_SB;
           // the next stage's first part goes to the slot of the stage that has just ended
-          if (!wrap) issue(lastc, slab, buf, slot, st + 1, 0);
-          else if (slab + 2 < s_hi) issue(More{}, slab + 1, buf ^ 1, slot, 0, 0);
-          else issue(Last{}, slab + 1, buf ^ 1, slot, 0, 0);
+          if (!wrap) {
+            issue(lastc, buf, slot, st + 1, 0);
+          } else {
+            ch = chn;
+            chn = behind(ch);
+            if (slab + 2 < s_hi) issue(More{}, buf ^ 1, slot, 0, 0);
+            else issue(Last{}, buf ^ 1, slot, 0, 0);
+          }
         }
       }
       wslot = slot;
