@@ -41,6 +41,7 @@ struct AttnParams {
   long long vt_ld;
   NextReads next;
   int qblocks;     // attn_wave_d64: blocks of 32 queries; the rows of the grid beyond them read ahead
+  unsigned int qb_recip;   // the reciprocal of qblocks, where the grid counts them head by head, an eighth for each XCD
 };
 
 // Row of the fresh tensor that holds key j, or -1 if the key comes from the stale buffer (Section 4: the keys and
@@ -591,8 +592,8 @@ __device__ __forceinline__ void read_ahead(const AttnParams& p, int row) {
 // priority.  300 queries x 2400 keys x 20 heads, cold keys: 17.7 us; scores a tile ahead 16.5; priority 15.5.  Of these the
 // launch takes 1.5, the first tiles' way from HBM 3 (12 MB of keys for all heads), the merge 1; a round of eight tiles takes
 // 1.3 us where its 128 KB need 1.2 at the rate that L2 fills a compute unit (52 B per clock).
-template <int NW>
-__global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
+template <int NW, bool HEAD_BY_HEAD>
+__global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
   constexpr int D = 64, TK = 64;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   DF_ATRACE(0, wall_clock64());
@@ -605,9 +606,20 @@ __global__ __launch_bounds__(64 * NW) void attn_wave_d64(AttnParams p) {
   // Grid (heads rounded up to a multiple of 8, query blocks, batch): workgroups go round-robin over the 8 XCDs in
   // x-fastest order, so every query block of head h runs on XCD h % 8 and the blocks of a head, which read the same
   // K / V^T, share an L2 - without any index arithmetic (the divisions of a linear index were a tenth of this kernel).
-  const int h = blockIdx.x, qb = blockIdx.y, b = blockIdx.z;
-  if (qb >= p.qblocks) { read_ahead<NW>(p, qb - p.qblocks); return; }
-  if (h >= p.heads) return;
+  // That leaves the XCDs of the first heads % 8 a head more: where they do not hold it in one round, blocks are counted instead (700 queries x
+  // 1400 keys x 20 heads, 66 of 64 places, 23.8 -> 16.1 us; 352 x 704 x 20, 33 of 32, 10.9 -> 8.5).
+  int h = blockIdx.x, qb = blockIdx.y, b = blockIdx.z;
+  if constexpr (HEAD_BY_HEAD) {
+    const unsigned int xcd = blockIdx.x & 7, base = gridDim.x >> 3, rem = gridDim.x & 7;
+    const unsigned int t = xcd * base + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
+    h = (int)quotient_u32(t, (unsigned int)p.qblocks, p.qb_recip);
+    qb = (int)t - h * p.qblocks;
+    b = h < p.heads ? 0 : h / p.heads;
+    h -= b * p.heads;
+  } else {
+    if (qb >= p.qblocks) { read_ahead<NW>(p, qb - p.qblocks); return; }
+    if (h >= p.heads) return;
+  }
   const int q0 = qb * 32;
   const int NT = (p.L + TK - 1) / TK;
   const int t_lo = (int)((long long)wave * NT / NW), t_hi = (int)((long long)(wave + 1) * NT / NW);
@@ -1173,6 +1185,13 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   const bool wave_over_split = wave_fits && a.L >= 512 && (wave_env ? atoi(wave_env) != 0
       : 4.7 + 1.93 * (double)rounds < pipe_us(a.B, a.Lq, a.L, a.heads, false, pick_splits(a.B, a.Lq, a.L, a.heads, false)));
   const bool wave_few_rounds = wave_fits && (wave_env ? atoi(wave_env) != 0 : rounds <= 3 + 3 * qblocks / 4 && rounds <= 10);
+  // Up to twice as many blocks: four waves each, two workgroups per compute unit, where the keys are few for the number of blocks
+  // (the split form has a workgroup per 128 queries on less than half of the units).  Microseconds, split form against this: 416 queries x 416
+  // keys x 20 heads 10.2 / 8.5, 494 x 988 x 20 16.1 / 13.4, 608 x 1216 x 20 16.2 / 14.3, 960 x 960 x 10 12.7 / 11.7, two batch items of 300 x 1200 x 20
+  // 17.9 / 14.5, 700 x 1400 x 20 19.8 / 16.1, 1600 x 1600 x 10 18.9 / 17.6; the other way 432 x 1728 x 20 16.6 / 17.1, 1024 x 2048 x 10 18.9 / 19.8.
+  const bool four_waves = a.v_transposed && a.L >= 64 && qblocks * a.heads * a.B > 256 && qblocks * a.heads * a.B <= 512 &&
+      (wave_env ? atoi(wave_env) != 0
+                : 5.2 + 1.85 * (double)cdiv(cdiv(a.L, 64), 4) < pipe_us(a.B, a.Lq, a.L, a.heads, false, pick_splits(a.B, a.Lq, a.L, a.heads, false)));
   auto launch_wave = [&]() -> int {
     if (!a.k_stale || !a.v_stale || a.own_n != 0 || a.own_period != 0 || a.vt_ld % 8 || a.vt_ld < (long long)cdiv(a.L, 64) * 64) return DF_EINVAL;
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
@@ -1202,11 +1221,20 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     static_assert(NW * 34 * 64 * 4 <= smem, "the merge fits");
     static bool attr_set = false;
     if (!attr_set) {
-      if (hipFuncSetAttribute((const void*)attn_wave_d64<NW>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
+      if (hipFuncSetAttribute((const void*)attn_wave_d64<NW, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess ||
+          hipFuncSetAttribute((const void*)attn_wave_d64<NW, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
         return DF_EHIP;
       attr_set = true;
     }
-    hipLaunchKernelGGL(attn_wave_d64<NW>, grid, dim3(64 * NW), smem, st, p);
+    if (four_waves || (p.next.n == 0 && cols / 8 * qblocks * a.B > 32)) {
+      p.next.n = 0;
+      p.qb_recip = reciprocal_u32((unsigned int)qblocks);
+      const dim3 blocks((unsigned)(qblocks * a.heads * a.B));
+      if (four_waves) hipLaunchKernelGGL((attn_wave_d64<4, true>), blocks, dim3(256), smem / 2, st, p);
+      else hipLaunchKernelGGL((attn_wave_d64<NW, true>), blocks, dim3(64 * NW), smem, st, p);
+    } else {
+      hipLaunchKernelGGL((attn_wave_d64<NW, false>), grid, dim3(64 * NW), smem, st, p);
+    }
     DF_LAUNCH_CHECK();
     return DF_OK;
   };
@@ -1226,7 +1254,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
       p.part_ml = p.part_o + (size_t)ns * a.B * a.heads * a.Lq * 64;
     }
   }
-  if (wave_few_rounds) return launch_wave();             // (what the caller has to provide stays that of the split form)
+  if (wave_few_rounds || four_waves) return launch_wave();   // (what the caller has to provide stays that of the split form)
   const long long nwg = (long long)cdiv(a.Lq, 128) * a.heads * a.B * p.nsplit;
   if (nwg > 0x7fffffffLL) return DF_ESHAPE;
   if (a.v_transposed) {

@@ -117,6 +117,14 @@ __device__ __forceinline__ void lds_load16(const void* base, unsigned int ofs, c
 }
 #pragma clang diagnostic pop
 
+// x / d of 32 bits from the reciprocal of d rounded down, (2^32 - 1) / d: that is at most 1 less than 2^32 / d, so the product's upper half
+// is the quotient or one less, for every x and d.
+__host__ __device__ inline unsigned int reciprocal_u32(unsigned int d) { return 0xffffffffu / d; }
+__host__ __device__ inline unsigned int quotient_u32(unsigned int x, unsigned int d, unsigned int reciprocal) {
+  const unsigned int q = (unsigned int)(((unsigned long long)x * reciprocal) >> 32);
+  return q + (x - q * d >= d ? 1u : 0u);
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

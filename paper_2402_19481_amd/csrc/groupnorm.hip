@@ -23,7 +23,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
-#include "wgemm.h"
+#include "kernels.h"
 
 namespace df {
 

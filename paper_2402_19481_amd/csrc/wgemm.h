@@ -42,14 +42,6 @@ struct WParams {
   int group_m;          // bgemm: token tiles of a panel in the tile order (see there)
 };
 
-// x / d of 32 bits from the reciprocal of d rounded down, (2^32 - 1) / d: that is at most 1 less than 2^32 / d, so the product's upper half
-// is the quotient or one less, for every x and d.
-__host__ __device__ inline unsigned int reciprocal_u32(unsigned int d) { return 0xffffffffu / d; }
-__host__ __device__ inline unsigned int quotient_u32(unsigned int x, unsigned int d, unsigned int reciprocal) {
-  const unsigned int q = (unsigned int)(((unsigned long long)x * reciprocal) >> 32);
-  return q + (x - q * d >= d ? 1u : 0u);
-}
-
 // Arguments of the segment that a fragment of 32 features lies in (seg_w % 32 == 0).  `n0`, its first feature, is the same for the
 // whole wave and the three are chosen by scalar selects: indexed by a lane's feature number the arguments came by four dependent
 // vector loads per unit, most of the 3.5 us that the epilogue of a 128 x 128 query / key / value tile took.

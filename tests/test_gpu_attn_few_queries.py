@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
     (1, 128, 1000, 5, False),        # two rounds, a tile of 40 keys last
     (1, 64, 2048, 10, True),         # two blocks: four rounds, the most for them
     (1, 320, 5083, 4, False),        # ten rounds, the most of all
-    (1, 33, 64, 129, False),         # 258 workgroups of 32 queries: 128 queries per workgroup
+    (1, 33, 64, 129, False),         # 258 blocks of 32 queries: more than one per compute unit
     (2, 96, 200, 43, True),
     (1, 40, 63, 2, False),           # fewer keys than a tile
     (1, 40, 2750, 2, False),         # ranges of keys, the last ragged
