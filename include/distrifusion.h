@@ -238,6 +238,9 @@ int df_attn_stale_vt(const void* q, const void* k, const void* vt, void* out, in
                      long long vt_ld, float scale, int out_packed, void* stream);
 size_t df_packed_text_kv_bytes(int B, int text_len, int count, int C);
 int df_pack_text_kv(const void* kv, void* packed, int B, int text_len, int count, int C, void* stream);
+/* The projection and df_pack_text_kv in one: text [B*text_len, text_dim] bf16, w [count*2C, text_dim] bf16 row-major (per block C key then C
+ * value rows) -> the fragments; text_len <= 128, text_dim % 64 == 0, C % 64 == 0.  16-byte aligned. */
+int df_text_kv(const void* text, const void* w, void* packed, int B, int text_len, int text_dim, int count, int C, void* stream);
 int df_cross_attn_packed(const void* xp, const void* wq_packed, const float* ln_s, const float* ln_t, float ln_eps,
                          const void* text_kv_packed, void* out_packed, int B, int rows_per_batch, int C, int text_len,
                          int count, int block, float scale, void* stream);

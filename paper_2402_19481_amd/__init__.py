@@ -74,6 +74,7 @@ def lib():
     L.df_packed_text_kv_bytes.restype = sz
     L.df_packed_text_kv_bytes.argtypes = [i, i, i, i]
     L.df_pack_text_kv.argtypes = [vp, vp, i, i, i, i, vp]
+    L.df_text_kv.argtypes = [vp, vp, vp, i, i, i, i, i, vp]
     L.df_cross_attn_packed.argtypes = [vp, vp, vp, vp, f, vp, vp, i, i, i, i, i, i, f, vp]
     L.df_packed_bytes.restype = sz
     L.df_packed_bytes.argtypes = [ll, ll]
@@ -113,7 +114,7 @@ def lib():
     L.df_unet_profile_kernel.argtypes = [vp, i, ctypes.c_char_p, i, ctypes.POINTER(i), dp, dp, dp, ctypes.POINTER(ll)]
     L.df_unet_profile_kernel.restype = i
     for name in ("df_copy_bytes", "df_buffer_refresh", "df_groupnorm_stale", "df_conv3x3_halo", "df_attn_displaced",
-                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv",
+                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv", "df_text_kv",
                  "df_cross_attn_packed", "df_packed_bytes", "df_pack_rows", "df_pack_linear_weight", "df_linear_packed", "df_linear_packed_scratch", "df_unet_num_weights", "df_unet_weight_info", "df_unet_create",
                  "df_unet_stale_lookup", "df_unet_num_stale", "df_unet_stale_name", "df_patch_unet_step",
                  "df_unet_profile_enable", "df_unet_set_graph", "df_unet_profile_reset", "df_unet_profile_num_classes",
@@ -256,6 +257,13 @@ def pack_text_kv(kv, B, text_len, count, C):
     """kv [B*text_len, count*2C] bf16 (projected text keys / values of `count` blocks) -> per-head MFMA fragments."""
     out = torch.empty(lib().df_packed_text_kv_bytes(B, text_len, count, C) // 2, dtype=torch.bfloat16, device=kv.device)
     _check(lib().df_pack_text_kv(_ptr(kv), _ptr(out), B, text_len, count, C, _stream()))
+    return out
+
+
+def text_kv(text, w, B, text_len, count, C):
+    """text [B*text_len, K] bf16, w [count*2C, K] bf16 -> what pack_text_kv makes of text @ w.T"""
+    out = torch.empty(lib().df_packed_text_kv_bytes(B, text_len, count, C) // 2, dtype=torch.bfloat16, device=text.device)
+    _check(lib().df_text_kv(_ptr(text), _ptr(w), _ptr(out), B, text_len, text.shape[1], count, C, _stream()))
     return out
 
 

@@ -217,6 +217,15 @@ int df_pack_text_kv(const void* kv, void* packed, int B, int text_len, int count
                              (hipStream_t)stream);
 }
 
+int df_text_kv(const void* text, const void* w, void* packed, int B, int text_len, int text_dim, int count, int C, void* stream) {
+  if (!text || !w || !packed) return DF_EINVAL;
+  if (C <= 0 || C % 64) return DF_ESHAPE;
+  TextKvArgs a = {};
+  a.text = text; a.B = B; a.TL = text_len; a.K = text_dim; a.nseg = 1;
+  a.seg[0].w = w; a.seg[0].out = packed; a.seg[0].heads = C / 64; a.seg[0].count = count;
+  return launch_text_kv(a, (hipStream_t)stream);
+}
+
 int df_cross_attn_packed(const void* xp, const void* wq_packed, const float* ln_s, const float* ln_t, float ln_eps,
                          const void* text_kv_packed, void* out_packed, int B, int rows_per_batch, int C, int text_len,
                          int count, int block, float scale, void* stream) {

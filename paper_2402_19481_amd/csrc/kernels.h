@@ -182,6 +182,23 @@ int launch_pack_wfrag(const bf16_t* w, const float* gamma, bf16_t* out, int N, i
 size_t packed_text_kv_bytes(int B, int TL, int count, int C);
 int launch_pack_text_kv(const bf16_t* kv, long long ld, bf16_t* out, int B, int TL, int count, int C, hipStream_t st);
 
+// ---- textkv.hip ----
+// The same fragments straight from the text tokens [B*TL, K] and the projections' weights w [count*2C, K] (packed_w: in the tiled layout of
+// launch_pack_weight), for the levels of a network at once.  TL <= 128, K % 64 == 0.
+constexpr int kTextKvSegs = 4;
+struct TextKvSeg {
+  const void* w;
+  void* out;
+  int heads, count;
+  int tiles;             // set by the launcher
+};
+struct TextKvArgs {
+  const void* text;
+  int B, TL, K, packed_w, nseg;
+  TextKvSeg seg[kTextKvSegs];
+};
+int launch_text_kv(const TextKvArgs& a, hipStream_t st);
+
 // ---- attn.hip ----
 // Read-only memory that the next launches of the stream will read (their weights), in the order of use.
 constexpr int kNextMax = 6;

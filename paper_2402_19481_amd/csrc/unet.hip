@@ -698,9 +698,8 @@ struct Exec {
       // cross-attention to the text tokens
       const long long kvld = (long long)kv_count[b.level] * 2 * C;
       const int kvi = kv_cursor[b.level];
-      const bf16_t* kv2 = kv2_all[b.level] + (size_t)kvi * 2 * C;
       kv_cursor[b.level] += 1;
-      const bool fuse_x = xkv_all[b.level] != nullptr && (B() == 1 || Lq % 32 == 0);
+      const bool fuse_x = xkv_all[b.level] != nullptr;
       if (fuse_x) {
         // a head is one 64-feature tile of the query projection: attention against the packed text keys / values
         // runs in that layer's epilogue and writes the packed attention output
@@ -726,6 +725,7 @@ struct Exec {
           if (need > scratch_need) scratch_need = need;
         }
         if (live()) {
+          const bf16_t* kv2 = kv2_all[b.level] + (size_t)kvi * 2 * C;
           AttnArgs a = {};
           a.q = qkv; a.k_fresh = kv2; a.v_fresh = kv2 + C; a.out = aop; a.out_packed = 1;
           a.B = B(); a.Lq = Lq; a.L = TL; a.heads = heads; a.d = c.head_dim; a.own_lo = 0; a.own_n = TL;
@@ -861,27 +861,43 @@ struct Exec {
     emb_cursor = 0;
     emb_all = (float*)alloc((size_t)B() * emb_n * 4);
     gemm_w(emb_act, c.emb_dim, emb_w_all, emb_b_all, nullptr, 0, emb_all, emb_n, B(), emb_n, c.emb_dim, DF_F32);
+    // Keys and values of the text tokens for all blocks: where the cross-attention is fused into the query projection, as its fragments, by one
+    // launch for all levels; else as rows of a level.
+    TextKvArgs kv = {};
+    kv.text = text; kv.B = B(); kv.TL = c.text_len; kv.K = c.text_dim;
+    kv.packed_w = (c.text_dim % 64 == 0 && c.text_dim >= 128) ? 1 : 0;
+    // (a pass over the weights takes two batch items; with short texts a tile of the general path holds more of them)
+    const bool kv_once = c.text_dim % 64 == 0 && cdiv(B(), 2) <= cdiv(B() * c.text_len, 128);
+    double kv_flops = 0.0, kv_bytes = 0.0;
     for (int lv = 0; lv < c.n_levels; ++lv) {
       kv_cursor[lv] = 0;
+      xkv_all[lv] = nullptr;
       if (kv_count[lv] == 0) continue;
-      const int Nkv = kv_count[lv] * 2 * c.levels[lv];
+      const int Cl = c.levels[lv], cnt = kv_count[lv], Nkv = cnt * 2 * Cl;
+      if (fold_ok(Cl) && c.text_len <= 128 && c.head_dim == 64 && (B() == 1 || rows(lv) * width(lv) % 32 == 0))
+        xkv_all[lv] = (bf16_t*)alloc(packed_text_kv_bytes(B(), c.text_len, cnt, Cl));
+      if (xkv_all[lv] && kv_once) {
+        TextKvSeg& g = kv.seg[kv.nseg++];
+        g.w = kv_packed[lv]; g.out = xkv_all[lv]; g.heads = Cl / 64; g.count = cnt;
+        kv_flops += 2.0 * B() * c.text_len * (double)Nkv * c.text_dim;
+        kv_bytes += 2.0 * (double)Nkv * c.text_dim + (double)packed_text_kv_bytes(B(), c.text_len, cnt, Cl);
+        continue;
+      }
       kv2_all[lv] = (bf16_t*)alloc((size_t)B() * c.text_len * Nkv * 2);
       GemmArgs ex = {};
-      ex.packed_w = (c.text_dim % 64 == 0 && c.text_dim >= 128) ? 1 : 0;
+      ex.packed_w = kv.packed_w;
       gemm_w(text, c.text_dim, kv_packed[lv], nullptr, nullptr, 0, kv2_all[lv], Nkv, B() * c.text_len, Nkv, c.text_dim,
              DF_BF16, &ex);
-      // the same keys / values as MFMA fragments per head, for the cross-attention fused into the query projection
-      xkv_all[lv] = nullptr;
-      if (fold_ok(c.levels[lv]) && c.text_len <= 128 && c.head_dim == 64) {
-        xkv_all[lv] = (bf16_t*)alloc(packed_text_kv_bytes(B(), c.text_len, kv_count[lv], c.levels[lv]));
-        if (live()) {
-          bf16_t* dst = xkv_all[lv];
-          const bf16_t* src = kv2_all[lv];
-          const int cnt = kv_count[lv], Cl = c.levels[lv];
-          timed(PC_ELEMENTWISE, 0.0, 4.0 * B() * c.text_len * Nkv,
-                [&] { return launch_pack_text_kv(src, Nkv, dst, B(), c.text_len, cnt, Cl, st); });
-        }
+      if (xkv_all[lv] && live()) {                          // (an odd width of the text, or short texts)
+        bf16_t* dst = xkv_all[lv];
+        const bf16_t* src = kv2_all[lv];
+        timed(PC_ELEMENTWISE, 0.0, 4.0 * B() * c.text_len * Nkv,
+              [&] { return launch_pack_text_kv(src, Nkv, dst, B(), c.text_len, cnt, Cl, st); });
       }
+    }
+    if (kv.nseg > 0 && live()) {
+      label = "text_kv " + dims({B() * c.text_len, c.text_dim});
+      timed(PC_GEMM, kv_flops, kv_bytes + 2.0 * B() * c.text_len * (double)c.text_dim, [&] { return launch_text_kv(kv, st); });
     }
     for (const BlockDesc& b : blocks) {
       if (err != DF_OK) break;
