@@ -10,8 +10,9 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdistrifusion.so")
 SOURCES = ["api.hip", "refresh.hip", "groupnorm.hip", "conv_gemm.hip", "tgemm.hip", "rconv.hip", "wgemm.hip", "bgemm.hip", "textkv.hip", "attn.hip", "elementwise.hip", "unet.hip"]
+# (Up to 14 dwords of a kernel's leading scalar and pointer arguments come in registers instead of a load at its start.)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden", "-Wall",
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 # The tuning build (python -m paper_2402_19481_amd.build --tuning) compiles the environment switches in (DF_TG,

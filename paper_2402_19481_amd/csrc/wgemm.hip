@@ -47,8 +47,13 @@ __device__ long long g_wg_trace[1024 * 16];
 // and fetched its arguments again).
 enum { MODE_PLAIN = 0, MODE_GEGLU = 1, MODE_SEG = 2 };
 
+// The arguments that the first requests need are the leading ones, which the compiler has the hardware put into scalar registers before a wave
+// starts (build.py): fetched by the wave they were a round trip to memory, and the grid's size, which lies behind all arguments, a second one.
+// 512 x 512 step, four patches, 700 launches: 4516 -> 4437 us; 1280 x 1920, eight patches 7330 -> 7261; 1024 x 1024 with guidance 6506 -> 6482.
+// (A struct of arguments is never preloaded; one whose members the kernel overwrites lands in scratch, segmented layers 3 us slower.)
 template <int TM, int TN, int KSPLIT, int PF, bool LN, int XA, bool PART, int MODE>
-__global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
+__global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(const bf16x8* Xp, const bf16x8* Wp, int M, int N, int K, int mgroups, int kfw,
+                                                                unsigned int mg_recip, unsigned int kfw_recip, int nwg, WParams p) {
   constexpr bool GEGLU = MODE == MODE_GEGLU, SEG = MODE == MODE_SEG;
   static_assert(!GEGLU || (TN % 2 == 0 && XA == 0 && !PART), "");
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
@@ -68,15 +73,12 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // of arguments first used under a condition (norm vectors, bias, residual, operand pointers) are issued where that
   // code starts, and the prologue of these few-microsecond kernels became a chain of four or five dependent round
   // trips to the scalar cache.
-  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.mg_recip), "s"(p.kfw_recip), "s"(p.mgroups), "s"(p.kfw),
-               "s"(p.bias), "s"(p.ln_s), "s"(p.ln_t), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the k-walk and tile addresses stay off the vector ALU
   const int tok = lane & 31, g = lane >> 5;
-  const int MT = (p.M + 31) >> 5;                      // 32-token fragments rows
-  const int MG = p.mgroups;                            // tile groups along M
-  const int NTo = p.N >> 5;                            // 32-feature output fragments
-  const int nwg = gridDim.x;
+  const int MT = (M + 31) >> 5;                      // 32-token fragments rows
+  const int MG = mgroups;                            // tile groups along M
+  const int NTo = N >> 5;                            // 32-feature output fragments
   int t = blockIdx.x;
   {
     // workgroups go round-robin over the 8 XCDs; give each XCD a contiguous run of tiles, token tiles fastest, so
@@ -85,8 +87,8 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int base = nwg >> 3, rem = nwg & 7;
     t = xcd * base + (xcd < rem ? xcd : rem) + loc;
   }
-  const int ng = (int)quotient_u32((unsigned int)t, (unsigned int)MG, p.mg_recip), mg = t - ng * MG;
-  const int KF = p.K >> 4, KFw = p.kfw;                // k-fragments of a wave
+  const int ng = (int)quotient_u32((unsigned int)t, (unsigned int)MG, mg_recip), mg = t - ng * MG;
+  const int KF = K >> 4, KFw = kfw;                // k-fragments of a wave
   const int kf0 = ((PART ? (int)blockIdx.y * KSPLIT : 0) + wave) * KFw;
 #ifdef DF_TUNING
   asm volatile("" ::"s"(kf0), "s"(mg), "s"(ng));
@@ -99,12 +101,12 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   for (int i = 0; i < TM; ++i) {
     int mt = mg * TM + i;
     if (mt > MT - 1) mt = MT - 1;                     // ragged last group: recompute the last fragment row, never stored
-    xb[i] = p.Xp + ((size_t)mt * KF + kf0) * 64 + lane;
+    xb[i] = Xp + ((size_t)mt * KF + kf0) * 64 + lane;
   }
 #pragma unroll
   for (int j = 0; j < TN; ++j) {
     const int nt = GEGLU ? (j < GP ? ng * GP + j : NTo + ng * GP + (j - GP)) : ng * TN + j;
-    wb[j] = p.Wp + ((size_t)nt * KF + kf0) * 64 + lane;
+    wb[j] = Wp + ((size_t)nt * KF + kf0) * 64 + lane;
   }
 
   bf16x8 xr[PF][TM], wr[PF][TN];
@@ -113,7 +115,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   // streams of all waves are otherwise aligned modulo the fragment-row pitch and hit the same few L2 / memory
   // channels at any moment.  The order is a fixed function of the tile, so results stay reproducible.
   const unsigned int rsum = (unsigned int)(mg * 7 + ng * 3 + wave * 5);
-  const int rot = (int)(rsum - (unsigned int)KFw * quotient_u32(rsum, (unsigned int)KFw, p.kfw_recip));   // rsum % KFw
+  const int rot = (int)(rsum - (unsigned int)KFw * quotient_u32(rsum, (unsigned int)KFw, kfw_recip));   // rsum % KFw
   auto pos = [&](int step) {
     const int k = step + rot;
     return (size_t)(k < KFw ? k : k - KFw) * 64;
@@ -137,6 +139,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
   float ln_sum[TM], ln_sq[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) { ln_sum[i] = 0.f; ln_sq[i] = 0.f; }
+  asm volatile("" ::"s"(p.bias), "s"(p.ln_s), "s"(p.ln_t), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   constexpr bool ln = LN;
 
   // Epilogue operands are requested between the first operands and the K loop: their latency would otherwise sit, un-overlapped, at the end
@@ -154,9 +157,9 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int n0 = ng * JO * 32;
     constexpr bool gg = GEGLU;
     const float* src = nullptr;                        // (uniform)
-    if (ln) src = wave == 0 ? p.ln_s + n0 : wave == 1 ? p.ln_t + n0 : (gg && wave == 2) ? p.ln_s + p.N + n0
-                                                          : (gg && wave == 3) ? p.ln_t + p.N + n0 : nullptr;
-    else if (!PART && p.bias) src = wave == 0 ? p.bias + n0 : (gg && wave == 2) ? p.bias + p.N + n0 : nullptr;
+    if (ln) src = wave == 0 ? p.ln_s + n0 : wave == 1 ? p.ln_t + n0 : (gg && wave == 2) ? p.ln_s + N + n0
+                                                          : (gg && wave == 3) ? p.ln_t + N + n0 : nullptr;
+    else if (!PART && p.bias) src = wave == 0 ? p.bias + n0 : (gg && wave == 2) ? p.bias + N + n0 : nullptr;
     if (src && lane * 4 < JO * 32) vec_pre = *reinterpret_cast<const f32x4*>(src + 4 * lane);
   }
   struct Epi { float r[8]; };
@@ -165,9 +168,9 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     const int j = (pu >> 1) % JO;
     const int mt = mg * TM + i0 + (pu >> 1) / JO;
     const int m = mt * 32 + tok;
-    if (!PART && !SEG && XA == 0 && p.residual && (p.res_frag ? mt < MT : m < p.M)) {
+    if (!PART && !SEG && XA == 0 && p.residual && (p.res_frag ? mt < MT : m < M)) {
       int next;
-      const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, (ng * JO + j) * 32, 16 * f + 8 * g, lane, &next);
+      const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, N, mt, m, (ng * JO + j) * 32, 16 * f + 8 * g, lane, &next);
       ld_vec(rp, e.r); ld_vec(rp + next, e.r + 4);
     }
   };
@@ -327,7 +330,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       }
       // hardware reciprocal and reciprocal square root (1 ulp) in place of the IEEE division and square root
       // sequences: this epilogue runs once per workgroup and is not hidden behind anything
-      const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+      const float inv_k = __builtin_amdgcn_rcpf((float)K);
       const float mean = sm * inv_k;
       const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
       const float rstd = __builtin_amdgcn_rsqf(var + p.ln_eps);
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
       qlds[(2 * j + f) * 64 + lane] = qv;
       continue;
     }
-    const bool row_ok = m < p.M;
+    const bool row_ok = m < M;
     if (!SEG && p.residual && (row_ok || p.res_frag)) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) v[q] += e.r[q];
@@ -441,7 +444,7 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(WParams p) {
     }
     const float inv = 1.0f / l;
     const float o8[8] = {a.x * inv, a.y * inv, a.z * inv, a.w * inv, c.x * inv, c.y * inv, c.z * inv, c.w * inv};
-    const int KFo = p.N >> 4;
+    const int KFo = N >> 4;
     st_vec(p.out_packed + (((size_t)mg * KFo + ng * 4 + dt * 2 + f2) * 64 + lane) * 8, o8);
   }
 }
@@ -550,7 +553,8 @@ int launch_one(const WParams& pin, hipStream_t st) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)(MG * NG), PART ? (unsigned)p.parts : 1u), dim3(64 * KSPLIT), smem, st, p);
+  hipLaunchKernelGGL(k, dim3((unsigned)(MG * NG), PART ? (unsigned)p.parts : 1u), dim3(64 * KSPLIT), smem, st,
+                     p.Xp, p.Wp, p.M, p.N, p.K, p.mgroups, p.kfw, p.mg_recip, p.kfw_recip, MG * NG, p);
   DF_LAUNCH_CHECK();
   if constexpr (PART) return launch_part_sums(p, st);
   return DF_OK;
