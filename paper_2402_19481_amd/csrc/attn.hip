@@ -593,7 +593,8 @@ __device__ __forceinline__ void read_ahead(const AttnParams& p, int row) {
 // launch takes 1.5, the first tiles' way from HBM 3 (12 MB of keys for all heads), the merge 1; a round of eight tiles takes
 // 1.3 us where its 128 KB need 1.2 at the rate that L2 fills a compute unit (52 B per clock).
 template <int NW, bool HEAD_BY_HEAD>
-__global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
+__global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(const bf16_t* q, const bf16_t* ks, const bf16_t* vs, int Lq, int L, int heads, int qblocks,
+                                                             int ldq, int ldks, int vt_ld, unsigned int qb_recip, AttnParams p) {
   constexpr int D = 64, TK = 64;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   DF_ATRACE(0, wall_clock64());
@@ -612,29 +613,32 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
   if constexpr (HEAD_BY_HEAD) {
     const unsigned int xcd = blockIdx.x & 7, base = gridDim.x >> 3, rem = gridDim.x & 7;
     const unsigned int t = xcd * base + (xcd < rem ? xcd : rem) + (blockIdx.x >> 3);
-    h = (int)quotient_u32(t, (unsigned int)p.qblocks, p.qb_recip);
-    qb = (int)t - h * p.qblocks;
-    b = h < p.heads ? 0 : h / p.heads;
-    h -= b * p.heads;
+    h = (int)quotient_u32(t, (unsigned int)qblocks, qb_recip);
+    qb = (int)t - h * qblocks;
+    b = h < heads ? 0 : h / heads;
+    h -= b * heads;
   } else {
-    if (qb >= p.qblocks) { read_ahead<NW>(p, qb - p.qblocks); return; }
-    if (h >= p.heads) return;
+    if (qb >= qblocks) { read_ahead<NW>(p, qb - qblocks); return; }
+    if (h >= heads) return;
   }
   const int q0 = qb * 32;
-  const int NT = (p.L + TK - 1) / TK;
+  const int NT = (L + TK - 1) / TK;
   const int t_lo = (int)((long long)wave * NT / NW), t_hi = (int)((long long)(wave + 1) * NT / NW);
 
-  const bf16_t* kg = (const bf16_t*)p.ks + (long long)b * p.bsks + h * D;
-  const bf16_t* vg = (const bf16_t*)p.vs + (long long)b * p.bsvs + (long long)h * D * p.vt_ld;
+  const bf16_t *kg = ks + h * D, *vg = vs + (long long)h * D * vt_ld, *qg = q + h * D;
+  if (b > 0) {                                               // (the strides are not among the arguments that come in registers)
+    asm volatile("");
+    kg += (long long)b * p.bsks; vg += (long long)b * p.bsvs; qg += (long long)b * p.bsq;
+  }
 
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
-    const bf16_t* qp = (const bf16_t*)p.q + (long long)b * p.bsq + (long long)qi * p.ldq + h * D;
+    const bf16_t* qp = qg + (long long)qi * ldq;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 tq = {0u, 0u, 0u, 0u};
-      if (qi < p.Lq) tq = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * g);
+      if (qi < Lq) tq = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * g);
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
@@ -645,15 +649,15 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     const int row = j * 8 + lr;
-    kofs[j] = (unsigned int)row * (unsigned int)p.ldks + (unsigned int)((slot ^ ((row >> 1) & 7)) * 8);
-    vofs[j] = (unsigned int)row * (unsigned int)p.vt_ld + (unsigned int)((slot ^ (row & 7) ^ (row >> 3)) * 8);
+    kofs[j] = (unsigned int)row * (unsigned int)ldks + (unsigned int)((slot ^ ((row >> 1) & 7)) * 8);
+    vofs[j] = (unsigned int)row * (unsigned int)vt_ld + (unsigned int)((slot ^ (row & 7) ^ (row >> 3)) * 8);
   }
   char* sk = smem + wave * (2 * TK * D * 2);                 // this wave's K tile [key][d], then its V^T tile [d][key]
   char* sv = sk + TK * D * 2;
   auto issue_k = [&](int tl) {
     const int key0 = tl * TK;
-    if (key0 + TK <= p.L) {                                  // (uniform) every key row of the tile exists
-      const bf16_t* kb0 = kg + (long long)key0 * p.ldks;
+    if (key0 + TK <= L) {                                  // (uniform) every key row of the tile exists
+      const bf16_t* kb0 = kg + (long long)key0 * ldks;
 #pragma unroll
       for (int j = 0; j < 8; ++j) lds_load16(kb0, 2u * kofs[j], sk + j * 1024);
     } else {
@@ -661,8 +665,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
       for (int j = 0; j < 8; ++j) {
         const int row = j * 8 + lr;
         int key = key0 + row;
-        if (key > p.L - 1) key = p.L - 1;                    // rows beyond the last key are masked in the tile body
-        lds_load16(kg + (long long)key * p.ldks + ((slot ^ ((row >> 1) & 7)) * 8), sk + j * 1024);
+        if (key > L - 1) key = L - 1;                    // rows beyond the last key are masked in the tile body
+        lds_load16(kg + (long long)key * ldks + ((slot ^ ((row >> 1) & 7)) * 8), sk + j * 1024);
       }
     }
   };
@@ -752,7 +756,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
   // ten blocks keep ten tiles per wave slot in flight and find the others' tiles in L2.  The order is a fixed
   // function of the indices, so results stay reproducible.  A tile with fewer than 64 keys stays the last.
   const int nt = t_hi - t_lo;
-  const int nrot = t_hi * TK > p.L ? nt - 1 : nt;
+  const int nrot = t_hi * TK > L ? nt - 1 : nt;
   const int rot = ((qb & 7) * nrot) >> 3;                    // < nrot, spread over the run
   auto tile_at = [&](int i) { const int k = i + rot; return t_lo + (i >= nrot ? i : k < nrot ? k : k - nrot); };
   // The scores run one tile ahead: while the exponentials and sums of tile i are on the vector ALU, the matrix cores take
@@ -819,14 +823,14 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
     landed();
     DF_ATRACE(3 + 3 * i, __builtin_readcyclecounter());
     read_v();
-    if (tile_base + TK > p.L) {
+    if (tile_base + TK > L) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
           const int j = e >> 2, r = e & 3;
           const int key = tile_base + 32 * kb + 16 * (j >> 1) + 8 * g + 4 * (j & 1) + r;
-          if (key >= p.L) s_a[kb][e] = -INFINITY;
+          if (key >= L) s_a[kb][e] = -INFINITY;
         }
 #pragma unroll
       for (int ts = 0; ts < 4; ++ts)
@@ -834,10 +838,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
         for (int db = 0; db < 2; ++db) {                     // keys beyond the range: P is 0, V must be finite
           const int key = tile_base + (4 * (ts >> 1) + 2 * (ts & 1) + g) * 8;
           u32x4& vraw = vfr[ts][db];
-          if (key + 0 >= p.L) vraw.x = 0u; else if (key + 1 >= p.L) vraw.x &= 0xffffu;
-          if (key + 2 >= p.L) vraw.y = 0u; else if (key + 3 >= p.L) vraw.y &= 0xffffu;
-          if (key + 4 >= p.L) vraw.z = 0u; else if (key + 5 >= p.L) vraw.z &= 0xffffu;
-          if (key + 6 >= p.L) vraw.w = 0u; else if (key + 7 >= p.L) vraw.w &= 0xffffu;
+          if (key + 0 >= L) vraw.x = 0u; else if (key + 1 >= L) vraw.x &= 0xffffu;
+          if (key + 2 >= L) vraw.y = 0u; else if (key + 3 >= L) vraw.y &= 0xffffu;
+          if (key + 4 >= L) vraw.z = 0u; else if (key + 5 >= L) vraw.z &= 0xffffu;
+          if (key + 6 >= L) vraw.w = 0u; else if (key + 7 >= L) vraw.w &= 0xffffu;
         }
     }
     const float m_new = new_max(s_a);
@@ -869,7 +873,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
   DF_ATRACE(28, __builtin_readcyclecounter());
   DF_ATRACE(31, nt);
   const int qi = q0 + c;
-  if (qi >= p.Lq) return;
+  if (qi >= Lq) return;
   float mw[NW], m_all = -INFINITY;
 #pragma unroll
   for (int w = 0; w < NW; ++w) { mw[w] = mrg[(w * 34 + 32) * 64 + lane]; m_all = fmaxf(m_all, mw[w]); }
@@ -895,8 +899,8 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_wave_d64(AttnParams p) {
   const int db = e0 >> 4, f = (e0 >> 3) & 1, eo = e0 & 7;
   bf16_t* dst;
   if (p.out_packed) {
-    const long long m = (long long)b * p.Lq + qi;
-    dst = (bf16_t*)p.out + (((m >> 5) * (long long)(p.heads * D / 16) + h * (D / 16)) * 64 + (m & 31) + 32 * g) * 8 +
+    const long long m = (long long)b * Lq + qi;
+    dst = (bf16_t*)p.out + (((m >> 5) * (long long)(heads * D / 16) + h * (D / 16)) * 64 + (m & 31) + 32 * g) * 8 +
           (2 * db + f) * 512 + eo;
   } else {
     dst = (bf16_t*)p.out + (long long)b * p.bso + (long long)qi * p.ldo + h * D + 32 * db + 16 * f + 8 * g + eo;
@@ -1226,15 +1230,20 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
         return DF_EHIP;
       attr_set = true;
     }
+    // (the pitches of keys and values are bounded above; every caller's queries have heads * 64)
+#define DF_WAVE_ARGS                                                                                                         \
+  (const bf16_t*)p.q, (const bf16_t*)p.ks, (const bf16_t*)p.vs, p.Lq, p.L, p.heads, p.qblocks, (int)p.ldq, (int)p.ldks, (int)p.vt_ld, \
+      p.qb_recip, p
     if (four_waves || (p.next.n == 0 && cols / 8 * qblocks * a.B > 32)) {
       p.next.n = 0;
       p.qb_recip = reciprocal_u32((unsigned int)qblocks);
       const dim3 blocks((unsigned)(qblocks * a.heads * a.B));
-      if (four_waves) hipLaunchKernelGGL((attn_wave_d64<4, true>), blocks, dim3(256), smem / 2, st, p);
-      else hipLaunchKernelGGL((attn_wave_d64<NW, true>), blocks, dim3(64 * NW), smem, st, p);
+      if (four_waves) hipLaunchKernelGGL((attn_wave_d64<4, true>), blocks, dim3(256), smem / 2, st, DF_WAVE_ARGS);
+      else hipLaunchKernelGGL((attn_wave_d64<NW, true>), blocks, dim3(64 * NW), smem, st, DF_WAVE_ARGS);
     } else {
-      hipLaunchKernelGGL((attn_wave_d64<NW, false>), grid, dim3(64 * NW), smem, st, p);
+      hipLaunchKernelGGL((attn_wave_d64<NW, false>), grid, dim3(64 * NW), smem, st, DF_WAVE_ARGS);
     }
+#undef DF_WAVE_ARGS
     DF_LAUNCH_CHECK();
     return DF_OK;
   };

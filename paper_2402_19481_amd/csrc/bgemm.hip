@@ -131,8 +131,13 @@ struct Direct {
 // for LDS reads exact (lds_load_buf): 1800 x 1280 x 5120 48.9 -> 41.4 us, 1800 x 3840 x 1280 30.4 -> 27.5, 4096 x 1280 x 1280 27.2
 // -> 24.7.  With the epilogue of a single k-group in the accumulators and its arguments requested early: 1024 x 10240 x 1280 with GEGLU
 // 35.4 -> 31.4 us, 1800 x 10240 x 1280 61 -> 53, 1024 x 3840 x 1280 split into queries, keys and values 20 -> 17.5.
+// As in wgemm.hip the leading arguments come in scalar registers: operands, the per-feature vectors, the residual, sizes, and in `order` the token
+// tiles of a panel, the parts of K (from bit 26) and whether the residual is in fragments (bit 30).  With attn_wave_d64's the same way, step of
+// 1024 x 1024 with guidance 6467 -> 6351 us, 1280 x 1920 7140 -> 7070, 832 x 1216 8717 -> 8667, 1024 x 1024 full 11870 -> 11778.
 template <int WT, int WF, int TT, int TF, int KG, int KS, int ST, int OCC, int EPI, bool LN, int XA>
-__global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(WParams p) {
+__global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) void bgemm_kernel(const bf16x8* Xp, const bf16x8* Wp, const float* vec_s,
+                                                                                              const float* vec_t, const float* residual, int M, int N, int K,
+                                                                                              unsigned int order, WParams p) {
   using E = Epi<WT, WF, TT, TF, KG, OCC, LN>;
   constexpr int NW = WT * WF * KG;                     // waves
   constexpr int BT = WT * TT, BF = WF * TF;            // token / feature fragment rows of the workgroup tile
@@ -145,12 +150,13 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   static_assert(EPI != EPI_QKV || LN, "the segmented epilogue applies the folded LayerNorm");
   extern __shared__ __attribute__((aligned(16))) char smem[];
 
-  asm volatile("" ::"s"(p.Xp), "s"(p.Wp), "s"(p.M), "s"(p.N), "s"(p.K), "s"(p.group_m), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
+  const int group_m = (int)(order & 0x3ffffff), parts = (int)(order >> 26 & 15);
+  const bool res_frag = order >> 30;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int tok = lane & 31, g = lane >> 5;
   const int kg = wave / (WT * WF), wq = wave % (WT * WF), wt = wq % WT, wf = wq / WT;
-  const int MT = (p.M + 31) >> 5, NF = p.N >> 5;
+  const int MT = (M + 31) >> 5, NF = N >> 5;
   constexpr int BFO = EPI == EPI_GEGLU ? BF / 2 : BF;  // output fragments of the tile along the features
   const int MG = (MT + BT - 1) / BT, NG = (NF + BFO - 1) / BFO, nwg = MG * NG;
   int t = blockIdx.x;
@@ -161,16 +167,16 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
   }
   int mg, ng;
   {
-    const int per = p.group_m * NG, pn = t / per, r = t - pn * per, m0 = pn * p.group_m;
-    const int gh = MG - m0 < p.group_m ? MG - m0 : p.group_m;
+    const int per = group_m * NG, pn = t / per, r = t - pn * per, m0 = pn * group_m;
+    const int gh = MG - m0 < group_m ? MG - m0 : group_m;
     ng = r / gh;
     mg = m0 + r - ng * gh;
   }
-  const int KF = p.K >> 4;
+  const int KF = K >> 4;
   int KT = KF / BKF, kt0 = 0;                          // stages of this workgroup, the first of them
   if constexpr (EPI == EPI_PART) {
-    kt0 = (int)((long long)KT * blockIdx.y / gridDim.y);
-    KT = (int)((long long)KT * (blockIdx.y + 1) / gridDim.y) - kt0;
+    kt0 = (int)((long long)KT * blockIdx.y / parts);
+    KT = (int)((long long)KT * (blockIdx.y + 1) / parts) - kt0;
   }
 
   // fragment row of the weights behind row r (0 .. BF-1) of the tile.  GEGLU, several k-groups: the first half are value rows, the
@@ -205,7 +211,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     const int row = i / BKF, kk = i - row * BKF;
     int mt = mg * BT + row;
     if (mt > MT - 1) mt = MT - 1;                      // ragged last tile: re-read, never stored
-    src[q] = (row < BT ? (const char*)p.Xp + (size_t)mt * KF * 1024 : (const char*)p.Wp + (size_t)wrow(row - BT) * KF * 1024) +
+    src[q] = (row < BT ? (const char*)Xp + (size_t)mt * KF * 1024 : (const char*)Wp + (size_t)wrow(row - BT) * KF * 1024) +
              ((size_t)kt0 * BKF + kk) * 1024;
   }
   // Plain layers of whole 1024s of tokens: the XCDs walk K from different stages on, an eighth apart.  Their shares of the tokens then begin
@@ -238,14 +244,16 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     vs[q] = vt[q] = 0.f;
     if (r < BF * 32) {
       const int n = wrow(r >> 5) * 32 + (r & 31);
-      if constexpr (LN) { vs[q] = p.ln_s[n]; vt[q] = p.ln_t[n]; }
-      else if (EPI != EPI_PART && p.bias) vt[q] = p.bias[n];
+      if constexpr (LN) { vs[q] = vec_s[n]; vt[q] = vec_t[n]; }
+      else if (EPI != EPI_PART && vec_t) vt[q] = vec_t[n];
     }
   }
   f32x16 acc[TT][TF];
   constexpr bool kResInit = EPI == EPI_PLAIN && !LN;
-  if (kResInit && p.residual && kg == 0) {
+  if (kResInit && residual && kg == 0) {
     // the residual is the accumulators' start value: its latency runs beside the first stages'
+    long long ldr = 0;                                 // (not among the arguments that come in registers)
+    if (!res_frag) { asm volatile(""); ldr = p.ldr; }
 #pragma unroll
     for (int i = 0; i < TT; ++i) {
       const int m = (mg * BT + wt * TT + i) * 32 + tok;
@@ -255,10 +263,10 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         f32x4 r[4];
 #pragma unroll
         for (int f = 0; f < 4; ++f) r[f] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if ((p.res_frag ? m < MT * 32 : m < p.M) && nt < NF) {
+        if ((res_frag ? m < MT * 32 : m < M) && nt < NF) {
           int next;
-          const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, m >> 5, m, nt * 32, 8 * g, lane, &next);
-          const int half = p.res_frag ? 512 : 16;      // from the first eight features to the others
+          const float* rp = wg_float_unit(residual, res_frag, ldr, N, m >> 5, m, nt * 32, 8 * g, lane, &next);
+          const int half = res_frag ? 512 : 16;      // from the first eight features to the others
 #pragma unroll
           for (int f = 0; f < 4; ++f) r[f] = *reinterpret_cast<const f32x4*>(rp + half * (f >> 1) + next * (f & 1));
         }
@@ -442,7 +450,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
 
   auto add_residual = [&](int mt, int m, int n0, int fo, int ln, float* v) {
     int next;
-    const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, p.N, mt, m, n0, fo, ln, &next);
+    const float* rp = wg_float_unit(p.residual, p.res_frag, p.ldr, N, mt, m, n0, fo, ln, &next);
     float r8[8];
     ld_vec(rp, r8); ld_vec(rp + next, r8 + 4);
 #pragma unroll
@@ -514,7 +522,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
             const float* q = s_part + ((w * BT + wt * TT + i) * 32 + tok) * 2;
             sm += q[0]; sq += q[1];
           }
-          const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+          const float inv_k = __builtin_amdgcn_rcpf((float)K);
           const float mean = sm * inv_k;
           const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
           rstd = __builtin_amdgcn_rsqf(var + p.ln_eps);
@@ -530,7 +538,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         auto store = [&](int nt, int f, float* v) {
           if (mt >= MT || nt >= NF) return;
           if constexpr (!kResInit) {
-            if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * g, lane, v);
+            if (p.residual && (m < M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * g, lane, v);
           }
           wg_store_unit<SEG>(p, out, mt, m, nt * 32, 16 * f + 8 * g, lane, v);
         };
@@ -541,7 +549,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
             float v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = a[8 * f + q] * gelu_erf(gt[8 * f + q]);
-            if (packed_only) st_vec(out.packed + (((size_t)mt * (p.N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
+            if (packed_only) st_vec(out.packed + (((size_t)mt * (N >> 4) + nt * 2 + f) * 64 + lane) * 8, v);
             else store(nt, f, v);
           };
 #pragma unroll
@@ -656,7 +664,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
           float sm = 0.f, sq = 0.f;
 #pragma unroll
           for (int w = 0; w < KG * WF; ++w) { sm += s_part[(w * BT * 32 + r) * 2]; sq += s_part[(w * BT * 32 + r) * 2 + 1]; }
-          const float inv_k = __builtin_amdgcn_rcpf((float)p.K);
+          const float inv_k = __builtin_amdgcn_rcpf((float)K);
           const float mean = sm * inv_k;
           const float var = fmaxf(fmaf(sq, inv_k, -mean * mean), 0.f);
           s_mr[2 * r] = mean;
@@ -734,7 +742,7 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
         }
         const int m = mt * 32 + tk;
         if constexpr (!kResInit) {
-          if (p.residual && (m < p.M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
+          if (p.residual && (m < M || p.res_frag)) add_residual(mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
         }
         wg_store_unit<SEG>(p, out, mt, m, nt * 32, 16 * f + 8 * gg, tk + 32 * gg, v);
       }
@@ -814,7 +822,9 @@ int launch_one(const WParams& pin, hipStream_t st) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)parts), dim3(64 * NW), smem, st, p);
+  const unsigned int order = (unsigned int)p.group_m | (unsigned int)parts << 26 | (p.res_frag ? 1u << 30 : 0u);   // (parts: at most eight)
+  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)parts), dim3(64 * NW), smem, st, p.Xp, p.Wp, p.ln_s, LN ? p.ln_t : p.bias, p.residual,
+                     p.M, p.N, p.K, order, p);
   DF_LAUNCH_CHECK();
   if constexpr (EPI == EPI_PART) {
     return launch_part_sums(p, st);
