@@ -57,8 +57,11 @@ constexpr int pass_rows(int rows, int kg, int bn) {
 // stage that ended at the last barrier; a stage ends with the wait for the next one's loads, lgkmcnt(0) and a barrier, and
 // its last matrix instructions (operands in registers) run behind that barrier beside the next stage's first reads.  The other
 // buffer of pixels was last read in the stage before the current channels' first, so its refill is behind a barrier too.
+// What the requests of the first weights need are the leading arguments, which come in scalar registers (as in wgemm.hip): GroupNorm and
+// convolution of 128 x 128 x 320 over four patches 19.9 -> 19.5 us, 512 x 512 step 4428 -> 4407, 1024 x 1024 with guidance 6361 -> 6329.
 template <int PM, int PN, int TM, int TN, int KG, int TAPS, int ST, int NIN, typename OutT>
-__global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) {
+__global__ __launch_bounds__(512, 2) void rconv_kernel(const bf16_t* Wt, const bf16_t* A, int N, int Cin, int ldw, int MT, int group_m, int nsplit,
+                                                       int per_img, int tiles_c, int R, int W, TileParams p, RcExtra x) {
   static_assert(PM * PN * KG == 8, "eight waves");
   constexpr int BN = PN * TN * 32;
   constexpr int NST = 9 / TAPS;                            // stages of 64 channels
@@ -76,8 +79,7 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = wave / (PM * PN), wq = wave % (PM * PN), wm = wq % PM, wn = wq / PM;
-  const int per_img = x.tiles_r * x.tiles_c;
-  const int MT = per_img * (p.M / (p.R * p.W)), NT = (p.N + BN - 1) / BN, nwg = MT * NT;
+  const int NT = (N + BN - 1) / BN, nwg = MT * NT;
   int t = blockIdx.x;
   {
     const int xcd = t & 7, loc = t >> 3;
@@ -86,16 +88,16 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   }
   int mt, n0;
   {
-    const int per = x.group_m * NT, pn = t / per, r = t - pn * per, mf = pn * x.group_m;
-    const int gh = MT - mf < x.group_m ? MT - mf : x.group_m;
+    const int per = group_m * NT, pn = t / per, r = t - pn * per, mf = pn * group_m;
+    const int gh = MT - mf < group_m ? MT - mf : group_m;
     n0 = r / gh;
     mt = mf + r - n0 * gh;
     n0 *= BN;
   }
   const int bi = mt / per_img, trc = mt - bi * per_img;
-  const int r0 = trc / x.tiles_c * x.th, c0 = (trc - trc / x.tiles_c * x.tiles_c) * x.tw;
-  const int slabs_all = p.Cin / 64;
-  const int s_lo = (int)((long long)slabs_all * blockIdx.y / gridDim.y), s_hi = (int)((long long)slabs_all * (blockIdx.y + 1) / gridDim.y);
+  const int r0 = trc / tiles_c * x.th, c0 = (trc - trc / tiles_c * tiles_c) * x.tw;
+  const int slabs_all = Cin / 64;
+  const int s_lo = (int)((long long)slabs_all * blockIdx.y / nsplit), s_hi = (int)((long long)slabs_all * (blockIdx.y + 1) / nsplit);
 
   // First channel of the slab that is being computed and of the one behind it.  The XCDs begin with different slabs: all
   // of them read the same weights, and in step they ask the same channels of the last-level cache.  64 x 1280 -> 1280 13.9 -> 13.7 us, 494
@@ -107,17 +109,17 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   // weight loads: instruction j of a tap covers output channels wrow(j) .. +7 of the tile, lane / 8 one of them
   const int lr = lane >> 3;
   auto wrow = [&](int j) { return (j * 8 + wave < BN / 8 ? j * 8 + wave : BN / 8 - 1) * 8; };
-  const char* const w_tile = (const char*)(p.Wt + (long long)n0 * p.ldw);
+  const char* const w_tile = (const char*)(Wt + (long long)n0 * ldw);
   unsigned int w_ofs[WJ];
 #pragma unroll
   for (int j = 0; j < WJ; ++j) {
     const int row = wrow(j) + lr;
-    const int n = (n0 + row < p.N ? n0 + row : p.N - 1) - n0;   // ragged last tile: re-read, never stored
-    w_ofs[j] = 2u * ((unsigned int)n * (unsigned int)p.ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8);
+    const int n = (n0 + row < N ? n0 + row : N - 1) - n0;   // ragged last tile: re-read, never stored
+    w_ofs[j] = 2u * ((unsigned int)n * (unsigned int)ldw + ((lane & 7) ^ ((row >> 1) & 7)) * 8);
   }
   auto load_w = [&](int ch, int st, int slot, int l) {     // load l of a stage: tap l / WJ, instruction l % WJ
     const int tp = l / WJ, j = l % WJ;
-    lds_load_buf(w_tile, w_ofs[j], 2u * ((st * TAPS + tp) * p.Cin + ch), smem + 2 * IB + slot * WB + tp * (BN * 128) + wrow(j) * 128);
+    lds_load_buf(w_tile, w_ofs[j], 2u * ((st * TAPS + tp) * Cin + ch), smem + 2 * IB + slot * WB + tp * (BN * 128) + wrow(j) * 128);
   };
   // the first stage's weights, the coldest of what the loop waits for, are requested before the pixels' addresses are known
 #pragma unroll
@@ -132,8 +134,8 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
     const int pr = (int)(((unsigned)px * x.rw_magic) >> 20), pc = px - pr * RW;
     const int ri = r0 + pr - 1, ci = c0 + pc - 1;
     const bf16_t* src = nullptr;
-    if (px < np && ri <= p.R && ci <= p.W)
-      src = conv_tap_src(p.A, p.top, p.bot, p.halo_bs, p.left, p.right, p.side_bs, p.side_rs, bi, ri, ci, p.R, p.W, p.Cin);
+    if (px < np && ri <= R && ci <= W)
+      src = conv_tap_src(A, p.top, p.bot, p.halo_bs, p.left, p.right, p.side_bs, p.side_rs, bi, ri, ci, R, W, Cin);
     in_zero[q] = src == nullptr;
     in_ptr[q] = (src ? src : x.zeros) + ((lane & 7) ^ ((px >> 1) & 7)) * 8;
   }
@@ -272,9 +274,9 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
   for (int slab = s_lo; slab + 1 < s_hi; ++slab) channels(More{}, slab);
   // What the epilogue adds per channel is requested where only weights are left to request.
   constexpr int RS = 512 / (BN / 4);                       // rows per round of the epilogue; a thread keeps its columns
-  const bool part = gridDim.y > 1;
+  const bool part = nsplit > 1;
   const int c4 = (tid % (BN / 4)) * 4, col = n0 + c4;
-  const bool mine = tid < RS * (BN / 4) && col < p.N;
+  const bool mine = tid < RS * (BN / 4) && col < N;
   f32x4 add = {0.f, 0.f, 0.f, 0.f}, add_image = add;
   if (!part && mine) {
     if (p.bias) add = *reinterpret_cast<const f32x4*>(p.bias + col);
@@ -311,8 +313,8 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
         for (int k = 0; k < U; ++k) {
           const int s = f0 * 32 + l0 + k * RS;
           const int tr = (int)(((unsigned)s * x.tw_magic) >> 16), tc = s - tr * x.tw;
-          const bool ok = l0 + k * RS < RP * 32 && tr < x.th && r0 + tr < p.R && c0 + tc < p.W;
-          row[k] = ok ? ((long long)bi * p.R + r0 + tr) * p.W + c0 + tc : -1;
+          const bool ok = l0 + k * RS < RP * 32 && tr < x.th && r0 + tr < R && c0 + tc < W;
+          row[k] = ok ? ((long long)bi * R + r0 + tr) * W + c0 + tc : -1;
           res[k] = f32x4{0.f, 0.f, 0.f, 0.f};
           if (!part && p.residual && ok) res[k] = *reinterpret_cast<const f32x4*>(p.residual + row[k] * p.ldr + col);
         }
@@ -324,7 +326,7 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(TileParams p, RcExtra x) 
 #pragma unroll
           for (int h = 1; h < KG; ++h) v += *reinterpret_cast<const f32x4*>(tp + h * RP * 32 * PT);
           if (part) {
-            *reinterpret_cast<f32x4*>(x.partials + ((size_t)blockIdx.y * p.M + row[k]) * p.N + col) = v;
+            *reinterpret_cast<f32x4*>(x.partials + ((size_t)blockIdx.y * p.M + row[k]) * N + col) = v;
             continue;
           }
           v += add + add_image;
@@ -406,7 +408,8 @@ int launch_one(const TileParams& p, const Geo& g, int nsplit, hipStream_t st) {
     if (hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess) return DF_EHIP;
     attr_set = true;
   }
-  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)nsplit), dim3(512), smem, st, p, x);
+  hipLaunchKernelGGL(k, dim3((unsigned)nwg, (unsigned)nsplit), dim3(512), smem, st, p.Wt, p.A, p.N, p.Cin, (int)p.ldw, (int)MT,
+                     x.group_m, (int)nsplit, x.tiles_r * x.tiles_c, x.tiles_c, p.R, p.W, p, x);
   DF_LAUNCH_CHECK();
   return nsplit > 1 ? launch_conv_reduce(p, x.partials, nsplit, sizeof(OutT) == 4 ? DF_F32 : DF_BF16, st) : DF_OK;
 }
