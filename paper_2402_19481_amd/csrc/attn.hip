@@ -117,7 +117,10 @@ __device__ long long g_attn_trace[512 * 32];
 enum { kSrcVt = 0, kSrcRows = 1, kSrcPeriodic = 2 };
 
 template <bool PRE, int SRC>
-__global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
+__global__ __launch_bounds__(256, 2) void attn_pipe_d64(const bf16_t* q, const bf16_t* ks, const bf16_t* vs, int Lq, int L, unsigned int heads_splits, int keys_per_split,
+                                                        int ldq, int ldks, int ldv, int nwg, AttnParams p) {
+  // (leading arguments come in scalar registers, see wgemm.hip; ldv: the pitch of V^T or of the stale V)
+  const int heads = (int)(heads_splits & 0xffffff), nsplit = (int)(heads_splits >> 24);
   constexpr int D = 64, TK = 64, KB = TK * D * 2;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -127,24 +130,26 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   const int csig = (c & 0x13) | ((c & 4) << 1) | ((c & 8) >> 1);
   int t = blockIdx.x;
   {
-    const int nwg = gridDim.x;
     const int xcd = t & 7, loc = t >> 3;
     const int base = nwg >> 3, rem = nwg & 7;
     t = xcd * base + (xcd < rem ? xcd : rem) + loc;
   }
-  const int nqb = (p.Lq + 127) / 128;
+  const int nqb = (Lq + 127) / 128;
   const int qb = t % nqb;
-  const int h = (t / nqb) % p.heads;
-  const int zz = t / (nqb * p.heads);
-  const int b = zz / p.nsplit, split = zz % p.nsplit;
+  const int h = (t / nqb) % heads;
+  const int zz = t / (nqb * heads);
+  const int b = zz / nsplit, split = zz % nsplit;
   const int q0 = qb * 128 + wave * 32;
-  const int kv_lo = split * p.keys_per_split;              // multiple of 64
-  int kv_hi = kv_lo + p.keys_per_split;
-  if (kv_hi > p.L) kv_hi = p.L;
+  const int kv_lo = split * keys_per_split;              // multiple of 64
+  int kv_hi = kv_lo + keys_per_split;
+  if (kv_hi > L) kv_hi = L;
   const int ntiles = (kv_hi - kv_lo + TK - 1) / TK;
 
-  const bf16_t* kg = (const bf16_t*)p.ks + (long long)b * p.bsks + h * D;
-  const bf16_t* vg = (const bf16_t*)p.vs + (long long)b * p.bsvs + (SRC == kSrcVt ? (long long)h * D * p.vt_ld : (long long)h * D);
+  const bf16_t *kg = ks + h * D, *vg = vs + (SRC == kSrcVt ? (long long)h * D * ldv : (long long)h * D), *qg = q + h * D;
+  if (b > 0) {
+    asm volatile("");
+    kg += (long long)b * p.bsks; vg += (long long)b * p.bsvs; qg += (long long)b * p.bsq;
+  }
   const bf16_t* kfr = (const bf16_t*)p.kf + (long long)b * p.bskf + h * D;
   const bf16_t* vfr = (const bf16_t*)p.vf + (long long)b * p.bsvf + h * D;
 
@@ -164,15 +169,15 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   unsigned int kofs[2], vofs[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    kofs[j] = (unsigned int)trow[j] * (unsigned int)p.ldks + (unsigned int)kch[j];
-    vofs[j] = (unsigned int)trow[j] * (unsigned int)(SRC == kSrcVt ? p.vt_ld : p.ldvs) + (unsigned int)vch[j];
+    kofs[j] = (unsigned int)trow[j] * (unsigned int)ldks + (unsigned int)kch[j];
+    vofs[j] = (unsigned int)trow[j] * (unsigned int)ldv + (unsigned int)vch[j];
   }
   // kSrcVt: kofr are the offsets inside the last tile when it is ragged
   unsigned int kofr[2];
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const int left = p.L - 1 - (kv_lo + (ntiles - 1) * TK);
-    kofr[j] = (unsigned int)(trow[j] < left ? trow[j] : left) * (unsigned int)p.ldks + (unsigned int)kch[j];
+    const int left = L - 1 - (kv_lo + (ntiles - 1) * TK);
+    kofr[j] = (unsigned int)(trow[j] < left ? trow[j] : left) * (unsigned int)ldks + (unsigned int)kch[j];
   }
   // Byte offsets of the K loads (kSrcVt) of the tile requested next; those of the last tile from the iteration that requests it on
   unsigned int kcur[2];
@@ -183,11 +188,11 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     constexpr bool V = decltype(isv)::value;
     const int key0 = kv_lo + ti * TK;
     if constexpr (SRC == kSrcVt) {
-      lds_load16(V ? vg + key0 : kg + (long long)key0 * p.ldks, V ? 2u * vofs[j] : kcur[j], to);
+      lds_load16(V ? vg + key0 : kg + (long long)key0 * ldks, V ? 2u * vofs[j] : kcur[j], to);
       return;
     }
     // rows beyond the last key re-read it (masked)
-    unsigned int key = (unsigned int)(key0 + trow[j] < p.L ? key0 + trow[j] : p.L - 1), row = key - (unsigned int)p.own_lo;
+    unsigned int key = (unsigned int)(key0 + trow[j] < L ? key0 + trow[j] : L - 1), row = key - (unsigned int)p.own_lo;
     bool own = row < (unsigned int)p.own_n;
     if constexpr (SRC == kSrcPeriodic) {
       // key = q * P + r, q from the rounded-down reciprocal (at most one too small)
@@ -198,19 +203,19 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
       row += q * (unsigned int)p.own_n;
     }
     row = own ? row : key;
-    if constexpr (V) lds_load16((own ? vfr : vg) + (unsigned long long)row * (unsigned int)(own ? p.ldvf : p.ldvs) + vch[j], to);
-    else lds_load16((own ? kfr : kg) + (unsigned long long)row * (unsigned int)(own ? p.ldkf : p.ldks) + kch[j], to);
+    if constexpr (V) lds_load16((own ? vfr : vg) + (unsigned long long)row * (unsigned int)(own ? p.ldvf : ldv) + vch[j], to);
+    else lds_load16((own ? kfr : kg) + (unsigned long long)row * (unsigned int)(own ? p.ldkf : ldks) + kch[j], to);
   };
   using IsK = std::false_type;
   using IsV = std::true_type;
   bf16x8 qreg[4];
   {
     const int qi = q0 + c;
-    const bf16_t* qp = (const bf16_t*)p.q + (long long)b * p.bsq + (long long)qi * p.ldq + h * D;
+    const bf16_t* qp = qg + (long long)qi * ldq;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       u32x4 tq = {0u, 0u, 0u, 0u};
-      if (qi < p.Lq) tq = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * g);
+      if (qi < Lq) tq = *reinterpret_cast<const u32x4*>(qp + 16 * s + 8 * g);
       qreg[s] = __builtin_bit_cast(bf16x8, tq);
     }
   }
@@ -419,7 +424,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
     for (int kb = 0; kb < 2; ++kb) {
       const int key = kv_lo + tl * TK + 32 * kb + key_of_mfma_row(c);
       const long long fr = SRC == kSrcVt ? -1 : fresh_row(p.own_lo, p.own_n, SRC == kSrcPeriodic ? p.own_period : 0, key);
-      const bf16_t* kr = (fr >= 0 ? kfr + fr * p.ldkf : kg + (long long)key * p.ldks) + 8 * g;
+      const bf16_t* kr = (fr >= 0 ? kfr + fr * p.ldkf : kg + (long long)key * ldks) + 8 * g;
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         t[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(kr + 16 * s)), qreg[s],
@@ -518,12 +523,12 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
   l_run += __int_as_float(__builtin_amdgcn_ds_bpermute(xor32, __float_as_int(l_run)));
 
   const int qi = q0 + c;
-  if (qi >= p.Lq) return;
-  if (p.nsplit == 1) {
+  if (qi >= Lq) return;
+  if (nsplit == 1) {
     const float inv = 1.0f / l_run;
     bf16_t* op = (bf16_t*)p.out + (long long)b * p.bso + (long long)qi * p.ldo + h * D;
-    const long long m = (long long)b * p.Lq + qi;
-    bf16_t* pp = (bf16_t*)p.out + (((m >> 5) * (long long)(p.heads * D / 16) + h * (D / 16)) * 64 + (m & 31) + 32 * g) * 8;
+    const long long m = (long long)b * Lq + qi;
+    bf16_t* pp = (bf16_t*)p.out + (((m >> 5) * (long long)(heads * D / 16) + h * (D / 16)) * 64 + (m & 31) + 32 * g) * 8;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -537,7 +542,7 @@ __global__ __launch_bounds__(256, 2) void attn_pipe_d64(AttnParams p) {
         else *reinterpret_cast<u32x4*>(op + 32 * db + 16 * f + 8 * g) = tq;
       }
   } else {
-    const long long row = (((long long)split * p.B + b) * p.heads + h) * p.Lq + qi;
+    const long long row = (((long long)split * p.B + b) * heads + h) * Lq + qi;
     float* po = p.part_o + row * D;
 #pragma unroll
     for (int db = 0; db < 2; ++db)
@@ -1265,6 +1270,9 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   }
   if (wave_few_rounds || four_waves) return launch_wave();   // (what the caller has to provide stays that of the split form)
   const long long nwg = (long long)cdiv(a.Lq, 128) * a.heads * a.B * p.nsplit;
+#define DF_PIPE(KERNEL, LDV)                                                                                                      \
+  hipLaunchKernelGGL(KERNEL, dim3((unsigned)nwg), dim3(256), smem, st, (const bf16_t*)p.q, (const bf16_t*)p.ks, (const bf16_t*)p.vs, p.Lq, \
+                     p.L, (unsigned int)p.heads | (unsigned int)p.nsplit << 24, p.keys_per_split, (int)p.ldq, (int)p.ldks, (int)(LDV), (int)nwg, p)
   if (nwg > 0x7fffffffLL) return DF_ESHAPE;
   if (a.v_transposed) {
     // every key from k_stale (row-major) / v_stale (V^T, row pitch vt_ld >= L rounded up to whole 64-key tiles)
@@ -1272,15 +1280,16 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
     if (a.ldks <= 0 || a.ldks >= (1 << 23) || a.vt_ld >= (1 << 25)) return DF_ESHAPE;   // 32-bit offsets inside a tile
     p.vt_ld = a.vt_ld;
     constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V^T tiles
-    if (scaled) hipLaunchKernelGGL((attn_pipe_d64<true, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
-    else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcVt>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    if (scaled) DF_PIPE((attn_pipe_d64<true, kSrcVt>), p.vt_ld);
+    else DF_PIPE((attn_pipe_d64<false, kSrcVt>), p.vt_ld);
   } else {
     // 32-bit row offsets inside a 64-key tile
     if (a.ldkf >= (1 << 24) || a.ldvf >= (1 << 24) || a.ldks >= (1 << 24) || a.ldvs >= (1 << 24)) return DF_ESHAPE;
     constexpr int smem = 6 * 64 * 64 * 2;                // three K and three V tiles
-    if (a.own_period > 0) hipLaunchKernelGGL((attn_pipe_d64<false, kSrcPeriodic>), dim3((unsigned)nwg), dim3(256), smem, st, p);
-    else hipLaunchKernelGGL((attn_pipe_d64<false, kSrcRows>), dim3((unsigned)nwg), dim3(256), smem, st, p);
+    if (a.own_period > 0) DF_PIPE((attn_pipe_d64<false, kSrcPeriodic>), p.ldvs);
+    else DF_PIPE((attn_pipe_d64<false, kSrcRows>), p.ldvs);
   }
+#undef DF_PIPE
   DF_LAUNCH_CHECK();
   if (ns > 1) {
     const long long n = (long long)a.B * a.heads * a.Lq * 8;
