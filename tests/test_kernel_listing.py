@@ -48,3 +48,16 @@ def test_every_direct_load_follows_its_own_write_of_m0(source, tmp_path):
             loads += 1
             assert last is inside, (loads, line)
     assert loads > 0
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="needs the compiler")
+@pytest.mark.parametrize("source,kernels,dwords", [("attn.hip", "attn_wave_d64|attn_pipe_d64", 14), ("tgemm.hip", "tgemm_kernel", 12)])
+def test_leading_arguments_come_in_registers(source, kernels, dwords, tmp_path):
+    """The kernels whose first requests need only their leading arguments: the code object asks for all of those in scalar registers."""
+    out = tmp_path / "k.s"
+    subprocess.run(["hipcc", *build.FLAGS, "--offload-device-only", "-S", os.path.join(build.CSRC, source), "-o", str(out)],
+                   check=True, capture_output=True)
+    got = re.findall(r"\.amdhsa_kernel (\S*(?:%s)\S*)\n(.*?)\.end_amdhsa_kernel" % kernels, out.read_text(), re.S)
+    assert got
+    for name, body in got:
+        assert int(re.search(r"kernarg_preload_length (\d+)", body)[1]) >= dwords, name
