@@ -186,11 +186,14 @@ def groupnorm_stale(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5
                                                fresh_stats_out)
 
 
-def groupnorm_stale_alone(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS, fuse_silu=False):
+def groupnorm_stale_alone(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS, fuse_silu=False,
+                          fresh_stats_out=None):
     """groupnorm_stale whose workgroups wait for nobody: the same result, slower (for tests)."""
     B, R, W, C = x_fresh.shape
     y = torch.empty_like(x_fresh)
-    fs = torch.empty(B, G, 2, dtype=torch.float32, device=x_fresh.device)
+    fs = fresh_stats_out
+    if fs is None:
+        fs = torch.empty(B, G, 2, dtype=torch.float32, device=x_fresh.device)
     _check(lib().df_groupnorm_stale_alone(_ptr(x_fresh), _ptr(y), _ptr(stale_stats), _ptr(fs), _ptr(gamma), _ptr(beta), B, R, W, C, G,
                                           patch_idx, N, eps, stat_mode, int(fuse_silu), _dt(x_fresh), _stream()))
     return y, fs

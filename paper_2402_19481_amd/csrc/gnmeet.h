@@ -1,0 +1,28 @@
+// What the workgroups of gn_meet_kernel (groupnorm.hip) go by when they hand each other sums: rules of a few integers, for the host as well, so
+// that all interleavings of a launch can be tried there.
+#pragma once
+#include "kernels.h"
+
+namespace df {
+
+// The patch's own cached sums [B, G, 2] may be refreshed in place (sums_out inside stale).  Two statistic modes read the old entry, in every
+// workgroup of a slab; one that is late to start must not find the new one there.
+inline bool gn_reads_own(int stat_mode) { return stat_mode == DF_GN_EQ2 || stat_mode == DF_GN_STALE; }
+
+// Which workgroup of a slab writes the patch's own sums (all of them know the totals).  `counted`: each has added one to the slab's counter behind
+// its read of the cached sums and found `arrived` there; no other launch counts meanwhile and every launch adds P, so the last to arrive, waited
+// for or not, knows that all have read.  Not counted: nobody reads what is written.
+__host__ __device__ inline bool gn_meet_writes(bool counted, unsigned int arrived, int P, int part) {
+  return counted ? (arrived & (unsigned int)(P - 1)) == (unsigned int)(P - 1) : part == 0;
+}
+
+// Without a counter of its own (the library's words serve calls that overlap) a launch that would overwrite cached sums that it reads takes them from
+// a copy, made by a launch before it.  `n` floats of a patch; the own entry alone, where the mode does not read it, needs none.
+inline bool gn_meet_copies(const float* stale, const float* sums_out, long long n, int patch_idx, int N, int stat_mode) {
+  if (!stale || !sums_out) return false;
+  const uintptr_t s = (uintptr_t)stale, o = (uintptr_t)sums_out, entry = (uintptr_t)n * sizeof(float);
+  if (o >= s + N * entry || s >= o + entry) return false;
+  return gn_reads_own(stat_mode) || o != s + patch_idx * entry;
+}
+
+}  // namespace df

@@ -23,6 +23,7 @@
 #include <atomic>
 #include <cstdlib>
 #include <mutex>
+#include "gnmeet.h"
 #include "kernels.h"
 
 namespace df {
@@ -749,7 +750,7 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
 // 1024 x 1280 bf16 10.8 -> 6.1, 4096 x 640 float 15.1 -> 8.8, 16384 x 960 bf16 27.1 -> 24.7.  One lane-ordered sum in LDS for the
 // eight words of a workgroup (sums through LDS lane by lane, moments with the cached sums behind the exchange) took 2.5 us more.
 constexpr int kGnMeetParts = 32, kGnMeetBatch = 8, kGnMeetGroups = 4, kGnMeetWait = 1024;
-// 8-byte words of a (batch item, slab): a line with the counter of tickets, then 8 per workgroup; and of a launch with P workgroups per slab
+// 8-byte words of a (batch item, slab): a line with the counters of tickets and of arrivals, then 8 per workgroup; and of a launch with P workgroups per slab
 __host__ __device__ constexpr int gn_meet_stride(int P) { return 8 + 8 * P; }
 constexpr size_t gn_meet_words(int P) { return (size_t)kGnMeetBatch * 8 * gn_meet_stride(P); }
 // launches with 2, 4, .. 32 workgroups per slab have words of their own, one after the other
@@ -768,6 +769,7 @@ struct GnMeet {
   unsigned long long* words;
   unsigned int id, tp_recip, cg_recip;
   int lgP, lgS, tp, ppb, pix_part, wait;                 // lgS: of the workgroups of a segment
+  int counted;                                           // the last to arrive writes the patch's own sums (gnmeet.h)
 };
 
 // The wave's sums of eight words per lane: word 4 (lane / 32) + 2 (lane / 16 % 2) + lane / 8 % 2 in every eight lanes.  A step adds half of the
@@ -908,9 +910,12 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
   bool met = false;
   float val[NP];                                         // word lane % 8 of range lane / 8 + 8 i
   double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
+  bool writes = false;                                   // the patch's own sums
   if (wave == 0) {
-    // the cached sums are here before this workgroup's sums go out: the first one writes the patch's own, which may lie among them
-    asm volatile("" ::"v"(st.x), "v"(st.y));
+    // the cached sums are here before this workgroup counts itself: the last to do so overwrites the patch's own, which may lie among them
+    unsigned int one = 1u, arrived = 0;
+    asm volatile("" : "+v"(one) : "v"(st.x), "v"(st.y));
+    if (mt.counted && lane == 0) arrived = __hip_atomic_fetch_add((unsigned int*)words + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned int tag = (mt.id << 16) | (((unsigned int)__builtin_amdgcn_readfirstlane((int)ticket) >> mt.lgP) & 0xffffu);
     if (lane < 8)
       __hip_atomic_store(words + 8 + part * 8 + lane, (unsigned long long)tag << 32 | __float_as_uint(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -931,6 +936,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
       met = __all(ok);
     }
     if (lane == 0) s_met = met;
+    writes = gn_meet_writes(mt.counted, (unsigned int)__builtin_amdgcn_readfirstlane((int)arrived), P, part);
   }
   auto moments = [&] {                                   // of the slab's groups, by lanes 0 .. Gs - 1 of the first wave
     double tot_s = 0.0, tot_q = 0.0;
@@ -938,7 +944,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
       double S, SS;
       gn_unshift(t, lane_move<0x104>(t), cnt.n_loc, gpiv, S, SS);   // row_shl:4
       tot_s += S; tot_q += SS;
-      if (nseg > 1 && part == 0 && lane < Gs) {
+      if (nseg > 1 && writes && lane < Gs) {
         float* o = sums_out + (((long long)sg * B + b) * G + g0 + lane) * 2;
         o[0] = (float)S; o[1] = (float)SS;
       }
@@ -962,7 +968,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
     if (lane < Gs) {
       const GnMoments mo = gn_combine_pre(tot_s, tot_q, cnt, nseg, N, stat_mode, st_s, st_q, own_s, own_q, eps);
       s_mom[lane][0] = mo.mean_hi; s_mom[lane][1] = mo.mean_lo; s_mom[lane][2] = mo.rstd;
-      if (nseg == 1 && sums_out != nullptr && part == 0) {
+      if (nseg == 1 && sums_out != nullptr && writes) {
         float* o = sums_out + ((long long)b * G + g0 + lane) * 2;
         o[0] = (float)tot_s; o[1] = (float)tot_q;
       }
@@ -1121,6 +1127,11 @@ bool groupnorm_takes_pair(const GnArgs& a) {
 }
 
 namespace {
+__global__ __launch_bounds__(256) void gn_copy_sums(const float* __restrict__ stale, float* __restrict__ copy, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) copy[i] = stale[i];
+}
+
 int ilog2(int n) { return n > 1 ? 1 + ilog2(n / 2) : 0; }
 unsigned int gn_call_number() {
   static std::atomic<unsigned int> n{0};
@@ -1172,18 +1183,30 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   const double n_loc = (double)pix_seg * (double)(a.C / a.G);
   const double n_all = n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1);
   const GnCount cnt = {n_loc, 1.0 / n_loc, n_all, 1.0 / n_all};
+  const bool need_stale = !(a.nseg > 1 || (a.N == 1 && a.stat_mode != DF_GN_STALE));
+  const int stale_n = need_stale ? a.N * a.B * a.G * 2 : 0;
   // small tensors: the whole GroupNorm in one launch, one workgroup per (group, batch item)
   {
     const GnForm form = gn_form(a);
     const int v = form.v, nv = form.nv;
     if (a.x2 && form.group) return DF_ESHAPE;
     if (form.P) {
+      const float* stale = a.stale;
+      if (need_stale && !a.meet && gn_meet_copies(stale, a.sums_out, (long long)a.B * a.G * 2, a.patch_idx, a.N, a.stat_mode)) {
+        char* scr = scratch_region(a.scr, groupnorm_scratch_bytes(a.B, a.nseg, a.G, a.N));
+        if (!scr) return DF_ENOMEM;
+        float* copy = (float*)(scr + kScratchCounterBytes);
+        hipLaunchKernelGGL(gn_copy_sums, dim3(cdiv(stale_n, 256)), dim3(256), 0, st, stale, copy, stale_n);
+        DF_LAUNCH_CHECK();
+        stale = copy;
+      }
       const unsigned int call = gn_call_number();
       const GnMeet mt = {gn_words(a, form.P, call), call, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
-                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : kGnMeetWait};
+                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : kGnMeetWait,
+                         a.meet && need_stale && gn_reads_own(a.stat_mode)};
       if (!mt.words) return DF_EHIP;
 #define DF_GN_MEET(TI, TO, NVV, PR)                                                                                         \
-  hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, a.stale, \
+  hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,      \
                      a.silu, a.y_packed, halo, cnt, mt, gn_from<PR>(a))
 #define DF_GN_MEET_T(NVV)                                                                                                    \
@@ -1249,8 +1272,6 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   if (L.threads > 1024 || L.ppb > kGnMaxPpb) return DF_ESHAPE;
   char* scr = scratch_region(a.scr, groupnorm_scratch_bytes(a.B, a.nseg, a.G, a.N));
   if (!scr) return DF_ENOMEM;
-  const bool need_stale = !(a.nseg > 1 || (a.N == 1 && a.stat_mode != DF_GN_STALE));
-  const int stale_n = need_stale ? a.N * a.B * a.G * 2 : 0;
   float* stale_copy = (float*)(scr + kScratchCounterBytes);
   float* partial = stale_copy + (((size_t)a.N * a.B * a.G * 2 + 63) / 64) * 64;
   dim3 gs(L.nblk, a.nseg, a.B);

@@ -57,6 +57,22 @@ def test_groupnorm_sums_refreshed_in_place():
         assert torch.equal(cache[[0, 1, 3]], dev(st)[[0, 1, 3]])
 
 
+@pytest.mark.parametrize("B", [1, 3])
+@pytest.mark.parametrize("mode", [0, 1, 2, 3])
+def test_groupnorm_sums_refreshed_in_place_by_nobody_who_waits(mode, B):
+    """The same, and no workgroup knows of another: the old sums are still those that all of them read."""
+    N, patch = 4, 2
+    full, st, gamma, beta = _gn_case(31, B, N * 32, 64, 640, 32, N, True)
+    x = dev(full[:, patch * 32:(patch + 1) * 32], True)
+    args = (dev(gamma), dev(beta), 32, patch, N, 1e-5, mode, True)
+    y0, fs0 = df.groupnorm_stale(x, dev(st), *args)
+    for call in (df.groupnorm_stale, df.groupnorm_stale_alone):
+        cache = dev(st)
+        y, fs = call(x, cache, *args, fresh_stats_out=cache[patch])
+        assert torch.equal(_bits(y), _bits(y0)) and torch.equal(cache[patch], fs0)
+        assert torch.equal(cache[[0, 1, 3]], dev(st)[[0, 1, 3]])
+
+
 def test_groupnorm_replays_and_streams():
     N, patch = 2, 1
     cases = []
