@@ -25,4 +25,16 @@ inline bool gn_meet_copies(const float* stale, const float* sums_out, long long 
   return gn_reads_own(stat_mode) || o != s + patch_idx * entry;
 }
 
+// The number that a launch's words carry.  A word counts with the right number only, so no other launch whose words may lie there has the same.
+//   - Words of one plan (id 0): its launches do not overlap, each takes P tickets, so a ticket's multiple of P is the launch's; older words are always
+//     the previous launch's.
+//   - The library's words serve calls that overlap, and tickets that are dealt out in turns say nothing there: of two launches a replay can find
+//     half of a multiple its own and half the replay's before.  The call has a number of its own instead; an eager one gets it back after 2^31
+//     others.  A recorded one keeps it for all replays (so those have numbers that no eager call has), and its words are cleared by a launch
+//     before it: others on the same words can take a word away, not bring back the replay's before.
+__host__ __device__ inline unsigned int gn_meet_number(unsigned int id, unsigned int ticket, int lgP) { return id ? id : (ticket >> lgP) + 1u; }
+inline unsigned int gn_call_id(unsigned long long n, bool recorded) {
+  return (unsigned int)(n % 0x7fffffffull) + 1u + (recorded ? 0x80000000u : 0u);   // (never 0: words that nobody has written)
+}
+
 }  // namespace df

@@ -741,9 +741,7 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
 // over all XCDs takes 5 and a second launch 2 and another read of x.
 //   - The result depends neither on where the workgroups are nor on all of them being there at once: a word counts only with the right number, and
 //     after `wait` polls a workgroup adds up the other ranges itself, in the same order, with the same bits.  So every wait ends.
-//   - The number is the call's, never the same for two calls that can be under way together, and the how manieth launch on its words this
-//     is (each workgroup takes a ticket as it starts): a graph that is replayed does not take the words of the replay before for its own,
-//     and calls that overlap on the same words find numbers that are not theirs.
+//   - A word is of this launch and no other: gnmeet.h says how the number is chosen, also for replays of a recorded call and for calls that overlap.
 // Bound by two round trips to memory and the exchange (32 x 128 x 320 bf16, us from the first start: requests out 1.6, sums 2.4, all
 // there 3.3, moments 3.8, stored 4.4), by the rates of both beyond some 10 MB.  A launch after another, against two launches or (up to sixteen
 // pixels per lane) a workgroup per group: 1024 x 320 float 7.3 -> 5.0 us, 4096 x 320 bf16 12.1 -> 6.7, 494 x 1280 float 6.5 -> 5.2,
@@ -821,7 +819,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
   const int b = loc >> mt.lgP, part = loc & (P - 1), pps = 1 << mt.lgS;
   unsigned long long* const words = mt.words + (size_t)(b * 8 + slab) * gn_meet_stride(P);
   unsigned int ticket = 0;
-  if (tid == 0) ticket = __hip_atomic_fetch_add((unsigned int*)words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (mt.id == 0 && tid == 0) ticket = __hip_atomic_fetch_add((unsigned int*)words, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const int Gs = G >> 3, g0 = slab * Gs, cg = C / G;
   const int psub = (int)quotient_u32(tid, mt.tp, mt.tp_recip), tc = tid - psub * mt.tp;
   const int cl = tc * V, la = (int)quotient_u32(cl, cg, mt.cg_recip), nb = (la + 1) * cg - cl;   // group of the slab, and its channels here
@@ -916,7 +914,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
     unsigned int one = 1u, arrived = 0;
     asm volatile("" : "+v"(one) : "v"(st.x), "v"(st.y));
     if (mt.counted && lane == 0) arrived = __hip_atomic_fetch_add((unsigned int*)words + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned int tag = (mt.id << 16) | (((unsigned int)__builtin_amdgcn_readfirstlane((int)ticket) >> mt.lgP) & 0xffffu);
+    const unsigned int tag = gn_meet_number(mt.id, (unsigned int)__builtin_amdgcn_readfirstlane((int)ticket), mt.lgP);
     if (lane < 8)
       __hip_atomic_store(words + 8 + part * 8 + lane, (unsigned long long)tag << 32 | __float_as_uint(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (cached)
@@ -1133,24 +1131,44 @@ __global__ __launch_bounds__(256) void gn_copy_sums(const float* __restrict__ st
 }
 
 int ilog2(int n) { return n > 1 ? 1 + ilog2(n / 2) : 0; }
-unsigned int gn_call_number() {
-  static std::atomic<unsigned int> n{0};
-  return n.fetch_add(1, std::memory_order_relaxed) % 0xffffu + 1;   // (never 0: words that nobody has written)
+__global__ __launch_bounds__(256) void gn_clear_words(unsigned long long* words, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) __hip_atomic_store(words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// The words of a launch: the caller's, or the library's on the current device
-unsigned long long* gn_words(const GnArgs& a, int P, unsigned int call) {
-  if (a.meet) return (unsigned long long*)a.meet + gn_meet_offset(P);
+bool recording(hipStream_t st) {
+  if (!st) return false;                                 // (the default stream cannot be recorded)
+  hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &s) != hipSuccess) { (void)hipGetLastError(); return true; }
+  return s != hipStreamCaptureStatusNone;
+}
+// The words of a launch and its number (gnmeet.h): the caller's, or the library's on the current device
+int gn_words(const GnArgs& a, int P, hipStream_t st, unsigned long long** words, unsigned int* id) {
+  if (a.meet) {
+    *words = (unsigned long long*)a.meet + gn_meet_offset(P);
+    *id = 0;
+    return DF_OK;
+  }
   static std::atomic<unsigned long long*> at[64];
+  static std::atomic<unsigned long long> calls[2];
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return nullptr;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return DF_EHIP;
   unsigned long long* w = at[dev].load(std::memory_order_relaxed);
   if (!w) {
     void* ptr = nullptr;
-    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_gn_words)) != hipSuccess || !ptr) { (void)hipGetLastError(); return nullptr; }
+    if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(g_gn_words)) != hipSuccess || !ptr) { (void)hipGetLastError(); return DF_EHIP; }
     w = (unsigned long long*)ptr;
     at[dev].store(w, std::memory_order_relaxed);
   }
-  return w + (call % kGnMeetCopies) * kGnMeetWords + gn_meet_offset(P);
+  const bool rec = recording(st);
+  const unsigned long long n = calls[rec].fetch_add(1, std::memory_order_relaxed);
+  *id = gn_call_id(n, rec);
+  *words = w + (n % kGnMeetCopies) * kGnMeetWords + gn_meet_offset(P);
+  if (rec) {
+    const int cleared = a.B * 8 * gn_meet_stride(P);
+    hipLaunchKernelGGL(gn_clear_words, dim3(cdiv(cleared, 256)), dim3(256), 0, st, *words, cleared);
+    DF_LAUNCH_CHECK();
+  }
+  return DF_OK;
 }
 }  // namespace
 
@@ -1200,11 +1218,12 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
         DF_LAUNCH_CHECK();
         stale = copy;
       }
-      const unsigned int call = gn_call_number();
-      const GnMeet mt = {gn_words(a, form.P, call), call, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
+      unsigned long long* words = nullptr;
+      unsigned int id = 0;
+      if (const int rc = gn_words(a, form.P, st, &words, &id)) return rc;
+      const GnMeet mt = {words, id, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
                          ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : kGnMeetWait,
                          a.meet && need_stale && gn_reads_own(a.stat_mode)};
-      if (!mt.words) return DF_EHIP;
 #define DF_GN_MEET(TI, TO, NVV, PR)                                                                                         \
   hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,      \

@@ -106,6 +106,31 @@ def test_groupnorm_replays_and_streams():
         assert torch.equal(_bits(y), _bits(want[k][0])) and torch.equal(fs, want[k][1])
 
 
+def test_groupnorm_replays_beside_other_calls():
+    """A recorded call on new values each time, while calls of the same size run on another stream (and share its words now and then)."""
+    N, patch, R, W, C = 2, 1, 32, 32, 1280
+    full, st, gamma, beta = _gn_case(37, 1, N * R, W, C, 32, N, True)
+    args = (dev(st), dev(gamma), dev(beta), 32, patch, N, 1e-5, 0, True)
+    xs = [dev(full[:, R:] * (1 + k), True) for k in range(3)]
+    want = [df.groupnorm_stale(x, *args) for x in xs]
+    buf, one, two = xs[0].clone(), torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=one):
+        y, fs = df.groupnorm_stale(buf, *args)
+    got, other = [], []
+    for rep in range(24):
+        with torch.cuda.stream(two):
+            other += [(k, df.groupnorm_stale(xs[k], *args)) for k in range(3)]
+        with torch.cuda.stream(one):
+            buf.copy_(xs[rep % 3])
+            g.replay()
+            got.append((rep % 3, (y.clone(), fs.clone())))
+    torch.cuda.synchronize()
+    for k, (yy, ff) in got + other:
+        assert torch.equal(_bits(yy), _bits(want[k][0])) and torch.equal(ff, want[k][1]), k
+
+
 def test_groupnorm_in_place():
     """y over x: the form whose workgroups might read it again is not taken."""
     full, st, gamma, beta = _gn_case(29, 1, 2 * 32, 32, 1280, 32, 2, True)

@@ -89,3 +89,77 @@ int main() {
 
 def test_own_sums_are_written_when_all_have_read_the_old_ones(tmp_path):
     run(tmp_path, REFRESH)
+
+
+NUMBERS = r"""
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "gnmeet.h"
+
+// A slab's words while one call is replayed and others run beside it on another stream, in random order: a workgroup takes its number, publishes,
+// and looks; a word with its number has to be of its own launch.  clear: a recorded launch's words are cleared before its workgroups start.
+// beside: the other calls, eager ones with numbers of their own.
+constexpr int P = 4, LGP = 2;
+struct Word { unsigned int tag; int launch; };
+struct Group { int pc; unsigned int tag; };
+template <typename Number>
+long long wrong(std::mt19937& rng, bool clear, bool beside, unsigned int recorded_id, Number number) {
+  Word words[P] = {};
+  unsigned int tickets = 0;
+  unsigned long long calls = 0;
+  int launches = 0;
+  long long bad = 0;
+  struct Launch { int serial; unsigned int id; std::vector<Group> g; bool clear; } run[2] = {};
+  for (int step = 0; step < 400; ++step) {
+    const int k = beside ? (int)(rng() % 2) : 0;
+    Launch& l = run[k];
+    std::vector<int> open;
+    for (int i = 0; i < (int)l.g.size(); ++i) if (l.g[i].pc < 3) open.push_back(i);
+    if (open.empty()) {                                     // the stream's next launch
+      l.serial = ++launches;
+      l.id = k == 0 ? recorded_id : df::gn_call_id(calls++, false);
+      l.g.assign(P, Group{0, 0});
+      if (k == 0 && clear) for (Word& w : words) w = Word{0, 0};
+      continue;
+    }
+    const int i = open[rng() % open.size()];
+    Group& g = l.g[i];
+    if (g.pc == 0) g.tag = number(l.id, tickets++);
+    if (g.pc == 1) words[i] = Word{g.tag, l.serial};
+    if (g.pc == 2) {
+      for (const Word& w : words) bad += w.tag == g.tag && w.launch != l.serial;
+      if (rng() % 2) continue;                              // looks again
+    }
+    ++g.pc;
+  }
+  return bad;
+}
+
+int main() {
+  std::mt19937 rng(3);
+  auto number = [](unsigned int id, unsigned int ticket) { return df::gn_meet_number(id, ticket, LGP); };
+  auto by_ticket = [](unsigned int id, unsigned int ticket) { return id << 16 | (ticket >> LGP & 0xffff); };
+  long long plan = 0, lib = 0, tickets = 0, unclear = 0;
+  const unsigned int rec = df::gn_call_id(0, true);
+  for (int i = 0; i < 20000; ++i) {
+    plan += wrong(rng, false, false, 0, number);            // words of a plan's own
+    lib += wrong(rng, true, true, rec, number);
+    tickets += wrong(rng, false, true, 7000, by_ticket);    // tickets of launches that overlap: not sound
+    unclear += wrong(rng, false, true, rec, number);        // nor a recorded call's number alone
+  }
+  printf("%lld %lld %lld %lld\n", plan, lib, tickets, unclear);
+  if (plan || lib || !tickets || !unclear) return 1;
+  const unsigned long long M = 0x7fffffffull;
+  for (unsigned long long n : {0ull, 1ull, M - 1, M, M + 1, 5 * M - 1, ~0ull}) {
+    const unsigned int e = df::gn_call_id(n, false), r = df::gn_call_id(n, true);
+    if (!e || e >> 31 || r >> 31 != 1 || df::gn_call_id(n + 1, false) == e || df::gn_call_id(n + 1, true) == r) return 2;
+  }
+  if (!df::gn_meet_number(0, 0, 1) || !df::gn_meet_number(0, ~0u, 1) || df::gn_meet_number(9, ~0u, 1) != 9) return 3;
+  return 0;
+}
+"""
+
+
+def test_a_word_counts_in_its_own_launch_only(tmp_path):
+    run(tmp_path, NUMBERS)
