@@ -7,7 +7,7 @@ namespace df {
 
 // The patch's own cached sums [B, G, 2] may be refreshed in place (sums_out inside stale).  Two statistic modes read the old entry, in every
 // workgroup of a slab; one that is late to start must not find the new one there.
-inline bool gn_reads_own(int stat_mode) { return stat_mode == DF_GN_EQ2 || stat_mode == DF_GN_STALE; }
+__host__ __device__ inline bool gn_reads_own(int stat_mode) { return stat_mode == DF_GN_EQ2 || stat_mode == DF_GN_STALE; }
 
 // Which workgroup of a slab writes the patch's own sums (all of them know the totals).  `counted`: each has added one to the slab's counter behind
 // its read of the cached sums and found `arrived` there; no other launch counts meanwhile and every launch adds P, so the last to arrive, waited

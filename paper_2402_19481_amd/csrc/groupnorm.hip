@@ -739,15 +739,18 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
 // (workgroups go round-robin over the eight, so blockIdx % 8 is the slab), and a sum goes through that XCD's L2 as an 8-byte word with the
 // launch's number beside the float, so one store and one poll pass it on: 0.9 us with the wait for the slowest, where an exchange
 // over all XCDs takes 5 and a second launch 2 and another read of x.
-//   - The result depends neither on where the workgroups are nor on all of them being there at once: a word counts only with the right number, and
-//     after `wait` polls a workgroup adds up the other ranges itself, in the same order, with the same bits.  So every wait ends.
+//   - The result depends neither on where the workgroups are nor on all of them being there at once: after `wait` polls (0.2 us each, all
+//     together what a second launch costs; launches and steps with the chip to themselves are as fast with 8 as with 1024) a workgroup adds up the
+//     ranges that are missing itself, in the same order, with the same bits, and hands them on.  So every wait ends.  Beside a kernel of another
+//     stream on one unit of each XCD, 16384 x 960 bf16 45 us a launch (two launches 46); with 1024 polls, and every workgroup adding up all
+//     ranges again, 361.  Where nobody waits for anybody 151 us, 4096 x 320 48.
 //   - A word is of this launch and no other: gnmeet.h says how the number is chosen, also for replays of a recorded call and for calls that overlap.
 // Bound by two round trips to memory and the exchange (32 x 128 x 320 bf16, us from the first start: requests out 1.6, sums 2.4, all
 // there 3.3, moments 3.8, stored 4.4), by the rates of both beyond some 10 MB.  A launch after another, against two launches or (up to sixteen
 // pixels per lane) a workgroup per group: 1024 x 320 float 7.3 -> 5.0 us, 4096 x 320 bf16 12.1 -> 6.7, 494 x 1280 float 6.5 -> 5.2,
 // 1024 x 1280 bf16 10.8 -> 6.1, 4096 x 640 float 15.1 -> 8.8, 16384 x 960 bf16 27.1 -> 24.7.  One lane-ordered sum in LDS for the
 // eight words of a workgroup (sums through LDS lane by lane, moments with the cached sums behind the exchange) took 2.5 us more.
-constexpr int kGnMeetParts = 32, kGnMeetBatch = 8, kGnMeetGroups = 4, kGnMeetWait = 1024;
+constexpr int kGnMeetParts = 32, kGnMeetBatch = 8, kGnMeetGroups = 4, kGnMeetWait = 16;
 // 8-byte words of a (batch item, slab): a line with the counters of tickets and of arrivals, then 8 per workgroup; and of a launch with P workgroups per slab
 __host__ __device__ constexpr int gn_meet_stride(int P) { return 8 + 8 * P; }
 constexpr size_t gn_meet_words(int P) { return (size_t)kGnMeetBatch * 8 * gn_meet_stride(P); }
@@ -767,7 +770,6 @@ struct GnMeet {
   unsigned long long* words;
   unsigned int id, tp_recip, cg_recip;
   int lgP, lgS, tp, ppb, pix_part, wait;                 // lgS: of the workgroups of a segment
-  int counted;                                           // the last to arrive writes the patch's own sums (gnmeet.h)
 };
 
 // The wave's sums of eight words per lane: word 4 (lane / 32) + 2 (lane / 16 % 2) + lane / 8 % 2 in every eight lanes.  A step adds half of the
@@ -812,7 +814,8 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
                                                        int patch_idx, int N, float eps, int stat_mode, int silu, int packed,
                                                        GnHalo halo, GnCount cnt, GnMeet mt, GnFrom<PAIR> pr) {
   constexpr int V = Elem<Tin>::kVec, NP = kGnMeetParts / 8;
-  __shared__ float s_wave[2][16][8], s_all[kGnMeetParts][8], s_mom[kGnMeetGroups][3];
+  __shared__ float s_wave[16][8], s_all[kGnMeetParts][8], s_mom[kGnMeetGroups][3];
+  __shared__ unsigned int s_missing;
   __shared__ int s_met;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int slab = blockIdx.x & 7, loc = blockIdx.x >> 3, P = 1 << mt.lgP;
@@ -867,7 +870,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
   };
   // sums of range q, which is in the registers, to the first wave: word lane % 8 is the sum (0 - 3) or the sum of squares (4 - 7) of x - pivot
   // of group lane % 4
-  auto sums = [&](int q, int buf) {
+  auto sums = [&](int q) {
     int lo, hi;
     range(q, lo, hi);
     float s0 = 0.f, q0 = 0.f, s1 = 0.f, q1 = 0.f;
@@ -893,30 +896,57 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
       w[i + 4] = la == i ? q0 : la + 1 == i ? q1 : 0.f;
     }
     const float t = wave_total8(w, lane);
-    if ((lane & 7) == 0) s_wave[buf][wave][lane >> 3] = t;
+    if ((lane & 7) == 0) s_wave[wave][lane >> 3] = t;
     __syncthreads();
     float r = 0.f;
-    if (wave == 0) r = eighth_total(s_wave[buf][lane >> 3][lane & 7] + s_wave[buf][8 + (lane >> 3)][lane & 7], 8);
+    if (wave == 0) r = eighth_total(s_wave[lane >> 3][lane & 7] + s_wave[8 + (lane >> 3)][lane & 7], 8);
     return r;
   };
   request(part);
-  const float mine = sums(part, 0);
+  const float mine = sums(part);
   float gm[V], bt[V];                                    // (beside the exchange)
   ld_vec(gamma + c0, gm); ld_vec(beta + c0, bt);
   if constexpr (V == 8) { ld_vec(gamma + c0 + 4, gm + 4); ld_vec(beta + c0 + 4, bt + 4); }
   __builtin_amdgcn_sched_barrier(0);
   bool met = false;
   float val[NP];                                         // word lane % 8 of range lane / 8 + 8 i
+  unsigned int tag = 0;
   double st_s = 0.0, st_q = 0.0, own_s = 0.0, own_q = 0.0;
   bool writes = false;                                   // the patch's own sums
-  if (wave == 0) {
-    // the cached sums are here before this workgroup counts itself: the last to do so overwrites the patch's own, which may lie among them
-    unsigned int one = 1u, arrived = 0;
-    asm volatile("" : "+v"(one) : "v"(st.x), "v"(st.y));
-    if (mt.counted && lane == 0) arrived = __hip_atomic_fetch_add((unsigned int*)words + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned int tag = gn_meet_number(mt.id, (unsigned int)__builtin_amdgcn_readfirstlane((int)ticket), mt.lgP);
+  auto hand = [&](int q, float t) {                      // the sums of range q
     if (lane < 8)
-      __hip_atomic_store(words + 8 + part * 8 + lane, (unsigned long long)tag << 32 | __float_as_uint(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(words + 8 + q * 8 + lane, (unsigned long long)tag << 32 | __float_as_uint(t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
+  // the words of the ranges in `missing` (a bit each) that have come, to s_all; those that have not
+  auto look = [&](unsigned int missing) {
+    unsigned int left = 0;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int q = (lane >> 3) + 8 * i;
+      bool gone = missing >> q & 1u;
+      if (gone) {
+        const unsigned long long w = __hip_atomic_load(words + 8 + lane + 64 * i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        gone = (unsigned int)(w >> 32) != tag;
+        if (!gone) s_all[q][lane & 7] = __uint_as_float((unsigned int)w);
+      }
+      unsigned long long m = __ballot(gone);             // a bit per word: gathered to one per range
+      m |= m >> 4; m |= m >> 2; m |= m >> 1;
+      left |= (unsigned int)((m & 0x0101010101010101ull) * 0x0102040810204080ull >> 56) << (8 * i);
+    }
+    return left;
+  };
+  if (wave == 0) {
+    tag = gn_meet_number(mt.id, (unsigned int)__builtin_amdgcn_readfirstlane((int)ticket), mt.lgP);
+    hand(part, mine);
+    writes = gn_meet_writes(false, 0, P, part);
+    unsigned int arrived = 0;
+    const bool counted = mt.id == 0 && cached && gn_reads_own(stat_mode);   // (id 0: words that no other launch uses)
+    if (counted) {
+      // the cached sums are here before this workgroup counts itself: the last to do so overwrites the patch's own, which may lie among them
+      unsigned int one = 1u;
+      asm volatile("" : "+v"(one) : "v"(st.x), "v"(st.y));
+      if (lane == 0) arrived = __hip_atomic_fetch_add((unsigned int*)words + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (cached)
       for (int j = 0; j < N; ++j) {                      // patch order fixes the order of the additions
         const float aj = __shfl(st.x, j * Gs + (lane & (Gs - 1)), 64), cj = __shfl(st.y, j * Gs + (lane & (Gs - 1)), 64);
@@ -934,11 +964,11 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
       met = __all(ok);
     }
     if (lane == 0) s_met = met;
-    writes = gn_meet_writes(mt.counted, (unsigned int)__builtin_amdgcn_readfirstlane((int)arrived), P, part);
+    if (counted) writes = gn_meet_writes(true, (unsigned int)__builtin_amdgcn_readfirstlane((int)arrived), P, part);
   }
   auto moments = [&] {                                   // of the slab's groups, by lanes 0 .. Gs - 1 of the first wave
     double tot_s = 0.0, tot_q = 0.0;
-    auto add = [&](float t, int sg) {                    // a segment's words
+    auto segment = [&](float t, int sg) {                // a segment's words
       double S, SS;
       gn_unshift(t, lane_move<0x104>(t), cnt.n_loc, gpiv, S, SS);   // row_shl:4
       tot_s += S; tot_q += SS;
@@ -951,7 +981,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
       float t = val[0];
 #pragma unroll
       for (int i = 1; i < NP; ++i) t += val[i];
-      add(eighth_total(t, 8), 0);
+      segment(eighth_total(t, 8), 0);
     } else {
 #pragma unroll
       for (int i = 0; i < NP; ++i) val[i] = eighth_total(val[i], pps < 8 ? pps : 8);
@@ -960,7 +990,7 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
 #pragma unroll
         for (int i = 0; i < NP; ++i)
           if (i >= (sg * pps) >> 3 && 8 * i < (sg + 1) * pps) t += val[i];
-        add(__shfl(t, ((sg * pps) & 7) * 8 + (lane & 7), 64), sg);
+        segment(__shfl(t, ((sg * pps) & 7) * 8 + (lane & 7), 64), sg);
       }
     }
     if (lane < Gs) {
@@ -974,15 +1004,32 @@ __global__ __launch_bounds__(1024) void gn_meet_kernel(const Tin* __restrict__ x
   };
   if (met) moments();
   __syncthreads();
-  if (!s_met) {
-    // a range did not appear: this workgroup adds up all of them itself
-#pragma unroll 1
-    for (int q = 0; q < P; ++q) {
+  if (__builtin_expect(!s_met, 0)) {
+    // Some range did not appear.  Those that are missing are added up here, each workgroup beginning with another one.
+    auto left = [&](unsigned int missing) {              // told to all waves
+      if (wave == 0) {
+        if (mt.wait > 0 && missing) missing = look(missing);
+        if (lane == 0) s_missing = missing;
+      }
+      __syncthreads();
+      return (unsigned int)__builtin_amdgcn_readfirstlane((int)s_missing);
+    };
+    unsigned int missing = left(P < 32 ? (1u << P) - 1u : ~0u);
+    while (missing) {
+      unsigned int rest = missing;
+      for (int k = part % __popc(missing); k > 0; --k) rest &= rest - 1;
+      const int q = __ffs(rest) - 1;
       request(q);
-      const float r = sums(q, (q + 1) & 1);
-      if (wave == 0 && lane < 8) s_all[q][lane] = r;
+      const float t = sums(q);
+      if (wave == 0) {
+        if (lane < 8) s_all[q][lane] = t;
+        if (mt.wait > 0) hand(q, t);
+      }
+      missing = left(missing & ~(1u << q));
     }
-    request(part);
+    int own = part;                                      // (the addresses of the first time kept until here did not fit the registers)
+    asm volatile("" : "+s"(own));
+    request(own);
     if (wave == 0) {
 #pragma unroll
       for (int i = 0; i < NP; ++i) val[i] = (lane >> 3) + 8 * i < P ? s_all[(lane >> 3) + 8 * i][lane & 7] : 0.f;
@@ -1135,6 +1182,10 @@ __global__ __launch_bounds__(256) void gn_clear_words(unsigned long long* words,
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) __hip_atomic_store(words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+int gn_meet_wait(int looks) {
+  const char* e = tune_env("DF_GN_WAIT");
+  return looks < 0 ? 0 : e ? atoi(e) : kGnMeetWait;
+}
 bool recording(hipStream_t st) {
   if (!st) return false;                                 // (the default stream cannot be recorded)
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -1222,8 +1273,7 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
       unsigned int id = 0;
       if (const int rc = gn_words(a, form.P, st, &words, &id)) return rc;
       const GnMeet mt = {words, id, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
-                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : kGnMeetWait,
-                         a.meet && need_stale && gn_reads_own(a.stat_mode)};
+                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, gn_meet_wait(a.looks)};
 #define DF_GN_MEET(TI, TO, NVV, PR)                                                                                         \
   hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,      \

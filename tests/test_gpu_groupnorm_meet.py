@@ -131,6 +131,27 @@ def test_groupnorm_replays_beside_other_calls():
         assert torch.equal(_bits(yy), _bits(want[k][0])) and torch.equal(ff, want[k][1]), k
 
 
+def test_groupnorm_beside_a_kernel_that_holds_units():
+    """Eight pixels per lane, so a workgroup needs a unit's registers: those of units that another stream's kernel holds start when others have left,
+    which add up the missing ranges."""
+    N, patch = 2, 1
+    full, st, gamma, beta = _gn_case(41, 1, N * 64, 256, 960, 32, N, True)
+    args = (dev(full[:, 64:], True), dev(st), dev(gamma), dev(beta), 32, patch, N, 1e-5, 0, True)
+    y0, fs0 = df.groupnorm_stale_alone(*args)
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    for blocks in (8, 100, 250):
+        got = []
+        torch.cuda.synchronize()
+        with torch.cuda.stream(streams[0]):
+            df.mfma_probe(blocks, 20000)                       # (0.5 ms)
+        for s in streams[1:]:                                  # (one of them may share the hardware queue of the first)
+            with torch.cuda.stream(s):
+                got += [df.groupnorm_stale(*args) for _ in range(4)]
+        torch.cuda.synchronize()
+        for y, fs in got:
+            assert torch.equal(_bits(y), _bits(y0)) and torch.equal(fs, fs0), blocks
+
+
 def test_groupnorm_in_place():
     """y over x: the form whose workgroups might read it again is not taken."""
     full, st, gamma, beta = _gn_case(29, 1, 2 * 32, 32, 1280, 32, 2, True)
