@@ -1253,6 +1253,7 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
   const double n_all = n_loc * (double)(a.nseg > 1 ? a.nseg : a.N > 1 ? a.N : 1);
   const GnCount cnt = {n_loc, 1.0 / n_loc, n_all, 1.0 / n_all};
   const bool need_stale = !(a.nseg > 1 || (a.N == 1 && a.stat_mode != DF_GN_STALE));
+  if (need_stale && !a.stale) return DF_EINVAL;
   const int stale_n = need_stale ? a.N * a.B * a.G * 2 : 0;
   // small tensors: the whole GroupNorm in one launch, one workgroup per (group, batch item)
   {

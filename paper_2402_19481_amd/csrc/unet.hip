@@ -443,7 +443,7 @@ struct Exec {
     a.x = x; a.y = y; a.gamma = gamma; a.beta = beta;
     norm_segments(a, level_rows, W, C, in_dtype);
     a.eps = eps; a.silu = silu;
-    a.stat_mode = gn_mode;
+    a.stat_mode = full() ? DF_GN_SUMS : gn_mode;         // (a synchronous step has no cached sums: the statistics of the whole image)
     a.y_packed = y_packed;
     a.scr = scr; a.meet = meet;
     if (cat) { a.x = cat->a; a.x2 = cat->b; a.x2_from = cat->ca; a.cat_out = cat->bf; }

@@ -463,6 +463,22 @@ def test_small_unet_groupnorm_modes(stat_mode):
     net.close()
 
 
+@pytest.mark.parametrize("H,W,N,axis", [(8, 16, 2, df.SPLIT_COLS), (16, 8, 1, df.SPLIT_ROWS), (16, 8, 2, df.SPLIT_ROWS)])
+def test_synchronous_steps_have_no_statistic_mode(H, W, N, axis):
+    """A FULL step uses the statistics of the whole image in every mode, also where the image is one segment (vertical strips, one patch)."""
+    cfg = ut.UNetCfg(H=H, W=W, N=N, **ut.SMALL)
+    t = configs.unet_inputs(cfg, seed=19, stale_std=0.5)
+    net = df.PatchUNet(cfg, _upload(configs.unet_weights(cfg, seed=19, threads=8)), B=1, device=DEV, split_axis=axis)
+    want = None
+    for mode in (df.GN_SUMS, df.GN_EQ2, df.GN_SEPARATE, df.GN_STALE):
+        net.set_gn_mode(mode)
+        net.stale.zero_()
+        got = net.step(dev(t["x_prev"]), dev(t["emb"]), dev(t["text"], True), mode=df.MODE_FULL), net.stale.clone()
+        want = want or got
+        assert torch.isfinite(got[0]).all() and torch.equal(got[0], want[0]) and torch.equal(got[1], want[1]), mode
+    net.close()
+
+
 def test_small_unet_sampling_loop_with_warmup():
     """PatchUNet.sample_patch: two synchronous warm-up steps, then displaced steps on one patch, against the same loop
     written with oracle calls (Section 4: warm-up steps precede the displaced ones)."""
