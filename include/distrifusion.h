@@ -97,8 +97,8 @@ int df_groupnorm_stale(const void* x_fresh, void* y, const float* stale_stats, f
                        const float* gamma, const float* beta, int B, int R, int W, int C, int G,
                        int patch_idx, int N, float eps, int stat_mode, int fuse_silu, int dtype, void* stream);
 
-/* df_groupnorm_stale whose workgroups wait for nobody: where they would hand each other sums inside a launch, each adds up everything itself.
- * The same result, bit for bit, and slower: what a launch falls back to when a workgroup does not appear, for tests. */
+/* Diagnosis: df_groupnorm_stale whose workgroups wait for nobody.  Where they would hand each other sums inside a launch, each adds up everything
+ * itself: the same result, bit for bit, and slower - what a launch comes to, in part, when workgroups do not appear in time. */
 int df_groupnorm_stale_alone(const void* x_fresh, void* y, const float* stale_stats, float* fresh_stats_out,
                              const float* gamma, const float* beta, int B, int R, int W, int C, int G, int patch_idx, int N,
                              float eps, int stat_mode, int fuse_silu, int dtype, void* stream);
@@ -312,6 +312,8 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
  * displaced ones) need no entry point of their own: the caller runs DF_MODE_FULL for them.
  */
 int df_unet_set_gn_mode(df_unet* u, int stat_mode);
+/* Diagnosis: on = 1, the GroupNorms of the plan's further steps as df_groupnorm_stale_alone (the same results, slower). */
+int df_unet_set_gn_alone(df_unet* u, int on);
 
 /*
  * df_patch_unet_step records the launches of a step into a HIP graph the second time it sees the same call (mode,

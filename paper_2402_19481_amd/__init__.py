@@ -103,6 +103,7 @@ def lib():
     L.df_unet_profile_enable.argtypes = [vp, i]
     L.df_unet_set_graph.argtypes = [vp, i]
     L.df_unet_set_gn_mode.argtypes = [vp, i]
+    L.df_unet_set_gn_alone.argtypes = [vp, i]
     L.df_unet_profile_reset.argtypes = [vp]
     L.df_unet_profile_num_classes.argtypes = []
     L.df_unet_profile_class_name.argtypes = [i]
@@ -114,7 +115,7 @@ def lib():
     L.df_unet_profile_kernel.argtypes = [vp, i, ctypes.c_char_p, i, ctypes.POINTER(i), dp, dp, dp, ctypes.POINTER(ll)]
     L.df_unet_profile_kernel.restype = i
     for name in ("df_copy_bytes", "df_buffer_refresh", "df_groupnorm_stale", "df_conv3x3_halo", "df_attn_displaced",
-                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv", "df_text_kv",
+                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_unet_set_gn_alone", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv", "df_text_kv",
                  "df_cross_attn_packed", "df_packed_bytes", "df_pack_rows", "df_pack_linear_weight", "df_linear_packed", "df_linear_packed_scratch", "df_unet_num_weights", "df_unet_weight_info", "df_unet_create",
                  "df_unet_stale_lookup", "df_unet_num_stale", "df_unet_stale_name", "df_patch_unet_step",
                  "df_unet_profile_enable", "df_unet_set_graph", "df_unet_profile_reset", "df_unet_profile_num_classes",
@@ -188,7 +189,7 @@ def groupnorm_stale(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5
 
 def groupnorm_stale_alone(x_fresh, stale_stats, gamma, beta, G, patch_idx, N, eps=1e-5, stat_mode=GN_SUMS, fuse_silu=False,
                           fresh_stats_out=None):
-    """groupnorm_stale whose workgroups wait for nobody: the same result, slower (for tests)."""
+    """groupnorm_stale whose workgroups wait for nobody: the same result, slower (a diagnosis)."""
     B, R, W, C = x_fresh.shape
     y = torch.empty_like(x_fresh)
     fs = fresh_stats_out
@@ -425,6 +426,10 @@ class PatchUNet:
     def set_gn_mode(self, stat_mode):
         """GroupNorm statistic mode of the displaced steps (GN_SUMS default, GN_EQ2, GN_SEPARATE, GN_STALE)."""
         _check(lib().df_unet_set_gn_mode(self.handle, int(stat_mode)))
+
+    def set_gn_alone(self, on):
+        """Diagnosis: GroupNorms whose workgroups wait for nobody (groupnorm_stale_alone) in further steps."""
+        _check(lib().df_unet_set_gn_alone(self.handle, int(on)))
 
     def _loop_buffer(self, key, shape):
         """Persistent float buffers of the sampling loop: the step's graph cache is keyed on its pointers, so the

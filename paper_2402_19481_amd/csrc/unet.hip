@@ -264,7 +264,7 @@ struct PackedW {
 // out of the critical path (the counterpart of the paper's CUDAGraph use, Section 5.1).  A graph is tied to the
 // mode, patch, refresh flag, stream and every pointer of the call that recorded it.
 struct GraphEntry {
-  int mode, patch, refresh, gn_mode;
+  int mode, patch, refresh, gn_mode, gn_looks;
   const void *x, *emb, *text, *eps;
   void* stale;
   hipStream_t stream;
@@ -278,6 +278,7 @@ struct df_unet {
   Prof prof;
   bool use_graph = true;
   int gn_mode = DF_GN_SUMS;      // statistic mode of the DISPLACED steps (df_unet_set_gn_mode)
+  int gn_looks = 0;              // -1: its workgroups wait for nobody (df_unet_set_gn_alone)
   std::vector<GraphEntry> graphs;
   std::map<std::string, PackedW> packed;
   std::vector<BlockDesc> blocks;
@@ -323,6 +324,7 @@ struct Exec {
   Prof* prof = nullptr;
   const std::map<std::string, PackedW>* packed = nullptr;
   int gn_mode = DF_GN_SUMS;      // GroupNorm statistic mode of a DISPLACED step
+  int gn_looks = 0;
   const Scratch* scr = nullptr;  // the plan's scratch region
   void* meet = nullptr;          // where workgroups of its GroupNorms hand each other their sums
   const bf16_t* kv_packed[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -445,7 +447,7 @@ struct Exec {
     a.eps = eps; a.silu = silu;
     a.stat_mode = full() ? DF_GN_SUMS : gn_mode;         // (a synchronous step has no cached sums: the statistics of the whole image)
     a.y_packed = y_packed;
-    a.scr = scr; a.meet = meet;
+    a.scr = scr; a.meet = meet; a.looks = gn_looks;
     if (cat) { a.x = cat->a; a.x2 = cat->b; a.x2_from = cat->ca; a.cat_out = cat->bf; }
     if (halo_entry && (full() || refresh)) {
       // the consumer convolution's boundary-row (boundary-column) state is refreshed by this kernel's store loop
@@ -1236,6 +1238,7 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
   }
   e.packed = &u->packed;
   e.gn_mode = u->gn_mode;
+  e.gn_looks = u->gn_looks;
   e.emb_w_all = (const bf16_t*)(u->ws + u->emb_w_off);
   e.emb_b_all = (const float*)(u->ws + u->emb_b_off);
   e.stale_base = (char*)stale;
@@ -1248,16 +1251,16 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
     return e.step((const float*)x, (const float*)emb, (const bf16_t*)text, (float*)eps_out);
   GraphEntry* ge = nullptr;
   for (GraphEntry& g : u->graphs)
-    if (g.mode == mode && g.patch == e.patch && g.refresh == e.refresh && g.gn_mode == e.gn_mode && g.x == x && g.emb == emb && g.text == text &&
-        g.eps == eps_out && g.stale == stale && g.stream == st) { ge = &g; break; }
+    if (g.mode == mode && g.patch == e.patch && g.refresh == e.refresh && g.gn_mode == e.gn_mode && g.gn_looks == e.gn_looks && g.x == x && g.emb == emb &&
+        g.text == text && g.eps == eps_out && g.stale == stale && g.stream == st) { ge = &g; break; }
   if (!ge) {
     if (u->graphs.size() >= 64) {   // bound the cache: drop the oldest entry
       if (u->graphs.front().exec) (void)hipGraphExecDestroy(u->graphs.front().exec);
       u->graphs.erase(u->graphs.begin());
     }
     GraphEntry g;
-    g.mode = mode; g.patch = e.patch; g.refresh = e.refresh; g.gn_mode = e.gn_mode; g.x = x; g.emb = emb; g.text = text; g.eps = eps_out;
-    g.stale = stale; g.stream = st;
+    g.mode = mode; g.patch = e.patch; g.refresh = e.refresh; g.gn_mode = e.gn_mode; g.gn_looks = e.gn_looks;
+    g.x = x; g.emb = emb; g.text = text; g.eps = eps_out; g.stale = stale; g.stream = st;
     u->graphs.push_back(g);
     ge = &u->graphs.back();
   }
@@ -1289,6 +1292,12 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
 int df_unet_set_gn_mode(df_unet* u, int stat_mode) {
   if (!u || stat_mode < DF_GN_SUMS || stat_mode > DF_GN_STALE) return DF_EINVAL;
   u->gn_mode = stat_mode;
+  return DF_OK;
+}
+
+int df_unet_set_gn_alone(df_unet* u, int on) {
+  if (!u) return DF_EINVAL;
+  u->gn_looks = on ? -1 : 0;
   return DF_OK;
 }
 
