@@ -168,7 +168,7 @@ def _native():
             from . import _binding
         except ImportError as e:
             raise DfError(f"{_HERE}/_binding.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` first") from e
-        _binding.setup(DfError, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
+        _binding.setup(DfError, torch.OutOfMemoryError, torch.AcceleratorError, *(ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
             "df_strerror", "df_groupnorm_stale", "df_conv3x3_halo_axis", "df_attn_displaced", "df_attn_displaced_axis", "df_linear",
             "df_buffer_refresh")))
         _ops = _binding

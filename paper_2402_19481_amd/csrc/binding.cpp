@@ -14,7 +14,7 @@
 namespace {
 
 enum { kF32 = 0, kBF16 = 1 };
-PyObject* g_error = nullptr;                           // DfError
+PyObject *g_error = nullptr, *g_torch_memory = nullptr, *g_torch_device = nullptr;   // DfError, torch.OutOfMemoryError, torch.AcceleratorError
 const char* (*g_strerror)(int) = nullptr;
 
 struct Failed {};                                      // a Python exception is set
@@ -81,6 +81,10 @@ PyObject* guarded(F f) {
     return nullptr;
   } catch (python_error& e) {
     e.restore();
+  } catch (const c10::OutOfMemoryError& e) {           // (as torch raises them: its own translation is not exported)
+    PyErr_SetString(g_torch_memory, e.what_without_backtrace());
+  } catch (const c10::AcceleratorError& e) {
+    PyErr_SetString(g_torch_device, e.what_without_backtrace());
   } catch (const c10::Error& e) {
     PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
   } catch (const std::exception& e) {
@@ -111,16 +115,19 @@ AttnAxisFn g_attn_axis;
 LinearFn g_linear;
 RefreshFn g_refresh;
 
-// setup(DfError, addresses of df_strerror, df_groupnorm_stale, df_conv3x3_halo_axis, df_attn_displaced, df_attn_displaced_axis, df_linear,
-// df_buffer_refresh)
+// setup(DfError, torch.OutOfMemoryError, torch.AcceleratorError, addresses of df_strerror, df_groupnorm_stale, df_conv3x3_halo_axis,
+// df_attn_displaced, df_attn_displaced_axis, df_linear, df_buffer_refresh)
 PyObject* setup(PyObject*, PyObject* const* a, Py_ssize_t na) {
-  DF_ARGS(8)
+  DF_ARGS(10)
   return guarded([&]() -> PyObject* {
     void* f[7];
-    for (int i = 0; i < 7; ++i) f[i] = (void*)integer(a[i + 1]);
-    Py_INCREF(a[0]);
-    Py_XDECREF(g_error);
-    g_error = a[0];
+    for (int i = 0; i < 7; ++i) f[i] = (void*)integer(a[i + 3]);
+    PyObject** const kinds[] = {&g_error, &g_torch_memory, &g_torch_device};
+    for (int i = 0; i < 3; ++i) {
+      Py_INCREF(a[i]);
+      Py_XDECREF(*kinds[i]);
+      *kinds[i] = a[i];
+    }
     g_strerror = (const char* (*)(int))f[0];
     g_gn = (GnFn)f[1]; g_conv = (ConvFn)f[2]; g_attn = (AttnFn)f[3]; g_attn_axis = (AttnAxisFn)f[4]; g_linear = (LinearFn)f[5];
     g_refresh = (RefreshFn)f[6];
