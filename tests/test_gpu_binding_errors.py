@@ -20,4 +20,4 @@ def test_result_that_does_not_fit():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     y, fs = df.groupnorm_stale(x, None, g, g, 32, 0, 1)
-    assert not y.any() and not fs.any()
+    assert (y == 1).all() and not fs.any()                     # the shift of a tensor of zeros
