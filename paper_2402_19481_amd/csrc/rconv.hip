@@ -99,11 +99,12 @@ __global__ __launch_bounds__(512, 2) void rconv_kernel(const bf16_t* Wt, const b
   const int slabs_all = Cin / 64;
   const int s_lo = (int)((long long)slabs_all * blockIdx.y / nsplit), s_hi = (int)((long long)slabs_all * (blockIdx.y + 1) / nsplit);
 
-  // First channel of the slab that is being computed and of the one behind it.  The XCDs begin with different slabs: all
-  // of them read the same weights, and in step they ask the same channels of the last-level cache.  64 x 1280 -> 1280 13.9 -> 13.7 us, 494
-  // x 2560 -> 1280 44.8 -> 42.9, 1024 x 1280 -> 1280 40.8 -> 40.2, 4096 x 960 -> 320 31.1 -> 30.5; 300 x 2560 -> 1280 loses, 31.8 -> 33.7;
-  // 32 shapes 0.5 % on average.
-  const int slabs = s_hi - s_lo, rot = (int)((blockIdx.x & 7) * (unsigned int)slabs >> 3);
+  // First channel of the slab that is being computed and of the one behind it.  The XCDs begin with different slabs, where the channels are not
+  // split over workgroups or a tile has 64 pixels: all of them read the same weights, and in step they ask the same channels of the last-level
+  // cache.  640 -> 640 of 32 x 32 19.2 -> 16.0 us, 960 -> 320 of 26 x 76 25.7 -> 21.1, 640 -> 1280 of 26 x 19 19.1 -> 17.5; 100 layers of 64 to 7904
+  // pixels 0.974 on average, 1.019 at most.  Parts of the channels begin at different slabs already: with larger tiles the start costs up to 9 %
+  // (300 x 2560 -> 1280 in four parts 33.5 -> 35.7 us, 1024 x 1920 -> 640 in three 30.4 -> 31.9; 76 layers 1.011).
+  const int slabs = s_hi - s_lo, rot = nsplit == 1 || PM * TM == 2 ? (int)((blockIdx.x & 7) * (unsigned int)slabs >> 3) : 0;
   auto behind = [&](int c) { return c + 64 < s_hi * 64 ? c + 64 : s_lo * 64; };
   int ch = (s_lo + rot) * 64, chn = behind(ch);
   // weight loads: instruction j of a tap covers output channels wrow(j) .. +7 of the tile, lane / 8 one of them
