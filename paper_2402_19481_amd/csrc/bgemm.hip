@@ -214,12 +214,13 @@ __global__ __launch_bounds__(64 * WT * WF * KG, (WT * WF * KG * OCC + 3) / 4) vo
     src[q] = (row < BT ? (const char*)Xp + (size_t)mt * KF * 1024 : (const char*)Wp + (size_t)wrow(row - BT) * KF * 1024) +
              ((size_t)kt0 * BKF + kk) * 1024;
   }
-  // Plain layers of whole 1024s of tokens: the XCDs walk K from different stages on, an eighth apart.  Their shares of the tokens then begin
-  // powers of two apart, and in step the eight ask the same channels of the last-level cache: 2048 x 1280 x 5120 46.7 -> 40.5 us,
-  // 4096 x 640 x 2560 27.2 -> 24.6, 1024 x 1280 x 1280 11.2 -> 11.0; 1024 x 1024 full step 12.96 -> 12.78 ms, 2048 x 2048 strips 15.54 ->
-  // 15.36.  Other counts: 1800 x 1280 x 5120 38.7 -> 40.0, 7200 x 1280 x 1280 40.7 -> 41.3, on average of forty 1.000; the layers that
-  // fold a LayerNorm 0 - 3 % slower.  Within an XCD the workgroups stay in step, so that what one has fetched the others find in its L2 (an
-  // offset per tile: steps 2 - 5 % slower).
+  // Plain layers of whole 1024s of tokens, up to 31 of them missing: the XCDs walk K from different stages on, an eighth apart.  Their shares of
+  // the tokens begin whole tiles apart there, and in step the eight ask the same channels of the last-level cache.  In step / apart, weights from
+  // HBM: 1280 x 5120 1000 tokens 28.5 / 24.1 us, 1024 28.6 / 24.1, 2048 42.2 / 35.8, 3072 49.2 / 44.5, 4096 58.9 / 56.3, 5120 82.9 / 78.4; 640 x 2560
+  // 3072 20.4 / 19.2, 4096 23.8 / 21.8, 5120 25.9 / 23.6; with a K of 640 or 1280 the same within 1 % (8192 x 640 x 640 3 % faster); 1024 x 1024 full
+  // step 12.96 / 12.78 ms, 2048 x 2048 strips 15.54 / 15.36.  Multiples of 256 alone would gain with 5120 too (1536 35.8 / 32.8, 2304 44.1 / 39.0)
+  // and keep their order; other counts lose (1800 35.6 / 36.1, 4000 55.3 / 56.1, 7200 91.7 / 93.4), the layers that fold a LayerNorm 0 - 3 %.
+  // Within an XCD the workgroups stay in step, so that what one has fetched the others find in its L2 (an offset per tile: steps 2 - 5 % slower).
   const int rot = EPI == EPI_PLAIN && !LN && MT % 32 == 0 ? (int)((blockIdx.x & 7) * (unsigned int)KT >> 3) : 0;
   // loads of a stage: all (STEP < 0), or part STEP of KS
   auto issue = [&](int kt, int slot, auto stepc) {
