@@ -1173,6 +1173,7 @@ int launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.d != 64) return DF_ESHAPE;
   const long long lds[] = {a.ldq, a.ldkf, a.ldvf, a.ldks, a.ldvs, a.ldo, a.bsq, a.bskf, a.bsvf, a.bsks, a.bsvs, a.bso};
   for (long long v : lds) if (v % 8) return DF_EINVAL;
+  if (a.heads >= (1 << 24) || a.ldq >= (1LL << 31)) return DF_ESHAPE;   // (as the kernels' leading arguments hold them, beside at most 16 parts of the keys)
   const void* ptrs[] = {a.q, a.k_fresh, a.v_fresh, a.k_stale, a.v_stale, a.out};
   for (const void* q : ptrs) if ((uintptr_t)q % 16) return DF_EINVAL;
   // Few queries (the patch at the deepest levels): one workgroup per 32-query block and head whose eight waves split the

@@ -13,12 +13,6 @@ template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
 }
-__device__ __forceinline__ void block_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 enum { EPI_PLAIN = 0, EPI_GEGLU = 1, EPI_QKV = 2, EPI_XA = 3, EPI_PART = 4 };
 
 // Geometry of a tile's epilogue: the accumulators go through LDS in passes of R token fragment rows of the tile (row

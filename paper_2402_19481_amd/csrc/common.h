@@ -125,6 +125,13 @@ __host__ __device__ inline unsigned int quotient_u32(unsigned int x, unsigned in
   return q + (x - q * d >= d ? 1u : 0u);
 }
 
+// A barrier that no memory access is moved across, without the wait for all of them that __syncthreads brings
+__device__ __forceinline__ void block_sync() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

@@ -16,12 +16,6 @@ __device__ __forceinline__ void wait_vm_lds(int n) {   // the same with a count 
   if (n == MOST) wait_vm_lds<MOST>();
   else if constexpr (MOST > 0) wait_vm_lds<MOST - 1>(n);
 }
-__device__ __forceinline__ void block_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 struct RcExtra {
   const bf16_t* zeros;
   float* partials;

@@ -10,11 +10,6 @@ template <int VM>
 __device__ __forceinline__ void wait_vm() {   // s_waitcnt vmcnt(VM)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
-__device__ __forceinline__ void block_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
 
 struct TextKvParams {
   const bf16_t* text;

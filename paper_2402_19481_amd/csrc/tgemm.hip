@@ -11,12 +11,6 @@ template <int VM>
 __device__ __forceinline__ void wait_vm_lds() {   // s_waitcnt vmcnt(VM) lgkmcnt(0)
   __builtin_amdgcn_s_waitcnt((VM & 0xF) | ((VM >> 4) << 14) | (0x7 << 4));
 }
-__device__ __forceinline__ void block_sync() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // Epilogue of four consecutive columns of one output row: what is added, requested at once, and the rest
 struct Added { f32x4 bias, chan, res; };
 template <bool kConv>

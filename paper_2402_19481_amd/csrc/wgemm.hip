@@ -69,10 +69,6 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(const bf16x8* Xp, co
   constexpr int GP = TN >= 2 ? TN / 2 : 1;   // geglu: the tile's first GP fragments are value rows, the last GP their gates
   constexpr int JO = GEGLU ? GP : TN;        // output fragments per row of the tile
 
-  // Every kernel argument the prologue needs is requested here, in one batch: left to the compiler, the scalar loads
-  // of arguments first used under a condition (norm vectors, bias, residual, operand pointers) are issued where that
-  // code starts, and the prologue of these few-microsecond kernels became a chain of four or five dependent round
-  // trips to the scalar cache.
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // scalar: the k-walk and tile addresses stay off the vector ALU
   const int tok = lane & 31, g = lane >> 5;
@@ -139,6 +135,9 @@ __global__ __launch_bounds__(64 * KSPLIT) void wgemm_kernel(const bf16x8* Xp, co
   float ln_sum[TM], ln_sq[TM];
 #pragma unroll
   for (int i = 0; i < TM; ++i) { ln_sum[i] = 0.f; ln_sq[i] = 0.f; }
+  // The arguments of the epilogue's requests come here, in one batch behind the first operands' requests: left to the compiler, the scalar
+  // loads of arguments first used under a condition (norm vectors, bias, residual) are issued where that code starts, a chain of round trips to
+  // the scalar cache in kernels of a few microseconds.
   asm volatile("" ::"s"(p.bias), "s"(p.ln_s), "s"(p.ln_t), "s"(p.residual), "s"(p.ldr), "s"(p.res_frag));
   constexpr bool ln = LN;
 
