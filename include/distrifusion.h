@@ -312,8 +312,9 @@ int df_patch_unet_step(df_unet* u, const void* x, const void* emb, const void* t
  * displaced ones) need no entry point of their own: the caller runs DF_MODE_FULL for them.
  */
 int df_unet_set_gn_mode(df_unet* u, int stat_mode);
-/* Diagnosis: on = 1, the GroupNorms of the plan's further steps as df_groupnorm_stale_alone (the same results, slower). */
-int df_unet_set_gn_alone(df_unet* u, int on);
+/* Diagnosis: how often the workgroups of a GroupNorm look for each other's sums, in the plan's further steps, before they add up what is missing
+ * themselves: 0 not at all (as df_groupnorm_stale_alone), negative: the default; at most 1024.  The same results. */
+int df_unet_set_gn_looks(df_unet* u, int looks);
 
 /*
  * df_patch_unet_step records the launches of a step into a HIP graph the second time it sees the same call (mode,

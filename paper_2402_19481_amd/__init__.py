@@ -103,7 +103,7 @@ def lib():
     L.df_unet_profile_enable.argtypes = [vp, i]
     L.df_unet_set_graph.argtypes = [vp, i]
     L.df_unet_set_gn_mode.argtypes = [vp, i]
-    L.df_unet_set_gn_alone.argtypes = [vp, i]
+    L.df_unet_set_gn_looks.argtypes = [vp, i]
     L.df_unet_profile_reset.argtypes = [vp]
     L.df_unet_profile_num_classes.argtypes = []
     L.df_unet_profile_class_name.argtypes = [i]
@@ -115,7 +115,7 @@ def lib():
     L.df_unet_profile_kernel.argtypes = [vp, i, ctypes.c_char_p, i, ctypes.POINTER(i), dp, dp, dp, ctypes.POINTER(ll)]
     L.df_unet_profile_kernel.restype = i
     for name in ("df_copy_bytes", "df_buffer_refresh", "df_groupnorm_stale", "df_conv3x3_halo", "df_attn_displaced",
-                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_unet_set_gn_alone", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv", "df_text_kv",
+                 "df_euler_update", "df_linear", "df_unet_set_gn_mode", "df_unet_set_gn_looks", "df_scale_input", "df_mfma_probe", "df_attn_stale_vt", "df_packed_text_kv_bytes", "df_pack_text_kv", "df_text_kv",
                  "df_cross_attn_packed", "df_packed_bytes", "df_pack_rows", "df_pack_linear_weight", "df_linear_packed", "df_linear_packed_scratch", "df_unet_num_weights", "df_unet_weight_info", "df_unet_create",
                  "df_unet_stale_lookup", "df_unet_num_stale", "df_unet_stale_name", "df_patch_unet_step",
                  "df_unet_profile_enable", "df_unet_set_graph", "df_unet_profile_reset", "df_unet_profile_num_classes",
@@ -427,9 +427,10 @@ class PatchUNet:
         """GroupNorm statistic mode of the displaced steps (GN_SUMS default, GN_EQ2, GN_SEPARATE, GN_STALE)."""
         _check(lib().df_unet_set_gn_mode(self.handle, int(stat_mode)))
 
-    def set_gn_alone(self, on):
-        """Diagnosis: GroupNorms whose workgroups wait for nobody (groupnorm_stale_alone) in further steps."""
-        _check(lib().df_unet_set_gn_alone(self.handle, int(on)))
+    def set_gn_looks(self, looks):
+        """Diagnosis: how often workgroups of a GroupNorm look for each other's sums before they add up what is missing themselves, in further
+        steps (0: not at all; negative: the default)."""
+        _check(lib().df_unet_set_gn_looks(self.handle, int(looks)))
 
     def _loop_buffer(self, key, shape):
         """Persistent float buffers of the sampling loop: the step's graph cache is keyed on its pointers, so the

@@ -1182,10 +1182,6 @@ __global__ __launch_bounds__(256) void gn_clear_words(unsigned long long* words,
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i < n) __hip_atomic_store(words + i, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-int gn_meet_wait(int looks) {
-  const char* e = tune_env("DF_GN_WAIT");
-  return looks < 0 ? 0 : e ? atoi(e) : kGnMeetWait;
-}
 bool recording(hipStream_t st) {
   if (!st) return false;                                 // (the default stream cannot be recorded)
   hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
@@ -1274,7 +1270,7 @@ int launch_groupnorm(const GnArgs& a, hipStream_t st) {
       unsigned int id = 0;
       if (const int rc = gn_words(a, form.P, st, &words, &id)) return rc;
       const GnMeet mt = {words, id, reciprocal_u32(form.tp), reciprocal_u32(a.C / a.G), ilog2(form.P),
-                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, gn_meet_wait(a.looks)};
+                         ilog2(form.P / a.nseg), form.tp, form.ppb, form.pix_part, a.looks < 0 ? 0 : a.looks ? a.looks : kGnMeetWait};
 #define DF_GN_MEET(TI, TO, NVV, PR)                                                                                         \
   hipLaunchKernelGGL((gn_meet_kernel<TI, TO, NVV, PR>), dim3(8 * form.P * a.B), dim3(1024), 0, st, (const TI*)a.x, (TO*)a.y, stale, \
                      a.sums_out, a.gamma, a.beta, (int)pix_seg, a.C, a.G, a.nseg, a.B, a.patch_idx, a.N, a.eps, a.stat_mode,      \

@@ -62,7 +62,7 @@ struct GnArgs {
   void* cat_out;
   // groupnorm_meet_bytes() in which workgroups hand each other sums, zero once and not used by launches that overlap; nullptr: the library's
   void* meet;
-  int looks;            // -1: workgroups add up everything themselves (the same result, slower: a diagnosis)
+  int looks;            // times that workgroups look for each other's sums: 0 the default, -1 not at all (the same result, slower: a diagnosis)
 };
 size_t groupnorm_meet_bytes();
 bool groupnorm_takes_pair(const GnArgs& a);

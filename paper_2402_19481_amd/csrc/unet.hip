@@ -278,7 +278,7 @@ struct df_unet {
   Prof prof;
   bool use_graph = true;
   int gn_mode = DF_GN_SUMS;      // statistic mode of the DISPLACED steps (df_unet_set_gn_mode)
-  int gn_looks = 0;              // -1: its workgroups wait for nobody (df_unet_set_gn_alone)
+  int gn_looks = 0;              // GnArgs::looks (df_unet_set_gn_looks)
   std::vector<GraphEntry> graphs;
   std::map<std::string, PackedW> packed;
   std::vector<BlockDesc> blocks;
@@ -1295,9 +1295,9 @@ int df_unet_set_gn_mode(df_unet* u, int stat_mode) {
   return DF_OK;
 }
 
-int df_unet_set_gn_alone(df_unet* u, int on) {
-  if (!u) return DF_EINVAL;
-  u->gn_looks = on ? -1 : 0;
+int df_unet_set_gn_looks(df_unet* u, int looks) {
+  if (!u || looks > 1024) return DF_EINVAL;
+  u->gn_looks = looks < 0 ? 0 : looks == 0 ? -1 : looks;
   return DF_OK;
 }
 
