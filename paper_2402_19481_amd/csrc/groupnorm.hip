@@ -747,8 +747,8 @@ __global__ __launch_bounds__(1024) void gn_group_reg_kernel(const Tin* __restric
 //   - A word is of this launch and no other: gnmeet.h says how the number is chosen, also for replays of a recorded call and for calls that overlap.
 // Bound by two round trips to memory and the exchange (32 x 128 x 320 bf16, us from the first start: requests out 1.6, sums 2.4, all
 // there 3.3, moments 3.8, stored 4.4), by the rates of both beyond some 10 MB.  A launch after another, against two launches or (up to sixteen
-// pixels per lane) a workgroup per group: 1024 x 320 float 7.3 -> 5.0 us, 4096 x 320 bf16 12.1 -> 6.7, 494 x 1280 float 6.5 -> 5.2,
-// 1024 x 1280 bf16 10.8 -> 6.1, 4096 x 640 float 15.1 -> 8.8, 16384 x 960 bf16 27.1 -> 24.7.  One lane-ordered sum in LDS for the
+// pixels per lane) a workgroup per group: 1024 x 320 float 7.3 -> 5.0 us, 4096 x 320 bf16 12.1 -> 6.5, 494 x 1280 float 6.5 -> 5.1,
+// 1024 x 1280 bf16 10.8 -> 5.95, 4096 x 640 float 15.1 -> 8.4, 16384 x 960 bf16 27.1 -> 24.5.  One lane-ordered sum in LDS for the
 // eight words of a workgroup (sums through LDS lane by lane, moments with the cached sums behind the exchange) took 2.5 us more.
 constexpr int kGnMeetParts = 32, kGnMeetBatch = 8, kGnMeetGroups = 4, kGnMeetWait = 16;
 // 8-byte words of a (batch item, slab): a line with the counters of tickets and of arrivals, then 8 per workgroup; and of a launch with P workgroups per slab
