@@ -71,6 +71,9 @@ def test_groupnorm_sums_refreshed_in_place_by_nobody_who_waits(mode, B):
         y, fs = call(x, cache, *args, fresh_stats_out=cache[patch])
         assert torch.equal(_bits(y), _bits(y0)) and torch.equal(cache[patch], fs0)
         assert torch.equal(cache[[0, 1, 3]], dev(st)[[0, 1, 3]])
+    cache, y = dev(st), torch.empty_like(x)                    # and by the entry point that allocates nothing
+    df.groupnorm_stale_noalloc(x, cache, dev(gamma), dev(beta), 32, patch, N, y, cache[patch], 1e-5, mode, True)
+    assert torch.equal(_bits(y), _bits(y0)) and torch.equal(cache[patch], fs0)
 
 
 def test_groupnorm_replays_and_streams():
